@@ -469,13 +469,13 @@ __global__ __launch_bounds__(BS_THREADS) void bs_rank_unique_kernel(const KeyT* 
   bs_rank_unique_part<KeyT>(blockIdx.x, keys1, win, *n_kept, sorted, bits, ccnt);
 }
 
-// out = the marked positions of `sorted`, in order; their number to *n_out.  One workgroup per chunk
+// out = the marked positions of `sorted`, in order, and their number.  One workgroup per chunk
 // of BS_CHUNK positions: the keys before the chunk are the sum of the earlier chunks' counters.
 template <typename KeyT>
 __global__ __launch_bounds__(BS_THREADS) void bs_compact_kernel(const KeyT* __restrict__ sorted, const uint32_t* __restrict__ bits,
                                                                 const int32_t* __restrict__ ccnt,
                                                                 const int32_t* __restrict__ n_kept, KeyT* __restrict__ out,
-                                                                int32_t* __restrict__ n_out) {
+                                                                CountOut count) {
   static_assert(BS_CHUNK == 4 * BS_THREADS, "four positions per thread");
   __shared__ int red[2][BS_THREADS / 64];
   __shared__ int wsum[BS_CHUNK / 32];
@@ -505,7 +505,7 @@ __global__ __launch_bounds__(BS_THREADS) void bs_compact_kernel(const KeyT* __re
     before += red[0][w];
     all += red[1][w];
   }
-  if (b == 0 && t == 0) *n_out = all;
+  if (b == 0 && t == 0) count.publish(all);
   int rank = before + __popc(word & ((1u << (4 * sub)) - 1u));
   for (int w = 0; w < wi; ++w) rank += wsum[w];
 #pragma unroll
@@ -731,7 +731,7 @@ static_assert(BS_SMALL_BINS <= BS_SMALL_THREADS && BS_SMALL_BINS % 64 == 0, "one
 constexpr int BS_SMALL_MAX = 4096;  // >= BS_MIN_N - 1
 template <typename KeyT, typename Src, bool DEDUP>
 __global__ __launch_bounds__(BS_SMALL_THREADS) void bs_small_sort_kernel(Src src, int n, int shift, KeyT* __restrict__ out_k,
-                                                                        int32_t* __restrict__ out_v, int32_t* __restrict__ n_out) {
+                                                                        int32_t* __restrict__ out_v, CountOut count) {
   __shared__ KeyT sk0[BS_SMALL_MAX], sk1[BS_SMALL_MAX];
   __shared__ int16_t sv1[BS_SMALL_MAX];
   __shared__ int s_start[BS_SMALL_BINS + 1], s_cur[BS_SMALL_BINS];
@@ -835,35 +835,36 @@ __global__ __launch_bounds__(BS_SMALL_THREADS) void bs_small_sort_kernel(Src src
     const int i = tid * per + u;
     if (i < n && (i == 0 || sk0[i] != sk0[i - 1])) out_k[base++] = sk0[i];
   }
-  if (tid == 0) *n_out = total;
+  if (tid == 0) count.publish(total);
 }
 
 template <typename KeyT, typename Src, bool DEDUP>
-static void launch_small_sort(const Src& src, int64_t n, int used_bits, void* out_k, int32_t* out_v, int32_t* n_out, hipStream_t s) {
+static void launch_small_sort(const Src& src, int64_t n, int used_bits, void* out_k, int32_t* out_v, const CountOut& count,
+                              hipStream_t s) {
   static_assert(BS_SMALL_MAX >= BS_MIN_N - 1, "the small path covers every size below the partitioning sort's");
   const int shift = std::max(0, used_bits - BS_SMALL_BIN_BITS);  // bins = the top used key bits
   hipLaunchKernelGGL((bs_small_sort_kernel<KeyT, Src, DEDUP>), dim3(1), dim3(BS_SMALL_THREADS), 0, s, src, static_cast<int>(n), shift,
-                     static_cast<KeyT*>(out_k), out_v, n_out);
+                     static_cast<KeyT*>(out_k), out_v, count);
 }
 
 int small_pack_sort(int key_bits, const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status, void* keys_out,
                     int32_t* perm_out, hipStream_t s) {
   if (key_bits == 32)
-    launch_small_sort<uint32_t, SrcPack<uint32_t>, false>(SrcPack<uint32_t>{coords, pp, status}, n, used_bits, keys_out, perm_out, nullptr, s);
+    launch_small_sort<uint32_t, SrcPack<uint32_t>, false>(SrcPack<uint32_t>{coords, pp, status}, n, used_bits, keys_out, perm_out, CountOut{}, s);
   else
-    launch_small_sort<uint64_t, SrcPack<uint64_t>, false>(SrcPack<uint64_t>{coords, pp, status}, n, used_bits, keys_out, perm_out, nullptr, s);
+    launch_small_sort<uint64_t, SrcPack<uint64_t>, false>(SrcPack<uint64_t>{coords, pp, status}, n, used_bits, keys_out, perm_out, CountOut{}, s);
   if (hipGetLastError() != hipSuccess) return set_error(SPC_ERR_HIP, "sort launch failed");
   return SPC_OK;
 }
 
-int small_mask_unique(int key_bits, const void* keys_in, int64_t n, uint64_t mask, int used_bits, void* keys_out, int32_t* n_out,
-                      hipStream_t s) {
+int small_mask_unique(int key_bits, const void* keys_in, int64_t n, uint64_t mask, int used_bits, void* keys_out,
+                      const CountOut& count, hipStream_t s) {
   if (key_bits == 32)
     launch_small_sort<uint32_t, SrcMask<uint32_t>, true>(SrcMask<uint32_t>{static_cast<const uint32_t*>(keys_in), static_cast<uint32_t>(mask)}, n,
-                                                         used_bits, keys_out, nullptr, n_out, s);
+                                                         used_bits, keys_out, nullptr, count, s);
   else
     launch_small_sort<uint64_t, SrcMask<uint64_t>, true>(SrcMask<uint64_t>{static_cast<const uint64_t*>(keys_in), mask}, n, used_bits,
-                                                         keys_out, nullptr, n_out, s);
+                                                         keys_out, nullptr, count, s);
   if (hipGetLastError() != hipSuccess) return set_error(SPC_ERR_HIP, "downsample launch failed");
   return SPC_OK;
 }
@@ -997,8 +998,8 @@ int bucket_pack_sort(int key_bits, const int4* coords, int64_t n, const PackPara
 }
 
 template <typename KeyT>
-static int mask_unique_t(const void* keys_in, int64_t n, uint64_t mask, int used_bits, void* keys_out, int32_t* n_out, void* ws,
-                         hipStream_t s) {
+static int mask_unique_t(const void* keys_in, int64_t n, uint64_t mask, int used_bits, void* keys_out, const CountOut& count,
+                         void* ws, hipStream_t s) {
   const BucketPlan p = bucket_plan(n, used_bits);
   const Ws<KeyT> w = carve<KeyT>(ws, n);
   partition<KeyT, true>(SrcMask<KeyT>{static_cast<const KeyT*>(keys_in), static_cast<KeyT>(mask)}, n, p, w, s);
@@ -1015,15 +1016,15 @@ static int mask_unique_t(const void* keys_in, int64_t n, uint64_t mask, int used
     hipLaunchKernelGGL(bs_rank_unique_kernel<KeyT>, dim3(n_part), dim3(BS_THREADS), 0, s, w.keys1, w.win, w.n_kept, w.keys0, w.bits,
                        w.ccnt);
   hipLaunchKernelGGL(bs_compact_kernel<KeyT>, dim3(n_chunk), dim3(BS_THREADS), 0, s, w.keys0, w.bits, w.ccnt, w.n_kept,
-                     static_cast<KeyT*>(keys_out), n_out);
+                     static_cast<KeyT*>(keys_out), count);
   if (hipGetLastError() != hipSuccess) return set_error(SPC_ERR_HIP, "downsample launch failed");
   return SPC_OK;
 }
 
 int bucket_mask_unique(int key_bits, const void* keys_in, int64_t n, uint64_t mask, int used_bits, void* keys_out,
-                       int32_t* n_out, void* ws, hipStream_t s) {
-  return key_bits == 32 ? mask_unique_t<uint32_t>(keys_in, n, mask, used_bits, keys_out, n_out, ws, s)
-                        : mask_unique_t<uint64_t>(keys_in, n, mask, used_bits, keys_out, n_out, ws, s);
+                       const CountOut& count, void* ws, hipStream_t s) {
+  return key_bits == 32 ? mask_unique_t<uint32_t>(keys_in, n, mask, used_bits, keys_out, count, ws, s)
+                        : mask_unique_t<uint64_t>(keys_in, n, mask, used_bits, keys_out, count, ws, s);
 }
 
 }  // namespace spc

@@ -1079,6 +1079,8 @@ static int conv_typed(const ConvArgs& a0, bool allow_mfma) {
   return rc;
 }
 
+constexpr int32_t T_ALL_OS = 0x7fffffff;  // threshold above every norm: all offsets output-stationary
+
 // Common part of the two entry points: offsets with L1 norm < t run output-stationary, the others
 // weight-stationary.
 static int conv_entry(spc_kmap* m, const void* feats_in, int64_t ld_in, const void* weights, void* feats_out, int64_t ld_out,
@@ -1087,10 +1089,16 @@ static int conv_entry(spc_kmap* m, const void* feats_in, int64_t ld_in, const vo
   if (cin < 1 || cout < 1 || ld_in < cin || ld_out < cout) return set_error(SPC_ERR_ARG, "bad channel counts or row pitches");
   ConvArgs a{};
   a.m = m;
-  for (int k = 0; k < m->K3; ++k) {
-    const bool dense = offset_l1(m->desc.K, k) < t;
-    (dense ? a.os_mask : a.ws_mask).w[k >> 5] |= 1u << (k & 31);
-    (dense ? a.any_os : a.any_ws) = true;
+  if (t == 0 || t == T_ALL_OS) {  // a single dataflow: no offset to look at
+    KMask& all = t == 0 ? a.ws_mask : a.os_mask;
+    for (int w = 0; w * 32 < m->K3; ++w) all.w[w] = m->K3 - w * 32 >= 32 ? ~0u : (1u << (m->K3 - w * 32)) - 1u;
+    (t == 0 ? a.any_ws : a.any_os) = true;
+  } else {
+    for (int k = 0; k < m->K3; ++k) {
+      const bool dense = offset_l1(m->desc.K, k) < t;
+      (dense ? a.os_mask : a.ws_mask).w[k >> 5] |= 1u << (k & 31);
+      (dense ? a.any_os : a.any_ws) = true;
+    }
   }
   if (a.any_os && !(m->desc.layout & SPC_LAYOUT_OS)) return set_error(SPC_ERR_ARG, "map has no OS layout");
   if (a.any_ws && !(m->desc.layout & SPC_LAYOUT_WS)) return set_error(SPC_ERR_ARG, "map has no WS layout");
@@ -1123,6 +1131,7 @@ static int conv_entry(spc_kmap* m, const void* feats_in, int64_t ld_in, const vo
   a.rows_cap = ol->n_host < 0 ? m->out_cap : ol->n_host;
   a.rows_sel = (ol->n_host < 0 && m->n_out_hint >= 0) ? std::min(m->n_out_hint, a.rows_cap) : a.rows_cap;
   a.s = static_cast<hipStream_t>(stream);
+  const StreamWorkNote note{a.s};
   // a map of a pipelined network build: nobody has joined its build stream, this stream waits for the map itself
   // (once per consumer stream: stream order covers the later layers that share the map)
   if (m->wait_on_use && m->ready && m->stream != a.s && m->last_waiter != a.s) {
@@ -1148,7 +1157,7 @@ extern "C" int spc_conv_forward(spc_kmap* m, const void* feats_in, int64_t ld_in
                                 void* stream) {
   if (dataflow != SPC_DATAFLOW_OS && dataflow != SPC_DATAFLOW_WS) return spc::set_error(SPC_ERR_ARG, "bad dataflow");
   // single dataflows are the two ends of the threshold range
-  const int32_t t = dataflow == SPC_DATAFLOW_OS ? 0x7fffffff : 0;
+  const int32_t t = dataflow == SPC_DATAFLOW_OS ? spc::T_ALL_OS : 0;
   return spc::conv_entry(m, feats_in, ld_in, weights, feats_out, ld_out, cin, cout, dtype, t, flags, stream);
 }
 

@@ -847,7 +847,8 @@ static int ilog2(int v) {
 
 // Builds the map object for given input/output levels (references are taken).
 static int build_on_levels(Level* in, Level* out, const PackInfo& pi, const spc_layer_desc& l, hipStream_t s, spc_kmap** res,
-                           const int32_t* in_perm = nullptr, bool want_inverse = false) {
+                           const int32_t* in_perm = nullptr, bool want_inverse = false, bool want_event = false) {
+  const StreamWorkNote note{s};
   spc_kmap* m = new spc_kmap;
   m->in_perm = in_perm;
   m->pi = pi;
@@ -916,7 +917,7 @@ static int build_on_levels(Level* in, Level* out, const PackInfo& pi, const spc_
     m->tile_pairs = nullptr;
   }
   if (rc == SPC_OK && hipGetLastError() != hipSuccess) rc = set_error(SPC_ERR_HIP, "kernel-map launch failed");
-  if (rc == SPC_OK && (hipEventCreateWithFlags(&m->ready, hipEventDisableTiming) != hipSuccess ||
+  if (rc == SPC_OK && want_event && (hipEventCreateWithFlags(&m->ready, hipEventDisableTiming) != hipSuccess ||
                        hipEventRecord(m->ready, s) != hipSuccess))
     rc = set_error(SPC_ERR_HIP, "event record failed");
   if (rc != SPC_OK) {
@@ -935,15 +936,16 @@ static bool twin_can_share(const spc_layer_desc& strided, const spc_layer_desc& 
          strided.K * strided.K * strided.K <= 32;
 }
 
-// The transposed map from its strided twin (see transposed_from_parent_kernel): the matrix from the twin's inverse,
+// The transposed map from its strided twin, built on the same stream (see transposed_from_parent_kernel): the matrix from the twin's inverse,
 // the lists by taking the twin's with inputs and outputs swapped (for a fixed offset both index sequences ascend
 // together, so the order by output index is kept).  Returns SPC_ERR_UNSUPPORTED when the twin lacks what is needed.
 static int build_transposed_from_twin(spc_kmap* twin, Level* coarse, Level* fine, const PackInfo& pi, const spc_layer_desc& l,
-                                      hipStream_t s, spc_kmap** res) {
+                                      hipStream_t s, spc_kmap** res, bool want_event) {
   const bool with_os = (l.layout & SPC_LAYOUT_OS) != 0, with_ws = (l.layout & SPC_LAYOUT_WS) != 0;
   if (!twin_can_share(twin->desc, l) || (l.layout & ~SPC_LAYOUT_BOTH) || (with_os && !twin->inv_parent) ||
       (with_ws && (!(twin->desc.layout & SPC_LAYOUT_WS) || twin->hybrid_t || twin->sym)))
     return SPC_ERR_UNSUPPORTED;
+  const StreamWorkNote note{s};
   spc_kmap* m = new spc_kmap;
   m->pi = pi;
   m->desc = l;
@@ -968,9 +970,7 @@ static int build_transposed_from_twin(spc_kmap* twin, Level* coarse, Level* fine
   m->twin = twin;
   twin->refs++;
   int rc = SPC_OK;
-  if (s != twin->stream && twin->ready && hipStreamWaitEvent(s, twin->ready, 0) != hipSuccess)
-    rc = set_error(SPC_ERR_HIP, "hipStreamWaitEvent failed");
-  if (rc == SPC_OK && with_os) {
+  if (with_os) {
     m->os_map = static_cast<int32_t*>(pool_alloc(std::max<size_t>(size_t(m->n_blocks_cap) * 32 * m->K3 * 4, 256), s));
     m->block_masks = static_cast<uint32_t*>(pool_alloc(std::max<size_t>(size_t(m->n_blocks_cap) * 4, 256), s));
     if (!m->os_map || !m->block_masks) rc = SPC_ERR_NOMEM;
@@ -986,7 +986,7 @@ static int build_transposed_from_twin(spc_kmap* twin, Level* coarse, Level* fine
     m->ws_stride = twin->ws_stride;
   }
   if (rc == SPC_OK && hipGetLastError() != hipSuccess) rc = set_error(SPC_ERR_HIP, "kernel-map launch failed");
-  if (rc == SPC_OK && (hipEventCreateWithFlags(&m->ready, hipEventDisableTiming) != hipSuccess ||
+  if (rc == SPC_OK && want_event && (hipEventCreateWithFlags(&m->ready, hipEventDisableTiming) != hipSuccess ||
                        hipEventRecord(m->ready, s) != hipSuccess))
     rc = set_error(SPC_ERR_HIP, "event record failed");
   if (rc != SPC_OK) {
@@ -1007,6 +1007,36 @@ static Level* borrowed_level(const void* keys, int64_t n, int stride) {
   return lv;
 }
 
+// Waits for what a build has enqueued: its event where one was recorded, else everything on its stream so far (a stream
+// that is being captured by now cannot be waited for on its own: the device is drained).
+static int wait_stream(bool captured, hipEvent_t ready, hipStream_t s) {
+  if (captured || (!ready && stream_is_capturing(s))) SPC_HIP_CHECK(hipDeviceSynchronize());
+  else if (ready) SPC_HIP_CHECK(hipEventSynchronize(ready));
+  else SPC_HIP_CHECK(hipStreamSynchronize(s));
+  return SPC_OK;
+}
+
+// Spins until the level's count shows up in its pinned slot.  False when the stream has nothing left to run, or reports
+// an error, and the count is not there: the caller then waits and copies, which reports what happened.
+static bool poll_count(Level* lv, int* v) {
+  auto seen = [&]() {
+    const unsigned long long x = __atomic_load_n(lv->slot.host, __ATOMIC_ACQUIRE);
+    *v = static_cast<int>(static_cast<uint32_t>(x));
+    return static_cast<uint32_t>(x >> 32) == lv->slot.tag;
+  };
+  for (;;) {
+    for (int spin = 0; spin < 20000; ++spin) {  // some hundred microseconds
+      if (seen()) return true;
+      __builtin_ia32_pause();
+    }
+    if (stream_is_capturing(lv->stream)) return false;
+    const hipError_t e = hipStreamQuery(lv->stream);
+    if (e == hipErrorNotReady) continue;
+    (void)hipGetLastError();
+    return seen();
+  }
+}
+
 // Host copy of a level's voxel count in lv->n_fetched.  A level built under stream capture is
 // rewritten by every replay of the graph: its events cannot be waited for (they belong to the
 // capture), so the whole device is drained instead, and the value is never cached.
@@ -1015,9 +1045,12 @@ static int fetch_level_n(Level* lv) {
     lv->n_fetched = lv->n_host;
     return SPC_OK;
   }
-  if (lv->captured) SPC_HIP_CHECK(hipDeviceSynchronize());
-  else if (lv->ready) SPC_HIP_CHECK(hipEventSynchronize(lv->ready));
   int v = 0;
+  if (lv->slot.host && poll_count(lv, &v)) {
+    lv->n_host = lv->n_fetched = v;
+    return SPC_OK;
+  }
+  SPC_RETURN_IF(wait_stream(lv->captured, lv->ready, lv->stream));
   SPC_HIP_CHECK(hipMemcpy(&v, lv->n_dev, sizeof(int), hipMemcpyDeviceToHost));
   lv->n_fetched = v;
   if (!lv->captured) lv->n_host = v;
@@ -1025,11 +1058,7 @@ static int fetch_level_n(Level* lv) {
 }
 
 // Waits until the map's arrays are complete (see fetch_level_n for captured builds).
-static int wait_map(const spc_kmap* m) {
-  if (m->captured) SPC_HIP_CHECK(hipDeviceSynchronize());
-  else if (m->ready) SPC_HIP_CHECK(hipEventSynchronize(m->ready));
-  return SPC_OK;
-}
+static int wait_map(const spc_kmap* m) { return wait_stream(m->captured, m->ready, m->stream); }
 
 // Layout every distinct map of a network is built with: the union of what its layers ask for; a map
 // shared by layers that disagree about the half-map keeps the full lists.
@@ -1063,20 +1092,20 @@ static std::map<NetKey, int> net_layouts(const spc_layer_desc* layers, int n_lay
 // wanted maps leaves its inverse behind for it.  Everything else is searched.
 static int build_network_map(const NetKey& key, const spc_layer_desc& l, const std::map<NetKey, int>& want,
                              const std::map<NetKey, spc_kmap*>& maps, Level* fine, Level* coarse, const PackInfo& pi, hipStream_t s,
-                             spc_kmap** m) {
+                             spc_kmap** m, bool want_event) {
   const NetKey other(std::get<0>(key), std::get<1>(key), std::get<2>(key), l.transposed ? 0 : 1);
   if (l.transposed) {
     auto it = maps.find(other);
     if (it != maps.end() && it->second->stream == s) {
-      const int rc = build_transposed_from_twin(it->second, coarse, fine, pi, l, s, m);
+      const int rc = build_transposed_from_twin(it->second, coarse, fine, pi, l, s, m, want_event);
       if (rc != SPC_ERR_UNSUPPORTED) return rc;
     }
-    return build_on_levels(coarse, fine, pi, l, s, m);
+    return build_on_levels(coarse, fine, pi, l, s, m, nullptr, false, want_event);
   }
   spc_layer_desc t = l;
   t.transposed = 1;
   const bool inverse = want.count(other) != 0 && twin_can_share(l, t);
-  return build_on_levels(fine, coarse, pi, l, s, m, nullptr, inverse);
+  return build_on_levels(fine, coarse, pi, l, s, m, nullptr, inverse, want_event);
 }
 
 // SPC_NET_PIPELINED: one build stream, work in the order of first use (a level right before the first
@@ -1098,7 +1127,7 @@ static int build_network_pipelined(const void* v0_keys, int64_t n0, const PackIn
       for (int j = 0; j < 2 && rc == SPC_OK; ++j) {
         if (levels.count(need[j])) continue;
         Level* lv = nullptr;
-        rc = downsample_level(v0_keys, n0, nullptr, pi, ilog2(need[j]), &lv, sl);
+        rc = downsample_level(v0_keys, n0, pi, ilog2(need[j]), &lv, sl, true);
         if (rc == SPC_OK) levels[need[j]] = lv;
       }
     }
@@ -1111,7 +1140,7 @@ static int build_network_pipelined(const void* v0_keys, int64_t n0, const PackIn
     for (int j = 0; j < 2 && rc == SPC_OK; ++j) {
       if (!levels.count(need[j])) {  // one build stream: the level right before the first map that reads it
         Level* lv = nullptr;
-        rc = downsample_level(v0_keys, n0, nullptr, pi, ilog2(need[j]), &lv, sb);
+        rc = downsample_level(v0_keys, n0, pi, ilog2(need[j]), &lv, sb, false);
         if (rc == SPC_OK) levels[need[j]] = lv;
       } else if (sl != sb && levels[need[j]]->ready && awaited.insert(levels[need[j]]).second) {
         if (hipStreamWaitEvent(sb, levels[need[j]]->ready, 0) != hipSuccess) rc = set_error(SPC_ERR_HIP, "hipStreamWaitEvent failed");
@@ -1121,7 +1150,7 @@ static int build_network_pipelined(const void* v0_keys, int64_t n0, const PackIn
     Level* fine = levels[l.in_stride];
     Level* coarse = levels[l.in_stride * l.layer_stride];
     spc_kmap* m = nullptr;
-    rc = build_network_map(key, l, want, maps, fine, coarse, pi, sb, &m);
+    rc = build_network_map(key, l, want, maps, fine, coarse, pi, sb, &m, true);
     if (rc == SPC_OK) {
       m->wait_on_use = true;
       maps[key] = m;
@@ -1167,7 +1196,7 @@ int spc_build_kmap_perm(const void* in_keys, int64_t n_in, const int32_t* in_per
   Level* given = borrowed_level(in_keys, n_in, l->in_stride);
   Level* derived = nullptr;
   int rc = SPC_OK;
-  if (l->layer_stride > 1) rc = downsample_level(in_keys, n_in, nullptr, pi, ilog2(l->in_stride * l->layer_stride), &derived, s);
+  if (l->layer_stride > 1) rc = downsample_level(in_keys, n_in, pi, ilog2(l->in_stride * l->layer_stride), &derived, s, false);
   if (rc == SPC_OK) {
     if (in_perm && l->transposed) rc = set_error(SPC_ERR_ARG, "in_perm applies to the given level, which a transposed layer writes");
     else if (in_perm && (l->layout & SPC_LAYOUT_WS_SYM))
@@ -1218,7 +1247,7 @@ int spc_build_kmaps_network(const void* v0_keys, int64_t n0, const spc_pack_desc
       if (levels.count(need[j])) continue;
       const int si = (next++) % ns;
       Level* lv = nullptr;
-      rc = downsample_level(v0_keys, n0, nullptr, pi, ilog2(need[j]), &lv, st[si]);
+      rc = downsample_level(v0_keys, n0, pi, ilog2(need[j]), &lv, st[si], ns > 1);
       if (rc == SPC_OK) {
         levels[need[j]] = lv;
         level_stream[need[j]] = si;
@@ -1277,7 +1306,7 @@ int spc_build_kmaps_network(const void* v0_keys, int64_t n0, const spc_pack_desc
         if (e != hipSuccess) rc = set_error(SPC_ERR_HIP, "hipStreamWaitEvent: %s", hipGetErrorString(e));
       }
     spc_kmap* m = nullptr;
-    if (rc == SPC_OK) rc = build_network_map(kv.first, l, want, maps, fine, coarse, pi, st[si], &m);
+    if (rc == SPC_OK) rc = build_network_map(kv.first, l, want, maps, fine, coarse, pi, st[si], &m, false);
     if (rc == SPC_OK) maps[kv.first] = m;
   }
   // join: streams[0] continues only after everything the other streams were given

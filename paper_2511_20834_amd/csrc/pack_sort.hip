@@ -78,6 +78,7 @@ __global__ __launch_bounds__(256) void dup_check_kernel(const KeyT* __restrict__
 }
 
 __global__ void set_int_kernel(int32_t* p, int32_t v) { *p = v; }
+__global__ void publish_count_kernel(CountOut count, int32_t v) { count.publish(v); }
 
 template <typename KeyT>
 __global__ __launch_bounds__(256) void mask_kernel(const KeyT* __restrict__ in, int64_t n, KeyT mask, KeyT* __restrict__ out) {
@@ -130,9 +131,9 @@ __global__ __launch_bounds__(UQ_THREADS) void unique_count_kernel(const KeyT* __
   if (threadIdx.x == 0) block_counts[blockIdx.x] = total;
 }
 
-// Single workgroup: exclusive scan of n_blocks counts in place; the grand total goes to *n_out.
+// Single workgroup: exclusive scan of n_blocks counts in place; the grand total is the level's count.
 __global__ __launch_bounds__(UQ_THREADS) void scan_counts_kernel(int32_t* __restrict__ counts, int n_blocks,
-                                                                 int32_t* __restrict__ n_out) {
+                                                                 CountOut count) {
   int carry = 0;
   for (int b0 = 0; b0 < n_blocks; b0 += UQ_THREADS) {
     const int i = b0 + threadIdx.x;
@@ -142,7 +143,7 @@ __global__ __launch_bounds__(UQ_THREADS) void scan_counts_kernel(int32_t* __rest
     if (i < n_blocks) counts[i] = carry + ex;
     carry += total;
   }
-  if (threadIdx.x == 0) *n_out = carry;
+  if (threadIdx.x == 0) count.publish(carry);
 }
 
 template <typename KeyT>
@@ -163,14 +164,15 @@ __global__ __launch_bounds__(UQ_THREADS) void unique_write_kernel(const KeyT* __
 
 template <typename KeyT>
 static int downsample_t(const void* src, int64_t n, const PackInfo& pi, int m, Level* lv, hipStream_t s) {
+  const CountOut count{lv->n_dev, lv->slot.dev, lv->slot.tag};
   if (use_bucket_sort(n)) {
     char* scratch = static_cast<char*>(pool_alloc(bucket_sort_ws_bytes(pi.key_bits, n), s));
     if (!scratch) return SPC_ERR_NOMEM;
-    const int rc = bucket_mask_unique(pi.key_bits, src, n, level_mask(pi, m), pi.used_bits, lv->keys, lv->n_dev, scratch, s);
+    const int rc = bucket_mask_unique(pi.key_bits, src, n, level_mask(pi, m), pi.used_bits, lv->keys, count, scratch, s);
     pool_free(scratch, s);  // reuse is ordered behind these kernels on this stream
     return rc;
   }
-  if (n > 0 && n < BS_MIN_N) return small_mask_unique(pi.key_bits, src, n, level_mask(pi, m), pi.used_bits, lv->keys, lv->n_dev, s);
+  if (n > 0 && n < BS_MIN_N) return small_mask_unique(pi.key_bits, src, n, level_mask(pi, m), pi.used_bits, lv->keys, count, s);
   if (n > 0) SPC_RETURN_IF(refuse_if_capturing(s, n));
   const size_t ksz = sizeof(KeyT);
   const size_t tb = sort_keys_temp_bytes(pi.key_bits, n);
@@ -192,12 +194,12 @@ static int downsample_t(const void* src, int64_t n, const PackInfo& pi, int m, L
     rc = sort_keys(pi.key_bits, masked, sorted, n, pi.used_bits, scratch + off_temp, tb, s);
     if (rc == SPC_OK) {
       hipLaunchKernelGGL(unique_count_kernel<KeyT>, dim3(n_blocks), dim3(UQ_THREADS), 0, s, sorted, n, counts);
-      hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(UQ_THREADS), 0, s, counts, n_blocks, lv->n_dev);
+      hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(UQ_THREADS), 0, s, counts, n_blocks, count);
       hipLaunchKernelGGL(unique_write_kernel<KeyT>, dim3(n_blocks), dim3(UQ_THREADS), 0, s, sorted, n, counts,
                          static_cast<KeyT*>(lv->keys));
     }
   } else {
-    hipLaunchKernelGGL(set_int_kernel, dim3(1), dim3(1), 0, s, lv->n_dev, 0);
+    hipLaunchKernelGGL(publish_count_kernel, dim3(1), dim3(1), 0, s, count, 0);
   }
   // The scratch block returns to the cache now; reuse is ordered behind these kernels
   // as long as later library calls are ordered after this stream's work.
@@ -206,8 +208,8 @@ static int downsample_t(const void* src, int64_t n, const PackInfo& pi, int m, L
   return rc;
 }
 
-int downsample_level(const void* src_keys, int64_t n_src, const int* /*n_src_dev*/, const PackInfo& pi, int m, Level** out,
-                     hipStream_t stream) {
+int downsample_level(const void* src_keys, int64_t n_src, const PackInfo& pi, int m, Level** out, hipStream_t stream,
+                     bool want_event) {
   Level* lv = new Level;
   lv->cap = n_src;
   lv->stride = 1 << m;
@@ -216,13 +218,15 @@ int downsample_level(const void* src_keys, int64_t n_src, const int* /*n_src_dev
   lv->captured = stream_is_capturing(stream);
   lv->keys = pool_alloc(std::max<size_t>(size_t(n_src) * (pi.key_bits / 8), 256), stream);
   lv->n_dev = static_cast<int*>(pool_alloc(256, stream));
+  if (!lv->captured) lv->slot = count_slot_alloc(stream);
+  const StreamWorkNote note{stream};
   if (!lv->keys || !lv->n_dev) {
     level_unref(lv);
     return SPC_ERR_NOMEM;
   }
   int rc = pi.key_bits == 32 ? downsample_t<uint32_t>(src_keys, n_src, pi, m, lv, stream)
                              : downsample_t<uint64_t>(src_keys, n_src, pi, m, lv, stream);
-  if (rc == SPC_OK) {
+  if (rc == SPC_OK && want_event) {
     if (hipEventCreateWithFlags(&lv->ready, hipEventDisableTiming) != hipSuccess ||
         hipEventRecord(lv->ready, stream) != hipSuccess)
       rc = set_error(SPC_ERR_HIP, "event record failed");

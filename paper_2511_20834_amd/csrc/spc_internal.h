@@ -36,9 +36,44 @@ void* pool_alloc(size_t bytes, hipStream_t stream);  // nullptr on failure (erro
 void pool_free(void* p, hipStream_t stream);
 int pool_release_all();
 // Makes everything enqueued on `waiter` from now on run after what `producer` holds at this moment
-// (an event recorded on `producer`; nothing happens when the two are the same stream).  Used before a
+// (an event recorded on `producer`; nothing happens when the two are the same stream, or when `waiter` has been
+// ordered behind `producer` before and the library has enqueued nothing on `producer` since).  Used before a
 // block goes back to the cache of a stream other than the one whose kernels last read it.
 void order_stream_after(hipStream_t waiter, hipStream_t producer);
+// Every library call that enqueues kernels reading pooled blocks on `s` says so once they are enqueued (an order that
+// another thread makes meanwhile is then made again): order_stream_after relies on it.
+void note_stream_work(hipStream_t s);
+struct StreamWorkNote {
+  hipStream_t s;
+  ~StreamWorkNote() { note_stream_work(s); }
+};
+
+// ---------------------------------------------------------------- counts the host waits for
+// Where a kernel leaves a count: always in device memory, and (slot given) also in pinned host memory, tagged with a
+// number of this build's own, so that the host can poll for exactly this value.  A host that waited for an event and
+// copied four bytes paid 21 us from the kernel's end to the number; the poll sees it about 2 us after the store.
+struct CountOut {
+  int32_t* n_out = nullptr;
+  unsigned long long* slot = nullptr;  // device address of the pinned slot, or NULL
+  uint32_t tag = 0;
+#ifdef __HIPCC__
+  __device__ void publish(int v) const {
+    *n_out = v;
+    if (slot)
+      __hip_atomic_store(slot, (static_cast<unsigned long long>(tag) << 32) | static_cast<uint32_t>(v), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+#endif
+};
+// A slot is handed out again only to work on the stream that wrote it last (stream order keeps an earlier owner's late
+// store in front of the new owner's, and the tag tells them apart).
+struct CountSlot {
+  unsigned long long* host = nullptr;
+  unsigned long long* dev = nullptr;
+  uint32_t tag = 0;
+};
+CountSlot count_slot_alloc(hipStream_t s);  // host == nullptr when no pinned memory is to be had
+void count_slot_free(const CountSlot& c, hipStream_t s);
 
 // ---------------------------------------------------------------- packing
 struct PackInfo {
@@ -83,8 +118,9 @@ struct Level {
   int64_t n_fetched = -1; // last value read back from n_dev (equals n_host unless the level was built under capture)
   bool captured = false;  // produced while its stream was being captured into a graph: every replay rewrites it
   int* n_dev = nullptr;   // device int (nullptr when n_host is authoritative from the start)
+  CountSlot slot;         // where the host polls for the count (not for levels built under capture)
   int stride = 1;
-  hipEvent_t ready = nullptr;  // recorded after the level's last kernel
+  hipEvent_t ready = nullptr;  // recorded after the level's last kernel when other streams are going to wait for it
   hipStream_t stream = nullptr;  // stream the level was produced on
   std::vector<hipStream_t> readers;  // other streams whose kernels read the keys (map searches)
   void add_reader(hipStream_t s) {
@@ -98,8 +134,9 @@ void level_unref(Level* l);
 bool stream_is_capturing(hipStream_t s);
 
 // Derive the level with stride 2^m of `src_keys` (mask, sort, unique).  Enqueues only.
-int downsample_level(const void* src_keys, int64_t n_src, const int* n_src_dev, const PackInfo& pi, int m,
-                     Level** out, hipStream_t stream);
+// want_event: other streams will wait for the level (an event record costs the host 3 us and the stream 2 us).
+int downsample_level(const void* src_keys, int64_t n_src, const PackInfo& pi, int m, Level** out, hipStream_t stream,
+                     bool want_event);
 
 // ---------------------------------------------------------------- packing (Section 5.3)
 struct PackParams {
@@ -155,15 +192,15 @@ size_t bucket_sort_ws_bytes(int key_bits, int64_t n);
 // coords -> sorted keys (+ permutation); enqueues four kernels (count, colscan, scatter, rank)
 int bucket_pack_sort(int key_bits, const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status,
                      void* keys_out, int32_t* perm_out, void* ws, hipStream_t s);
-// sorted distinct values of keys_in & mask, count to *n_out [device]; enqueues five kernels
+// sorted distinct values of keys_in & mask and their count; enqueues five kernels
 int bucket_mask_unique(int key_bits, const void* keys_in, int64_t n, uint64_t mask, int used_bits, void* keys_out,
-                       int32_t* n_out, void* ws, hipStream_t s);
+                       const CountOut& count, void* ws, hipStream_t s);
 
-// fewer than BS_MIN_N keys: one workgroup sorts them in LDS, one launch (n_out [device] receives the distinct count)
+// fewer than BS_MIN_N keys: one workgroup sorts them in LDS, one launch
 int small_pack_sort(int key_bits, const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status, void* keys_out,
                     int32_t* perm_out, hipStream_t s);
-int small_mask_unique(int key_bits, const void* keys_in, int64_t n, uint64_t mask, int used_bits, void* keys_out, int32_t* n_out,
-                      hipStream_t s);
+int small_mask_unique(int key_bits, const void* keys_in, int64_t n, uint64_t mask, int used_bits, void* keys_out,
+                      const CountOut& count, hipStream_t s);
 
 // ---------------------------------------------------------------- sort (rocPRIM radix sort)
 size_t sort_pairs_temp_bytes(int key_bits, int64_t n);
@@ -205,7 +242,7 @@ struct spc_kmap {
   spc_kmap* twin = nullptr;         // transposed map derived from its strided twin (a reference is held): WS lists alias the twin's
   int tile = 0, n_tiles = 0;
   std::vector<int64_t> nnz_host;    // filled lazily
-  hipEvent_t ready = nullptr;       // recorded after the last build kernel
+  hipEvent_t ready = nullptr;       // recorded after the last build kernel of a map whose consumers wait for it (wait_on_use)
   bool wait_on_use = false;         // nobody has joined the build stream: consumers on other streams wait for `ready`
   hipStream_t last_waiter = nullptr;  // the consumer stream that has waited for `ready` most recently
   std::vector<hipStream_t> consumers;  // streams other than `stream` whose feature kernels have read the map

@@ -30,6 +30,7 @@ class SpcNetwork:
         self.maps = None
         self.size_hints = None  # per layer: n_out seen by the last learn_sizes()
         self._packed = None  # per layer: weights in the MFMA operand layout, or None
+        self._descs = (None, None)  # (settings it was made for, the layers' descriptors in C form)
         # concat plan: tensor name -> (buffer name, column offset); a buffer holds [src | skip]
         self._placement = {}
         for l in layers:
@@ -42,12 +43,15 @@ class SpcNetwork:
     def build_maps(self, v0_keys, desc, streams=None, flags=0, use_hints=False):
         """use_hints: hand the level sizes of the last learn_sizes() to the new maps, so that the feature
         kernels are chosen for those sizes without anybody waiting for the true counts."""
-        req = []
-        for l, df, t in zip(self.layers, self.dataflow, self.hybrid_t):
-            # a hybrid layer asks for exactly the split it will use: dense offsets in the matrix, sparse ones in lists
-            layout = (B.LAYOUT_BOTH | B.LAYOUT_HYBRID_T(t)) if t is not None else (B.LAYOUT_OS if df == B.DATAFLOW_OS else B.LAYOUT_WS)
-            req.append((l["K"], l["in_stride"], l["layer_stride"], l["transposed"], layout))
-        self.maps = B.spc_build_kmaps_network(v0_keys, desc, req, streams, flags)
+        settings = (tuple(self.dataflow), tuple(self.hybrid_t))
+        if self._descs[0] != settings:
+            req = []
+            for l, df, t in zip(self.layers, self.dataflow, self.hybrid_t):
+                # a hybrid layer asks for exactly the split it will use: dense offsets in the matrix, sparse ones in lists
+                layout = (B.LAYOUT_BOTH | B.LAYOUT_HYBRID_T(t)) if t is not None else (B.LAYOUT_OS if df == B.DATAFLOW_OS else B.LAYOUT_WS)
+                req.append((l["K"], l["in_stride"], l["layer_stride"], l["transposed"], layout))
+            self._descs = (settings, B.layer_descs(req))
+        self.maps = B.spc_build_kmaps_network(v0_keys, desc, self._descs[1], streams, flags)
         if use_hints and self.size_hints is not None:
             for m, h in zip(self.maps, self.size_hints):
                 m.set_size_hint(h)
@@ -88,25 +92,29 @@ class SpcNetwork:
         T = {"input": feats}
         bufs = {}
         y = None
+        # the 25 calls of a forward are host work as much as GPU work: the stream is looked up once, and tensors exist
+        # only where a caller sees them or a concat buffer is filled by columns
+        stream = B.current_raw_stream()
         for j, l in enumerate(self.layers):
             m = self.maps[j]
             n_out = m.n_out if static_rows is None else int(static_rows)
             x = T[l["src"]]
             if l["skip"] is not None:
-                buf, _, _ = self._placement[l["src"]]
-                x = bufs[buf]  # both halves were written in place by their producers
-            out = None
-            if l["save"] in self._placement:
-                buf, col, width = self._placement[l["save"]]
+                x = bufs[self._placement[l["src"]][0]]  # both halves were written in place by their producers
+            save, out = l["save"], None
+            if save in self._placement:
+                buf, col, width = self._placement[save]
                 if buf not in bufs:
-                    bufs[buf] = torch.empty((n_out, width), dtype=feats.dtype, device=feats.device)
-                out = bufs[buf][:, col:col + l["cout"]]
+                    bufs[buf] = feats.new_empty((n_out, width))
+                out = bufs[buf].narrow(1, col, l["cout"])
+            else:
+                out = feats.new_empty((n_out, l["cout"]))
             flags = B.CONV_RELU if l["relu"] else 0
             w = self.weights[j]
             if self._packed[j] is not None:
                 w, flags = self._packed[j], flags | B.CONV_PACKED_WEIGHTS
-            y = B.spc_conv_forward(m, x, w, self.dataflow[j], flags, out=out, n_out=n_out, hybrid_t=self.hybrid_t[j])
-            T[l["save"]] = y
+            y = B.spc_conv_forward(m, x, w, self.dataflow[j], flags, out=out, stream=stream, hybrid_t=self.hybrid_t[j])
+            T[save] = y
         return (y, T) if keep else y
 
     def tune(self, v0_keys, desc, feats, reps=5):
