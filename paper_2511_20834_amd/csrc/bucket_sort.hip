@@ -23,6 +23,7 @@
 // position, first arrivals are marked in a bitmap and counted per chunk with global atomics,
 // and a fifth kernel, compact, closes the gaps.
 #include <algorithm>
+#include <type_traits>
 
 #include "spc_internal.h"
 
@@ -51,6 +52,7 @@ struct SrcPack {
   __device__ static void pin(Raw& r) { SPC_PIN_LOADED(r.c.x); }
   __device__ KeyT key(const Raw& r, bool& bad) const { return pack_key_flag<KeyT>(r.c, p, bad); }
   __device__ bool skip(const Raw&, KeyT) const { return false; }
+  __device__ SrcPack level(int) const { return *this; }
   __device__ void report(bool bad) const {
     if (bad && status) atomicOr(status, 1);
   }
@@ -74,23 +76,42 @@ struct SrcMask {
   __device__ bool skip(const Raw& r, KeyT key) const { return r.has_prev && (r.prev & mask) == key; }
   __device__ void report(bool) const {}
 };
+// A batch of levels of one network is produced by the same launches: block row y makes level y.
+template <typename KeyT>
+struct SrcMasks {
+  const KeyT* keys;
+  KeyT masks[BS_MAX_LEVELS];
+  __device__ SrcMask<KeyT> level(int y) const { return SrcMask<KeyT>{keys, masks[y]}; }
+};
+
+// This block row's copy of a workspace array: the workspaces of a batch of levels lie ws_pitch bytes apart.
+template <typename T>
+__device__ inline T* level_ws(T* p, size_t ws_pitch) {
+  using Byte = std::conditional_t<std::is_const<T>::value, const char, char>;
+  return reinterpret_cast<T*>(reinterpret_cast<Byte*>(p) + blockIdx.y * ws_pitch);
+}
 
 // ---------------------------------------------------------------- count
 template <typename KeyT, typename Src>
-__global__ __launch_bounds__(BS_WIDE) void bs_count_kernel(Src src, int64_t n, int per, int shift, int n_bin,
-                                                           KeyT* __restrict__ keys0, int32_t* __restrict__ table) {
+__global__ __launch_bounds__(BS_WIDE) void bs_count_kernel(const Src srcs, int64_t n, int per, int shift, int n_bin,
+                                                           KeyT* __restrict__ keys0, int32_t* __restrict__ table,
+                                                           size_t ws_pitch) {
   extern __shared__ int hist[];  // [n_bin]
+  const auto src = srcs.level(blockIdx.y);
+  using Level = std::remove_const_t<decltype(src)>;
+  keys0 = level_ws(keys0, ws_pitch);
+  table = level_ws(table, ws_pitch);
   for (int b = threadIdx.x; b < n_bin; b += BS_WIDE) hist[b] = 0;
   __syncthreads();
   const int64_t lo = int64_t(blockIdx.x) * per, hi = min<int64_t>(n, lo + per);
   bool bad = false;
   // four rows per thread and pass, fetched before any of them is turned into a key
   for (int64_t i0 = lo + threadIdx.x; i0 < hi; i0 += 4 * BS_WIDE) {
-    typename Src::Raw raw[4];
+    typename Level::Raw raw[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) raw[u] = src.load(min<int64_t>(i0 + u * BS_WIDE, hi - 1));
 #pragma unroll
-    for (int u = 0; u < 4; ++u) Src::pin(raw[u]);
+    for (int u = 0; u < 4; ++u) Level::pin(raw[u]);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       bool bad_u = false;
@@ -113,8 +134,11 @@ __global__ __launch_bounds__(BS_WIDE) void bs_count_kernel(Src src, int64_t n, i
 constexpr int BS_COL_THREADS = 64;
 __global__ __launch_bounds__(BS_COL_THREADS) void bs_colscan_kernel(const int32_t* __restrict__ table,
                                                                     int32_t* __restrict__ before, int n_wg, int n_bin,
-                                                                    int32_t* __restrict__ tot) {
+                                                                    int32_t* __restrict__ tot, size_t ws_pitch) {
   constexpr int ROWS = 16;
+  table = level_ws(table, ws_pitch);
+  before = level_ws(before, ws_pitch);
+  tot = level_ws(tot, ws_pitch);
   const int f0 = (blockIdx.x * BS_COL_THREADS + threadIdx.x) * 4;
   if (f0 >= n_bin) return;  // n_bin is a multiple of 4
   int4 run = make_int4(0, 0, 0, 0);
@@ -149,8 +173,19 @@ __global__ __launch_bounds__(BS_WIDE) void bs_scatter_kernel(const KeyT* __restr
                                                              int32_t* __restrict__ vals1, int2* __restrict__ win,
                                                              int32_t* __restrict__ n_part_keys, uint32_t* __restrict__ bits,
                                                              int n_words, int32_t* __restrict__ ccnt, int n_chunks,
-                                                             int32_t* __restrict__ rest_count) {
+                                                             int32_t* __restrict__ rest_count, size_t ws_pitch) {
   extern __shared__ int lds_bins[];
+  if (DEDUP) {
+    keys0 = level_ws(keys0, ws_pitch);
+    before = level_ws(before, ws_pitch);
+    tot = level_ws(tot, ws_pitch);
+    keys1 = level_ws(keys1, ws_pitch);
+    win = level_ws(win, ws_pitch);
+    n_part_keys = level_ws(n_part_keys, ws_pitch);
+    bits = level_ws(bits, ws_pitch);
+    ccnt = level_ws(ccnt, ws_pitch);
+    rest_count = level_ws(rest_count, ws_pitch);
+  }
   int* pos = lds_bins;                    // [n_bin + 1] this workgroup's running position in every bin
   int* bin_start = lds_bins + n_bin + 1;  // [n_bin + 1] where every bin starts
   __shared__ int wave_tot[BS_WIDE / 64];
@@ -464,18 +499,31 @@ template <typename KeyT>
 __global__ __launch_bounds__(BS_THREADS) void bs_rank_unique_kernel(const KeyT* __restrict__ keys1, const int2* __restrict__ win,
                                                                     const int32_t* __restrict__ n_kept,
                                                                     KeyT* __restrict__ sorted, uint32_t* __restrict__ bits,
-                                                                    int32_t* __restrict__ ccnt) {
+                                                                    int32_t* __restrict__ ccnt, size_t ws_pitch) {
   // (the grid is sized for the level before the equal neighbours were dropped)
-  bs_rank_unique_part<KeyT>(blockIdx.x, keys1, win, *n_kept, sorted, bits, ccnt);
+  bs_rank_unique_part<KeyT>(blockIdx.x, level_ws(keys1, ws_pitch), level_ws(win, ws_pitch), *level_ws(n_kept, ws_pitch),
+                            level_ws(sorted, ws_pitch), level_ws(bits, ws_pitch), level_ws(ccnt, ws_pitch));
 }
+
+// Where the levels of a batch go.
+template <typename KeyT>
+struct LevelOut {
+  KeyT* keys[BS_MAX_LEVELS];
+  CountOut count[BS_MAX_LEVELS];
+};
 
 // out = the marked positions of `sorted`, in order, and their number.  One workgroup per chunk
 // of BS_CHUNK positions: the keys before the chunk are the sum of the earlier chunks' counters.
 template <typename KeyT>
 __global__ __launch_bounds__(BS_THREADS) void bs_compact_kernel(const KeyT* __restrict__ sorted, const uint32_t* __restrict__ bits,
                                                                 const int32_t* __restrict__ ccnt,
-                                                                const int32_t* __restrict__ n_kept, KeyT* __restrict__ out,
-                                                                CountOut count) {
+                                                                const int32_t* __restrict__ n_kept, const LevelOut<KeyT> lo,
+                                                                size_t ws_pitch) {
+  sorted = level_ws(sorted, ws_pitch);
+  bits = level_ws(bits, ws_pitch);
+  ccnt = level_ws(ccnt, ws_pitch);
+  n_kept = level_ws(n_kept, ws_pitch);
+  KeyT* __restrict__ out = lo.keys[blockIdx.y];
   static_assert(BS_CHUNK == 4 * BS_THREADS, "four positions per thread");
   __shared__ int red[2][BS_THREADS / 64];
   __shared__ int wsum[BS_CHUNK / 32];
@@ -505,7 +553,7 @@ __global__ __launch_bounds__(BS_THREADS) void bs_compact_kernel(const KeyT* __re
     before += red[0][w];
     all += red[1][w];
   }
-  if (b == 0 && t == 0) count.publish(all);
+  if (b == 0 && t == 0) lo.count[blockIdx.y].publish(all);
   int rank = before + __popc(word & ((1u << (4 * sub)) - 1u));
   for (int w = 0; w < wi; ++w) rank += wsum[w];
 #pragma unroll
@@ -547,8 +595,19 @@ __global__ __launch_bounds__(BS_LT) void bs_rank_lds_kernel(const KeyT* __restri
                                                             const int32_t* __restrict__ n_d, int shift, int n_bin,
                                                             KeyT* __restrict__ out_k, int32_t* __restrict__ out_v,
                                                             uint32_t* __restrict__ bits, int32_t* __restrict__ ccnt,
-                                                            int32_t* __restrict__ rest_count, int32_t* __restrict__ rest) {
+                                                            int32_t* __restrict__ rest_count, int32_t* __restrict__ rest,
+                                                            size_t ws_pitch) {
   constexpr int WAVES = BS_LT / 64;
+  if (UNIQUE) {
+    keys1 = level_ws(keys1, ws_pitch);
+    win = level_ws(win, ws_pitch);
+    n_d = level_ws(n_d, ws_pitch);
+    out_k = level_ws(out_k, ws_pitch);
+    bits = level_ws(bits, ws_pitch);
+    ccnt = level_ws(ccnt, ws_pitch);
+    rest_count = level_ws(rest_count, ws_pitch);
+    rest = level_ws(rest, ws_pitch);
+  }
   __shared__ KeyT skey[BS_LW];
   __shared__ uint16_t sidx[BS_LW];
   __shared__ int hist[BS_LSUB];
@@ -701,7 +760,17 @@ __global__ __launch_bounds__(BS_THREADS) void bs_rank_rest_kernel(const int32_t*
                                                                   const int2* __restrict__ win, int n_h,
                                                                   const int32_t* __restrict__ n_d, KeyT* __restrict__ out_k,
                                                                   int32_t* __restrict__ out_v, uint32_t* __restrict__ bits,
-                                                                  int32_t* __restrict__ ccnt) {
+                                                                  int32_t* __restrict__ ccnt, size_t ws_pitch) {
+  if (UNIQUE) {
+    rest_count = level_ws(rest_count, ws_pitch);
+    rest = level_ws(rest, ws_pitch);
+    keys1 = level_ws(keys1, ws_pitch);
+    win = level_ws(win, ws_pitch);
+    n_d = level_ws(n_d, ws_pitch);
+    out_k = level_ws(out_k, ws_pitch);
+    bits = level_ws(bits, ws_pitch);
+    ccnt = level_ws(ccnt, ws_pitch);
+  }
   constexpr int PER = BS_LP / BS_PART;  // 64-position parts per listed workgroup
   const int n = n_d ? *n_d : n_h;
   const int todo = *rest_count * PER;
@@ -730,8 +799,10 @@ constexpr int BS_SMALL_BINS = 1 << BS_SMALL_BIN_BITS;
 static_assert(BS_SMALL_BINS <= BS_SMALL_THREADS && BS_SMALL_BINS % 64 == 0, "one thread clears a bin; wave 0 scans whole groups");
 constexpr int BS_SMALL_MAX = 4096;  // >= BS_MIN_N - 1
 template <typename KeyT, typename Src, bool DEDUP>
-__global__ __launch_bounds__(BS_SMALL_THREADS) void bs_small_sort_kernel(Src src, int n, int shift, KeyT* __restrict__ out_k,
-                                                                        int32_t* __restrict__ out_v, CountOut count) {
+__global__ __launch_bounds__(BS_SMALL_THREADS) void bs_small_sort_kernel(const Src srcs, int n, int shift, const LevelOut<KeyT> lo,
+                                                                        int32_t* __restrict__ out_v) {
+  const auto src = srcs.level(blockIdx.y);
+  KeyT* __restrict__ out_k = lo.keys[blockIdx.y];
   __shared__ KeyT sk0[BS_SMALL_MAX], sk1[BS_SMALL_MAX];
   __shared__ int16_t sv1[BS_SMALL_MAX];
   __shared__ int s_start[BS_SMALL_BINS + 1], s_cur[BS_SMALL_BINS];
@@ -835,36 +906,56 @@ __global__ __launch_bounds__(BS_SMALL_THREADS) void bs_small_sort_kernel(Src src
     const int i = tid * per + u;
     if (i < n && (i == 0 || sk0[i] != sk0[i - 1])) out_k[base++] = sk0[i];
   }
-  if (tid == 0) count.publish(total);
+  if (tid == 0) lo.count[blockIdx.y].publish(total);
 }
 
 template <typename KeyT, typename Src, bool DEDUP>
-static void launch_small_sort(const Src& src, int64_t n, int used_bits, void* out_k, int32_t* out_v, const CountOut& count,
+static void launch_small_sort(const Src& src, int64_t n, int used_bits, const LevelOut<KeyT>& lo, int n_levels, int32_t* out_v,
                               hipStream_t s) {
   static_assert(BS_SMALL_MAX >= BS_MIN_N - 1, "the small path covers every size below the partitioning sort's");
   const int shift = std::max(0, used_bits - BS_SMALL_BIN_BITS);  // bins = the top used key bits
-  hipLaunchKernelGGL((bs_small_sort_kernel<KeyT, Src, DEDUP>), dim3(1), dim3(BS_SMALL_THREADS), 0, s, src, static_cast<int>(n), shift,
-                     static_cast<KeyT*>(out_k), out_v, count);
+  hipLaunchKernelGGL((bs_small_sort_kernel<KeyT, Src, DEDUP>), dim3(1, n_levels), dim3(BS_SMALL_THREADS), 0, s, src,
+                     static_cast<int>(n), shift, lo, out_v);
+}
+
+template <typename KeyT>
+static void small_pack_sort_t(const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status, void* keys_out,
+                              int32_t* perm_out, hipStream_t s) {
+  LevelOut<KeyT> lo{};
+  lo.keys[0] = static_cast<KeyT*>(keys_out);
+  launch_small_sort<KeyT, SrcPack<KeyT>, false>(SrcPack<KeyT>{coords, pp, status}, n, used_bits, lo, 1, perm_out, s);
 }
 
 int small_pack_sort(int key_bits, const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status, void* keys_out,
                     int32_t* perm_out, hipStream_t s) {
-  if (key_bits == 32)
-    launch_small_sort<uint32_t, SrcPack<uint32_t>, false>(SrcPack<uint32_t>{coords, pp, status}, n, used_bits, keys_out, perm_out, CountOut{}, s);
-  else
-    launch_small_sort<uint64_t, SrcPack<uint64_t>, false>(SrcPack<uint64_t>{coords, pp, status}, n, used_bits, keys_out, perm_out, CountOut{}, s);
+  if (key_bits == 32) small_pack_sort_t<uint32_t>(coords, n, pp, used_bits, status, keys_out, perm_out, s);
+  else small_pack_sort_t<uint64_t>(coords, n, pp, used_bits, status, keys_out, perm_out, s);
   if (hipGetLastError() != hipSuccess) return set_error(SPC_ERR_HIP, "sort launch failed");
   return SPC_OK;
 }
 
-int small_mask_unique(int key_bits, const void* keys_in, int64_t n, uint64_t mask, int used_bits, void* keys_out,
-                      const CountOut& count, hipStream_t s) {
-  if (key_bits == 32)
-    launch_small_sort<uint32_t, SrcMask<uint32_t>, true>(SrcMask<uint32_t>{static_cast<const uint32_t*>(keys_in), static_cast<uint32_t>(mask)}, n,
-                                                         used_bits, keys_out, nullptr, count, s);
-  else
-    launch_small_sort<uint64_t, SrcMask<uint64_t>, true>(SrcMask<uint64_t>{static_cast<const uint64_t*>(keys_in), mask}, n, used_bits,
-                                                         keys_out, nullptr, count, s);
+template <typename KeyT>
+static void batch_args(const void* keys_in, const LevelJob* jobs, int n_levels, SrcMasks<KeyT>* src, LevelOut<KeyT>* lo) {
+  *src = SrcMasks<KeyT>{static_cast<const KeyT*>(keys_in), {}};
+  *lo = LevelOut<KeyT>{};
+  for (int y = 0; y < n_levels; ++y) {
+    src->masks[y] = static_cast<KeyT>(jobs[y].mask);
+    lo->keys[y] = static_cast<KeyT*>(jobs[y].keys_out);
+    lo->count[y] = jobs[y].count;
+  }
+}
+
+template <typename KeyT>
+static void small_mask_unique_t(const void* keys_in, int64_t n, const LevelJob* jobs, int n_levels, int used_bits, hipStream_t s) {
+  SrcMasks<KeyT> src;
+  LevelOut<KeyT> lo;
+  batch_args(keys_in, jobs, n_levels, &src, &lo);
+  launch_small_sort<KeyT, SrcMasks<KeyT>, true>(src, n, used_bits, lo, n_levels, nullptr, s);
+}
+
+int small_mask_unique(int key_bits, const void* keys_in, int64_t n, const LevelJob* jobs, int n_levels, int used_bits, hipStream_t s) {
+  if (key_bits == 32) small_mask_unique_t<uint32_t>(keys_in, n, jobs, n_levels, used_bits, s);
+  else small_mask_unique_t<uint64_t>(keys_in, n, jobs, n_levels, used_bits, s);
   if (hipGetLastError() != hipSuccess) return set_error(SPC_ERR_HIP, "downsample launch failed");
   return SPC_OK;
 }
@@ -937,19 +1028,20 @@ Ws<KeyT> carve(void* ws, int64_t n) {
 
 // count, column scan, scatter: keys1 (vals1) partitioned by fine bin, rank windows
 template <typename KeyT, bool DEDUP, typename Src>
-void partition(const Src& src, int64_t n, const BucketPlan& p, const Ws<KeyT>& w, hipStream_t s) {
-  hipLaunchKernelGGL((bs_count_kernel<KeyT, Src>), dim3(p.n_wg), dim3(BS_WIDE), size_t(p.n_bin) * 4, s, src, n, p.per, p.shift,
-                     p.n_bin, w.keys0, w.table);
+void partition(const Src& src, int64_t n, const BucketPlan& p, const Ws<KeyT>& w, int n_levels, size_t ws_pitch, hipStream_t s) {
+  hipLaunchKernelGGL((bs_count_kernel<KeyT, Src>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(p.n_bin) * 4, s, src, n, p.per,
+                     p.shift, p.n_bin, w.keys0, w.table, ws_pitch);
   const int col_wg = (p.n_bin / 4 + BS_COL_THREADS - 1) / BS_COL_THREADS;
-  hipLaunchKernelGGL(bs_colscan_kernel, dim3(col_wg), dim3(BS_COL_THREADS), 0, s, w.table, w.before, p.n_wg, p.n_bin, w.fstart);
+  hipLaunchKernelGGL(bs_colscan_kernel, dim3(col_wg, n_levels), dim3(BS_COL_THREADS), 0, s, w.table, w.before, p.n_wg, p.n_bin,
+                     w.fstart, ws_pitch);
   // (the scatter pass holds two ints per bin: beyond 8191 bins that is more than the default LDS limit)
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bs_scatter_kernel<KeyT, DEDUP>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (2 * BS_MAX_BIN + 2) * 4);
   (void)attr;
-  hipLaunchKernelGGL((bs_scatter_kernel<KeyT, DEDUP>), dim3(p.n_wg), dim3(BS_WIDE), size_t(2 * p.n_bin + 2) * 4, s, w.keys0, n, p.per,
+  hipLaunchKernelGGL((bs_scatter_kernel<KeyT, DEDUP>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(2 * p.n_bin + 2) * 4, s, w.keys0, n, p.per,
                      p.shift, p.n_bin, w.before,
                      w.fstart, w.keys1, w.vals1, w.win, DEDUP ? w.n_kept : static_cast<int32_t*>(nullptr), w.bits, w.n_words, w.ccnt,
-                     w.n_chunks, w.rest_count);
+                     w.n_chunks, w.rest_count, ws_pitch);
 }
 }  // namespace
 
@@ -966,7 +1058,7 @@ static int pack_sort_t(const int4* coords, int64_t n, const PackParams& pp, int 
                        int32_t* perm_out, void* ws, hipStream_t s) {
   const BucketPlan p = bucket_plan(n, used_bits);
   const Ws<KeyT> w = carve<KeyT>(ws, n);
-  partition<KeyT, false>(SrcPack<KeyT>{coords, pp, status}, n, p, w, s);
+  partition<KeyT, false>(SrcPack<KeyT>{coords, pp, status}, n, p, w, 1, 0, s);
   const int n_part = static_cast<int>((n + BS_PART - 1) / BS_PART);
   // Four waves share a part's window while the launch is latency-bound (its time is that of the part with
   // the largest window); from BS_RANK_SOLO_N keys on (25 parts per CU) the pass is bound by how many parts
@@ -977,10 +1069,10 @@ static int pack_sort_t(const int4* coords, int64_t n, const PackParams& pp, int 
     hipLaunchKernelGGL((bs_rank_lds_kernel<KeyT, false>), dim3(static_cast<int>((n + BS_LP - 1) / BS_LP)), dim3(BS_LT), 0, s, w.keys1,
                        w.vals1, w.win, static_cast<int>(n), static_cast<const int32_t*>(nullptr), p.shift, p.n_bin,
                        static_cast<KeyT*>(keys_out), perm_out, static_cast<uint32_t*>(nullptr), static_cast<int32_t*>(nullptr),
-                       w.rest_count, w.rest);
+                       w.rest_count, w.rest, size_t(0));
     hipLaunchKernelGGL((bs_rank_rest_kernel<KeyT, false>), dim3(BS_REST_WG), dim3(BS_THREADS), 0, s, w.rest_count, w.rest, w.keys1,
                        w.vals1, w.win, static_cast<int>(n), static_cast<const int32_t*>(nullptr), static_cast<KeyT*>(keys_out),
-                       perm_out, static_cast<uint32_t*>(nullptr), static_cast<int32_t*>(nullptr));
+                       perm_out, static_cast<uint32_t*>(nullptr), static_cast<int32_t*>(nullptr), size_t(0));
   } else if (n >= BS_RANK_SOLO_N)
     hipLaunchKernelGGL((bs_rank_kernel<KeyT, 1>), dim3(n_part), dim3(64), 0, s, w.keys1, w.vals1, w.win, static_cast<int>(n),
                        static_cast<KeyT*>(keys_out), perm_out);
@@ -998,33 +1090,36 @@ int bucket_pack_sort(int key_bits, const int4* coords, int64_t n, const PackPara
 }
 
 template <typename KeyT>
-static int mask_unique_t(const void* keys_in, int64_t n, uint64_t mask, int used_bits, void* keys_out, const CountOut& count,
-                         void* ws, hipStream_t s) {
+static int mask_unique_t(const void* keys_in, int64_t n, const LevelJob* jobs, int n_levels, int used_bits, void* ws, size_t ws_pitch,
+                         hipStream_t s) {
   const BucketPlan p = bucket_plan(n, used_bits);
   const Ws<KeyT> w = carve<KeyT>(ws, n);
-  partition<KeyT, true>(SrcMask<KeyT>{static_cast<const KeyT*>(keys_in), static_cast<KeyT>(mask)}, n, p, w, s);
+  SrcMasks<KeyT> src;
+  LevelOut<KeyT> lo;
+  batch_args(keys_in, jobs, n_levels, &src, &lo);
+  partition<KeyT, true>(src, n, p, w, n_levels, ws_pitch, s);
   // the sorted keys (with gaps) go to keys0, which is free again by now
   const int n_part = static_cast<int>((n + BS_PART - 1) / BS_PART), n_chunk = static_cast<int>((n + BS_CHUNK - 1) / BS_CHUNK);
   if (n >= BS_RANK_LDS_N) {
-    hipLaunchKernelGGL((bs_rank_lds_kernel<KeyT, true>), dim3(static_cast<int>((n + BS_LP - 1) / BS_LP)), dim3(BS_LT), 0, s, w.keys1,
-                       static_cast<const int32_t*>(nullptr), w.win, static_cast<int>(n), w.n_kept, p.shift, p.n_bin, w.keys0,
-                       static_cast<int32_t*>(nullptr), w.bits, w.ccnt, w.rest_count, w.rest);
-    hipLaunchKernelGGL((bs_rank_rest_kernel<KeyT, true>), dim3(BS_REST_WG), dim3(BS_THREADS), 0, s, w.rest_count, w.rest, w.keys1,
-                       static_cast<const int32_t*>(nullptr), w.win, static_cast<int>(n), w.n_kept, w.keys0,
-                       static_cast<int32_t*>(nullptr), w.bits, w.ccnt);
+    hipLaunchKernelGGL((bs_rank_lds_kernel<KeyT, true>), dim3(static_cast<int>((n + BS_LP - 1) / BS_LP), n_levels), dim3(BS_LT), 0, s,
+                       w.keys1, static_cast<const int32_t*>(nullptr), w.win, static_cast<int>(n), w.n_kept, p.shift, p.n_bin, w.keys0,
+                       static_cast<int32_t*>(nullptr), w.bits, w.ccnt, w.rest_count, w.rest, ws_pitch);
+    hipLaunchKernelGGL((bs_rank_rest_kernel<KeyT, true>), dim3(BS_REST_WG, n_levels), dim3(BS_THREADS), 0, s, w.rest_count, w.rest,
+                       w.keys1, static_cast<const int32_t*>(nullptr), w.win, static_cast<int>(n), w.n_kept, w.keys0,
+                       static_cast<int32_t*>(nullptr), w.bits, w.ccnt, ws_pitch);
   } else
-    hipLaunchKernelGGL(bs_rank_unique_kernel<KeyT>, dim3(n_part), dim3(BS_THREADS), 0, s, w.keys1, w.win, w.n_kept, w.keys0, w.bits,
-                       w.ccnt);
-  hipLaunchKernelGGL(bs_compact_kernel<KeyT>, dim3(n_chunk), dim3(BS_THREADS), 0, s, w.keys0, w.bits, w.ccnt, w.n_kept,
-                     static_cast<KeyT*>(keys_out), count);
+    hipLaunchKernelGGL(bs_rank_unique_kernel<KeyT>, dim3(n_part, n_levels), dim3(BS_THREADS), 0, s, w.keys1, w.win, w.n_kept, w.keys0,
+                       w.bits, w.ccnt, ws_pitch);
+  hipLaunchKernelGGL(bs_compact_kernel<KeyT>, dim3(n_chunk, n_levels), dim3(BS_THREADS), 0, s, w.keys0, w.bits, w.ccnt, w.n_kept, lo,
+                     ws_pitch);
   if (hipGetLastError() != hipSuccess) return set_error(SPC_ERR_HIP, "downsample launch failed");
   return SPC_OK;
 }
 
-int bucket_mask_unique(int key_bits, const void* keys_in, int64_t n, uint64_t mask, int used_bits, void* keys_out,
-                       const CountOut& count, void* ws, hipStream_t s) {
-  return key_bits == 32 ? mask_unique_t<uint32_t>(keys_in, n, mask, used_bits, keys_out, count, ws, s)
-                        : mask_unique_t<uint64_t>(keys_in, n, mask, used_bits, keys_out, count, ws, s);
+int bucket_mask_unique(int key_bits, const void* keys_in, int64_t n, const LevelJob* jobs, int n_levels, int used_bits, void* ws,
+                       size_t ws_pitch, hipStream_t s) {
+  return key_bits == 32 ? mask_unique_t<uint32_t>(keys_in, n, jobs, n_levels, used_bits, ws, ws_pitch, s)
+                        : mask_unique_t<uint64_t>(keys_in, n, jobs, n_levels, used_bits, ws, ws_pitch, s);
 }
 
 }  // namespace spc

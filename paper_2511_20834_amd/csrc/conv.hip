@@ -1134,9 +1134,9 @@ static int conv_entry(spc_kmap* m, const void* feats_in, int64_t ld_in, const vo
   const StreamWorkNote note{a.s};
   // a map of a pipelined network build: nobody has joined its build stream, this stream waits for the map itself
   // (once per consumer stream: stream order covers the later layers that share the map)
-  if (m->wait_on_use && m->ready && m->stream != a.s && m->last_waiter != a.s) {
-    SPC_HIP_CHECK(hipStreamWaitEvent(a.s, m->ready, 0));
-    m->last_waiter = a.s;
+  if (m->ready && m->stream != a.s && m->ready->last_waiter != a.s) {
+    SPC_HIP_CHECK(hipStreamWaitEvent(a.s, m->ready->e, 0));
+    m->ready->last_waiter = a.s;
   }
   // remembered for spc_kmap_destroy: the build stream's cache must not hand the map's arrays out again
   // before this stream's kernels have read them

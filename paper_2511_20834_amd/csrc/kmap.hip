@@ -182,13 +182,54 @@ inline int search_tile(int K, int64_t n_out) { return K <= 3 ? (n_out >= SEARCH_
 //         tile * K^3 pairs, of which only the first sum-of-hits are touched); tile_counts gets the hits per
 //         (offset, tile).
 // Groups none of whose offsets is wanted are not searched (the second half of a symmetric map, for example).
-template <typename KeyT, int K, int TILE, bool PAIRS>
-__global__ __launch_bounds__(SEARCH_THREADS) void kmap_search_kernel(
-    const KeyT* __restrict__ in_keys, int n_in_h, const int* __restrict__ n_in_d, const KeyT* __restrict__ out_keys,
-    int n_out_h, const int* __restrict__ n_out_d, SearchParams<KeyT> sp, int32_t* __restrict__ M,
-    uint32_t* __restrict__ block_masks, int32_t* __restrict__ tile_counts, int n_tiles_cap,
-    const int32_t* __restrict__ in_perm, KMask os_k, KMask ws_k, int2* __restrict__ tile_pairs,
-    int32_t* __restrict__ inv_parent) {
+//
+// One launch searches NB maps of the same kernel size, block row y map y (NB = 1: a map of its own).  The maps of a
+// network's coarse levels are far too small to fill the chip, and a launch each costs more than their work: the nine
+// searches of a 25-layer UNet on 120 k voxels took nine launches and 79 us one after the other.
+template <typename KeyT>
+struct SearchArgs {
+  const KeyT* in_keys;
+  const int* n_in_d;
+  const KeyT* out_keys;
+  const int* n_out_d;
+  int n_in_h, n_out_h;
+  SearchParams<KeyT> sp;
+  int32_t* M;
+  uint32_t* block_masks;
+  int32_t* tile_counts;
+  const int32_t* in_perm;
+  int2* tile_pairs;
+  int32_t* inv_parent;
+  KMask os_k, ws_k;
+  int n_tiles_cap;
+};
+constexpr int SEARCH_BATCH = 8;
+// A level's voxel count, kept in a scalar register.  (A pointer that comes out of an indexed argument array is a generic
+// one to the compiler: loaded as such, the count and everything derived from it would be per-lane values.)
+__device__ inline int level_count(const int* n_d, int n_h) {
+  int n = n_h;
+  if (n_d) n = *(const __attribute__((address_space(1))) int*)n_d;
+  return __builtin_amdgcn_readfirstlane(n);
+}
+template <typename KeyT, int NB>
+struct SearchBatch {
+  SearchArgs<KeyT> a[NB];
+};
+
+template <typename KeyT, int K, int TILE, bool PAIRS, int NB>
+__global__ __launch_bounds__(SEARCH_THREADS) void kmap_search_kernel(const SearchBatch<KeyT, NB> batch) {
+  const SearchArgs<KeyT>& args = batch.a[NB == 1 ? 0 : blockIdx.y];
+  const KeyT* __restrict__ in_keys = args.in_keys;
+  const KeyT* __restrict__ out_keys = args.out_keys;
+  int32_t* __restrict__ M = args.M;
+  uint32_t* __restrict__ block_masks = args.block_masks;
+  int32_t* __restrict__ tile_counts = args.tile_counts;
+  const int32_t* __restrict__ in_perm = args.in_perm;
+  int2* __restrict__ tile_pairs = args.tile_pairs;
+  int32_t* __restrict__ inv_parent = args.inv_parent;
+  const SearchParams<KeyT>& sp = args.sp;
+  const KMask &os_k = args.os_k, &ws_k = args.ws_k;
+  const int n_tiles_cap = args.n_tiles_cap;
   constexpr int G = K * K, K3 = K * K * K;
   constexpr int tile = TILE;
   constexpr int SEARCH_GB = K <= 3 ? SEARCH_GB_SMALL : SEARCH_GB_LARGE;
@@ -213,8 +254,8 @@ __global__ __launch_bounds__(SEARCH_THREADS) void kmap_search_kernel(
   __shared__ unsigned s_mask[MAX_BLOCKS * MW];
   __shared__ KeyT s_gd[G];  // packed (dx,dy,zmin) offset of every group
 
-  const int n_in = n_in_d ? *n_in_d : n_in_h;
-  const int n_out = n_out_d ? *n_out_d : n_out_h;
+  const int n_in = level_count(args.n_in_d, args.n_in_h);
+  const int n_out = level_count(args.n_out_d, args.n_out_h);
   const int i0 = blockIdx.x * tile;
   if (i0 >= n_out) return;  // whole workgroup leaves together
   const int rows = min(tile, n_out - i0);
@@ -688,10 +729,24 @@ __global__ __launch_bounds__(256) void ws_scan_kernel(int32_t* __restrict__ tile
 // Where the twin's offsets partition its inputs (K = layer stride, e.g. 2x2x2 at stride 2), every output voxel p of
 // the transposed layer has exactly one pair, (input parent[p] / K^3, offset parent[p] % K^3): a thread per voxel
 // writes its row of the blocked matrix (full lines per offset) and the block masks fall out of ballots.
-__global__ __launch_bounds__(256) void transposed_from_parent_kernel(const int32_t* __restrict__ parent, int n_h,
-                                                                     const int* __restrict__ n_d, int K3,
-                                                                     int32_t* __restrict__ Mt, uint32_t* __restrict__ block_masks) {
-  const int n = n_d ? *n_d : n_h;
+// Block row y does map y of the batch.
+struct TransposedArgs {
+  const int32_t* parent;
+  const int* n_d;
+  int n_h, K3;
+  int32_t* Mt;
+  uint32_t* block_masks;
+};
+struct TransposedBatch {
+  TransposedArgs a[SEARCH_BATCH];
+};
+__global__ __launch_bounds__(256) void transposed_from_parent_kernel(const TransposedBatch batch) {
+  const TransposedArgs& args = batch.a[blockIdx.y];
+  const int32_t* __restrict__ parent = args.parent;
+  int32_t* __restrict__ Mt = args.Mt;
+  uint32_t* __restrict__ block_masks = args.block_masks;
+  const int K3 = args.K3;
+  const int n = level_count(args.n_d, args.n_h);
   const int64_t p = int64_t(blockIdx.x) * 256 + threadIdx.x;
   const int64_t blk = p >> 5;
   if (blk * 32 >= n) return;  // whole 32-row blocks leave together (the ballots below stay among one wave's lanes)
@@ -715,8 +770,8 @@ static int axis_offset(int K, int s, int i) { return (K % 2 == 1) ? (i - (K - 1)
 
 static std::atomic<int64_t> g_search_launches{0};  // searches enqueued by this process (see spc_search_count)
 
-template <typename KeyT, int K, int TILE>
-static int launch_search(spc_kmap* m, hipStream_t s) {
+template <typename KeyT, int K>
+static SearchArgs<KeyT> search_args(const spc_kmap* m) {
   const PackInfo& pi = m->pi;
   const int sp_stride = m->desc.in_stride;
   const int sign = m->desc.transposed ? -1 : 1;
@@ -737,37 +792,69 @@ static int launch_search(spc_kmap* m, hipStream_t s) {
       if ((m->os_map && m->os_k.has(g * K + t)) || m->ws_k.has(g * K + t)) sp.need |= 1ull << g;
   const Level* in = m->in_level;
   const Level* out = m->out_level;
+  SearchArgs<KeyT> a{};
+  a.in_keys = static_cast<const KeyT*>(in->keys);
+  a.n_in_h = static_cast<int>(in->n_host < 0 ? 0 : in->n_host);
+  a.n_in_d = in->n_dev;
+  a.out_keys = static_cast<const KeyT*>(out->keys);
+  a.n_out_h = static_cast<int>(out->n_host < 0 ? 0 : out->n_host);
+  a.n_out_d = out->n_dev;
+  a.sp = sp;
+  a.M = m->os_map;
+  a.block_masks = m->block_masks;
+  a.tile_counts = m->tile_counts;
+  a.n_tiles_cap = m->n_tiles;
+  a.in_perm = m->in_perm;
+  a.os_k = m->os_k;
+  a.ws_k = m->ws_k;
+  a.tile_pairs = m->tile_pairs;
+  a.inv_parent = m->inv_parent;
+  return a;
+}
+
+// The searches of ms[0..count): one kernel size, tile length and form (with or without lists) for all.
+template <typename KeyT, int K, int TILE>
+static void launch_search(spc_kmap* const* ms, int count, hipStream_t s) {
+  const spc_kmap* m = ms[0];
   const bool pairs = (m->desc.layout & SPC_LAYOUT_WS) != 0;
   const size_t lds = size_t(m->tile) * sizeof(KeyT) + WIN_CAP_BYTES + MAX_K * sizeof(KeyT) + (pairs ? size_t(K) * K * m->tile * 5 : 0);
-  auto go = [&](auto PAIRS_) {
+  auto go = [&](auto PAIRS_, auto NB_, int first, int n, int n_tiles) {
     constexpr bool PAIRS = decltype(PAIRS_)::value;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&kmap_search_kernel<KeyT, K, TILE, PAIRS>),
+    constexpr int NB = decltype(NB_)::value;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&kmap_search_kernel<KeyT, K, TILE, PAIRS, NB>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
     (void)attr;
-    hipLaunchKernelGGL((kmap_search_kernel<KeyT, K, TILE, PAIRS>), dim3(m->n_tiles), dim3(SEARCH_THREADS), lds, s,
-                       static_cast<const KeyT*>(in->keys), static_cast<int>(in->n_host < 0 ? 0 : in->n_host), in->n_dev,
-                       static_cast<const KeyT*>(out->keys), static_cast<int>(out->n_host < 0 ? 0 : out->n_host), out->n_dev,
-                       sp, m->os_map, m->block_masks, m->tile_counts, m->n_tiles, m->in_perm, m->os_k, m->ws_k,
-                       m->tile_pairs, m->inv_parent);
+    SearchBatch<KeyT, NB> b{};
+    for (int i = 0; i < n; ++i) b.a[i] = search_args<KeyT, K>(ms[first + i]);
+    hipLaunchKernelGGL((kmap_search_kernel<KeyT, K, TILE, PAIRS, NB>), dim3(n_tiles, n), dim3(SEARCH_THREADS), lds, s, b);
   };
-  if (m->n_tiles > 0) {
-    if (pairs) go(std::true_type{});
-    else go(std::false_type{});
+  // the large kernels are searched one map at a time: their levels' searches are long enough to stand alone
+  constexpr int MOST = K <= 3 ? SEARCH_BATCH : 1;
+  for (int first = 0; first < count; first += MOST) {
+    const int n = std::min(count - first, MOST);
+    int n_tiles = 0;
+    for (int i = 0; i < n; ++i) n_tiles = std::max(n_tiles, ms[first + i]->n_tiles);
+    if (n_tiles == 0) continue;
+    using One = std::integral_constant<int, 1>;
+    using Most = std::integral_constant<int, MOST>;
+    if (n == 1) pairs ? go(std::true_type{}, One{}, first, n, n_tiles) : go(std::false_type{}, One{}, first, n, n_tiles);
+    else pairs ? go(std::true_type{}, Most{}, first, n, n_tiles) : go(std::false_type{}, Most{}, first, n, n_tiles);
   }
-  g_search_launches.fetch_add(1, std::memory_order_relaxed);
-  return SPC_OK;
+  g_search_launches.fetch_add(count, std::memory_order_relaxed);
 }
 
 template <typename KeyT>
-static int launch_search_k(spc_kmap* m, hipStream_t s) {
-  switch (m->desc.K) {
-    case 1: return m->tile == 256 ? launch_search<KeyT, 1, 256>(m, s) : launch_search<KeyT, 1, 128>(m, s);
-    case 2: return m->tile == 256 ? launch_search<KeyT, 2, 256>(m, s) : launch_search<KeyT, 2, 128>(m, s);
-    case 3: return m->tile == 256 ? launch_search<KeyT, 3, 256>(m, s) : launch_search<KeyT, 3, 128>(m, s);
-    case 5: return launch_search<KeyT, 5, 128>(m, s);
-    case 7: return launch_search<KeyT, 7, 64>(m, s);
+static int launch_search_k(spc_kmap* const* ms, int count, hipStream_t s) {
+  const bool longer = ms[0]->tile == 256;
+  switch (ms[0]->desc.K) {
+    case 1: longer ? launch_search<KeyT, 1, 256>(ms, count, s) : launch_search<KeyT, 1, 128>(ms, count, s); break;
+    case 2: longer ? launch_search<KeyT, 2, 256>(ms, count, s) : launch_search<KeyT, 2, 128>(ms, count, s); break;
+    case 3: longer ? launch_search<KeyT, 3, 256>(ms, count, s) : launch_search<KeyT, 3, 128>(ms, count, s); break;
+    case 5: launch_search<KeyT, 5, 128>(ms, count, s); break;
+    case 7: launch_search<KeyT, 7, 64>(ms, count, s); break;
+    default: return set_error(SPC_ERR_UNSUPPORTED, "kernel size %d not built (1,2,3,5,7 are)", ms[0]->desc.K);
   }
-  return set_error(SPC_ERR_UNSUPPORTED, "kernel size %d not built (1,2,3,5,7 are)", m->desc.K);
+  return SPC_OK;
 }
 
 static void kmap_free(spc_kmap* m) {
@@ -796,8 +883,6 @@ static void kmap_free(spc_kmap* m) {
   pool_free(m->inv_parent, m->stream);
   level_unref(m->in_level);
   level_unref(m->out_level);
-  if (m->ready) (void)hipEventDestroy(m->ready);
-  for (hipEvent_t e : m->aux_events) (void)hipEventDestroy(e);
   delete m;
 }
 
@@ -845,10 +930,9 @@ static int ilog2(int v) {
   return b;
 }
 
-// Builds the map object for given input/output levels (references are taken).
-static int build_on_levels(Level* in, Level* out, const PackInfo& pi, const spc_layer_desc& l, hipStream_t s, spc_kmap** res,
-                           const int32_t* in_perm = nullptr, bool want_inverse = false, bool want_event = false) {
-  const StreamWorkNote note{s};
+// Makes the map object for given input/output levels (references are taken) with its arrays; nothing is searched yet.
+static int prepare_map(Level* in, Level* out, const PackInfo& pi, const spc_layer_desc& l, hipStream_t s, spc_kmap** res,
+                       const int32_t* in_perm, bool want_inverse) {
   spc_kmap* m = new spc_kmap;
   m->in_perm = in_perm;
   m->pi = pi;
@@ -904,8 +988,17 @@ static int build_on_levels(Level* in, Level* out, const PackInfo& pi, const spc_
     kmap_free(m);
     return SPC_ERR_NOMEM;
   }
-  int rc = pi.key_bits == 32 ? launch_search_k<uint32_t>(m, s) : launch_search_k<uint64_t>(m, s);
-  if (rc == SPC_OK && (l.layout & SPC_LAYOUT_WS)) {
+  *res = m;
+  return SPC_OK;
+}
+
+// Searches and lists of prepared maps that agree in kernel size, tile length, key width and in whether they have lists.
+static int search_maps(spc_kmap* const* ms, int count, hipStream_t s) {
+  SPC_RETURN_IF(ms[0]->pi.key_bits == 32 ? launch_search_k<uint32_t>(ms, count, s) : launch_search_k<uint64_t>(ms, count, s));
+  for (int i = 0; i < count; ++i) {
+    spc_kmap* m = ms[i];
+    if (!(m->desc.layout & SPC_LAYOUT_WS)) break;
+    const Level* out = m->out_level;
     const int n_out_h = static_cast<int>(out->n_host < 0 ? 0 : out->n_host);
     hipLaunchKernelGGL(ws_scan_kernel, dim3(m->K3), dim3(256), 0, s, m->tile_counts, m->n_tiles, m->tile, n_out_h,
                        out->n_dev, m->nnz_dev, m->k_lim);
@@ -916,10 +1009,17 @@ static int build_on_levels(Level* in, Level* out, const PackInfo& pi, const spc_
     pool_free(m->tile_pairs, s);
     m->tile_pairs = nullptr;
   }
-  if (rc == SPC_OK && hipGetLastError() != hipSuccess) rc = set_error(SPC_ERR_HIP, "kernel-map launch failed");
-  if (rc == SPC_OK && want_event && (hipEventCreateWithFlags(&m->ready, hipEventDisableTiming) != hipSuccess ||
-                       hipEventRecord(m->ready, s) != hipSuccess))
-    rc = set_error(SPC_ERR_HIP, "event record failed");
+  if (hipGetLastError() != hipSuccess) return set_error(SPC_ERR_HIP, "kernel-map launch failed");
+  return SPC_OK;
+}
+
+// One map, searched on its own.
+static int build_on_levels(Level* in, Level* out, const PackInfo& pi, const spc_layer_desc& l, hipStream_t s, spc_kmap** res,
+                           const int32_t* in_perm = nullptr, bool want_inverse = false) {
+  const StreamWorkNote note{s};
+  spc_kmap* m = nullptr;
+  SPC_RETURN_IF(prepare_map(in, out, pi, l, s, &m, in_perm, want_inverse));
+  const int rc = search_maps(&m, 1, s);
   if (rc != SPC_OK) {
     kmap_free(m);
     return rc;
@@ -939,13 +1039,12 @@ static bool twin_can_share(const spc_layer_desc& strided, const spc_layer_desc& 
 // The transposed map from its strided twin, built on the same stream (see transposed_from_parent_kernel): the matrix from the twin's inverse,
 // the lists by taking the twin's with inputs and outputs swapped (for a fixed offset both index sequences ascend
 // together, so the order by output index is kept).  Returns SPC_ERR_UNSUPPORTED when the twin lacks what is needed.
-static int build_transposed_from_twin(spc_kmap* twin, Level* coarse, Level* fine, const PackInfo& pi, const spc_layer_desc& l,
-                                      hipStream_t s, spc_kmap** res, bool want_event) {
+static int prepare_from_twin(spc_kmap* twin, Level* coarse, Level* fine, const PackInfo& pi, const spc_layer_desc& l,
+                             hipStream_t s, spc_kmap** res) {
   const bool with_os = (l.layout & SPC_LAYOUT_OS) != 0, with_ws = (l.layout & SPC_LAYOUT_WS) != 0;
   if (!twin_can_share(twin->desc, l) || (l.layout & ~SPC_LAYOUT_BOTH) || (with_os && !twin->inv_parent) ||
       (with_ws && (!(twin->desc.layout & SPC_LAYOUT_WS) || twin->hybrid_t || twin->sym)))
     return SPC_ERR_UNSUPPORTED;
-  const StreamWorkNote note{s};
   spc_kmap* m = new spc_kmap;
   m->pi = pi;
   m->desc = l;
@@ -974,10 +1073,6 @@ static int build_transposed_from_twin(spc_kmap* twin, Level* coarse, Level* fine
     m->os_map = static_cast<int32_t*>(pool_alloc(std::max<size_t>(size_t(m->n_blocks_cap) * 32 * m->K3 * 4, 256), s));
     m->block_masks = static_cast<uint32_t*>(pool_alloc(std::max<size_t>(size_t(m->n_blocks_cap) * 4, 256), s));
     if (!m->os_map || !m->block_masks) rc = SPC_ERR_NOMEM;
-    else if (m->out_cap > 0)
-      hipLaunchKernelGGL(transposed_from_parent_kernel, dim3(static_cast<unsigned>((m->out_cap + 255) / 256)), dim3(256), 0, s,
-                         twin->inv_parent, static_cast<int>(fine->n_host < 0 ? 0 : fine->n_host), fine->n_host < 0 ? fine->n_dev : nullptr,
-                         m->K3, m->os_map, m->block_masks);
   }
   if (rc == SPC_OK && with_ws) {
     m->ws_in = twin->ws_out;
@@ -985,15 +1080,32 @@ static int build_transposed_from_twin(spc_kmap* twin, Level* coarse, Level* fine
     m->nnz_dev = twin->nnz_dev;
     m->ws_stride = twin->ws_stride;
   }
-  if (rc == SPC_OK && hipGetLastError() != hipSuccess) rc = set_error(SPC_ERR_HIP, "kernel-map launch failed");
-  if (rc == SPC_OK && want_event && (hipEventCreateWithFlags(&m->ready, hipEventDisableTiming) != hipSuccess ||
-                       hipEventRecord(m->ready, s) != hipSuccess))
-    rc = set_error(SPC_ERR_HIP, "event record failed");
   if (rc != SPC_OK) {
     kmap_free(m);
     return rc;
   }
   *res = m;
+  return SPC_OK;
+}
+
+// The matrices of prepared transposed maps (their twins have been searched on the same stream before).
+static int fill_from_twins(spc_kmap* const* ms, int count, hipStream_t s) {
+  for (int first = 0; first < count; first += SEARCH_BATCH) {
+    const int n = std::min(count - first, SEARCH_BATCH);
+    TransposedBatch b{};
+    int64_t rows = 0;
+    for (int i = 0; i < n; ++i) {
+      const spc_kmap* m = ms[first + i];
+      const Level* fine = m->out_level;
+      if (!m->os_map) continue;  // lists only: the twin's (its argument entry has no rows)
+      b.a[i] = TransposedArgs{m->twin->inv_parent, fine->n_host < 0 ? fine->n_dev : nullptr,
+                              static_cast<int>(fine->n_host < 0 ? 0 : fine->n_host), m->K3, m->os_map, m->block_masks};
+      rows = std::max(rows, m->out_cap);
+    }
+    if (rows > 0)
+      hipLaunchKernelGGL(transposed_from_parent_kernel, dim3(static_cast<unsigned>((rows + 255) / 256), n), dim3(256), 0, s, b);
+  }
+  if (hipGetLastError() != hipSuccess) return set_error(SPC_ERR_HIP, "kernel-map launch failed");
   return SPC_OK;
 }
 
@@ -1007,11 +1119,10 @@ static Level* borrowed_level(const void* keys, int64_t n, int stride) {
   return lv;
 }
 
-// Waits for what a build has enqueued: its event where one was recorded, else everything on its stream so far (a stream
-// that is being captured by now cannot be waited for on its own: the device is drained).
-static int wait_stream(bool captured, hipEvent_t ready, hipStream_t s) {
-  if (captured || (!ready && stream_is_capturing(s))) SPC_HIP_CHECK(hipDeviceSynchronize());
-  else if (ready) SPC_HIP_CHECK(hipEventSynchronize(ready));
+// Waits for what a build has enqueued on its stream (a stream that is being captured by now cannot be waited for on
+// its own: the device is drained).
+static int wait_stream(bool captured, hipStream_t s) {
+  if (captured || stream_is_capturing(s)) SPC_HIP_CHECK(hipDeviceSynchronize());
   else SPC_HIP_CHECK(hipStreamSynchronize(s));
   return SPC_OK;
 }
@@ -1050,7 +1161,7 @@ static int fetch_level_n(Level* lv) {
     lv->n_host = lv->n_fetched = v;
     return SPC_OK;
   }
-  SPC_RETURN_IF(wait_stream(lv->captured, lv->ready, lv->stream));
+  SPC_RETURN_IF(wait_stream(lv->captured, lv->stream));
   SPC_HIP_CHECK(hipMemcpy(&v, lv->n_dev, sizeof(int), hipMemcpyDeviceToHost));
   lv->n_fetched = v;
   if (!lv->captured) lv->n_host = v;
@@ -1058,7 +1169,7 @@ static int fetch_level_n(Level* lv) {
 }
 
 // Waits until the map's arrays are complete (see fetch_level_n for captured builds).
-static int wait_map(const spc_kmap* m) { return wait_stream(m->captured, m->ready, m->stream); }
+static int wait_map(const spc_kmap* m) { return wait_stream(m->captured, m->stream); }
 
 // Layout every distinct map of a network is built with: the union of what its layers ask for; a map
 // shared by layers that disagree about the half-map keeps the full lists.
@@ -1087,90 +1198,120 @@ static std::map<NetKey, int> net_layouts(const spc_layer_desc* layers, int n_lay
   return want;
 }
 
-// One map of a network build.  A transposed layer whose strided twin has been built on the same stream (no
-// cross-stream edge is added) takes the twin's pairs; a strided layer with such a transposed twin among the
-// wanted maps leaves its inverse behind for it.  Everything else is searched.
-static int build_network_map(const NetKey& key, const spc_layer_desc& l, const std::map<NetKey, int>& want,
-                             const std::map<NetKey, spc_kmap*>& maps, Level* fine, Level* coarse, const PackInfo& pi, hipStream_t s,
-                             spc_kmap** m, bool want_event) {
-  const NetKey other(std::get<0>(key), std::get<1>(key), std::get<2>(key), l.transposed ? 0 : 1);
-  if (l.transposed) {
-    auto it = maps.find(other);
-    if (it != maps.end() && it->second->stream == s) {
-      const int rc = build_transposed_from_twin(it->second, coarse, fine, pi, l, s, m, want_event);
-      if (rc != SPC_ERR_UNSUPPORTED) return rc;
-    }
-    return build_on_levels(coarse, fine, pi, l, s, m, nullptr, false, want_event);
-  }
-  spc_layer_desc t = l;
-  t.transposed = 1;
-  const bool inverse = want.count(other) != 0 && twin_can_share(l, t);
-  return build_on_levels(fine, coarse, pi, l, s, m, nullptr, inverse, want_event);
-}
-
-// SPC_NET_PIPELINED: one build stream, work in the order of first use (a level right before the first
-// map that reads it), no join: the maps are marked so that their consumers wait for them.
-static int build_network_pipelined(const void* v0_keys, int64_t n0, const PackInfo& pi, const spc_layer_desc* layers,
-                                   int n_layers, spc_kmap** out, hipStream_t sb, hipStream_t sl, hipEvent_t fork) {
-  // sl: the stream of the coordinate levels (sb itself, or a stream of its own: every level comes straight from
-  // V_0, so the levels then run ahead of the searches, which wait for the level they read)
-  std::map<int, Level*> levels;
-  levels[1] = borrowed_level(v0_keys, n0, 1);
-  const std::map<NetKey, int> want = net_layouts(layers, n_layers);
+// ---------------------------------------------------------------- network builds
+// All levels of a network come straight from V_0 (closed form, Section 5.5) and therefore from the same launches, and its
+// maps are independent of each other given the levels: maps of one kernel size are searched by one launch, transposed
+// maps derived from their strided twins by another.  A 25-layer UNet is built by 5 + 3 launches instead of 33, on one
+// stream: with a launch per level and map, events tied three streams together and the host spent 206 us on it (120 k
+// voxels); the levels took 110 us of GPU time and take 35.
+struct NetBuild {
+  const PackInfo& pi;
+  std::map<NetKey, int> want;       // layout every distinct map is built with
+  std::map<int, Level*> levels;     // stride -> level
   std::map<NetKey, spc_kmap*> maps;
-  std::set<Level*> awaited;
-  spc_kmap* first = nullptr;
-  int rc = SPC_OK;
-  if (sl != sb)  // all levels up front, in the order of first use
-    for (int i = 0; i < n_layers && rc == SPC_OK; ++i) {
-      const int need[2] = {layers[i].in_stride, layers[i].in_stride * layers[i].layer_stride};
-      for (int j = 0; j < 2 && rc == SPC_OK; ++j) {
-        if (levels.count(need[j])) continue;
-        Level* lv = nullptr;
-        rc = downsample_level(v0_keys, n0, pi, ilog2(need[j]), &lv, sl, true);
-        if (rc == SPC_OK) levels[need[j]] = lv;
-      }
-    }
-  for (int i = 0; i < n_layers && rc == SPC_OK; ++i) {
-    const NetKey key = net_key(layers[i]);
-    if (maps.count(key)) continue;
-    spc_layer_desc l = layers[i];
-    l.layout = want.at(key);
-    const int need[2] = {l.in_stride, l.in_stride * l.layer_stride};
-    for (int j = 0; j < 2 && rc == SPC_OK; ++j) {
-      if (!levels.count(need[j])) {  // one build stream: the level right before the first map that reads it
-        Level* lv = nullptr;
-        rc = downsample_level(v0_keys, n0, pi, ilog2(need[j]), &lv, sb, false);
-        if (rc == SPC_OK) levels[need[j]] = lv;
-      } else if (sl != sb && levels[need[j]]->ready && awaited.insert(levels[need[j]]).second) {
-        if (hipStreamWaitEvent(sb, levels[need[j]]->ready, 0) != hipSuccess) rc = set_error(SPC_ERR_HIP, "hipStreamWaitEvent failed");
-      }
-    }
-    if (rc != SPC_OK) break;
-    Level* fine = levels[l.in_stride];
-    Level* coarse = levels[l.in_stride * l.layer_stride];
-    spc_kmap* m = nullptr;
-    rc = build_network_map(key, l, want, maps, fine, coarse, pi, sb, &m, true);
-    if (rc == SPC_OK) {
-      m->wait_on_use = true;
+  NetBuild(const PackInfo& p, const void* v0_keys, int64_t n0, const spc_layer_desc* layers, int n_layers)
+      : pi(p), want(net_layouts(layers, n_layers)) {
+    levels[1] = borrowed_level(v0_keys, n0, 1);
+  }
+  ~NetBuild() {  // drops the builder's own references
+    for (auto& kv : maps)
+      if (kv.second->refs.fetch_sub(1) == 1) kmap_free(kv.second);
+    for (auto& kv : levels) level_unref(kv.second);
+  }
+
+  // The levels the layers [0, n) need and nobody has made yet.
+  int make_levels(const spc_layer_desc* layers, int n, hipStream_t s) {
+    std::vector<int> ms;
+    std::set<int> seen;
+    for (int i = 0; i < n; ++i)
+      for (int stride : {layers[i].in_stride, layers[i].in_stride * layers[i].layer_stride})
+        if (!levels.count(stride) && seen.insert(stride).second) ms.push_back(ilog2(stride));
+    if (ms.empty()) return SPC_OK;
+    std::vector<Level*> made(ms.size());
+    SPC_RETURN_IF(downsample_levels(levels[1]->keys, levels[1]->n_host, pi, ms.data(), static_cast<int>(ms.size()), made.data(), s));
+    for (Level* lv : made) levels[lv->stride] = lv;
+    return SPC_OK;
+  }
+
+  // The distinct maps of layers [0, n) that nobody has made yet, in the order of first use, `most` at a launch (1: every
+  // map is searched by a launch of its own).
+  // A transposed layer whose strided twin has been built on the same stream takes the twin's pairs; a strided
+  // layer with such a transposed twin among the wanted maps leaves its inverse behind for it.
+  int make_maps(const spc_layer_desc* layers, int n, hipStream_t s, int most) {
+    const StreamWorkNote note{s};
+    using Group = std::tuple<int, int, bool>;  // kernel size, tile length, lists
+    std::vector<std::pair<Group, std::vector<spc_kmap*>>> groups;
+    std::vector<std::pair<NetKey, spc_layer_desc>> transposed;
+    int rc = SPC_OK;
+    auto enter = [&](const NetKey& key, spc_kmap* m) {
       maps[key] = m;
-      if (!first) first = m;
+      const Group g(m->desc.K, m->tile, (m->desc.layout & SPC_LAYOUT_WS) != 0);
+      for (auto& kv : groups)
+        if (kv.first == g && static_cast<int>(kv.second.size()) < most) {
+          kv.second.push_back(m);
+          return;
+        }
+      groups.push_back({g, {m}});
+    };
+    for (int i = 0; i < n && rc == SPC_OK; ++i) {
+      const NetKey key = net_key(layers[i]);
+      if (maps.count(key)) continue;
+      spc_layer_desc l = layers[i];
+      l.layout = want.at(key);
+      if (l.transposed) {
+        bool listed = false;
+        for (auto& t : transposed) listed |= t.first == key;
+        if (!listed) transposed.push_back({key, l});
+        continue;
+      }
+      spc_layer_desc t = l;
+      t.transposed = 1;
+      const bool inverse = want.count(net_key(t)) != 0 && twin_can_share(l, t);
+      spc_kmap* m = nullptr;
+      rc = prepare_map(levels[l.in_stride], levels[l.in_stride * l.layer_stride], pi, l, s, &m, nullptr, inverse);
+      if (rc == SPC_OK) enter(key, m);
+    }
+    std::vector<spc_kmap*> derived;
+    for (size_t i = 0; i < transposed.size() && rc == SPC_OK; ++i) {
+      const NetKey& key = transposed[i].first;
+      const spc_layer_desc& l = transposed[i].second;
+      Level* fine = levels[l.in_stride];
+      Level* coarse = levels[l.in_stride * l.layer_stride];
+      auto it = maps.find(NetKey(l.K, l.in_stride, l.layer_stride, 0));
+      spc_kmap* m = nullptr;
+      rc = SPC_ERR_UNSUPPORTED;
+      if (it != maps.end() && it->second->stream == s) rc = prepare_from_twin(it->second, coarse, fine, pi, l, s, &m);
+      if (rc == SPC_OK) {
+        maps[key] = m;
+        derived.push_back(m);
+      } else if (rc == SPC_ERR_UNSUPPORTED) {
+        rc = prepare_map(coarse, fine, pi, l, s, &m, nullptr, false);
+        if (rc == SPC_OK) enter(key, m);
+      }
+    }
+    for (auto& kv : groups)
+      if (rc == SPC_OK) rc = search_maps(kv.second.data(), static_cast<int>(kv.second.size()), s);
+    for (size_t i = 0; i < derived.size() && rc == SPC_OK; i += most)
+      rc = fill_from_twins(derived.data() + i, static_cast<int>(std::min<size_t>(derived.size() - i, most)), s);
+    return rc;
+  }
+
+  // Consumers on streams other than s wait for the maps (each stream once).
+  int mark_ready(hipStream_t s) {
+    auto r = std::make_shared<MapsReady>();
+    if (hipEventCreateWithFlags(&r->e, hipEventDisableTiming) != hipSuccess || hipEventRecord(r->e, s) != hipSuccess)
+      return set_error(SPC_ERR_HIP, "event record failed");
+    for (auto& kv : maps) kv.second->ready = r;
+    return SPC_OK;
+  }
+
+  void hand_out(const spc_layer_desc* layers, int n_layers, spc_kmap** out) {
+    for (int i = 0; i < n_layers; ++i) {
+      out[i] = maps[net_key(layers[i])];
+      out[i]->refs++;
     }
   }
-  // the fork event lives as long as the maps (a capture of this call refers to it)
-  if (rc == SPC_OK && first) first->aux_events.push_back(fork);
-  else (void)hipEventDestroy(fork);
-  if (rc == SPC_OK)
-    for (int i = 0; i < n_layers; ++i) {
-      spc_kmap* m = maps[net_key(layers[i])];
-      m->refs++;
-      out[i] = m;
-    }
-  for (auto& kv : maps)  // drop the builder's own reference
-    if (kv.second->refs.fetch_sub(1) == 1) kmap_free(kv.second);
-  for (auto& kv : levels) level_unref(kv.second);
-  return rc;
-}
+};
 
 }  // namespace spc
 
@@ -1196,7 +1337,8 @@ int spc_build_kmap_perm(const void* in_keys, int64_t n_in, const int32_t* in_per
   Level* given = borrowed_level(in_keys, n_in, l->in_stride);
   Level* derived = nullptr;
   int rc = SPC_OK;
-  if (l->layer_stride > 1) rc = downsample_level(in_keys, n_in, pi, ilog2(l->in_stride * l->layer_stride), &derived, s, false);
+  const int m = ilog2(l->in_stride * l->layer_stride);
+  if (l->layer_stride > 1) rc = downsample_levels(in_keys, n_in, pi, &m, 1, &derived, s);
   if (rc == SPC_OK) {
     if (in_perm && l->transposed) rc = set_error(SPC_ERR_ARG, "in_perm applies to the given level, which a transposed layer writes");
     else if (in_perm && (l->layout & SPC_LAYOUT_WS_SYM))
@@ -1221,118 +1363,24 @@ int spc_build_kmaps_network(const void* v0_keys, int64_t n0, const spc_pack_desc
     SPC_RETURN_IF(check_layer(&layers[i]));
     SPC_RETURN_IF(check_desc_layer(d, &layers[i]));
   }
-  const int ns = (flags & SPC_NET_SEQUENTIAL) ? 1 : n_streams;
-  std::vector<hipStream_t> st(ns);
-  for (int i = 0; i < ns; ++i) st[i] = static_cast<hipStream_t>(streams[i]);
-
-  // fork: every other stream waits for what streams[0] has enqueued so far (the pack/sort)
-  hipEvent_t fork = nullptr;
-  const bool pipelined = (flags & SPC_NET_PIPELINED) && ns >= 2;
-  if (ns > 1) {
-    SPC_HIP_CHECK(hipEventCreateWithFlags(&fork, hipEventDisableTiming));
-    SPC_HIP_CHECK(hipEventRecord(fork, st[0]));
-    for (int i = 1; i < (pipelined ? std::min(ns, 3) : ns); ++i) SPC_HIP_CHECK(hipStreamWaitEvent(st[i], fork, 0));
-  }
-  if (pipelined) return build_network_pipelined(v0_keys, n0, pi, layers, n_layers, out, st[1], ns >= 3 ? st[2] : st[1], fork);
-
-  // ---- phase 1: all coordinate levels, each straight from V_0 (closed form, Section 5.5)
-  std::map<int, Level*> levels;          // stride -> level
-  std::map<int, int> level_stream;       // stride -> index of the stream that produces it
-  levels[1] = borrowed_level(v0_keys, n0, 1);
-  level_stream[1] = 0;
-  int rc = SPC_OK, next = 0;
-  for (int i = 0; i < n_layers && rc == SPC_OK; ++i) {
-    const int need[2] = {layers[i].in_stride, layers[i].in_stride * layers[i].layer_stride};
-    for (int j = 0; j < 2 && rc == SPC_OK; ++j) {
-      if (levels.count(need[j])) continue;
-      const int si = (next++) % ns;
-      Level* lv = nullptr;
-      rc = downsample_level(v0_keys, n0, pi, ilog2(need[j]), &lv, st[si], ns > 1);
-      if (rc == SPC_OK) {
-        levels[need[j]] = lv;
-        level_stream[need[j]] = si;
-      }
-    }
-  }
-
-  std::vector<hipEvent_t> aux;
-  if (fork) aux.push_back(fork);
-  // Under stream capture the two-phase shape is forced: recording the free-form dependency
-  // pattern (streams waiting for each other's levels) has crashed the runtime's capture on
-  // ROCm 7.2, while fork / join / fork / join through streams[0] records fine.
-  const bool barrier = ns > 1 && ((flags & SPC_NET_PHASE_BARRIER) || stream_is_capturing(st[0]));
-  if (barrier && rc == SPC_OK) {
-    // all levels complete on streams[0], then every stream continues from there
-    for (int i = 1; i < ns; ++i) {
-      hipEvent_t j = nullptr;
-      if (hipEventCreateWithFlags(&j, hipEventDisableTiming) != hipSuccess || hipEventRecord(j, st[i]) != hipSuccess ||
-          hipStreamWaitEvent(st[0], j, 0) != hipSuccess)
-        rc = set_error(SPC_ERR_HIP, "joining stream %d failed", i);
-      if (j) aux.push_back(j);
-    }
-    hipEvent_t f2 = nullptr;
-    if (hipEventCreateWithFlags(&f2, hipEventDisableTiming) != hipSuccess || hipEventRecord(f2, st[0]) != hipSuccess)
-      rc = set_error(SPC_ERR_HIP, "fork failed");
-    if (f2) aux.push_back(f2);
-    for (int i = 1; i < ns && rc == SPC_OK; ++i)
-      if (hipStreamWaitEvent(st[i], f2, 0) != hipSuccess) rc = set_error(SPC_ERR_HIP, "fork failed");
-  }
-
-  // ---- phase 2: one search per distinct (K, in_stride, layer_stride, transposed)
-  using Key = NetKey;
-  std::map<Key, spc_kmap*> maps;
-  std::map<Key, int> want = net_layouts(layers, n_layers);
-  // A stream waits for each foreign event at most once (stream order covers everything it
-  // enqueues later), and the other streams join streams[0] once, at the end: few, distinct
-  // cross-stream edges, which is also what a graph capture of this call records.
-  std::vector<std::set<hipEvent_t>> waited(ns);
-  std::map<Key, int> map_stream;
-  next = 0;
-  for (auto& kv : want) {
-    if (rc != SPC_OK) break;
-    spc_layer_desc l{std::get<0>(kv.first), std::get<1>(kv.first), std::get<2>(kv.first), std::get<3>(kv.first), kv.second};
-    Level* fine = levels[l.in_stride];
-    Level* coarse = levels[l.in_stride * l.layer_stride];
-    Level* in = l.transposed ? coarse : fine;
-    Level* outl = l.transposed ? fine : coarse;
-    // a transposed map goes to the stream of its strided twin (built just before it: the keys are ordered that way),
-    // so that it can take the twin's pairs without a cross-stream wait
-    const Key twin_key(std::get<0>(kv.first), std::get<1>(kv.first), std::get<2>(kv.first), 0);
-    const int si = (l.transposed && map_stream.count(twin_key)) ? map_stream[twin_key] : (next++) % ns;
-    map_stream[kv.first] = si;
-    for (Level* dep : {in, outl})  // the map's stream waits for the levels it reads
-      if (!barrier && dep->ready && level_stream[dep->stride] != si && waited[si].insert(dep->ready).second) {
-        hipError_t e = hipStreamWaitEvent(st[si], dep->ready, 0);
-        if (e != hipSuccess) rc = set_error(SPC_ERR_HIP, "hipStreamWaitEvent: %s", hipGetErrorString(e));
-      }
-    spc_kmap* m = nullptr;
-    if (rc == SPC_OK) rc = build_network_map(kv.first, l, want, maps, fine, coarse, pi, st[si], &m, false);
-    if (rc == SPC_OK) maps[kv.first] = m;
-  }
-  // join: streams[0] continues only after everything the other streams were given
-  for (int i = 1; i < ns; ++i) {
-    hipEvent_t j = nullptr;
-    if (hipEventCreateWithFlags(&j, hipEventDisableTiming) != hipSuccess || hipEventRecord(j, st[i]) != hipSuccess ||
-        hipStreamWaitEvent(st[0], j, 0) != hipSuccess)
-      rc = set_error(SPC_ERR_HIP, "joining stream %d failed", i);
-    if (j) aux.push_back(j);
-  }
-  // these events live as long as the maps (a capture of this call refers to them): the first map owns them
-  if (rc == SPC_OK && !maps.empty()) maps.begin()->second->aux_events = aux;
-  else
-    for (hipEvent_t e : aux) (void)hipEventDestroy(e);
-
-  if (rc == SPC_OK) {
+  // Everything runs on streams[0].  Spread over several streams, or pipelined against the feature layers with a stream
+  // each for levels and searches, the same launches were slower at every size measured (a replayed 25-layer UNet step,
+  // three streams / one: 20 k voxels 378 / 316 us, 120 k 507 / 457, 200 k 610 / 568, 10^6 5339 / 5325): an edge between
+  // two streams costs about 14 us, and the batched launches leave little to overlap.
+  hipStream_t s = static_cast<hipStream_t>(streams[0]);
+  NetBuild b(pi, v0_keys, n0, layers, n_layers);
+  if (flags & SPC_NET_SEQUENTIAL) {  // a launch per level and per map, in the order of first use
     for (int i = 0; i < n_layers; ++i) {
-      spc_kmap* m = maps[Key(layers[i].K, layers[i].in_stride, layers[i].layer_stride, layers[i].transposed)];
-      m->refs++;
-      out[i] = m;
+      SPC_RETURN_IF(b.make_levels(layers + i, 1, s));
+      SPC_RETURN_IF(b.make_maps(layers + i, 1, s, 1));
     }
+  } else {
+    SPC_RETURN_IF(b.make_levels(layers, n_layers, s));
+    SPC_RETURN_IF(b.make_maps(layers, n_layers, s, SEARCH_BATCH));
   }
-  for (auto& kv : maps)  // drop the builder's own reference
-    if (kv.second->refs.fetch_sub(1) == 1) kmap_free(kv.second);
-  for (auto& kv : levels) level_unref(kv.second);
-  return rc;
+  if (flags & SPC_NET_PIPELINED) SPC_RETURN_IF(b.mark_ready(s));
+  b.hand_out(layers, n_layers, out);
+  return SPC_OK;
 }
 
 int spc_kmap_set_size_hint(spc_kmap* m, int64_t n_out_hint) {

@@ -1,5 +1,6 @@
 // Coordinate packing (Section 5.3), the one-time sort (Section 5.2) and the
 // packed-native downsampling of a stride level (Eq. 1 via mask, sort, unique).
+#include <algorithm>
 #include <cstring>
 
 #include <rocprim/device/device_radix_sort.hpp>
@@ -162,17 +163,10 @@ __global__ __launch_bounds__(UQ_THREADS) void unique_write_kernel(const KeyT* __
   }
 }
 
+// One level of a size the library's own sort does not take.
 template <typename KeyT>
 static int downsample_t(const void* src, int64_t n, const PackInfo& pi, int m, Level* lv, hipStream_t s) {
   const CountOut count{lv->n_dev, lv->slot.dev, lv->slot.tag};
-  if (use_bucket_sort(n)) {
-    char* scratch = static_cast<char*>(pool_alloc(bucket_sort_ws_bytes(pi.key_bits, n), s));
-    if (!scratch) return SPC_ERR_NOMEM;
-    const int rc = bucket_mask_unique(pi.key_bits, src, n, level_mask(pi, m), pi.used_bits, lv->keys, count, scratch, s);
-    pool_free(scratch, s);  // reuse is ordered behind these kernels on this stream
-    return rc;
-  }
-  if (n > 0 && n < BS_MIN_N) return small_mask_unique(pi.key_bits, src, n, level_mask(pi, m), pi.used_bits, lv->keys, count, s);
   if (n > 0) SPC_RETURN_IF(refuse_if_capturing(s, n));
   const size_t ksz = sizeof(KeyT);
   const size_t tb = sort_keys_temp_bytes(pi.key_bits, n);
@@ -208,35 +202,53 @@ static int downsample_t(const void* src, int64_t n, const PackInfo& pi, int m, L
   return rc;
 }
 
-int downsample_level(const void* src_keys, int64_t n_src, const PackInfo& pi, int m, Level** out, hipStream_t stream,
-                     bool want_event) {
-  Level* lv = new Level;
-  lv->cap = n_src;
-  lv->stride = 1 << m;
-  lv->owns_keys = true;
-  lv->stream = stream;
-  lv->captured = stream_is_capturing(stream);
-  lv->keys = pool_alloc(std::max<size_t>(size_t(n_src) * (pi.key_bits / 8), 256), stream);
-  lv->n_dev = static_cast<int*>(pool_alloc(256, stream));
-  if (!lv->captured) lv->slot = count_slot_alloc(stream);
+// Up to BS_MAX_LEVELS levels of one key array.  They share every launch where the library's own sort runs (a level's
+// five launches are bound by their launch and their dependent round trips at the sizes of a network: the four levels of
+// 120 k voxels took 20 launches and 110 us one after the other).
+static int downsample_batch(const void* src, int64_t n, const PackInfo& pi, const int* m, int count, Level** lv, hipStream_t s) {
+  const bool bucket = use_bucket_sort(n), small = n > 0 && n < BS_MIN_N;
+  if (!bucket && !small) {
+    for (int i = 0; i < count; ++i)
+      SPC_RETURN_IF(pi.key_bits == 32 ? downsample_t<uint32_t>(src, n, pi, m[i], lv[i], s) : downsample_t<uint64_t>(src, n, pi, m[i], lv[i], s));
+    return SPC_OK;
+  }
+  LevelJob jobs[BS_MAX_LEVELS];
+  for (int i = 0; i < count; ++i)
+    jobs[i] = LevelJob{level_mask(pi, m[i]), lv[i]->keys, CountOut{lv[i]->n_dev, lv[i]->slot.dev, lv[i]->slot.tag}};
+  if (small) return small_mask_unique(pi.key_bits, src, n, jobs, count, pi.used_bits, s);
+  const size_t pitch = (bucket_sort_ws_bytes(pi.key_bits, n) + 255) / 256 * 256;
+  char* scratch = static_cast<char*>(pool_alloc(pitch * count, s));
+  if (!scratch) return SPC_ERR_NOMEM;
+  const int rc = bucket_mask_unique(pi.key_bits, src, n, jobs, count, pi.used_bits, scratch, pitch, s);
+  pool_free(scratch, s);  // reuse is ordered behind these kernels on this stream
+  return rc;
+}
+
+int downsample_levels(const void* src_keys, int64_t n_src, const PackInfo& pi, const int* m, int count, Level** out,
+                      hipStream_t stream) {
   const StreamWorkNote note{stream};
-  if (!lv->keys || !lv->n_dev) {
-    level_unref(lv);
-    return SPC_ERR_NOMEM;
+  const bool captured = stream_is_capturing(stream);
+  int rc = SPC_OK;
+  for (int i = 0; i < count; ++i) {
+    Level* lv = out[i] = new Level;
+    lv->cap = n_src;
+    lv->stride = 1 << m[i];
+    lv->owns_keys = true;
+    lv->stream = stream;
+    lv->captured = captured;
+    lv->keys = pool_alloc(std::max<size_t>(size_t(n_src) * (pi.key_bits / 8), 256), stream);
+    lv->n_dev = static_cast<int*>(pool_alloc(256, stream));
+    if (!captured) lv->slot = count_slot_alloc(stream);
+    if (!lv->keys || !lv->n_dev) rc = SPC_ERR_NOMEM;
   }
-  int rc = pi.key_bits == 32 ? downsample_t<uint32_t>(src_keys, n_src, pi, m, lv, stream)
-                             : downsample_t<uint64_t>(src_keys, n_src, pi, m, lv, stream);
-  if (rc == SPC_OK && want_event) {
-    if (hipEventCreateWithFlags(&lv->ready, hipEventDisableTiming) != hipSuccess ||
-        hipEventRecord(lv->ready, stream) != hipSuccess)
-      rc = set_error(SPC_ERR_HIP, "event record failed");
-  }
-  if (rc != SPC_OK) {
-    level_unref(lv);
-    return rc;
-  }
-  *out = lv;
-  return SPC_OK;
+  for (int i = 0; i < count && rc == SPC_OK; i += BS_MAX_LEVELS)
+    rc = downsample_batch(src_keys, n_src, pi, m + i, std::min(count - i, BS_MAX_LEVELS), out + i, stream);
+  if (rc != SPC_OK)
+    for (int i = 0; i < count; ++i) {
+      level_unref(out[i]);
+      out[i] = nullptr;
+    }
+  return rc;
 }
 
 }  // namespace spc

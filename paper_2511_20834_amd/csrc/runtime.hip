@@ -257,7 +257,6 @@ void level_unref(Level* l) {
     if (l->owns_keys) pool_free(l->keys, l->stream);
     pool_free(l->n_dev, l->stream);
     count_slot_free(l->slot, l->stream);
-    if (l->ready) (void)hipEventDestroy(l->ready);
     delete l;
   }
 }

@@ -6,6 +6,7 @@
 #include <cstdarg>
 #include <cstdint>
 #include <cstdio>
+#include <memory>
 #include <mutex>
 #include <vector>
 
@@ -120,7 +121,6 @@ struct Level {
   int* n_dev = nullptr;   // device int (nullptr when n_host is authoritative from the start)
   CountSlot slot;         // where the host polls for the count (not for levels built under capture)
   int stride = 1;
-  hipEvent_t ready = nullptr;  // recorded after the level's last kernel when other streams are going to wait for it
   hipStream_t stream = nullptr;  // stream the level was produced on
   std::vector<hipStream_t> readers;  // other streams whose kernels read the keys (map searches)
   void add_reader(hipStream_t s) {
@@ -133,10 +133,9 @@ struct Level {
 void level_unref(Level* l);
 bool stream_is_capturing(hipStream_t s);
 
-// Derive the level with stride 2^m of `src_keys` (mask, sort, unique).  Enqueues only.
-// want_event: other streams will wait for the level (an event record costs the host 3 us and the stream 2 us).
-int downsample_level(const void* src_keys, int64_t n_src, const PackInfo& pi, int m, Level** out, hipStream_t stream,
-                     bool want_event);
+// Derive the levels with strides 2^m[i] of `src_keys` (mask, sort, unique), out[i] for i < count.  Enqueues only.
+int downsample_levels(const void* src_keys, int64_t n_src, const PackInfo& pi, const int* m, int count, Level** out,
+                      hipStream_t stream);
 
 // ---------------------------------------------------------------- packing (Section 5.3)
 struct PackParams {
@@ -192,15 +191,21 @@ size_t bucket_sort_ws_bytes(int key_bits, int64_t n);
 // coords -> sorted keys (+ permutation); enqueues four kernels (count, colscan, scatter, rank)
 int bucket_pack_sort(int key_bits, const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status,
                      void* keys_out, int32_t* perm_out, void* ws, hipStream_t s);
-// sorted distinct values of keys_in & mask and their count; enqueues five kernels
-int bucket_mask_unique(int key_bits, const void* keys_in, int64_t n, uint64_t mask, int used_bits, void* keys_out,
-                       const CountOut& count, void* ws, hipStream_t s);
+// One level to produce: the sorted distinct values of keys_in & mask, and their count.
+constexpr int BS_MAX_LEVELS = 8;  // levels of one batch (the block rows of its launches)
+struct LevelJob {
+  uint64_t mask;
+  void* keys_out;
+  CountOut count;
+};
+// n_levels <= BS_MAX_LEVELS levels of the same keys by the same five launches; level y works in ws + y * ws_pitch
+int bucket_mask_unique(int key_bits, const void* keys_in, int64_t n, const LevelJob* jobs, int n_levels, int used_bits, void* ws,
+                       size_t ws_pitch, hipStream_t s);
 
 // fewer than BS_MIN_N keys: one workgroup sorts them in LDS, one launch
 int small_pack_sort(int key_bits, const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status, void* keys_out,
                     int32_t* perm_out, hipStream_t s);
-int small_mask_unique(int key_bits, const void* keys_in, int64_t n, uint64_t mask, int used_bits, void* keys_out,
-                      const CountOut& count, hipStream_t s);
+int small_mask_unique(int key_bits, const void* keys_in, int64_t n, const LevelJob* jobs, int n_levels, int used_bits, hipStream_t s);
 
 // ---------------------------------------------------------------- sort (rocPRIM radix sort)
 size_t sort_pairs_temp_bytes(int key_bits, int64_t n);
@@ -210,6 +215,18 @@ size_t sort_keys_temp_bytes(int key_bits, int64_t n);
 int sort_keys(int key_bits, const void* keys_in, void* keys_out, int64_t n, int end_bit, void* temp,
               size_t temp_bytes, hipStream_t s);
 
+}  // namespace spc
+
+namespace spc {
+// Event behind the last kernel of a network build, and the consumer stream that has waited for it most recently (stream
+// order covers the maps' later uses there).
+struct MapsReady {
+  hipEvent_t e = nullptr;
+  hipStream_t last_waiter = nullptr;
+  ~MapsReady() {
+    if (e) (void)hipEventDestroy(e);
+  }
+};
 }  // namespace spc
 
 // ---------------------------------------------------------------- kernel map object
@@ -242,11 +259,8 @@ struct spc_kmap {
   spc_kmap* twin = nullptr;         // transposed map derived from its strided twin (a reference is held): WS lists alias the twin's
   int tile = 0, n_tiles = 0;
   std::vector<int64_t> nnz_host;    // filled lazily
-  hipEvent_t ready = nullptr;       // recorded after the last build kernel of a map whose consumers wait for it (wait_on_use)
-  bool wait_on_use = false;         // nobody has joined the build stream: consumers on other streams wait for `ready`
-  hipStream_t last_waiter = nullptr;  // the consumer stream that has waited for `ready` most recently
+  std::shared_ptr<spc::MapsReady> ready;  // set when nobody has joined the build stream: consumers on other streams wait for it
   std::vector<hipStream_t> consumers;  // streams other than `stream` whose feature kernels have read the map
-  std::vector<hipEvent_t> aux_events;  // fork/join events of the network build that made this map
   hipStream_t stream = nullptr;     // stream the map was built on
   int device = 0;
 };
