@@ -59,8 +59,8 @@ extern "C" {
  * t (other requests return SPC_ERR_ARG); accessors report each offset from the layout that holds it. */
 #define SPC_LAYOUT_HYBRID_T(t) ((t) << 8)
 
-#define SPC_DATAFLOW_OS 0 /* output-stationary: no atomics, bit-reproducible */
-#define SPC_DATAFLOW_WS 1 /* weight-stationary: fp32 atomic accumulation */
+#define SPC_DATAFLOW_OS 0 /* output-stationary: pairs from the matrix */
+#define SPC_DATAFLOW_WS 1 /* weight-stationary: pairs from the per-offset lists */
 
 #define SPC_PACK_VALIDATE 1 /* spc_pack_coords: check ranges and duplicates, wait, report */
 #define SPC_CONV_RELU 1     /* spc_conv_forward: apply max(x,0) before the output is stored */
@@ -266,16 +266,16 @@ void spc_kmap_destroy(spc_kmap* m);
  *   feats_out [device] n_out rows of cout elements, row pitch ld_out (lets a caller
  *             write straight into one half of a concatenated buffer).  Overwritten.
  *   dtype     SPC_DTYPE_F16 / BF16: MFMA contraction, fp32 accumulation, output rounded
- *             to nearest even.  SPC_DTYPE_F32: fp32 FMA arithmetic throughout.
+ *             to nearest even.  SPC_DTYPE_F32: fp32 products and sums throughout.
  *   dataflow  SPC_DATAFLOW_OS needs the OS layout, SPC_DATAFLOW_WS the WS layout
- *             (Section 2.2).  OS results are bit-reproducible; WS uses fp32 atomics.
+ *             (Section 2.2).  Results are bit-reproducible in both.
  *   flags     SPC_CONV_RELU; SPC_CONV_PACKED_WEIGHTS (see spc_conv_prepare_weights);
  *             SPC_CONV_OS_PHASE or SPC_CONV_OS_SPLITK pick one of the two OS MFMA kernels
  *             (default: chosen from the layer's size; both give the same result up to the
  *             fp32 summation order, and each one alone is bit-reproducible).
- * 16-bit layers with cout % 32 == 0 (OS) or cout in {32,64,128,256} (WS) run on MFMA; input
+ * Every shape and type runs on the matrix cores.  Where the phase kernel is taken, input
  * channel counts that are not a multiple of 16, and rows that are not 16-byte aligned, are
- * first copied into a zero-padded scratch buffer.  Everything else runs plain FMA kernels.
+ * first copied into a zero-padded scratch buffer.
  * Nothing is waited for, and nothing is allocated with hipMalloc once the library's block
  * cache holds the scratch sizes of this call (i.e. after one call of the same shape on the same
  * stream), so a warmed-up call sequence can be captured into a HIP graph: spc_pack_coords
@@ -296,9 +296,8 @@ int spc_conv_forward(spc_kmap* m, const void* feats_in, int64_t ld_in, const voi
 /*
  * Hybrid dual dataflow (Section 5.4): weight offsets whose L1 norm, in units of the layer's input
  * stride, is below the threshold t (the dense ones: the centre and its nearest neighbours) are
- * computed output-stationary, the others weight-stationary, and the two partial sums are merged
- * without an extra pass: the weight-stationary part accumulates in an fp32 buffer from which the
- * output-stationary kernel starts.  t = 0 is the pure weight-stationary dataflow, any t above the
+ * computed output-stationary, the others weight-stationary, and one kernel sums both in registers:
+ * the pairs of a block of outputs come from the matrix or from the lists, offset by offset.  t = 0 is the pure weight-stationary dataflow, any t above the
  * largest norm (3 * (K-1)/2 for odd K) the pure output-stationary one.  The map must hold both
  * layouts unless one part is empty.  Everything else as spc_conv_forward.
  */
@@ -330,8 +329,7 @@ int spc_conv_tune_threshold(spc_kmap* m, const void* feats_in, int64_t ld_in, co
 /*
  * Weights are constant during inference, so their re-layout into MFMA operand order can
  * be hoisted out of the layer call.  Writes K^3 * cin16 * cout elements to packed_out [device]
- * (same dtype), cin16 = cin rounded up to a multiple of 16 (the padding channels are zeros; a
- * layer with such a cin still copies its feature rows into a padded scratch buffer at every call),
+ * (same dtype), cin16 = cin rounded up to a multiple of 16 (the padding channels are zeros),
  * for use with SPC_CONV_PACKED_WEIGHTS.  Returns SPC_ERR_UNSUPPORTED for the shapes/dtypes
  * that do not take prepacked weights (fp32, cout % 32 != 0); those layers take the plain
  * [K^3][cin][cout] weights only.  The WS dataflow accepts prepacked weights for cout in

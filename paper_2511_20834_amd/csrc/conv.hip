@@ -1,16 +1,13 @@
 // Feature computation, Eq. (2): out[i,:] = sum_k F[M[i,k],:] W_k, in the
 // output-stationary and the weight-stationary dataflow (Section 2.2, Section 5.4).
 //
-// fp16 / bf16: the per-offset contraction runs on 32x32x16 MFMA with fp32
-// accumulators.  A wave owns 32-row blocks of output voxels (OS) or of (in,out)
-// pairs (WS).  Gathered feature rows go straight from global memory (L2) into the
-// MFMA A-operand registers: lane l needs 8 consecutive channels of row l%32, which is
-// one 16-byte load, so no LDS round trip is needed for them.  The weight slice W_k is
-// re-laid once per call into B-operand order and staged through LDS, where all waves
-// of the workgroup read it with conflict-free 16-byte loads.
-// OS skips an offset for a 32-row block when no row has a valid entry — outputs are
-// spatially sorted, so emptiness is coherent (the map builder records it per block).
-// fp32 (and channel counts the MFMA tiling does not cover) use plain FMA kernels.
+// The per-offset contraction runs on the matrix cores: 32x32x16 MFMA for fp16 / bf16, 32x32x2 for fp32, with fp32
+// accumulators that stay in registers for all offsets of 32 output voxels.  Gathered feature rows go straight from
+// global memory (L2) into the MFMA A-operand registers: lane l needs 16 consecutive bytes of row l%32.
+// An offset is skipped for a 32-row block when no row has a valid entry: outputs are spatially sorted, so emptiness is
+// coherent (the map builder records it per block).
+// The dataflows differ in where a block's (input row, output row) pairs come from: the |V_q| x K^3 matrix (OS), the
+// filtered per-offset lists (WS), or either by offset (hybrid).
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
 
@@ -27,21 +24,38 @@ typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// One slab = the input channels of one operand register pair: lane l holds LPC consecutive channels (16 bytes) of row
+// (A) or column (B) l%32, starting at LPC * (l/32).
 template <typename T>
 struct Mfma;
 template <>
 struct Mfma<_Float16> {
-  using V8 = half8;
-  __device__ static inline floatx16 mma(V8 a, V8 b, floatx16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
+  using V = half8;
+  static constexpr int LPC = 8;
+  __device__ static inline floatx16 mma(V a, V b, floatx16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
 };
 template <>
 struct Mfma<__bf16> {
-  using V8 = bf16x8;
-  __device__ static inline floatx16 mma(V8 a, V8 b, floatx16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
+  using V = bf16x8;
+  static constexpr int LPC = 8;
+  __device__ static inline floatx16 mma(V a, V b, floatx16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
+};
+// fp32: the 32x32x2 instruction takes one channel per lane, so a slab of 8 channels is four of them (channels j and
+// 4 + j together); products and sums are fp32 as in the vector unit, at the same peak rate, but a gathered row serves
+// 32 output columns from one register.
+template <>
+struct Mfma<float> {
+  using V = floatx4;
+  static constexpr int LPC = 4;
+  __device__ static inline floatx16 mma(V a, V b, floatx16 c) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], b[j], c, 0, 0, 0);
+    return c;
+  }
 };
 
-template <typename T>
-__device__ inline float to_f32(T v) { return static_cast<float>(v); }
 template <typename T>
 __device__ inline T from_f32(float v) { return static_cast<T>(v); }  // round to nearest even
 
@@ -55,9 +69,6 @@ template <int N, typename Fn>
 __device__ inline void static_for(Fn&& f) {
   static_for_impl(std::make_integer_sequence<int, N>{}, f);
 }
-
-constexpr int CONV_THREADS = 256;
-constexpr int CK = 64;  // input channels staged per step
 
 // W [K3][cin][cout]  ->  Wp [K3][cin/16][cout/32][64 lanes][8]: lane l holds channels
 // 16*kk + 8*(l/32) + 0..7 of output column 32*nb + l%32 (the B operand of one MFMA).
@@ -93,45 +104,6 @@ __global__ __launch_bounds__(256) void pad_rows_kernel(const T* __restrict__ F, 
   if (r < n) out[gid] = c < cin ? F[r * ld_in + c] : T(0);
 }
 
-// Shared inner step: stage nkk*NB B-fragments of offset k, channels [c0, c0+16*nkk), then
-// multiply the wave's RB row blocks.  idx[rb] is the gathered input row (or -1) of lane%32.
-template <typename T, int NB, int RB>
-__device__ inline void contract_offset(const T* __restrict__ F, int64_t ld_in, const T* __restrict__ Wp_k, int cin,
-                                       const int (&idx)[RB], bool wave_has, typename Mfma<T>::V8* sB,
-                                       floatx16 (&acc)[RB][NB]) {
-  using V8 = typename Mfma<T>::V8;
-  const int tid = threadIdx.x, lane = tid & 63, lh = lane >> 5;
-  for (int c0 = 0; c0 < cin; c0 += CK) {
-    const int nkk = min(CK, cin - c0) / 16;
-    if (c0 > 0) __syncthreads();  // previous chunk fully consumed
-    const V8* src = reinterpret_cast<const V8*>(Wp_k) + int64_t(c0 / 16) * NB * 64;
-    for (int e = tid; e < nkk * NB * 64; e += CONV_THREADS) sB[e] = src[e];
-    __syncthreads();
-    if (wave_has) {
-      V8 a[RB][CK / 16];
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int kk = 0; kk < CK / 16; ++kk) {
-          V8 v = {};
-          if (kk < nkk && idx[rb] >= 0) v = *reinterpret_cast<const V8*>(F + int64_t(idx[rb]) * ld_in + c0 + kk * 16 + 8 * lh);
-          a[rb][kk] = v;
-        }
-#pragma unroll
-      for (int kk = 0; kk < CK / 16; ++kk) {
-        if (kk < nkk) {
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb) {
-            const V8 b = sB[(kk * NB + nb) * 64 + lane];
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) acc[rb][nb] = Mfma<T>::mma(a[rb][kk], b, acc[rb][nb]);
-          }
-        }
-      }
-    }
-  }
-}
-
 // Output-stationary kernel: waves are autonomous, weights are staged through LDS in phases.
 //
 // A workgroup of WAVES waves walks the weight tensor once, in phases of up to HALF_BYTES.
@@ -158,7 +130,6 @@ __device__ inline void contract_offset(const T* __restrict__ F, int64_t ld_in, c
 // which gather the same feature rows, run on the same XCD and share its L2.
 constexpr int HALF_BYTES = 72 * 1024;  // 9 offsets of 64x64 fp16: one x-slab of a 3x3x3 kernel per phase
 constexpr int KLIST_CAP = 352;  // >= 7^3
-constexpr int WS_MAX_K3 = 343;  // 7^3: the largest kernel the library takes
 __device__ __align__(16) uint32_t g_zero_row[64];  // zero-initialised, never written
 
 constexpr int PHASE_XCD_CHUNK = 16;  // tiles (of two 32-row blocks) per chunk; 4 to 64 measured alike
@@ -186,9 +157,8 @@ __global__ __launch_bounds__(64 * WAVES) void conv_os_phase_kernel(const int32_t
                                                                    const T* __restrict__ F, int64_t ld_in,
                                                                    const T* __restrict__ Wp, T* __restrict__ out,
                                                                    int64_t ld_out, int cin, int relu, int chunks_per_phase,
-                                                                   int n_wg_per_xcd, int nb_total, KMask kmask,
-                                                                   const float* __restrict__ init) {
-  using V8 = typename Mfma<T>::V8;
+                                                                   int n_wg_per_xcd, int nb_total, KMask kmask) {
+  using V8 = typename Mfma<T>::V;
   constexpr int CKS = 16 * NKK;
   constexpr int THREADS = 64 * WAVES;
   constexpr int cout = NB * 32;
@@ -420,9 +390,6 @@ __global__ __launch_bounds__(64 * WAVES) void conv_os_phase_kernel(const int32_t
       const int rows = static_cast<int>(max<int64_t>(0, min<int64_t>(32, n_out - i0)));
       if (rows == 0) continue;
       T* prow = out + (i0 + 4 * lh) * ld_out + lr;
-      // hybrid dataflow: the weight-stationary part of the sum arrives in an fp32 buffer [n_out][cout]
-      const int64_t ld_init = int64_t(nb_total) * 32;
-      const float* irow = init + (i0 + 4 * lh) * ld_init + slab * (NB * 32) + lr;  // used only when init is given
       auto store_all = [&](auto FULL_) {
         constexpr bool FULL = decltype(FULL_)::value;
 #pragma unroll
@@ -432,7 +399,6 @@ __global__ __launch_bounds__(64 * WAVES) void conv_os_phase_kernel(const int32_t
             const int rr = 8 * (r / 4) + (r % 4);  // row = rr + 4 * lh
             if (FULL || rr + 4 * lh < rows) {
               float v = acc[rb][nb][r];
-              if (init) v += irow[rr * ld_init + nb * 32];
               if (relu) v = fmaxf(v, 0.f);
               prow[rr * ld_out + nb * 32] = from_f32<T>(v);
             }
@@ -444,40 +410,76 @@ __global__ __launch_bounds__(64 * WAVES) void conv_os_phase_kernel(const int32_t
   }
 }
 
-// Output-stationary kernel for layers whose weight traffic is small next to the chip's L2
-// bandwidth (few output voxels, or few channels): one workgroup per block of 32 output voxels
-// and slab of NB*32 output channels, and the offsets present in the block are dealt round-robin
-// to the workgroup's four waves (a split of the reduction over k, Eq. (2)).  Nothing is staged
-// through LDS and no barrier sits inside the loop: a wave reads the B fragments of its offsets
-// straight from the prepacked weights (1 KB coalesced per fragment, L2-resident) next to the
-// gathered A rows, D = 2 (offset, 16-channel slab) entries ahead of the MFMA that consumes them.
-// The four partial accumulators meet in LDS and are summed in wave order, so results stay
-// bit-reproducible; the sum leaves LDS transposed, each thread storing consecutive channels of
-// one row.  Compared with the phase kernel this trades redundant weight reads (every block
-// re-reads its offsets' weights) for many more, much shorter dependency chains, which is what
-// the coarse levels of a network need: there a layer has fewer row blocks than the chip has
-// compute units.
+// Kernel for layers whose weight traffic is small next to the chip's L2 bandwidth (few output voxels, or few
+// channels), for fp32, for channel counts and rows that fit no tile, and for all offsets that come from lists: one
+// workgroup per block of 32 output voxels and slab of NB*32 output channels, and the offsets present in the block are
+// dealt round-robin to the workgroup's four waves (a split of the reduction over k, Eq. (2)).  Nothing is staged
+// through LDS and no barrier sits inside the loop: a wave reads the B fragments of its offsets straight from the
+// weights (L2-resident; 1 KB coalesced per fragment) next to the gathered A rows, D = 2 (offset, slab of channels)
+// entries ahead of the MFMA that consumes them.  The four partial accumulators meet in LDS and are summed in wave
+// order, so results are bit-reproducible; the sum leaves LDS transposed, each thread storing consecutive channels of
+// one row.  Compared with the phase kernel this trades redundant weight reads (every block re-reads its offsets'
+// weights) for many more, much shorter dependency chains, which is what the coarse levels of a network need: there a
+// layer has fewer row blocks than the chip has compute units.
+//
+// LISTS: offsets of the weight-stationary lists.  A list is ordered by output row, and the builder left behind where
+// every 32-row block starts in it, so a block's pairs of an offset are one contiguous piece of at most 32 entries; the
+// wave that owns the offset spreads them over the block's 32 rows in LDS.  From there on list and matrix offsets are
+// the same, and the sum over all offsets happens in registers.  (The form this replaces ran over the lists offset by
+// offset and merged with fp32 atomics in L2, which take about 1.2 TB/s, between a clearing and a rounding pass: 120 k
+// voxels, 64->64: 177 us, now 38.)
+//
+// What a wave reads (AM): 16-byte pieces of rows (A_VEC); the same with a channel count that ends inside the last slab
+// (A_RAGGED: pieces past the end come from the zero row); rows that are not 16-byte aligned or end inside a piece, one
+// channel at a time (A_ELEM); four-channel rows (A_QUAD), where a 16-channel slab holds four offsets instead of one
+// offset and twelve zeros.
 constexpr int SPLITK_WAVES = 4;
-constexpr int SPLITK_KL_CAP = 96;  // >= ceil(7^3 / 4) + 1
+constexpr int SPLITK_KL_CAP = 96;  // >= ceil(7^3 / 4) + 4
+enum { A_VEC = 0, A_RAGGED = 1, A_ELEM = 2, A_QUAD = 3 };
+
+struct ListArgs {
+  const int32_t *in, *out;          // pairs, list k at k * stride
+  const int32_t *base;              // [n_blocks + 1][K3]: first entry of list k whose output row is >= 32 * block
+  const int32_t *base_in;           // symmetric half-map: the same by input row
+  int64_t stride;
+  int sym;
+  KMask mask;
+};
+struct SplitkArgs {
+  const int32_t* M;
+  const uint32_t* block_masks;
+  const int* n_out_d;
+  const void *F, *W;
+  void* out;
+  int64_t ld_in, ld_out;
+  int mask_words, n_out_h, K3, cin, cout, relu, nb_total, vec_store;
+  KMask os_mask;
+  ListArgs lists;
+};
+constexpr int splitk_idx_rows(int K3, int AM) { return (K3 + SPLITK_WAVES - 1) / SPLITK_WAVES + (AM == A_QUAD ? 4 : 1); }
 
 // LOOP: the grid was sized from an estimate of the output count and tiles are walked with a grid
 // stride; otherwise one tile per workgroup (the loop costs about 30 registers per lane).
-template <typename T, int NB, int RB, int D, bool LOOP>
-__global__ __launch_bounds__(64 * SPLITK_WAVES) void conv_os_splitk_kernel(const int32_t* __restrict__ M,
-                                                                          const uint32_t* __restrict__ block_masks,
-                                                                          int mask_words, int n_out_h,
-                                                                          const int* __restrict__ n_out_d, int K3,
-                                                                          const T* __restrict__ F, int64_t ld_in,
-                                                                          const T* __restrict__ Wp, T* __restrict__ out,
-                                                                          int64_t ld_out, int cin, int relu, int nb_total,
-                                                                          int vec_store, KMask kmask,
-                                                                          const float* __restrict__ init) {
-  using V8 = typename Mfma<T>::V8;
+// PACKED: weights in MFMA operand order; otherwise the caller's [K^3][cin][cout], read a channel at a time (a fragment is
+// then 32-column rows of W instead of 16 bytes per lane: the same bytes in more instructions, but no re-layout pass).
+template <typename T, int NB, int RB, int D, bool LOOP, int AM, bool PACKED, bool LISTS>
+__global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 2 ? 6 : 8) : 1) void conv_os_splitk_kernel(const SplitkArgs a) {
+  using V = typename Mfma<T>::V;
+  constexpr int LPC = Mfma<T>::LPC, SLAB = 2 * LPC;
+  static_assert(RB == 1 || (AM == A_VEC && !LISTS), "two row blocks: plain layers only");
+  static_assert(AM != A_QUAD || sizeof(T) == 2, "four offsets per slab: 16-bit types");
   extern __shared__ __align__(16) unsigned char smem[];
-  const int n_out = n_out_d ? *n_out_d : n_out_h;
+  const int32_t* __restrict__ M = a.M;
+  const uint32_t* __restrict__ block_masks = a.block_masks;
+  const T* __restrict__ F = static_cast<const T*>(a.F);
+  const T* __restrict__ W = static_cast<const T*>(a.W);
+  T* __restrict__ out = static_cast<T*>(a.out);
+  const int64_t ld_in = a.ld_in, ld_out = a.ld_out;
+  const int K3 = a.K3, cin = a.cin, cout = a.cout, nb_total = a.nb_total;
+  const int n_out = a.n_out_d ? *a.n_out_d : a.n_out_h;
   const int64_t n_blocks = (int64_t(n_out) + 31) >> 5;
   const int slab = blockIdx.y;
-  const int KK = cin / 16;
+  const int KK = (cin + SLAB - 1) / SLAB;
   // tiles of RB blocks; the trip count is uniform per workgroup, so the barriers below are
   // reached by all of its waves or by none
   for (int64_t blk0 = int64_t(blockIdx.x) * RB; blk0 < n_blocks; blk0 += LOOP ? int64_t(gridDim.x) * RB : n_blocks) {
@@ -488,31 +490,68 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES) void conv_os_splitk_kernel(const
   if constexpr (LOOP) asm volatile("" : "+v"(tid));
   const int lane = tid & 63, lr = lane & 31, lh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int idx_rows = (K3 + SPLITK_WAVES - 1) / SPLITK_WAVES + 1;  // per wave, with the all-invalid row at the end
+  const int idx_rows = splitk_idx_rows(K3, AM);  // per wave, with all-invalid rows at the end
   int32_t* sIdx = reinterpret_cast<int32_t*>(smem) + wave * idx_rows * (RB * 32);
-  int16_t* kl = reinterpret_cast<int16_t*>(smem + size_t(SPLITK_WAVES) * idx_rows * (RB * 128)) + wave * SPLITK_KL_CAP;
+  unsigned char* kl_base = smem + size_t(SPLITK_WAVES) * idx_rows * (RB * 128);
+  int16_t* kl = reinterpret_cast<int16_t*>(kl_base) + wave * SPLITK_KL_CAP;
+  // LISTS: where the pairs of this wave's offsets start, and how many there are (-1: from the matrix, -2: row = row)
+  int32_t* s_first = reinterpret_cast<int32_t*>(kl_base + SPLITK_WAVES * SPLITK_KL_CAP * 2) + wave * SPLITK_KL_CAP;
+  int32_t* s_num = s_first + SPLITK_WAVES * SPLITK_KL_CAP;
 
-  // this wave's offsets: those present in the tile (union of the builder's block masks) whose
-  // rank is wave mod 4
+  // this wave's offsets: those present in the tile whose rank is wave mod 4
   int cnt = 0;
-  for (int wd = 0; wd < mask_words; ++wd) {
-    unsigned m = 0;
+  if constexpr (!LISTS) {  // (union of the builder's block masks)
+    for (int wd = 0; wd < a.mask_words; ++wd) {
+      unsigned m = 0;
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-      if (blk0 + rb < n_blocks) m |= block_masks[(blk0 + rb) * mask_words + wd];
-    m = __builtin_amdgcn_readfirstlane(m & kmask.w[wd]);
-    if (lane < 32 && ((m >> lane) & 1u)) {
-      const int rank = cnt + __builtin_popcount(m & ((1u << lane) - 1u));
-      if ((rank & (SPLITK_WAVES - 1)) == wave) kl[rank / SPLITK_WAVES] = static_cast<int16_t>(wd * 32 + lane);
+      for (int rb = 0; rb < RB; ++rb)
+        if (blk0 + rb < n_blocks) m |= block_masks[(blk0 + rb) * a.mask_words + wd];
+      m = __builtin_amdgcn_readfirstlane(m & a.os_mask.w[wd]);
+      if (lane < 32 && ((m >> lane) & 1u)) {
+        const int rank = cnt + __builtin_popcount(m & ((1u << lane) - 1u));
+        if ((rank & (SPLITK_WAVES - 1)) == wave) kl[rank / SPLITK_WAVES] = static_cast<int16_t>(wd * 32 + lane);
+      }
+      cnt += __builtin_popcount(m);
     }
-    cnt += __builtin_popcount(m);
+  } else {
+    const int kc = (K3 - 1) / 2;
+    for (int k0 = 0; k0 < K3; k0 += 64) {
+      const int k = k0 + lane;
+      int first = 0, num = 0;
+      if (k < K3) {
+        if (a.lists.mask.has(k)) {
+          if (a.lists.sym && k == kc) {
+            num = -2;
+          } else {  // second half of a symmetric map: the opposite offset's list with the roles swapped
+            const bool mirror = a.lists.sym && k > kc;
+            const int32_t* tab = (mirror ? a.lists.base_in : a.lists.base) + blk0 * K3 + (mirror ? K3 - 1 - k : k);
+            first = tab[0];
+            num = tab[K3] - first;
+          }
+        } else if (a.os_mask.has(k) && ((block_masks[blk0 * a.mask_words + (k >> 5)] >> (k & 31)) & 1u)) {
+          num = -1;
+        }
+      }
+      const unsigned long long bal = __ballot(num != 0);
+      const int rank = cnt + __builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(bal >> 32),
+                                                       __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(bal), 0));
+      if (num != 0 && (rank & (SPLITK_WAVES - 1)) == wave) {
+        kl[rank / SPLITK_WAVES] = static_cast<int16_t>(k);
+        s_first[rank / SPLITK_WAVES] = first;
+        s_num[rank / SPLITK_WAVES] = num;
+      }
+      cnt += __popcll(bal);
+    }
   }
-  const int n_i = cnt > wave ? (cnt - wave + SPLITK_WAVES - 1) / SPLITK_WAVES : 0;
-  if (lane == 0) kl[n_i] = 0;  // entries past the end read offset 0's weights (never multiplied)
+  const int n_i = __builtin_amdgcn_readfirstlane(cnt > wave ? (cnt - wave + SPLITK_WAVES - 1) / SPLITK_WAVES : 0);
+  // entries past the end read offset 0's weights and all-invalid rows
+  constexpr int TAIL = AM == A_QUAD ? 4 : 1;
+  if (lane < TAIL) kl[n_i + lane] = 0;
+  for (int q = lane; q < TAIL * RB * 32; q += 64) sIdx[n_i * RB * 32 + q] = -1;
   __builtin_amdgcn_wave_barrier();
-  // their map rows (32 input indices per block), eight (offset, block) pairs per pass:
-  // lane -> (pair, 4 rows); blocks past the end of the level count as all-invalid
-  {
+  if constexpr (!LISTS) {
+    // their map rows (32 input indices per block), eight (offset, block) pairs per pass:
+    // lane -> (pair, 4 rows); blocks past the end of the level count as all-invalid
     const int part = lane & 7;
     for (int p = lane >> 3; p < n_i * RB; p += 8) {
       const int i = p / RB, rb = p % RB;
@@ -521,7 +560,39 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES) void conv_os_splitk_kernel(const
         v = *reinterpret_cast<const int4*>(M + ((blk0 + rb) * int64_t(K3) + kl[i]) * 32 + part * 4);
       *reinterpret_cast<int4*>(sIdx + p * 32 + part * 4) = v;
     }
-    for (int q = lane; q < RB * 32; q += 64) sIdx[n_i * RB * 32 + q] = -1;
+  } else {
+    // two offsets per pass (a half-wave each, lane = row or pair), four passes' loads in flight together
+    for (int p0 = lh; p0 < n_i; p0 += 8) {
+      int row[4], val[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int p = p0 + 2 * u;
+        row[u] = -1;
+        val[u] = -1;
+        if (p < n_i) {
+          const int k = kl[p], num = s_num[p];
+          if (num == -1) {
+            row[u] = lr;
+            val[u] = M[(blk0 * K3 + k) * 32 + lr];
+          } else if (num == -2) {
+            row[u] = lr;
+            val[u] = blk0 * 32 + lr < n_out ? static_cast<int>(blk0 * 32) + lr : -1;
+          } else if (lr < num) {
+            const bool mirror = a.lists.sym && k > (K3 - 1) / 2;
+            const int64_t at = (mirror ? K3 - 1 - k : k) * a.lists.stride + s_first[p] + lr;
+            row[u] = (mirror ? a.lists.in : a.lists.out)[at] & 31;
+            val[u] = (mirror ? a.lists.out : a.lists.in)[at];
+          }
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (p0 + 2 * u < n_i) sIdx[(p0 + 2 * u) * 32 + lr] = -1;
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (row[u] >= 0) sIdx[(p0 + 2 * u) * 32 + row[u]] = val[u];
+    }
   }
   __builtin_amdgcn_wave_barrier();
 
@@ -533,47 +604,113 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES) void conv_os_splitk_kernel(const
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[rb][nb][r] = 0.f;
 
-  // entry e = (i-th offset of this wave, 16-channel slab kk), kk fastest
-  const int n_entries = n_i * KK;
-  const T* zero_row = reinterpret_cast<const T*>(g_zero_row) + 8 * lh;
-  const V8* Wv = reinterpret_cast<const V8*>(Wp) + int64_t(slab) * NB * 64 + lane;
-  V8 a[D][RB];
-  V8 b[D][NB];
-  int i_n = 0, kk_n = 0;
-  int idx_n[RB];
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) idx_n[rb] = sIdx[rb * 32 + lr];
-  int k_n = __builtin_amdgcn_readfirstlane(static_cast<int>(kl[0]));
-  auto issue = [&](auto S_) {
-    constexpr int S = decltype(S_)::value;
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      const T* src = idx_n[rb] < 0 ? zero_row : F + int64_t(idx_n[rb]) * ld_in + kk_n * 16 + 8 * lh;
-      a[S][rb] = *reinterpret_cast<const V8*>(src);
-    }
-    const V8* wsrc = Wv + (int64_t(k_n) * KK + kk_n) * nb_total * 64;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) b[S][nb] = wsrc[nb * 64];
-    if (++kk_n == KK) {
-      kk_n = 0;
-      i_n = min(i_n + 1, n_i);
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) idx_n[rb] = sIdx[(i_n * RB + rb) * 32 + lr];
-      k_n = __builtin_amdgcn_readfirstlane(static_cast<int>(kl[i_n]));
-    }
-  };
-  static_for<D>([&](auto S_) { issue(S_); });
-  for (int e0 = 0; e0 < n_entries; e0 += D) {
-    static_for<D>([&](auto S_) {
+  const T* zero_row = reinterpret_cast<const T*>(g_zero_row) + LPC * lh;
+  V av[D][RB];
+  V bv[D][NB];
+  if constexpr (AM == A_QUAD) {
+    // entry e = offsets 4e .. 4e+3 of this wave: lanes of the lower half hold four channels of each of the first two,
+    // lanes of the upper half of the last two
+    using V4 = T __attribute__((ext_vector_type(4)));
+    const int n_entries = (n_i + 3) / 4;
+    const T* zero4 = reinterpret_cast<const T*>(g_zero_row);
+    int e_n = 0;
+    auto issue = [&](auto S_) {
       constexpr int S = decltype(S_)::value;
-      if (e0 + S < n_entries) {
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
+      for (int h = 0; h < 2; ++h) {
+        const int q = min(4 * e_n + 2 * lh + h, n_i);  // past the end: offset 0, no rows
+        const int idx = sIdx[q * 32 + lr];
+        const V4 f = *reinterpret_cast<const V4*>(idx < 0 ? zero4 : F + int64_t(idx) * ld_in);
+        const int k = kl[q];
 #pragma unroll
-          for (int rb = 0; rb < RB; ++rb) acc[rb][nb] = Mfma<T>::mma(a[S][rb], b[S][nb], acc[rb][nb]);
+        for (int j = 0; j < 4; ++j) av[S][0][4 * h + j] = f[j];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          if constexpr (PACKED) {
+            const V4 w = *reinterpret_cast<const V4*>(W + ((int64_t(k) * nb_total + slab * NB + nb) * 64 + lr) * 8);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) bv[S][nb][4 * h + j] = w[j];
+          } else {
+            const T* w = W + int64_t(k) * 4 * cout + min((slab * NB + nb) * 32 + lr, cout - 1);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) bv[S][nb][4 * h + j] = w[j * cout];
+          }
+        }
       }
-      issue(S_);
-    });
+      ++e_n;
+    };
+    static_for<D>([&](auto S_) { issue(S_); });
+    for (int e0 = 0; e0 < n_entries; e0 += D) {
+      static_for<D>([&](auto S_) {
+        constexpr int S = decltype(S_)::value;
+        if (e0 + S < n_entries) {
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) acc[0][nb] = Mfma<T>::mma(av[S][0], bv[S][nb], acc[0][nb]);
+        }
+        issue(S_);
+      });
+    }
+  } else {
+    // entry e = (i-th offset of this wave, slab kk of channels), kk fastest
+    const int n_entries = n_i * KK;
+    const V* Wv = reinterpret_cast<const V*>(W) + int64_t(slab) * NB * 64 + lane;  // PACKED
+    int i_n = 0, kk_n = 0;
+    int idx_n[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) idx_n[rb] = sIdx[rb * 32 + lr];
+    int k_n = __builtin_amdgcn_readfirstlane(static_cast<int>(kl[0]));
+    auto issue = [&](auto S_) {
+      constexpr int S = decltype(S_)::value;
+      const int c0 = kk_n * SLAB + LPC * lh;  // this lane's first channel
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        if constexpr (AM == A_ELEM) {
+          const T* src = F + int64_t(idx_n[rb]) * ld_in + c0;
+#pragma unroll
+          for (int j = 0; j < LPC; ++j) av[S][rb][j] = *(idx_n[rb] < 0 || c0 + j >= cin ? zero_row : src + j);
+        } else {
+          const bool none = idx_n[rb] < 0 || (AM == A_RAGGED && c0 >= cin);
+          av[S][rb] = *reinterpret_cast<const V*>(none ? zero_row : F + int64_t(idx_n[rb]) * ld_in + c0);
+        }
+      }
+      if constexpr (PACKED) {
+        const V* wsrc = Wv + (int64_t(k_n) * KK + kk_n) * nb_total * 64;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) bv[S][nb] = wsrc[nb * 64];
+      } else {
+        // channels past the end multiply zeros: the last one's weights stand in for theirs
+        const T* wk = W + (int64_t(k_n) * cin + (AM == A_VEC ? kk_n * SLAB : 0)) * cout;  // uniform
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          const unsigned col = min((slab * NB + nb) * 32 + lr, cout - 1);  // (columns past the end are not stored)
+#pragma unroll
+          for (int j = 0; j < LPC; ++j) {
+            if constexpr (AM == A_VEC) bv[S][nb][j] = (wk + j * cout)[unsigned(LPC * lh * cout) + col];
+            else bv[S][nb][j] = wk[unsigned(min(c0 + j, cin - 1) * cout) + col];
+          }
+        }
+      }
+      if (++kk_n == KK) {
+        kk_n = 0;
+        i_n = min(i_n + 1, n_i);
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) idx_n[rb] = sIdx[(i_n * RB + rb) * 32 + lr];
+        k_n = __builtin_amdgcn_readfirstlane(static_cast<int>(kl[i_n]));
+      }
+    };
+    static_for<D>([&](auto S_) { issue(S_); });
+    for (int e0 = 0; e0 < n_entries; e0 += D) {
+      static_for<D>([&](auto S_) {
+        constexpr int S = decltype(S_)::value;
+        if (e0 + S < n_entries) {
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) acc[rb][nb] = Mfma<T>::mma(av[S][rb], bv[S][nb], acc[rb][nb]);
+        }
+        issue(S_);
+      });
+    }
   }
 
   // The four partial sums meet in one LDS tile (the index area is dead by now): the waves add
@@ -610,217 +747,37 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES) void conv_os_splitk_kernel(const
   const int row = tid >> 3, c0 = (tid & 7) * EPT;
   const int nb = c0 >> 5, cc = c0 & 31;
   const int q = row >> 3, h = (row & 7) >> 2, rr = row & 3;
+  const int oc = slab * (NB * 32) + c0;  // first output channel
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     const int64_t i = (blk0 + rb) * 32 + row;
     const float* p = red + ((((rb * NB + nb) * 4 + q) * 64) + h * 32 + cc) * 4 + rr;
-    T o[EPT];
-    // hybrid dataflow: the weight-stationary part of the sum arrives in an fp32 buffer [n_out][cout]
-    const float* ip = (init && i < n_out) ? init + i * (nb_total * 32) + slab * (NB * 32) + c0 : nullptr;
+    __align__(16) T o[EPT];
 #pragma unroll
     for (int j = 0; j < EPT; ++j) {
-      float v = p[4 * j];
-      if (ip) v += ip[j];
-      o[j] = from_f32<T>(relu ? fmaxf(v, 0.f) : v);
+      const float v = p[4 * j];
+      o[j] = from_f32<T>(a.relu ? fmaxf(v, 0.f) : v);
     }
-    if (i < n_out) {
-      T* dst = out + i * ld_out + slab * (NB * 32) + c0;
-      if (vec_store) {
-        if constexpr (EPT == 8) *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(o);
-        else *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<const uint2*>(o);
+    if (i < n_out && oc < cout) {
+      T* dst = out + i * ld_out + oc;
+      if (a.vec_store) {  // (cout is a multiple of EPT then)
+        if constexpr (EPT * sizeof(T) == 32) {
+          reinterpret_cast<uint4*>(dst)[0] = reinterpret_cast<const uint4*>(o)[0];
+          reinterpret_cast<uint4*>(dst)[1] = reinterpret_cast<const uint4*>(o)[1];
+        } else if constexpr (EPT * sizeof(T) == 16) {
+          *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(o);
+        } else {
+          *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<const uint2*>(o);
+        }
       } else {
 #pragma unroll
-        for (int j = 0; j < EPT; ++j) dst[j] = o[j];
+        for (int j = 0; j < EPT; ++j)
+          if (oc + j < cout) dst[j] = o[j];
       }
     }
   }
   if constexpr (LOOP) __syncthreads();  // the LDS tile is reused as the next tile's index area
   }
-}
-
-// Weight-stationary: workgroup = one offset k and 4 x RB blocks of 32 (in,out) pairs;
-// partial sums are merged into an fp32 buffer with hardware float atomics.  On a symmetric
-// half-map every pair block is used twice: as stored with W_k, and with input and output
-// swapped with the weights of the opposite offset (Section 5.4).
-template <typename T, int NB, int RB>
-__global__ __launch_bounds__(CONV_THREADS) void conv_ws_mfma_kernel(const int32_t* __restrict__ ws_in,
-                                                                    const int32_t* __restrict__ ws_out,
-                                                                    const int32_t* __restrict__ nnz, int64_t ws_stride,
-                                                                    const T* __restrict__ F, int64_t ld_in,
-                                                                    const T* __restrict__ Wp, float* __restrict__ accum,
-                                                                    int cin, KMask kmask, int sym, int K3, int n_out_h,
-                                                                    const int* __restrict__ n_out_d) {
-  using V8 = typename Mfma<T>::V8;
-  constexpr int WROWS = 32 * RB, TROWS = 4 * WROWS;
-  extern __shared__ __align__(16) unsigned char smem[];
-  V8* sB = reinterpret_cast<V8*>(smem);
-  __shared__ int s_out[TROWS], s_in[TROWS];
-  __shared__ int s_first[WS_MAX_K3 + 1];  // first work item of every offset; [n_k] = number of items
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 31, lh = lane >> 5;
-  // The list lengths only exist on the device, so the grid cannot be cut to the work: a fixed number of
-  // workgroups walks the items (offset k, chunk of TROWS pairs) with a grid stride.  Every workgroup
-  // numbers the items itself: chunks per offset, scanned by wave 0.
-  // symmetric half-map: lists exist for k < centre; the centre offset pairs every voxel with itself
-  const int kc = (K3 - 1) / 2;
-  const int n_k = sym ? kc + 1 : K3;
-  const int n_out = n_out_d ? *n_out_d : n_out_h;
-  if (wave == 0) {
-    int carry = 0;
-    for (int k0 = 0; k0 < n_k; k0 += 64) {
-      const int k = k0 + lane;
-      int c = 0;
-      if (k < n_k && kmask.has(k)) c = ((sym && k == kc ? n_out : nnz[k]) + TROWS - 1) / TROWS;
-      int x = c;
-      for (int d = 1; d < 64; d <<= 1) {
-        const int y = __shfl_up(x, d, 64);
-        if (lane >= d) x += y;
-      }
-      if (k < n_k) s_first[k] = carry + x - c;
-      carry += __shfl(x, 63, 64);
-    }
-    if (lane == 0) s_first[n_k] = carry;
-  }
-  __syncthreads();
-  const int n_items = s_first[n_k];
-  const int cout = NB * 32;
-  for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
-  // last offset whose first item is <= item (offsets without items share their successor's first item)
-  int k = 0;
-  for (int bit = 256; bit > 0; bit >>= 1)
-    if (k + bit < n_k && s_first[k + bit] <= item) k += bit;
-  const bool centre = sym && k == kc;
-  const int cnt = centre ? n_out : nnz[k];
-  const int p0 = (item - s_first[k]) * TROWS;
-  const int rows = min(TROWS, cnt - p0);
-  const int32_t* li = ws_in + int64_t(k) * ws_stride + p0;
-  const int32_t* lo = ws_out + int64_t(k) * ws_stride + p0;
-  __syncthreads();  // everybody is done with the item before (its index lists and its weights)
-  for (int r = tid; r < TROWS; r += CONV_THREADS) {
-    s_out[r] = r < rows ? (centre ? p0 + r : lo[r]) : -1;
-    s_in[r] = r < rows ? (centre ? p0 + r : li[r]) : -1;
-  }
-  __syncthreads();
-  // pass 0: F[in] W_k -> out.  pass 1 (symmetric maps, not the centre): F[out] W_{K^3-1-k} -> in
-  const int passes = (sym && !centre) ? 2 : 1;
-  for (int pass = 0; pass < passes; ++pass) {
-    const int* gat = pass == 0 ? s_in : s_out;
-    const int* sca = pass == 0 ? s_out : s_in;
-    const int kw = pass == 0 ? k : K3 - 1 - k;
-    floatx16 acc[RB][NB];
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[rb][nb][r] = 0.f;
-    int idx[RB];
-    bool has = false;
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      idx[rb] = gat[wave * WROWS + rb * 32 + lr];
-      has |= idx[rb] >= 0;
-    }
-    const bool wave_has = __ballot(has) != 0ull;
-    if (pass > 0) __syncthreads();  // everybody is done with the weights of the pass before
-    contract_offset<T, NB, RB>(F, ld_in, Wp + int64_t(kw) * cin * cout, cin, idx, wave_has, sB, acc);
-    if (!wave_has) continue;
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = wave * WROWS + rb * 32 + 8 * (r / 4) + 4 * lh + (r % 4);
-        const int o = sca[row];
-        if (o >= 0) {
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb) unsafeAtomicAdd(accum + int64_t(o) * cout + nb * 32 + lr, acc[rb][nb][r]);
-        }
-      }
-  }
-  }  // items
-}
-
-// ---------------------------------------------------------------- plain FMA kernels
-template <typename T>
-__global__ __launch_bounds__(256) void conv_os_simple_kernel(const int32_t* __restrict__ M, int n_out_h,
-                                                             const int* __restrict__ n_out_d, int K3,
-                                                             const T* __restrict__ F, int64_t ld_in,
-                                                             const T* __restrict__ W, T* __restrict__ out,
-                                                             int64_t ld_out, int cin, int cout, int relu, KMask kmask,
-                                                             const float* __restrict__ init) {
-  const int n_out = n_out_d ? *n_out_d : n_out_h;
-  const int64_t gid = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-  const int64_t i = gid / cout;
-  const int co = static_cast<int>(gid - i * cout);
-  if (i >= n_out) return;
-  float acc = init ? init[gid] : 0.f;
-  // map entries are fetched eight offsets at a time, so that their loads (and then the feature
-  // rows') are in flight together instead of one dependent chain per offset
-  const int32_t* Mi = M + (i >> 5) * int64_t(K3) * 32 + (i & 31);
-  for (int k0 = 0; k0 < K3; k0 += 8) {
-    int j[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int k = k0 + u;
-      j[u] = (k < K3 && kmask.has(k)) ? Mi[k * 32] : -1;
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      if (j[u] < 0) continue;
-      const T* f = F + int64_t(j[u]) * ld_in;
-      const T* w = W + int64_t(k0 + u) * cin * cout + co;
-#pragma unroll 8
-      for (int ci = 0; ci < cin; ++ci) acc = fmaf(to_f32(f[ci]), to_f32(w[int64_t(ci) * cout]), acc);
-    }
-  }
-  if (relu) acc = fmaxf(acc, 0.f);
-  out[i * ld_out + co] = from_f32<T>(acc);
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void conv_ws_simple_kernel(const int32_t* __restrict__ ws_in,
-                                                             const int32_t* __restrict__ ws_out,
-                                                             const int32_t* __restrict__ nnz, int64_t ws_stride,
-                                                             const T* __restrict__ F, int64_t ld_in,
-                                                             const T* __restrict__ W, float* __restrict__ accum,
-                                                             int cin, int cout, KMask kmask, int sym, int K3, int n_out_h,
-                                                             const int* __restrict__ n_out_d) {
-  const int k = blockIdx.y;
-  if (!kmask.has(k)) return;
-  const int kc = (K3 - 1) / 2;
-  const bool centre = sym && k == kc;
-  const int64_t gid = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-  const int64_t p = gid / cout;
-  const int co = static_cast<int>(gid - p * cout);
-  if (p >= (centre ? (n_out_d ? *n_out_d : n_out_h) : nnz[k])) return;
-  const int j = centre ? static_cast<int>(p) : ws_in[int64_t(k) * ws_stride + p];
-  const int o = centre ? static_cast<int>(p) : ws_out[int64_t(k) * ws_stride + p];
-  const int passes = (sym && !centre) ? 2 : 1;  // second pass: the opposite offset, roles swapped
-  for (int pass = 0; pass < passes; ++pass) {
-    const T* f = F + int64_t(pass == 0 ? j : o) * ld_in;
-    const T* w = W + int64_t(pass == 0 ? k : K3 - 1 - k) * cin * cout + co;
-    float acc = 0.f;
-    for (int ci = 0; ci < cin; ++ci) acc = fmaf(to_f32(f[ci]), to_f32(w[int64_t(ci) * cout]), acc);
-    unsafeAtomicAdd(accum + int64_t(pass == 0 ? o : j) * cout + co, acc);
-  }
-}
-
-__global__ __launch_bounds__(256) void zero_f32_kernel(float4* __restrict__ p, int64_t n4) {
-  const int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-  if (i < n4) p[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void finalize_kernel(const float* __restrict__ accum, int n_out_h,
-                                                       const int* __restrict__ n_out_d, int cout, T* __restrict__ out,
-                                                       int64_t ld_out, int relu) {
-  const int n_out = n_out_d ? *n_out_d : n_out_h;
-  const int64_t gid = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-  const int64_t i = gid / cout;
-  const int co = static_cast<int>(gid - i * cout);
-  if (i >= n_out) return;
-  float v = accum[gid];
-  if (relu) v = fmaxf(v, 0.f);
-  out[i * ld_out + co] = from_f32<T>(v);
 }
 
 // ---------------------------------------------------------------- dispatch
@@ -832,7 +789,7 @@ struct ConvArgs {
   const void* W;
   void* out;
   int64_t ld_out;
-  int cin, cout, relu, dataflow;
+  int cin, cout, relu;
   int os_variant;  // 0: chosen from the layer's size, 1: phase kernel, 2: split-k kernel
   int splitk_rb;   // 0: chosen from the layer's size, else row blocks per workgroup (1, 2)
   int n_out_h;
@@ -848,7 +805,7 @@ struct ConvArgs {
 // odd multiple of 32).  Small slabs keep the accumulators of two row blocks in registers and give
 // the coarse, wide layers of a network enough workgroups to fill the chip.
 template <typename T, int NB>
-static void launch_os_mfma(const ConvArgs& a, const T* Wp, const float* init) {
+static void launch_os_mfma(const ConvArgs& a, const T* Wp) {
   // 64-column slabs: sixteen waves with one row block each (twice the gathers in flight per CU; measured
   // 8-23 % faster than eight waves with two blocks on 120 k and 240 k voxels, 64..256 channels);
   // 32-column slabs: eight waves with two blocks (each weight fragment read from LDS serves both)
@@ -872,69 +829,105 @@ static void launch_os_mfma(const ConvArgs& a, const T* Wp, const float* init) {
     hipLaunchKernelGGL((conv_os_phase_kernel<T, NB, RBK, WAVES, NKK, DEPTH>), dim3(per_xcd * 8, n_slabs), dim3(64 * WAVES), lds,
                        a.s, a.m->os_map, a.m->block_masks, a.m->mask_words, a.n_out_h, a.n_out_d, a.m->K3,
                        static_cast<const T*>(a.F), a.ld_in, Wp, static_cast<T*>(a.out), a.ld_out, a.cin, a.relu, cpp, per_xcd,
-                       nb_total, a.os_mask, init);
+                       nb_total, a.os_mask);
   };
   if (a.cin % 64 == 0) go(std::integral_constant<int, 4>{});
   else if (a.cin % 32 == 0) go(std::integral_constant<int, 2>{});
   else go(std::integral_constant<int, 1>{});
 }
 
-static size_t splitk_lds_bytes(int K3, int NB, int RB) {
-  const int idx_rows = (K3 + SPLITK_WAVES - 1) / SPLITK_WAVES + 1;
-  return std::max(size_t(SPLITK_WAVES) * idx_rows * RB * 128 + size_t(SPLITK_WAVES) * SPLITK_KL_CAP * 2,
-                  size_t(RB) * NB * 16 * 64 * 4);
+static size_t splitk_lds_bytes(int K3, int NB, int RB, int AM, bool lists) {
+  const size_t idx = size_t(SPLITK_WAVES) * splitk_idx_rows(K3, AM) * RB * 128 + size_t(SPLITK_WAVES) * SPLITK_KL_CAP * (lists ? 10 : 2);
+  return std::max(idx, size_t(RB) * NB * 16 * 64 * 4);
 }
 
-template <typename T, int NB, int RB>
-static void launch_os_splitk(const ConvArgs& a, const T* Wp, const float* init) {
+template <typename T, int NB, int RB, int AM, bool PACKED, bool LISTS>
+static void launch_splitk(const ConvArgs& a, const void* W) {
   // entries in flight per wave: two.  Deeper rings cost the registers that hold more waves per SIMD, and the
   // waves hide more latency than the ring does (25 layers of a UNet on 120 k voxels, all on this kernel: 403 us
   // summed with 6-12 entries, 352 us with two or three, 391 us with one)
   constexpr int D = 2;
-  const int nb_total = a.cout / 32, n_slabs = nb_total / NB;
+  SplitkArgs k{};
+  k.M = a.m->os_map;
+  k.block_masks = a.m->block_masks;
+  k.n_out_d = a.n_out_d;
+  k.F = a.F;
+  k.W = W;
+  k.out = a.out;
+  k.ld_in = a.ld_in;
+  k.ld_out = a.ld_out;
+  k.mask_words = a.m->mask_words;
+  k.n_out_h = a.n_out_h;
+  k.K3 = a.m->K3;
+  k.cin = a.cin;
+  k.cout = a.cout;
+  k.relu = a.relu;
+  k.nb_total = (a.cout + 31) / 32;
+  k.os_mask = a.os_mask;
+  constexpr int EPT = NB * 4;
+  constexpr int store = EPT * sizeof(T) < 16 ? EPT * sizeof(T) : 16;  // bytes per store
+  k.vec_store = a.cout % EPT == 0 && a.ld_out * sizeof(T) % store == 0 && reinterpret_cast<uintptr_t>(a.out) % store == 0;
+  if (LISTS) k.lists = ListArgs{a.m->ws_in, a.m->ws_out, a.m->list_base, a.m->list_base_in, a.m->ws_stride, a.m->sym ? 1 : 0, a.ws_mask};
   // an estimated output count sizes the grid of the variant that walks tiles with a grid stride
   const bool loop = a.rows_sel != a.rows_cap;
   const int64_t n_blocks = std::max<int64_t>((a.rows_sel + 31) / 32, 1);
-  const size_t lds = splitk_lds_bytes(a.m->K3, NB, RB);
+  const size_t lds = splitk_lds_bytes(a.m->K3, NB, RB, AM, LISTS);
   // once per instantiation: both variants may use all of a CU's LDS (large kernels need more than the default 64 KB)
   static const hipError_t attr = [] {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_os_splitk_kernel<T, NB, RB, D, false>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_os_splitk_kernel<T, NB, RB, D, false, AM, PACKED, LISTS>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    const hipError_t f = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_os_splitk_kernel<T, NB, RB, D, true>),
+    const hipError_t f = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_os_splitk_kernel<T, NB, RB, D, true, AM, PACKED, LISTS>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     return e != hipSuccess ? e : f;
   }();
   (void)attr;
-  constexpr int EPT = NB * 4;
-  T* out = static_cast<T*>(a.out);
-  const int vec = a.ld_out % EPT == 0 && reinterpret_cast<uintptr_t>(out) % (EPT * sizeof(T)) == 0;
-  const dim3 grid(static_cast<unsigned>((n_blocks + RB - 1) / RB), n_slabs);
+  const dim3 grid(static_cast<unsigned>((n_blocks + RB - 1) / RB), k.nb_total / NB);
   if (loop)
-    hipLaunchKernelGGL((conv_os_splitk_kernel<T, NB, RB, D, true>), grid, dim3(64 * SPLITK_WAVES), lds, a.s, a.m->os_map,
-                       a.m->block_masks, a.m->mask_words, a.n_out_h, a.n_out_d, a.m->K3, static_cast<const T*>(a.F), a.ld_in, Wp,
-                       out, a.ld_out, a.cin, a.relu, nb_total, vec, a.os_mask, init);
+    hipLaunchKernelGGL((conv_os_splitk_kernel<T, NB, RB, D, true, AM, PACKED, LISTS>), grid, dim3(64 * SPLITK_WAVES), lds, a.s, k);
   else
-    hipLaunchKernelGGL((conv_os_splitk_kernel<T, NB, RB, D, false>), grid, dim3(64 * SPLITK_WAVES), lds, a.s, a.m->os_map,
-                       a.m->block_masks, a.m->mask_words, a.n_out_h, a.n_out_d, a.m->K3, static_cast<const T*>(a.F), a.ld_in, Wp,
-                       out, a.ld_out, a.cin, a.relu, nb_total, vec, a.os_mask, init);
+    hipLaunchKernelGGL((conv_os_splitk_kernel<T, NB, RB, D, false, AM, PACKED, LISTS>), grid, dim3(64 * SPLITK_WAVES), lds, a.s, k);
 }
 
-// Row blocks per workgroup of the split-k kernel: more blocks share each weight fragment read
-// (less L2 traffic) but leave fewer workgroups and cost registers; one block measured faster than two
-// at every size (120 k voxels 64->64: 37.4 vs 39.1 us; 240 k voxels 5x5x5 32->32: 37.7 vs 47.7), so two
-// is only taken on request.
-static int splitk_rb(const ConvArgs& a, int NB) {
-  int rb = a.splitk_rb ? a.splitk_rb : 1;
-  while (rb > 1 && splitk_lds_bytes(a.m->K3, NB, rb) > 80 * 1024) rb >>= 1;
-  return rb;
-}
-
-template <typename T, int NB>
-static void launch_os_splitk_any(const ConvArgs& a, const T* Wp, const float* init) {
-  switch (splitk_rb(a, NB)) {
-    case 2: launch_os_splitk<T, NB, 2>(a, Wp, init); break;
-    default: launch_os_splitk<T, NB, 1>(a, Wp, init); break;
-  }
+// Split-k kernel in the form that the layer's rows, weights and offsets need.
+template <typename T>
+static void launch_os_splitk(const ConvArgs& a) {
+  constexpr int LPC = Mfma<T>::LPC;
+  using Yes = std::true_type;
+  using No = std::false_type;
+  const bool aligned = a.ld_in % LPC == 0 && reinterpret_cast<uintptr_t>(a.F) % 16 == 0;
+  const bool quad = sizeof(T) == 2 && a.cin == 4 && a.ld_in % 4 == 0 && reinterpret_cast<uintptr_t>(a.F) % 8 == 0;
+  auto columns = [&](auto NB_) {
+    constexpr int NB = decltype(NB_)::value;
+    auto rows = [&](auto PACKED_, auto LISTS_) {
+      constexpr bool PACKED = decltype(PACKED_)::value, LISTS = decltype(LISTS_)::value;
+      if (quad) {
+        if constexpr (sizeof(T) == 2) launch_splitk<T, NB, 1, A_QUAD, PACKED, LISTS>(a, a.W);
+      } else if (!aligned || a.cin % LPC != 0) {
+        launch_splitk<T, NB, 1, A_ELEM, PACKED, LISTS>(a, a.W);
+      } else if (a.cin % (2 * LPC) != 0) {
+        launch_splitk<T, NB, 1, A_RAGGED, PACKED, LISTS>(a, a.W);
+      } else {
+        // Row blocks per workgroup: two blocks share each weight fragment read (less L2 traffic) but leave fewer
+        // workgroups and cost registers; one measured faster at every size (120 k voxels 64->64: 37.4 vs 39.1 us; 240 k
+        // voxels 5x5x5 32->32: 37.7 vs 47.7), so two is only taken on request.
+        if constexpr (PACKED && !LISTS) {
+          if (a.splitk_rb == 2 && splitk_lds_bytes(a.m->K3, NB, 2, A_VEC, false) <= 80 * 1024) {
+            launch_splitk<T, NB, 2, A_VEC, true, false>(a, a.W);
+            return;
+          }
+        }
+        launch_splitk<T, NB, 1, A_VEC, PACKED, LISTS>(a, a.W);
+      }
+    };
+    if constexpr (sizeof(T) == 2) {
+      if (a.packed) {
+        a.any_ws ? rows(Yes{}, Yes{}) : rows(Yes{}, No{});
+        return;
+      }
+    }
+    a.any_ws ? rows(No{}, Yes{}) : rows(No{}, No{});
+  };
+  ((a.cout + 31) / 32) % 2 == 0 ? columns(std::integral_constant<int, 2>{}) : columns(std::integral_constant<int, 1>{});
 }
 
 // Measured crossover on MI355X (3x3x3 layers, 32..256 channels, 18 k / 49 k / 120 k voxels).  The phase
@@ -955,128 +948,67 @@ static bool prefer_splitk(const ConvArgs& a) {
   return wgs * a.cin < 7000;
 }
 
-template <typename T, int NB, int RB>
-static void launch_ws_mfma(const ConvArgs& a, const T* Wp, float* accum) {
-  constexpr int TROWS = 128 * RB;
-  const size_t lds = size_t(CK / 16) * NB * 64 * 16;
-  // at most this many items exist (every offset's list holds at most one pair per output row); the grid stops
-  // at a few workgroups per CU and strides
-  const int gy = a.m->sym ? (a.m->K3 - 1) / 2 + 1 : a.m->K3;  // a symmetric map is walked up to the centre offset
-  const int64_t max_items = ((a.rows_cap + TROWS - 1) / TROWS) * gy;
-  const int gx = static_cast<int>(std::min<int64_t>(max_items, 2048));
-  hipLaunchKernelGGL((conv_ws_mfma_kernel<T, NB, RB>), dim3(gx), dim3(CONV_THREADS), lds, a.s, a.m->ws_in, a.m->ws_out,
-                     a.m->nnz_dev, a.m->ws_stride, static_cast<const T*>(a.F), a.ld_in, Wp, accum, a.cin, a.ws_mask,
-                     a.m->sym ? 1 : 0, a.m->K3, a.n_out_h, a.n_out_d);
-}
-
-// Shapes the MFMA kernels run (16-bit types): input channels a multiple of 16 (smaller or ragged
-// counts are zero-padded by the caller below), output channels a multiple of 32 for the OS
-// part and one of 32/64/128/256 for the WS part.
-static bool mfma_shape(int cin, int cout, bool any_ws) {
-  if (cin % 16 != 0 || cout % 32 != 0) return false;
+// Shapes that take prepacked weights (16-bit types): any input channels (padded to a multiple of 16), output channels a
+// multiple of 32 and, with a weight-stationary part, one of 32/64/128/256.
+static bool packed_shape(int cout, bool any_ws) {
+  if (cout % 32 != 0) return false;
   return !any_ws || cout == 32 || cout == 64 || cout == 128 || cout == 256;
 }
 
-// The weight-stationary part (if any) accumulates into an fp32 buffer first; the output-stationary
-// part (if any) then starts from that buffer and writes the layer's output, otherwise a small
-// kernel rounds the buffer.
+// The phase kernel on rows and weights as it wants them: ragged input channel counts and unaligned rows go through a
+// zero-padded copy of the features, weights that are not prepacked are re-laid.
 template <typename T>
-static int conv_typed(const ConvArgs& a0, bool allow_mfma) {
-  ConvArgs a = a0;
+static int conv_phase(ConvArgs a) {
   const int K3 = a.m->K3;
-  const int64_t out_elems = a.rows_cap * a.cout;
-  const bool aligned = a.ld_in % 8 == 0 && reinterpret_cast<uintptr_t>(a.F) % 16 == 0;
   const int cin_pad = (a.cin + 15) / 16 * 16;
-  if (a.packed && !(allow_mfma && mfma_shape(cin_pad, a.cout, a.any_ws)))
-    return set_error(SPC_ERR_ARG, "packed weights given for a shape the MFMA kernels do not run");
-  if (a.rows_cap <= 0) return SPC_OK;
-  // ragged input channel counts and unaligned rows go through a zero-padded copy of the features
-  // (prepacked weights already hold zeros for the padding channels)
-  const bool repack_rows = cin_pad != a.cin || !aligned;
-  const bool use_mfma = allow_mfma && mfma_shape(cin_pad, a.cout, a.any_ws);
-  float* accum = nullptr;
-  if (a.any_ws) {
-    accum = static_cast<float*>(pool_alloc(std::max<size_t>(size_t(out_elems) * 4 + 16, 256), a.s));
-    if (!accum) return SPC_ERR_NOMEM;
-    const int64_t n4 = (out_elems + 3) / 4;
-    hipLaunchKernelGGL(zero_f32_kernel, dim3((n4 + 255) / 256), dim3(256), 0, a.s, reinterpret_cast<float4*>(accum), n4);
+  const bool aligned = a.ld_in % 8 == 0 && reinterpret_cast<uintptr_t>(a.F) % 16 == 0;
+  T *Fpad = nullptr, *Wtmp = nullptr;
+  if (cin_pad != a.cin || !aligned) {
+    const Level* il = a.m->in_level;
+    const int64_t rows_in = il->n_host < 0 ? il->cap : il->n_host;
+    Fpad = static_cast<T*>(pool_alloc(std::max<size_t>(size_t(rows_in) * cin_pad * sizeof(T), 256), a.s));
+    if (!Fpad) return SPC_ERR_NOMEM;
+    const int64_t total = rows_in * cin_pad;
+    if (total > 0)
+      hipLaunchKernelGGL(pad_rows_kernel<T>, dim3((total + 255) / 256), dim3(256), 0, a.s, static_cast<const T*>(a.F), a.ld_in,
+                         static_cast<int>(il->n_host < 0 ? 0 : il->n_host), il->n_host < 0 ? il->n_dev : nullptr, a.cin, cin_pad, Fpad);
+    a.F = Fpad;
+    a.ld_in = cin_pad;
   }
-  const float* init = a.any_os ? accum : nullptr;  // what the OS part starts from
-  int rc = SPC_OK;
-  if constexpr (!std::is_same<T, float>::value) {
-    if (use_mfma) {
-      T* Fpad = nullptr;
-      if (repack_rows) {
-        const Level* il = a.m->in_level;
-        const int64_t rows_in = il->n_host < 0 ? il->cap : il->n_host;
-        Fpad = static_cast<T*>(pool_alloc(std::max<size_t>(size_t(rows_in) * cin_pad * sizeof(T), 256), a.s));
-        if (!Fpad) {
-          pool_free(accum, a.s);
-          return SPC_ERR_NOMEM;
-        }
-        const int64_t total = rows_in * cin_pad;
-        if (total > 0)
-          hipLaunchKernelGGL(pad_rows_kernel<T>, dim3((total + 255) / 256), dim3(256), 0, a.s, static_cast<const T*>(a.F), a.ld_in,
-                             static_cast<int>(il->n_host < 0 ? 0 : il->n_host), il->n_host < 0 ? il->n_dev : nullptr, a.cin, cin_pad,
-                             Fpad);
-        a.F = Fpad;
-        a.ld_in = cin_pad;
-      }
-      const T* Wp = static_cast<const T*>(a.W);
-      T* Wtmp = nullptr;
-      if (!a.packed) {
-        Wtmp = static_cast<T*>(pool_alloc(size_t(K3) * cin_pad * a.cout * sizeof(T), a.s));
-        if (!Wtmp) {
-          pool_free(accum, a.s);
-          pool_free(Fpad, a.s);
-          return SPC_ERR_NOMEM;
-        }
-        const int64_t total = int64_t(K3) * (cin_pad / 16) * (a.cout / 32) * 64;
-        hipLaunchKernelGGL(prepack_weights_kernel<T>, dim3((total + 255) / 256), dim3(256), 0, a.s, static_cast<const T*>(a.W),
-                           Wtmp, K3, a.cin, cin_pad, a.cout);
-        Wp = Wtmp;
-      }
-      a.cin = cin_pad;
-      if (a.any_ws) {
-        switch (a.cout) {
-          case 32: launch_ws_mfma<T, 1, 2>(a, Wp, accum); break;
-          case 64: launch_ws_mfma<T, 2, 2>(a, Wp, accum); break;
-          case 128: launch_ws_mfma<T, 4, 1>(a, Wp, accum); break;
-          case 256: launch_ws_mfma<T, 8, 1>(a, Wp, accum); break;
-        }
-      }
-      if (a.any_os) {
-        const bool splitk = a.os_variant == 2 || (a.os_variant == 0 && prefer_splitk(a));
-        if (splitk) {
-          if (a.cout % 64 == 0) launch_os_splitk_any<T, 2>(a, Wp, init);
-          else launch_os_splitk_any<T, 1>(a, Wp, init);
-        } else {
-          if (a.cout % 64 == 0) launch_os_mfma<T, 2>(a, Wp, init);
-          else launch_os_mfma<T, 1>(a, Wp, init);
-        }
-      }
-      // reuse of these blocks is ordered behind this stream's work
-      pool_free(Wtmp, a.s);
+  const T* Wp = static_cast<const T*>(a.W);
+  if (!a.packed) {
+    Wtmp = static_cast<T*>(pool_alloc(size_t(K3) * cin_pad * a.cout * sizeof(T), a.s));
+    if (!Wtmp) {
       pool_free(Fpad, a.s);
+      return SPC_ERR_NOMEM;
     }
+    const int64_t total = int64_t(K3) * (cin_pad / 16) * (a.cout / 32) * 64;
+    hipLaunchKernelGGL(prepack_weights_kernel<T>, dim3((total + 255) / 256), dim3(256), 0, a.s, static_cast<const T*>(a.W), Wtmp, K3,
+                       a.cin, cin_pad, a.cout);
+    Wp = Wtmp;
   }
-  if (!use_mfma) {
-    // nnz[k] <= n_out for every offset
-    if (a.any_ws)
-      hipLaunchKernelGGL(conv_ws_simple_kernel<T>, dim3((out_elems + 255) / 256, a.m->sym ? (K3 - 1) / 2 + 1 : K3), dim3(256), 0,
-                         a.s, a.m->ws_in, a.m->ws_out, a.m->nnz_dev, a.m->ws_stride, static_cast<const T*>(a.F), a.ld_in,
-                         static_cast<const T*>(a.W), accum, a.cin, a.cout, a.ws_mask, a.m->sym ? 1 : 0, K3, a.n_out_h, a.n_out_d);
-    if (a.any_os)
-      hipLaunchKernelGGL(conv_os_simple_kernel<T>, dim3((out_elems + 255) / 256), dim3(256), 0, a.s, a.m->os_map, a.n_out_h,
-                         a.n_out_d, K3, static_cast<const T*>(a.F), a.ld_in, static_cast<const T*>(a.W), static_cast<T*>(a.out),
-                         a.ld_out, a.cin, a.cout, a.relu, a.os_mask, init);
+  a.cin = cin_pad;
+  if (a.cout % 64 == 0) launch_os_mfma<T, 2>(a, Wp);
+  else launch_os_mfma<T, 1>(a, Wp);
+  // reuse of these blocks is ordered behind this stream's work
+  pool_free(Wtmp, a.s);
+  pool_free(Fpad, a.s);
+  return SPC_OK;
+}
+
+template <typename T>
+static int conv_typed(const ConvArgs& a) {
+  if (a.packed && !(sizeof(T) == 2 && packed_shape(a.cout, a.any_ws)))
+    return set_error(SPC_ERR_ARG, "packed weights given for a shape that does not take them");
+  if (a.rows_cap <= 0) return SPC_OK;
+  bool phase = false;
+  if constexpr (sizeof(T) == 2) {
+    phase = !a.any_ws && a.cout % 32 == 0 && (a.os_variant == 1 || (a.os_variant == 0 && !prefer_splitk(a)));
+    if (phase) SPC_RETURN_IF(conv_phase<T>(a));
   }
-  if (!a.any_os)
-    hipLaunchKernelGGL(finalize_kernel<T>, dim3((out_elems + 255) / 256), dim3(256), 0, a.s, accum, a.n_out_h, a.n_out_d, a.cout,
-                       static_cast<T*>(a.out), a.ld_out, a.relu);
-  pool_free(accum, a.s);
-  if (hipGetLastError() != hipSuccess) rc = set_error(SPC_ERR_HIP, "feature kernel launch failed");
-  return rc;
+  if (!phase) launch_os_splitk<T>(a);
+  if (hipGetLastError() != hipSuccess) return set_error(SPC_ERR_HIP, "feature kernel launch failed");
+  return SPC_OK;
 }
 
 constexpr int32_t T_ALL_OS = 0x7fffffff;  // threshold above every norm: all offsets output-stationary
@@ -1143,9 +1075,9 @@ static int conv_entry(spc_kmap* m, const void* feats_in, int64_t ld_in, const vo
   if (a.s != m->stream && std::find(m->consumers.begin(), m->consumers.end(), a.s) == m->consumers.end())
     m->consumers.push_back(a.s);
   switch (dtype) {
-    case SPC_DTYPE_F16: return conv_typed<_Float16>(a, true);
-    case SPC_DTYPE_BF16: return conv_typed<__bf16>(a, true);
-    case SPC_DTYPE_F32: return conv_typed<float>(a, false);
+    case SPC_DTYPE_F16: return conv_typed<_Float16>(a);
+    case SPC_DTYPE_BF16: return conv_typed<__bf16>(a);
+    case SPC_DTYPE_F32: return conv_typed<float>(a);
   }
   return set_error(SPC_ERR_ARG, "bad dtype");
 }

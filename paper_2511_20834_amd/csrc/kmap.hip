@@ -199,6 +199,7 @@ struct SearchArgs {
   int32_t* tile_counts;
   const int32_t* in_perm;
   int2* tile_pairs;
+  uint8_t* tile_sub;
   int32_t* inv_parent;
   KMask os_k, ws_k;
   int n_tiles_cap;
@@ -600,6 +601,7 @@ __global__ __launch_bounds__(SEARCH_THREADS) void kmap_search_kernel(const Searc
     // compaction: a wave takes an offset at a time and walks the tile's rows in steps of 64; the hit's input
     // position is the group's lower bound plus the number of the group's earlier queries that hit
     int2* slab = tile_pairs + int64_t(blockIdx.x) * tile * K3;
+    uint8_t* sub = args.tile_sub + int64_t(blockIdx.x) * K3 * MAX_BLOCKS;  // (unused for offsets without pairs)
     for (int k = wave; k < K3; k += NW) {
       if (s_cnt[k] == 0) continue;  // uniform (offsets outside ws_k are never counted)
       const int g = k / K, tk = k - g * K, tq = sp.zrev ? K - 1 - tk : tk;
@@ -613,6 +615,8 @@ __global__ __launch_bounds__(SEARCH_THREADS) void kmap_search_kernel(const Searc
           const int jpos = s_pos[g * tile + vv] + __popc(msk & ((1u << tq) - 1u));
           slab[at + lanemask_lt_popc(bal)] = make_int2(in_perm ? in_perm[jpos] : jpos, i0 + vv);
         }
+        if (lane < 2)  // pairs of the offset in the tile's blocks before this one
+          sub[k * MAX_BLOCKS + (v0 >> 5) + lane] = static_cast<uint8_t>(at - s_off[k] + (lane ? __popc(static_cast<unsigned>(bal)) : 0));
         at += __popcll(bal);
       }
     }
@@ -625,12 +629,14 @@ __global__ __launch_bounds__(SEARCH_THREADS) void kmap_search_kernel(const Searc
 
 // Weight-stationary lists from the tiles' slabs of compacted pairs (the search kernel in its PAIRS form): one
 // workgroup per tile copies its hits, offset by offset, to where the scan of the per-tile counts puts them.  List k
-// comes out ordered by output index, without atomics and without a |V_q| x K^3 matrix having existed.
+// comes out ordered by output index, without atomics and without a |V_q| x K^3 matrix having existed.  list_base gets
+// where the pairs of every 32-row block start in every list, which is how the feature kernel finds a block's pairs.
 __global__ __launch_bounds__(256) void ws_fill_pairs_kernel(const int2* __restrict__ tile_pairs, int n_out_h,
                                                             const int* __restrict__ n_out_d, int K3, int tile,
                                                             const int32_t* __restrict__ tile_base, int n_tiles_cap,
-                                                            const int32_t* __restrict__ nnz, int32_t* __restrict__ ws_in,
-                                                            int32_t* __restrict__ ws_out, int64_t ws_stride, int k_lim) {
+                                                            const int32_t* __restrict__ nnz, const uint8_t* __restrict__ tile_sub,
+                                                            int32_t* __restrict__ ws_in, int32_t* __restrict__ ws_out,
+                                                            int64_t ws_stride, int k_lim, int32_t* __restrict__ list_base) {
   __shared__ int s_off[WS_MAX_K3_SEARCH + 1], s_dst[WS_MAX_K3_SEARCH];
   const int n_out = n_out_d ? *n_out_d : n_out_h;
   const int i0 = blockIdx.x * tile;
@@ -643,6 +649,7 @@ __global__ __launch_bounds__(256) void ws_fill_pairs_kernel(const int2* __restri
     for (int k0 = 0; k0 < K3; k0 += 64) {
       const int k = k0 + lane;
       int c = 0;
+      if (k < K3) s_dst[k] = 0;
       if (k < k_lim) {
         const int32_t* col = tile_base + int64_t(k) * n_tiles_cap;
         const int b = col[blockIdx.x];
@@ -662,6 +669,15 @@ __global__ __launch_bounds__(256) void ws_fill_pairs_kernel(const int2* __restri
   __syncthreads();
   const int total = s_off[K3];
   const int2* slab = tile_pairs + int64_t(blockIdx.x) * tile * K3;
+  const int tile_blocks = tile >> 5, n_bl = (min(tile, n_out - i0) + 31) >> 5;
+  const uint8_t* sub = tile_sub + int64_t(blockIdx.x) * K3 * tile_blocks;
+  int32_t* base = list_base + (int64_t(i0) >> 5) * K3;
+  for (int e = tid; e < n_bl * K3; e += 256) {
+    const int b = e / K3, k = e - b * K3;
+    base[e] = s_dst[k] + (s_off[k + 1] > s_off[k] ? sub[k * tile_blocks + b] : 0);
+  }
+  if (int(blockIdx.x) + 1 == n_tiles)  // one row more than blocks: the lists' ends
+    for (int k = tid; k < K3; k += 256) base[n_bl * K3 + k] = s_dst[k] + s_off[k + 1] - s_off[k];
   for (int e = tid; e < total; e += 256) {
     int k = 0;  // last offset whose pairs start at or before e (offsets without pairs share their successor's start)
     for (int bit = 256; bit > 0; bit >>= 1)
@@ -722,6 +738,26 @@ __global__ __launch_bounds__(256) void ws_scan_kernel(int32_t* __restrict__ tile
     carry += tot;
   }
   if (threadIdx.x == 0) nnz[blockIdx.x] = carry;
+}
+
+// list_base of lists that no tile of a search has left behind (the lists of a transposed map, which are its strided twin's;
+// a symmetric half-map's by input row): a thread per (block, list) searches the list's ascending rows.
+__global__ __launch_bounds__(256) void list_base_kernel(const int32_t* __restrict__ rows, int64_t stride, const int32_t* __restrict__ nnz,
+                                                        int K3, int k_lim, int n_h, const int* __restrict__ n_d,
+                                                        int32_t* __restrict__ list_base) {
+  const int n = n_d ? *n_d : n_h;
+  const int64_t gid = blockIdx.x * int64_t(256) + threadIdx.x;
+  const int b = static_cast<int>(gid / K3), k = static_cast<int>(gid - int64_t(b) * K3);
+  if (b > (n + 31) >> 5 || k >= k_lim) return;
+  const int32_t* list = rows + int64_t(k) * stride;
+  int lo = 0, len = nnz[k];
+  while (len > 0) {
+    const int half = len >> 1;
+    const bool less = list[lo + half] < b * 32;
+    lo = less ? lo + half + 1 : lo;
+    len = less ? len - half - 1 : half;
+  }
+  list_base[gid] = lo;
 }
 
 // Output-stationary layout of a transposed layer from the inverse its strided twin's search left behind (pairs
@@ -808,6 +844,7 @@ static SearchArgs<KeyT> search_args(const spc_kmap* m) {
   a.os_k = m->os_k;
   a.ws_k = m->ws_k;
   a.tile_pairs = m->tile_pairs;
+  a.tile_sub = m->tile_sub;
   a.inv_parent = m->inv_parent;
   return a;
 }
@@ -880,6 +917,9 @@ static void kmap_free(spc_kmap* m) {
   pool_free(m->nnz_dev, m->stream);
   pool_free(m->tile_counts, m->stream);
   pool_free(m->tile_pairs, m->stream);
+  pool_free(m->tile_sub, m->stream);
+  pool_free(m->list_base, m->stream);
+  pool_free(m->list_base_in, m->stream);
   pool_free(m->inv_parent, m->stream);
   level_unref(m->in_level);
   level_unref(m->out_level);
@@ -982,7 +1022,11 @@ static int prepare_map(Level* in, Level* out, const PackInfo& pi, const spc_laye
     m->tile_counts = static_cast<int32_t*>(pool_alloc(std::max<size_t>(size_t(m->n_tiles) * m->K3 * 4, 256), s));
     // slabs of compacted pairs, one per search tile (bounded by tile * K^3 pairs each; a tile writes its hits only)
     m->tile_pairs = static_cast<int2*>(pool_alloc(std::max<size_t>(size_t(m->n_tiles) * m->tile * m->K3 * 8, 256), s));
-    ok = m->ws_in && m->ws_out && m->tile_counts && m->tile_pairs;
+    m->tile_sub = static_cast<uint8_t*>(pool_alloc(std::max<size_t>(size_t(m->n_tiles) * (m->tile / 32) * m->K3, 256), s));
+    const size_t base_bytes = size_t(m->n_blocks_cap + 1) * m->K3 * 4;
+    m->list_base = static_cast<int32_t*>(pool_alloc(base_bytes, s));
+    if (m->sym) m->list_base_in = static_cast<int32_t*>(pool_alloc(base_bytes, s));
+    ok = m->ws_in && m->ws_out && m->tile_counts && m->tile_pairs && m->tile_sub && m->list_base && (!m->sym || m->list_base_in);
   }
   if (!ok) {
     kmap_free(m);
@@ -990,6 +1034,12 @@ static int prepare_map(Level* in, Level* out, const PackInfo& pi, const spc_laye
   }
   *res = m;
   return SPC_OK;
+}
+
+static void launch_list_base(const spc_kmap* m, const int32_t* rows, int k_lim, const Level* lv, int32_t* base, hipStream_t s) {
+  const int64_t total = (m->n_blocks_cap + 1) * m->K3;
+  hipLaunchKernelGGL(list_base_kernel, dim3(static_cast<unsigned>((total + 255) / 256)), dim3(256), 0, s, rows, m->ws_stride, m->nnz_dev,
+                     m->K3, k_lim, static_cast<int>(lv->n_host < 0 ? 0 : lv->n_host), lv->n_host < 0 ? lv->n_dev : nullptr, base);
 }
 
 // Searches and lists of prepared maps that agree in kernel size, tile length, key width and in whether they have lists.
@@ -1004,10 +1054,14 @@ static int search_maps(spc_kmap* const* ms, int count, hipStream_t s) {
                        out->n_dev, m->nnz_dev, m->k_lim);
     if (m->n_tiles > 0)
       hipLaunchKernelGGL(ws_fill_pairs_kernel, dim3(m->n_tiles), dim3(256), 0, s, m->tile_pairs, n_out_h, out->n_dev, m->K3,
-                         m->tile, m->tile_counts, m->n_tiles, m->nnz_dev, m->ws_in, m->ws_out, m->out_cap, m->k_lim);
+                         m->tile, m->tile_counts, m->n_tiles, m->nnz_dev, m->tile_sub, m->ws_in, m->ws_out, m->out_cap, m->k_lim,
+                         m->list_base);
+    if (m->sym) launch_list_base(m, m->ws_in, m->k_lim, out, m->list_base_in, s);
     // the slabs are dead once the lists are filled: back to the cache (reuse is ordered behind this stream's work)
     pool_free(m->tile_pairs, s);
+    pool_free(m->tile_sub, s);
     m->tile_pairs = nullptr;
+    m->tile_sub = nullptr;
   }
   if (hipGetLastError() != hipSuccess) return set_error(SPC_ERR_HIP, "kernel-map launch failed");
   return SPC_OK;
@@ -1079,6 +1133,8 @@ static int prepare_from_twin(spc_kmap* twin, Level* coarse, Level* fine, const P
     m->ws_out = twin->ws_in;
     m->nnz_dev = twin->nnz_dev;
     m->ws_stride = twin->ws_stride;
+    m->list_base = static_cast<int32_t*>(pool_alloc(size_t(m->n_blocks_cap + 1) * m->K3 * 4, s));
+    if (!m->list_base) rc = SPC_ERR_NOMEM;
   }
   if (rc != SPC_OK) {
     kmap_free(m);
@@ -1088,7 +1144,7 @@ static int prepare_from_twin(spc_kmap* twin, Level* coarse, Level* fine, const P
   return SPC_OK;
 }
 
-// The matrices of prepared transposed maps (their twins have been searched on the same stream before).
+// The matrices and list tables of prepared transposed maps (their twins have been searched on the same stream before).
 static int fill_from_twins(spc_kmap* const* ms, int count, hipStream_t s) {
   for (int first = 0; first < count; first += SEARCH_BATCH) {
     const int n = std::min(count - first, SEARCH_BATCH);
@@ -1097,6 +1153,7 @@ static int fill_from_twins(spc_kmap* const* ms, int count, hipStream_t s) {
     for (int i = 0; i < n; ++i) {
       const spc_kmap* m = ms[first + i];
       const Level* fine = m->out_level;
+      if (m->list_base) launch_list_base(m, m->ws_out, m->K3, fine, m->list_base, s);
       if (!m->os_map) continue;  // lists only: the twin's (its argument entry has no rows)
       b.a[i] = TransposedArgs{m->twin->inv_parent, fine->n_host < 0 ? fine->n_dev : nullptr,
                               static_cast<int>(fine->n_host < 0 ? 0 : fine->n_host), m->K3, m->os_map, m->block_masks};

@@ -253,6 +253,9 @@ struct spc_kmap {
   int32_t* ws_out = nullptr;        // [K3][out_cap]
   int32_t* nnz_dev = nullptr;       // [K3]
   int32_t* tile_counts = nullptr;   // [K3][n_tiles] scratch of the two-pass compaction
+  int32_t* list_base = nullptr;     // [n_blocks+1][K3]: first entry of every list whose output row is >= 32 * block
+  int32_t* list_base_in = nullptr;  // symmetric half-map: the same by input row
+  uint8_t* tile_sub = nullptr;      // [n_tiles][K3][tile/32]: pairs of the tile before every 32-row block (scratch of the list build)
   int2* tile_pairs = nullptr;       // per search tile a slab of compacted (in, out) pairs (scratch of the list build)
   int64_t ws_stride = 0;            // entries between consecutive lists in ws_in / ws_out
   int32_t* inv_parent = nullptr;    // strided maps, on request: for every INPUT voxel p its pair (out q, offset k) as q*K^3+k

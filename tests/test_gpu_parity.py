@@ -739,3 +739,42 @@ def test_hybrid_layout_holds_each_offset_once(name, K, s_l, sym):
         km.destroy()
     with pytest.raises(B.SpcError):  # a threshold needs both layouts
         B.spc_build_kmap(keys, desc, K, 1, s_l, 0, B.LAYOUT_OS | B.LAYOUT_HYBRID_T(1))
+
+
+# ----------------------------------------------------------------------------- shapes of the split-k kernel
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 64, 129, 4097])
+@pytest.mark.parametrize("dtype,cin,cout,ld", [
+    (torch.float32, 6, 10, 7),     # rows that are not 16-byte aligned, one channel at a time
+    (torch.float32, 12, 33, 12),   # last slab half full, one column behind a full tile
+    (torch.float32, 32, 64, 40),
+    (torch.float16, 4, 40, 8),     # four offsets per slab
+    (torch.float16, 4, 64, 5),     # four channels, rows not 8-byte aligned
+    (torch.bfloat16, 24, 40, 24),
+    (torch.float16, 17, 70, 19),
+    (torch.float16, 16, 96, 16),
+])
+def test_conv_shapes_and_sizes(n, dtype, cin, cout, ld):
+    """Matrix, list and mixed offsets at block and slab edges, rows with a pitch, outputs inside a wider buffer."""
+    rng = np.random.default_rng(n * 131 + cin)
+    side = max(2, int(round((n / 0.3) ** (1 / 3))) + 1)
+    lin = rng.choice(side ** 3, size=n, replace=False)
+    c = np.stack([np.zeros(n, int), lin // side ** 2, lin // side % side, lin % side], 1).astype(np.int32)
+    desc = fit_desc(c, [(3, 1, 1)])
+    keys, _ = gpu_pack(c, desc)
+    cs, _ = oracle.sort_coords(c)
+    M = oracle.kernel_map(cs, cs, 3, 1)
+    np_dt = np.float32 if dtype == torch.float32 else np.float16
+    wide, _ = to_torch(synth.features(n, ld, np_dt, seed=31), dtype)
+    Ft = wide[:, :cin]
+    Wt, W64 = to_torch(synth.weights(27, cin, cout, np_dt, seed=32), dtype)
+    ref = oracle.conv(M, np.ascontiguousarray(Ft.cpu().to(torch.float64).numpy()), W64)
+    for layout, kw in ((B.LAYOUT_OS, dict(dataflow=B.DATAFLOW_OS)), (B.LAYOUT_WS, dict(dataflow=B.DATAFLOW_WS)),
+                       (B.LAYOUT_WS | B.LAYOUT_WS_SYM, dict(dataflow=B.DATAFLOW_WS)),
+                       (B.LAYOUT_BOTH | B.LAYOUT_HYBRID_T(2), dict(hybrid_t=2))):
+        km = B.spc_build_kmap(keys, desc, 3, layout=layout)
+        out = torch.full((n, cout + 3), 7.0, dtype=dtype, device="cuda")
+        B.spc_conv_forward(km, Ft, Wt, out=out[:, 1:1 + cout], **kw)
+        o = out.cpu().to(torch.float64).numpy()
+        assert_close(o[:, 1:1 + cout], ref, TOL[dtype], (layout, kw))
+        assert np.all(o[:, 0] == 7.0) and np.all(o[:, 1 + cout:] == 7.0), (layout, kw)
+        km.destroy()
