@@ -92,9 +92,9 @@ __device__ inline T* level_ws(T* p, size_t ws_pitch) {
 }
 
 // ---------------------------------------------------------------- count
-template <typename KeyT, typename Src>
+template <typename KeyT, typename Src, typename CountT>
 __global__ __launch_bounds__(BS_WIDE) void bs_count_kernel(const Src srcs, int64_t n, int per, int shift, int n_bin,
-                                                           KeyT* __restrict__ keys0, int32_t* __restrict__ table,
+                                                           KeyT* __restrict__ keys0, CountT* __restrict__ table,
                                                            size_t ws_pitch) {
   extern __shared__ int hist[];  // [n_bin]
   const auto src = srcs.level(blockIdx.y);
@@ -125,10 +125,10 @@ __global__ __launch_bounds__(BS_WIDE) void bs_count_kernel(const Src srcs, int64
   }
   src.report(bad);
   __syncthreads();
-  for (int b = threadIdx.x; b < n_bin; b += BS_WIDE) table[int64_t(blockIdx.x) * n_bin + b] = hist[b];
+  for (int b = threadIdx.x; b < n_bin; b += BS_WIDE) table[int64_t(blockIdx.x) * n_bin + b] = static_cast<CountT>(hist[b]);
 }
 
-// ---------------------------------------------------------------- column scan
+// ---------------------------------------------------------------- column scan (tables too large for the scatter pass to sum)
 // One thread per four bins: before[w][f] receives the number of keys of bin f held by workgroups
 // < w, tot[f] the bin's total.  The loads of 16 table rows are in flight together.
 constexpr int BS_COL_THREADS = 64;
@@ -162,14 +162,20 @@ __global__ __launch_bounds__(BS_COL_THREADS) void bs_colscan_kernel(const int32_
 // ---------------------------------------------------------------- scatter
 // Every workgroup scans the bin totals on its own (16 KB; cheaper than one more launch): start
 // of bin f, then the workgroup's first position in the bin, and moves its keys, with their source
-// index, to their bin's range.  It also prepares the rank pass: for every BS_PART scattered
+// index, to their bin's range.
+// SUM (small tables of 16-bit counts, see bucket_plan): the totals and the counts of the workgroups before this one are
+// summed here from the whole table, which saves the column scan's launch (4 to 5 us).  A thread sums four bins, two per
+// register: a workgroup counts at most 4096 keys, so 15 rows fit 16 bits before they have to be widened.  It also prepares the rank pass: for every BS_PART scattered
 // positions the window of whole bins that covers them, BS_PAD_KEYS all-ones keys behind the last
 // key, the number of keys that take part and, for the downsampling variant (DEDUP: of a run of
 // equal adjacent keys only the first takes part), the cleared position bitmap and chunk counters.
-template <typename KeyT, bool DEDUP>
+constexpr int BS_SUM_ROWS = 15;
+constexpr int BS_SUM_MAX_WG = 8;  // rows of the largest table that is summed here
+template <typename KeyT, bool DEDUP, bool SUM>
 __global__ __launch_bounds__(BS_WIDE) void bs_scatter_kernel(const KeyT* __restrict__ keys0, int64_t n, int per, int shift,
                                                              int n_bin, const int32_t* __restrict__ before,
-                                                             const int32_t* __restrict__ tot, KeyT* __restrict__ keys1,
+                                                             const int32_t* __restrict__ tot,
+                                                             const uint16_t* __restrict__ table, KeyT* __restrict__ keys1,
                                                              int32_t* __restrict__ vals1, int2* __restrict__ win,
                                                              int32_t* __restrict__ n_part_keys, uint32_t* __restrict__ bits,
                                                              int n_words, int32_t* __restrict__ ccnt, int n_chunks,
@@ -179,6 +185,7 @@ __global__ __launch_bounds__(BS_WIDE) void bs_scatter_kernel(const KeyT* __restr
     keys0 = level_ws(keys0, ws_pitch);
     before = level_ws(before, ws_pitch);
     tot = level_ws(tot, ws_pitch);
+    table = level_ws(table, ws_pitch);
     keys1 = level_ws(keys1, ws_pitch);
     win = level_ws(win, ws_pitch);
     n_part_keys = level_ws(n_part_keys, ws_pitch);
@@ -194,14 +201,50 @@ __global__ __launch_bounds__(BS_WIDE) void bs_scatter_kernel(const KeyT* __restr
     for (int i = blockIdx.x * BS_WIDE + t; i < n_words; i += gridDim.x * BS_WIDE) bits[i] = 0u;
     for (int i = blockIdx.x * BS_WIDE + t; i < n_chunks; i += gridDim.x * BS_WIDE) ccnt[i] = 0;
   }
+  // a pass takes four keys per thread; the first pass's are requested before the scan, so that they arrive under it
+  const int64_t lo = int64_t(blockIdx.x) * per, hi = min<int64_t>(n, lo + per);
+  KeyT key[4], prev[4];
+  auto fetch = [&](int64_t i0) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t i = min<int64_t>(i0 + u * BS_WIDE, hi - 1);
+      key[u] = keys0[i];
+      prev[u] = DEDUP ? keys0[i > 0 ? i - 1 : 0] : KeyT(0);
+    }
+  };
+  fetch(lo + threadIdx.x);
   // exclusive scan of the bin totals, four bins per thread and round (one round up to 4096 bins)
   int total = 0;  // keys that take part (all of them unless DEDUP)
   for (int r0 = 0; r0 < n_bin; r0 += 4 * BS_WIDE) {
     const int f0 = r0 + t * 4;
     int4 c = make_int4(0, 0, 0, 0), bef = c;
     if (f0 < n_bin) {
-      c = *reinterpret_cast<const int4*>(tot + f0);
-      bef = *reinterpret_cast<const int4*>(before + int64_t(blockIdx.x) * n_bin + f0);
+      if constexpr (SUM) {
+        auto add_rows = [&](int w, int w_end, int4& acc) {
+          for (; w < w_end; w += BS_SUM_ROWS) {
+            uint2 row[BS_SUM_ROWS];
+#pragma unroll
+            for (int r = 0; r < BS_SUM_ROWS; ++r)
+              row[r] = *reinterpret_cast<const uint2*>(table + int64_t(min(w + r, w_end - 1)) * n_bin + f0);
+            unsigned a = 0, b = 0;  // two 16-bit sums each
+#pragma unroll
+            for (int r = 0; r < BS_SUM_ROWS; ++r) {
+              a += w + r < w_end ? row[r].x : 0u;
+              b += w + r < w_end ? row[r].y : 0u;
+            }
+            acc.x += a & 0xffffu;
+            acc.y += a >> 16;
+            acc.z += b & 0xffffu;
+            acc.w += b >> 16;
+          }
+        };
+        add_rows(0, blockIdx.x, bef);
+        c = bef;
+        add_rows(blockIdx.x, gridDim.x, c);
+      } else {
+        c = *reinterpret_cast<const int4*>(tot + f0);
+        bef = *reinterpret_cast<const int4*>(before + int64_t(blockIdx.x) * n_bin + f0);
+      }
     }
     const int sum = c.x + c.y + c.z + c.w;
     int x = sum;
@@ -231,18 +274,11 @@ __global__ __launch_bounds__(BS_WIDE) void bs_scatter_kernel(const KeyT* __restr
   }
   if (t == 0) bin_start[n_bin] = total;
   __syncthreads();
-  const int64_t lo = int64_t(blockIdx.x) * per, hi = min<int64_t>(n, lo + per);
   for (int64_t i0 = lo + threadIdx.x; i0 < hi; i0 += 4 * BS_WIDE) {
     // all keys of the pass are fetched, then all positions drawn, then everything stored
-    KeyT key[4], prev[4];
     bool use[4];
     int p[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int64_t i = min<int64_t>(i0 + u * BS_WIDE, hi - 1);
-      key[u] = keys0[i];
-      prev[u] = DEDUP ? keys0[i > 0 ? i - 1 : 0] : KeyT(0);
-    }
+    if (i0 >= lo + 4 * BS_WIDE) fetch(i0);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       SPC_PIN_LOADED(key[u]);
@@ -975,6 +1011,10 @@ BucketPlan bucket_plan(int64_t n, int used_bits) {
   while (fb < 12 && (int64_t(16) << fb) < n) ++fb;
   if (n > 200000) fb = 13;
   if (n > 524288) fb = 14;
+  // The scatter pass sums tables of a few rows itself: pack + sort, column scan / summed, 4.1 k keys 14.4 / 12.5 us, 12 k
+  // 16.3 / 15.3, 30 k (8 rows) 17.6 / 16.9, 45 k (11 rows) 19.2 / 19.9, 120 k 26.0 / 27.0 (every workgroup then reads up to
+  // half a megabyte that other XCDs have written)
+  p.sum = fb <= 12 && p.per <= 4096 && p.n_wg <= BS_SUM_MAX_WG;
   static_assert(BS_MAX_BIN_BITS >= 14, "bin table sizes");
   fb = std::max(2, std::min(fb, used_bits));
   p.shift = used_bits - fb;
@@ -1029,18 +1069,27 @@ Ws<KeyT> carve(void* ws, int64_t n) {
 // count, column scan, scatter: keys1 (vals1) partitioned by fine bin, rank windows
 template <typename KeyT, bool DEDUP, typename Src>
 void partition(const Src& src, int64_t n, const BucketPlan& p, const Ws<KeyT>& w, int n_levels, size_t ws_pitch, hipStream_t s) {
-  hipLaunchKernelGGL((bs_count_kernel<KeyT, Src>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(p.n_bin) * 4, s, src, n, p.per,
+  if (p.sum) {
+    uint16_t* table = reinterpret_cast<uint16_t*>(w.table);
+    hipLaunchKernelGGL((bs_count_kernel<KeyT, Src, uint16_t>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(p.n_bin) * 4, s, src, n,
+                       p.per, p.shift, p.n_bin, w.keys0, table, ws_pitch);
+    hipLaunchKernelGGL((bs_scatter_kernel<KeyT, DEDUP, true>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(2 * p.n_bin + 2) * 4, s,
+                       w.keys0, n, p.per, p.shift, p.n_bin, static_cast<const int32_t*>(nullptr), static_cast<const int32_t*>(nullptr),
+                       table, w.keys1, w.vals1, w.win, DEDUP ? w.n_kept : static_cast<int32_t*>(nullptr), w.bits, w.n_words, w.ccnt,
+                       w.n_chunks, w.rest_count, ws_pitch);
+    return;
+  }
+  hipLaunchKernelGGL((bs_count_kernel<KeyT, Src, int32_t>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(p.n_bin) * 4, s, src, n, p.per,
                      p.shift, p.n_bin, w.keys0, w.table, ws_pitch);
   const int col_wg = (p.n_bin / 4 + BS_COL_THREADS - 1) / BS_COL_THREADS;
   hipLaunchKernelGGL(bs_colscan_kernel, dim3(col_wg, n_levels), dim3(BS_COL_THREADS), 0, s, w.table, w.before, p.n_wg, p.n_bin,
                      w.fstart, ws_pitch);
   // (the scatter pass holds two ints per bin: beyond 8191 bins that is more than the default LDS limit)
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bs_scatter_kernel<KeyT, DEDUP>),
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bs_scatter_kernel<KeyT, DEDUP, false>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (2 * BS_MAX_BIN + 2) * 4);
   (void)attr;
-  hipLaunchKernelGGL((bs_scatter_kernel<KeyT, DEDUP>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(2 * p.n_bin + 2) * 4, s, w.keys0, n, p.per,
-                     p.shift, p.n_bin, w.before,
-                     w.fstart, w.keys1, w.vals1, w.win, DEDUP ? w.n_kept : static_cast<int32_t*>(nullptr), w.bits, w.n_words, w.ccnt,
+  hipLaunchKernelGGL((bs_scatter_kernel<KeyT, DEDUP, false>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(2 * p.n_bin + 2) * 4, s, w.keys0,
+                     n, p.per, p.shift, p.n_bin, w.before, w.fstart, static_cast<const uint16_t*>(nullptr), w.keys1, w.vals1, w.win, DEDUP ? w.n_kept : static_cast<int32_t*>(nullptr), w.bits, w.n_words, w.ccnt,
                      w.n_chunks, w.rest_count, ws_pitch);
 }
 }  // namespace

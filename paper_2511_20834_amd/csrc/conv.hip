@@ -12,7 +12,6 @@
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
-#include <cstdlib>
 #include <type_traits>
 #include <utility>
 
@@ -453,6 +452,9 @@ struct SplitkArgs {
   void* out;
   int64_t ld_in, ld_out;
   int mask_words, n_out_h, K3, cin, cout, relu, nb_total, vec_store;
+  int log_waves;      // log2 of the waves that share a tile's offsets: 2, or more with several workgroups per tile
+  float* partial;     // [tile][slab][part][32 * NB * 32]: the parts' sums, when a tile is shared by workgroups
+  int32_t* arrived;   // [tile][slab]: parts that have stored theirs; zero between launches
   KMask os_mask;
   ListArgs lists;
 };
@@ -463,10 +465,11 @@ constexpr int splitk_idx_rows(int K3, int AM) { return (K3 + SPLITK_WAVES - 1) /
 // PACKED: weights in MFMA operand order; otherwise the caller's [K^3][cin][cout], read a channel at a time (a fragment is
 // then 32-column rows of W instead of 16 bytes per lane: the same bytes in more instructions, but no re-layout pass).
 template <typename T, int NB, int RB, int D, bool LOOP, int AM, bool PACKED, bool LISTS>
-__global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 2 ? 6 : 8) : 1) void conv_os_splitk_kernel(const SplitkArgs a) {
+__global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 4 ? 4 : NB == 2 || LOOP ? 6 : 8) : 1) void conv_os_splitk_kernel(const SplitkArgs a) {
   using V = typename Mfma<T>::V;
   constexpr int LPC = Mfma<T>::LPC, SLAB = 2 * LPC;
   static_assert(RB == 1 || (AM == A_VEC && !LISTS), "two row blocks: plain layers only");
+  constexpr bool SHARED = RB == 1 && AM == A_VEC && NB <= 2;  // whether several workgroups may share a tile's offsets
   static_assert(AM != A_QUAD || sizeof(T) == 2, "four offsets per slab: 16-bit types");
   extern __shared__ __align__(16) unsigned char smem[];
   const int32_t* __restrict__ M = a.M;
@@ -480,6 +483,7 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 2 ?
   const int64_t n_blocks = (int64_t(n_out) + 31) >> 5;
   const int slab = blockIdx.y;
   const int KK = (cin + SLAB - 1) / SLAB;
+  int log_waves = a.log_waves;
   // tiles of RB blocks; the trip count is uniform per workgroup, so the barriers below are
   // reached by all of its waves or by none
   for (int64_t blk0 = int64_t(blockIdx.x) * RB; blk0 < n_blocks; blk0 += LOOP ? int64_t(gridDim.x) * RB : n_blocks) {
@@ -498,7 +502,9 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 2 ?
   int32_t* s_first = reinterpret_cast<int32_t*>(kl_base + SPLITK_WAVES * SPLITK_KL_CAP * 2) + wave * SPLITK_KL_CAP;
   int32_t* s_num = s_first + SPLITK_WAVES * SPLITK_KL_CAP;
 
-  // this wave's offsets: those present in the tile whose rank is wave mod 4
+  // this wave's offsets: those present in the tile whose rank is its share mod the number of shares (cnt - share >= -31, so
+  // the count of a share behind the last rank comes out as zero)
+  const int share = SHARED && log_waves > 2 ? blockIdx.z * SPLITK_WAVES + wave : wave;
   int cnt = 0;
   if constexpr (!LISTS) {  // (union of the builder's block masks)
     for (int wd = 0; wd < a.mask_words; ++wd) {
@@ -509,7 +515,7 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 2 ?
       m = __builtin_amdgcn_readfirstlane(m & a.os_mask.w[wd]);
       if (lane < 32 && ((m >> lane) & 1u)) {
         const int rank = cnt + __builtin_popcount(m & ((1u << lane) - 1u));
-        if ((rank & (SPLITK_WAVES - 1)) == wave) kl[rank / SPLITK_WAVES] = static_cast<int16_t>(wd * 32 + lane);
+        if ((rank & ((1 << log_waves) - 1)) == share) kl[rank >> log_waves] = static_cast<int16_t>(wd * 32 + lane);
       }
       cnt += __builtin_popcount(m);
     }
@@ -535,15 +541,16 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 2 ?
       const unsigned long long bal = __ballot(num != 0);
       const int rank = cnt + __builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(bal >> 32),
                                                        __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(bal), 0));
-      if (num != 0 && (rank & (SPLITK_WAVES - 1)) == wave) {
-        kl[rank / SPLITK_WAVES] = static_cast<int16_t>(k);
-        s_first[rank / SPLITK_WAVES] = first;
-        s_num[rank / SPLITK_WAVES] = num;
+      if (num != 0 && (rank & ((1 << log_waves) - 1)) == share) {
+        const int at = rank >> log_waves;
+        kl[at] = static_cast<int16_t>(k);
+        s_first[at] = first;
+        s_num[at] = num;
       }
       cnt += __popcll(bal);
     }
   }
-  const int n_i = __builtin_amdgcn_readfirstlane(cnt > wave ? (cnt - wave + SPLITK_WAVES - 1) / SPLITK_WAVES : 0);
+  const int n_i = __builtin_amdgcn_readfirstlane((cnt - share + (1 << log_waves) - 1) >> log_waves);
   // entries past the end read offset 0's weights and all-invalid rows
   constexpr int TAIL = AM == A_QUAD ? 4 : 1;
   if (lane < TAIL) kl[n_i + lane] = 0;
@@ -744,6 +751,49 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 2 ?
   // Thread t stores EPT consecutive channels of row t/8 of every block.
   constexpr int EPT = NB * 4;
   const float* red = reinterpret_cast<const float*>(smem);
+  if (SHARED && log_waves > 2) {
+    // This workgroup's part of the sum goes to memory; whoever finds all other parts there adds them up, in the order
+    // of the parts whoever it is.  Nobody waits.  Parts travel between XCDs, whose L2s are not coherent: they are
+    // stored and loaded at device scope, and a part is announced once its stores have completed.
+    constexpr int PART = NB * 1024;
+    const int parts = gridDim.z;
+    const int64_t slot = int64_t(blockIdx.x) * gridDim.y + slab;
+    using Pair = unsigned long long;  // two sums per access
+    constexpr int PER = PART / 2 / (64 * SPLITK_WAVES);
+    Pair* part0 = reinterpret_cast<Pair*>(a.partial) + slot * parts * (PART / 2) + tid;
+    Pair* red2 = reinterpret_cast<Pair*>(smem) + tid;
+#pragma unroll
+    for (int e = 0; e < PER; ++e)
+      __hip_atomic_store(part0 + blockIdx.z * (PART / 2) + e * 256, red2[e * 256], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    int* s_last = reinterpret_cast<int*>(smem) + PART;
+    if (tid == 0) *s_last = __hip_atomic_fetch_add(a.arrived + slot, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1;
+    __syncthreads();
+    if (!*s_last) return;
+    if (tid == 0) __hip_atomic_store(a.arrived + slot, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
+    float2 v[PER];
+#pragma unroll
+    for (int e = 0; e < PER; ++e) v[e] = make_float2(0.f, 0.f);
+    for (int q = 0; q < parts; q += 2) {  // (an even number)
+      Pair t[2][PER];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int e = 0; e < PER; ++e)
+          t[h][e] = __hip_atomic_load(part0 + (q + h) * (PART / 2) + e * 256, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int e = 0; e < PER; ++e) {
+          v[e].x += __uint_as_float(static_cast<unsigned>(t[h][e]));
+          v[e].y += __uint_as_float(static_cast<unsigned>(t[h][e] >> 32));
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < PER; ++e) reinterpret_cast<float2*>(smem)[tid + e * 256] = v[e];
+    __syncthreads();
+  }
   const int row = tid >> 3, c0 = (tid & 7) * EPT;
   const int nb = c0 >> 5, cc = c0 & 31;
   const int q = row >> 3, h = (row & 7) >> 2, rr = row & 3;
@@ -761,11 +811,9 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 2 ?
     if (i < n_out && oc < cout) {
       T* dst = out + i * ld_out + oc;
       if (a.vec_store) {  // (cout is a multiple of EPT then)
-        if constexpr (EPT * sizeof(T) == 32) {
-          reinterpret_cast<uint4*>(dst)[0] = reinterpret_cast<const uint4*>(o)[0];
-          reinterpret_cast<uint4*>(dst)[1] = reinterpret_cast<const uint4*>(o)[1];
-        } else if constexpr (EPT * sizeof(T) == 16) {
-          *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(o);
+        if constexpr (EPT * sizeof(T) >= 16) {
+#pragma unroll
+          for (int j = 0; j < int(EPT * sizeof(T)) / 16; ++j) reinterpret_cast<uint4*>(dst)[j] = reinterpret_cast<const uint4*>(o)[j];
         } else {
           *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<const uint2*>(o);
         }
@@ -777,6 +825,7 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 2 ?
     }
   }
   if constexpr (LOOP) __syncthreads();  // the LDS tile is reused as the next tile's index area
+  log_waves = 2;  // only the first tile is shared (its slot is then free again); who finished it goes on alone
   }
 }
 
@@ -838,7 +887,40 @@ static void launch_os_mfma(const ConvArgs& a, const T* Wp) {
 
 static size_t splitk_lds_bytes(int K3, int NB, int RB, int AM, bool lists) {
   const size_t idx = size_t(SPLITK_WAVES) * splitk_idx_rows(K3, AM) * RB * 128 + size_t(SPLITK_WAVES) * SPLITK_KL_CAP * (lists ? 10 : 2);
-  return std::max(idx, size_t(RB) * NB * 16 * 64 * 4);
+  return std::max(idx, size_t(RB) * NB * 16 * 64 * 4 + 16);
+}
+
+// Whether the feature rows are as the vector loads and whole slabs of the split-k and phase kernels want them.
+template <typename T>
+static bool plain_rows(const ConvArgs& a) {
+  constexpr int LPC = Mfma<T>::LPC;
+  return a.ld_in % LPC == 0 && reinterpret_cast<uintptr_t>(a.F) % 16 == 0 && a.cin % (2 * LPC) == 0;
+}
+
+// Workgroups that share the offsets of a tile (a power of two).  A tile's weights and rows go through one CU, so a layer
+// with fewer tiles than the chip has CUs, or a few more, takes as long as its longest tiles; sharing them costs about 4 us
+// (the parts travel through memory) and pays where a tile is long.  us, alone / two / four: 480 rows 256->256 16.9 / 14.4 /
+// 12.2, 1426 rows 256->128 16.7 / 13.0 / 12.3, 1426 rows 128->128 10.4 / 9.4 / 9.1, 4188 rows 128->64 10.4 / 9.3 / 9.8,
+// 2368 rows 256->256 27.8 / 25.5 / 23.9; but 6821 rows 256->128 27.5 / 30.5 / 29.0.
+// Only on the map's own stream: its counters must not be in two launches at once.
+template <typename T>
+static int splitk_parts(const ConvArgs& a, int64_t tiles) {
+  const int steps = a.m->K3 * (a.cin / (2 * Mfma<T>::LPC)) * (sizeof(T) == 4 ? 2 : 1);
+  const int parts = steps >= 432 && tiles <= 320 ? 4 : steps >= 216 && tiles <= 160 ? 2 : 1;
+  if (parts == 1 || !a.m->arrived || a.m->stream != a.s) return 1;
+  // (a recorded launch may be replayed on any stream: fine for a map that is rebuilt by every replay, and only there)
+  return a.m->captured || !stream_is_capturing(a.s) ? parts : 1;
+}
+
+// 128-column slabs (wide layers): every gathered row then serves 128 columns instead of 64, at half the workgroups of
+// twice the registers.  us, 64 / 128 columns: 120 k voxels 256->256 433 / 317, 128->128 117 / 91; 18 k 128->128 28.8 / 24.4;
+// 6 k 64->128 10.2 / 9.8, 128->256 21.5 / 23.0, 10 k 128->128 20.6 / 21.6: a tile of 128 columns takes about 1.6 times
+// one of 64, and what counts is how many of them the fullest CU gets.
+static bool splitk_wide(const ConvArgs& a) {
+  if (a.cout % 128 != 0 || a.m->K3 < 27) return false;
+  const int64_t tiles = std::max<int64_t>((a.rows_sel + 31) / 32, 1) * (a.cout / 128);
+  const int64_t wide = (tiles + 255) / 256, narrow = (2 * tiles + 255) / 256;
+  return wide * 100 <= narrow * 62;
 }
 
 template <typename T, int NB, int RB, int AM, bool PACKED, bool LISTS>
@@ -881,11 +963,24 @@ static void launch_splitk(const ConvArgs& a, const void* W) {
     return e != hipSuccess ? e : f;
   }();
   (void)attr;
-  const dim3 grid(static_cast<unsigned>((n_blocks + RB - 1) / RB), k.nb_total / NB);
+  k.log_waves = 2;
+  int parts = 1;
+  if (RB == 1 && AM == A_VEC && NB <= 2) {
+    const int64_t tiles = n_blocks * (k.nb_total / NB);
+    parts = splitk_parts<T>(a, tiles);
+    if (parts > 1) {
+      k.partial = static_cast<float*>(pool_alloc(size_t(tiles) * parts * NB * 4096, a.s));
+      if (!k.partial) parts = 1;  // (not worth failing for)
+      k.arrived = a.m->arrived;
+    }
+    for (int q = parts; q > 1; q >>= 1) ++k.log_waves;
+  }
+  const dim3 grid(static_cast<unsigned>((n_blocks + RB - 1) / RB), k.nb_total / NB, parts);
   if (loop)
     hipLaunchKernelGGL((conv_os_splitk_kernel<T, NB, RB, D, true, AM, PACKED, LISTS>), grid, dim3(64 * SPLITK_WAVES), lds, a.s, k);
   else
     hipLaunchKernelGGL((conv_os_splitk_kernel<T, NB, RB, D, false, AM, PACKED, LISTS>), grid, dim3(64 * SPLITK_WAVES), lds, a.s, k);
+  pool_free(k.partial, a.s);  // reuse is ordered behind this stream's work
 }
 
 // Split-k kernel in the form that the layer's rows, weights and offsets need.
@@ -927,25 +1022,44 @@ static void launch_os_splitk(const ConvArgs& a) {
     }
     a.any_ws ? rows(No{}, Yes{}) : rows(No{}, No{});
   };
-  ((a.cout + 31) / 32) % 2 == 0 ? columns(std::integral_constant<int, 2>{}) : columns(std::integral_constant<int, 1>{});
+  const int nb_total = (a.cout + 31) / 32;
+  if constexpr (sizeof(T) == 2) {
+    if (a.packed && plain_rows<T>(a) && a.splitk_rb == 0 && splitk_wide(a) && splitk_parts<T>(a, (a.rows_sel + 31) / 32 * (a.cout / 64)) == 1) {
+      a.any_ws ? launch_splitk<T, 4, 1, A_VEC, true, true>(a, a.W) : launch_splitk<T, 4, 1, A_VEC, true, false>(a, a.W);
+      return;
+    }
+  }
+  nb_total % 2 == 0 ? columns(std::integral_constant<int, 2>{}) : columns(std::integral_constant<int, 1>{});
 }
 
-// Measured crossover on MI355X (3x3x3 layers, 32..256 channels, 18 k / 49 k / 120 k voxels).  The phase
+// Phase kernel or split-k kernel, measured on MI355X (3x3x3 layers, 32..256 channels, 6 k to 120 k voxels).  The phase
 // kernel stages every weight once per sixteen row blocks and wins where that matters: enough tiles for
 // 64 sixteen-wave workgroups (per slab of output channels; they are dealt to up to 256 workgroups, see
 // phase_wgs_per_xcd) and enough input channels behind every tile.  Below that the split-k kernel's many
 // short workgroups win in spite of their redundant weight reads: us, phase / split-k, 49 k voxels
-// 32->64 15.2 / 11.6, 64->64 19.4 / 19.1, 64->128 25.5 / 30.6; 18 k voxels 64->64 17.5 / 10.7, 128->128
-// 29.7 / 28.8, 128->256 38.8 / 46.5; 120 k voxels 32->64 20.6 / 22.9, 64->64 30.5 / 37.3.  With 32-column
+// 32->64 15.2 / 11.6, 64->64 19.4 / 19.1, 64->128 25.5 / 30.6; 18 k voxels 64->64 17.5 / 10.7; 120 k voxels 32->64
+// 20.6 / 22.9, 64->64 30.5 / 37.3.  With 32-column
 // slabs the split-k kernel wins or ties at every size measured (32->32: 120 k voxels 18.8 / 15.6, 10^6
 // voxels 118 / 80, 3 * 10^6 voxels 359 / 269; 64->32 at 120 k voxels 27.6 / 27.4).  Large kernels (5x5x5
 // and up) favour the split-k kernel at every size measured.
+// Layers the split-k kernel runs with 128-column slabs: the phase kernel (one workgroup of sixteen 64-column tiles per
+// CU) wins while one round of its workgroups holds the layer and leaves less than half of their waves idle: us, phase / split-k,
+// 60 k voxels 128->128 48.2 / 58.6, 35 k 37.1 / 39.4, 18 k 128->256 38.0 / 41.6; with fewer tiles 18 k 128->128 29.2 / 24.4;
+// with more, 35 k 256->256 168 / 120, 120 k 128->128 97 / 91, 256->256 336 / 317, 100 k random voxels 253 / 185.
+template <typename T>
 static bool prefer_splitk(const ConvArgs& a) {
   const int64_t n_blocks = (a.rows_sel + 31) / 32;
   const int n_slabs = a.cout % 64 == 0 ? a.cout / 64 : a.cout / 32;
   const int64_t wgs = (n_blocks + 15) / 16 * n_slabs;
   if (a.m->K3 > 64 || wgs < 64 || a.cout % 64 != 0) return true;
-  return wgs * a.cin < 7000;
+  if (a.packed && plain_rows<T>(a) && a.cout % 128 == 0 && a.m->K3 >= 27) {
+    const int64_t tiles = n_blocks * n_slabs;
+    return tiles < 8 * 256 || tiles > 16 * 256;
+  }
+  // a last round of phase workgroups that is far from full costs as much as a full one: us, phase / split-k, 64->64, 150 k
+  // voxels (1.14 rounds) 55 / 46, 300 k (2.3) 66 / 60, 400 k (3.05) 79 / 73; 200 k (1.53) 57 / 58
+  const int64_t tiles = n_blocks * n_slabs, room = (tiles + 4095) / 4096 * 4096;
+  return wgs * a.cin < 7000 || (tiles > 4096 && tiles * 5 < room * 4);
 }
 
 // Shapes that take prepacked weights (16-bit types): any input channels (padded to a multiple of 16), output channels a
@@ -1003,7 +1117,7 @@ static int conv_typed(const ConvArgs& a) {
   if (a.rows_cap <= 0) return SPC_OK;
   bool phase = false;
   if constexpr (sizeof(T) == 2) {
-    phase = !a.any_ws && a.cout % 32 == 0 && (a.os_variant == 1 || (a.os_variant == 0 && !prefer_splitk(a)));
+    phase = !a.any_ws && a.cout % 32 == 0 && (a.os_variant == 1 || (a.os_variant == 0 && !prefer_splitk<T>(a)));
     if (phase) SPC_RETURN_IF(conv_phase<T>(a));
   }
   if (!phase) launch_os_splitk<T>(a);

@@ -201,6 +201,7 @@ struct SearchArgs {
   int2* tile_pairs;
   uint8_t* tile_sub;
   int32_t* inv_parent;
+  int32_t* arrived;
   KMask os_k, ws_k;
   int n_tiles_cap;
 };
@@ -261,6 +262,8 @@ __global__ __launch_bounds__(SEARCH_THREADS) void kmap_search_kernel(const Searc
   if (i0 >= n_out) return;  // whole workgroup leaves together
   const int rows = min(tile, n_out - i0);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (blockIdx.x == 0)
+    for (int j = tid; j < SHARED_TILES; j += SEARCH_THREADS) args.arrived[j] = 0;
 
   // first-round probes of the window-bound searches (the same N_PROBES keys for everybody: L2-resident)
   {
@@ -772,6 +775,7 @@ struct TransposedArgs {
   int n_h, K3;
   int32_t* Mt;
   uint32_t* block_masks;
+  int32_t* arrived;
 };
 struct TransposedBatch {
   TransposedArgs a[SEARCH_BATCH];
@@ -783,6 +787,8 @@ __global__ __launch_bounds__(256) void transposed_from_parent_kernel(const Trans
   uint32_t* __restrict__ block_masks = args.block_masks;
   const int K3 = args.K3;
   const int n = level_count(args.n_d, args.n_h);
+  if (blockIdx.x == 0 && n > 0)
+    for (int j = threadIdx.x; j < SHARED_TILES; j += 256) args.arrived[j] = 0;
   const int64_t p = int64_t(blockIdx.x) * 256 + threadIdx.x;
   const int64_t blk = p >> 5;
   if (blk * 32 >= n) return;  // whole 32-row blocks leave together (the ballots below stay among one wave's lanes)
@@ -846,6 +852,7 @@ static SearchArgs<KeyT> search_args(const spc_kmap* m) {
   a.tile_pairs = m->tile_pairs;
   a.tile_sub = m->tile_sub;
   a.inv_parent = m->inv_parent;
+  a.arrived = m->arrived;
   return a;
 }
 
@@ -921,6 +928,7 @@ static void kmap_free(spc_kmap* m) {
   pool_free(m->list_base, m->stream);
   pool_free(m->list_base_in, m->stream);
   pool_free(m->inv_parent, m->stream);
+  pool_free(m->arrived, m->stream);
   level_unref(m->in_level);
   level_unref(m->out_level);
   delete m;
@@ -1015,7 +1023,8 @@ static int prepare_map(Level* in, Level* out, const PackInfo& pi, const spc_laye
   m->ws_stride = m->out_cap;
   if (want_inverse && !in_perm)
     m->inv_parent = static_cast<int32_t*>(pool_alloc(std::max<size_t>(size_t(in->n_host >= 0 ? in->n_host : in->cap) * 4, 256), s));
-  bool ok = m->nnz_dev && (!with_os || (m->os_map && m->block_masks)) && (m->inv_parent || !(want_inverse && !in_perm));
+  m->arrived = static_cast<int32_t*>(pool_alloc(SHARED_TILES * 4, s));
+  bool ok = m->nnz_dev && m->arrived && (!with_os || (m->os_map && m->block_masks)) && (m->inv_parent || !(want_inverse && !in_perm));
   if (ok && (l.layout & SPC_LAYOUT_WS)) {
     m->ws_in = static_cast<int32_t*>(pool_alloc(cells * 4, s));
     m->ws_out = static_cast<int32_t*>(pool_alloc(cells * 4, s));
@@ -1126,7 +1135,8 @@ static int prepare_from_twin(spc_kmap* twin, Level* coarse, Level* fine, const P
   if (with_os) {
     m->os_map = static_cast<int32_t*>(pool_alloc(std::max<size_t>(size_t(m->n_blocks_cap) * 32 * m->K3 * 4, 256), s));
     m->block_masks = static_cast<uint32_t*>(pool_alloc(std::max<size_t>(size_t(m->n_blocks_cap) * 4, 256), s));
-    if (!m->os_map || !m->block_masks) rc = SPC_ERR_NOMEM;
+    m->arrived = static_cast<int32_t*>(pool_alloc(SHARED_TILES * 4, s));
+    if (!m->os_map || !m->block_masks || !m->arrived) rc = SPC_ERR_NOMEM;
   }
   if (rc == SPC_OK && with_ws) {
     m->ws_in = twin->ws_out;
@@ -1156,7 +1166,7 @@ static int fill_from_twins(spc_kmap* const* ms, int count, hipStream_t s) {
       if (m->list_base) launch_list_base(m, m->ws_out, m->K3, fine, m->list_base, s);
       if (!m->os_map) continue;  // lists only: the twin's (its argument entry has no rows)
       b.a[i] = TransposedArgs{m->twin->inv_parent, fine->n_host < 0 ? fine->n_dev : nullptr,
-                              static_cast<int>(fine->n_host < 0 ? 0 : fine->n_host), m->K3, m->os_map, m->block_masks};
+                              static_cast<int>(fine->n_host < 0 ? 0 : fine->n_host), m->K3, m->os_map, m->block_masks, m->arrived};
       rows = std::max(rows, m->out_cap);
     }
     if (rows > 0)

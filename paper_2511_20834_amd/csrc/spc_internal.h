@@ -185,10 +185,11 @@ constexpr int BS_PART = 64;         // keys per rank workgroup
 constexpr int BS_PAD_KEYS = 32;     // all-ones keys kept behind the scattered keys
 struct BucketPlan {
   int n_wg, per, shift, n_bin;
+  bool sum;  // the scatter pass sums the counts itself (no column scan)
 };
 BucketPlan bucket_plan(int64_t n, int used_bits);
 size_t bucket_sort_ws_bytes(int key_bits, int64_t n);
-// coords -> sorted keys (+ permutation); enqueues four kernels (count, colscan, scatter, rank)
+// coords -> sorted keys (+ permutation); enqueues three kernels (count, scatter, rank), or four with the column scan of large tables
 int bucket_pack_sort(int key_bits, const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status,
                      void* keys_out, int32_t* perm_out, void* ws, hipStream_t s);
 // One level to produce: the sorted distinct values of keys_in & mask, and their count.
@@ -229,6 +230,8 @@ struct MapsReady {
 };
 }  // namespace spc
 
+constexpr int SHARED_TILES = 1024;  // tiles of a feature kernel that may be shared by several workgroups
+
 // ---------------------------------------------------------------- kernel map object
 struct spc_kmap {
   std::atomic<int> refs{1};
@@ -258,6 +261,7 @@ struct spc_kmap {
   uint8_t* tile_sub = nullptr;      // [n_tiles][K3][tile/32]: pairs of the tile before every 32-row block (scratch of the list build)
   int2* tile_pairs = nullptr;       // per search tile a slab of compacted (in, out) pairs (scratch of the list build)
   int64_t ws_stride = 0;            // entries between consecutive lists in ws_in / ws_out
+  int32_t* arrived = nullptr;       // [SHARED_TILES] counters of feature kernels whose workgroups share tiles: zeroed by the build, left zero
   int32_t* inv_parent = nullptr;    // strided maps, on request: for every INPUT voxel p its pair (out q, offset k) as q*K^3+k
   spc_kmap* twin = nullptr;         // transposed map derived from its strided twin (a reference is held): WS lists alias the twin's
   int tile = 0, n_tiles = 0;
