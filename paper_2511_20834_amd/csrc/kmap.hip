@@ -8,180 +8,123 @@
 // the other K-1 are resolved on consecutive positions; queries are formed by adding a
 // packed offset to a packed key.
 // What is different (CDNA4): a workgroup owns a contiguous tile of sorted output
-// voxels.  Because adding a constant keeps the order, all queries of a tile and group
-// fall into one contiguous window of the input array.  The 2 K^2 window bounds are found
-// by groups of lanes, 16-ary (4-ary for K >= 5), the first rounds on 256 probes shared by all
-// searches in LDS (one or two dependent loads for 2^18 keys instead of 18), the
-// windows are copied into LDS with coalesced loads, and every lane then searches in LDS
-// with the window state in scalar registers (the kernel is bound by instruction issue).
-// Windows that do not fit the LDS budget are searched in global memory, restricted to
-// the window, with the same code.
+// voxels, and each of its K waves one x offset.  Because adding a constant keeps the order, all
+// queries of a tile with one x offset fall into one contiguous window of the input array.  A wave finds
+// its window's two ends 32-ary, the first rounds on 256 probes in LDS (one or two dependent loads for 2^18 keys
+// instead of 18), copies the window, with the row numbers its hits will store, into LDS with
+// coalesced loads, and every lane then searches in LDS with the window state in scalar registers
+// (the kernel is bound by instruction issue).
+// Of windows that do not fit the LDS budget every step-th key is staged, and the last few
+// probes of their searches go to global memory.
 #include <algorithm>
 #include <map>
 #include <set>
 #include <tuple>
+#include <type_traits>
 
 #include "spc_internal.h"
 
 namespace spc {
 
-constexpr int SEARCH_THREADS = 256;       // 128 and 512 measured slower at every level size (10^5 .. 3 * 10^6 voxels)
-constexpr int WIN_CAP_BYTES = 20 * 1024;  // LDS budget for staged windows per workgroup (several workgroups share a CU)
-constexpr int N_PROBES = 256;             // first-round probes of the window-bound searches (a power of 4 and of 16)
+constexpr int N_PROBES = 256;  // first-round probes of the window-bound searches
 constexpr int MAX_K = 7;
 constexpr int WS_MAX_K3_SEARCH = MAX_K * MAX_K * MAX_K;
+#define SPC_GLOBAL __attribute__((address_space(1)))
 
 template <typename KeyT>
 struct SearchParams {
-  KeyT X0, dX;    // packed x offset of ix = 0 and its step per ix (wrapping arithmetic: the offsets of an axis are
-  KeyT Y0, dY;    // an arithmetic sequence); the same for y
-  KeyT zmin;      // packed smallest z offset
-  KeyT zstep;     // distance between consecutive z offsets (= input stride)
-  int zrev;       // 1: z offsets descend with iz (transposed maps)
-  unsigned long long need;  // bit g: group g = ix * K + iy has an offset in one of the two subsets
+  KeyT X0, dX;      // packed x offset of ix = 0 and its step per ix (wrapping arithmetic: the offsets of an axis are
+  KeyT Y0, dY;      // an arithmetic sequence); the same for y
+  KeyT ymin, ymax;  // packed smallest and largest y offset
+  KeyT zmin;        // packed smallest z offset
+  KeyT zstep;       // distance between consecutive z offsets (= input stride)
+  int zrev;         // 1: z offsets descend with iz (transposed maps)
+  unsigned need;    // bit ix: the offsets with this ix include some of one of the two subsets
 };
 
 __device__ inline int lanemask_lt_popc(unsigned long long m) {
   return __builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(m >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(m), 0));
 }
-
-// Window-bound searches over keys[0,n): groups of P lanes run one search each (64/P searches per wave
-// instruction), U passes of them interleaved so that the loads of all passes are in flight together.
-// upper=false: first index with key >= q; true: first index with key > q.  q and upper are the same
-// in all lanes of a group, and odd groups search upper bounds.  The first rounds need no memory
-// access: every search starts from the same N_PROBES probes (the last key of every 1/N_PROBES slice, loaded
-// once per workgroup into LDS), searched P-ary by the group's lanes with a ballot per round.  From then on
-// lane p of a group probes the last key of the p-th of P sub-slices, and the group's bits of the ballot
-// give the sub-slice.  The searches stop once every answer is known to within `slack` positions and return
-// the outer ends (slack 0: exact bounds): a window that is a few keys too wide costs less than
-// another round of dependent loads.  P = 16 reads 16 cache lines per search and round where a search
-// by the whole wave read 64, for the same number of dependent rounds at these sizes (2^18 keys:
-// 4096 -> 256 -> 16); with 25 groups of offsets the wave-wide form spent most of the kernel
-// fetching probe lines.
-template <typename KeyT>
-__device__ inline KeyT lane_value(KeyT v, int src_lane) {
-  if constexpr (sizeof(KeyT) == 4) {
-    return static_cast<KeyT>(__builtin_amdgcn_readlane(static_cast<int>(v), src_lane));
-  } else {
-    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(v)), src_lane);
-    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(v >> 32)), src_lane);
-    return (static_cast<KeyT>(hi) << 32) | lo;
-  }
+// OR over the lanes of each half of the wave; lanes 31 and 63 receive it.
+__device__ inline unsigned half_wave_or(unsigned x) {
+  x |= static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x111, 0xf, 0xf, true));  // row_shr 1, 2, 4, 8
+  x |= static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x112, 0xf, 0xf, true));
+  x |= static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x114, 0xf, 0xf, true));
+  x |= static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x118, 0xf, 0xf, true));
+  x |= static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x142, 0xf, 0xf, true));  // lane 15 of a row to the next row
+  return x;
 }
 
-template <typename KeyT, int P, int U>
-__device__ inline void group_bounds(const KeyT* __restrict__ keys, int n, const KeyT* s_probe, const KeyT (&q)[U], int (&res)[U],
-                                    int slack) {
-  constexpr int Q = 64 / P;
-  static_assert(Q % 2 == 0, "odd groups search upper bounds");
-  const int lane = threadIdx.x & 63, grp = lane / P, p = lane % P;
-  const bool upper = (grp & 1) != 0;
+// Both ends of a window by one wave: the lower half searches the first index with key >= q, the upper half the first
+// index with key > q (q per half).  The first rounds need no memory: both searches start from the same N_PROBES probes
+// (the last key of every 1/N_PROBES slice, in LDS), searched 32-ary by the half's lanes with a ballot per round.
+// From then on lane p of a half probes the last key of the p-th of 32 sub-slices, and the half's bits of the ballot
+// give the sub-slice.  The searches stop once both answers are known to within `slack` positions and return
+// the outer ends: a window that is a few keys too wide costs less than
+// another round of dependent loads.
+template <typename KeyT>
+__device__ inline int half_wave_bound(const SPC_GLOBAL KeyT* keys, int n, const KeyT* s_probe, KeyT q, int slack) {
+  constexpr int P = 32;
+  const int lane = threadIdx.x & 63, p = lane % P;
+  const bool upper = lane >= P;
   const int chunk0 = (n + N_PROBES - 1) / N_PROBES;
-  int lo[U], hi[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    // number of probes before the answer, P-ary in LDS (probe j is the last key of slice j; slices past the
-    // end of the array hold no probe and count as "not before")
-    int base = 0;
-    bool all = false;
-#pragma unroll
-    for (int sub = N_PROBES / P; sub >= 1; sub /= P) {
-      const int j = base + (p + 1) * sub - 1;
-      const KeyT pv = s_probe[j];
-      const bool pr = (long long)j * chunk0 < n && (upper ? (pv <= q[u]) : (pv < q[u]));
-      const int c = __popcll((__ballot(pr) >> (grp * P)) & ((1ull << P) - 1));
-      if (sub == N_PROBES / P && c == P) all = true;  // only the first round can find every probe before the answer
-      base += (c == P ? P - 1 : c) * sub;  // (when all are before, the value of base no longer matters)
-    }
-    const int c = all ? N_PROBES : base;
-    if ((long long)c * chunk0 >= n) {  // every slice lies before the answer (or there are no keys)
-      lo[u] = n;
-      hi[u] = n;
-    } else {
-      lo[u] = c * chunk0;
-      hi[u] = min(lo[u] + chunk0 - 1, n - 1);
-    }
-  }
-  auto unfinished = [&]() {
-    int maxlen = 0;
-#pragma unroll
-    for (int u = 0; u < U; ++u) maxlen = max(maxlen, hi[u] - lo[u]);
-    return __ballot(maxlen > slack) != 0;
+  auto before = [&](KeyT v) { return upper ? (v <= q) : (v < q); };
+  auto count = [&](bool pred) {
+    const unsigned long long b = __ballot(pred);
+    return __popc(upper ? static_cast<unsigned>(b >> 32) : static_cast<unsigned>(b));
   };
-  while (unfinished()) {  // every round shortens every unfinished search
-    bool pred[U];
-    int chunk[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int len = hi[u] - lo[u];
-      chunk[u] = (len + P - 1) / P;
-      const long long first = (long long)lo[u] + (long long)p * chunk[u];
-      // clamped, unconditional load: the loads of all passes are issued back to back
-      const long long idx = max(0ll, min(min(first + chunk[u] - 1, (long long)hi[u] - 1), (long long)n - 1));
-      const KeyT v = keys[idx];
-      pred[u] = len > 0 && first < hi[u] && (upper ? (v <= q[u]) : (v < q[u]));
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int len = hi[u] - lo[u];
-      const unsigned long long bal = __ballot(pred[u]);
-      if (len > 0) {
-        const int c = __popcll((bal >> (grp * P)) & ((1ull << P) - 1));
-        const int nlo = lo[u] + c * chunk[u];
-        if (c * chunk[u] >= len) {  // every sub-slice lies before the answer
-          lo[u] = hi[u];
-        } else {
-          hi[u] = min(nlo + chunk[u] - 1, hi[u] - 1);
-          lo[u] = nlo;
-        }
+  // number of probes before the answer (probe j is the last key of slice j)
+  const int n_probes = (n + chunk0 - 1) / max(chunk0, 1);
+  constexpr int STEP = N_PROBES / P;
+  const int j1 = (p + 1) * STEP - 1;
+  const int c1 = min(count(j1 < n_probes && before(s_probe[j1])), P - 1);
+  const int j2 = c1 * STEP + p;
+  const int c = c1 * STEP + count(p < STEP && j2 < n_probes && before(s_probe[min(j2, N_PROBES - 1)]));
+  int lo = n, hi = n;
+  if (c < n_probes) {
+    lo = c * chunk0;
+    hi = min(lo + chunk0 - 1, n - 1);
+  }
+  while (__ballot(hi - lo > slack) != 0) {  // every round shortens every unfinished search
+    const int len = hi - lo, chunk = (len + P - 1) / P;
+    const int first = min(lo + p * chunk, hi);
+    const KeyT v = keys[max(0, min(first + chunk - 1, hi - 1))];
+    const int m = count(len > 0 && first < hi && before(v));
+    if (len > 0) {
+      const int nlo = lo + m * chunk;
+      if (m * chunk >= len) {  // every sub-slice lies before the answer
+        lo = hi;
+      } else {
+        hi = min(nlo + chunk - 1, hi - 1);
+        lo = nlo;
       }
     }
   }
   // the answer lies in [lo, hi]: the low end for a window start, the high end for a window end
-#pragma unroll
-  for (int u = 0; u < U; ++u) res[u] = upper ? hi[u] : lo[u];
+  return upper ? hi : lo;
 }
 
-// Per-lane lower bound in a window of wsz keys (used for windows that stay in global memory).
-template <typename KeyT, typename Ptr>
-__device__ inline int lane_lower_bound(Ptr win, int wsz, KeyT q) {
-  int lo = 0, len = wsz;
-  while (len > 0) {
-    const int half = len >> 1;
-    const bool less = win[lo + half] < q;
-    lo = less ? lo + half + 1 : lo;
-    len = less ? len - half - 1 : half;
-  }
-  return lo;
-}
-
-// Groups whose LDS searches one lane keeps in flight together.  K <= 3: five (one lane's share of the nine groups
-// in one go; 44 registers with 32-bit keys, 64 with 64-bit keys).  Larger kernels: four (three and five measured
-// within 5 % on 240 k voxels, 5x5x5).
-constexpr int SEARCH_GB_SMALL = 5, SEARCH_GB_LARGE = 4;
-// Whether some part p < parts has `rem` groups left after whole batches of gb (its groups are p, p + parts, ... < G).
-__host__ __device__ constexpr bool remainder_occurs(int G, int parts, int gb, int rem) {
-  for (int p = 0; p < parts && p < G; ++p)
-    if (((G - p + parts - 1) / parts) % gb == rem) return true;
-  return false;
-}
-// Output voxels per search workgroup (a multiple of the wave size that divides SEARCH_THREADS).  Every tile pays for
-// its window bounds, their placement and the staging, so longer tiles do less work per voxel, and shorter ones
-// spread a small level over more compute units: 3x3x3, 128 -> 256 rows: 3 * 10^6 voxels 162 -> 140 us,
-// 10^6 60 -> 56 us, 120 k 16.8 -> 21 us; 5x5x5, 64 -> 128 rows: 240 k voxels 65 -> 62 us.
-constexpr int64_t SEARCH_LONG_TILE_FROM = 750000;  // output voxels from which K <= 3 takes 256-row tiles
-inline int search_tile(int K, int64_t n_out) { return K <= 3 ? (n_out >= SEARCH_LONG_TILE_FROM ? 256 : 128) : K <= 5 ? 128 : 64; }
+// Output voxels per search workgroup (a multiple of the wave size).
+// Short tiles spread a small level over the chip
+// and keep a workgroup's life short; longer ones pay for their windows less often: us, 64 / 128 / 256 rows, 3x3x3,
+// 30 k voxels 6.3 / 7.1 / 10.1, 120 k 12.0 / 12.4 / 16.1, 190 k 17.0 / 15.9 / 18.5, 500 k 34.6 / 27.0 / 24.8,
+// 3 * 10^6 179 / 122 / 103; 5x5x5, 64 / 128 rows: 30 k 10.6 / 13.1, 240 k 44 / 46.
+inline int search_tile(int K, int64_t n_out) { return K > 3 ? 64 : n_out >= 400000 ? 256 : n_out >= 150000 ? 128 : 64; }
+// Input keys (with their row numbers) that the window of one x offset may occupy in LDS.  A window holds what the tile's
+// rows can reach: about as many keys as the tile has rows (more where the input level is finer than the output level),
+// a few columns of the scene, and the slack of its bounds.
+constexpr int search_win_cap(int tile) { return tile == 64 ? 384 : tile == 128 ? 512 : 640; }
 
 // Two outputs, each for its own subset of the K^3 offsets (Section 5.4: all offsets in one of them for a single
 // dataflow; the dense offsets in the matrix and the sparse ones in the lists for the hybrid dual dataflow):
 //   os_k: columns of the blocked |V_q| x K^3 matrix M and bits of the per-block offset masks (M = NULL: none);
 //   ws_k: (PAIRS = true) weight-stationary lists.  They never pass through a matrix: a tile keeps, per (group,
-//         row), the position of its lower bound and the hit bits of the group's K queries in LDS (5 bytes where
+//         row), the place of its lower bound and the hit bits of the group's K queries in LDS (5 bytes where
 //         the matrix has 4 K), and once all groups are searched it writes the hits of the ws_k offsets as
 //         compacted (in, out) pairs, offset-major and row-ascending, into its own slab of `tile_pairs` (slab =
 //         tile * K^3 pairs, of which only the first sum-of-hits are touched); tile_counts gets the hits per
 //         (offset, tile).
-// Groups none of whose offsets is wanted are not searched (the second half of a symmetric map, for example).
+// x offsets none of whose columns is wanted are not searched (the second half of a symmetric map, for example).
 //
 // One launch searches NB maps of the same kernel size, block row y map y (NB = 1: a map of its own).  The maps of a
 // network's coarse levels are far too small to fill the chip, and a launch each costs more than their work: the nine
@@ -210,7 +153,7 @@ constexpr int SEARCH_BATCH = 8;
 // one to the compiler: loaded as such, the count and everything derived from it would be per-lane values.)
 __device__ inline int level_count(const int* n_d, int n_h) {
   int n = n_h;
-  if (n_d) n = *(const __attribute__((address_space(1))) int*)n_d;
+  if (n_d) n = *(const SPC_GLOBAL int*)n_d;
   return __builtin_amdgcn_readfirstlane(n);
 }
 template <typename KeyT, int NB>
@@ -218,405 +161,358 @@ struct SearchBatch {
   SearchArgs<KeyT> a[NB];
 };
 
+template <typename KeyT, int K, int TILE, bool PAIRS>
+constexpr size_t search_lds_bytes() {
+  return size_t(K) * (search_win_cap(TILE) * (sizeof(KeyT) + 4) + N_PROBES * sizeof(KeyT)) + (PAIRS ? size_t(K) * K * TILE * 5 : 0);
+}
+
+// Wave w of the K waves of a workgroup owns x offset w: it finds the window of the input array that the tile's queries
+// with this x offset can hit, stages it in LDS and searches the tile's rows, 64 at a time, for its K y offsets.  The
+// waves never wait for each other before the block masks are put together.
 template <typename KeyT, int K, int TILE, bool PAIRS, int NB>
-__global__ __launch_bounds__(SEARCH_THREADS) void kmap_search_kernel(const SearchBatch<KeyT, NB> batch) {
+__global__ __launch_bounds__(64 * K) void kmap_search_kernel(const SearchBatch<KeyT, NB> batch) {
   const SearchArgs<KeyT>& args = batch.a[NB == 1 ? 0 : blockIdx.y];
-  const KeyT* __restrict__ in_keys = args.in_keys;
-  const KeyT* __restrict__ out_keys = args.out_keys;
-  int32_t* __restrict__ M = args.M;
-  uint32_t* __restrict__ block_masks = args.block_masks;
-  int32_t* __restrict__ tile_counts = args.tile_counts;
-  const int32_t* __restrict__ in_perm = args.in_perm;
-  int2* __restrict__ tile_pairs = args.tile_pairs;
-  int32_t* __restrict__ inv_parent = args.inv_parent;
+  const SPC_GLOBAL KeyT* in_keys = (const SPC_GLOBAL KeyT*)args.in_keys;
+  const SPC_GLOBAL KeyT* out_keys = (const SPC_GLOBAL KeyT*)args.out_keys;
+  const SPC_GLOBAL int32_t* in_perm = (const SPC_GLOBAL int32_t*)args.in_perm;
+  SPC_GLOBAL char* M = (SPC_GLOBAL char*)args.M;
+  SPC_GLOBAL int32_t* inv_parent = (SPC_GLOBAL int32_t*)args.inv_parent;
   const SearchParams<KeyT>& sp = args.sp;
   const KMask &os_k = args.os_k, &ws_k = args.ws_k;
-  const int n_tiles_cap = args.n_tiles_cap;
   constexpr int G = K * K, K3 = K * K * K;
-  constexpr int tile = TILE;
-  constexpr int SEARCH_GB = K <= 3 ? SEARCH_GB_SMALL : SEARCH_GB_LARGE;
-  constexpr int MW = (K3 + 31) / 32;   // mask words per 32-row block
-  constexpr int MAX_BLOCKS = TILE / 32;
-  constexpr int WIN_CAP = WIN_CAP_BYTES / sizeof(KeyT);
-  constexpr int NW = SEARCH_THREADS / 64;
-  // lanes per window-bound search: with many groups of offsets the probe lines fetched count for more than the
-  // number of dependent rounds (240 k voxels, 5x5x5: 16 lanes 98.6 us, 8 lanes 94.6, 4 lanes 92.2)
-  constexpr int BOUND_P = G <= 9 ? 16 : 4;
-  constexpr int BOUND_SLACK = G <= 9 ? 32 : 16;  // extra keys per window end: 2 * G * slack must stay small next to WIN_CAP
+  constexpr int MW = (K3 + 31) / 32;  // mask words per 32-row block
+  constexpr int CHUNKS = TILE / 64, MAX_BLOCKS = TILE / 32;
+  constexpr int NJ = K <= 5 ? K : 4;  // groups (y offsets) whose searches are in flight together
+  static_assert(NJ * K <= 32, "the hits of a batch fit one register");
+  constexpr int WIN_CAP = search_win_cap(TILE);
+  constexpr int PAD = K;  // all-ones keys behind the window: reads behind a lower bound need no bound
+  constexpr int BOUND_SLACK = 32;
+  constexpr unsigned KB = sizeof(KeyT);
   extern __shared__ __align__(16) unsigned char smem[];
-  KeyT* okeys = reinterpret_cast<KeyT*>(smem);   // [tile]
-  KeyT* win = okeys + tile;                      // [WIN_CAP + MAX_K]: staged windows, and room for reads behind the last one
-  int32_t* s_pos = reinterpret_cast<int32_t*>(win + WIN_CAP + MAX_K);       // PAIRS: [G][tile] input position of the group's lower bound
-  uint8_t* s_hit = reinterpret_cast<uint8_t*>(s_pos + G * tile);      // PAIRS: [G][tile] bit t: the group's t-th query (ascending z) hit
-  __shared__ int s_off[PAIRS ? K3 + 1 : 1];                           // PAIRS: where every offset's pairs start in the tile's slab
-  __shared__ KeyT s_probe[N_PROBES];
-  __shared__ int4 s_grp[G];  // window of group g: x = first input position, y = keys, z = place in `win` (-1: not staged)
-  __shared__ int s_bound[2 * G];
-  __shared__ int s_cnt[K3];
+  __shared__ int s_off[PAIRS ? K3 + 1 : 1];  // PAIRS: where every offset's pairs start in the tile's slab
+  __shared__ int s_cnt[PAIRS ? K3 : 1];
   __shared__ unsigned s_mask[MAX_BLOCKS * MW];
-  __shared__ KeyT s_gd[G];  // packed (dx,dy,zmin) offset of every group
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int ix = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int32_t* wval = reinterpret_cast<int32_t*>(smem) + ix * WIN_CAP;                                     // row numbers of the staged keys
+  KeyT* win = reinterpret_cast<KeyT*>(smem + size_t(K) * WIN_CAP * 4) + ix * WIN_CAP;                  // staged window
+  KeyT* s_probe = reinterpret_cast<KeyT*>(smem + size_t(K) * WIN_CAP * (4 + KB)) + ix * N_PROBES;
+  unsigned char* s_rec = smem + size_t(K) * (WIN_CAP * (4 + KB) + N_PROBES * KB);
+  int32_t* s_pos = reinterpret_cast<int32_t*>(s_rec);             // PAIRS: [G][TILE] place of the group's lower bound among the staged row numbers, or ~position in the input
+  uint8_t* s_hit = reinterpret_cast<uint8_t*>(s_pos + G * TILE);  // PAIRS: [G][TILE] bit t: the group's t-th query (ascending z) hit
 
   const int n_in = level_count(args.n_in_d, args.n_in_h);
   const int n_out = level_count(args.n_out_d, args.n_out_h);
-  const int i0 = blockIdx.x * tile;
+  const int i0 = blockIdx.x * TILE;
   if (i0 >= n_out) return;  // whole workgroup leaves together
-  const int rows = min(tile, n_out - i0);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int rows = min(TILE, n_out - i0);
   if (blockIdx.x == 0)
-    for (int j = tid; j < SHARED_TILES; j += SEARCH_THREADS) args.arrived[j] = 0;
+    for (int j = tid; j < SHARED_TILES; j += 64 * K) ((SPC_GLOBAL int32_t*)args.arrived)[j] = 0;
+  if constexpr (PAIRS)
+    for (int k = tid; k < K3; k += 64 * K) s_cnt[k] = 0;
+  for (int k = tid; k < MAX_BLOCKS * MW; k += 64 * K) s_mask[k] = 0u;
 
-  // first-round probes of the window-bound searches (the same N_PROBES keys for everybody: L2-resident)
-  {
-    const int chunk0 = (n_in + N_PROBES - 1) / N_PROBES;
-    for (int j = tid; j < N_PROBES; j += SEARCH_THREADS)
-      s_probe[j] = (n_in > 0 && (long long)j * chunk0 < n_in) ? in_keys[min((long long)(j + 1) * chunk0 - 1, (long long)n_in - 1)] : KeyT(0);
-  }
-
-  for (int v = tid; v < rows; v += SEARCH_THREADS) okeys[v] = out_keys[i0 + v];
-  for (int k = tid; k < K3; k += SEARCH_THREADS) s_cnt[k] = 0;
-  for (int k = tid; k < MAX_BLOCKS * MW; k += SEARCH_THREADS) s_mask[k] = 0u;
-  for (int k = tid; k < 2 * G; k += SEARCH_THREADS) s_bound[k] = 0;
-  if (tid < G) s_gd[tid] = sp.X0 + KeyT(tid / K) * sp.dX + sp.Y0 + KeyT(tid % K) * sp.dY + sp.zmin;
-  __syncthreads();
-  const KeyT kfirst = okeys[0], klast = okeys[rows - 1];
+  KeyT okey[CHUNKS];
+#pragma unroll
+  for (int c = 0; c < CHUNKS; ++c) okey[c] = out_keys[i0 + min(c * 64 + lane, rows - 1)];  // lanes past the end repeat the last row
+  const KeyT xoff = sp.X0 + KeyT(ix) * sp.dX + sp.zmin;
   const KeyT zspan = KeyT(K - 1) * sp.zstep;
 
-  // ---- window bounds: search s = 2*g + side; pass u of wave w runs searches (u*NW + w)*Q .. +Q-1, one per group
-  // of BOUND_P lanes (searches past the last one repeat it and are not recorded)
-  {
-    constexpr int Q = 64 / BOUND_P;
-    constexpr int U = (2 * G + NW * Q - 1) / (NW * Q);
-    const int grp = lane / BOUND_P;
-    auto run_bounds = [&](auto U_) {
-      constexpr int UU = decltype(U_)::value;
-      KeyT q[UU];
-      int res[UU];
+  // ---- window: adding a constant keeps the order, so what the tile's queries with one x offset can hit is one
+  // contiguous piece of the input array (y and z offsets only widen it by a few columns of the scene)
+  int wlo = 0, wsz = n_in;  // a small level is one window as a whole
+  if (n_in + PAD > WIN_CAP) {
+    const int chunk0 = (n_in + N_PROBES - 1) / N_PROBES;
+    KeyT pr[N_PROBES / 64];
 #pragma unroll
-      for (int u = 0; u < UU; ++u) {
-        const int sc = min((u * NW + wave) * Q + grp, 2 * G - 1);
-        const KeyT d = s_gd[sc >> 1];
-        q[u] = (grp & 1) ? KeyT(klast + d + zspan) : KeyT(kfirst + d);
-      }
-      group_bounds<KeyT, BOUND_P, UU>(in_keys, n_in, s_probe, q, res, BOUND_SLACK);
+    for (int u = 0; u < N_PROBES / 64; ++u)  // (slices past the end are never looked at)
+      pr[u] = in_keys[min((long long)(u * 64 + lane + 1) * chunk0 - 1, (long long)n_in - 1)];
+    const KeyT kfirst = out_keys[i0], klast = out_keys[i0 + rows - 1];
 #pragma unroll
-      for (int u = 0; u < UU; ++u) {
-        const int sc = (u * NW + wave) * Q + grp;
-        // only groups with a wanted offset are searched: the others keep empty windows
-        if (lane % BOUND_P == 0 && sc < 2 * G && ((sp.need >> (sc >> 1)) & 1ull)) s_bound[sc] = res[u];
-      }
-    };
-    // the last pass is short of searches: only the waves that have one there run it
-    if (U == 1 || ((U - 1) * NW + wave) * Q < 2 * G) run_bounds(std::integral_constant<int, U>{});
-    else run_bounds(std::integral_constant<int, (U > 1 ? U - 1 : 1)>{});
+    for (int u = 0; u < N_PROBES / 64; ++u) s_probe[u * 64 + lane] = pr[u];
+    __builtin_amdgcn_wave_barrier();
+    const KeyT q = lane >= 32 ? KeyT(klast + xoff + sp.ymax + zspan) : KeyT(kfirst + xoff + sp.ymin);
+    const int b = half_wave_bound<KeyT>(in_keys, n_in, s_probe, q, BOUND_SLACK);
+    wlo = __builtin_amdgcn_readlane(b, 0);
+    wsz = max(0, __builtin_amdgcn_readlane(b, 32) - wlo);
   }
-  __syncthreads();
+  if (!((sp.need >> ix) & 1u)) wsz = 0;
+  // a window that does not fit is sampled: LDS then holds the last key of every `step` keys
+  const int step = max(1, (wsz + WIN_CAP - PAD - 1) / (WIN_CAP - PAD));
+  const bool sampled = step > 1;
 
-  // ---- window placement in LDS: a prefix sum over the groups by wave 0; groups whose window
-  // ends beyond the LDS budget stay in global memory
-  if (wave == 0) {
-    const int lo = lane < G ? s_bound[2 * lane] : 0;
-    const int sz = lane < G ? max(0, s_bound[2 * lane + 1] - lo) : 0;
-    int incl = sz;
-    for (int d = 1; d < 64; d <<= 1) {
-      const int y = __shfl_up(incl, d, 64);
-      if (lane >= d) incl += y;
-    }
-    if (lane < G) s_grp[lane] = make_int4(lo, sz, incl <= WIN_CAP ? incl - sz : -1, 0);
-  }
-  __syncthreads();
-
-  // ---- staging, window after window.  A team of lanes copies a window, lane e its keys e, e + team size, ...:
-  // the whole workgroup for the long windows of 128-row tiles, a wave for the short ones of 64-row tiles (with
-  // 25 or 49 groups a workgroup-wide copy would leave three lanes in four idle), the waves then taking different
-  // groups.  Window positions and sizes are read into scalar registers, so a copy costs a compare and two
-  // address additions per lane, and the loads of all of a team's windows are in flight together.
-  {
-    constexpr int TEAM = tile >= 128 ? SEARCH_THREADS : 64;  // lanes per window
-    const __amdgpu_buffer_rsrc_t keys_rsrc =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<KeyT*>(in_keys), 0, sizeof(KeyT) == 4 ? n_in * 4 : 0, 0x00020000);
-    constexpr int N_TEAMS = SEARCH_THREADS / TEAM;
-    constexpr int STAGE_U = (G + N_TEAMS - 1) / N_TEAMS;       // windows per team
-    const int team = __builtin_amdgcn_readfirstlane(tid / TEAM), lt = tid % TEAM;
-    KeyT tmp[STAGE_U];
-    int woff[STAGE_U], wsz[STAGE_U], wlo[STAGE_U];
-    int longest = 0;
+  // ---- staging: keys and row numbers (the caller's, through the sort permutation, or positions)
+  const int staged = (wsz + step - 1) / step;
+  if (sampled) {
+    for (int e = lane; e < staged + PAD; e += 64) win[e] = e < staged ? in_keys[wlo + min((e + 1) * step, wsz) - 1] : ~KeyT(0);
+  } else {
+    constexpr int U = 4;
+    for (int e0 = lane; e0 < wsz + PAD; e0 += 64 * U) {
+      KeyT key[U];
+      int32_t val[U];
+      if (wsz > 0) {
 #pragma unroll
-    for (int i = 0; i < STAGE_U; ++i) {
-      const int g = team + i * N_TEAMS;
-      const int4 gw = s_grp[min(g, G - 1)];
-      wlo[i] = __builtin_amdgcn_readfirstlane(gw.x);
-      woff[i] = __builtin_amdgcn_readfirstlane(gw.z);
-      wsz[i] = g < G && woff[i] >= 0 ? __builtin_amdgcn_readfirstlane(gw.y) : 0;
-      longest = max(longest, wsz[i]);
-      // (through a descriptor of the n_in keys: lanes past the window read a neighbouring key or, past the
-      // array, zero; nothing of that is stored)
-      if constexpr (sizeof(KeyT) == 4) {
-        tmp[i] = __builtin_amdgcn_raw_buffer_load_b32(keys_rsrc, lt * 4, wlo[i] * 4, 0);
-      } else {
-        tmp[i] = 0;
-        if (lt < wsz[i]) tmp[i] = (in_keys + wlo[i])[lt];
+        for (int u = 0; u < U; ++u) key[u] = in_keys[wlo + min(e0 + u * 64, wsz - 1)];
+        if (in_perm) {
+#pragma unroll
+          for (int u = 0; u < U; ++u) val[u] = in_perm[wlo + min(e0 + u * 64, wsz - 1)];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int e = e0 + u * 64;
+        if (e < wsz + PAD) {
+          win[e] = e < wsz ? key[u] : ~KeyT(0);
+          wval[e] = in_perm ? val[u] : wlo + e;
+        }
       }
     }
-#pragma unroll
-    for (int i = 0; i < STAGE_U; ++i)
-      if (lt < wsz[i]) (win + woff[i])[lt] = tmp[i];
-    if (longest > TEAM) {  // rare
-#pragma unroll
-      for (int i = 0; i < STAGE_U; ++i)
-        for (int e = lt + TEAM; e < wsz[i]; e += TEAM) (win + woff[i])[e] = (in_keys + wlo[i])[e];
-    }
   }
-  __syncthreads();
+  __syncthreads();  // the counters and masks are cleared (the wave's own window needs no barrier)
 
-  // ---- per-lane searches.  A wave holds 64 consecutive output voxels and takes NJ groups of offsets at a time,
-  // their searches interleaved (independent LDS chains hide each other's latency).  The phase is bound by the
-  // number of vector instructions, so everything that is the same for the 64 lanes lives in scalar registers:
-  // a group's window (LDS position, size, position in the input array) and the remaining length n of its search.
+  // ---- per-lane searches, 64 output voxels at a time, the K y offsets interleaved (independent LDS chains hide each
+  // other's latency).  The phase is bound by the number of instructions, so everything that is the same for the 64
+  // lanes lives in scalar registers.
   // A search keeps the LDS byte address `ab` of the key before its lower bound's current base; a round probes the
   // key half = ceil(n/2) further on and moves the base behind it when that key is smaller than the query, which
   // leaves floor(n/2) keys: one addition, one compare and one select per round, no bounds to check (a probe never
   // leaves the window; finished searches probe the key at `ab` again, which changes nothing).
-  const int64_t b0 = int64_t(i0) >> 5;
-  const int rows32 = (rows + 31) & ~31;
-  constexpr int parts = SEARCH_THREADS / tile;     // threads per output voxel
-  const int v = tid % tile;
-  const int part = __builtin_amdgcn_readfirstlane(tid / tile);  // uniform in a wave (tile is a multiple of 64)
-  const bool act = v < rows;
-  const bool stored = v < rows32;                  // rows past the end of the last block hold -1
-  const KeyT okey = okeys[min(v, rows - 1)];       // lanes past the end repeat the last row; their results are dropped
-  const int v0 = __builtin_amdgcn_readfirstlane(v & ~63);
-  const int bl0 = v0 >> 5;                         // the wave's two 32-row blocks: bl0, bl0 + 1
-  int32_t* Mw = M + (b0 + bl0) * int64_t(K3) * 32;  // uniform; lane l writes at l%32 of block bl0 + l/32
-  const unsigned lane_off = (unsigned(lane >> 5) * unsigned(K3 * 32) + unsigned(lane & 31)) * 4u;  // bytes
   // (pointers typed as LDS addresses: 32 bits wide, and every access through them is an LDS instruction)
   using LdsBytes = const __attribute__((address_space(3))) unsigned char*;
   using LdsKey = const __attribute__((address_space(3))) KeyT*;
-  const LdsBytes lbase = (LdsBytes)smem;
-  constexpr unsigned KB = sizeof(KeyT);
-  unsigned hbits[MW];  // offsets this lane's row has hit, among those of the matrix (the block masks are their OR over 32 lanes)
+  using LdsInt = const __attribute__((address_space(3))) int32_t*;
+  const LdsBytes lwin = (LdsBytes)(const unsigned char*)win, lval = (LdsBytes)(const unsigned char*)wval;
+  const unsigned lane_off = (unsigned(lane >> 5) * unsigned(K3 * 32) + unsigned(lane & 31)) * 4u;  // bytes
+  const int64_t b0 = int64_t(i0) >> 5;
+  // n bits of a subset from bit b on (the words are picked with scalar selects: static indices keep the masks in scalar registers)
+  auto subset_bits = [&](const KMask& m, int b) {
+    unsigned lo = 0u, hi = 0u;
 #pragma unroll
-  for (int w = 0; w < MW; ++w) hbits[w] = 0u;
-  // subset tests on the kernel arguments: the word is picked with scalar selects (static indices keep the masks in
-  // scalar registers), so a test costs no LDS access
-  auto subset_word = [&](const KMask& m, int wd) {
-    unsigned x = m.w[0];
-#pragma unroll
-    for (int i = 1; i < MW; ++i) x = wd == i ? m.w[i] : x;
-    return x;
-  };
-  // the K bits of group g (offsets g*K .. g*K + K - 1) in a subset
-  auto subset_field = [&](const KMask& m, int g) {
-    const int wd = (g * K) >> 5, sh = (g * K) & 31;
-    const unsigned long long two = (static_cast<unsigned long long>(wd + 1 < MW ? subset_word(m, wd + 1) : 0u) << 32) | subset_word(m, wd);
-    return static_cast<unsigned>(two >> sh) & ((1u << K) - 1u);
-  };
-  // row numbers are fetched through a buffer descriptor of in_perm's n_in entries: the hardware returns 0 for
-  // positions past the end (candidates behind the last key of the array), so no lane needs a bounds check
-  const __amdgpu_buffer_rsrc_t perm_rsrc =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(in_perm), 0, in_perm ? n_in * 4 : 0, 0x00020000);
-  const int col0 = sp.zrev ? K - 1 : 0, cstep = sp.zrev ? -1 : 1;  // column of a group's query t: col0 + t * cstep
-  auto search_groups = [&](auto NJ_, int gb) {
-    constexpr int NJ = decltype(NJ_)::value;
-    int g[NJ], wsz[NJ], wlo[NJ], n[NJ];
-    bool glob[NJ];
-    LdsBytes ab0[NJ], ab[NJ];
-    KeyT q0[NJ];
-    int nmax = 0;
-    bool any_glob = false;
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      g[j] = gb + j * parts;  // < G (the caller counts the groups)
-      const int4 gw = s_grp[g[j]];  // (groups without a wanted offset have empty windows)
-      wlo[j] = __builtin_amdgcn_readfirstlane(gw.x);
-      wsz[j] = __builtin_amdgcn_readfirstlane(gw.y);
-      const int woff = __builtin_amdgcn_readfirstlane(gw.z);
-      glob[j] = woff < 0 && wsz[j] > 0;  // window kept in global memory
-      any_glob |= glob[j];
-      n[j] = woff >= 0 ? wsz[j] : 0;
-      // LDS address of the key before the window: the output keys lie before the windows, so this is a valid
-      // address for the first window too
-      ab0[j] = lbase + (unsigned(tile) + unsigned(max(woff, 0))) * KB - KB;
-      ab[j] = ab0[j];
-      q0[j] = okey + s_gd[g[j]];
-      nmax = max(nmax, n[j]);
+    for (int i = 0; i < MW; ++i) {
+      lo = (b >> 5) == i ? m.w[i] : lo;
+      hi = (b >> 5) + 1 == i ? m.w[i] : hi;
     }
-    for (int rounds = nmax > 0 ? 32 - __builtin_clz(nmax) : 0; rounds > 0; --rounds) {
-      LdsBytes cand[NJ];
-      KeyT kv[NJ];
+    return static_cast<unsigned>(((static_cast<unsigned long long>(hi) << 32) | lo) >> (b & 31));
+  };
+  auto search_groups = [&](auto N_, auto IY_, int c, KeyT ok) {
+    constexpr int N = decltype(N_)::value, IY = decltype(IY_)::value;  // y offsets IY .. IY + N - 1
+    const int v = c * 64 + lane;
+    const bool act = v < rows;
+    LdsBytes ab[N];
+    KeyT q0[N];
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const int rest = n[j] >> 1, half = n[j] - rest;  // half = ceil(n / 2)
-        n[j] = rest;
+    for (int j = 0; j < N; ++j) {
+      ab[j] = lwin - KB;  // the key before the window
+      q0[j] = ok + (xoff + sp.Y0 + KeyT(IY + j) * sp.dY);
+    }
+    KeyT d[N][K];  // key - smallest query, for the K keys from the lower bound on, and their row numbers: the K
+    int32_t val[N][K];  // z-consecutive queries of a group hit consecutive positions (keys are sorted integers whose z components are multiples of the input stride, Section 5.2)
+    for (int n = staged; n > 0;) {
+      const int rest = n >> 1, half = n - rest;  // half = ceil(n / 2)
+      n = rest;
+      LdsBytes cand[N];
+      KeyT kv[N];
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
         cand[j] = ab[j] + unsigned(half) * KB;
         kv[j] = *(LdsKey)cand[j];
       }
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) ab[j] = kv[j] < q0[j] ? cand[j] : ab[j];
+      for (int j = 0; j < N; ++j) ab[j] = kv[j] < q0[j] ? cand[j] : ab[j];
     }
-    // the K keys from each lower bound on: the K z-consecutive queries of a group hit consecutive
-    // positions (keys are sorted integers whose z components are multiples of the input stride,
-    // Section 5.2).  Reads may run up to K - 1 keys past the window, into the next window or the padding
-    // behind the last one; `rem` below says how many of them belong to the window.
-    KeyT w[NJ][K];
-    int pos[NJ];
+    if (!sampled) {
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
+      for (int j = 0; j < N; ++j) {
+        LdsBytes vb;
+        if constexpr (KB == 4) vb = ab[j] + (lval - lwin) + 4;
+        else vb = lval + (unsigned(ab[j] - lwin + KB) >> 1);
 #pragma unroll
-      for (int i = 0; i < K; ++i) w[j][i] = *(LdsKey)(ab[j] + (i + 1) * KB);
-      pos[j] = static_cast<int>((ab[j] - ab0[j]) / KB);
-    }
-    if (any_glob) {  // windows that stayed in global memory (rare): per-lane lower bound, same K keys
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-        if (glob[j]) {
-          pos[j] = lane_lower_bound<KeyT>(in_keys + wlo[j], wsz[j], q0[j]);
-#pragma unroll
-          for (int i = 0; i < K; ++i) w[j][i] = in_keys[wlo[j] + min(pos[j] + i, wsz[j] - 1)];
+        for (int i = 0; i < K; ++i) {
+          d[j][i] = *(LdsKey)(ab[j] + (i + 1) * KB);
+          val[j][i] = *(LdsInt)(vb + i * 4);
         }
-    }
-    // what the map stores for position rpos + i: the position, or the caller's row number of that voxel.  The
-    // row numbers of all NJ groups are requested before the first of them is used.
-    int rpos[NJ];
-    int32_t val[NJ][K];
-    bool valid[NJ][K];
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int rem = wsz[j] - pos[j];  // window keys from the lower bound on
-      rpos[j] = wlo[j] + pos[j];        // the lower bound's position in the input array
-#pragma unroll
-      for (int i = 0; i < K; ++i) {
-        valid[j][i] = act && i < rem;
-        val[j][i] = rpos[j] + i;
+        if constexpr (PAIRS) s_pos[((ix * K) + IY + j) * TILE + v] = static_cast<int>(unsigned(ab[j] - lwin + KB) / KB) + ix * WIN_CAP;
       }
-      if (in_perm) {
+    } else {  // the samples say which `step` keys of the array the lower bound is among: the rest of the way in global memory
+      // (large kernels: one group after the other, in rolled rounds, so that this rare path does not set the registers)
+      const SPC_GLOBAL KeyT* wkeys = in_keys + wlo;
+      constexpr int SIDE = K < 5 ? N : 1;
 #pragma unroll
-        for (int i = 0; i < K; ++i) val[j][i] = __builtin_amdgcn_raw_buffer_load_b32(perm_rsrc, rpos[j] * 4 + i * 4, 0, 0);
+      for (int j0 = 0; j0 < N; j0 += SIDE) {
+        int pos[SIDE], len[SIDE];
+#pragma unroll
+        for (int u = 0; u < SIDE; ++u) {
+          pos[u] = static_cast<int>(unsigned(ab[j0 + u] - lwin + KB) / KB) * step;
+          len[u] = max(0, min(step - 1, wsz - pos[u]));
+        }
+        for (int left = step; left > 1; left = (left + 1) >> 1) {
+          KeyT kv[SIDE];
+#pragma unroll
+          for (int u = 0; u < SIDE; ++u) kv[u] = wkeys[unsigned(min(pos[u] + (len[u] >> 1), wsz - 1))];
+#pragma unroll
+          for (int u = 0; u < SIDE; ++u) {
+            const int half = len[u] >> 1;
+            const bool less = len[u] > 0 && kv[u] < q0[j0 + u];
+            pos[u] += less ? half + 1 : 0;
+            len[u] = less ? len[u] - half - 1 : half;
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < SIDE; ++u) {
+          const int j = j0 + u;
+#pragma unroll
+          for (int i = 0; i < K; ++i) {
+            const bool in = pos[u] + i < wsz;
+            const unsigned at = min(pos[u] + i, wsz - 1);
+            const KeyT key = wkeys[at];
+            d[j][i] = in ? key : KeyT(q0[j] - 1);
+            val[j][i] = in_perm ? (in_perm + wlo)[at] : wlo + static_cast<int>(at);
+          }
+          if constexpr (PAIRS) s_pos[((ix * K) + IY + j) * TILE + v] = ~(wlo + pos[u]);
+        }
+        if constexpr (SIDE < N) asm volatile("" ::: "memory");
       }
     }
+    // A query that reaches the all-ones key could take the padding behind its window for a voxel, and a lane past the
+    // last row must not hit at all: waves with such lanes look at every key's place.
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      // query t (ascending z) sits i <= t positions behind the lower bound, i = number of earlier queries that hit
-      KeyT d[K];
+    for (int j = 0; j < N; ++j) {
+      if (__ballot(KeyT(~q0[j]) <= zspan || !act)) {
+        const int rem = static_cast<int>(unsigned(lwin + unsigned(wsz) * KB - KB - ab[j]) / KB);  // keys of the window from the lower bound on
 #pragma unroll
-      for (int i = 0; i < K; ++i) d[i] = w[j][i] - q0[j];
+        for (int i = 0; i < K; ++i) d[j][i] = act && (sampled || i < rem) ? d[j][i] : KeyT(q0[j] - 1);
+      }
+    }
+    constexpr int BIT0 = IY * K;
+    const unsigned osb = M ? subset_bits(os_k, ix * G + BIT0) : 0u, wsb = PAIRS ? subset_bits(ws_k, ix * G + BIT0) : 0u;
+    unsigned hb = 0u;  // bit j * K + t: query t of group j hit
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      // query t (ascending z) sits i <= t positions behind the lower bound, i = number of earlier queries that hit:
+      // the key looked at moves on by one where a query has hit
       int32_t r[K];
       bool hit[K];
-      unsigned hm = 0u;  // bit t: query t hit
+#pragma unroll
+      for (int i = 0; i < K; ++i) d[j][i] -= q0[j];
 #pragma unroll
       for (int t = 0; t < K; ++t) {
-        r[t] = -1;
-        hit[t] = false;
-        const KeyT dt = KeyT(t) * sp.zstep;
+        hit[t] = d[j][0] == KeyT(t) * sp.zstep;
+        r[t] = hit[t] ? val[j][0] : -1;
 #pragma unroll
-        for (int i = 0; i <= t; ++i) {
-          const bool m = valid[j][i] && d[i] == dt;
-          r[t] = m ? val[j][i] : r[t];
-          hit[t] = hit[t] || m;
+        for (int i = 0; i + 1 < K - t; ++i) {
+          d[j][i] = hit[t] ? d[j][i + 1] : d[j][i];
+          val[j][i] = hit[t] ? val[j][i + 1] : val[j][i];
         }
-        if constexpr (PAIRS) hm |= hit[t] ? 1u << t : 0u;
       }
-      const int gj = g[j];
-      // column of query t: offsets of a group ascend with z, queries too unless the z offsets descend with iz
-      auto col = [&](int t) { return col0 + t * cstep; };
-      // inverse of a strided map whose offsets partition the inputs (K = layer stride): every input voxel is hit by
+      unsigned hm = 0u;
+#pragma unroll
+      for (int t = K - 1; t >= 0; --t) hm = hm + hm + (hit[t] ? 1u : 0u);
+      hb |= hm << (j * K);
+      const int gj = ix * K + IY + j;
+      // column of query t: offsets of a group ascend with z, queries too unless the z offsets descend with iz.
+      // Inverse of a strided map whose offsets partition the inputs (K = layer stride): every input voxel is hit by
       // exactly one (output, offset), which is all its transposed twin needs (such maps are built without a
       // row permutation, so r holds positions)
       if (inv_parent) {
 #pragma unroll
         for (int t = 0; t < K; ++t)
-          if (hit[t]) inv_parent[r[t]] = (i0 + v) * K3 + gj * K + col(t);
+          if (hit[t]) inv_parent[r[t]] = (i0 + v) * K3 + gj * K + (sp.zrev ? K - 1 - t : t);
       }
       if constexpr (PAIRS) {
         // the tile's records stay in LDS; hits are counted per offset (a wave speaks for its 64 rows)
-        const unsigned wsf = subset_field(ws_k, gj);
-        s_pos[gj * tile + v] = rpos[j];
-        s_hit[gj * tile + v] = static_cast<uint8_t>(hm);
+        s_hit[gj * TILE + v] = static_cast<uint8_t>(hm);
+        if ((wsb >> (j * K)) & ((1u << K) - 1u)) {
 #pragma unroll
-        for (int t = 0; t < K; ++t) {
-          if (!((wsf >> col(t)) & 1u)) continue;
-          const unsigned long long bal = __ballot(hit[t]);
-          if (bal && lane == 0) atomicAdd(&s_cnt[gj * K + col(t)], __popcll(bal));
+          for (int t = 0; t < K; ++t) {
+            const int col = sp.zrev ? K - 1 - t : t;
+            const unsigned long long bal = __ballot(hit[t]);
+            if (bal && ((wsb >> (j * K + col)) & 1u) && lane == 0) atomicAdd(&s_cnt[gj * K + col], __popcll(bal));
+          }
         }
       }
-      if (!M) continue;  // no offset goes to the matrix (uniform over the launch)
-      const unsigned osf = subset_field(os_k, gj);
-      // Every store into the blocked map M[block][k][32] is two full 128-byte segments.
-      if (stored) {
-        char* Mb = reinterpret_cast<char*>(Mw);  // + a 32-bit offset: column k starts k * 128 bytes into the block
-        if (osf == (1u << K) - 1u) {  // all of the group's offsets (the usual case)
+      const unsigned osf = (osb >> (j * K)) & ((1u << K) - 1u);
+      if (!M || osf == 0u) continue;  // no offset goes to the matrix (uniform)
+      // Every store into the blocked map M[block][k][32] is two full 128-byte segments; rows past the end of the last
+      // block hold -1.
+      if (c * 64 + (lane & 32) < rows) {
+        SPC_GLOBAL char* Mg = M + ((b0 + c * 2) * int64_t(K3) + gj * K) * 128;  // uniform
+        if (!sp.zrev && osf == (1u << K) - 1u) {  // the usual case
 #pragma unroll
-          for (int t = 0; t < K; ++t) *reinterpret_cast<int32_t*>(Mb + (lane_off + unsigned(gj * K + col(t)) * 128u)) = r[t];
+          for (int t = 0; t < K; ++t) *(SPC_GLOBAL int32_t*)(Mg + t * 128 + lane_off) = r[t];
         } else {
 #pragma unroll
-          for (int t = 0; t < K; ++t)
-            if ((osf >> col(t)) & 1u) *reinterpret_cast<int32_t*>(Mb + (lane_off + unsigned(gj * K + col(t)) * 128u)) = r[t];
+          for (int t = 0; t < K; ++t) {
+            const int col = sp.zrev ? K - 1 - t : t;
+            if ((osf >> col) & 1u) *(SPC_GLOBAL int32_t*)(Mg + col * 128 + lane_off) = r[t];
+          }
         }
       }
-      // the row's hits among the matrix offsets, as bits gj*K .. gj*K + K - 1 of the lane's mask words
-      unsigned hc = 0u;
+    }
+    if (M) {  // the blocks' masks
+      if (sp.zrev) {  // queries of a group to columns
+        unsigned x = 0u;
 #pragma unroll
-      for (int t = 0; t < K; ++t) hc |= hit[t] ? 1u << col(t) : 0u;
-      const int wd = (gj * K) >> 5, sh = (gj * K) & 31;
-      const unsigned long long f = static_cast<unsigned long long>(hc & osf) << sh;
+        for (int j = 0; j < N; ++j)
 #pragma unroll
-      for (int w = 0; w < MW; ++w) hbits[w] |= (wd == w ? static_cast<unsigned>(f) : 0u) | (wd + 1 == w ? static_cast<unsigned>(f >> 32) : 0u);
+          for (int t = 0; t < K; ++t) x |= ((hb >> (j * K + t)) & 1u) << (j * K + K - 1 - t);
+        hb = x;
+      }
+      hb = half_wave_or(hb & osb);
+      const int bit = ix * G + BIT0;
+      if ((lane & 31) == 31 && hb) {
+        const unsigned long long f = static_cast<unsigned long long>(hb) << (bit & 31);
+        unsigned* m = &s_mask[(c * 2 + (lane >> 5)) * MW + (bit >> 5)];
+        if (static_cast<unsigned>(f)) atomicOr(m, static_cast<unsigned>(f));
+        if (static_cast<unsigned>(f >> 32)) atomicOr(m + 1, static_cast<unsigned>(f >> 32));
+      }
     }
   };
-  // the wave's groups: part, part + parts, ...; SEARCH_GB at a time, then the remainder
-  {
-    const int mine = part < G ? (G - part + parts - 1) / parts : 0;
-    int done = 0;
-    for (; done + SEARCH_GB <= mine; done += SEARCH_GB) search_groups(std::integral_constant<int, SEARCH_GB>{}, part + done * parts);
-    const int left = mine - done;
-    const int gb = part + done * parts;
-    // (only the remainders that some part of this kernel size can have are compiled)
-    if constexpr (remainder_occurs(G, parts, SEARCH_GB, 1)) if (left == 1) search_groups(std::integral_constant<int, 1>{}, gb);
-    if constexpr (remainder_occurs(G, parts, SEARCH_GB, 2)) if (left == 2) search_groups(std::integral_constant<int, 2>{}, gb);
-    if constexpr (remainder_occurs(G, parts, SEARCH_GB, 3)) if (left == 3) search_groups(std::integral_constant<int, 3>{}, gb);
-    if constexpr (remainder_occurs(G, parts, SEARCH_GB, 4)) if (left == 4) search_groups(std::integral_constant<int, 4>{}, gb);
-    static_assert(SEARCH_GB <= 5, "remainders above four groups are not dispatched");
-  }
-  if (M) {
 #pragma unroll
-    for (int w = 0; w < MW; ++w)
-      if (hbits[w]) atomicOr(&s_mask[(bl0 + (lane >> 5)) * MW + w], hbits[w]);
+  for (int c = 0; c < CHUNKS; ++c) {
+    if (c * 64 >= rows) break;  // uniform
+    search_groups(std::integral_constant<int, NJ>{}, std::integral_constant<int, 0>{}, c, okey[c]);
+    if constexpr (K > NJ) search_groups(std::integral_constant<int, K - NJ>{}, std::integral_constant<int, NJ>{}, c, okey[c]);
   }
   __syncthreads();
   if constexpr (PAIRS) {
     // where every offset's pairs start in the slab: exclusive prefix of the counts, by wave 0
-    if (wave == 0) {
+    if (ix == 0) {
       int carry = 0;
       for (int k0 = 0; k0 < K3; k0 += 64) {
         const int k = k0 + lane;
         const int c = k < K3 ? s_cnt[k] : 0;
         int x = c;
-        for (int d = 1; d < 64; d <<= 1) {
-          const int y = __shfl_up(x, d, 64);
-          if (lane >= d) x += y;
+        for (int s = 1; s < 64; s <<= 1) {
+          const int y = __shfl_up(x, s, 64);
+          if (lane >= s) x += y;
         }
         if (k < K3) s_off[k] = carry + x - c;
         carry += __shfl(x, 63, 64);
       }
       if (lane == 0) s_off[K3] = carry;
     }
-    for (int k = tid; k < K3; k += SEARCH_THREADS) tile_counts[int64_t(k) * n_tiles_cap + blockIdx.x] = s_cnt[k];
+    for (int k = tid; k < K3; k += 64 * K) args.tile_counts[int64_t(k) * args.n_tiles_cap + blockIdx.x] = s_cnt[k];
     __syncthreads();
-    // compaction: a wave takes an offset at a time and walks the tile's rows in steps of 64; the hit's input
-    // position is the group's lower bound plus the number of the group's earlier queries that hit
-    int2* slab = tile_pairs + int64_t(blockIdx.x) * tile * K3;
+    // compaction: a wave takes an offset at a time and walks the tile's rows in steps of 64; the hit's row
+    // number is that of the group's lower bound or one of the next, by the number of the group's earlier queries that hit
+    int2* slab = args.tile_pairs + int64_t(blockIdx.x) * TILE * K3;
     uint8_t* sub = args.tile_sub + int64_t(blockIdx.x) * K3 * MAX_BLOCKS;  // (unused for offsets without pairs)
-    for (int k = wave; k < K3; k += NW) {
+    const int32_t* wval0 = reinterpret_cast<const int32_t*>(smem);
+    for (int k = ix; k < K3; k += K) {
       if (s_cnt[k] == 0) continue;  // uniform (offsets outside ws_k are never counted)
       const int g = k / K, tk = k - g * K, tq = sp.zrev ? K - 1 - tk : tk;
       int at = s_off[k];
       for (int v0 = 0; v0 < rows; v0 += 64) {
         const int vv = v0 + lane;
-        const unsigned msk = vv < tile ? s_hit[g * tile + vv] : 0u;
+        const unsigned msk = s_hit[g * TILE + vv];
         const bool hit = vv < rows && ((msk >> tq) & 1u);
         const unsigned long long bal = __ballot(hit);
         if (hit) {
-          const int jpos = s_pos[g * tile + vv] + __popc(msk & ((1u << tq) - 1u));
-          slab[at + lanemask_lt_popc(bal)] = make_int2(in_perm ? in_perm[jpos] : jpos, i0 + vv);
+          const int pos = s_pos[g * TILE + vv], ahead = __popc(msk & ((1u << tq) - 1u));
+          int in;
+          if (pos >= 0) in = wval0[pos + ahead];
+          else in = in_perm ? in_perm[~pos + ahead] : ~pos + ahead;
+          slab[at + lanemask_lt_popc(bal)] = make_int2(in, i0 + vv);
         }
         if (lane < 2)  // pairs of the offset in the tile's blocks before this one
           sub[k * MAX_BLOCKS + (v0 >> 5) + lane] = static_cast<uint8_t>(at - s_off[k] + (lane ? __popc(static_cast<unsigned>(bal)) : 0));
@@ -625,8 +521,8 @@ __global__ __launch_bounds__(SEARCH_THREADS) void kmap_search_kernel(const Searc
     }
   }
   if (M) {
-    const int n_bl = rows32 >> 5;
-    for (int e = tid; e < n_bl * MW; e += SEARCH_THREADS) block_masks[b0 * MW + e] = s_mask[e];
+    const int n_bl = (rows + 31) >> 5;
+    for (int e = tid; e < n_bl * MW; e += 64 * K) args.block_masks[b0 * MW + e] = s_mask[e];
   }
 }
 
@@ -825,13 +721,15 @@ static SearchArgs<KeyT> search_args(const spc_kmap* m) {
   sp.dX = K > 1 ? static_cast<KeyT>(packed(1, pi.sh_x) - sp.X0) : KeyT(0);
   sp.Y0 = packed(0, pi.sh_y);
   sp.dY = K > 1 ? static_cast<KeyT>(packed(1, pi.sh_y) - sp.Y0) : KeyT(0);
+  const bool yrev = int64_t(sign) * axis_offset(K, sp_stride, 0) > int64_t(sign) * axis_offset(K, sp_stride, K - 1);
+  sp.ymin = packed(yrev ? K - 1 : 0, pi.sh_y);
+  sp.ymax = packed(yrev ? 0 : K - 1, pi.sh_y);
   const int64_t z_a = int64_t(sign) * axis_offset(K, sp_stride, 0), z_b = int64_t(sign) * axis_offset(K, sp_stride, K - 1);
   sp.zmin = static_cast<KeyT>(static_cast<uint64_t>(std::min(z_a, z_b)));
   sp.zstep = static_cast<KeyT>(sp_stride);
   sp.zrev = (K > 1 && z_a > z_b) ? 1 : 0;
-  for (int g = 0; g < K * K; ++g)
-    for (int t = 0; t < K; ++t)
-      if ((m->os_map && m->os_k.has(g * K + t)) || m->ws_k.has(g * K + t)) sp.need |= 1ull << g;
+  for (int k = 0; k < K * K * K; ++k)
+    if ((m->os_map && m->os_k.has(k)) || m->ws_k.has(k)) sp.need |= 1u << (k / (K * K));
   const Level* in = m->in_level;
   const Level* out = m->out_level;
   SearchArgs<KeyT> a{};
@@ -861,16 +759,16 @@ template <typename KeyT, int K, int TILE>
 static void launch_search(spc_kmap* const* ms, int count, hipStream_t s) {
   const spc_kmap* m = ms[0];
   const bool pairs = (m->desc.layout & SPC_LAYOUT_WS) != 0;
-  const size_t lds = size_t(m->tile) * sizeof(KeyT) + WIN_CAP_BYTES + MAX_K * sizeof(KeyT) + (pairs ? size_t(K) * K * m->tile * 5 : 0);
   auto go = [&](auto PAIRS_, auto NB_, int first, int n, int n_tiles) {
     constexpr bool PAIRS = decltype(PAIRS_)::value;
     constexpr int NB = decltype(NB_)::value;
+    constexpr size_t lds = search_lds_bytes<KeyT, K, TILE, PAIRS>();
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&kmap_search_kernel<KeyT, K, TILE, PAIRS, NB>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
     (void)attr;
     SearchBatch<KeyT, NB> b{};
     for (int i = 0; i < n; ++i) b.a[i] = search_args<KeyT, K>(ms[first + i]);
-    hipLaunchKernelGGL((kmap_search_kernel<KeyT, K, TILE, PAIRS, NB>), dim3(n_tiles, n), dim3(SEARCH_THREADS), lds, s, b);
+    hipLaunchKernelGGL((kmap_search_kernel<KeyT, K, TILE, PAIRS, NB>), dim3(n_tiles, n), dim3(64 * K), lds, s, b);
   };
   // the large kernels are searched one map at a time: their levels' searches are long enough to stand alone
   constexpr int MOST = K <= 3 ? SEARCH_BATCH : 1;
@@ -889,12 +787,19 @@ static void launch_search(spc_kmap* const* ms, int count, hipStream_t s) {
 
 template <typename KeyT>
 static int launch_search_k(spc_kmap* const* ms, int count, hipStream_t s) {
-  const bool longer = ms[0]->tile == 256;
+  auto by_tile = [&](auto K_) {
+    constexpr int K = decltype(K_)::value;
+    switch (ms[0]->tile) {
+      case 64: launch_search<KeyT, K, 64>(ms, count, s); break;
+      case 128: launch_search<KeyT, K, 128>(ms, count, s); break;
+      default: launch_search<KeyT, K, 256>(ms, count, s); break;
+    }
+  };
   switch (ms[0]->desc.K) {
-    case 1: longer ? launch_search<KeyT, 1, 256>(ms, count, s) : launch_search<KeyT, 1, 128>(ms, count, s); break;
-    case 2: longer ? launch_search<KeyT, 2, 256>(ms, count, s) : launch_search<KeyT, 2, 128>(ms, count, s); break;
-    case 3: longer ? launch_search<KeyT, 3, 256>(ms, count, s) : launch_search<KeyT, 3, 128>(ms, count, s); break;
-    case 5: launch_search<KeyT, 5, 128>(ms, count, s); break;
+    case 1: by_tile(std::integral_constant<int, 1>{}); break;
+    case 2: by_tile(std::integral_constant<int, 2>{}); break;
+    case 3: by_tile(std::integral_constant<int, 3>{}); break;
+    case 5: launch_search<KeyT, 5, 64>(ms, count, s); break;
     case 7: launch_search<KeyT, 7, 64>(ms, count, s); break;
     default: return set_error(SPC_ERR_UNSUPPORTED, "kernel size %d not built (1,2,3,5,7 are)", ms[0]->desc.K);
   }
@@ -1564,7 +1469,7 @@ int64_t spc_search_count(void) { return g_search_launches.load(std::memory_order
 int spc_kmap_search_info(const spc_kmap* m, int32_t* tile_rows, int32_t* window_keys) {
   if (!m) return set_error(SPC_ERR_ARG, "map is NULL");
   if (tile_rows) *tile_rows = m->tile;
-  if (window_keys) *window_keys = WIN_CAP_BYTES / (m->pi.key_bits / 8);
+  if (window_keys) *window_keys = m->desc.K * search_win_cap(m->tile);
   return SPC_OK;
 }
 
