@@ -435,6 +435,10 @@ __global__ __launch_bounds__(64 * WAVES) void conv_os_phase_kernel(const int32_t
 constexpr int SPLITK_WAVES = 4;
 constexpr int SPLITK_KL_CAP = 96;  // >= ceil(7^3 / 4) + 4
 enum { A_VEC = 0, A_RAGGED = 1, A_ELEM = 2, A_QUAD = 3 };
+// Where a tile's pairs come from: the matrix, one row of 32 indices per present offset; the matrix of a kernel of at most
+// 32 offsets, all rows at once (one 16-byte load per thread, requested together with the masks instead of after them);
+// the lists (or the matrix, by offset).
+enum { MATRIX = 0, MATRIX_SMALL = 1, LISTS = 2 };
 
 struct ListArgs {
   const int32_t *in, *out;          // pairs, list k at k * stride
@@ -458,17 +462,22 @@ struct SplitkArgs {
   KMask os_mask;
   ListArgs lists;
 };
-constexpr int splitk_idx_rows(int K3, int AM) { return (K3 + SPLITK_WAVES - 1) / SPLITK_WAVES + (AM == A_QUAD ? 4 : 1); }
+// rows of 32 input indices in LDS, with all-invalid rows at the end: per wave, or (MATRIX_SMALL) for all waves
+__host__ __device__ constexpr int splitk_idx_rows(int K3, int AM, int FROM) {
+  return FROM == MATRIX_SMALL ? K3 + 1 : (K3 + SPLITK_WAVES - 1) / SPLITK_WAVES + (AM == A_QUAD ? 4 : 1);
+}
+// The waves' partial sums meet in LDS in four areas where they are small, else in two (two waves add theirs to the others').
+constexpr int splitk_areas(int NB, int RB) { return NB * RB == 1 ? 4 : 2; }
 
 // LOOP: the grid was sized from an estimate of the output count and tiles are walked with a grid
 // stride; otherwise one tile per workgroup (the loop costs about 30 registers per lane).
 // PACKED: weights in MFMA operand order; otherwise the caller's [K^3][cin][cout], read a channel at a time (a fragment is
 // then 32-column rows of W instead of 16 bytes per lane: the same bytes in more instructions, but no re-layout pass).
-template <typename T, int NB, int RB, int D, bool LOOP, int AM, bool PACKED, bool LISTS>
+template <typename T, int NB, int RB, int D, bool LOOP, int AM, bool PACKED, int FROM>
 __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 4 ? 4 : NB == 2 || LOOP ? 6 : 8) : 1) void conv_os_splitk_kernel(const SplitkArgs a) {
   using V = typename Mfma<T>::V;
   constexpr int LPC = Mfma<T>::LPC, SLAB = 2 * LPC;
-  static_assert(RB == 1 || (AM == A_VEC && !LISTS), "two row blocks: plain layers only");
+  static_assert(RB == 1 || (AM == A_VEC && FROM == MATRIX), "two row blocks: plain layers only");
   constexpr bool SHARED = RB == 1 && AM == A_VEC && NB <= 2;  // whether several workgroups may share a tile's offsets
   static_assert(AM != A_QUAD || sizeof(T) == 2, "four offsets per slab: 16-bit types");
   extern __shared__ __align__(16) unsigned char smem[];
@@ -494,19 +503,23 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 4 ?
   if constexpr (LOOP) asm volatile("" : "+v"(tid));
   const int lane = tid & 63, lr = lane & 31, lh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int idx_rows = splitk_idx_rows(K3, AM);  // per wave, with all-invalid rows at the end
-  int32_t* sIdx = reinterpret_cast<int32_t*>(smem) + wave * idx_rows * (RB * 32);
-  unsigned char* kl_base = smem + size_t(SPLITK_WAVES) * idx_rows * (RB * 128);
+  const int idx_rows = splitk_idx_rows(K3, AM, FROM);
+  int32_t* sIdx = reinterpret_cast<int32_t*>(smem) + (FROM == MATRIX_SMALL ? 0 : wave * idx_rows * (RB * 32));
+  unsigned char* kl_base = smem + size_t(FROM == MATRIX_SMALL ? 1 : SPLITK_WAVES) * idx_rows * (RB * 128);
   int16_t* kl = reinterpret_cast<int16_t*>(kl_base) + wave * SPLITK_KL_CAP;
-  // LISTS: where the pairs of this wave's offsets start, and how many there are (-1: from the matrix, -2: row = row)
+  // lists: where the pairs of this wave's offsets start, and how many there are (-1: from the matrix, -2: row = row)
   int32_t* s_first = reinterpret_cast<int32_t*>(kl_base + SPLITK_WAVES * SPLITK_KL_CAP * 2) + wave * SPLITK_KL_CAP;
   int32_t* s_num = s_first + SPLITK_WAVES * SPLITK_KL_CAP;
 
+  int4 rows = {-1, -1, -1, -1};
+  if constexpr (FROM == MATRIX_SMALL) {
+    if (tid < K3 * 8) rows = *reinterpret_cast<const int4*>(M + blk0 * (K3 * 32) + tid * 4);
+  }
   // this wave's offsets: those present in the tile whose rank is its share mod the number of shares (cnt - share >= -31, so
   // the count of a share behind the last rank comes out as zero)
   const int share = SHARED && log_waves > 2 ? blockIdx.z * SPLITK_WAVES + wave : wave;
   int cnt = 0;
-  if constexpr (!LISTS) {  // (union of the builder's block masks)
+  if constexpr (FROM != LISTS) {  // (union of the builder's block masks)
     for (int wd = 0; wd < a.mask_words; ++wd) {
       unsigned m = 0;
 #pragma unroll
@@ -551,12 +564,21 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 4 ?
     }
   }
   const int n_i = __builtin_amdgcn_readfirstlane((cnt - share + (1 << log_waves) - 1) >> log_waves);
-  // entries past the end read offset 0's weights and all-invalid rows
+  // entries past the end read some offset's weights and all-invalid rows
   constexpr int TAIL = AM == A_QUAD ? 4 : 1;
-  if (lane < TAIL) kl[n_i + lane] = 0;
-  for (int q = lane; q < TAIL * RB * 32; q += 64) sIdx[n_i * RB * 32 + q] = -1;
+  if (lane < TAIL) kl[n_i + lane] = FROM == MATRIX_SMALL ? K3 : 0;
+  if constexpr (FROM == MATRIX_SMALL) {
+    if (tid < K3 * 8) reinterpret_cast<int4*>(sIdx)[tid] = rows;
+    if (tid < 32) sIdx[K3 * 32 + tid] = -1;
+    __syncthreads();
+  } else {
+    for (int q = lane; q < TAIL * RB * 32; q += 64) sIdx[n_i * RB * 32 + q] = -1;
+  }
   __builtin_amdgcn_wave_barrier();
-  if constexpr (!LISTS) {
+  // row of indices of this wave's i-th offset k
+  auto idx_row = [&](int i, int k) { return FROM == MATRIX_SMALL ? k : i; };
+  auto weight_k = [&](int k) { return FROM == MATRIX_SMALL ? min(k, K3 - 1) : k; };
+  if constexpr (FROM == MATRIX) {
     // their map rows (32 input indices per block), eight (offset, block) pairs per pass:
     // lane -> (pair, 4 rows); blocks past the end of the level count as all-invalid
     const int part = lane & 7;
@@ -567,7 +589,7 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 4 ?
         v = *reinterpret_cast<const int4*>(M + ((blk0 + rb) * int64_t(K3) + kl[i]) * 32 + part * 4);
       *reinterpret_cast<int4*>(sIdx + p * 32 + part * 4) = v;
     }
-  } else {
+  } else if constexpr (FROM == LISTS) {
     // two offsets per pass (a half-wave each, lane = row or pair), four passes' loads in flight together
     for (int p0 = lh; p0 < n_i; p0 += 8) {
       int row[4], val[4];
@@ -626,9 +648,9 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 4 ?
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const int q = min(4 * e_n + 2 * lh + h, n_i);  // past the end: offset 0, no rows
-        const int idx = sIdx[q * 32 + lr];
+        const int kq = kl[q], k = weight_k(kq);
+        const int idx = sIdx[idx_row(q, kq) * 32 + lr];
         const V4 f = *reinterpret_cast<const V4*>(idx < 0 ? zero4 : F + int64_t(idx) * ld_in);
-        const int k = kl[q];
 #pragma unroll
         for (int j = 0; j < 4; ++j) av[S][0][4 * h + j] = f[j];
 #pragma unroll
@@ -663,9 +685,9 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 4 ?
     const V* Wv = reinterpret_cast<const V*>(W) + int64_t(slab) * NB * 64 + lane;  // PACKED
     int i_n = 0, kk_n = 0;
     int idx_n[RB];
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) idx_n[rb] = sIdx[rb * 32 + lr];
     int k_n = __builtin_amdgcn_readfirstlane(static_cast<int>(kl[0]));
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) idx_n[rb] = sIdx[(idx_row(0, k_n) * RB + rb) * 32 + lr];
     auto issue = [&](auto S_) {
       constexpr int S = decltype(S_)::value;
       const int c0 = kk_n * SLAB + LPC * lh;  // this lane's first channel
@@ -681,12 +703,12 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 4 ?
         }
       }
       if constexpr (PACKED) {
-        const V* wsrc = Wv + (int64_t(k_n) * KK + kk_n) * nb_total * 64;
+        const V* wsrc = Wv + (int64_t(weight_k(k_n)) * KK + kk_n) * nb_total * 64;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) bv[S][nb] = wsrc[nb * 64];
       } else {
         // channels past the end multiply zeros: the last one's weights stand in for theirs
-        const T* wk = W + (int64_t(k_n) * cin + (AM == A_VEC ? kk_n * SLAB : 0)) * cout;  // uniform
+        const T* wk = W + (int64_t(weight_k(k_n)) * cin + (AM == A_VEC ? kk_n * SLAB : 0)) * cout;  // uniform
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
           const unsigned col = min((slab * NB + nb) * 32 + lr, cout - 1);  // (columns past the end are not stored)
@@ -700,9 +722,9 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 4 ?
       if (++kk_n == KK) {
         kk_n = 0;
         i_n = min(i_n + 1, n_i);
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) idx_n[rb] = sIdx[(i_n * RB + rb) * 32 + lr];
         k_n = __builtin_amdgcn_readfirstlane(static_cast<int>(kl[i_n]));
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) idx_n[rb] = sIdx[(idx_row(i_n, k_n) * RB + rb) * 32 + lr];
       }
     };
     static_for<D>([&](auto S_) { issue(S_); });
@@ -720,37 +742,45 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 4 ?
     }
   }
 
-  // The four partial sums meet in one LDS tile (the index area is dead by now): the waves add
-  // theirs in turn, last wave first.  Value (rb, nb, r, lane) sits at float
+  // The four partial sums meet in LDS (the index area is dead by now).  Value (rb, nb, r, lane) of an area sits at float
   // (((rb*NB + nb)*4 + r/4)*64 + lane)*4 + r%4, so a lane moves four registers per access.
-  float4* red4 = reinterpret_cast<float4*>(smem);
-  for (int w = SPLITK_WAVES - 1; w >= 0; --w) {
-    __syncthreads();
-    if (wave == w) {
+  constexpr int AREAS = splitk_areas(NB, RB), AREA = RB * NB * 1024;
+  auto area = [&](int w) { return reinterpret_cast<float4*>(smem) + w * (AREA / 4) + lane; };
+  auto put = [&](float4* p, bool add) {
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            float4* p = red4 + ((rb * NB + nb) * 4 + q) * 64 + lane;
-            float4 t = {acc[rb][nb][4 * q], acc[rb][nb][4 * q + 1], acc[rb][nb][4 * q + 2], acc[rb][nb][4 * q + 3]};
-            if (w != SPLITK_WAVES - 1) {
-              const float4 u = *p;
-              t.x += u.x;
-              t.y += u.y;
-              t.z += u.z;
-              t.w += u.w;
-            }
-            *p = t;
-          }
+    for (int i = 0; i < RB * NB * 4; ++i) {
+      const floatx16& v = acc[i / 4 / NB][i / 4 % NB];
+      const int q = i % 4;
+      float4 t = {v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+      if (add) {
+        const float4 u = p[i * 64];
+        t.x += u.x;
+        t.y += u.y;
+        t.z += u.z;
+        t.w += u.w;
+      }
+      p[i * 64] = t;
     }
+  };
+  __syncthreads();
+  if constexpr (AREAS == 4) {
+    put(area(wave), false);
+  } else {
+    if (wave >= 2) put(area(wave - 2), false);
+    __syncthreads();
+    if (wave < 2) put(area(wave), true);
   }
   __syncthreads();
+  auto total = [&](int e) {
+    const float* r = reinterpret_cast<const float*>(smem);
+    float v = r[e] + r[AREA + e];
+    if constexpr (AREAS == 4) v += r[2 * AREA + e] + r[3 * AREA + e];
+    return v;
+  };
   // D layout of the 32x32 MFMA: register r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l%32.
   // Thread t stores EPT consecutive channels of row t/8 of every block.
   constexpr int EPT = NB * 4;
-  const float* red = reinterpret_cast<const float*>(smem);
+  bool summed = false;  // area 0 holds the total
   if (SHARED && log_waves > 2) {
     // This workgroup's part of the sum goes to memory; whoever finds all other parts there adds them up, in the order
     // of the parts whoever it is.  Nobody waits.  Parts travel between XCDs, whose L2s are not coherent: they are
@@ -761,13 +791,15 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 4 ?
     using Pair = unsigned long long;  // two sums per access
     constexpr int PER = PART / 2 / (64 * SPLITK_WAVES);
     Pair* part0 = reinterpret_cast<Pair*>(a.partial) + slot * parts * (PART / 2) + tid;
-    Pair* red2 = reinterpret_cast<Pair*>(smem) + tid;
 #pragma unroll
-    for (int e = 0; e < PER; ++e)
-      __hip_atomic_store(part0 + blockIdx.z * (PART / 2) + e * 256, red2[e * 256], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int e = 0; e < PER; ++e) {
+      const int at = (tid + e * 256) * 2;
+      const Pair both = (static_cast<Pair>(__float_as_uint(total(at + 1))) << 32) | __float_as_uint(total(at));
+      __hip_atomic_store(part0 + blockIdx.z * (PART / 2) + e * 256, both, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    int* s_last = reinterpret_cast<int*>(smem) + PART;
+    int* s_last = reinterpret_cast<int*>(smem) + AREAS * AREA;
     if (tid == 0) *s_last = __hip_atomic_fetch_add(a.arrived + slot, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1;
     __syncthreads();
     if (!*s_last) return;
@@ -792,6 +824,7 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 4 ?
     }
 #pragma unroll
     for (int e = 0; e < PER; ++e) reinterpret_cast<float2*>(smem)[tid + e * 256] = v[e];
+    summed = true;
     __syncthreads();
   }
   const int row = tid >> 3, c0 = (tid & 7) * EPT;
@@ -801,11 +834,11 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 4 ?
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     const int64_t i = (blk0 + rb) * 32 + row;
-    const float* p = red + ((((rb * NB + nb) * 4 + q) * 64) + h * 32 + cc) * 4 + rr;
+    const int at = ((((rb * NB + nb) * 4 + q) * 64) + h * 32 + cc) * 4 + rr;
     __align__(16) T o[EPT];
 #pragma unroll
     for (int j = 0; j < EPT; ++j) {
-      const float v = p[4 * j];
+      const float v = SHARED && summed ? reinterpret_cast<const float*>(smem)[at + 4 * j] : total(at + 4 * j);
       o[j] = from_f32<T>(a.relu ? fmaxf(v, 0.f) : v);
     }
     if (i < n_out && oc < cout) {
@@ -885,9 +918,10 @@ static void launch_os_mfma(const ConvArgs& a, const T* Wp) {
   else go(std::integral_constant<int, 1>{});
 }
 
-static size_t splitk_lds_bytes(int K3, int NB, int RB, int AM, bool lists) {
-  const size_t idx = size_t(SPLITK_WAVES) * splitk_idx_rows(K3, AM) * RB * 128 + size_t(SPLITK_WAVES) * SPLITK_KL_CAP * (lists ? 10 : 2);
-  return std::max(idx, size_t(RB) * NB * 16 * 64 * 4 + 16);
+static size_t splitk_lds_bytes(int K3, int NB, int RB, int AM, int from) {
+  const size_t idx = size_t(from == MATRIX_SMALL ? 1 : SPLITK_WAVES) * splitk_idx_rows(K3, AM, from) * RB * 128 +
+                     size_t(SPLITK_WAVES) * SPLITK_KL_CAP * (from == LISTS ? 10 : 2);
+  return std::max(idx, size_t(splitk_areas(NB, RB)) * RB * NB * 4096 + 16);
 }
 
 // Whether the feature rows are as the vector loads and whole slabs of the split-k and phase kernels want them.
@@ -923,7 +957,7 @@ static bool splitk_wide(const ConvArgs& a) {
   return wide * 100 <= narrow * 62;
 }
 
-template <typename T, int NB, int RB, int AM, bool PACKED, bool LISTS>
+template <typename T, int NB, int RB, int AM, bool PACKED, int FROM>
 static void launch_splitk(const ConvArgs& a, const void* W) {
   // entries in flight per wave: two.  Deeper rings cost the registers that hold more waves per SIMD, and the
   // waves hide more latency than the ring does (25 layers of a UNet on 120 k voxels, all on this kernel: 403 us
@@ -949,16 +983,16 @@ static void launch_splitk(const ConvArgs& a, const void* W) {
   constexpr int EPT = NB * 4;
   constexpr int store = EPT * sizeof(T) < 16 ? EPT * sizeof(T) : 16;  // bytes per store
   k.vec_store = a.cout % EPT == 0 && a.ld_out * sizeof(T) % store == 0 && reinterpret_cast<uintptr_t>(a.out) % store == 0;
-  if (LISTS) k.lists = ListArgs{a.m->ws_in, a.m->ws_out, a.m->list_base, a.m->list_base_in, a.m->ws_stride, a.m->sym ? 1 : 0, a.ws_mask};
+  if (FROM == LISTS) k.lists = ListArgs{a.m->ws_in, a.m->ws_out, a.m->list_base, a.m->list_base_in, a.m->ws_stride, a.m->sym ? 1 : 0, a.ws_mask};
   // an estimated output count sizes the grid of the variant that walks tiles with a grid stride
   const bool loop = a.rows_sel != a.rows_cap;
   const int64_t n_blocks = std::max<int64_t>((a.rows_sel + 31) / 32, 1);
-  const size_t lds = splitk_lds_bytes(a.m->K3, NB, RB, AM, LISTS);
+  const size_t lds = splitk_lds_bytes(a.m->K3, NB, RB, AM, FROM);
   // once per instantiation: both variants may use all of a CU's LDS (large kernels need more than the default 64 KB)
   static const hipError_t attr = [] {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_os_splitk_kernel<T, NB, RB, D, false, AM, PACKED, LISTS>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_os_splitk_kernel<T, NB, RB, D, false, AM, PACKED, FROM>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    const hipError_t f = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_os_splitk_kernel<T, NB, RB, D, true, AM, PACKED, LISTS>),
+    const hipError_t f = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_os_splitk_kernel<T, NB, RB, D, true, AM, PACKED, FROM>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     return e != hipSuccess ? e : f;
   }();
@@ -977,9 +1011,9 @@ static void launch_splitk(const ConvArgs& a, const void* W) {
   }
   const dim3 grid(static_cast<unsigned>((n_blocks + RB - 1) / RB), k.nb_total / NB, parts);
   if (loop)
-    hipLaunchKernelGGL((conv_os_splitk_kernel<T, NB, RB, D, true, AM, PACKED, LISTS>), grid, dim3(64 * SPLITK_WAVES), lds, a.s, k);
+    hipLaunchKernelGGL((conv_os_splitk_kernel<T, NB, RB, D, true, AM, PACKED, FROM>), grid, dim3(64 * SPLITK_WAVES), lds, a.s, k);
   else
-    hipLaunchKernelGGL((conv_os_splitk_kernel<T, NB, RB, D, false, AM, PACKED, LISTS>), grid, dim3(64 * SPLITK_WAVES), lds, a.s, k);
+    hipLaunchKernelGGL((conv_os_splitk_kernel<T, NB, RB, D, false, AM, PACKED, FROM>), grid, dim3(64 * SPLITK_WAVES), lds, a.s, k);
   pool_free(k.partial, a.s);  // reuse is ordered behind this stream's work
 }
 
@@ -991,41 +1025,50 @@ static void launch_os_splitk(const ConvArgs& a) {
   using No = std::false_type;
   const bool aligned = a.ld_in % LPC == 0 && reinterpret_cast<uintptr_t>(a.F) % 16 == 0;
   const bool quad = sizeof(T) == 2 && a.cin == 4 && a.ld_in % 4 == 0 && reinterpret_cast<uintptr_t>(a.F) % 8 == 0;
+  const bool small = a.m->K3 <= 32;
   auto columns = [&](auto NB_) {
     constexpr int NB = decltype(NB_)::value;
-    auto rows = [&](auto PACKED_, auto LISTS_) {
-      constexpr bool PACKED = decltype(PACKED_)::value, LISTS = decltype(LISTS_)::value;
+    auto rows = [&](auto PACKED_, auto FROM_) {
+      constexpr bool PACKED = decltype(PACKED_)::value;
+      constexpr int FROM = decltype(FROM_)::value;
       if (quad) {
-        if constexpr (sizeof(T) == 2) launch_splitk<T, NB, 1, A_QUAD, PACKED, LISTS>(a, a.W);
+        if constexpr (sizeof(T) == 2) launch_splitk<T, NB, 1, A_QUAD, PACKED, FROM>(a, a.W);
       } else if (!aligned || a.cin % LPC != 0) {
-        launch_splitk<T, NB, 1, A_ELEM, PACKED, LISTS>(a, a.W);
+        launch_splitk<T, NB, 1, A_ELEM, PACKED, FROM>(a, a.W);
       } else if (a.cin % (2 * LPC) != 0) {
-        launch_splitk<T, NB, 1, A_RAGGED, PACKED, LISTS>(a, a.W);
+        launch_splitk<T, NB, 1, A_RAGGED, PACKED, FROM>(a, a.W);
       } else {
         // Row blocks per workgroup: two blocks share each weight fragment read (less L2 traffic) but leave fewer
         // workgroups and cost registers; one measured faster at every size (120 k voxels 64->64: 37.4 vs 39.1 us; 240 k
         // voxels 5x5x5 32->32: 37.7 vs 47.7), so two is only taken on request.
-        if constexpr (PACKED && !LISTS) {
-          if (a.splitk_rb == 2 && splitk_lds_bytes(a.m->K3, NB, 2, A_VEC, false) <= 80 * 1024) {
-            launch_splitk<T, NB, 2, A_VEC, true, false>(a, a.W);
+        if constexpr (PACKED && FROM != LISTS) {
+          if (a.splitk_rb == 2 && splitk_lds_bytes(a.m->K3, NB, 2, A_VEC, MATRIX) <= 80 * 1024) {
+            launch_splitk<T, NB, 2, A_VEC, true, MATRIX>(a, a.W);
             return;
           }
         }
-        launch_splitk<T, NB, 1, A_VEC, PACKED, LISTS>(a, a.W);
+        launch_splitk<T, NB, 1, A_VEC, PACKED, FROM>(a, a.W);
       }
+    };
+    auto from = [&](auto PACKED_) {
+      if (a.any_ws) rows(PACKED_, std::integral_constant<int, LISTS>{});
+      else if (small) rows(PACKED_, std::integral_constant<int, MATRIX_SMALL>{});
+      else rows(PACKED_, std::integral_constant<int, MATRIX>{});
     };
     if constexpr (sizeof(T) == 2) {
       if (a.packed) {
-        a.any_ws ? rows(Yes{}, Yes{}) : rows(Yes{}, No{});
+        from(Yes{});
         return;
       }
     }
-    a.any_ws ? rows(No{}, Yes{}) : rows(No{}, No{});
+    from(No{});
   };
   const int nb_total = (a.cout + 31) / 32;
   if constexpr (sizeof(T) == 2) {
     if (a.packed && plain_rows<T>(a) && a.splitk_rb == 0 && splitk_wide(a) && splitk_parts<T>(a, (a.rows_sel + 31) / 32 * (a.cout / 64)) == 1) {
-      a.any_ws ? launch_splitk<T, 4, 1, A_VEC, true, true>(a, a.W) : launch_splitk<T, 4, 1, A_VEC, true, false>(a, a.W);
+      if (a.any_ws) launch_splitk<T, 4, 1, A_VEC, true, LISTS>(a, a.W);
+      else if (small) launch_splitk<T, 4, 1, A_VEC, true, MATRIX_SMALL>(a, a.W);
+      else launch_splitk<T, 4, 1, A_VEC, true, MATRIX>(a, a.W);
       return;
     }
   }
