@@ -822,17 +822,18 @@ __global__ __launch_bounds__(BS_THREADS) void bs_rank_rest_kernel(const int32_t*
 // ---------------------------------------------------------------- small levels: one workgroup, one launch
 // Fewer than BS_MIN_N keys (the tiny cloud of a unit test, the coarsest levels of a network): the partitioning
 // scheme of the large path inside one workgroup and LDS.  The keys are produced (packed or masked) straight into
-// LDS and counted into 1024 bins of their top used bits; a scan gives the bin starts; the keys move, with their source
+// LDS and counted into 4096 bins of their top used bits; a scan gives the bin starts; the keys move, with their source
 // index, to their bin's range; and every key's final place is its bin's start plus the number of (key, index)
 // pairs of the bin that sort before it (the index breaks ties, so equal keys of an invalid cloud still get distinct
 // places).  The downsampling form writes the sorted keys back to LDS and keeps the first key of every run of equal
 // keys (a scan over the head flags).  One launch of a few microseconds where the large path has four (five) and a
 // library sort more; nothing but kernels is enqueued, so it can be recorded into a graph.  Work is quadratic in the
-// bin sizes: a cloud whose keys all share their top 10 used bits costs n^2 = 16 M comparisons at most.
+// bin sizes: a cloud whose keys all share their top 12 used bits costs n^2 = 16 M comparisons at most.  (1024 bins: 4000 voxels
+// of surfaces 15 us, their stride-2 level with its map 29; 4096 bins: 11 and 20.)
 constexpr int BS_SMALL_THREADS = 1024;
-constexpr int BS_SMALL_BIN_BITS = 10;
+constexpr int BS_SMALL_BIN_BITS = 12;
 constexpr int BS_SMALL_BINS = 1 << BS_SMALL_BIN_BITS;
-static_assert(BS_SMALL_BINS <= BS_SMALL_THREADS && BS_SMALL_BINS % 64 == 0, "one thread clears a bin; wave 0 scans whole groups");
+static_assert(BS_SMALL_BINS == 4 * BS_SMALL_THREADS, "four bins per thread");
 constexpr int BS_SMALL_MAX = 4096;  // >= BS_MIN_N - 1
 template <typename KeyT, typename Src, bool DEDUP>
 __global__ __launch_bounds__(BS_SMALL_THREADS) void bs_small_sort_kernel(const Src srcs, int n, int shift, const LevelOut<KeyT> lo,
@@ -841,10 +842,11 @@ __global__ __launch_bounds__(BS_SMALL_THREADS) void bs_small_sort_kernel(const S
   KeyT* __restrict__ out_k = lo.keys[blockIdx.y];
   __shared__ KeyT sk0[BS_SMALL_MAX], sk1[BS_SMALL_MAX];
   __shared__ int16_t sv1[BS_SMALL_MAX];
-  __shared__ int s_start[BS_SMALL_BINS + 1], s_cur[BS_SMALL_BINS];
+  __shared__ __align__(16) int s_cur[BS_SMALL_BINS];  // counts, then every bin's cursor, in the end where the bin ends
   __shared__ int wave_tot[BS_SMALL_THREADS / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid < BS_SMALL_BINS) s_cur[tid] = 0;
+  int4* cur4 = reinterpret_cast<int4*>(s_cur) + tid;
+  *cur4 = make_int4(0, 0, 0, 0);
   __syncthreads();
   bool bad = false;
   for (int i = tid; i < n; i += BS_SMALL_THREADS) {
@@ -856,27 +858,19 @@ __global__ __launch_bounds__(BS_SMALL_THREADS) void bs_small_sort_kernel(const S
   }
   src.report(bad);
   __syncthreads();
-  if (wave == 0) {  // exclusive scan of the bin counts, PL consecutive bins per lane
-    constexpr int PL = BS_SMALL_BINS / 64;
-    int c[PL], sum = 0;
-#pragma unroll
-    for (int u = 0; u < PL; ++u) {
-      c[u] = s_cur[lane * PL + u];
-      sum += c[u];
-    }
+  {  // exclusive scan of the bin counts, four bins per thread
+    const int4 c = *cur4;
+    const int sum = c.x + c.y + c.z + c.w;
     int x = sum;
     for (int d = 1; d < 64; d <<= 1) {
       const int y = __shfl_up(x, d, 64);
       if (lane >= d) x += y;
     }
+    if (lane == 63) wave_tot[wave] = x;
+    __syncthreads();
     int run = x - sum;
-#pragma unroll
-    for (int u = 0; u < PL; ++u) {
-      s_start[lane * PL + u] = run;
-      s_cur[lane * PL + u] = run;
-      run += c[u];
-    }
-    if (lane == 63) s_start[BS_SMALL_BINS] = run;
+    for (int w = 0; w < wave; ++w) run += wave_tot[w];
+    *cur4 = make_int4(run, run + c.x, run + c.x + c.y, run + c.x + c.y + c.z);
   }
   __syncthreads();
   for (int i = tid; i < n; i += BS_SMALL_THREADS) {
@@ -890,7 +884,7 @@ __global__ __launch_bounds__(BS_SMALL_THREADS) void bs_small_sort_kernel(const S
     const KeyT key = sk1[x];
     const int vi = sv1[x];
     const int b = bs_bin(key, shift, BS_SMALL_BINS);
-    const int a = s_start[b], e = s_start[b + 1];
+    const int a = b > 0 ? s_cur[b - 1] : 0, e = s_cur[b];
     int r = a;
     int y = a;
     // eight candidates per trip, read before any is compared: one LDS round trip per trip instead of one per key

@@ -530,10 +530,13 @@ __global__ __launch_bounds__(64 * K) void kmap_search_kernel(const SearchBatch<K
 // workgroup per tile copies its hits, offset by offset, to where the scan of the per-tile counts puts them.  List k
 // comes out ordered by output index, without atomics and without a |V_q| x K^3 matrix having existed.  list_base gets
 // where the pairs of every 32-row block start in every list, which is how the feature kernel finds a block's pairs.
+// SCAN: tile_base holds the per-tile counts themselves, and every workgroup adds up the tiles before its own (a few
+// tiles: cheaper than the scan's launch).
+template <bool SCAN>
 __global__ __launch_bounds__(256) void ws_fill_pairs_kernel(const int2* __restrict__ tile_pairs, int n_out_h,
                                                             const int* __restrict__ n_out_d, int K3, int tile,
                                                             const int32_t* __restrict__ tile_base, int n_tiles_cap,
-                                                            const int32_t* __restrict__ nnz, const uint8_t* __restrict__ tile_sub,
+                                                            int32_t* __restrict__ nnz, const uint8_t* __restrict__ tile_sub,
                                                             int32_t* __restrict__ ws_in, int32_t* __restrict__ ws_out,
                                                             int64_t ws_stride, int k_lim, int32_t* __restrict__ list_base) {
   __shared__ int s_off[WS_MAX_K3_SEARCH + 1], s_dst[WS_MAX_K3_SEARCH];
@@ -542,18 +545,42 @@ __global__ __launch_bounds__(256) void ws_fill_pairs_kernel(const int2* __restri
   if (i0 >= n_out) return;
   const int n_tiles = (n_out + tile - 1) / tile;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if constexpr (SCAN) {
+    // eight threads per offset, eight tiles' counts of a thread in flight
+    for (int k0 = 0; k0 < K3; k0 += 32) {
+      const int k = k0 + (tid >> 3);
+      int sum = 0;
+      if (k < k_lim) {
+        const int32_t* col = tile_base + int64_t(k) * n_tiles_cap;
+        for (int t0 = tid & 7; t0 < int(blockIdx.x); t0 += 64) {
+          int c[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) c[u] = col[min(t0 + u * 8, int(blockIdx.x))];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) sum += t0 + u * 8 < int(blockIdx.x) ? c[u] : 0;
+        }
+      }
+      for (int d = 4; d > 0; d >>= 1) sum += __shfl_xor(sum, d, 64);
+      if ((tid & 7) == 0 && k < K3) s_dst[k] = sum;
+    }
+    __syncthreads();
+  }
   // counts of this tile (difference of consecutive scanned bases) and their exclusive prefix
   if (wave == 0) {
     int carry = 0;
     for (int k0 = 0; k0 < K3; k0 += 64) {
       const int k = k0 + lane;
       int c = 0;
-      if (k < K3) s_dst[k] = 0;
+      if (!SCAN && k < K3) s_dst[k] = 0;
       if (k < k_lim) {
         const int32_t* col = tile_base + int64_t(k) * n_tiles_cap;
         const int b = col[blockIdx.x];
-        c = (int(blockIdx.x) + 1 < n_tiles ? col[blockIdx.x + 1] : nnz[k]) - b;
-        s_dst[k] = b;
+        if constexpr (SCAN) {
+          c = b;
+        } else {
+          c = (int(blockIdx.x) + 1 < n_tiles ? col[blockIdx.x + 1] : nnz[k]) - b;
+          s_dst[k] = b;
+        }
       }
       int x = c;
       for (int d = 1; d < 64; d <<= 1) {
@@ -576,7 +603,11 @@ __global__ __launch_bounds__(256) void ws_fill_pairs_kernel(const int2* __restri
     base[e] = s_dst[k] + (s_off[k + 1] > s_off[k] ? sub[k * tile_blocks + b] : 0);
   }
   if (int(blockIdx.x) + 1 == n_tiles)  // one row more than blocks: the lists' ends
-    for (int k = tid; k < K3; k += 256) base[n_bl * K3 + k] = s_dst[k] + s_off[k + 1] - s_off[k];
+    for (int k = tid; k < K3; k += 256) {
+      const int end = s_dst[k] + s_off[k + 1] - s_off[k];
+      base[n_bl * K3 + k] = end;
+      if (SCAN) nnz[k] = end;
+    }
   for (int e = tid; e < total; e += 256) {
     int k = 0;  // last offset whose pairs start at or before e (offsets without pairs share their successor's start)
     for (int bit = 256; bit > 0; bit >>= 1)
@@ -588,6 +619,9 @@ __global__ __launch_bounds__(256) void ws_fill_pairs_kernel(const int2* __restri
   }
 }
 
+// Counts up to which the fill pass adds them up itself: build with lists, 4.1 k voxels 13.8 -> 12.0 us, 20 k (8451 counts)
+// 15.7 / 15.2, 30 k 16.5 / 16.6, 60 k 19.6 / 21.7.
+constexpr int64_t WS_SCAN_IN_FILL = 6144;
 // One workgroup per offset k: exclusive scan of that offset's per-tile counts in place, total into nnz[k].
 // A thread owns a run of consecutive tiles; the runs are fetched in batches of WS_SCAN_U loads per thread that are
 // all in flight together (a loop of load, scan, store rounds over 256 tiles at a time took 7.6 us for 3750 tiles:
@@ -964,12 +998,19 @@ static int search_maps(spc_kmap* const* ms, int count, hipStream_t s) {
     if (!(m->desc.layout & SPC_LAYOUT_WS)) break;
     const Level* out = m->out_level;
     const int n_out_h = static_cast<int>(out->n_host < 0 ? 0 : out->n_host);
-    hipLaunchKernelGGL(ws_scan_kernel, dim3(m->K3), dim3(256), 0, s, m->tile_counts, m->n_tiles, m->tile, n_out_h,
-                       out->n_dev, m->nnz_dev, m->k_lim);
-    if (m->n_tiles > 0)
-      hipLaunchKernelGGL(ws_fill_pairs_kernel, dim3(m->n_tiles), dim3(256), 0, s, m->tile_pairs, n_out_h, out->n_dev, m->K3,
-                         m->tile, m->tile_counts, m->n_tiles, m->nnz_dev, m->tile_sub, m->ws_in, m->ws_out, m->out_cap, m->k_lim,
-                         m->list_base);
+    auto fill = [&](auto SCAN_) {
+      hipLaunchKernelGGL(ws_fill_pairs_kernel<decltype(SCAN_)::value>, dim3(m->n_tiles), dim3(256), 0, s, m->tile_pairs, n_out_h,
+                         out->n_dev, m->K3, m->tile, m->tile_counts, m->n_tiles, m->nnz_dev, m->tile_sub, m->ws_in, m->ws_out,
+                         m->out_cap, m->k_lim, m->list_base);
+    };
+    // (a level that may turn out empty leaves its list lengths to the scan)
+    if (out->n_host > 0 && int64_t(m->n_tiles) * m->k_lim <= WS_SCAN_IN_FILL) {
+      fill(std::true_type{});
+    } else {
+      hipLaunchKernelGGL(ws_scan_kernel, dim3(m->K3), dim3(256), 0, s, m->tile_counts, m->n_tiles, m->tile, n_out_h,
+                         out->n_dev, m->nnz_dev, m->k_lim);
+      if (m->n_tiles > 0) fill(std::false_type{});
+    }
     if (m->sym) launch_list_base(m, m->ws_in, m->k_lim, out, m->list_base_in, s);
     // the slabs are dead once the lists are filled: back to the cache (reuse is ordered behind this stream's work)
     pool_free(m->tile_pairs, s);
