@@ -337,7 +337,9 @@ extern "C" int spc_pack_coords(const int32_t* coords, int64_t n, const spc_pack_
   int32_t* iota = reinterpret_cast<int32_t*>(ws + off_iota);
   // the status word is only kept when somebody is going to read it
   int32_t* status = (flags & SPC_PACK_VALIDATE) ? reinterpret_cast<int32_t*>(ws + off_status) : nullptr;
-  PackParams p{pi.sh_b, pi.sh_x, pi.sh_y, pi.bits_b, pi.bits_x, pi.bits_y, pi.bits_z, d->origin[0], d->origin[1], d->origin[2], d->pad};
+  auto limit = [&](int bits) { return static_cast<uint32_t>(std::max<int64_t>(0, (int64_t(1) << bits) - 2 * int64_t(d->pad))); };
+  PackParams p{pi.sh_b, pi.sh_x, pi.sh_y, pi.bits_b, pi.bits_x, pi.bits_y, pi.bits_z, d->origin[0], d->origin[1], d->origin[2], d->pad,
+               limit(pi.bits_x), limit(pi.bits_y), limit(pi.bits_z)};
   if (status) hipLaunchKernelGGL(set_int_kernel, dim3(1), dim3(1), 0, s, status, 0);
   if (bucket) {
     SPC_RETURN_IF(bucket_pack_sort(pi.key_bits, reinterpret_cast<const int4*>(coords), n, p, pi.used_bits, status, keys_out, perm_out,

@@ -142,6 +142,7 @@ struct PackParams {
   int sh_b, sh_x, sh_y;
   int bits_b, bits_x, bits_y, bits_z;
   int ox, oy, oz, pad;
+  uint32_t lim_x, lim_y, lim_z;  // a field holds v - origin below 2^bits - 2 pad
 };
 
 #ifdef __HIPCC__
@@ -149,10 +150,9 @@ struct PackParams {
 // gives the all-ones key and sets `bad`.
 template <typename KeyT>
 __device__ inline KeyT pack_key_flag(const int4 c, const PackParams& p, bool& bad) {
-  const int64_t fx = int64_t(c.y) - p.ox, fy = int64_t(c.z) - p.oy, fz = int64_t(c.w) - p.oz;
-  const bool ok = c.x >= 0 && (int64_t(c.x) < (int64_t(1) << p.bits_b)) && fx >= 0 && fy >= 0 && fz >= 0 &&
-                  fx + 2 * int64_t(p.pad) < (int64_t(1) << p.bits_x) && fy + 2 * int64_t(p.pad) < (int64_t(1) << p.bits_y) &&
-                  fz + 2 * int64_t(p.pad) < (int64_t(1) << p.bits_z);
+  // (in 32 bits: where v >= origin, the difference is the wrapped one; a limit of 2^bits - 2 pad below zero admits nothing)
+  const uint32_t fx = uint32_t(c.y) - uint32_t(p.ox), fy = uint32_t(c.z) - uint32_t(p.oy), fz = uint32_t(c.w) - uint32_t(p.oz);
+  const bool ok = uint32_t(c.x) < (1u << p.bits_b) && c.y >= p.ox && c.z >= p.oy && c.w >= p.oz && fx < p.lim_x && fy < p.lim_y && fz < p.lim_z;
   bad |= !ok;
   return ok ? (KeyT(c.x) << p.sh_b) | (KeyT(fx + p.pad) << p.sh_x) | (KeyT(fy + p.pad) << p.sh_y) | KeyT(fz + p.pad)
             : ~KeyT(0);
