@@ -103,6 +103,271 @@ __global__ __launch_bounds__(256) void pad_rows_kernel(const T* __restrict__ F, 
   if (r < n) out[gid] = c < cin ? F[r * ld_in + c] : T(0);
 }
 
+__device__ __align__(16) uint32_t g_zero_row[64];  // zero-initialised, never written
+
+// The phase kernel's other way through a 3x3x3 layer, for levels whose neighbourhoods are nearly empty.  Every kernel that
+// walks (32-row block, offset) cells pays for a cell as for 32 rows; on uniformly random voxels (1.25 % full) a block has
+// 9.6 cells, of which all but the centre's hold 1.2 valid rows.  Here a workgroup takes POOL_BLOCKS blocks, two per wave:
+//   1. each half-wave lists the pairs of its block.  Cells of POOL_DENSE valid rows or more are left for step 2; the pairs of
+//      the others are counted per offset over the whole tile, and each draws a number among its offset's pairs;
+//   2. the dense cells are multiplied as everywhere else, by 32x32x16 MFMA into the block's accumulators;
+//   3. an offset's pairs from all blocks are multiplied together, 16 at a time, by 16x16x32 MFMA: its weights are read once
+//      per tile instead of once per block.  The product rows stay in LDS, in fp32;
+//   4. every wave adds its blocks' product rows to its accumulators, two at a time, by 32x32x2 fp32 MFMA with a selection
+//      matrix of zeros and ones, and stores its rows.
+// Pairs for more product rows than the LDS area holds are done in several rounds over ranges of offsets.  A row's sum is
+// taken in a fixed order (dense cells by offset, then pairs by offset), and a product does not depend on the number it
+// drew, so results are bit-reproducible.
+// A tile of 1024 rows takes 26 us (listing 5, dense cells 7, products 5, additions 4, stores 3): the latencies of a chain of
+// dependent loads, of which one workgroup fills a CU's LDS.  3 M random voxels, 64->64: 513 us by phases, 326 us pooled;
+// 1 M: 176 / 104; 200 k: 43 / 33; indoor scans, 240 k: 46 / 40.
+constexpr int POOL_WAVES = 16, POOL_BLOCKS = 32;
+constexpr int POOL_DENSE = 8;     // valid rows from which a cell is multiplied on its own
+constexpr int POOL_PAIRS = 64;    // pairs in a block's list (a cell that does not fit any more is multiplied on its own too)
+constexpr int POOL_MAX_K3 = 27;
+constexpr int POOL_SLOTS = 400;   // product rows in LDS
+constexpr int POOL_KCAP = (POOL_DENSE - 1) * POOL_BLOCKS;  // pairs of one offset in a tile
+constexpr int POOL_DROWS = 2;     // dense cells of a block whose indices stay in LDS
+static_assert(POOL_KCAP <= POOL_SLOTS, "an offset's pairs fit one round");
+
+typedef float floatx4v __attribute__((ext_vector_type(4)));
+template <typename T>
+__device__ inline floatx4v mma16(typename Mfma<T>::V a, typename Mfma<T>::V b, floatx4v c);
+template <>
+__device__ inline floatx4v mma16<_Float16>(half8 a, half8 b, floatx4v c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
+template <>
+__device__ inline floatx4v mma16<__bf16>(bf16x8 a, bf16x8 b, floatx4v c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+
+struct PoolLds {
+  static constexpr int PITCH = 68;  // floats (the four row groups of a 16x16 result then fall on different banks)
+  float stage[POOL_SLOTS][PITCH];
+  int in[POOL_MAX_K3][POOL_KCAP];        // input rows of the pairs of every offset
+  int pairs[POOL_BLOCKS][POOL_PAIRS];    // offset | row << 5 | number within the offset's pairs << 10
+  int drow[POOL_BLOCKS][POOL_DROWS][32];
+  int kcnt[32];                          // pairs of every offset
+  unsigned char dense[POOL_BLOCKS][POOL_MAX_K3 + 1];
+};
+
+template <typename T, int NKK>
+__device__ inline void conv_pool_tile(PoolLds& L, const int64_t blk0, const int64_t n_blocks, const int n_out, const int32_t* __restrict__ M,
+                                      const uint32_t* __restrict__ block_masks, const unsigned kmask, const int K3, const T* __restrict__ F,
+                                      const int64_t ld_in, const T* __restrict__ Wp, T* __restrict__ out, const int64_t ld_out,
+                                      const int cin, const int relu, const int nb_total, const int slab) {
+  using V = typename Mfma<T>::V;
+  constexpr int NB = 2;
+  const V* __restrict__ W = reinterpret_cast<const V*>(Wp);
+  const int KK = cin / 16;
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const T* zero_row = reinterpret_cast<const T*>(g_zero_row);
+  if (tid < 32) L.kcnt[tid] = 0;
+
+  // ---- 1. the pairs of block 2 * wave + lh
+  int np = 0, nd = 0;  // pairs and dense cells listed so far, the same in a half-wave
+  const int bl = 2 * wave + lh;
+  unsigned present = blk0 + bl < n_blocks ? block_masks[blk0 + bl] & kmask : 0u;
+  const int32_t* Mb = M + (blk0 + bl) * K3 * 32 + lr;
+  __syncthreads();
+  while (__ballot(present != 0u)) {
+    constexpr int U = 12;  // cells whose indices are fetched together
+    int k[U], val[U], place[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      k[u] = present != 0u ? __builtin_ctz(present) : -1;
+      present &= present - 1u;
+      val[u] = -1;
+      if (k[u] >= 0) val[u] = Mb[k[u] * 32];
+    }
+    int count = 0;  // of offset lr, in this pass
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const unsigned long long bal = __ballot(val[u] >= 0);
+      const unsigned valid = static_cast<unsigned>(lh ? bal >> 32 : bal);
+      const int c = __popc(valid);
+      const bool pool = c < POOL_DENSE && np + c <= POOL_PAIRS;
+      place[u] = pool ? np + __popc(valid & ((1u << lr) - 1u)) : -1;
+      if (pool) {
+        np += c;
+        if (lr == k[u]) count = c;
+      } else {
+        if (nd < POOL_DROWS) L.drow[bl][nd][lr] = val[u];
+        if (lr == 0) L.dense[bl][nd] = static_cast<unsigned char>(k[u]);
+        ++nd;
+      }
+    }
+    int first = 0;
+    if (count > 0) first = atomicAdd(&L.kcnt[lr], count);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int f = __shfl(first, lh * 32 + max(k[u], 0), 64);
+      const unsigned long long bal = __ballot(val[u] >= 0);
+      const unsigned valid = static_cast<unsigned>(lh ? bal >> 32 : bal);
+      if (place[u] >= 0 && val[u] >= 0) {
+        const int at = f + __popc(valid & ((1u << lr) - 1u));
+        L.in[k[u]][at] = val[u];
+        L.pairs[bl][place[u]] = k[u] | (lr << 5) | (at << 10);
+      }
+    }
+  }
+  const int np_b[2] = {__builtin_amdgcn_readlane(np, 0), __builtin_amdgcn_readlane(np, 32)};
+  const int nd_b[2] = {__builtin_amdgcn_readlane(nd, 0), __builtin_amdgcn_readlane(nd, 32)};
+
+  floatx16 acc[2][NB];
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[b][nb][r] = 0.f;
+  // ---- 2. dense cells of the wave's two blocks, those of the same offset together
+  __builtin_amdgcn_wave_barrier();
+  int d[2] = {0, 0};
+  while (d[0] < nd_b[0] || d[1] < nd_b[1]) {
+    int kb[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+      kb[b] = d[b] < nd_b[b] ? __builtin_amdgcn_readfirstlane(static_cast<int>(L.dense[2 * wave + b][d[b]])) : 255;
+    const int k = min(kb[0], kb[1]);
+    const T* src[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      int idx = -1;
+      if (kb[b] == k) {
+        idx = d[b] < POOL_DROWS ? L.drow[2 * wave + b][d[b]][lr] : M[((blk0 + 2 * wave + b) * K3 + k) * 32 + lr];
+        ++d[b];
+      }
+      src[b] = idx < 0 ? nullptr : F + int64_t(idx) * ld_in + 8 * lh;
+    }
+    for (int k0 = 0; k0 < KK; k0 += NKK) {
+      V av[2][NKK];
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+        if (kb[b] == k) {
+          const T* s = src[b] ? src[b] + k0 * 16 : zero_row;
+#pragma unroll
+          for (int kk = 0; kk < NKK; ++kk) av[b][kk] = *reinterpret_cast<const V*>(s + kk * 16);
+        }
+      const V* w = W + ((int64_t(k) * KK + k0) * nb_total + slab * NB) * 64 + lane;
+#pragma unroll
+      for (int kk = 0; kk < NKK; ++kk) {
+        V bv[NB];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) bv[nb] = w[(int64_t(kk) * nb_total + nb) * 64];
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+          if (kb[b] == k)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) acc[b][nb] = Mfma<T>::mma(av[b][kk], bv[nb], acc[b][nb]);
+      }
+    }
+  }
+  __syncthreads();  // every block's pairs are listed
+
+  // lane k: the pairs of offset k, its first slot and its first task (16 slots of one offset)
+  const int c_k = lane < K3 ? L.kcnt[lane & 31] : 0, t_k = (c_k + 15) >> 4;
+  int scan = c_k | (t_k << 16);
+#pragma unroll
+  for (int s = 1; s < 32; s <<= 1) {
+    const int y = __shfl_up(scan, s, 64);
+    if (lane >= s) scan += y;
+  }
+  const int base_k = (scan & 0xffff) - c_k, task_k = (scan >> 16) - t_k;
+
+  // ---- 3., 4. product rows, as many offsets at a time as the LDS area holds
+  for (int ka = 0; ka < K3;) {
+    const int s0 = __builtin_amdgcn_readlane(base_k, ka), t0 = __builtin_amdgcn_readlane(task_k, ka);
+    // offsets ka .. kb - 1: as many as fit (an offset alone always does)
+    const int kb = __builtin_ctzll(__ballot(lane >= K3 || (lane >= ka && base_k + c_k - s0 > POOL_SLOTS)));
+    const int t1 = __builtin_amdgcn_readlane(scan, kb - 1) >> 16, s1 = __builtin_amdgcn_readlane(scan, kb - 1) & 0xffff;
+    const int l16 = lane & 15, g = lane >> 4;
+    for (int t = t0 + wave; t < t1; t += POOL_WAVES) {
+      const int k = 63 - __builtin_clzll(__ballot(lane < K3 && task_k <= t));
+      const int f = (t - __builtin_amdgcn_readlane(task_k, k)) * 16, rows = min(16, __builtin_amdgcn_readlane(c_k, k) - f);
+      const int slot = __builtin_amdgcn_readlane(base_k, k) + f - s0;
+      const int idx = l16 < rows ? L.in[k][f + l16] : -1;
+      const T* src = idx < 0 ? nullptr : F + int64_t(idx) * ld_in + g * 8;
+      const V* w = W + (int64_t(k) * KK * nb_total + slab * NB) * 64 + (g & 1) * 32 + l16;
+      floatx4v c[2 * NB];
+#pragma unroll
+      for (int ct = 0; ct < 2 * NB; ++ct) c[ct] = floatx4v{0.f, 0.f, 0.f, 0.f};
+      for (int k0 = 0; k0 < KK; k0 += NKK) {  // 32 channels at a time: lane group g holds 8 of them
+        const T* s = src ? src + k0 * 16 : zero_row;
+        V av[NKK / 2], bv[NKK / 2][2 * NB];
+#pragma unroll
+        for (int u = 0; u < NKK / 2; ++u) {
+          av[u] = *reinterpret_cast<const V*>(s + u * 32);
+#pragma unroll
+          for (int ct = 0; ct < 2 * NB; ++ct)
+            bv[u][ct] = w[(int64_t(k0 + 2 * u + (g >> 1)) * nb_total + (ct >> 1)) * 64 + (ct & 1) * 16];
+        }
+#pragma unroll
+        for (int u = 0; u < NKK / 2; ++u)
+#pragma unroll
+          for (int ct = 0; ct < 2 * NB; ++ct) c[ct] = mma16<T>(av[u], bv[u][ct], c[ct]);
+      }
+      // D layout of the 16x16 MFMA: register r of lane l is row 4*(l/16) + r, column l%16
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (4 * g + r < rows) {
+          float* dst = &L.stage[slot + 4 * g + r][l16];
+#pragma unroll
+          for (int ct = 0; ct < 2 * NB; ++ct) dst[ct * 16] = c[ct][r];
+        }
+    }
+    __syncthreads();
+    static_for<2>([&](auto B_) {
+      constexpr int b = decltype(B_)::value;
+      // lane p: pair p of the block: slot | row << 16
+      int e = -1;
+      const int pr = lane < np_b[b] ? L.pairs[2 * wave + b][lane] : 0;
+      const int slot = __shfl(base_k, pr & 31, 64) + (pr >> 10);
+      if (lane < np_b[b] && slot >= s0 && slot < s1) e = (slot - s0) | (((pr >> 5) & 31) << 16);
+      for (int p = 0; p < np_b[b]; p += 2) {
+        const int x = __shfl(e, p + lh, 64);
+        const float sel = x >= 0 && (x >> 16) == lr ? 1.f : 0.f;
+        const float* src = &L.stage[x & 0xffff & (x >= 0 ? -1 : 0)][lr];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+          acc[b][nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(sel, x >= 0 ? src[nb * 32] : 0.f, acc[b][nb], 0, 0, 0);
+      }
+    });
+    ka = kb;
+    if (ka < K3) __syncthreads();  // the area is written again
+  }
+
+  // D layout of the 32x32 MFMA: register r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l%32
+  T* o = out + lr;
+  static_for<2>([&](auto B_) {
+    constexpr int b = decltype(B_)::value;
+    const int64_t i0 = (blk0 + 2 * wave + b) * 32;
+    const int rows = static_cast<int>(max<int64_t>(0, min<int64_t>(32, n_out - i0)));
+    T* prow = o + (i0 + 4 * lh) * ld_out;
+    auto store_all = [&](auto FULL_) {
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int rr = 8 * (r / 4) + (r % 4);  // row = rr + 4 * lh
+          if (decltype(FULL_)::value || rr + 4 * lh < rows) {
+            const float v = acc[b][nb][r];
+            prow[rr * ld_out + nb * 32] = from_f32<T>(relu ? fmaxf(v, 0.f) : v);
+          }
+        }
+    };
+    if (rows == 32) store_all(std::true_type{});
+    else if (rows > 0) store_all(std::false_type{});
+  });
+}
+
+// Whether a level is one for the pooled way: enough tiles to give most CUs one (100 k random voxels, 64->64: 23 us by phases,
+// 25 pooled), and three quarters of 64 blocks looked at marked by the search as holding at most POOL_BLOCK_PAIRS pairs.
+// Every workgroup finds the same.
+__device__ inline bool pool_level(const uint32_t* __restrict__ block_masks, int64_t n_blocks, int n_slabs, int lane) {
+  if (n_blocks * n_slabs < 128 * POOL_BLOCKS) return false;
+  const uint32_t m = block_masks[(n_blocks * lane) >> 6];
+  return __popcll(__ballot((m & POOL_MARK) != 0u)) >= 48;
+}
+
 // Output-stationary kernel: waves are autonomous, weights are staged through LDS in phases.
 //
 // A workgroup of WAVES waves walks the weight tensor once, in phases of up to HALF_BYTES.
@@ -129,7 +394,6 @@ __global__ __launch_bounds__(256) void pad_rows_kernel(const T* __restrict__ F, 
 // which gather the same feature rows, run on the same XCD and share its L2.
 constexpr int HALF_BYTES = 72 * 1024;  // 9 offsets of 64x64 fp16: one x-slab of a 3x3x3 kernel per phase
 constexpr int KLIST_CAP = 352;  // >= 7^3
-__device__ __align__(16) uint32_t g_zero_row[64];  // zero-initialised, never written
 
 constexpr int PHASE_XCD_CHUNK = 16;  // tiles (of two 32-row blocks) per chunk; 4 to 64 measured alike
 __host__ __device__ inline int64_t phase_tiles_per_xcd(int64_t n_tiles) {
@@ -195,6 +459,17 @@ __global__ __launch_bounds__(64 * WAVES) void conv_os_phase_kernel(const int32_t
   const int nch = cin / CKS;
   (void)n_wg_per_xcd;
 
+  if constexpr (NB == 2 && WAVES == POOL_WAVES && NKK >= 2) {
+    if (K3 == 27 && pool_level(block_masks, n_blocks, gridDim.y, lane)) {
+      // an XCD takes a contiguous range of tiles: neighbours in x are a few tiles away and share its L2
+      const int64_t n_pool = (n_blocks + POOL_BLOCKS - 1) / POOL_BLOCKS, per = (n_pool + 7) / 8, t = xcd * per + wg_in_xcd;
+      if (wg_in_xcd < per && t < n_pool)
+        conv_pool_tile<T, NKK>(*reinterpret_cast<PoolLds*>(smem), t * POOL_BLOCKS, n_blocks, n_out, M, block_masks, kmask.w[0], K3, F,
+                               ld_in, Wp, out, ld_out, cin, relu, nb_total, slab);
+      return;
+    }
+  }
+
   // phase 0 of the weights is requested first, so that its latency overlaps the set-up below
   const int n_chunks = K3 * nch;
   V8 st[SV];
@@ -218,7 +493,6 @@ __global__ __launch_bounds__(64 * WAVES) void conv_os_phase_kernel(const int32_t
       if (i * THREADS + tid < n_vec) half[i * THREADS + tid] = st[i];
   };
   stage_load(0);
-
   // offsets present in this wave's blocks: union of the blocks' masks, one word per 32 offsets,
   // parked in LDS; the positions below walk its set bits in ascending order with scalar ops
   unsigned* smask = reinterpret_cast<unsigned*>(klist);
@@ -899,7 +1173,8 @@ static void launch_os_mfma(const ConvArgs& a, const T* Wp) {
   const int64_t n_tiles = (n_blocks + RBK - 1) / RBK;
   const int64_t tiles_per_xcd = phase_tiles_per_xcd(n_tiles);
   const int per_xcd = phase_wgs_per_xcd(tiles_per_xcd, WAVES, n_slabs);
-  const size_t lds = 2 * HALF_BYTES + size_t(WAVES) * KLIST_CAP * 2;
+  constexpr size_t lds = 2 * HALF_BYTES + size_t(WAVES) * KLIST_CAP * 2;
+  static_assert(NB != 2 || sizeof(PoolLds) <= lds, "the pooled way fits the launch");
   auto go = [&](auto NKK_) {
     constexpr int NKK = decltype(NKK_)::value;
     const int cpp = std::max(1, HALF_BYTES / (16 * NKK * NB * 32 * int(sizeof(T))));

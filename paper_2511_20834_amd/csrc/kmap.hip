@@ -54,6 +54,14 @@ __device__ inline unsigned half_wave_or(unsigned x) {
   x |= static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0x142, 0xf, 0xf, true));  // lane 15 of a row to the next row
   return x;
 }
+// The same, summing.
+__device__ inline int half_wave_sum(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);
+  return x + __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, true);  // lane 15 of an even row to the next row
+}
 
 // Both ends of a window by one wave: the lower half searches the first index with key >= q, the upper half the first
 // index with key > q (q per half).  The first rounds need no memory: both searches start from the same N_PROBES probes
@@ -192,6 +200,7 @@ __global__ __launch_bounds__(64 * K) void kmap_search_kernel(const SearchBatch<K
   __shared__ int s_off[PAIRS ? K3 + 1 : 1];  // PAIRS: where every offset's pairs start in the tile's slab
   __shared__ int s_cnt[PAIRS ? K3 : 1];
   __shared__ unsigned s_mask[MAX_BLOCKS * MW];
+  __shared__ int s_pairs[K == 3 ? MAX_BLOCKS : 1];  // K = 3: hits of every block
   const int tid = threadIdx.x, lane = tid & 63;
   const int ix = __builtin_amdgcn_readfirstlane(tid >> 6);
   int32_t* wval = reinterpret_cast<int32_t*>(smem) + ix * WIN_CAP;                                     // row numbers of the staged keys
@@ -211,6 +220,7 @@ __global__ __launch_bounds__(64 * K) void kmap_search_kernel(const SearchBatch<K
   if constexpr (PAIRS)
     for (int k = tid; k < K3; k += 64 * K) s_cnt[k] = 0;
   for (int k = tid; k < MAX_BLOCKS * MW; k += 64 * K) s_mask[k] = 0u;
+  if (K == 3 && tid < MAX_BLOCKS) s_pairs[tid] = 0;
 
   KeyT okey[CHUNKS];
 #pragma unroll
@@ -457,7 +467,12 @@ __global__ __launch_bounds__(64 * K) void kmap_search_kernel(const SearchBatch<K
           for (int t = 0; t < K; ++t) x |= ((hb >> (j * K + t)) & 1u) << (j * K + K - 1 - t);
         hb = x;
       }
-      hb = half_wave_or(hb & osb);
+      hb &= osb;
+      if constexpr (K == 3) {
+        const int sum = half_wave_sum(__popc(hb));
+        if ((lane & 31) == 31) atomicAdd(&s_pairs[c * 2 + (lane >> 5)], sum);
+      }
+      hb = half_wave_or(hb);
       const int bit = ix * G + BIT0;
       if ((lane & 31) == 31 && hb) {
         const unsigned long long f = static_cast<unsigned long long>(hb) << (bit & 31);
@@ -522,7 +537,8 @@ __global__ __launch_bounds__(64 * K) void kmap_search_kernel(const SearchBatch<K
   }
   if (M) {
     const int n_bl = (rows + 31) >> 5;
-    for (int e = tid; e < n_bl * MW; e += 64 * K) args.block_masks[b0 * MW + e] = s_mask[e];
+    for (int e = tid; e < n_bl * MW; e += 64 * K)
+      args.block_masks[b0 * MW + e] = s_mask[e] | (K == 3 && s_pairs[K == 3 ? e : 0] <= POOL_BLOCK_PAIRS ? POOL_MARK : 0u);
   }
 }
 

@@ -778,3 +778,82 @@ def test_conv_shapes_and_sizes(n, dtype, cin, cout, ld):
         assert_close(o[:, 1:1 + cout], ref, TOL[dtype], (layout, kw))
         assert np.all(o[:, 0] == 7.0) and np.all(o[:, 1 + cout:] == 7.0), (layout, kw)
         km.destroy()
+
+
+def _lin_cloud(lin, dims):
+    return np.stack([np.zeros(len(lin), int), lin // (dims[1] * dims[2]), lin // dims[2] % dims[1], lin % dims[2]], 1).astype(np.int32)
+
+
+# ----------------------------------------------------------------------------- nearly empty neighbourhoods (pooled pairs)
+@pytest.mark.parametrize("n,cin,cout,dtype,density,cube", [
+    (32 * 1024, 64, 256, torch.float16, 0.01, 0),       # whole tiles
+    (32 * 1024 + 1, 32, 256, torch.bfloat16, 0.012, 0),  # a tile of one voxel
+    (36001, 96, 256, torch.float16, 0.002, 12),          # a full cube: cells multiplied on their own, more of them than stay in LDS
+    (40033, 64, 256, torch.bfloat16, 0.016, 9),          # tiles that need several rounds, lists that overflow
+    (131105, 128, 64, torch.float16, 0.012, 0),          # one slab
+])
+def test_conv_sparse_neighbourhoods(n, cin, cout, dtype, density, cube):
+    rng = np.random.default_rng(n)
+    side = int(round((n / density) ** (1 / 3))) + 1
+    dims = (side, side, side)
+    full = [(x * side + y) * side + z for x in range(cube) for y in range(cube) for z in range(cube)]
+    lin = np.unique(np.concatenate([np.array(full, np.int64), rng.choice(side ** 3, size=n + n // 4, replace=False)]))
+    rest = np.setdiff1d(lin, full)
+    c = _lin_cloud(np.concatenate([np.array(full, np.int64), rng.permutation(rest)[: n - len(full)]]), dims)
+    desc = fit_desc(c, [(3, 1, 1)])
+    keys, _ = gpu_pack(c, desc)
+    cs, _ = oracle.sort_coords(c)
+    M = oracle.kernel_map(cs, cs, 3, 1)
+    Ft, F64 = to_torch(synth.features(n, cin, np.float16, seed=33), dtype)
+    Wt, W64 = to_torch(synth.weights(27, cin, cout, np.float16, seed=34), dtype)
+    ref = oracle.conv(M, F64, W64)
+    km = B.spc_build_kmap(keys, desc, 3)
+    Wp = B.spc_conv_prepare_weights(Wt)
+    a = B.spc_conv_forward(km, Ft, Wp, flags=B.CONV_OS_PHASE | B.CONV_PACKED_WEIGHTS)
+    b = B.spc_conv_forward(km, Ft, Wt, flags=B.CONV_OS_PHASE | B.CONV_RELU)
+    assert_close(a.cpu().to(torch.float64).numpy(), ref, TOL[dtype], "pooled")
+    assert torch.equal(b, a.clamp_min(0))
+    assert torch.equal(a, B.spc_conv_forward(km, Ft, Wp, flags=B.CONV_OS_PHASE | B.CONV_PACKED_WEIGHTS))
+    km.destroy()
+
+
+# ----------------------------------------------------------------------------- wide slabs, tiles shared by workgroups
+@pytest.mark.parametrize("n,cin,cout", [(33, 256, 256), (480, 256, 256), (1025, 128, 256), (481, 128, 128), (2049, 64, 128), (6001, 64, 128)])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+def test_conv_wide(n, cin, cout, dtype):
+    rng = np.random.default_rng(n + cin)
+    side = max(3, int(round((n / 0.25) ** (1 / 3))) + 1)
+    c = _lin_cloud(rng.choice(side ** 3, size=n, replace=False), (side, side, side))
+    desc = fit_desc(c, [(3, 1, 1)])
+    keys, _ = gpu_pack(c, desc)
+    cs, _ = oracle.sort_coords(c)
+    Ft, F64 = to_torch(synth.features(n, cin, np.float16, seed=35), dtype)
+    Wt, W64 = to_torch(synth.weights(27, cin, cout, np.float16, seed=36), dtype)
+    ref = oracle.conv(oracle.kernel_map(cs, cs, 3, 1), F64, W64)
+    Wp = B.spc_conv_prepare_weights(Wt)
+    for layout, df in ((B.LAYOUT_OS, B.DATAFLOW_OS), (B.LAYOUT_WS, B.DATAFLOW_WS)):
+        km = B.spc_build_kmap(keys, desc, 3, layout=layout)
+        for _ in range(2):  # (the counters of shared tiles are left at zero)
+            o = B.spc_conv_forward(km, Ft, Wp, df, B.CONV_PACKED_WEIGHTS)
+            assert_close(o.cpu().to(torch.float64).numpy(), ref, TOL[dtype], (layout, "packed"))
+        assert_close(B.spc_conv_forward(km, Ft, Wt, df).cpu().to(torch.float64).numpy(), ref, TOL[dtype], (layout, "plain"))
+        km.destroy()
+
+
+# ----------------------------------------------------------------------------- edges of the sort's and the list build's size ranges
+@pytest.mark.parametrize("n", [4095, 4096, 4097, 14528, 14529, 32768, 32769, 36865])
+def test_sort_and_list_edges(n):
+    rng = np.random.default_rng(n)
+    dims = (400, 60, 40)
+    c = _lin_cloud(rng.choice(dims[0] * dims[1] * dims[2], size=n, replace=False), dims)
+    desc = fit_desc(c, [(3, 1, 1)])
+    keys, perm = gpu_pack(c, desc)
+    k = keys_to_u64(keys)
+    assert np.all(k[1:] > k[:-1])
+    cs, order = oracle.sort_coords(c)
+    assert np.array_equal(c[perm.cpu().numpy()], cs)
+    km = B.spc_build_kmap(keys, desc, 3, layout=B.LAYOUT_BOTH)
+    a, b = km.export_triples(B.LAYOUT_OS), km.export_triples(B.LAYOUT_WS)
+    srt = lambda t: t[np.lexsort(t.T[::-1])]
+    assert len(a) > n and np.array_equal(srt(a), srt(b))
+    km.destroy()
