@@ -165,8 +165,10 @@ def spc_pack_coords(coords: torch.Tensor, desc: PackDesc, want_perm: bool = True
                     perm_out: torch.Tensor | None = None):
     """coords: int32 [N,4] device tensor (b,x,y,z).  Returns (keys, perm): sorted packed keys
     (int32/int64 tensors holding the unsigned bit patterns) and the permutation (or None)."""
-    assert coords.dtype == torch.int32 and coords.dim() == 2 and coords.shape[1] == 4
-    n = coords.shape[0]
+    # (every attribute of a tensor costs about 0.1 us of host time, and a call reads some twenty: each is read once)
+    shape = coords.shape
+    assert coords.dtype == torch.int32 and len(shape) == 2 and shape[1] == 4
+    n = shape[0]
     if workspace is None:
         workspace = torch.empty(spc_pack_workspace_bytes(n, desc), dtype=torch.uint8, device=coords.device)
     kdt = torch.int32 if desc.key_bits == 32 else torch.int64
@@ -177,9 +179,10 @@ def spc_pack_coords(coords: torch.Tensor, desc: PackDesc, want_perm: bool = True
         perm = perm_out if perm_out is not None else torch.empty(n, dtype=torch.int32, device=coords.device)
         assert perm.dtype == torch.int32 and perm.numel() == n
     size = ctypes.c_size_t(workspace.numel())
-    _check(lib().spc_pack_coords(_dev_ptr(coords), n, ctypes.byref(desc), _dev_ptr(keys),
-                                 _dev_ptr(perm) if want_perm else None, _dev_ptr(workspace), ctypes.byref(size), flags,
-                                 _stream(stream)))
+    rc = lib().spc_pack_coords(_dev_ptr(coords), n, ctypes.byref(desc), _dev_ptr(keys), _dev_ptr(perm) if want_perm else None,
+                               _dev_ptr(workspace), ctypes.byref(size), flags, current_raw_stream() if stream is None else _stream(stream))
+    if rc:
+        _check(rc)
     return keys, perm
 
 
@@ -203,6 +206,7 @@ class KMap:
     def __init__(self, handle: int, keep=(), desc: PackDesc | None = None):
         self.handle = ctypes.c_void_p(handle)
         self._keep = keep
+        self._kvol = None
         self.desc = desc
 
     def destroy(self):
@@ -212,7 +216,8 @@ class KMap:
 
     def __del__(self):
         try:
-            self.destroy()
+            if self.handle:
+                self.destroy()
         except Exception:
             pass
 
@@ -235,7 +240,9 @@ class KMap:
 
     @property
     def kvol(self) -> int:
-        return int(lib().spc_kmap_kvol(self.handle))
+        if self._kvol is None:
+            self._kvol = int(lib().spc_kmap_kvol(self.handle))
+        return self._kvol
 
     def nnz(self):
         import numpy as np
@@ -273,19 +280,28 @@ def spc_kmap_search_info(kmap: KMap):
     return int(t.value), int(w.value)
 
 
+_layer_desc_of: dict = {}  # layer descriptors in C form (read only) by their values, the first few hundred
+
+
 def spc_build_kmap(in_keys: torch.Tensor, desc: PackDesc, K: int, in_stride: int = 1, layer_stride: int = 1,
                    transposed: int = 0, layout: int = LAYOUT_BOTH, stream=None, in_perm: torch.Tensor | None = None) -> KMap:
     """in_perm: the permutation returned by spc_pack_coords; the map then addresses the caller's unsorted
     feature rows (spc_build_kmap_perm)."""
-    l = LayerDesc(K, in_stride, layer_stride, transposed, layout)
+    key = (K, in_stride, layer_stride, transposed, layout)
+    l = _layer_desc_of.get(key)
+    if l is None:
+        l = LayerDesc(*key)
+        if len(_layer_desc_of) < 256:
+            _layer_desc_of[key] = l
     h = ctypes.c_void_p()
+    n, raw = in_keys.shape[0], current_raw_stream() if stream is None else _stream(stream)
     if in_perm is None:
-        _check(lib().spc_build_kmap(_dev_ptr(in_keys), in_keys.shape[0], ctypes.byref(desc), ctypes.byref(l), ctypes.byref(h),
-                                    _stream(stream)))
-        return KMap(h.value, keep=(in_keys,), desc=desc)
-    assert in_perm.dtype == torch.int32 and in_perm.shape[0] == in_keys.shape[0]
-    _check(lib().spc_build_kmap_perm(_dev_ptr(in_keys), in_keys.shape[0], _dev_ptr(in_perm), ctypes.byref(desc), ctypes.byref(l),
-                                     ctypes.byref(h), _stream(stream)))
+        rc = lib().spc_build_kmap(_dev_ptr(in_keys), n, ctypes.byref(desc), ctypes.byref(l), ctypes.byref(h), raw)
+    else:
+        assert in_perm.dtype == torch.int32 and in_perm.shape[0] == n
+        rc = lib().spc_build_kmap_perm(_dev_ptr(in_keys), n, _dev_ptr(in_perm), ctypes.byref(desc), ctypes.byref(l), ctypes.byref(h), raw)
+    if rc:
+        _check(rc)
     return KMap(h.value, keep=(in_keys, in_perm), desc=desc)
 
 
@@ -315,21 +331,27 @@ def spc_conv_forward(kmap: KMap, feats_in: torch.Tensor, weights: torch.Tensor, 
     column slice of a wider buffer (row pitch = stride(0)); it is allocated when None.  hybrid_t: threshold of the
     hybrid dual dataflow (spc_conv_forward_hybrid); `dataflow` is ignored then."""
     assert feats_in.is_cuda and weights.is_cuda and weights.is_contiguous()
-    assert feats_in.dim() == 2 and feats_in.stride(1) == 1 and weights.dim() == 3
-    assert feats_in.dtype == weights.dtype and feats_in.dtype in _TORCH_DTYPE
-    cin, cout = feats_in.shape[1], weights.shape[2]
+    fs, ws, fst, dtype = feats_in.shape, weights.shape, feats_in.stride(), feats_in.dtype
+    assert len(fs) == 2 and fst[1] == 1 and len(ws) == 3
+    code = _TORCH_DTYPE.get(dtype)
+    assert dtype == weights.dtype and code is not None
+    kvol, wcin, cout = ws
+    cin = fs[1]
     # (prepacked weights hold their input channels padded to a multiple of 16)
-    assert weights.shape[1] == ((cin + 15) // 16 * 16 if flags & CONV_PACKED_WEIGHTS else cin) and weights.shape[0] == kmap.kvol
+    assert wcin == ((cin + 15) // 16 * 16 if flags & CONV_PACKED_WEIGHTS else cin) and kvol == kmap.kvol
     if out is None:
-        out = torch.empty((n_out if n_out is not None else kmap.n_out, cout), dtype=feats_in.dtype, device=feats_in.device)
-    assert out.dim() == 2 and out.stride(1) == 1 and out.shape[1] == cout and out.dtype == feats_in.dtype
+        out = torch.empty((n_out if n_out is not None else kmap.n_out, cout), dtype=dtype, device=feats_in.device)
+    oshape, ost = out.shape, out.stride()
+    assert len(oshape) == 2 and ost[1] == 1 and oshape[1] == cout and out.dtype == dtype
+    raw = current_raw_stream() if stream is None else _stream(stream)
     if hybrid_t is not None:
-        _check(lib().spc_conv_forward_hybrid(kmap.handle, feats_in.data_ptr(), feats_in.stride(0), weights.data_ptr(),
-                                             out.data_ptr(), out.stride(0), cin, cout, _TORCH_DTYPE[feats_in.dtype], int(hybrid_t),
-                                             flags, _stream(stream)))
-        return out
-    _check(lib().spc_conv_forward(kmap.handle, feats_in.data_ptr(), feats_in.stride(0), weights.data_ptr(), out.data_ptr(),
-                                  out.stride(0), cin, cout, _TORCH_DTYPE[feats_in.dtype], dataflow, flags, _stream(stream)))
+        rc = lib().spc_conv_forward_hybrid(kmap.handle, feats_in.data_ptr(), fst[0], weights.data_ptr(), out.data_ptr(), ost[0], cin,
+                                           cout, code, int(hybrid_t), flags, raw)
+    else:
+        rc = lib().spc_conv_forward(kmap.handle, feats_in.data_ptr(), fst[0], weights.data_ptr(), out.data_ptr(), ost[0], cin, cout,
+                                    code, dataflow, flags, raw)
+    if rc:
+        _check(rc)
     return out
 
 
