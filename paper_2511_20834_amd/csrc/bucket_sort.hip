@@ -37,6 +37,10 @@ __device__ inline int bs_bin(uint64_t key, int shift, int n_bin) {
   return b < uint64_t(n_bin) ? static_cast<int>(b) : n_bin - 1;  // all-ones keys of rejected rows go last
 }
 
+// What the scatter pass moves: the key, or (REC) the record (32-bit key, source index), whose bin starts 32 bits higher.
+template <typename KeyT, bool REC>
+using BsElem = std::conditional_t<REC, uint64_t, KeyT>;
+
 // ---------------------------------------------------------------- key sources
 // A source splits "fetch" from "make the key": the kernels below fetch a batch of rows first and
 // only then compute, so that the batch's loads are in flight together.
@@ -171,11 +175,14 @@ __global__ __launch_bounds__(BS_COL_THREADS) void bs_colscan_kernel(const int32_
 // equal adjacent keys only the first takes part), the cleared position bitmap and chunk counters.
 constexpr int BS_SUM_ROWS = 15;
 constexpr int BS_SUM_MAX_WG = 8;  // rows of the largest table that is summed here
-template <typename KeyT, bool DEDUP, bool SUM>
+// REC (pack + sort of 32-bit keys that bs_rank_lds_kernel ranks): a key and its source index leave as one 8-byte record.
+// From half a million keys on hardly two keys of a workgroup share a bin, so every scattered store is a memory
+// transaction of its own, and one array of records takes half as many as two arrays.
+template <typename KeyT, bool DEDUP, bool SUM, bool REC>
 __global__ __launch_bounds__(BS_WIDE) void bs_scatter_kernel(const KeyT* __restrict__ keys0, int64_t n, int per, int shift,
                                                              int n_bin, const int32_t* __restrict__ before,
                                                              const int32_t* __restrict__ tot,
-                                                             const uint16_t* __restrict__ table, KeyT* __restrict__ keys1,
+                                                             const uint16_t* __restrict__ table, BsElem<KeyT, REC>* __restrict__ keys1,
                                                              int32_t* __restrict__ vals1, int2* __restrict__ win,
                                                              int32_t* __restrict__ n_part_keys, uint32_t* __restrict__ bits,
                                                              int n_words, int32_t* __restrict__ ccnt, int n_chunks,
@@ -291,8 +298,12 @@ __global__ __launch_bounds__(BS_WIDE) void bs_scatter_kernel(const KeyT* __restr
 #pragma unroll
     for (int u = 0; u < 4; ++u)
       if (use[u]) {
-        keys1[p[u]] = key[u];
-        if (!DEDUP) vals1[p[u]] = static_cast<int32_t>(i0 + u * BS_WIDE);
+        if constexpr (REC) {
+          keys1[p[u]] = (uint64_t(key[u]) << 32) | static_cast<uint32_t>(i0 + u * BS_WIDE);
+        } else {
+          keys1[p[u]] = key[u];
+          if (!DEDUP) vals1[p[u]] = static_cast<int32_t>(i0 + u * BS_WIDE);
+        }
       }
   }
   // Rank windows (see bs_rank_kernel): part p = scattered positions [p * BS_PART, ...) is ranked
@@ -300,7 +311,7 @@ __global__ __launch_bounds__(BS_WIDE) void bs_scatter_kernel(const KeyT* __restr
   // one per thread: two binary searches over the bin starts in LDS, done last, while the scattered
   // stores drain.
   if (blockIdx.x == 0) {
-    if (t < BS_PAD_KEYS) keys1[total + t] = ~KeyT(0);  // the rank kernels read whole steps
+    if (t < BS_PAD_KEYS) keys1[total + t] = ~BsElem<KeyT, REC>(0);  // the rank kernels read whole steps
     if (t == 0 && n_part_keys) *n_part_keys = total;
     if (t == 0) *rest_count = 0;  // windows left over by bs_rank_lds_kernel
   }
@@ -411,8 +422,8 @@ __device__ inline int bs_count_before(const KeyT* __restrict__ k, int a, int b, 
 
 // (a device function of the part number: the kernel below ranks part blockIdx.x, bs_rank_rest_kernel the parts
 // of the windows that bs_rank_lds_kernel has left over)
-template <typename KeyT, int WAVES, bool LISTED = false>
-__device__ inline void bs_rank_part(int part, const KeyT* __restrict__ keys1, const int32_t* __restrict__ vals1,
+template <typename KeyT, int WAVES, bool LISTED = false, bool REC = false>
+__device__ inline void bs_rank_part(int part, const BsElem<KeyT, REC>* __restrict__ keys1, const int32_t* __restrict__ vals1,
                                     const int2* __restrict__ win, int n, KeyT* __restrict__ out_k, int32_t* __restrict__ out_v) {
   static_assert(BS_PART == 64, "one key per lane");
   __shared__ int partial[WAVES][BS_PART];
@@ -422,8 +433,8 @@ __device__ inline void bs_rank_part(int part, const KeyT* __restrict__ keys1, co
   const int x = own0 + lane;
   const bool act = x < n;
   const int2 w = win[part];
-  const KeyT key = act ? keys1[x] : ~KeyT(0);
-  const int32_t val = (act && out_v && wave == 0) ? vals1[x] : 0;
+  const BsElem<KeyT, REC> key = act ? keys1[x] : ~BsElem<KeyT, REC>(0);
+  const int32_t val = REC ? static_cast<int32_t>(key) : (act && out_v && wave == 0) ? vals1[x] : 0;
   const int n_pad = (n + BS_RANK_STEP - 1) & ~(BS_RANK_STEP - 1);  // positions n .. n_pad - 1 hold all-ones keys
   const int g0 = w.x & ~(BS_RANK_STEP - 1);
   const int g1 = min(max((w.y + BS_RANK_STEP - 1) & ~(BS_RANK_STEP - 1), own0 + BS_PART), n_pad);
@@ -451,7 +462,7 @@ __device__ inline void bs_rank_part(int part, const KeyT* __restrict__ keys1, co
     for (int v = 0; v < WAVES; ++v) r += partial[v][lane];
   }
   if (wave == 0 && act) {
-    out_k[r] = key;
+    out_k[r] = static_cast<KeyT>(REC ? key >> (8 * (sizeof(key) - sizeof(KeyT))) : key);
     if (out_v) out_v[r] = val;
   }
 }
@@ -604,9 +615,9 @@ __global__ __launch_bounds__(BS_THREADS) void bs_compact_kernel(const KeyT* __re
 // count is capped (an LDS histogram per workgroup in the count pass): from about half a million keys on that pass
 // sets the time of the sort.  Here a workgroup takes BS_LP scattered positions and the window of whole bins around
 // them (through the 64-position windows the scatter pass has written), and splits the window once more in LDS:
-//   * a thread owns eight consecutive window keys; a key's bin rank inside the window is a prefix sum of "the bin
-//     changes here" flags (the scattered array is ordered by bin), so the empty bins of a sparse key space cost
-//     nothing;
+//   * a key's bin rank inside the window is a prefix sum of "the bin changes here" flags (the scattered array is
+//     ordered by bin), so the empty bins of a sparse key space cost nothing; a thread's eight keys lie BS_LT apart,
+//     so loads are coalesced and a ballot gives a wave's flags;
 //   * sub-bin = (bin rank, the next sb key bits below the bin bits), sb chosen per window so that all sub-bins fit
 //     the LDS histogram; histogram, exclusive scan, and the keys move, with their window index, to their sub-bin's
 //     slots (LDS atomics for the slot: the order inside a sub-bin does not matter);
@@ -615,6 +626,11 @@ __global__ __launch_bounds__(BS_THREADS) void bs_compact_kernel(const KeyT* __re
 //     then share a position; the one with the smallest window index marks the position and is counted for its chunk,
 //     which is the same on every workgroup that sees the bin, because all of a bin's keys lie in every window that
 //     touches it).
+// Pack + sort ranks whole bins, those that start among the workgroup's positions, so its keys fill a range of the
+// output and leave in order, lane next to lane; what bounded the pass before was the rate of single-lane stores.  With
+// that and the 8-byte records of the scatter pass, pack + sort of 10^6 random voxels 70 -> 50 us, 3 * 10^6 142 -> 89,
+// 1.2 * 10^6 indoor 130 -> 69 (own positions 3072 instead of 2048: 95); with 64-bit keys, which have no records, 3 * 10^6 151 -> 144.
+// Levels keep the window of all bins that touch the own positions: their marks must be counted once each.
 // A window that does not fit (bins of thousands of keys: the floors and walls of dense indoor scenes) is left to
 // bs_rank_rest_kernel: the workgroup appends its number to a list, and the 64-position parts of the listed
 // workgroups are ranked by comparing against their own windows as above, spread over a fixed grid.
@@ -625,15 +641,17 @@ constexpr int BS_LT = 512;     // threads: eight window keys each
 constexpr int BS_LK = BS_LW / BS_LT;
 static_assert(BS_LP % BS_PART == 0 && BS_LW >= BS_LP && BS_LK == 8, "window layout");
 
-template <typename KeyT, bool UNIQUE>
-__global__ __launch_bounds__(BS_LT) void bs_rank_lds_kernel(const KeyT* __restrict__ keys1, const int32_t* __restrict__ vals1,
-                                                            const int2* __restrict__ win, int n_h,
+template <typename KeyT, bool UNIQUE, bool REC>
+__global__ __launch_bounds__(BS_LT) void bs_rank_lds_kernel(const BsElem<KeyT, REC>* __restrict__ keys1,
+                                                            const int32_t* __restrict__ vals1, const int2* __restrict__ win, int n_h,
                                                             const int32_t* __restrict__ n_d, int shift, int n_bin,
                                                             KeyT* __restrict__ out_k, int32_t* __restrict__ out_v,
                                                             uint32_t* __restrict__ bits, int32_t* __restrict__ ccnt,
                                                             int32_t* __restrict__ rest_count, int32_t* __restrict__ rest,
                                                             size_t ws_pitch) {
+  using Elem = BsElem<KeyT, REC>;
   constexpr int WAVES = BS_LT / 64;
+  static_assert(WAVES * BS_LK == 64, "one wave scans the totals of all (key of the thread, wave) segments");
   if (UNIQUE) {
     keys1 = level_ws(keys1, ws_pitch);
     win = level_ws(win, ws_pitch);
@@ -644,75 +662,91 @@ __global__ __launch_bounds__(BS_LT) void bs_rank_lds_kernel(const KeyT* __restri
     rest_count = level_ws(rest_count, ws_pitch);
     rest = level_ws(rest, ws_pitch);
   }
-  __shared__ KeyT skey[BS_LW];
-  __shared__ uint16_t sidx[BS_LW];
+  __shared__ Elem skey[BS_LW];
+  __shared__ uint16_t sidx[REC ? 1 : BS_LW];  // (records are distinct and carry their source index)
   __shared__ int hist[BS_LSUB];
-  __shared__ KeyT s_last[BS_LT];
+  __shared__ Elem s_last[64];
+  __shared__ int s_seg[64];
   __shared__ int wave_tot[WAVES];
-  __shared__ uint32_t s_bits[BS_LW / 32 + 2];
-  __shared__ int s_cc[BS_LW / BS_CHUNK + 2];
+  __shared__ uint32_t s_bits[UNIQUE ? BS_LW / 32 + 2 : 1];
+  __shared__ int s_cc[UNIQUE ? BS_LW / BS_CHUNK + 2 : 1];
   const int n = n_d ? *n_d : n_h;
   const int own0 = blockIdx.x * BS_LP;
   if (own0 >= n) return;
   const int own1 = min(own0 + BS_LP, n);
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int g0 = win[own0 / BS_PART].x, g1 = win[(own1 - 1) / BS_PART].y;
-  const int W = g1 - g0;
-  if (W > BS_LW) {  // the window does not fit: bs_rank_rest_kernel ranks these positions
-    if (t == 0) rest[atomicAdd(rest_count, 1)] = blockIdx.x;
-    return;
+  const int part0 = own0 / BS_PART;
+  int g0 = win[part0].x;
+  const int g1 = win[(own1 - 1) / BS_PART].y;
+  bool listed;
+  if constexpr (UNIQUE) {
+    listed = g1 - g0 > BS_LW;
+  } else {
+    // the bins that start among the own positions; the rest of a bin that starts before them belongs to an earlier
+    // workgroup, and if that one's window does not fit, the own positions are listed as well
+    const int s = g0;
+    if (own0 > 0) g0 = win[part0 - 1].y;
+    listed = g1 - g0 > BS_LW;
+    if (s < own0) {
+      const int e = s / BS_LP;
+      listed |= g0 - (e > 0 ? win[e * (BS_LP / BS_PART) - 1].y : 0) > BS_LW;
+    }
   }
-  // ---- window keys, eight consecutive ones per thread
-  KeyT k[BS_LK];
-  const int j0 = t * BS_LK;
+  const int W = g1 - g0;
+  if (listed && t == 0) rest[atomicAdd(rest_count, 1)] = blockIdx.x;  // bs_rank_rest_kernel ranks these positions
+  if (W <= 0 || W > BS_LW) return;
+  // ---- window keys: key u of a thread is window key u * BS_LT + t
+  Elem k[BS_LK];
 #pragma unroll
-  for (int u = 0; u < BS_LK; ++u) k[u] = keys1[g0 + min(j0 + u, W - 1)];
+  for (int u = 0; u < BS_LK; ++u) k[u] = keys1[g0 + min(u * BS_LT + t, W - 1)];
   for (int i = t; i < BS_LSUB; i += BS_LT) hist[i] = 0;
-  if (UNIQUE) {
+  if constexpr (UNIQUE) {
     for (int i = t; i < BS_LW / 32 + 2; i += BS_LT) s_bits[i] = 0u;
     if (t < BS_LW / BS_CHUNK + 2) s_cc[t] = 0;
   }
-  s_last[t] = k[BS_LK - 1];
+  if (lane == 63) {
+#pragma unroll
+    for (int u = 0; u < BS_LK; ++u) s_last[u * WAVES + wave] = k[u];
+  }
   __syncthreads();
   // bin rank inside the window: inclusive prefix of the "bin changes" flags, minus one
-  int d[BS_LK], flags = 0;
-  {
-    int prev_bin = t > 0 ? bs_bin(s_last[t - 1], shift, n_bin) : -1;
+  int d[BS_LK];
 #pragma unroll
-    for (int u = 0; u < BS_LK; ++u) {
-      const int bin = bs_bin(k[u], shift, n_bin);
-      flags += (j0 + u < W && bin != prev_bin) ? 1 : 0;
-      d[u] = flags;
-      prev_bin = bin;
-    }
+  for (int u = 0; u < BS_LK; ++u) {
+    const int seg = u * WAVES + wave;
+    const int bin = bs_bin(k[u], shift, n_bin);
+    int prev_bin = __shfl_up(bin, 1, 64);
+    if (lane == 0) prev_bin = seg > 0 ? bs_bin(s_last[seg - 1], shift, n_bin) : -1;
+    const unsigned long long flags = __ballot(u * BS_LT + t < W && bin != prev_bin);
+    d[u] = __popcll(flags & (~0ull >> (63 - lane)));
+    if (lane == 0) s_seg[seg] = __popcll(flags);
   }
-  int x = flags;
+  __syncthreads();
+  const int seg_n = s_seg[lane];
+  int x = seg_n;
   for (int s = 1; s < 64; s <<= 1) {
     const int y = __shfl_up(x, s, 64);
     if (lane >= s) x += y;
   }
-  if (lane == 63) wave_tot[wave] = x;
-  __syncthreads();
-  int base = x - flags, n_bins_here = 0;
-  for (int w = 0; w < WAVES; ++w) {
-    if (w < wave) base += wave_tot[w];
-    n_bins_here += wave_tot[w];
-  }
+  const int n_bins_here = __shfl(x, 63, 64);
+  x -= seg_n;
   // sub-bin bits: as many as keep (bins in the window) << sb within the histogram, at most the key bits below the bins
   int sb = 0;
   while (sb < shift && sb < 12 && ((n_bins_here << (sb + 1)) <= BS_LSUB)) ++sb;
-  const KeyT sub_mask = (KeyT(1) << sb) - 1;
+  const Elem sub_mask = (Elem(1) << sb) - 1;
   int id[BS_LK];
 #pragma unroll
   for (int u = 0; u < BS_LK; ++u) {
+    const int base = __shfl(x, u * WAVES + wave, 64);
     id[u] = ((base + d[u] - 1) << sb) | static_cast<int>((k[u] >> (shift - sb)) & sub_mask);
-    if (j0 + u < W) atomicAdd(&hist[id[u]], 1);
+    if (u * BS_LT + t < W) atomicAdd(&hist[id[u]], 1);
   }
   __syncthreads();
   // exclusive scan of the sub-bin counts, eight per thread (BS_LSUB = 8 * BS_LT)
   static_assert(BS_LSUB == BS_LK * BS_LT, "eight sub-bins per thread");
   {
+    const int j0 = t * BS_LK;
     int c[BS_LK], sum = 0;
 #pragma unroll
     for (int u = 0; u < BS_LK; ++u) {
@@ -724,7 +758,6 @@ __global__ __launch_bounds__(BS_LT) void bs_rank_lds_kernel(const KeyT* __restri
       const int z = __shfl_up(y, s, 64);
       if (lane >= s) y += z;
     }
-    __syncthreads();  // everybody has read the counts and the wave totals of the flags
     if (lane == 63) wave_tot[wave] = y;
     __syncthreads();
     int run = y - sum;
@@ -738,42 +771,45 @@ __global__ __launch_bounds__(BS_LT) void bs_rank_lds_kernel(const KeyT* __restri
   __syncthreads();
 #pragma unroll
   for (int u = 0; u < BS_LK; ++u)
-    if (j0 + u < W) {
+    if (u * BS_LT + t < W) {
       const int slot = atomicAdd(&hist[id[u]], 1);
       skey[slot] = k[u];
-      sidx[slot] = static_cast<uint16_t>(j0 + u);
+      if constexpr (!REC) sidx[slot] = static_cast<uint16_t>(u * BS_LT + t);
     }
   __syncthreads();
   // after the moves hist[i] is the end of sub-bin i, i.e. the start of sub-bin i + 1
-  const int o0 = own0 - g0, o1 = own1 - g0;  // the own positions, as window indices
+  const int o0 = own0 - g0, o1 = own1 - g0;  // UNIQUE: the own positions, as window indices
 #pragma unroll
   for (int u = 0; u < BS_LK; ++u) {
-    const int j = j0 + u;
-    if (j < o0 || j >= o1) continue;
+    const int j = u * BS_LT + t;
+    if (UNIQUE ? j < o0 || j >= o1 : j >= W) continue;
     const int lo = id[u] > 0 ? hist[id[u] - 1] : 0, hi = hist[id[u]];
     int c = lo;
     bool first = true;  // UNIQUE: no equal key at a smaller window index
     for (int s = lo; s < hi; ++s) {
-      const KeyT e = skey[s];
-      const int ej = sidx[s];
-      if constexpr (UNIQUE) {
+      const Elem e = skey[s];
+      if constexpr (REC) {
         c += e < k[u] ? 1 : 0;
-        first = first && !(e == k[u] && ej < j);
+      } else if constexpr (UNIQUE) {
+        c += e < k[u] ? 1 : 0;
+        first = first && !(e == k[u] && sidx[s] < j);
       } else {
-        c += (e < k[u] || (e == k[u] && ej < j)) ? 1 : 0;
+        c += (e < k[u] || (e == k[u] && sidx[s] < j)) ? 1 : 0;
       }
     }
-    const int r = g0 + c;
-    out_k[r] = k[u];
     if constexpr (!UNIQUE) {
-      if (out_v) out_v[r] = vals1[g0 + j];
-    } else if (first) {
-      const int rel = r - (g0 & ~31);
-      atomicOr(&s_bits[rel >> 5], 1u << (rel & 31));
+      d[u] = c;
+    } else {
+      const int r = g0 + c;
+      out_k[r] = k[u];
+      if (first) {
+        const int rel = r - (g0 & ~31);
+        atomicOr(&s_bits[rel >> 5], 1u << (rel & 31));
+      }
     }
   }
+  __syncthreads();
   if constexpr (UNIQUE) {
-    __syncthreads();
     const int word0 = g0 >> 5, chunk0 = word0 / (BS_CHUNK / 32);
     if (t < BS_LW / 32 + 2) {
       const uint32_t word = s_bits[t];
@@ -784,16 +820,35 @@ __global__ __launch_bounds__(BS_LT) void bs_rank_lds_kernel(const KeyT* __restri
     }
     __syncthreads();
     if (t < BS_LW / BS_CHUNK + 2 && s_cc[t]) atomicAdd(&ccnt[chunk0 + t], s_cc[t]);
+  } else {
+    // whole bins are ranked: their keys leave in order, lane next to lane
+#pragma unroll
+    for (int u = 0; u < BS_LK; ++u)
+      if (u * BS_LT + t < W) {
+        skey[d[u]] = k[u];
+        if constexpr (!REC) sidx[d[u]] = static_cast<uint16_t>(u * BS_LT + t);
+      }
+    __syncthreads();
+    for (int i = t; i < W; i += BS_LT) {
+      const Elem e = skey[i];
+      if constexpr (REC) {
+        out_k[g0 + i] = static_cast<KeyT>(e >> 32);
+        if (out_v) out_v[g0 + i] = static_cast<int32_t>(e);
+      } else {
+        out_k[g0 + i] = e;
+        if (out_v) out_v[g0 + i] = vals1[g0 + sidx[i]];
+      }
+    }
   }
 }
 
 // The parts bs_rank_lds_kernel has listed (none for most clouds: the workgroups then read the count and leave).
 constexpr int BS_REST_WG = 2048;
-template <typename KeyT, bool UNIQUE>
+template <typename KeyT, bool UNIQUE, bool REC>
 __global__ __launch_bounds__(BS_THREADS) void bs_rank_rest_kernel(const int32_t* __restrict__ rest_count,
                                                                   const int32_t* __restrict__ rest,
-                                                                  const KeyT* __restrict__ keys1, const int32_t* __restrict__ vals1,
-                                                                  const int2* __restrict__ win, int n_h,
+                                                                  const BsElem<KeyT, REC>* __restrict__ keys1,
+                                                                  const int32_t* __restrict__ vals1, const int2* __restrict__ win, int n_h,
                                                                   const int32_t* __restrict__ n_d, KeyT* __restrict__ out_k,
                                                                   int32_t* __restrict__ out_v, uint32_t* __restrict__ bits,
                                                                   int32_t* __restrict__ ccnt, size_t ws_pitch) {
@@ -814,7 +869,7 @@ __global__ __launch_bounds__(BS_THREADS) void bs_rank_rest_kernel(const int32_t*
     const int part = rest[i / PER] * PER + i % PER;
     if (part * BS_PART >= n) continue;  // (uniform)
     if constexpr (UNIQUE) bs_rank_unique_part<KeyT, true>(part, keys1, win, n, out_k, bits, ccnt);
-    else bs_rank_part<KeyT, BS_THREADS / 64, true>(part, keys1, vals1, win, n, out_k, out_v);
+    else bs_rank_part<KeyT, BS_THREADS / 64, true, REC>(part, keys1, vals1, win, n, out_k, out_v);
     __syncthreads();  // the part functions' LDS is reused by the next part
   }
 }
@@ -1038,7 +1093,7 @@ size_t chunks_for(int64_t n) { return static_cast<size_t>(n / BS_CHUNK + 2); }
 template <typename KeyT>
 Ws<KeyT> carve(void* ws, int64_t n) {
   const size_t nn = static_cast<size_t>(std::max<int64_t>(n, 1));
-  const size_t k = ((nn + BS_PAD_KEYS) * sizeof(KeyT) + 255) / 256 * 256, v = (nn * 4 + 255) / 256 * 256;
+  const size_t k = ((nn + BS_PAD_KEYS) * sizeof(KeyT) + 255) / 256 * 256, v = ((nn + BS_PAD_KEYS) * 4 + 255) / 256 * 256;
   char* c = static_cast<char*>(ws);
   Ws<KeyT> w;
   w.keys0 = reinterpret_cast<KeyT*>(c);
@@ -1061,13 +1116,13 @@ Ws<KeyT> carve(void* ws, int64_t n) {
 }
 
 // count, column scan, scatter: keys1 (vals1) partitioned by fine bin, rank windows
-template <typename KeyT, bool DEDUP, typename Src>
+template <typename KeyT, bool DEDUP, bool REC, typename Src>
 void partition(const Src& src, int64_t n, const BucketPlan& p, const Ws<KeyT>& w, int n_levels, size_t ws_pitch, hipStream_t s) {
   if (p.sum) {
     uint16_t* table = reinterpret_cast<uint16_t*>(w.table);
     hipLaunchKernelGGL((bs_count_kernel<KeyT, Src, uint16_t>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(p.n_bin) * 4, s, src, n,
                        p.per, p.shift, p.n_bin, w.keys0, table, ws_pitch);
-    hipLaunchKernelGGL((bs_scatter_kernel<KeyT, DEDUP, true>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(2 * p.n_bin + 2) * 4, s,
+    hipLaunchKernelGGL((bs_scatter_kernel<KeyT, DEDUP, true, false>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(2 * p.n_bin + 2) * 4, s,
                        w.keys0, n, p.per, p.shift, p.n_bin, static_cast<const int32_t*>(nullptr), static_cast<const int32_t*>(nullptr),
                        table, w.keys1, w.vals1, w.win, DEDUP ? w.n_kept : static_cast<int32_t*>(nullptr), w.bits, w.n_words, w.ccnt,
                        w.n_chunks, w.rest_count, ws_pitch);
@@ -1079,18 +1134,18 @@ void partition(const Src& src, int64_t n, const BucketPlan& p, const Ws<KeyT>& w
   hipLaunchKernelGGL(bs_colscan_kernel, dim3(col_wg, n_levels), dim3(BS_COL_THREADS), 0, s, w.table, w.before, p.n_wg, p.n_bin,
                      w.fstart, ws_pitch);
   // (the scatter pass holds two ints per bin: beyond 8191 bins that is more than the default LDS limit)
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bs_scatter_kernel<KeyT, DEDUP, false>),
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bs_scatter_kernel<KeyT, DEDUP, false, REC>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (2 * BS_MAX_BIN + 2) * 4);
   (void)attr;
-  hipLaunchKernelGGL((bs_scatter_kernel<KeyT, DEDUP, false>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(2 * p.n_bin + 2) * 4, s, w.keys0,
-                     n, p.per, p.shift, p.n_bin, w.before, w.fstart, static_cast<const uint16_t*>(nullptr), w.keys1, w.vals1, w.win, DEDUP ? w.n_kept : static_cast<int32_t*>(nullptr), w.bits, w.n_words, w.ccnt,
+  hipLaunchKernelGGL((bs_scatter_kernel<KeyT, DEDUP, false, REC>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(2 * p.n_bin + 2) * 4, s, w.keys0,
+                     n, p.per, p.shift, p.n_bin, w.before, w.fstart, static_cast<const uint16_t*>(nullptr), reinterpret_cast<BsElem<KeyT, REC>*>(w.keys1), w.vals1, w.win, DEDUP ? w.n_kept : static_cast<int32_t*>(nullptr), w.bits, w.n_words, w.ccnt,
                      w.n_chunks, w.rest_count, ws_pitch);
 }
 }  // namespace
 
 size_t bucket_sort_ws_bytes(int key_bits, int64_t n) {
   const size_t nn = static_cast<size_t>(std::max<int64_t>(n, 1));
-  const size_t k = ((nn + BS_PAD_KEYS) * (key_bits / 8) + 255) / 256 * 256, v = (nn * 4 + 255) / 256 * 256;
+  const size_t k = ((nn + BS_PAD_KEYS) * (key_bits / 8) + 255) / 256 * 256, v = ((nn + BS_PAD_KEYS) * 4 + 255) / 256 * 256;
   const BucketPlan cap = bucket_plan(n, 64);
   const size_t tbl = (size_t(cap.n_wg) * cap.n_bin + 63) / 64 * 64;
   return 2 * k + v + (2 * tbl + cap.n_bin + 64 + 2 * (nn / BS_PART + 2) + 2 + chunks_for(n) + words_for(n) + (nn / BS_LP + 2)) * 4;
@@ -1101,7 +1156,11 @@ static int pack_sort_t(const int4* coords, int64_t n, const PackParams& pp, int 
                        int32_t* perm_out, void* ws, hipStream_t s) {
   const BucketPlan p = bucket_plan(n, used_bits);
   const Ws<KeyT> w = carve<KeyT>(ws, n);
-  partition<KeyT, false>(SrcPack<KeyT>{coords, pp, status}, n, p, w, 1, 0, s);
+  // one element array (see REC): over keys1 and vals1 together, which lie one behind the other
+  constexpr bool REC = sizeof(KeyT) == 4;
+  const SrcPack<KeyT> src{coords, pp, status};
+  if (n >= BS_RANK_LDS_N) partition<KeyT, false, REC>(src, n, p, w, 1, 0, s);
+  else partition<KeyT, false, false>(src, n, p, w, 1, 0, s);
   const int n_part = static_cast<int>((n + BS_PART - 1) / BS_PART);
   // Four waves share a part's window while the launch is latency-bound (its time is that of the part with
   // the largest window); from BS_RANK_SOLO_N keys on (25 parts per CU) the pass is bound by how many parts
@@ -1109,11 +1168,13 @@ static int pack_sort_t(const int4* coords, int64_t n, const PackParams& pp, int 
   // faster: 10^6 keys 32 -> 26 us, 2 * 10^6 keys 145 -> 129 us for the whole sort; at 240 k keys of
   // dense indoor scenes it was slower (37 -> 47 us).
   if (n >= BS_RANK_LDS_N) {
-    hipLaunchKernelGGL((bs_rank_lds_kernel<KeyT, false>), dim3(static_cast<int>((n + BS_LP - 1) / BS_LP)), dim3(BS_LT), 0, s, w.keys1,
-                       w.vals1, w.win, static_cast<int>(n), static_cast<const int32_t*>(nullptr), p.shift, p.n_bin,
+    const auto* elems = reinterpret_cast<const BsElem<KeyT, REC>*>(w.keys1);
+    const int shift = p.shift + (REC ? 32 : 0);
+    hipLaunchKernelGGL((bs_rank_lds_kernel<KeyT, false, REC>), dim3(static_cast<int>((n + BS_LP - 1) / BS_LP)), dim3(BS_LT), 0, s, elems,
+                       w.vals1, w.win, static_cast<int>(n), static_cast<const int32_t*>(nullptr), shift, p.n_bin,
                        static_cast<KeyT*>(keys_out), perm_out, static_cast<uint32_t*>(nullptr), static_cast<int32_t*>(nullptr),
                        w.rest_count, w.rest, size_t(0));
-    hipLaunchKernelGGL((bs_rank_rest_kernel<KeyT, false>), dim3(BS_REST_WG), dim3(BS_THREADS), 0, s, w.rest_count, w.rest, w.keys1,
+    hipLaunchKernelGGL((bs_rank_rest_kernel<KeyT, false, REC>), dim3(BS_REST_WG), dim3(BS_THREADS), 0, s, w.rest_count, w.rest, elems,
                        w.vals1, w.win, static_cast<int>(n), static_cast<const int32_t*>(nullptr), static_cast<KeyT*>(keys_out),
                        perm_out, static_cast<uint32_t*>(nullptr), static_cast<int32_t*>(nullptr), size_t(0));
   } else if (n >= BS_RANK_SOLO_N)
@@ -1140,14 +1201,14 @@ static int mask_unique_t(const void* keys_in, int64_t n, const LevelJob* jobs, i
   SrcMasks<KeyT> src;
   LevelOut<KeyT> lo;
   batch_args(keys_in, jobs, n_levels, &src, &lo);
-  partition<KeyT, true>(src, n, p, w, n_levels, ws_pitch, s);
+  partition<KeyT, true, false>(src, n, p, w, n_levels, ws_pitch, s);
   // the sorted keys (with gaps) go to keys0, which is free again by now
   const int n_part = static_cast<int>((n + BS_PART - 1) / BS_PART), n_chunk = static_cast<int>((n + BS_CHUNK - 1) / BS_CHUNK);
   if (n >= BS_RANK_LDS_N) {
-    hipLaunchKernelGGL((bs_rank_lds_kernel<KeyT, true>), dim3(static_cast<int>((n + BS_LP - 1) / BS_LP), n_levels), dim3(BS_LT), 0, s,
+    hipLaunchKernelGGL((bs_rank_lds_kernel<KeyT, true, false>), dim3(static_cast<int>((n + BS_LP - 1) / BS_LP), n_levels), dim3(BS_LT), 0, s,
                        w.keys1, static_cast<const int32_t*>(nullptr), w.win, static_cast<int>(n), w.n_kept, p.shift, p.n_bin, w.keys0,
                        static_cast<int32_t*>(nullptr), w.bits, w.ccnt, w.rest_count, w.rest, ws_pitch);
-    hipLaunchKernelGGL((bs_rank_rest_kernel<KeyT, true>), dim3(BS_REST_WG, n_levels), dim3(BS_THREADS), 0, s, w.rest_count, w.rest,
+    hipLaunchKernelGGL((bs_rank_rest_kernel<KeyT, true, false>), dim3(BS_REST_WG, n_levels), dim3(BS_THREADS), 0, s, w.rest_count, w.rest,
                        w.keys1, static_cast<const int32_t*>(nullptr), w.win, static_cast<int>(n), w.n_kept, w.keys0,
                        static_cast<int32_t*>(nullptr), w.bits, w.ccnt, ws_pitch);
   } else
