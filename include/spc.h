@@ -269,7 +269,9 @@ void spc_kmap_destroy(spc_kmap* m);
  *             to nearest even.  SPC_DTYPE_F32: fp32 products and sums throughout.
  *   dataflow  SPC_DATAFLOW_OS needs the OS layout, SPC_DATAFLOW_WS the WS layout
  *             (Section 2.2).  Results are bit-reproducible in both.
- *   flags     SPC_CONV_RELU; SPC_CONV_PACKED_WEIGHTS (see spc_conv_prepare_weights);
+ *   Infinities and NaN in features or weights reach an output through its own pairs only, in
+ *             every dtype, dataflow and kernel.
+ *   flags     SPC_CONV_RELU (NaN becomes 0, as in C's fmax); SPC_CONV_PACKED_WEIGHTS (see spc_conv_prepare_weights);
  *             SPC_CONV_OS_PHASE or SPC_CONV_OS_SPLITK pick one of the two OS MFMA kernels
  *             (default: chosen from the layer's size; both give the same result up to the
  *             fp32 summation order, and each one alone is bit-reproducible).

@@ -105,6 +105,60 @@ __global__ __launch_bounds__(256) void pad_rows_kernel(const T* __restrict__ F, 
 
 __device__ __align__(16) uint32_t g_zero_row[64];  // zero-initialised, never written
 
+// Outputs that come out as NaN.  The matrix cores multiply whole 32-row cells: a row without a pair at an offset adds zero
+// times the offset's weights, and the pooled way below adds every product row of a block to all of its rows, times zero or
+// one.  Zero times infinity or NaN is NaN, so one such weight or feature would reach rows that have no pair with it.  All
+// kernels therefore compute an output that came out as NaN once more, here, from its own pairs alone (whatever came in from
+// outside them has made the sum NaN).  The test costs an instruction per output.
+// A wave computes one output together (all lanes active, the same arguments in all): in_row(k) is the output row's input row
+// at offset k, or a negative number.
+template <typename T, bool PACKED, typename InRow>
+__device__ inline float conv_by_pairs(const InRow& in_row, int K3, const SPC_GLOBAL T* F, int64_t ld_in, const SPC_GLOBAL T* W, int cin,
+                                      int cout, int nb_total, int col) {
+  float sum = 0.f;
+#pragma unroll 1
+  for (int k = 0; k < K3; ++k) {
+    const int j = __builtin_amdgcn_readfirstlane(in_row(k));
+    if (j < 0) continue;
+#pragma unroll 1
+    for (int c = threadIdx.x & 63; c < cin; c += 64) {
+      const int64_t at = PACKED ? ((int64_t(k) * ((cin + 15) / 16) + c / 16) * nb_total + col / 32) * 512 + ((c & 8) * 4 + col % 32) * 8 + c % 8
+                                : (int64_t(k) * cin + c) * cout + col;
+      sum = fmaf(static_cast<float>(F[int64_t(j) * ld_in + c]), static_cast<float>(W[at]), sum);
+    }
+  }
+#pragma unroll 1
+  for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d, 64);
+  return sum;
+}
+// The same for a wave's 32 x 32 NB accumulators, whose first `rows` rows have been stored (lane l holds column l%32, and row
+// 0 of its registers is row 4*(l/32) at prow): by_pairs(row, column) replaces the NaNs.
+template <typename T, int NB, typename ByPairs>
+__device__ inline void redo_nan(const floatx16 (&acc)[NB], int rows, int lane, T* prow, int64_t ld_out, int relu, const ByPairs& by_pairs) {
+  float z = 0.f;  // NaN if any of them is NaN or infinite
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) z = fmaf(acc[nb][r], 0.f, z);
+  if (!__ballot(z != z)) return;
+  unsigned nan = 0u;
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) nan |= acc[nb][r] != acc[nb][r] ? 1u << (nb * 16 + r) : 0u;
+#pragma unroll 1
+  for (int b = 0; b < NB * 16; ++b) {
+    const int rr = 8 * (b % 16 / 4) + b % 4, nb = b / 16;
+#pragma unroll 1
+    for (unsigned long long todo = __ballot((nan >> b) & 1u); todo; todo &= todo - 1) {
+      const int l = __builtin_ctzll(todo), row = rr + 4 * (l >> 5);
+      if (row >= rows) continue;
+      const float v = by_pairs(row, nb * 32 + (l & 31));
+      if (lane == l) prow[rr * ld_out + nb * 32] = from_f32<T>(relu ? fmaxf(v, 0.f) : v);
+    }
+  }
+}
+
 // The phase kernel's other way through a 3x3x3 layer, for levels whose neighbourhoods are nearly empty.  Every kernel that
 // walks (32-row block, offset) cells pays for a cell as for 32 rows; on uniformly random voxels (1.25 % full) a block has
 // 9.6 cells, of which all but the centre's hold 1.2 valid rows.  Here a workgroup takes POOL_BLOCKS blocks, two per wave:
@@ -356,6 +410,12 @@ __device__ inline void conv_pool_tile(PoolLds& L, const int64_t blk0, const int6
     };
     if (rows == 32) store_all(std::true_type{});
     else if (rows > 0) store_all(std::false_type{});
+    redo_nan<T, NB>(acc[b], rows, lane, prow, ld_out, relu, [&](int row, int col) {
+      const int64_t blk = blk0 + 2 * wave + b;
+      const unsigned here = block_masks[blk] & kmask;
+      auto in_row = [&](int k) { return (here >> k) & 1u ? M[(blk * K3 + k) * 32 + row] : -1; };
+      return conv_by_pairs<T, true>(in_row, K3, (const SPC_GLOBAL T*)F, ld_in, (const SPC_GLOBAL T*)Wp, cin, nb_total * 32, nb_total, slab * (NB * 32) + col);
+    });
   });
 }
 
@@ -679,6 +739,14 @@ __global__ __launch_bounds__(64 * WAVES) void conv_os_phase_kernel(const int32_t
       };
       if (rows == 32) store_all(std::true_type{});
       else store_all(std::false_type{});
+      redo_nan<T, NB>(acc[rb], rows, lane, prow, ld_out, relu, [&](int row, int col) {
+        const int64_t blk = blk0 + rb;
+        auto in_row = [&](int k) {
+          const unsigned here = block_masks[blk * mask_words + (k >> 5)] & kmask.w[k >> 5];
+          return (here >> (k & 31)) & 1u ? M[(blk * K3 + k) * 32 + row] : -1;
+        };
+        return conv_by_pairs<T, true>(in_row, K3, (const SPC_GLOBAL T*)F, ld_in, (const SPC_GLOBAL T*)Wp, cin, nb_total * 32, nb_total, slab * (NB * 32) + col);
+      });
     }
   }
 }
@@ -736,6 +804,50 @@ struct SplitkArgs {
   KMask os_mask;
   ListArgs lists;
 };
+// The outputs that this wave has stored as NaN, from their own pairs (see conv_by_pairs).
+using SplitkKernarg = const __attribute__((address_space(4))) SplitkArgs;
+template <typename T, int NB, int RB, bool LOOP, bool PACKED, bool LISTED>
+__device__ inline void splitk_redo(SplitkKernarg* a) {
+  using Ints = const SPC_GLOBAL int32_t*;
+  constexpr int EPT = NB * 4;
+  const int n_out = a->n_out_d ? *(Ints)a->n_out_d : a->n_out_h;
+  const int n_blocks = (n_out + 31) >> 5, K3 = a->K3, kc = (K3 - 1) / 2;
+  const int lane = threadIdx.x & 63, row0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 8, oc0 = blockIdx.y * (NB * 32);
+#pragma unroll 1
+  for (int blk0 = blockIdx.x * RB; blk0 < n_blocks; blk0 += LOOP ? gridDim.x * RB : n_blocks)
+#pragma unroll 1
+    for (int e = 0; e < RB * EPT; ++e) {
+      const int blk = blk0 + e / EPT, my_i = blk * 32 + row0 + lane / 8, my_col = oc0 + lane % 8 * EPT + e % EPT;
+      SPC_GLOBAL T* dst = (SPC_GLOBAL T*)a->out + my_i * a->ld_out + my_col;
+      float was = 0.f;
+      if (my_i < n_out && my_col < a->cout) was = static_cast<float>(*dst);
+#pragma unroll 1
+      for (unsigned long long todo = __ballot(was != was); todo; todo &= todo - 1) {
+        const int l = __builtin_ctzll(todo), row = row0 + l / 8, col = oc0 + l % 8 * EPT + e % EPT;
+        auto in_row = [&](int k) -> int {
+          if ((a->os_mask.w[k >> 5] >> (k & 31)) & 1u) {
+            const unsigned here = ((Ints)a->block_masks)[int64_t(blk) * a->mask_words + (k >> 5)];
+            return (here >> (k & 31)) & 1u ? ((Ints)a->M)[(int64_t(blk) * K3 + k) * 32 + row] : -1;
+          }
+          if (!LISTED || !((a->lists.mask.w[k >> 5] >> (k & 31)) & 1u)) return -1;
+          const int i = blk * 32 + row;
+          if (a->lists.sym && k == kc) return i;
+          const bool mirror = a->lists.sym && k > kc;  // the opposite offset's list with the roles swapped
+          const int list = mirror ? K3 - 1 - k : k;
+          const Ints tab = (Ints)(mirror ? a->lists.base_in : a->lists.base) + int64_t(blk) * K3 + list;
+          const int64_t at = list * a->lists.stride + tab[0] + lane;  // (a block has at most 32 pairs of an offset)
+          int from = -1;
+          if (lane < tab[K3] - tab[0] && ((Ints)(mirror ? a->lists.in : a->lists.out))[at] == i)
+            from = ((Ints)(mirror ? a->lists.out : a->lists.in))[at];
+          const unsigned long long hit = __ballot(from >= 0);
+          return hit ? __builtin_amdgcn_readlane(from, __builtin_ctzll(hit)) : -1;
+        };
+        const float v = conv_by_pairs<T, PACKED>(in_row, K3, (const SPC_GLOBAL T*)a->F, a->ld_in, (const SPC_GLOBAL T*)a->W, a->cin,
+                                                 a->cout, a->nb_total, col);
+        if (lane == l) *dst = from_f32<T>(a->relu ? fmaxf(v, 0.f) : v);
+      }
+    }
+}
 // rows of 32 input indices in LDS, with all-invalid rows at the end: per wave, or (MATRIX_SMALL) for all waves
 __host__ __device__ constexpr int splitk_idx_rows(int K3, int AM, int FROM) {
   return FROM == MATRIX_SMALL ? K3 + 1 : (K3 + SPLITK_WAVES - 1) / SPLITK_WAVES + (AM == A_QUAD ? 4 : 1);
@@ -767,6 +879,8 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 4 ?
   const int slab = blockIdx.y;
   const int KK = (cin + SLAB - 1) / SLAB;
   int log_waves = a.log_waves;
+  float z = 0.f;  // NaN once this thread has stored NaN or infinity
+  const float least = a.relu ? 0.f : -__builtin_inff();
   // tiles of RB blocks; the trip count is uniform per workgroup, so the barriers below are
   // reached by all of its waves or by none
   for (int64_t blk0 = int64_t(blockIdx.x) * RB; blk0 < n_blocks; blk0 += LOOP ? int64_t(gridDim.x) * RB : n_blocks) {
@@ -1113,7 +1227,8 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 4 ?
 #pragma unroll
     for (int j = 0; j < EPT; ++j) {
       const float v = SHARED && summed ? reinterpret_cast<const float*>(smem)[at + 4 * j] : total(at + 4 * j);
-      o[j] = from_f32<T>(a.relu ? fmaxf(v, 0.f) : v);
+      o[j] = from_f32<T>(v < least ? least : v);  // (NaN stays and is computed again at the end)
+      z = fmaf(v, 0.f, z);
     }
     if (i < n_out && oc < cout) {
       T* dst = out + i * ld_out + oc;
@@ -1133,6 +1248,12 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 4 ?
   }
   if constexpr (LOOP) __syncthreads();  // the LDS tile is reused as the next tile's index area
   log_waves = 2;  // only the first tile is shared (its slot is then free again); who finished it goes on alone
+  }
+  if (__ballot(z != z)) {
+    // the arguments are loaded anew: kept in scalar registers for this, they would not fit in the variants that loop
+    SplitkKernarg* again = (SplitkKernarg*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(again));
+    splitk_redo<T, NB, RB, LOOP, PACKED, FROM == LISTS>(again);
   }
 }
 

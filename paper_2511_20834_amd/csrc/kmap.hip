@@ -29,7 +29,6 @@ namespace spc {
 constexpr int N_PROBES = 256;  // first-round probes of the window-bound searches
 constexpr int MAX_K = 7;
 constexpr int WS_MAX_K3_SEARCH = MAX_K * MAX_K * MAX_K;
-#define SPC_GLOBAL __attribute__((address_space(1)))
 
 template <typename KeyT>
 struct SearchParams {

@@ -165,6 +165,8 @@ __device__ inline KeyT pack_key(const int4 c, const PackParams& p, int32_t* stat
   if (bad && status) atomicOr(status, 1);
   return k;
 }
+// (a pointer that is not a kernel argument itself is a generic one to the compiler, and reads through it flat loads)
+#define SPC_GLOBAL __attribute__((address_space(1)))
 // Pins a loaded value in a vector register at this point of the program (used after a whole
 // batch of loads has been issued): the compiler can then neither sink the loads into later
 // branches nor spread them between other memory operations.  Loads and stores share one completion counter on this target, so a load
