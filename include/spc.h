@@ -253,7 +253,10 @@ int spc_kmap_set_size_hint(spc_kmap* m, int64_t n_out_hint);
  * wait: the map's arrays go back to the block cache of the stream the map was built on, and that
  * stream is first made to wait (an event, no host wait) for every stream that has run
  * spc_conv_forward on the map, so a build that follows immediately cannot overwrite arrays a
- * feature kernel is still reading.  Those streams must still exist when the map is destroyed.
+ * feature kernel is still reading.  Those streams must still exist when the map is destroyed, and the
+ * stream the map was built on as well.  Calls recorded into a graph count as run on the stream they were
+ * recorded on, which covers the replays on that stream; order replays on other streams before the destroy
+ * yourself.
  * Kernels of the caller's own that read the accessor pointers (os_map, ws lists, keys) on other
  * streams are not known to the library: order them before the destroy yourself.
  */

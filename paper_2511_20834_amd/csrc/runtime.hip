@@ -4,6 +4,7 @@
 #include <cstring>
 #include <map>
 #include <unordered_map>
+#include <unordered_set>
 #include <utility>
 #include <vector>
 
@@ -91,10 +92,14 @@ namespace {
 // How much the library has enqueued on every stream, and how much of it each (waiter, producer) pair has been ordered
 // behind: releasing the maps of a network asks for the same pair dozens of times with nothing new in between (a
 // release of 25 layers' maps on three streams took the host 230 us in event records and cross-stream waits, now 94).
+// A stream the library has been recorded on may also hold replays of that graph, which nobody counts: it is asked for an
+// event every time.
 struct StreamOrder {
   std::mutex mu;
   std::unordered_map<hipStream_t, uint64_t> work;
   std::map<std::pair<hipStream_t, hipStream_t>, uint64_t> ordered;
+  std::unordered_set<hipStream_t> recorded;
+  bool all_recorded = false;  // more recorded streams than are worth remembering: every stream counts as one
 };
 StreamOrder& stream_order() {
   static StreamOrder* o = new StreamOrder;
@@ -104,8 +109,11 @@ constexpr size_t MAX_TRACKED_STREAMS = 1024;
 }  // namespace
 
 void note_stream_work(hipStream_t s) {
+  const bool recording = stream_is_capturing(s);
   StreamOrder& O = stream_order();
   std::lock_guard<std::mutex> lk(O.mu);
+  if (recording && O.recorded.size() < MAX_TRACKED_STREAMS) O.recorded.insert(s);
+  else if (recording && !O.recorded.count(s)) O.all_recorded = true;
   if (O.work.size() > MAX_TRACKED_STREAMS || O.ordered.size() > MAX_TRACKED_STREAMS) {  // forgetting only means ordering once more
     O.work.clear();
     O.ordered.clear();
@@ -118,7 +126,7 @@ void order_stream_after(hipStream_t waiter, hipStream_t producer) {
   // (an order recorded into a graph says nothing about eager work, and the other way round)
   StreamOrder& O = stream_order();
   std::lock_guard<std::mutex> lk(O.mu);  // held until the wait is enqueued: whoever finds the entry may rely on it
-  if (!stream_is_capturing(waiter) && !stream_is_capturing(producer)) {
+  if (!stream_is_capturing(waiter) && !stream_is_capturing(producer) && !O.all_recorded && !O.recorded.count(producer)) {
     const uint64_t now = O.work[producer];
     auto it = O.ordered.find({waiter, producer});
     if (it != O.ordered.end() && it->second == now) return;

@@ -38,11 +38,11 @@ void pool_free(void* p, hipStream_t stream);
 int pool_release_all();
 // Makes everything enqueued on `waiter` from now on run after what `producer` holds at this moment
 // (an event recorded on `producer`; nothing happens when the two are the same stream, or when `waiter` has been
-// ordered behind `producer` before and the library has enqueued nothing on `producer` since).  Used before a
-// block goes back to the cache of a stream other than the one whose kernels last read it.
+// ordered behind `producer` before and the library has enqueued nothing on `producer` since and has never been recorded
+// into a graph there).  Used before a block goes back to the cache of a stream other than the one whose kernels last read it.
 void order_stream_after(hipStream_t waiter, hipStream_t producer);
-// Every library call that enqueues kernels reading pooled blocks on `s` says so once they are enqueued (an order that
-// another thread makes meanwhile is then made again): order_stream_after relies on it.
+// Every library call that enqueues kernels reading pooled blocks on `s` says so once they are enqueued, or recorded (an
+// order that another thread makes meanwhile is then made again): order_stream_after relies on it.
 void note_stream_work(hipStream_t s);
 struct StreamWorkNote {
   hipStream_t s;

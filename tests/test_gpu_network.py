@@ -260,6 +260,39 @@ def test_capture_of_a_large_cloud_replays():
     B.spc_release_cache()
 
 
+def test_release_waits_for_replays_on_the_recorded_stream():
+    """Feature calls on two maps are recorded into two graphs on one stream.  A replay enqueues nothing through the library,
+    yet the release of the second map must order the build stream behind its replay, although the release of the first one
+    has ordered the two streams before."""
+    coords = synth.cloud("lidar")
+    desc = B.spc_pack_desc_fit(coords[:, 1:].min(0), coords[:, 1:].max(0), 1, 1, 1)
+    build, feature = torch.cuda.Stream(), torch.cuda.Stream()
+    keys, _ = B.spc_pack_coords(torch.from_numpy(coords).cuda(), desc, False)
+    F = torch.from_numpy(synth.features(len(coords), 64, np.float16, seed=5)).cuda()
+    W = B.spc_conv_prepare_weights(torch.from_numpy(synth.weights(27, 64, 64, np.float16, seed=6)).cuda())
+    torch.cuda.synchronize()
+    maps = [B.spc_build_kmap(keys, desc, 3, layout=B.LAYOUT_OS, stream=build) for _ in range(2)]
+    torch.cuda.synchronize()
+    out, graphs = torch.empty_like(F), []
+    for m, calls in zip(maps, (1, 400)):  # the second replay takes some 10 ms
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1], stream=feature, capture_error_mode="relaxed"):
+            for _ in range(calls):
+                B.spc_conv_forward(m, F, W, B.DATAFLOW_OS, B.CONV_PACKED_WEIGHTS, out=out)
+    torch.cuda.synchronize()
+    replayed, built = torch.cuda.Event(), torch.cuda.Event()
+    with torch.cuda.stream(feature):
+        graphs[0].replay()
+        maps[0].destroy()
+        graphs[1].replay()
+        replayed.record()
+    maps[1].destroy()
+    built.record(build)  # (nothing takes the arrays again: only the order is looked at)
+    built.synchronize()
+    assert replayed.query()
+    torch.cuda.synchronize()
+
+
 def test_network_build_searches_nine_maps():
     """Configuration 4 in its default (all output-stationary) setting: 25 layers, 13 distinct maps, 9 searches."""
     coords, cs, operm, layers, W, desc, keys, F0, Fs = _setup("lidar")
