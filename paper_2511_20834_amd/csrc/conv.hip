@@ -880,7 +880,6 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 4 ?
   const int KK = (cin + SLAB - 1) / SLAB;
   int log_waves = a.log_waves;
   float z = 0.f;  // NaN once this thread has stored NaN or infinity
-  const float least = a.relu ? 0.f : -__builtin_inff();
   // tiles of RB blocks; the trip count is uniform per workgroup, so the barriers below are
   // reached by all of its waves or by none
   for (int64_t blk0 = int64_t(blockIdx.x) * RB; blk0 < n_blocks; blk0 += LOOP ? int64_t(gridDim.x) * RB : n_blocks) {
@@ -1219,18 +1218,19 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 4 ?
   const int nb = c0 >> 5, cc = c0 & 31;
   const int q = row >> 3, h = (row & 7) >> 2, rr = row & 3;
   const int oc = slab * (NB * 32) + c0;  // first output channel
+  const float least = a.relu ? 0.f : -__builtin_inff();
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     const int64_t i = (blk0 + rb) * 32 + row;
     const int at = ((((rb * NB + nb) * 4 + q) * 64) + h * 32 + cc) * 4 + rr;
-    __align__(16) T o[EPT];
-#pragma unroll
-    for (int j = 0; j < EPT; ++j) {
-      const float v = SHARED && summed ? reinterpret_cast<const float*>(smem)[at + 4 * j] : total(at + 4 * j);
-      o[j] = from_f32<T>(v < least ? least : v);  // (NaN stays and is computed again at the end)
-      z = fmaf(v, 0.f, z);
-    }
     if (i < n_out && oc < cout) {
+      __align__(16) T o[EPT];
+#pragma unroll
+      for (int j = 0; j < EPT; ++j) {
+        const float v = SHARED && summed ? reinterpret_cast<const float*>(smem)[at + 4 * j] : total(at + 4 * j);
+        o[j] = from_f32<T>(v < least ? least : v);  // (NaN stays and is computed again at the end)
+        z = fmaf(v, 0.f, z);
+      }
       T* dst = out + i * ld_out + oc;
       if (a.vec_store) {  // (cout is a multiple of EPT then)
         if constexpr (EPT * sizeof(T) >= 16) {
