@@ -198,12 +198,15 @@ int spc_build_kmaps_network(const void* v0_keys, int64_t n0, const spc_pack_desc
                             const spc_layer_desc* layers, int32_t n_layers, spc_kmap** out,
                             void* const* streams, int32_t n_streams, int32_t flags);
 
-/* Sizes.  For strided / transposed maps the counts are produced on the device; these
- * calls wait for the build to finish the first time.  Return a negative SPC_ERR_* on failure. */
+/* Sizes.  For strided / transposed maps the counts are produced on the device; the first of these calls
+ * waits until the level they count is complete: its keys may then be read on any stream.  The rest of the
+ * build (the map itself) may still be running: order other streams' readers of it behind the build's
+ * stream.  Return a negative SPC_ERR_* on failure. */
 int64_t spc_kmap_n_in(spc_kmap* m);
 int64_t spc_kmap_n_out(spc_kmap* m);
 int32_t spc_kmap_kvol(const spc_kmap* m); /* K^3 */
-/* [device] sorted keys of the layer's output (resp. input) voxels; valid while the map lives. */
+/* [device] sorted keys of the layer's output (resp. input) voxels; valid while the map lives, complete
+ * once spc_kmap_n_out (resp. n_in) has returned. */
 const void* spc_kmap_out_keys(const spc_kmap* m);
 const void* spc_kmap_in_keys(const spc_kmap* m);
 /* Copies the n_out sorted output keys to keys_host [host] (uint32 or uint64 per key_bits; `cap`

@@ -556,7 +556,7 @@ __global__ __launch_bounds__(BS_THREADS) void bs_rank_unique_kernel(const KeyT* 
 template <typename KeyT>
 struct LevelOut {
   KeyT* keys[BS_MAX_LEVELS];
-  CountOut count[BS_MAX_LEVELS];
+  int32_t* count[BS_MAX_LEVELS];
 };
 
 // out = the marked positions of `sorted`, in order, and their number.  One workgroup per chunk
@@ -600,7 +600,7 @@ __global__ __launch_bounds__(BS_THREADS) void bs_compact_kernel(const KeyT* __re
     before += red[0][w];
     all += red[1][w];
   }
-  if (b == 0 && t == 0) lo.count[blockIdx.y].publish(all);
+  if (b == 0 && t == 0) *lo.count[blockIdx.y] = all;
   int rank = before + __popc(word & ((1u << (4 * sub)) - 1u));
   for (int w = 0; w < wi; ++w) rank += wsum[w];
 #pragma unroll
@@ -991,7 +991,7 @@ __global__ __launch_bounds__(BS_SMALL_THREADS) void bs_small_sort_kernel(const S
     const int i = tid * per + u;
     if (i < n && (i == 0 || sk0[i] != sk0[i - 1])) out_k[base++] = sk0[i];
   }
-  if (tid == 0) lo.count[blockIdx.y].publish(total);
+  if (tid == 0) *lo.count[blockIdx.y] = total;
 }
 
 template <typename KeyT, typename Src, bool DEDUP>

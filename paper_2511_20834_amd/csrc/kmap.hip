@@ -154,6 +154,7 @@ struct SearchArgs {
   int32_t* arrived;
   KMask os_k, ws_k;
   int n_tiles_cap;
+  CountNote note_in, note_out;  // where the host polls for the levels' counts
 };
 constexpr int SEARCH_BATCH = 8;
 // A level's voxel count, kept in a scalar register.  (A pointer that comes out of an indexed argument array is a generic
@@ -212,6 +213,10 @@ __global__ __launch_bounds__(64 * K) void kmap_search_kernel(const SearchBatch<K
   const int n_in = level_count(args.n_in_d, args.n_in_h);
   const int n_out = level_count(args.n_out_d, args.n_out_h);
   const int i0 = blockIdx.x * TILE;
+  if (i0 == 0 && tid == 0) {
+    args.note_in.publish(n_in);
+    args.note_out.publish(n_out);
+  }
   if (i0 >= n_out) return;  // whole workgroup leaves together
   const int rows = min(TILE, n_out - i0);
   if (blockIdx.x == 0)
@@ -758,7 +763,7 @@ static int axis_offset(int K, int s, int i) { return (K % 2 == 1) ? (i - (K - 1)
 static std::atomic<int64_t> g_search_launches{0};  // searches enqueued by this process (see spc_search_count)
 
 template <typename KeyT, int K>
-static SearchArgs<KeyT> search_args(const spc_kmap* m) {
+static SearchArgs<KeyT> search_args(spc_kmap* m) {
   const PackInfo& pi = m->pi;
   const int sp_stride = m->desc.in_stride;
   const int sign = m->desc.transposed ? -1 : 1;
@@ -779,9 +784,16 @@ static SearchArgs<KeyT> search_args(const spc_kmap* m) {
   sp.zrev = (K > 1 && z_a > z_b) ? 1 : 0;
   for (int k = 0; k < K * K * K; ++k)
     if ((m->os_map && m->os_k.has(k)) || m->ws_k.has(k)) sp.need |= 1u << (k / (K * K));
-  const Level* in = m->in_level;
-  const Level* out = m->out_level;
+  Level* in = m->in_level;
+  Level* out = m->out_level;
   SearchArgs<KeyT> a{};
+  auto announce = [](Level* lv) {  // (a level is made on the stream of its searches)
+    if (lv->announced || !lv->slot.dev) return CountNote{};
+    lv->announced = true;
+    return CountNote{lv->slot.dev, lv->slot.tag};
+  };
+  a.note_in = announce(in);
+  a.note_out = announce(out);
   a.in_keys = static_cast<const KeyT*>(in->keys);
   a.n_in_h = static_cast<int>(in->n_host < 0 ? 0 : in->n_host);
   a.n_in_d = in->n_dev;
@@ -1155,7 +1167,7 @@ static int wait_stream(bool captured, hipStream_t s) {
   return SPC_OK;
 }
 
-// Spins until the level's count shows up in its pinned slot.  False when the stream has nothing left to run, or reports
+// Spins until the level's count shows up in its pinned slot (see CountNote).  False when the stream has nothing left to run, or reports
 // an error, and the count is not there: the caller then waits and copies, which reports what happened.
 static bool poll_count(Level* lv, int* v) {
   auto seen = [&]() {
@@ -1185,7 +1197,7 @@ static int fetch_level_n(Level* lv) {
     return SPC_OK;
   }
   int v = 0;
-  if (lv->slot.host && poll_count(lv, &v)) {
+  if (lv->announced && poll_count(lv, &v)) {
     lv->n_host = lv->n_fetched = v;
     return SPC_OK;
   }

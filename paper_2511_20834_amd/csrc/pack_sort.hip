@@ -79,7 +79,6 @@ __global__ __launch_bounds__(256) void dup_check_kernel(const KeyT* __restrict__
 }
 
 __global__ void set_int_kernel(int32_t* p, int32_t v) { *p = v; }
-__global__ void publish_count_kernel(CountOut count, int32_t v) { count.publish(v); }
 
 template <typename KeyT>
 __global__ __launch_bounds__(256) void mask_kernel(const KeyT* __restrict__ in, int64_t n, KeyT mask, KeyT* __restrict__ out) {
@@ -134,7 +133,7 @@ __global__ __launch_bounds__(UQ_THREADS) void unique_count_kernel(const KeyT* __
 
 // Single workgroup: exclusive scan of n_blocks counts in place; the grand total is the level's count.
 __global__ __launch_bounds__(UQ_THREADS) void scan_counts_kernel(int32_t* __restrict__ counts, int n_blocks,
-                                                                 CountOut count) {
+                                                                 int32_t* __restrict__ count) {
   int carry = 0;
   for (int b0 = 0; b0 < n_blocks; b0 += UQ_THREADS) {
     const int i = b0 + threadIdx.x;
@@ -144,7 +143,7 @@ __global__ __launch_bounds__(UQ_THREADS) void scan_counts_kernel(int32_t* __rest
     if (i < n_blocks) counts[i] = carry + ex;
     carry += total;
   }
-  if (threadIdx.x == 0) count.publish(carry);
+  if (threadIdx.x == 0) *count = carry;
 }
 
 template <typename KeyT>
@@ -166,7 +165,6 @@ __global__ __launch_bounds__(UQ_THREADS) void unique_write_kernel(const KeyT* __
 // One level of a size the library's own sort does not take.
 template <typename KeyT>
 static int downsample_t(const void* src, int64_t n, const PackInfo& pi, int m, Level* lv, hipStream_t s) {
-  const CountOut count{lv->n_dev, lv->slot.dev, lv->slot.tag};
   if (n > 0) SPC_RETURN_IF(refuse_if_capturing(s, n));
   const size_t ksz = sizeof(KeyT);
   const size_t tb = sort_keys_temp_bytes(pi.key_bits, n);
@@ -188,12 +186,12 @@ static int downsample_t(const void* src, int64_t n, const PackInfo& pi, int m, L
     rc = sort_keys(pi.key_bits, masked, sorted, n, pi.used_bits, scratch + off_temp, tb, s);
     if (rc == SPC_OK) {
       hipLaunchKernelGGL(unique_count_kernel<KeyT>, dim3(n_blocks), dim3(UQ_THREADS), 0, s, sorted, n, counts);
-      hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(UQ_THREADS), 0, s, counts, n_blocks, count);
+      hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(UQ_THREADS), 0, s, counts, n_blocks, lv->n_dev);
       hipLaunchKernelGGL(unique_write_kernel<KeyT>, dim3(n_blocks), dim3(UQ_THREADS), 0, s, sorted, n, counts,
                          static_cast<KeyT*>(lv->keys));
     }
   } else {
-    hipLaunchKernelGGL(publish_count_kernel, dim3(1), dim3(1), 0, s, count, 0);
+    hipLaunchKernelGGL(set_int_kernel, dim3(1), dim3(1), 0, s, lv->n_dev, 0);
   }
   // The scratch block returns to the cache now; reuse is ordered behind these kernels
   // as long as later library calls are ordered after this stream's work.
@@ -214,7 +212,7 @@ static int downsample_batch(const void* src, int64_t n, const PackInfo& pi, cons
   }
   LevelJob jobs[BS_MAX_LEVELS];
   for (int i = 0; i < count; ++i)
-    jobs[i] = LevelJob{level_mask(pi, m[i]), lv[i]->keys, CountOut{lv[i]->n_dev, lv[i]->slot.dev, lv[i]->slot.tag}};
+    jobs[i] = LevelJob{level_mask(pi, m[i]), lv[i]->keys, lv[i]->n_dev};
   if (small) return small_mask_unique(pi.key_bits, src, n, jobs, count, pi.used_bits, s);
   const size_t pitch = (bucket_sort_ws_bytes(pi.key_bits, n) + 255) / 256 * 256;
   char* scratch = static_cast<char*>(pool_alloc(pitch * count, s));

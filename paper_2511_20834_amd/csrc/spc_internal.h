@@ -50,16 +50,16 @@ struct StreamWorkNote {
 };
 
 // ---------------------------------------------------------------- counts the host waits for
-// Where a kernel leaves a count: always in device memory, and (slot given) also in pinned host memory, tagged with a
-// number of this build's own, so that the host can poll for exactly this value.  A host that waited for an event and
-// copied four bytes paid 21 us from the kernel's end to the number; the poll sees it about 2 us after the store.
-struct CountOut {
-  int32_t* n_out = nullptr;
+// A level's count goes to device memory, and from there to a slot in pinned host memory, tagged with a number of this
+// build's own, so that the host can poll for exactly this value.  A host that waited for an event and copied four bytes paid
+// 21 us from the kernel's end to the number; the poll sees it about 2 us after the store.  The slot is written by the first
+// search on the level, as it starts: by then the kernels that make the level have ended, so whoever has the count may read
+// the keys, on any stream.
+struct CountNote {
   unsigned long long* slot = nullptr;  // device address of the pinned slot, or NULL
   uint32_t tag = 0;
 #ifdef __HIPCC__
   __device__ void publish(int v) const {
-    *n_out = v;
     if (slot)
       __hip_atomic_store(slot, (static_cast<unsigned long long>(tag) << 32) | static_cast<uint32_t>(v), __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_SYSTEM);
@@ -120,6 +120,7 @@ struct Level {
   bool captured = false;  // produced while its stream was being captured into a graph: every replay rewrites it
   int* n_dev = nullptr;   // device int (nullptr when n_host is authoritative from the start)
   CountSlot slot;         // where the host polls for the count (not for levels built under capture)
+  bool announced = false; // a search that fills the slot has been enqueued
   int stride = 1;
   hipStream_t stream = nullptr;  // stream the level was produced on
   std::vector<hipStream_t> readers;  // other streams whose kernels read the keys (map searches)
@@ -199,7 +200,7 @@ constexpr int BS_MAX_LEVELS = 8;  // levels of one batch (the block rows of its 
 struct LevelJob {
   uint64_t mask;
   void* keys_out;
-  CountOut count;
+  int32_t* count;
 };
 // n_levels <= BS_MAX_LEVELS levels of the same keys by the same five launches; level y works in ws + y * ws_pitch
 int bucket_mask_unique(int key_bits, const void* keys_in, int64_t n, const LevelJob* jobs, int n_levels, int used_bits, void* ws,

@@ -628,6 +628,30 @@ def test_beyond_the_own_sort():
     B.spc_release_cache()
 
 
+@pytest.mark.parametrize("n", [3000, 70_001, 1_000_000])
+def test_level_keys_are_complete_once_the_count_is_known(n):
+    """Whoever has got n_out may read the output keys on any stream, while the search still runs on the build's.  Two clouds
+    of one size take turns, so that the other one's keys are in the blocks that a build gets."""
+    clouds = [synth.random_cloud(n, (400, 400, 200), seed=n + i)[:n] for i in range(2)]
+    desc = B.spc_pack_desc_fit((0, 0, 0), (399, 399, 199), 1, 2, 2)
+    refs = [oracle_keys(oracle.downsample(oracle.sort_coords(c)[0], 2), desc) for c in clouds]
+    keys = [gpu_pack(c, desc)[0] for c in clouds]
+    build, other = torch.cuda.Stream(), torch.cuda.Stream()
+    got = torch.zeros(n, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    for rep in range(8):
+        i = rep % 2
+        km = B.spc_build_kmap(keys[i], desc, 3, 1, 2, 0, B.LAYOUT_OS, stream=build)
+        n_out = km.n_out
+        assert n_out == len(refs[i])
+        whole = n_out // 4 * 4  # the copy moves 16 bytes at a time
+        B._check(B.lib().spc_probe_copy(B.lib().spc_kmap_out_keys(km.handle), got.data_ptr(), whole * 4, other.cuda_stream))
+        other.synchronize()
+        assert np.array_equal(keys_to_u64(got[:whole]), refs[i][:whole]), rep
+        torch.cuda.synchronize()
+        km.destroy()
+
+
 def test_destroy_and_rebuild_while_another_stream_still_reads_the_map():
     """spc_kmap_destroy hands the map's arrays back to the build stream's block cache without waiting.  A
     feature layer enqueued on another stream must still see its map when the next build on the build
