@@ -17,8 +17,10 @@
 // Of windows that do not fit the LDS budget every step-th key is staged, and the last few
 // probes of their searches go to global memory.
 #include <algorithm>
+#include <chrono>
 #include <map>
 #include <set>
+#include <thread>
 #include <tuple>
 #include <type_traits>
 
@@ -1167,24 +1169,33 @@ static int wait_stream(bool captured, hipStream_t s) {
   return SPC_OK;
 }
 
-// Spins until the level's count shows up in its pinned slot (see CountNote).  False when the stream has nothing left to run, or reports
-// an error, and the count is not there: the caller then waits and copies, which reports what happened.
+// Waits until the level's count shows up in its pinned slot (see CountNote): spinning for POLL_SPIN, which covers the level of
+// a few million voxels on an idle stream, then, behind whatever else the stream has to do, looking again after pauses of a
+// sixteenth of the time waited so far (1 ms at most).  False when the stream has nothing left to run, or reports an error, and
+// the count is not there: the caller then waits and copies, which reports what happened.
+constexpr std::chrono::microseconds POLL_SPIN{1000}, POLL_MOST{1000};
 static bool poll_count(Level* lv, int* v) {
+  using Clock = std::chrono::steady_clock;
   auto seen = [&]() {
     const unsigned long long x = __atomic_load_n(lv->slot.host, __ATOMIC_ACQUIRE);
     *v = static_cast<int>(static_cast<uint32_t>(x));
     return static_cast<uint32_t>(x >> 32) == lv->slot.tag;
   };
+  const Clock::time_point start = Clock::now();
   for (;;) {
-    for (int spin = 0; spin < 20000; ++spin) {  // some hundred microseconds
+    for (int spin = 0; spin < 64; ++spin) {
       if (seen()) return true;
       __builtin_ia32_pause();
     }
+    const auto waited = Clock::now() - start;
+    if (waited < POLL_SPIN) continue;
     if (stream_is_capturing(lv->stream)) return false;
     const hipError_t e = hipStreamQuery(lv->stream);
-    if (e == hipErrorNotReady) continue;
-    (void)hipGetLastError();
-    return seen();
+    if (e != hipErrorNotReady) {
+      (void)hipGetLastError();
+      return seen();
+    }
+    std::this_thread::sleep_for(std::min<Clock::duration>(waited / 16, POLL_MOST));
   }
 }
 

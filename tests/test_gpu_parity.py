@@ -2,6 +2,8 @@
 Kernel maps must be bit-exact (sorted (offset, in, out) triples); features within
 max|y - yhat| / max|yhat| <= 1e-2 for fp16/bf16 inputs with fp32 accumulation and
 1e-5 in fp32 mode."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -650,6 +652,29 @@ def test_level_keys_are_complete_once_the_count_is_known(n):
         assert np.array_equal(keys_to_u64(got[:whole]), refs[i][:whole]), rep
         torch.cuda.synchronize()
         km.destroy()
+
+
+def test_waiting_for_a_count_does_not_occupy_a_core():
+    """n_out behind a stream that is busy for some time: the wait ends with the right count, and the thread sleeps for most
+    of it."""
+    c = _cloud("rand_b3")
+    desc = fit_desc(c, [(2, 1, 2)])
+    keys, _ = gpu_pack(c, desc)
+    n_ref = len(oracle.downsample(oracle.sort_coords(c)[0], 2))
+    sink = torch.zeros(1, device="cuda")
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    a.record()
+    B.spc_probe_mfma(20000, sink)
+    b.record()
+    torch.cuda.synchronize()
+    for _ in range(int(100 / max(a.elapsed_time(b), 0.1)) + 1):  # some 100 ms
+        B.spc_probe_mfma(20000, sink)
+    t0, c0 = time.monotonic(), time.thread_time()
+    km = B.spc_build_kmap(keys, desc, 2, 1, 2, 0, B.LAYOUT_OS)
+    assert km.n_out == n_ref
+    wall, cpu = time.monotonic() - t0, time.thread_time() - c0
+    assert wall > 0.02 and cpu < wall / 3, (wall, cpu)
+    km.destroy()
 
 
 def test_destroy_and_rebuild_while_another_stream_still_reads_the_map():
