@@ -174,7 +174,9 @@ __device__ inline void redo_nan(const floatx16 (&acc)[NB], int rows, int lane, T
 // drew, so results are bit-reproducible.
 // A tile of 1024 rows takes 26 us (listing 5, dense cells 7, products 5, additions 4, stores 3): the latencies of a chain of
 // dependent loads, of which one workgroup fills a CU's LDS.  3 M random voxels, 64->64: 513 us by phases, 326 us pooled;
-// 1 M: 176 / 104; 200 k: 43 / 33; indoor scans, 240 k: 46 / 40.
+// 1 M: 176 / 104; 200 k: 43 / 33; indoor scans, 240 k: 46 / 40.  It is reached through the phase kernel: where the layer's
+// size alone makes prefer_splitk choose the other kernel (64 columns with a last round that is not full, such as 200 k and
+// 300 k voxels; most layers of 128 columns and more with prepacked weights), it is taken on request only.
 constexpr int POOL_WAVES = 16, POOL_BLOCKS = 32;
 constexpr int POOL_DENSE = 8;     // valid rows from which a cell is multiplied on its own
 constexpr int POOL_PAIRS = 64;    // pairs in a block's list (a cell that does not fit any more is multiplied on its own too)
@@ -1484,7 +1486,8 @@ static void launch_os_splitk(const ConvArgs& a) {
 // Layers the split-k kernel runs with 128-column slabs: the phase kernel (one workgroup of sixteen 64-column tiles per
 // CU) wins while one round of its workgroups holds the layer and leaves less than half of their waves idle: us, phase / split-k,
 // 60 k voxels 128->128 48.2 / 58.6, 35 k 37.1 / 39.4, 18 k 128->256 38.0 / 41.6; with fewer tiles 18 k 128->128 29.2 / 24.4;
-// with more, 35 k 256->256 168 / 120, 120 k 128->128 97 / 91, 256->256 336 / 317, 100 k random voxels 253 / 185.
+// with more, 35 k 256->256 168 / 120, 120 k 128->128 97 / 91, 256->256 336 / 317, 100 k random voxels 253 / 185.  (All of
+// this was measured where the phase kernel goes by phases; the host cannot see whether a level is one for its pooled way.)
 template <typename T>
 static bool prefer_splitk(const ConvArgs& a) {
   const int64_t n_blocks = (a.rows_sel + 31) / 32;

@@ -866,6 +866,52 @@ def test_conv_sparse_neighbourhoods(n, cin, cout, dtype, density, cube):
     km.destroy()
 
 
+@pytest.mark.parametrize("transposed", [0, 1])
+def test_conv_sparse_neighbourhoods_of_strided_layers(transposed):
+    """The pooled way on a 3x3x3 stride-2 level, whose voxel count only the device knows, and on its transposed layer."""
+    n, side = 150_003, 370
+    c = _lin_cloud(np.random.default_rng(81).choice(side ** 3, size=n, replace=False), (side, side, side))
+    desc = fit_desc(c, [(3, 1, 2)])
+    keys, _ = gpu_pack(c, desc)
+    cs, _ = oracle.sort_coords(c)
+    src, dst, M = oracle_layer(cs, 3, 1, 2, transposed)
+    pairs = np.add.reduceat((M >= 0).sum(1), np.arange(0, len(M), 32))
+    assert len(dst) > 131_072 and (pairs <= 50).mean() > 0.9  # a level for the pooled way
+    Ft, F64 = to_torch(synth.features(len(src), 32, np.float16, seed=82), torch.float16)
+    Wt, W64 = to_torch(synth.weights(27, 32, 64, np.float16, seed=83), torch.float16)
+    km = B.spc_build_kmap(keys, desc, 3, 1, 2, transposed, B.LAYOUT_OS)
+    out = torch.full((n, 64), 7.0, dtype=torch.float16, device="cuda")
+    B.spc_conv_forward(km, Ft, Wt, flags=B.CONV_OS_PHASE, out=out)
+    assert km.n_out == len(dst)
+    assert_close(out[: len(dst)].cpu().to(torch.float64).numpy(), oracle.conv(M, F64, W64), 1e-2, "pooled")
+    assert bool((out[len(dst):] == 7.0).all())
+    km.destroy()
+
+
+@pytest.mark.parametrize("n,density,want", [
+    (250_007, 0.0125, B.CONV_OS_PHASE), (1_000_003, 0.0125, B.CONV_OS_PHASE),  # (pooled, being nearly empty)
+    (200_003, 0.0125, B.CONV_OS_SPLITK),   # the last round of phase workgroups would be half full
+    (20_011, 0.2, B.CONV_OS_SPLITK), (60_013, 0.2, B.CONV_OS_PHASE),
+])
+def test_conv_default_kernel(n, density, want):
+    """Which output-stationary kernel a 3x3x3 64->64 layer with prepacked weights takes by itself: the two sum in different
+    orders, and each gives the same bits every time."""
+    side = int(round((n / density) ** (1 / 3))) + 1
+    rng = np.random.default_rng(n)
+    lin = np.unique(rng.integers(0, side ** 3, size=n + n // 3))
+    c = _lin_cloud(rng.choice(lin, size=n, replace=False), (side, side, side))
+    desc = fit_desc(c, [(3, 1, 1)])
+    keys, perm = gpu_pack(c, desc)
+    F = torch.from_numpy(synth.features(n, 64, np.float16, seed=84)).cuda()
+    W = B.spc_conv_prepare_weights(torch.from_numpy(synth.weights(27, 64, 64, np.float16, seed=85)).cuda())
+    km = B.spc_build_kmap(keys, desc, 3, layout=B.LAYOUT_OS, in_perm=perm)
+    own = B.spc_conv_forward(km, F, W, flags=B.CONV_PACKED_WEIGHTS)
+    for kernel in (B.CONV_OS_PHASE, B.CONV_OS_SPLITK):
+        y = B.spc_conv_forward(km, F, W, flags=B.CONV_PACKED_WEIGHTS | kernel)
+        assert torch.equal(own, y) == (kernel == want), kernel
+    km.destroy()
+
+
 # ----------------------------------------------------------------------------- wide slabs, tiles shared by workgroups
 @pytest.mark.parametrize("n,cin,cout", [(33, 256, 256), (480, 256, 256), (1025, 128, 256), (481, 128, 128), (2049, 64, 128), (6001, 64, 128)])
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
