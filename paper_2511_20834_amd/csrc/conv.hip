@@ -482,7 +482,7 @@ __global__ __launch_bounds__(64 * WAVES) void conv_os_phase_kernel(const int32_t
                                                                    const T* __restrict__ F, int64_t ld_in,
                                                                    const T* __restrict__ Wp, T* __restrict__ out,
                                                                    int64_t ld_out, int cin, int relu, int chunks_per_phase,
-                                                                   int n_wg_per_xcd, int nb_total, KMask kmask) {
+                                                                   int nb_total, KMask kmask) {
   using V8 = typename Mfma<T>::V;
   constexpr int CKS = 16 * NKK;
   constexpr int THREADS = 64 * WAVES;
@@ -519,7 +519,6 @@ __global__ __launch_bounds__(64 * WAVES) void conv_os_phase_kernel(const int32_t
   const bool active = t_in_xcd < tiles_per_xcd && tile < n_tiles;
   const int64_t blk0 = tile * RB;
   const int nch = cin / CKS;
-  (void)n_wg_per_xcd;
 
   if constexpr (NB == 2 && WAVES == POOL_WAVES && NKK >= 2) {
     if (K3 == 27 && pool_level(block_masks, n_blocks, gridDim.y, lane)) {
@@ -1308,7 +1307,7 @@ static void launch_os_mfma(const ConvArgs& a, const T* Wp) {
     (void)attr;
     hipLaunchKernelGGL((conv_os_phase_kernel<T, NB, RBK, WAVES, NKK, DEPTH>), dim3(per_xcd * 8, n_slabs), dim3(64 * WAVES), lds,
                        a.s, a.m->os_map, a.m->block_masks, a.m->mask_words, a.n_out_h, a.n_out_d, a.m->K3,
-                       static_cast<const T*>(a.F), a.ld_in, Wp, static_cast<T*>(a.out), a.ld_out, a.cin, a.relu, cpp, per_xcd,
+                       static_cast<const T*>(a.F), a.ld_in, Wp, static_cast<T*>(a.out), a.ld_out, a.cin, a.relu, cpp,
                        nb_total, a.os_mask);
   };
   if (a.cin % 64 == 0) go(std::integral_constant<int, 4>{});
