@@ -5,9 +5,8 @@ is one ``spc_conv_forward`` call.  Skip connections are realised without a copy:
 producers write into the two column halves of one buffer (row pitch arguments).
 
 ``SpcNetwork.capture_step`` records the whole step of one cloud size (pack + sort, feature
-permutation, map build on several streams, all feature layers) into one HIP graph: a step
-enqueues some 150 small kernels and as many event operations, which costs the host about as
-much time as the GPU needs to run them; replaying the graph removes the host from the loop."""
+permutation, map build, all feature layers; some 40 kernels on one stream) into one HIP graph:
+replaying it takes the host out of the loop."""
 from __future__ import annotations
 
 import torch

@@ -1,5 +1,5 @@
 """Configuration 4: the 25-layer UNet-style stack on the LiDAR-like cloud, with all kernel
-maps built up front by the network-wide builder on several HIP streams."""
+maps built up front by the network-wide builder."""
 import numpy as np
 import pytest
 import torch
