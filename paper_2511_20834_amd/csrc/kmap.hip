@@ -215,14 +215,15 @@ __global__ __launch_bounds__(64 * K) void kmap_search_kernel(const SearchBatch<K
   const int n_in = level_count(args.n_in_d, args.n_in_h);
   const int n_out = level_count(args.n_out_d, args.n_out_h);
   const int i0 = blockIdx.x * TILE;
-  if (i0 == 0 && tid == 0) {
-    args.note_in.publish(n_in);
-    args.note_out.publish(n_out);
-  }
   if (i0 >= n_out) return;  // whole workgroup leaves together
   const int rows = min(TILE, n_out - i0);
-  if (blockIdx.x == 0)
+  if (blockIdx.x == 0) {
+    if (tid == 0) {
+      args.note_in.publish(n_in);
+      args.note_out.publish(n_out);
+    }
     for (int j = tid; j < SHARED_TILES; j += 64 * K) ((SPC_GLOBAL int32_t*)args.arrived)[j] = 0;
+  }
   if constexpr (PAIRS)
     for (int k = tid; k < K3; k += 64 * K) s_cnt[k] = 0;
   for (int k = tid; k < MAX_BLOCKS * MW; k += 64 * K) s_mask[k] = 0u;
