@@ -24,6 +24,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef int intx4 __attribute__((ext_vector_type(4)));
 
 // One slab = the input channels of one operand register pair: lane l holds LPC consecutive channels (16 bytes) of row
 // (A) or column (B) l%32, starting at LPC * (l/32).
@@ -205,7 +206,7 @@ struct PoolLds {
 };
 
 template <typename T, int NKK>
-__device__ inline void conv_pool_tile(PoolLds& L, const int64_t blk0, const int64_t n_blocks, const int n_out, const int32_t* __restrict__ M,
+__device__ __forceinline__ void conv_pool_tile(PoolLds& L, const int64_t blk0, const int64_t n_blocks, const int n_out, const int32_t* __restrict__ M,
                                       const uint32_t* __restrict__ block_masks, const unsigned kmask, const int K3, const T* __restrict__ F,
                                       const int64_t ld_in, const T* __restrict__ Wp, T* __restrict__ out, const int64_t ld_out,
                                       const int cin, const int relu, const int nb_total, const int slab) {
@@ -430,26 +431,95 @@ __device__ inline bool pool_level(const uint32_t* __restrict__ block_masks, int6
   return __popcll(__ballot((m & POOL_MARK) != 0u)) >= 48;
 }
 
+// Gathers.  A CU's vector memory path takes a group of four lanes per cycle as long as the four read one 64-byte piece; four
+// lanes with a row each take a cycle each.  Loaded in the MFMA's operand order, where neighbouring lanes hold neighbouring
+// rows, rows arrive at 16 bytes per cycle and CU; with four lanes to 64 bytes of a row, at 50 (rows of 128 bytes at random
+// places, resident in L2).  So four (or two) neighbouring lanes fetch the pieces of their rows one row after the other, and
+// exchange them in registers when they are needed.
+// Lanes 2i and 2i+1 (PAIR = 1) or 4i+j and 4i+j+2 (2), for both pairs of registers: the first keeps a and takes the second's a
+// for its b, the second keeps b and takes the first's b for its a.  (Written by hand: the compiler takes twice the instructions.
+// An instruction that reads other lanes' registers, or a matrix instruction, wants two slots between itself and the write.)
+template <int PAIR>
+__device__ inline void lane_exchange(intx4& a, intx4& b, intx4& c, intx4& d) {
+  constexpr unsigned long long first = PAIR == 1 ? 0x5555555555555555ull : 0x3333333333333333ull;
+  intx4 t, u;
+#define SPC_EXCHANGE(PERM)                                                                                          \
+  asm("s_mov_b64 vcc, %24\n\ts_nop 0\n\t"                                                                          \
+      "v_cndmask_b32_dpp %0, %8, %16, vcc " PERM "\n\tv_cndmask_b32_dpp %1, %9, %17, vcc " PERM "\n\t"             \
+      "v_cndmask_b32_dpp %2, %10, %18, vcc " PERM "\n\tv_cndmask_b32_dpp %3, %11, %19, vcc " PERM "\n\t"           \
+      "v_cndmask_b32_dpp %4, %12, %20, vcc " PERM "\n\tv_cndmask_b32_dpp %5, %13, %21, vcc " PERM "\n\t"           \
+      "v_cndmask_b32_dpp %6, %14, %22, vcc " PERM "\n\tv_cndmask_b32_dpp %7, %15, %23, vcc " PERM                   \
+      : "=&v"(t.x), "=&v"(t.y), "=&v"(t.z), "=&v"(t.w), "=&v"(u.x), "=&v"(u.y), "=&v"(u.z), "=&v"(u.w)              \
+      : "v"(b.x), "v"(b.y), "v"(b.z), "v"(b.w), "v"(d.x), "v"(d.y), "v"(d.z), "v"(d.w), "v"(a.x), "v"(a.y),         \
+        "v"(a.z), "v"(a.w), "v"(c.x), "v"(c.y), "v"(c.z), "v"(c.w), "s"(first)                                      \
+      : "vcc");                                                                                                     \
+  asm("s_mov_b64 vcc, %16\n\ts_nop 0\n\t"                                                                          \
+      "v_cndmask_b32_dpp %0, %8, %0, vcc " PERM "\n\tv_cndmask_b32_dpp %1, %9, %1, vcc " PERM "\n\t"               \
+      "v_cndmask_b32_dpp %2, %10, %2, vcc " PERM "\n\tv_cndmask_b32_dpp %3, %11, %3, vcc " PERM "\n\t"             \
+      "v_cndmask_b32_dpp %4, %12, %4, vcc " PERM "\n\tv_cndmask_b32_dpp %5, %13, %5, vcc " PERM "\n\t"             \
+      "v_cndmask_b32_dpp %6, %14, %6, vcc " PERM "\n\tv_cndmask_b32_dpp %7, %15, %7, vcc " PERM "\n\ts_nop 1"     \
+      : "+v"(b.x), "+v"(b.y), "+v"(b.z), "+v"(b.w), "+v"(d.x), "+v"(d.y), "+v"(d.z), "+v"(d.w)                      \
+      : "v"(a.x), "v"(a.y), "v"(a.z), "v"(a.w), "v"(c.x), "v"(c.y), "v"(c.z), "v"(c.w), "s"(~first)                 \
+      : "vcc")
+  if constexpr (PAIR == 1) {
+    SPC_EXCHANGE("quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf");
+  } else {
+    SPC_EXCHANGE("quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf");
+  }
+#undef SPC_EXCHANGE
+  a = t;
+  c = u;
+}
+// Pieces as fetched (register i: a piece of the group's row i) to pieces as multiplied (register i: the lane's own row, piece i).
+template <typename V, int N>
+__device__ inline void rows_to_lanes(V (&v)[N]) {
+  if constexpr (N == 1) return;
+  intx4 x[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) x[i] = __builtin_bit_cast(intx4, v[i]);
+  if constexpr (N == 4) {
+    lane_exchange<1>(x[0], x[1], x[2], x[3]);
+    lane_exchange<2>(x[0], x[2], x[1], x[3]);
+  } else if constexpr (N == 2) {
+    intx4 y = x[0], z = x[1];
+    lane_exchange<1>(x[0], x[1], y, z);
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = __builtin_bit_cast(V, x[i]);
+}
+// x of lane i of the N lanes that fetch together.
+template <int N, int I>
+__device__ inline unsigned group_lane(unsigned x) {
+  constexpr int perm = N == 4 ? I * 0x55 : N == 2 ? I | (I << 2) | ((2 + I) << 4) | ((2 + I) << 6) : 0xe4;
+  return static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), perm, 0xf, 0xf, true));
+}
+// Bytes that the 32-bit offsets of buffer loads may reach; beyond, they answer zeros.
+constexpr uint32_t MAX_OFFSET = 0x80000000u;
+
 // Output-stationary kernel: waves are autonomous, weights are staged through LDS in phases.
 //
 // A workgroup of WAVES waves walks the weight tensor once, in phases of up to HALF_BYTES.
 // The phases alternate between two halves of the LDS buffer: while a phase is being
-// consumed, every thread already holds its share of the next phase in registers (loaded
-// before the compute started) and drops it into the other half afterwards — one barrier
-// per phase, and the L2 latency of the weights is off the critical path.
+// consumed, the next one's weights travel from memory to the other half (without passing through
+// registers, which frees twenty of them) — one barrier per phase, and the L2 latency of the
+// weights is off the critical path.
 // Each wave owns RB adjacent blocks of 32 consecutive output voxels and processes — on its
 // own, without further synchronisation — those of its steps whose weights are resident.
 // A step is one offset k with at least one valid row in the wave's blocks (the map
 // builder's block masks say which) and one chunk of CKS input channels:
-//   A operand: 32 gathered feature rows per block, straight from global memory into
-//              registers (lane l reads 16 bytes: channels 8*(l/32)..+7 of row l%32 per
-//              16-channel slab), kept in a ring of D buffers so that D-1 gathers are in
-//              flight behind the one being multiplied; rows without an input voxel gather
-//              from a zero row (selecting the address, not the data, keeps the loaded
-//              registers untouched until use, so nothing waits on a prefetch);
-//   B operand: 16-byte conflict-free LDS reads, each reused for the RB blocks;
+//   A operand: 32 gathered feature rows per block, from global memory into registers, a step
+//              ahead of its use.  The lanes of a group fetch the pieces of the group's rows, one
+//              row after the other (see lane_exchange), and swap them when the step begins.  The
+//              buffer loads' bounds check answers rows without an input voxel with zeros;
+//   B operand: 16-byte conflict-free LDS reads, each reused for the RB blocks, all requested
+//              before the first is waited for;
 //   MFMA 32x32x16 into fp32 accumulators that stay in registers for the whole kernel
 //   (no atomics; the offset order is ascending, so results are bit-reproducible).
+// What bounds it: the step chain of the fullest tiles (27 offsets where the average tile has 11; a workgroup's waves wait
+// for each other at every phase).  A step alone on its SIMD takes 775 cycles: 256 of matrix instructions, 180 of exchange, the rest
+// issue and LDS latency.  us, rows in operand order with a ring of two / this: 120 k LiDAR voxels 64->64 30.6 / 25.5, 64->128 56.8 / 46.0, 128->128 94 /
+// 80, stride 2 64->128 28.0 / 23.9.  The ring was worth little: a phase may end on either buffer, and the compiler then moved buffers
+// between registers and waited for the loads under way.
 // Tiles (a wave's RB blocks) go to the XCDs in chunks of PHASE_XCD_CHUNK and, inside an XCD, to
 // the workgroups round-robin: a workgroup's waves sit in different parts of the cloud (dense
 // and sparse regions mix, which balances the CUs and the XCDs), while neighbouring blocks,
@@ -474,7 +544,7 @@ __host__ __device__ inline int phase_wgs_per_xcd(int64_t tiles_per_xcd, int wave
   return static_cast<int>(full > s ? full : s);
 }
 
-template <typename T, int NB, int RB, int WAVES, int NKK, int D>
+template <typename T, int NB, int RB, int WAVES, int NKK, bool WIDE>
 __global__ __launch_bounds__(64 * WAVES) void conv_os_phase_kernel(const int32_t* __restrict__ M,
                                                                    const uint32_t* __restrict__ block_masks,
                                                                    int mask_words, int n_out_h,
@@ -531,42 +601,38 @@ __global__ __launch_bounds__(64 * WAVES) void conv_os_phase_kernel(const int32_t
     }
   }
 
-  // phase 0 of the weights is requested first, so that its latency overlaps the set-up below
+  // Weights go from memory to LDS without passing through registers.  The compiler does not know of these loads; they
+  // complete in the order of all of the wave's loads.  Phase 0 is requested first, so that its latency overlaps the set-up below.
   const int n_chunks = K3 * nch;
-  V8 st[SV];
-  auto stage_load = [&](int c_lo) {
-    const int hi = min(n_chunks, c_lo + chunks_per_phase);
-    const int n_vec = static_cast<int>(int64_t(hi - c_lo) * CKS * cout / 8);
+  auto stage = [&](int c, V8* dst) {
+    const int n_vec = static_cast<int>(int64_t(min(n_chunks, c + chunks_per_phase) - c) * CKS * cout / 8);
     // vector v of the phase, in slab view [chunk][kk][nb][lane], comes from [.][.][nb_total][lane] in memory
-    const V8* src = reinterpret_cast<const V8*>(Wp);
 #pragma unroll
     for (int i = 0; i < SV; ++i) {
-      const int v = min(i * THREADS + tid, n_vec - 1);
-      const int t = v >> 6, nbs = t % NB, kkg = t / NB;
-      st[i] = src[((int64_t(c_lo) * NKK + kkg) * nb_total + slab * NB + nbs) * 64 + (v & 63)];
+      const int t = i * WAVES + wave, nbs = t % NB, kkg = t / NB;
+      if (t * 64 < n_vec) {
+        const V8* src = reinterpret_cast<const V8*>(Wp) + ((int64_t(c) * NKK + kkg) * nb_total + slab * NB + nbs) * 64 + lane;
+        const unsigned at = static_cast<unsigned>(reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) V8*)(dst + t * 64)));
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(__builtin_amdgcn_readfirstlane(at)), "v"(src) : "memory", "m0");
+      }
     }
   };
-  auto stage_store = [&](int c_lo, V8* half) {
-    const int hi = min(n_chunks, c_lo + chunks_per_phase);
-    const int n_vec = static_cast<int>(int64_t(hi - c_lo) * CKS * cout / 8);
-#pragma unroll
-    for (int i = 0; i < SV; ++i)
-      if (i * THREADS + tid < n_vec) half[i * THREADS + tid] = st[i];
-  };
-  stage_load(0);
-  // offsets present in this wave's blocks: union of the blocks' masks, one word per 32 offsets,
-  // parked in LDS; the positions below walk its set bits in ascending order with scalar ops
-  unsigned* smask = reinterpret_cast<unsigned*>(klist);
-  for (int wd = lane; wd < mask_words; wd += 64) {
-    unsigned m = 0;
-    if (active) {
+  stage(0, sW);
+  // offsets present in this wave's blocks (union of the blocks' masks), in ascending order
+  int n_list = 0;
+  if (active)
+    for (int wd = 0; wd < mask_words; ++wd) {
+      unsigned m = 0;
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb)
         if (blk0 + rb < n_blocks) m |= block_masks[(blk0 + rb) * mask_words + wd];
+      m = __builtin_amdgcn_readfirstlane(m & kmask.w[wd]);
+      if (lane < 32 && ((m >> lane) & 1u)) klist[n_list + __builtin_popcount(m & ((1u << lane) - 1u))] = static_cast<int16_t>(wd * 32 + lane);
+      n_list += __builtin_popcount(m);
     }
-    smask[wd] = m & kmask.w[wd];
-  }
   __builtin_amdgcn_wave_barrier();
+  // lane i: the i-th offset, 64 of them at a time; past the last one K3, whose map rows and weights are never used
+  auto list_from = [&](int i) { return i + lane < n_list ? static_cast<int>(klist[i + lane]) : K3; };
 
   floatx16 acc[RB][NB];
 #pragma unroll
@@ -576,141 +642,107 @@ __global__ __launch_bounds__(64 * WAVES) void conv_os_phase_kernel(const int32_t
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[rb][nb][r] = 0.f;
 
-  // A position is (mask word, remaining bits of that word, channel chunk, current offset k).
-  // Positions past the end keep their last k, so that the pipeline issues the same loads every
-  // step (the surplus ones are never consumed).
-  struct Pos {
-    int wd;
-    unsigned rem;
-    int ch, k;
-    bool valid;
-  };
-  auto settle = [&](Pos& p) {
-    while (p.rem == 0 && p.wd + 1 < mask_words) {
-      ++p.wd;
-      p.rem = __builtin_amdgcn_readfirstlane(smask[p.wd]);
-    }
-    if (p.rem != 0) p.k = p.wd * 32 + __builtin_ctz(p.rem);
-    else p.valid = false;
-  };
-  auto advance = [&](Pos& p) {
-    if (++p.ch == nch) {
-      p.ch = 0;
-      p.rem &= p.rem - 1;
-      settle(p);
-    }
-  };
-  Pos p0{0, static_cast<unsigned>(__builtin_amdgcn_readfirstlane(smask[0])), 0, 0, true};
-  settle(p0);
   // a block past the end (odd tail) reads block 0's map rows; its results are never stored
-  const int32_t* Mb[RB];
+  __amdgpu_buffer_rsrc_t m_rsrc[RB];
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) Mb[rb] = M + ((active && blk0 + rb < n_blocks) ? blk0 + rb : 0) * int64_t(K3) * 32 + lr;
-  auto load_idx = [&](const Pos& p, int (&dst)[RB]) {
-    const int k32 = p.k * 32;
+  for (int rb = 0; rb < RB; ++rb)
+    m_rsrc[rb] = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(M) + ((active && blk0 + rb < n_blocks) ? blk0 + rb : 0) * int64_t(K3) * 32, 0,
+                                                   K3 * 128, 0x00020000);
+  auto load_idx = [&](int k, int (&dst)[RB]) {
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) dst[rb] = Mb[rb][k32];
+    for (int rb = 0; rb < RB; ++rb) dst[rb] = __builtin_amdgcn_raw_buffer_load_b32(m_rsrc[rb], lr * 4, k * 128, 0);
   };
   const T* zero_row = reinterpret_cast<const T*>(g_zero_row) + 8 * lh;
-  auto gather = [&](const Pos& p, const int (&j)[RB], V8 (&dst)[RB][NKK]) {
+  const __amdgpu_buffer_rsrc_t rows_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(F), 0, MAX_OFFSET, 0x00020000);
+  const unsigned row_bytes = static_cast<unsigned>(ld_in * sizeof(T));
+  const unsigned piece_off = NKK * 16 * lh + 16 * (lane & (NKK - 1));
+  auto gather = [&](int ch, const int (&j)[RB], V8 (&dst)[RB][NKK]) {
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-      const T* src = j[rb] < 0 ? zero_row : F + int64_t(j[rb]) * ld_in + p.ch * CKS + 8 * lh;
+      if constexpr (WIDE) {
+        const T* src = j[rb] < 0 ? zero_row : F + int64_t(j[rb]) * ld_in + ch * CKS + 8 * lh;
 #pragma unroll
-      for (int kk = 0; kk < NKK; ++kk) dst[rb][kk] = *reinterpret_cast<const V8*>(src + kk * 16);
+        for (int kk = 0; kk < NKK; ++kk) dst[rb][kk] = *reinterpret_cast<const V8*>(src + kk * 16);
+      } else {
+        const unsigned off = static_cast<unsigned>(j[rb]) * row_bytes;  // (of index -1: behind the 2 GB)
+        static_for<NKK>([&](auto I_) {
+          constexpr int I = decltype(I_)::value;
+          dst[rb][I] = __builtin_bit_cast(V8, __builtin_amdgcn_raw_buffer_load_b128(rows_rsrc, group_lane<NKK, I>(off) + piece_off, ch * (CKS * 2), 0));
+        });
+      }
     }
   };
 
-  // ring of D A-operand buffers: step u lives in buffer u % D and is refilled, once consumed,
-  // with step u + D; jj[b] holds the map indices for that refill, themselves loaded D steps earlier
-  V8 a[D][RB][NKK];
-  int jj[D][RB];
-  Pos pc = p0;  // current step
-  Pos pg = p0;  // next step to gather
-  Pos pi = p0;  // next step whose map indices are loaded
-#pragma unroll
-  for (int b = 0; b < D; ++b) {
-    load_idx(pg, jj[b]);
-    gather(pg, jj[b], a[b]);
-    advance(pg);
-  }
-  pi = pg;
-#pragma unroll
-  for (int b = 0; b < D; ++b) {
-    load_idx(pi, jj[b]);
-    advance(pi);
-  }
+  // A step's map indices are requested two steps before it, and its rows one step before.  (A ring of two buffers for the
+  // rows, filled two steps ahead, is no better: a phase may end on either of them, and the compiler then moves them between
+  // registers, waiting for the loads under way, or waits as if the other one had been filled last.)
+  V8 rows[RB][NKK];
+  int jj[RB];
+  int kv = list_from(0), i_next = 0, ch_next = 0;  // the next step whose indices are requested
+  int ch_rows = 0;                                 // the channels of the next step whose rows are
+  auto request = [&]() {  // returns the step's (offset, chunk of channels)
+    const int k = __builtin_amdgcn_readlane(kv, i_next & 63);
+    load_idx(k, jj);
+    const int chunk = k * nch + ch_next;
+    if (++ch_next == nch) {
+      ch_next = 0;
+      if ((++i_next & 63) == 0) kv = list_from(i_next);
+    }
+    return chunk;
+  };
+  auto fetch = [&]() {
+    gather(ch_rows, jj, rows);
+    if (++ch_rows == nch) ch_rows = 0;
+  };
+  int chunk = request();
+  fetch();
+  int chunk_next = request();
 
-  int c_hi = 0;
-  int64_t e_lo = 0;
+  int c_lo = 0, c_hi = 0;
   const V8* sWp = sW;  // LDS half of the current phase
-  auto can_step = [&]() -> bool { return pc.valid && pc.k * nch + pc.ch < c_hi; };
-  auto step = [&](auto B_) {
-    constexpr int B = decltype(B_)::value;
-    const V8* Bk = sWp + ((int64_t(pc.k) * cin + pc.ch * CKS) * cout - e_lo) / 8 + lane;
+  auto step = [&]() {
+    // piece c of a step's channels is in lanes 32 * (c % 2) + 0..31 of fragment c / 2; a lane holds pieces NKK * lh + 0..NKK-1 of
+    // its row (WIDE: every other one)
+    const V8* Bk = sWp + (chunk - c_lo) * (CKS * cout / 8) + (WIDE || NKK == 1 ? lane : lh * (NKK / 2 * NB * 64) + lr);
     V8 bw[NKK][NB];
 #pragma unroll
     for (int kk = 0; kk < NKK; ++kk)
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) bw[kk][nb] = Bk[(kk * NB + nb) * 64];
+      for (int nb = 0; nb < NB; ++nb) bw[kk][nb] = Bk[WIDE || NKK == 1 ? (kk * NB + nb) * 64 : (kk / 2 * NB + nb) * 64 + kk % 2 * 32];
+    __builtin_amdgcn_sched_barrier(0);  // (all fragments are requested before the first is waited for)
+    V8 a[RB][NKK];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+#pragma unroll
+      for (int kk = 0; kk < NKK; ++kk) a[rb][kk] = rows[rb][kk];
+      if constexpr (!WIDE) rows_to_lanes(a[rb]);
+    }
+    fetch();
+    chunk = chunk_next;
+    chunk_next = request();
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int kk = 0; kk < NKK; ++kk)
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) acc[rb][nb] = Mfma<T>::mma(a[B][rb][kk], bw[kk][nb], acc[rb][nb]);
-    gather(pg, jj[B], a[B]);
-    advance(pg);
-    load_idx(pi, jj[B]);
-    advance(pi);
-    advance(pc);
-  };
-  auto rotate_ring = [&]() {  // buffer 1 becomes buffer 0 (used when a phase ends off-phase; rare)
-    V8 t[RB][NKK];
-    int tj[RB];
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      tj[rb] = jj[0][rb];
-#pragma unroll
-      for (int kk = 0; kk < NKK; ++kk) t[rb][kk] = a[0][rb][kk];
-    }
-#pragma unroll
-    for (int b = 0; b + 1 < D; ++b)
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        jj[b][rb] = jj[b + 1][rb];
-#pragma unroll
-        for (int kk = 0; kk < NKK; ++kk) a[b][rb][kk] = a[b + 1][rb][kk];
-      }
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      jj[D - 1][rb] = tj[rb];
-#pragma unroll
-      for (int kk = 0; kk < NKK; ++kk) a[D - 1][rb][kk] = t[rb][kk];
-    }
+        for (int rb = 0; rb < RB; ++rb) acc[rb][nb] = Mfma<T>::mma(a[rb][kk], bw[kk][nb], acc[rb][nb]);
   };
 
-  stage_store(0, sW);
+  asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
   __syncthreads();
   int half = 0;
-  for (int c_lo = 0; c_lo < n_chunks; c_lo += chunks_per_phase) {
+  for (; c_lo < n_chunks; c_lo += chunks_per_phase) {
     c_hi = min(n_chunks, c_lo + chunks_per_phase);
-    e_lo = int64_t(c_lo) * CKS * cout;
     sWp = sW + half * (HALF_BYTES / 16);
     const bool more = c_hi < n_chunks;
-    if (more) stage_load(c_hi);
-    for (;;) {  // the current step always sits in buffer 0 here
-      if (!can_step()) break;
-      step(std::integral_constant<int, 0>{});
-      if (!can_step()) { rotate_ring(); break; }
-      step(std::integral_constant<int, 1>{});
-      if constexpr (D == 3) {
-        if (!can_step()) { rotate_ring(); rotate_ring(); break; }
-        step(std::integral_constant<int, 2>{});
-      }
-    }
+    if (more) stage(c_hi, sW + (half ^ 1) * (HALF_BYTES / 16));
+    const bool stepped = chunk < c_hi;
+    while (chunk < c_hi) step();
     half ^= 1;
-    if (more) stage_store(c_hi, sW + half * (HALF_BYTES / 16));
+    // the next phase's weights have arrived once all but the loads of the last step have
+    if (stepped) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(RB * (NKK + 1)) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
     __syncthreads();  // next phase visible; everybody is done with the half it will overwrite next
   }
   // D layout of the 32x32 MFMA: register r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l%32.
@@ -1279,6 +1311,13 @@ struct ConvArgs {
   hipStream_t s;
 };
 
+// Whether the feature rows are more than the 32-bit offsets of buffer loads reach.
+template <typename T>
+static bool wide_rows(const ConvArgs& a) {
+  const Level* il = a.m->in_level;
+  return (il->n_host < 0 ? il->cap : il->n_host) * a.ld_in * int64_t(sizeof(T)) > int64_t(MAX_OFFSET);
+}
+
 // OS: one grid row of workgroups per slab of NB*32 output channels (NB = 2, or 1 when cout is an
 // odd multiple of 32).  Small slabs keep the accumulators of two row blocks in registers and give
 // the coarse, wide layers of a network enough workgroups to fill the chip.
@@ -1289,7 +1328,6 @@ static void launch_os_mfma(const ConvArgs& a, const T* Wp) {
   // 32-column slabs: eight waves with two blocks (each weight fragment read from LDS serves both)
   constexpr int WAVES = NB == 2 ? 16 : 8;
   constexpr int RBK = NB == 2 ? 1 : 2;  // row blocks per wave
-  constexpr int DEPTH = 2;
   const int nb_total = a.cout / 32, n_slabs = nb_total / NB;
   const int64_t n_blocks = (a.rows_cap + 31) / 32;
   const int64_t n_tiles = (n_blocks + RBK - 1) / RBK;
@@ -1300,15 +1338,20 @@ static void launch_os_mfma(const ConvArgs& a, const T* Wp) {
   auto go = [&](auto NKK_) {
     constexpr int NKK = decltype(NKK_)::value;
     const int cpp = std::max(1, HALF_BYTES / (16 * NKK * NB * 32 * int(sizeof(T))));
-    // once per instantiation (initialisation of a local static is thread-safe); a failure shows up as a failed launch
-    static const hipError_t attr =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_os_phase_kernel<T, NB, RBK, WAVES, NKK, DEPTH>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-    (void)attr;
-    hipLaunchKernelGGL((conv_os_phase_kernel<T, NB, RBK, WAVES, NKK, DEPTH>), dim3(per_xcd * 8, n_slabs), dim3(64 * WAVES), lds,
-                       a.s, a.m->os_map, a.m->block_masks, a.m->mask_words, a.n_out_h, a.n_out_d, a.m->K3,
-                       static_cast<const T*>(a.F), a.ld_in, Wp, static_cast<T*>(a.out), a.ld_out, a.cin, a.relu, cpp,
-                       nb_total, a.os_mask);
+    auto launch = [&](auto WIDE_) {
+      constexpr bool WIDE = decltype(WIDE_)::value;
+      // once per instantiation (initialisation of a local static is thread-safe); a failure shows up as a failed launch
+      static const hipError_t attr =
+          hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_os_phase_kernel<T, NB, RBK, WAVES, NKK, WIDE>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+      (void)attr;
+      hipLaunchKernelGGL((conv_os_phase_kernel<T, NB, RBK, WAVES, NKK, WIDE>), dim3(per_xcd * 8, n_slabs), dim3(64 * WAVES), lds,
+                         a.s, a.m->os_map, a.m->block_masks, a.m->mask_words, a.n_out_h, a.n_out_d, a.m->K3,
+                         static_cast<const T*>(a.F), a.ld_in, Wp, static_cast<T*>(a.out), a.ld_out, a.cin, a.relu, cpp,
+                         nb_total, a.os_mask);
+    };
+    if (wide_rows<T>(a)) launch(std::true_type{});
+    else launch(std::false_type{});
   };
   if (a.cin % 64 == 0) go(std::integral_constant<int, 4>{});
   else if (a.cin % 32 == 0) go(std::integral_constant<int, 2>{});

@@ -1,0 +1,64 @@
+"""How the feature kernels fetch rows: channel counts that end inside a piece, a slab or a group of lanes, lists of more
+offsets than a wave has lanes, and features that lie beyond the reach of 32-bit byte offsets."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2511_20834_amd import binding as B
+from paper_2511_20834_amd import synth
+
+from gpu_common import assert_close, fit_desc, gpu_pack, to_torch
+
+pytestmark = pytest.mark.gpu
+
+# fp16 / bf16: the output's own rounding (2^-11, 2^-8) and fp32 sums in another order; fp32: at most 125 * 96 products, whose
+# rounding errors of 2^-24 each add up like their square root to about 1e-5 of the largest sum at the worst, 1e-6 as measured
+TOL = {torch.float16: 2e-3, torch.bfloat16: 1e-2, torch.float32: 1e-5}
+
+
+def _level(n, density, K, layout=B.LAYOUT_OS):
+    side = max(3, int(round((n / density) ** (1 / 3))) + 1)
+    lin = np.random.default_rng(n + K).choice(side ** 3, size=n, replace=False)
+    c = np.stack([np.zeros(n, np.int64), lin // (side * side), lin // side % side, lin % side], 1).astype(np.int32)
+    desc = fit_desc(c, [(K, 1, 1)])
+    keys, _ = gpu_pack(c, desc)
+    cs, _ = oracle.sort_coords(c)
+    return B.spc_build_kmap(keys, desc, K, layout=layout), oracle.kernel_map(cs, cs, K, 1)
+
+
+def _tensors(n, kvol, cin, cout, dtype):
+    src = np.float32 if dtype == torch.float32 else np.float16
+    F = to_torch(synth.features(n, cin, src, seed=91), dtype)
+    W = to_torch(synth.weights(kvol, cin, cout, src, seed=92), dtype)
+    return *F, *W
+
+
+@pytest.mark.parametrize("n,density,K", [(31, 0.5, 3), (4001, 0.3, 3), (2500, 0.6, 5)])
+@pytest.mark.parametrize("cin,cout", [(16, 64), (24, 32), (32, 64), (48, 96), (64, 128), (96, 64), (192, 64)])
+def test_phase_kernel_rows(n, density, K, cin, cout):
+    km, M = _level(n, density, K)
+    for dtype in (torch.float16, torch.bfloat16):
+        F, F64, W, W64 = _tensors(n, K ** 3, cin, cout, dtype)
+        y = B.spc_conv_forward(km, F, W, flags=B.CONV_OS_PHASE)
+        assert_close(y.cpu().to(torch.float64).numpy(), oracle.conv(M, F64, W64), TOL[dtype], (cin, cout, dtype))
+    km.destroy()
+
+
+def _far_apart(F):
+    """The same rows with a pitch that puts them on more than 2 GiB."""
+    pitch = (((1 << 31) // F.element_size()) // F.shape[0] + 64) // 64 * 64
+    wide = torch.empty((F.shape[0], pitch), dtype=F.dtype, device=F.device)
+    wide[:, : F.shape[1]] = F
+    assert wide.numel() * wide.element_size() > 1 << 31
+    return wide[:, : F.shape[1]]
+
+
+@pytest.mark.parametrize("cin", [32, 64])
+def test_phase_kernel_far_rows(cin):
+    n = 3001
+    km, M = _level(n, 0.3, 3)
+    F, F64, W, W64 = _tensors(n, 27, cin, 64, torch.float16)
+    y = B.spc_conv_forward(km, _far_apart(F), W, flags=B.CONV_OS_PHASE)
+    assert_close(y.cpu().to(torch.float64).numpy(), oracle.conv(M, F64, W64), TOL[torch.float16], cin)
+    km.destroy()
