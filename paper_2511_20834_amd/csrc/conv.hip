@@ -785,34 +785,42 @@ __global__ __launch_bounds__(64 * WAVES) void conv_os_phase_kernel(const int32_t
 }
 
 // Kernel for layers whose weight traffic is small next to the chip's L2 bandwidth (few output voxels, or few
-// channels), for fp32, for channel counts and rows that fit no tile, and for all offsets that come from lists: one
-// workgroup per block of 32 output voxels and slab of NB*32 output channels, and the offsets present in the block are
-// dealt round-robin to the workgroup's four waves (a split of the reduction over k, Eq. (2)).  Nothing is staged
-// through LDS and no barrier sits inside the loop: a wave reads the B fragments of its offsets straight from the
-// weights (L2-resident; 1 KB coalesced per fragment) next to the gathered A rows, D = 2 (offset, slab of channels)
-// entries ahead of the MFMA that consumes them.  The four partial accumulators meet in LDS and are summed in wave
-// order, so results are bit-reproducible; the sum leaves LDS transposed, each thread storing consecutive channels of
-// one row.  Compared with the phase kernel this trades redundant weight reads (every block re-reads its offsets'
-// weights) for many more, much shorter dependency chains, which is what the coarse levels of a network need: there a
-// layer has fewer row blocks than the chip has compute units.
+// channels), for fp32, for channel counts and rows that fit no tile, and for all offsets that come from lists.  A tile is
+// a block of 32 output voxels and a slab of NB*32 output channels.  One, two or four waves of a workgroup share a tile: the
+// offsets present in the block are dealt to them round-robin (a split of the reduction over k, Eq. (2)); a workgroup of four
+// waves holds four, two or one tiles (log_share, see splitk_share).  No barrier sits inside the loop: a wave reads the B
+// fragments of its offsets straight from the weights (L2-resident; 1 KB coalesced per fragment) next to the gathered rows,
+// an entry (an offset and 64 bytes of channels) ahead of the MFMA that consumes them.  Where waves share a tile their
+// accumulators meet in LDS and are summed in wave order, so results are bit-reproducible; the sum leaves through LDS, each
+// thread storing consecutive channels of one row.  Compared with the phase kernel this trades redundant weight reads (every
+// block re-reads its offsets' weights) for many more, much shorter dependency chains, which is what the coarse levels of a
+// network need: there a layer has fewer row blocks than the chip has compute units.
+//
+// Gathers.  A CU's vector memory path takes a group of four lanes per cycle, as long as the four read one 64-byte piece;
+// four lanes with a row each take a cycle each.  Loaded in the MFMA's operand order, where neighbouring lanes hold
+// neighbouring rows, rows therefore arrive at 16 bytes per cycle and CU; with four lanes to 64 bytes of a row they arrive at
+// 50 (rows of 128 bytes at random places, resident in L2).  So a wave loads 16 rows per instruction, four lanes
+// each, puts them down in 2 KB of LDS of its own and reads them back in operand order; the pieces of a row are swapped so
+// that neither side meets bank conflicts.  Rows are addressed by buffer loads, whose bounds check answers rows without an
+// input voxel and channels behind the last one with zeros.
 //
 // LISTS: offsets of the weight-stationary lists.  A list is ordered by output row, and the builder left behind where
 // every 32-row block starts in it, so a block's pairs of an offset are one contiguous piece of at most 32 entries; the
 // wave that owns the offset spreads them over the block's 32 rows in LDS.  From there on list and matrix offsets are
 // the same, and the sum over all offsets happens in registers.  (The form this replaces ran over the lists offset by
 // offset and merged with fp32 atomics in L2, which take about 1.2 TB/s, between a clearing and a rounding pass: 120 k
-// voxels, 64->64: 177 us, now 38.)
+// voxels, 64->64: 177 us.)
 //
 // What a wave reads (AM): 16-byte pieces of rows (A_VEC); the same with a channel count that ends inside the last slab
-// (A_RAGGED: pieces past the end come from the zero row); rows that are not 16-byte aligned or end inside a piece, one
-// channel at a time (A_ELEM); four-channel rows (A_QUAD), where a 16-channel slab holds four offsets instead of one
-// offset and twelve zeros.
+// (A_RAGGED); rows that are not 16-byte aligned or end inside a piece, one channel at a time (A_ELEM); four-channel rows
+// (A_QUAD), where a 16-channel slab holds four offsets instead of one offset and twelve zeros; features or weights of more
+// than 2 GB, which the 32-bit offsets of buffer loads do not reach (A_WIDE).
 constexpr int SPLITK_WAVES = 4;
-constexpr int SPLITK_KL_CAP = 96;  // >= ceil(7^3 / 4) + 4
-enum { A_VEC = 0, A_RAGGED = 1, A_ELEM = 2, A_QUAD = 3 };
+constexpr int SPLITK_CHUNK = 16;  // offsets of a wave whose rows are in LDS at a time (large kernels and lists)
+enum { A_VEC = 0, A_RAGGED = 1, A_ELEM = 2, A_QUAD = 3, A_WIDE = 4 };
 // Where a tile's pairs come from: the matrix, one row of 32 indices per present offset; the matrix of a kernel of at most
-// 32 offsets, all rows at once (one 16-byte load per thread, requested together with the masks instead of after them);
-// the lists (or the matrix, by offset).
+// 32 offsets, all rows at once (requested together with the masks instead of after them); the lists (or the matrix, by
+// offset).
 enum { MATRIX = 0, MATRIX_SMALL = 1, LISTS = 2 };
 
 struct ListArgs {
@@ -831,32 +839,71 @@ struct SplitkArgs {
   void* out;
   int64_t ld_in, ld_out;
   int mask_words, n_out_h, K3, cin, cout, relu, nb_total, vec_store;
-  int log_waves;      // log2 of the waves that share a tile's offsets: 2, or more with several workgroups per tile
-  float* partial;     // [tile][slab][part][32 * NB * 32]: the parts' sums, when a tile is shared by workgroups
-  int32_t* arrived;   // [tile][slab]: parts that have stored theirs; zero between launches
+  uint32_t row_bytes;  // pitch of the feature rows
+  uint32_t w_bytes;    // of the weights, as given
+  int has_os;          // lists: some offsets come from the matrix
+  int log_share;       // log2 of a workgroup's waves that share a tile
+  int log_waves;       // the same with the waves of other workgroups that share it
+  int kl_cap;          // entries of a wave's list of offsets
+  int tile_lds;        // bytes
+  float* partial;      // [tile][slab][part][32 * NB * 32]: the parts' sums, when a tile is shared by workgroups
+  int32_t* arrived;    // [tile][slab]: parts that have stored theirs; zero between launches
   KMask os_mask;
   ListArgs lists;
 };
+// LDS of a tile: rows of 32 input positions, with all-invalid ones at the end (for all of its waves, or per wave); its waves'
+// lists of offsets; their gathered rows.
+constexpr int splitk_tail(int AM) { return AM == A_QUAD ? 4 : 1; }
+__host__ __device__ constexpr int splitk_idx_bytes(int K3, int log_share, int AM, int FROM) {
+  return FROM == MATRIX_SMALL ? (K3 + 1) * 128 : ((SPLITK_CHUNK + splitk_tail(AM)) * 128) << log_share;
+}
+__host__ __device__ constexpr int splitk_list_bytes(int kl_cap, int log_share, int FROM) {
+  return (((kl_cap * (FROM == LISTS ? 10 : 2)) << log_share) + 15) / 16 * 16;
+}
+// Sums in LDS: rows of NB*32 floats and four more, which spreads the rows over the banks.  The partial sums of a tile meet
+// in one area per wave where they are small, else in one per two waves (the others add theirs).
+constexpr int splitk_pitch(int NB) { return NB * 32 + 4; }
+constexpr int splitk_areas(int NB) { return NB == 1 ? 4 : 2; }
+
+// Which output a thread stores as its e-th.
+template <int NB>
+__device__ inline void splitk_place(int log_share, int lane, int wave, int e, int& tile, int& row, int& col) {
+  if (log_share == 0) {
+    tile = wave;
+    row = lane >> 1;
+    col = e / 16 * 32 + (lane & 1) * 16 + e % 16;
+  } else {
+    tile = e / (NB * 4);
+    row = wave * 8 + lane / 8;
+    col = lane % 8 * (NB * 4) + e % (NB * 4);
+  }
+}
 // The outputs that this wave has stored as NaN, from their own pairs (see conv_by_pairs).
 using SplitkKernarg = const __attribute__((address_space(4))) SplitkArgs;
-template <typename T, int NB, int RB, bool LOOP, bool PACKED, bool LISTED>
+template <typename T, int NB, bool LOOP, bool PACKED, bool LISTED>
 __device__ inline void splitk_redo(SplitkKernarg* a) {
   using Ints = const SPC_GLOBAL int32_t*;
-  constexpr int EPT = NB * 4;
   const int n_out = a->n_out_d ? *(Ints)a->n_out_d : a->n_out_h;
   const int n_blocks = (n_out + 31) >> 5, K3 = a->K3, kc = (K3 - 1) / 2;
-  const int lane = threadIdx.x & 63, row0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 8, oc0 = blockIdx.y * (NB * 32);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int log_share = a->log_share, tiles = SPLITK_WAVES >> log_share, per = log_share == 0 ? NB * 16 : tiles * NB * 4;
 #pragma unroll 1
-  for (int blk0 = blockIdx.x * RB; blk0 < n_blocks; blk0 += LOOP ? gridDim.x * RB : n_blocks)
+  for (int first = blockIdx.x * tiles; first < n_blocks; first += LOOP ? gridDim.x * tiles : n_blocks)
 #pragma unroll 1
-    for (int e = 0; e < RB * EPT; ++e) {
-      const int blk = blk0 + e / EPT, my_i = blk * 32 + row0 + lane / 8, my_col = oc0 + lane % 8 * EPT + e % EPT;
+    for (int e = 0; e < per; ++e) {
+      int tile, my_row, my_col;
+      splitk_place<NB>(log_share, lane, wave, e, tile, my_row, my_col);
+      const int blk = first + tile, my_i = blk * 32 + my_row;
+      my_col += blockIdx.y * (NB * 32);
       SPC_GLOBAL T* dst = (SPC_GLOBAL T*)a->out + my_i * a->ld_out + my_col;
       float was = 0.f;
       if (my_i < n_out && my_col < a->cout) was = static_cast<float>(*dst);
 #pragma unroll 1
       for (unsigned long long todo = __ballot(was != was); todo; todo &= todo - 1) {
-        const int l = __builtin_ctzll(todo), row = row0 + l / 8, col = oc0 + l % 8 * EPT + e % EPT;
+        const int l = __builtin_ctzll(todo);
+        int row, col;
+        splitk_place<NB>(log_share, l, wave, e, tile, row, col);
+        col += blockIdx.y * (NB * 32);
         auto in_row = [&](int k) -> int {
           if ((a->os_mask.w[k >> 5] >> (k & 31)) & 1u) {
             const unsigned here = ((Ints)a->block_masks)[int64_t(blk) * a->mask_words + (k >> 5)];
@@ -881,71 +928,121 @@ __device__ inline void splitk_redo(SplitkKernarg* a) {
       }
     }
 }
-// rows of 32 input indices in LDS, with all-invalid rows at the end: per wave, or (MATRIX_SMALL) for all waves
-__host__ __device__ constexpr int splitk_idx_rows(int K3, int AM, int FROM) {
-  return FROM == MATRIX_SMALL ? K3 + 1 : (K3 + SPLITK_WAVES - 1) / SPLITK_WAVES + (AM == A_QUAD ? 4 : 1);
+
+// Waves per SIMD that the registers are kept for (prepacked weights).
+constexpr int splitk_occupancy(int NB, int FROM, bool LOOP) {
+  if (FROM == MATRIX_SMALL) return LOOP ? (NB == 4 ? 3 : NB == 2 ? 5 : 7) : NB == 4 ? 4 : NB == 2 ? 6 : 8;
+  return NB == 4 ? 3 : NB == 2 ? 5 : FROM == LISTS ? 6 : 8;  // (walking a list of offsets in pieces takes more)
 }
-// The waves' partial sums meet in LDS in four areas where they are small, else in two (two waves add theirs to the others').
-constexpr int splitk_areas(int NB, int RB) { return NB * RB == 1 ? 4 : 2; }
 
 // LOOP: the grid was sized from an estimate of the output count and tiles are walked with a grid
-// stride; otherwise one tile per workgroup (the loop costs about 30 registers per lane).
+// stride; otherwise one set of tiles per workgroup (the loop costs about 30 registers per lane).
 // PACKED: weights in MFMA operand order; otherwise the caller's [K^3][cin][cout], read a channel at a time (a fragment is
 // then 32-column rows of W instead of 16 bytes per lane: the same bytes in more instructions, but no re-layout pass).
-template <typename T, int NB, int RB, int D, bool LOOP, int AM, bool PACKED, int FROM>
-__global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 4 ? 4 : NB == 2 || LOOP ? 6 : 8) : 1) void conv_os_splitk_kernel(const SplitkArgs a) {
+template <typename T, int NB, bool LOOP, int AM, bool PACKED, int FROM, bool STAGED>
+__global__ __launch_bounds__(64 * SPLITK_WAVES, PACKED ? splitk_occupancy(NB, FROM, LOOP) : 1) void conv_os_splitk_kernel(const SplitkArgs) {
   using V = typename Mfma<T>::V;
+  using Ints = const SPC_GLOBAL int32_t*;
   constexpr int LPC = Mfma<T>::LPC, SLAB = 2 * LPC;
-  static_assert(RB == 1 || (AM == A_VEC && FROM == MATRIX), "two row blocks: plain layers only");
-  constexpr bool SHARED = RB == 1 && AM == A_VEC && NB <= 2;  // whether several workgroups may share a tile's offsets
+  constexpr bool SHARED = AM == A_VEC && NB <= 2;  // whether several workgroups may share a tile's offsets
+  constexpr bool OFFSETS = AM == A_VEC || AM == A_RAGGED || AM == A_QUAD;  // rows by byte offset, else by index
+  constexpr int TAIL = splitk_tail(AM), PITCH = splitk_pitch(NB);
   static_assert(AM != A_QUAD || sizeof(T) == 2, "four offsets per slab: 16-bit types");
   extern __shared__ __align__(16) unsigned char smem[];
-  const int32_t* __restrict__ M = a.M;
-  const uint32_t* __restrict__ block_masks = a.block_masks;
-  const T* __restrict__ F = static_cast<const T*>(a.F);
+  int first = 0, n_out = 0, step = 0;
+  bool again = false;  // (LOOP) this is not the first set of tiles
+  float z = 0.f;  // NaN once this thread has stored NaN or infinity
+  // the trip count is uniform per workgroup, so the barriers below are reached by all of its waves or by none
+  do {
+  // Everything that depends on the thread index or the arguments is derived anew in every trip from values the compiler
+  // cannot see through: hoisted out of the loop it would stay in registers across the whole body.
+  int tid = threadIdx.x;
+  SplitkKernarg* ap = (SplitkKernarg*)__builtin_amdgcn_kernarg_segment_ptr();
+  if constexpr (LOOP) asm volatile("" : "+v"(tid), "+s"(ap));
+  SplitkKernarg& a = *ap;
+  // What the set-up needs of them is asked for at once: a wait for each in turn would be a quarter of a small layer's time.
+  Ints M = (Ints)a.M, masks = (Ints)a.block_masks, n_out_d = (Ints)a.n_out_d;
+  int log_share = a.log_share, n_out_h = a.n_out_h, K3 = a.K3, mask_words = a.mask_words, kl_cap = a.kl_cap, tile_lds = a.tile_lds, log_waves = a.log_waves;
+  uint32_t row_bytes = a.row_bytes, os_word = a.os_mask.w[0];
+  asm volatile("" : "+s"(M), "+s"(masks), "+s"(n_out_d), "+s"(log_share), "+s"(n_out_h), "+s"(K3), "+s"(mask_words), "+s"(kl_cap), "+s"(tile_lds),
+               "+s"(log_waves), "+s"(row_bytes), "+s"(os_word));
+  const int tiles = SPLITK_WAVES >> log_share;
+  if (!LOOP || !again) {
+    n_out = n_out_d ? *n_out_d : n_out_h;
+    first = blockIdx.x * tiles;
+    if (first * 32 >= n_out) return;
+    if (LOOP) step = gridDim.x * tiles;
+  }
+  const int n_blocks = (n_out + 31) >> 5;
+  const T* __restrict__ F = reinterpret_cast<const T*>(a.F);
   const T* __restrict__ W = static_cast<const T*>(a.W);
   T* __restrict__ out = static_cast<T*>(a.out);
   const int64_t ld_in = a.ld_in, ld_out = a.ld_out;
-  const int K3 = a.K3, cin = a.cin, cout = a.cout, nb_total = a.nb_total;
-  const int n_out = a.n_out_d ? *a.n_out_d : a.n_out_h;
-  const int64_t n_blocks = (int64_t(n_out) + 31) >> 5;
+  const int cin = a.cin, cout = a.cout, nb_total = a.nb_total;
   const int slab = blockIdx.y;
   const int KK = (cin + SLAB - 1) / SLAB;
-  int log_waves = a.log_waves;
-  float z = 0.f;  // NaN once this thread has stored NaN or infinity
-  // tiles of RB blocks; the trip count is uniform per workgroup, so the barriers below are
-  // reached by all of its waves or by none
-  for (int64_t blk0 = int64_t(blockIdx.x) * RB; blk0 < n_blocks; blk0 += LOOP ? int64_t(gridDim.x) * RB : n_blocks) {
-  // Everything that depends on the thread index is derived anew in every trip from a value the
-  // compiler cannot see through: hoisted out of the loop, the lane constants of the set-up and of the
-  // epilogue would stay in registers across the whole body (26 registers, two waves per SIMD).
-  int tid = threadIdx.x;
-  if constexpr (LOOP) asm volatile("" : "+v"(tid));
+  const __amdgpu_buffer_rsrc_t rows_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(F), 0, MAX_OFFSET, 0x00020000);
+  const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(W), 0, a.w_bytes, 0x00020000);
+  // Where a row starts: its byte offset (that of index -1 lies behind the 2 GB, whatever the pitch), or its index.
+  auto row_pos = [&](int idx) { return OFFSETS ? static_cast<int>(static_cast<uint32_t>(idx) * row_bytes) : idx; };
+  auto row_pos4 = [&](intx4 v) { return intx4{row_pos(v.x), row_pos(v.y), row_pos(v.z), row_pos(v.w)}; };
+  // (only the first tile is shared with other workgroups: its slot is free again then, and who finished it goes on alone)
+  if (LOOP && again) log_waves = log_share;
   const int lane = tid & 63, lr = lane & 31, lh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int idx_rows = splitk_idx_rows(K3, AM, FROM);
-  int32_t* sIdx = reinterpret_cast<int32_t*>(smem) + (FROM == MATRIX_SMALL ? 0 : wave * idx_rows * (RB * 32));
-  unsigned char* kl_base = smem + size_t(FROM == MATRIX_SMALL ? 1 : SPLITK_WAVES) * idx_rows * (RB * 128);
-  int16_t* kl = reinterpret_cast<int16_t*>(kl_base) + wave * SPLITK_KL_CAP;
+  const int tile = wave >> log_share, blk = first + tile;
+  const bool here = blk < n_blocks;  // (the last workgroup's waves may have no tile)
+  auto sync = [&]() {  // of the waves that share a tile
+    if (log_share) __syncthreads();
+    else __builtin_amdgcn_wave_barrier();
+  };
+  const int member = wave & ((1 << log_share) - 1);  // among the waves of the tile
+  unsigned char* const tile_mem = smem + tile * tile_lds;
+  int32_t* sIdx = reinterpret_cast<int32_t*>(tile_mem) + (FROM == MATRIX_SMALL ? 0 : member * (SPLITK_CHUNK + TAIL) * 32);
+  unsigned char* kl_base = tile_mem + splitk_idx_bytes(K3, log_share, AM, FROM);
   // lists: where the pairs of this wave's offsets start, and how many there are (-1: from the matrix, -2: row = row)
-  int32_t* s_first = reinterpret_cast<int32_t*>(kl_base + SPLITK_WAVES * SPLITK_KL_CAP * 2) + wave * SPLITK_KL_CAP;
-  int32_t* s_num = s_first + SPLITK_WAVES * SPLITK_KL_CAP;
+  int32_t* s_first = reinterpret_cast<int32_t*>(kl_base) + member * kl_cap;
+  int32_t* s_num = s_first + (kl_cap << log_share);
+  int16_t* kl = reinterpret_cast<int16_t*>(kl_base + (FROM == LISTS ? (kl_cap << log_share) * 8 : 0)) + member * kl_cap;  // this wave's offsets
+  V* stage = reinterpret_cast<V*>(kl_base + splitk_list_bytes(kl_cap, log_share, FROM)) + member * 128;
 
-  int4 rows = {-1, -1, -1, -1};
+  intx4 rows[4];
+  const int lid = tid & ((64 << log_share) - 1);
+  // (MATRIX_SMALL) its up to 256 pieces of map rows, 64 << log_share at a time
+  auto pieces = [&](auto&& f) {
+    f(std::integral_constant<int, 0>{});
+    if (log_share < 2) f(std::integral_constant<int, 1>{});
+    if (log_share < 1) {
+      f(std::integral_constant<int, 2>{});
+      f(std::integral_constant<int, 3>{});
+    }
+  };
+  unsigned word = 0u;
   if constexpr (FROM == MATRIX_SMALL) {
-    if (tid < K3 * 8) rows = *reinterpret_cast<const int4*>(M + blk0 * (K3 * 32) + tid * 4);
+    if (here) word = masks[blk] & os_word;
+    pieces([&](auto U_) {
+      constexpr int U = decltype(U_)::value;
+      const int at = lid + (U << (6 + log_share));
+      rows[U] = intx4{-1, -1, -1, -1};
+      if (at < K3 * 8 && here) rows[U] = *(const SPC_GLOBAL intx4*)(M + int64_t(blk) * (K3 * 32) + at * 4);
+    });
   }
   // this wave's offsets: those present in the tile whose rank is its share mod the number of shares (cnt - share >= -31, so
   // the count of a share behind the last rank comes out as zero)
-  const int share = SHARED && log_waves > 2 ? blockIdx.z * SPLITK_WAVES + wave : wave;
+  int share = member;
+  if (SHARED && log_waves > log_share) share += blockIdx.z * SPLITK_WAVES;
   int cnt = 0;
-  if constexpr (FROM != LISTS) {  // (union of the builder's block masks)
-    for (int wd = 0; wd < a.mask_words; ++wd) {
-      unsigned m = 0;
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
-        if (blk0 + rb < n_blocks) m |= block_masks[(blk0 + rb) * a.mask_words + wd];
-      m = __builtin_amdgcn_readfirstlane(m & a.os_mask.w[wd]);
+  // lists: (pointers that the compiler is to keep as such, instead of choosing among the arguments per lane)
+  Ints l_in = (Ints)a.lists.in, l_out = (Ints)a.lists.out, l_base = (Ints)a.lists.base, l_base_in = (Ints)a.lists.base_in;
+  const bool sym = a.lists.sym, has_os = a.has_os;
+  const int kc = (K3 - 1) / 2;
+  if constexpr (FROM == LISTS) {
+    if (!sym) l_base_in = l_base;
+    asm volatile("" : "+s"(l_in), "+s"(l_out), "+s"(l_base), "+s"(l_base_in));
+  }
+  if constexpr (FROM != LISTS) {
+    for (int wd = 0; wd < (FROM == MATRIX_SMALL ? 1 : mask_words); ++wd) {
+      const unsigned m = FROM == MATRIX_SMALL ? word : here ? __builtin_amdgcn_readfirstlane(masks[int64_t(blk) * mask_words + wd] & a.os_mask.w[wd]) : 0u;
       if (lane < 32 && ((m >> lane) & 1u)) {
         const int rank = cnt + __builtin_popcount(m & ((1u << lane) - 1u));
         if ((rank & ((1 << log_waves) - 1)) == share) kl[rank >> log_waves] = static_cast<int16_t>(wd * 32 + lane);
@@ -953,31 +1050,30 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 4 ?
       cnt += __builtin_popcount(m);
     }
   } else {
-    const int kc = (K3 - 1) / 2;
     for (int k0 = 0; k0 < K3; k0 += 64) {
-      const int k = k0 + lane;
-      int first = 0, num = 0;
-      if (k < K3) {
-        if (a.lists.mask.has(k)) {
-          if (a.lists.sym && k == kc) {
-            num = -2;
-          } else {  // second half of a symmetric map: the opposite offset's list with the roles swapped
-            const bool mirror = a.lists.sym && k > kc;
-            const int32_t* tab = (mirror ? a.lists.base_in : a.lists.base) + blk0 * K3 + (mirror ? K3 - 1 - k : k);
-            first = tab[0];
-            num = tab[K3] - first;
-          }
-        } else if (a.os_mask.has(k) && ((block_masks[blk0 * a.mask_words + (k >> 5)] >> (k & 31)) & 1u)) {
-          num = -1;
-        }
+      const int k = k0 + lane, w0 = k0 >> 5, w1 = min(w0 + 1, KMASK_WORDS - 1);
+      // (the words of the masks are the same for each half of the wave)
+      const uint32_t lists2[2] = {a.lists.mask.w[w0], a.lists.mask.w[w1]};
+      uint32_t os2[2] = {a.os_mask.w[w0], a.os_mask.w[w1]};
+      if (has_os && here) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) os2[h] &= __builtin_amdgcn_readfirstlane(masks[int64_t(blk) * mask_words + min(w0 + h, mask_words - 1)]);
       }
+      // second half of a symmetric map: the opposite offset's list with the roles swapped
+      const bool in_list = k < K3 && here && (((lh ? lists2[1] : lists2[0]) >> lr) & 1u), mirror = sym && k > kc;
+      const Ints tab = (mirror ? l_base_in : l_base) + int64_t(here ? blk : 0) * K3 + (in_list ? (mirror ? K3 - 1 - k : k) : 0);
+      int from = tab[0], end = tab[K3];
+      SPC_PIN_LOADED(from);
+      SPC_PIN_LOADED(end);
+      int num = in_list ? end - from : k < K3 && here && (((lh ? os2[1] : os2[0]) >> lr) & 1u) ? -1 : 0;
+      if (sym && k == kc && in_list) num = -2;
       const unsigned long long bal = __ballot(num != 0);
       const int rank = cnt + __builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(bal >> 32),
                                                        __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(bal), 0));
       if (num != 0 && (rank & ((1 << log_waves) - 1)) == share) {
         const int at = rank >> log_waves;
         kl[at] = static_cast<int16_t>(k);
-        s_first[at] = first;
+        s_first[at] = from;
         s_num[at] = num;
       }
       cnt += __popcll(bal);
@@ -985,308 +1081,406 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, (RB == 1 && PACKED) ? (NB == 4 ?
   }
   const int n_i = __builtin_amdgcn_readfirstlane((cnt - share + (1 << log_waves) - 1) >> log_waves);
   // entries past the end read some offset's weights and all-invalid rows
-  constexpr int TAIL = AM == A_QUAD ? 4 : 1;
   if (lane < TAIL) kl[n_i + lane] = FROM == MATRIX_SMALL ? K3 : 0;
   if constexpr (FROM == MATRIX_SMALL) {
-    if (tid < K3 * 8) reinterpret_cast<int4*>(sIdx)[tid] = rows;
-    if (tid < 32) sIdx[K3 * 32 + tid] = -1;
-    __syncthreads();
+    pieces([&](auto U_) {
+      constexpr int U = decltype(U_)::value;
+      const int at = lid + (U << (6 + log_share));
+      if (at < K3 * 8) reinterpret_cast<intx4*>(sIdx)[at] = row_pos4(rows[U]);
+    });
+    if (lid < 32) sIdx[K3 * 32 + lid] = row_pos(-1);
+    sync();
   } else {
-    for (int q = lane; q < TAIL * RB * 32; q += 64) sIdx[n_i * RB * 32 + q] = -1;
-  }
-  __builtin_amdgcn_wave_barrier();
-  // row of indices of this wave's i-th offset k
-  auto idx_row = [&](int i, int k) { return FROM == MATRIX_SMALL ? k : i; };
-  auto weight_k = [&](int k) { return FROM == MATRIX_SMALL ? min(k, K3 - 1) : k; };
-  if constexpr (FROM == MATRIX) {
-    // their map rows (32 input indices per block), eight (offset, block) pairs per pass:
-    // lane -> (pair, 4 rows); blocks past the end of the level count as all-invalid
-    const int part = lane & 7;
-    for (int p = lane >> 3; p < n_i * RB; p += 8) {
-      const int i = p / RB, rb = p % RB;
-      int4 v = {-1, -1, -1, -1};
-      if (blk0 + rb < n_blocks)
-        v = *reinterpret_cast<const int4*>(M + ((blk0 + rb) * int64_t(K3) + kl[i]) * 32 + part * 4);
-      *reinterpret_cast<int4*>(sIdx + p * 32 + part * 4) = v;
-    }
-  } else if constexpr (FROM == LISTS) {
-    // two offsets per pass (a half-wave each, lane = row or pair), four passes' loads in flight together
-    for (int p0 = lh; p0 < n_i; p0 += 8) {
-      int row[4], val[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int p = p0 + 2 * u;
-        row[u] = -1;
-        val[u] = -1;
-        if (p < n_i) {
-          const int k = kl[p], num = s_num[p];
-          if (num == -1) {
-            row[u] = lr;
-            val[u] = M[(blk0 * K3 + k) * 32 + lr];
-          } else if (num == -2) {
-            row[u] = lr;
-            val[u] = blk0 * 32 + lr < n_out ? static_cast<int>(blk0 * 32) + lr : -1;
-          } else if (lr < num) {
-            const bool mirror = a.lists.sym && k > (K3 - 1) / 2;
-            const int64_t at = (mirror ? K3 - 1 - k : k) * a.lists.stride + s_first[p] + lr;
-            row[u] = (mirror ? a.lists.in : a.lists.out)[at] & 31;
-            val[u] = (mirror ? a.lists.out : a.lists.in)[at];
-          }
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (p0 + 2 * u < n_i) sIdx[(p0 + 2 * u) * 32 + lr] = -1;
-      __builtin_amdgcn_wave_barrier();
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (row[u] >= 0) sIdx[(p0 + 2 * u) * 32 + row[u]] = val[u];
-    }
-  }
-  __builtin_amdgcn_wave_barrier();
-
-  floatx16 acc[RB][NB];
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[rb][nb][r] = 0.f;
-
-  const T* zero_row = reinterpret_cast<const T*>(g_zero_row) + LPC * lh;
-  V av[D][RB];
-  V bv[D][NB];
-  if constexpr (AM == A_QUAD) {
-    // entry e = offsets 4e .. 4e+3 of this wave: lanes of the lower half hold four channels of each of the first two,
-    // lanes of the upper half of the last two
-    using V4 = T __attribute__((ext_vector_type(4)));
-    const int n_entries = (n_i + 3) / 4;
-    const T* zero4 = reinterpret_cast<const T*>(g_zero_row);
-    int e_n = 0;
-    auto issue = [&](auto S_) {
-      constexpr int S = decltype(S_)::value;
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int q = min(4 * e_n + 2 * lh + h, n_i);  // past the end: offset 0, no rows
-        const int kq = kl[q], k = weight_k(kq);
-        const int idx = sIdx[idx_row(q, kq) * 32 + lr];
-        const V4 f = *reinterpret_cast<const V4*>(idx < 0 ? zero4 : F + int64_t(idx) * ld_in);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) av[S][0][4 * h + j] = f[j];
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-          if constexpr (PACKED) {
-            const V4 w = *reinterpret_cast<const V4*>(W + ((int64_t(k) * nb_total + slab * NB + nb) * 64 + lr) * 8);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) bv[S][nb][4 * h + j] = w[j];
-          } else {
-            const T* w = W + int64_t(k) * 4 * cout + min((slab * NB + nb) * 32 + lr, cout - 1);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) bv[S][nb][4 * h + j] = w[j * cout];
-          }
-        }
-      }
-      ++e_n;
-    };
-    static_for<D>([&](auto S_) { issue(S_); });
-    for (int e0 = 0; e0 < n_entries; e0 += D) {
-      static_for<D>([&](auto S_) {
-        constexpr int S = decltype(S_)::value;
-        if (e0 + S < n_entries) {
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb) acc[0][nb] = Mfma<T>::mma(av[S][0], bv[S][nb], acc[0][nb]);
-        }
-        issue(S_);
-      });
-    }
-  } else {
-    // entry e = (i-th offset of this wave, slab kk of channels), kk fastest
-    const int n_entries = n_i * KK;
-    const V* Wv = reinterpret_cast<const V*>(W) + int64_t(slab) * NB * 64 + lane;  // PACKED
-    int i_n = 0, kk_n = 0;
-    int idx_n[RB];
-    int k_n = __builtin_amdgcn_readfirstlane(static_cast<int>(kl[0]));
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) idx_n[rb] = sIdx[(idx_row(0, k_n) * RB + rb) * 32 + lr];
-    auto issue = [&](auto S_) {
-      constexpr int S = decltype(S_)::value;
-      const int c0 = kk_n * SLAB + LPC * lh;  // this lane's first channel
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        if constexpr (AM == A_ELEM) {
-          const T* src = F + int64_t(idx_n[rb]) * ld_in + c0;
-#pragma unroll
-          for (int j = 0; j < LPC; ++j) av[S][rb][j] = *(idx_n[rb] < 0 || c0 + j >= cin ? zero_row : src + j);
-        } else {
-          const bool none = idx_n[rb] < 0 || (AM == A_RAGGED && c0 >= cin);
-          av[S][rb] = *reinterpret_cast<const V*>(none ? zero_row : F + int64_t(idx_n[rb]) * ld_in + c0);
-        }
-      }
-      if constexpr (PACKED) {
-        const V* wsrc = Wv + (int64_t(weight_k(k_n)) * KK + kk_n) * nb_total * 64;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) bv[S][nb] = wsrc[nb * 64];
-      } else {
-        // channels past the end multiply zeros: the last one's weights stand in for theirs
-        const T* wk = W + (int64_t(weight_k(k_n)) * cin + (AM == A_VEC ? kk_n * SLAB : 0)) * cout;  // uniform
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-          const unsigned col = min((slab * NB + nb) * 32 + lr, cout - 1);  // (columns past the end are not stored)
-#pragma unroll
-          for (int j = 0; j < LPC; ++j) {
-            if constexpr (AM == A_VEC) bv[S][nb][j] = (wk + j * cout)[unsigned(LPC * lh * cout) + col];
-            else bv[S][nb][j] = wk[unsigned(min(c0 + j, cin - 1) * cout) + col];
-          }
-        }
-      }
-      if (++kk_n == KK) {
-        kk_n = 0;
-        i_n = min(i_n + 1, n_i);
-        k_n = __builtin_amdgcn_readfirstlane(static_cast<int>(kl[i_n]));
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) idx_n[rb] = sIdx[(idx_row(i_n, k_n) * RB + rb) * 32 + lr];
-      }
-    };
-    static_for<D>([&](auto S_) { issue(S_); });
-    for (int e0 = 0; e0 < n_entries; e0 += D) {
-      static_for<D>([&](auto S_) {
-        constexpr int S = decltype(S_)::value;
-        if (e0 + S < n_entries) {
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) acc[rb][nb] = Mfma<T>::mma(av[S][rb], bv[S][nb], acc[rb][nb]);
-        }
-        issue(S_);
-      });
-    }
+    __builtin_amdgcn_wave_barrier();
   }
 
-  // The four partial sums meet in LDS (the index area is dead by now).  Value (rb, nb, r, lane) of an area sits at float
-  // (((rb*NB + nb)*4 + r/4)*64 + lane)*4 + r%4, so a lane moves four registers per access.
-  constexpr int AREAS = splitk_areas(NB, RB), AREA = RB * NB * 1024;
-  auto area = [&](int w) { return reinterpret_cast<float4*>(smem) + w * (AREA / 4) + lane; };
-  auto put = [&](float4* p, bool add) {
+  floatx16 acc[NB];
 #pragma unroll
-    for (int i = 0; i < RB * NB * 4; ++i) {
-      const floatx16& v = acc[i / 4 / NB][i / 4 % NB];
-      const int q = i % 4;
-      float4 t = {v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
-      if (add) {
-        const float4 u = p[i * 64];
-        t.x += u.x;
-        t.y += u.y;
-        t.z += u.z;
-        t.w += u.w;
+  for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[nb][r] = 0.f;
+
+  // offsets i_lo .. i_hi - 1 of this wave: their rows' positions into LDS
+  auto fetch_rows = [&](int i_lo, int n) {
+    if constexpr (FROM == MATRIX) {  // eight offsets per pass: lane -> (offset, 4 rows)
+      const int part = lane & 7;
+      for (int p = lane >> 3; p < n; p += 8)
+        *reinterpret_cast<intx4*>(sIdx + p * 32 + part * 4) =
+            row_pos4(*(const SPC_GLOBAL intx4*)(M + (int64_t(blk) * K3 + kl[i_lo + p]) * 32 + part * 4));
+    } else if constexpr (FROM == LISTS) {
+      // two offsets per pass (a half-wave each, lane = row or pair), four passes' loads in flight together: every lane loads,
+      // from the start of the arrays where it has nothing to load
+      for (int p0 = 0; p0 < n; p0 += 8) {
+        int row[4], val[4], num[4], m[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int p = p0 + 2 * u + lh, e = i_lo + min(p, n - 1), k = kl[e];
+          num[u] = p < n ? s_num[e] : 0;
+          const bool mirror = sym && k > kc;
+          const int64_t at = lr < num[u] ? int64_t(mirror ? K3 - 1 - k : k) * a.lists.stride + s_first[e] + lr : 0;
+          row[u] = (mirror ? l_in : l_out)[at];
+          val[u] = (mirror ? l_out : l_in)[at];
+          m[u] = blk * 32 + lr < n_out ? blk * 32 + lr : -1;
+          if (has_os) m[u] = num[u] == -2 ? m[u] : M[(int64_t(blk) * K3 + (num[u] == -1 ? k : 0)) * 32 + lr];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          SPC_PIN_LOADED(row[u]);
+          SPC_PIN_LOADED(val[u]);
+          SPC_PIN_LOADED(m[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (p0 + 2 * u + lh < n) sIdx[(p0 + 2 * u + lh) * 32 + lr] = row_pos(num[u] < 0 ? m[u] : -1);
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (lr < num[u]) sIdx[(p0 + 2 * u + lh) * 32 + (row[u] & 31)] = row_pos(val[u]);
       }
-      p[i * 64] = t;
     }
+    if constexpr (FROM != MATRIX_SMALL)
+      for (int q = lane; q < TAIL * 32; q += 64) sIdx[n * 32 + q] = row_pos(-1);
+    __builtin_amdgcn_wave_barrier();
   };
-  __syncthreads();
-  if constexpr (AREAS == 4) {
-    put(area(wave), false);
-  } else {
-    if (wave >= 2) put(area(wave - 2), false);
-    __syncthreads();
-    if (wave < 2) put(area(wave), true);
+  auto weight_k = [&](int k) { return FROM == MATRIX_SMALL ? min(k, K3 - 1) : k; };
+
+  if (n_i > 0) {
+  int i_lo = 0;
+  do {
+    const int n = FROM == MATRIX_SMALL ? n_i : min(n_i - i_lo, SPLITK_CHUNK);
+    if (i_lo > 0) __builtin_amdgcn_wave_barrier();  // (the rows of the chunk before have been read)
+    fetch_rows(i_lo, n);
+    const int kv = kl[i_lo + min(lane, n + TAIL - 1)];  // lane i: the chunk's i-th offset
+    if constexpr (AM == A_QUAD) {
+      // entry e = offsets 4e .. 4e+3 of this wave: lanes of the lower half hold four channels of each of the first two,
+      // lanes of the upper half of the last two
+      using V4 = T __attribute__((ext_vector_type(4)));
+      constexpr int D = 2;
+      V av[D];
+      V bv[D][NB];
+      const int n_entries = (n + 3) / 4;
+      int e_n = 0;
+      auto issue = [&](auto S_) {
+        constexpr int S = decltype(S_)::value;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int q = min(4 * e_n + 2 * lh + h, n);  // past the end: no rows
+          const int kq = __shfl(kv, q, 64);
+          const int kr = FROM == MATRIX_SMALL ? kq : q, k = weight_k(kq);
+          const V4 f = __builtin_bit_cast(V4, __builtin_amdgcn_raw_buffer_load_b64(rows_rsrc, sIdx[kr * 32 + lr], 0, 0));
+#pragma unroll
+          for (int j = 0; j < 4; ++j) av[S][4 * h + j] = f[j];
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) {
+            if constexpr (PACKED) {
+              const V4 w = *reinterpret_cast<const V4*>(W + ((int64_t(k) * nb_total + slab * NB + nb) * 64 + lr) * 8);
+#pragma unroll
+              for (int j = 0; j < 4; ++j) bv[S][nb][4 * h + j] = w[j];
+            } else {
+              const T* w = W + int64_t(k) * 4 * cout + min((slab * NB + nb) * 32 + lr, cout - 1);
+#pragma unroll
+              for (int j = 0; j < 4; ++j) bv[S][nb][4 * h + j] = w[j * cout];
+            }
+          }
+        }
+        ++e_n;
+      };
+      static_for<D>([&](auto S_) { issue(S_); });
+      for (int e0 = 0; e0 < n_entries; e0 += D) {
+        static_for<D>([&](auto S_) {
+          constexpr int S = decltype(S_)::value;
+          if (e0 + S < n_entries) {
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) acc[nb] = Mfma<T>::mma(av[S], bv[S][nb], acc[nb]);
+          }
+          issue(S_);
+        });
+      }
+    } else {
+      // entry = (offset, group g of slabs of channels), g fastest: two slabs (64 bytes) where rows pass through LDS, else one
+      constexpr int GS = STAGED ? 2 : 1, D = STAGED ? 1 : 2;
+      const int KG = (KK + GS - 1) / GS;
+      // what a lane gathers: a piece (16 bytes) of rows lane_row and 16 + lane_row, or what it multiplies, half a slab of row lr
+      const int lane_row = STAGED ? lane >> 2 : lr, lane_piece = STAGED ? lane & 3 : lh;
+      V* put_at = stage + lane_row * 4 + (lane_piece ^ ((lane_row >> 1) & 3));
+      const V* get_at[2] = {stage + lr * 4 + (lh ^ ((lr >> 1) & 3)), stage + lr * 4 + ((2 + lh) ^ ((lr >> 1) & 3))};
+      const unsigned piece_off = lane_piece * 16, lane_off = lane * 16;
+      // pieces behind the last channel (of the last group): beyond what the loads may reach
+      const unsigned past = ((KG - 1) * 2 * GS + lane_piece) * LPC >= cin ? MAX_OFFSET : 0u;
+      const T* zero_row = reinterpret_cast<const T*>(g_zero_row);
+      V av[D][GS];
+      V bv[D][GS][NB];
+      int i_n = 0, g_n = 0, g_c = 0;
+      int k_n = __builtin_amdgcn_readlane(kv, 0);
+      int pos_n[GS];
+      auto next_rows = [&]() {
+        const int32_t* p = sIdx + (FROM == MATRIX_SMALL ? k_n : i_n) * 32 + lane_row;
+#pragma unroll
+        for (int u = 0; u < GS; ++u) pos_n[u] = p[u * 16];
+      };
+      auto issue_rows = [&](auto E_) {
+        constexpr int E = decltype(E_)::value;
+#pragma unroll
+        for (int u = 0; u < GS; ++u) {
+          if constexpr (OFFSETS) {
+            unsigned off = pos_n[u] + piece_off;
+            if (g_n == KG - 1) off |= past;
+            av[E][u] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(rows_rsrc, off, g_n * (GS * 32), 0));
+          } else {
+            const int c0 = (g_n * (2 * GS) + lane_piece) * LPC;
+            const T* src = F + int64_t(pos_n[u]) * ld_in + c0;
+            if constexpr (AM == A_ELEM) {
+#pragma unroll
+              for (int j = 0; j < LPC; ++j) av[E][u][j] = *(pos_n[u] < 0 || c0 + j >= cin ? zero_row : src + j);
+            } else {
+              av[E][u] = *reinterpret_cast<const V*>(pos_n[u] < 0 || c0 >= cin ? zero_row : src);
+            }
+          }
+        }
+      };
+      auto issue_weights = [&](auto E_, auto S_) {  // slab S of group g_n of offset k_n
+        constexpr int E = decltype(E_)::value, S = decltype(S_)::value;
+        const int kk = min(GS * g_n + S, KK - 1), k = weight_k(k_n);
+        if constexpr (PACKED && AM != A_WIDE) {
+          const unsigned w = ((unsigned(k) * KK + kk) * nb_total + slab * NB) * 1024u;  // uniform
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) bv[E][S][nb] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, lane_off + nb * 1024, w, 0));
+        } else if constexpr (PACKED) {
+          const V* w = reinterpret_cast<const V*>(W) + ((int64_t(k) * KK + kk) * nb_total + slab * NB) * 64 + lane;
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) bv[E][S][nb] = w[nb * 64];
+        } else {
+          // (columns past the end are not stored)
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) {
+            const unsigned col = min((slab * NB + nb) * 32 + lr, cout - 1);
+            if constexpr (AM == A_VEC) {
+              const T* wk = W + (int64_t(k) * cin + kk * SLAB) * cout;  // uniform
+#pragma unroll
+              for (int j = 0; j < LPC; ++j) bv[E][S][nb][j] = (wk + j * cout)[unsigned(LPC * lh * cout) + col];
+            } else if constexpr (AM != A_WIDE) {
+              // channels past the end multiply zeros: what follows in memory stands in for theirs
+              const unsigned at = (lh * LPC * unsigned(cout) + col) * sizeof(T);
+#pragma unroll
+              for (int j = 0; j < LPC; ++j) {
+                const unsigned w = (unsigned(k) * cin + kk * SLAB + j) * cout * sizeof(T);  // uniform
+                if constexpr (sizeof(T) == 2) bv[E][S][nb][j] = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b16(w_rsrc, at + w, 0, 0));
+                else bv[E][S][nb][j] = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(w_rsrc, at + w, 0, 0));
+              }
+            } else {  // (the last one's weights)
+#pragma unroll
+              for (int j = 0; j < LPC; ++j) bv[E][S][nb][j] = W[(int64_t(k) * cin + min(kk * SLAB + lh * LPC + j, cin - 1)) * cout + col];
+            }
+          }
+        }
+      };
+      auto advance = [&]() {
+        if (++g_n == KG) {
+          g_n = 0;
+          i_n = min(i_n + 1, n);  // (after the last one: the all-invalid row behind it)
+          k_n = __builtin_amdgcn_readlane(kv, i_n);
+          next_rows();
+        }
+      };
+      next_rows();
+      static_for<D>([&](auto E_) {
+        if (decltype(E_)::value > 0) advance();
+        issue_rows(E_);
+        static_for<GS>([&](auto S_) { issue_weights(E_, S_); });
+      });
+      for (int left = n * KG; left > 0; left -= D) {
+        static_for<D>([&](auto E_) {
+          constexpr int E = decltype(E_)::value;
+          if (E > 0 && left <= E) return;
+          V a_now[GS];
+          if constexpr (STAGED) {
+            put_at[0] = av[E][0];
+            put_at[64] = av[E][1];
+            advance();
+            issue_rows(E_);
+            __builtin_amdgcn_wave_barrier();
+            a_now[0] = *get_at[0];
+            a_now[1] = *get_at[1];
+            __builtin_amdgcn_wave_barrier();
+          } else {
+            a_now[0] = av[E][0];
+          }
+          static_for<GS>([&](auto S_) {
+            constexpr int S = decltype(S_)::value;
+            if (S == 0 || GS * g_c + S < KK) {  // (uniform)
+#pragma unroll
+              for (int nb = 0; nb < NB; ++nb) acc[nb] = Mfma<T>::mma(a_now[S], bv[E][S][nb], acc[nb]);
+            }
+            if constexpr (!STAGED) {
+              advance();
+              issue_rows(E_);
+            }
+            issue_weights(E_, S_);
+          });
+          if (++g_c == KG) g_c = 0;
+        });
+      }
+    }
+    i_lo += SPLITK_CHUNK;
+  } while (FROM != MATRIX_SMALL && i_lo < n_i);
   }
-  __syncthreads();
-  auto total = [&](int e) {
-    const float* r = reinterpret_cast<const float*>(smem);
-    float v = r[e] + r[AREA + e];
-    if constexpr (AREAS == 4) v += r[2 * AREA + e] + r[3 * AREA + e];
-    return v;
+
+  // ---- sums and stores (the index area is dead by now)
+  const float least = a.relu ? 0.f : -__builtin_inff();
+  // N consecutive channels of a row, from column c of the slab on
+  auto store = [&](auto N_, int i, int c, const float* v) {
+    constexpr int N = decltype(N_)::value;
+    constexpr int P = N * sizeof(T) >= 16 ? LPC : N;  // channels per store
+    if (i >= n_out) return;
+    T* dst = out + i * ld_out + slab * (NB * 32) + c;
+#pragma unroll
+    for (int p = 0; p < N; p += P) {
+      const int oc = slab * (NB * 32) + c + p;
+      if (oc >= cout) break;
+      __align__(16) T o[P];
+#pragma unroll
+      for (int j = 0; j < P; ++j) {
+        o[j] = from_f32<T>(v[p + j] < least ? least : v[p + j]);  // (NaN stays and is computed again at the end)
+        z = fmaf(v[p + j], 0.f, z);
+      }
+      if (a.vec_store) {  // (cout is a multiple of P then)
+        if constexpr (P * sizeof(T) == 16) *reinterpret_cast<uint4*>(dst + p) = *reinterpret_cast<const uint4*>(o);
+        else *reinterpret_cast<uint2*>(dst + p) = *reinterpret_cast<const uint2*>(o);
+      } else {
+#pragma unroll
+        for (int j = 0; j < P; ++j)
+          if (oc + j < cout) dst[p + j] = o[j];
+      }
+    }
   };
   // D layout of the 32x32 MFMA: register r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l%32.
-  // Thread t stores EPT consecutive channels of row t/8 of every block.
-  constexpr int EPT = NB * 4;
-  bool summed = false;  // area 0 holds the total
-  if (SHARED && log_waves > 2) {
-    // This workgroup's part of the sum goes to memory; whoever finds all other parts there adds them up, in the order
-    // of the parts whoever it is.  Nobody waits.  Parts travel between XCDs, whose L2s are not coherent: they are
-    // stored and loaded at device scope, and a part is announced once its stores have completed.
-    constexpr int PART = NB * 1024;
-    const int parts = gridDim.z;
-    const int64_t slot = int64_t(blockIdx.x) * gridDim.y + slab;
-    using Pair = unsigned long long;  // two sums per access
-    constexpr int PER = PART / 2 / (64 * SPLITK_WAVES);
-    Pair* part0 = reinterpret_cast<Pair*>(a.partial) + slot * parts * (PART / 2) + tid;
+  if (log_share == 0) {
+    // The wave has its tile to itself: 32 columns at a time through LDS of its own
+    constexpr int P1 = splitk_pitch(1);
+    float* area = reinterpret_cast<float*>(tile_mem);
+    __builtin_amdgcn_wave_barrier();
+    static_for<NB>([&](auto NB_) {
+      constexpr int nb = decltype(NB_)::value;
 #pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      const int at = (tid + e * 256) * 2;
-      const Pair both = (static_cast<Pair>(__float_as_uint(total(at + 1))) << 32) | __float_as_uint(total(at));
-      __hip_atomic_store(part0 + blockIdx.z * (PART / 2) + e * 256, both, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    int* s_last = reinterpret_cast<int*>(smem) + AREAS * AREA;
-    if (tid == 0) *s_last = __hip_atomic_fetch_add(a.arrived + slot, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1;
-    __syncthreads();
-    if (!*s_last) return;
-    if (tid == 0) __hip_atomic_store(a.arrived + slot, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
-    float2 v[PER];
+      for (int r = 0; r < 16; ++r) area[(8 * (r / 4) + 4 * lh + r % 4) * P1 + lr] = acc[nb][r];
+      __builtin_amdgcn_wave_barrier();
+      const float4* src = reinterpret_cast<const float4*>(area + (lane >> 1) * P1 + (lane & 1) * 16);
+      float4 v[4];
 #pragma unroll
-    for (int e = 0; e < PER; ++e) v[e] = make_float2(0.f, 0.f);
-    for (int q = 0; q < parts; q += 2) {  // (an even number)
-      Pair t[2][PER];
+      for (int q = 0; q < 4; ++q) v[q] = src[q];
+      __builtin_amdgcn_wave_barrier();
+      store(std::integral_constant<int, 16>{}, blk * 32 + (lane >> 1), nb * 32 + (lane & 1) * 16, reinterpret_cast<const float*>(v));
+    });
+  }
+  else {
+    constexpr int AREAS = splitk_areas(NB), AREA = 32 * PITCH, EPT = NB * 4;
+    float* const sums = reinterpret_cast<float*>(smem);
+    auto put = [&](float* area, bool add) {
+      float* p = area + 4 * lh * PITCH + lr;
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
+      for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int e = 0; e < PER; ++e)
-          t[h][e] = __hip_atomic_load(part0 + (q + h) * (PART / 2) + e * 256, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int e = 0; e < PER; ++e) {
-          v[e].x += __uint_as_float(static_cast<unsigned>(t[h][e]));
-          v[e].y += __uint_as_float(static_cast<unsigned>(t[h][e] >> 32));
+        for (int r = 0; r < 16; ++r) {
+          float* at = p + (8 * (r / 4) + r % 4) * PITCH + nb * 32;
+          *at = add ? *at + acc[nb][r] : acc[nb][r];
         }
-    }
-#pragma unroll
-    for (int e = 0; e < PER; ++e) reinterpret_cast<float2*>(smem)[tid + e * 256] = v[e];
-    summed = true;
+    };
     __syncthreads();
-  }
-  const int row = tid >> 3, c0 = (tid & 7) * EPT;
-  const int nb = c0 >> 5, cc = c0 & 31;
-  const int q = row >> 3, h = (row & 7) >> 2, rr = row & 3;
-  const int oc = slab * (NB * 32) + c0;  // first output channel
-  const float least = a.relu ? 0.f : -__builtin_inff();
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    const int64_t i = (blk0 + rb) * 32 + row;
-    const int at = ((((rb * NB + nb) * 4 + q) * 64) + h * 32 + cc) * 4 + rr;
-    if (i < n_out && oc < cout) {
-      __align__(16) T o[EPT];
-#pragma unroll
-      for (int j = 0; j < EPT; ++j) {
-        const float v = SHARED && summed ? reinterpret_cast<const float*>(smem)[at + 4 * j] : total(at + 4 * j);
-        o[j] = from_f32<T>(v < least ? least : v);  // (NaN stays and is computed again at the end)
-        z = fmaf(v, 0.f, z);
-      }
-      T* dst = out + i * ld_out + oc;
-      if (a.vec_store) {  // (cout is a multiple of EPT then)
-        if constexpr (EPT * sizeof(T) >= 16) {
-#pragma unroll
-          for (int j = 0; j < int(EPT * sizeof(T)) / 16; ++j) reinterpret_cast<uint4*>(dst)[j] = reinterpret_cast<const uint4*>(o)[j];
-        } else {
-          *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<const uint2*>(o);
-        }
-      } else {
-#pragma unroll
-        for (int j = 0; j < EPT; ++j)
-          if (oc + j < cout) dst[j] = o[j];
-      }
+    if constexpr (AREAS == 4) {
+      put(sums + wave * AREA, false);
+    } else if (log_share == 2) {
+      if (wave >= 2) put(sums + (wave - 2) * AREA, false);
+      __syncthreads();
+      if (wave < 2) put(sums + wave * AREA, true);
+    } else {
+      if (member == 1) put(sums + tile * AREA, false);
+      __syncthreads();
+      if (member == 0) put(sums + tile * AREA, true);
     }
+    __syncthreads();
+    // N consecutive sums of tile s
+    auto total = [&](auto N_, int s, int row, int col, float* v) {
+      constexpr int N = decltype(N_)::value;
+      using VN = float __attribute__((ext_vector_type(N)));
+      const float* p = sums + row * PITCH + col + (AREAS == 4 ? s << log_share : log_share == 2 ? 0 : s) * AREA;
+      VN t = *reinterpret_cast<const VN*>(p);
+      if (AREAS == 4 || log_share == 2) t += *reinterpret_cast<const VN*>(p + AREA);
+      if (AREAS == 4 && log_share == 2) t += *reinterpret_cast<const VN*>(p + 2 * AREA) + *reinterpret_cast<const VN*>(p + 3 * AREA);
+#pragma unroll
+      for (int j = 0; j < N; ++j) v[j] = t[j];
+    };
+    bool summed = false;  // area 0 holds the total
+    if (SHARED && log_waves > log_share) {
+      // This workgroup's part of the sum goes to memory; whoever finds all other parts there adds them up, in the order
+      // of the parts whoever it is.  Nobody waits.  Parts travel between XCDs, whose L2s are not coherent: they are
+      // stored and loaded at device scope, and a part is announced once its stores have completed.
+      constexpr int PART = NB * 1024;
+      const int parts = gridDim.z;
+      const int64_t slot = int64_t(blockIdx.x) * gridDim.y + slab;
+      using Pair = unsigned long long;  // two sums per access
+      constexpr int PER = PART / 2 / (64 * SPLITK_WAVES);
+      Pair* part0 = reinterpret_cast<Pair*>(a.partial) + slot * parts * (PART / 2) + tid;
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        const int at = (tid + e * 256) * 2;
+        float t[2];
+        total(std::integral_constant<int, 2>{}, 0, at / (NB * 32), at % (NB * 32), t);
+        const Pair both = (static_cast<Pair>(__float_as_uint(t[1])) << 32) | __float_as_uint(t[0]);
+        __hip_atomic_store(part0 + blockIdx.z * (PART / 2) + e * 256, both, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      int* s_last = reinterpret_cast<int*>(sums + AREAS * AREA);
+      if (tid == 0) *s_last = __hip_atomic_fetch_add(a.arrived + slot, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1;
+      __syncthreads();
+      if (!*s_last) return;
+      if (tid == 0) __hip_atomic_store(a.arrived + slot, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
+      float2 v[PER];
+#pragma unroll
+      for (int e = 0; e < PER; ++e) v[e] = make_float2(0.f, 0.f);
+      for (int q = 0; q < parts; q += 2) {  // (an even number)
+        Pair t[2][PER];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int e = 0; e < PER; ++e)
+            t[h][e] = __hip_atomic_load(part0 + (q + h) * (PART / 2) + e * 256, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int e = 0; e < PER; ++e) {
+            v[e].x += __uint_as_float(static_cast<unsigned>(t[h][e]));
+            v[e].y += __uint_as_float(static_cast<unsigned>(t[h][e] >> 32));
+          }
+      }
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        const int at = (tid + e * 256) * 2;
+        *reinterpret_cast<float2*>(sums + at / (NB * 32) * PITCH + at % (NB * 32)) = v[e];
+      }
+      summed = true;
+      __syncthreads();
+    }
+    const int row = tid >> 3, c0 = (tid & 7) * EPT;
+    for (int s = 0; s < tiles; ++s) {
+      __align__(16) float v[EPT];
+#pragma unroll
+      for (int q = 0; q < NB; ++q) {
+        if (SHARED && summed) *reinterpret_cast<float4*>(v + 4 * q) = *reinterpret_cast<const float4*>(sums + row * PITCH + c0 + 4 * q);
+        else total(std::integral_constant<int, 4>{}, s, row, c0 + 4 * q, v + 4 * q);
+      }
+      store(std::integral_constant<int, EPT>{}, (first + s) * 32 + row, c0, v);
+    }
+    if constexpr (LOOP) __syncthreads();  // the LDS tile is reused as the next tile's index area
   }
-  if constexpr (LOOP) __syncthreads();  // the LDS tile is reused as the next tile's index area
-  log_waves = 2;  // only the first tile is shared (its slot is then free again); who finished it goes on alone
-  }
+  first += step;
+  again = true;
+  } while (LOOP && first * 32 < n_out);
   if (__ballot(z != z)) {
-    // the arguments are loaded anew: kept in scalar registers for this, they would not fit in the variants that loop
-    SplitkKernarg* again = (SplitkKernarg*)__builtin_amdgcn_kernarg_segment_ptr();
-    asm volatile("" : "+s"(again));
-    splitk_redo<T, NB, RB, LOOP, PACKED, FROM == LISTS>(again);
+    // (with the arguments loaded anew: kept in scalar registers for this, they would not fit)
+    SplitkKernarg* ap = (SplitkKernarg*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(ap));
+    splitk_redo<T, NB, LOOP, PACKED, FROM == LISTS>(ap);
   }
 }
 
@@ -1358,12 +1552,6 @@ static void launch_os_mfma(const ConvArgs& a, const T* Wp) {
   else go(std::integral_constant<int, 1>{});
 }
 
-static size_t splitk_lds_bytes(int K3, int NB, int RB, int AM, int from) {
-  const size_t idx = size_t(from == MATRIX_SMALL ? 1 : SPLITK_WAVES) * splitk_idx_rows(K3, AM, from) * RB * 128 +
-                     size_t(SPLITK_WAVES) * SPLITK_KL_CAP * (from == LISTS ? 10 : 2);
-  return std::max(idx, size_t(splitk_areas(NB, RB)) * RB * NB * 4096 + 16);
-}
-
 // Whether the feature rows are as the vector loads and whole slabs of the split-k and phase kernels want them.
 template <typename T>
 static bool plain_rows(const ConvArgs& a) {
@@ -1397,18 +1585,30 @@ static bool splitk_wide(const ConvArgs& a) {
   return wide * 100 <= narrow * 62;
 }
 
-template <typename T, int NB, int RB, int AM, bool PACKED, int FROM>
-static void launch_splitk(const ConvArgs& a, const void* W) {
-  // entries in flight per wave: two.  Deeper rings cost the registers that hold more waves per SIMD, and the
-  // waves hide more latency than the ring does (25 layers of a UNet on 120 k voxels, all on this kernel: 403 us
-  // summed with 6-12 entries, 352 us with two or three, 391 us with one)
-  constexpr int D = 2;
+// Waves that share a tile (log2): four, or two where there are so many tiles that the waves are still enough, which then
+// spend less of their time on starting and on adding up.  us, four / two (/ one), 16-bit types: 3x3x3 32->32, LiDAR, 120 k voxels 16.3 / 16.6 /
+// 18.6, 160 k 20.2 / 20.0 / 22.8, 200 k 23.1 / 22.7, random 160 k 17.4 / 16.5, 200 k 21.0 / 18.6, 10^6 80 / 65 / 71; 4->32 (short
+// tiles) 30 k 5.6 / 5.6 / 6.6, 60 k 8.4 / 7.0 / 7.4, 120 k 13.1 / 10.3; 2x2x2 50 k output voxels 7.1 / 6.3 / 7.8, 19 k 5.9 / 6.1;
+// lists, 5x5x5, 240 k 53.3 / 51.0 / 57; matrix 5x5x5 38.8 / 39.6 / 48.  fp32 100 k 37.5 / 40.6.
+template <typename T>
+static int splitk_share(const ConvArgs& a, int AM, int FROM, int64_t n_blocks) {
+  if (a.splitk_rb) return a.splitk_rb == 1 ? 2 : 1;
+  if (sizeof(T) == 4 || FROM == MATRIX) return 2;
+  return n_blocks >= (AM == A_QUAD || a.m->K3 <= 8 ? 1280 : 4800) ? 1 : 2;
+}
+
+template <typename T, int NB, int AM, bool PACKED, int FROM, bool STAGED>
+static void launch_splitk(const ConvArgs& a) {
   SplitkArgs k{};
+  k.nb_total = (a.cout + 31) / 32;
+  // an estimated output count sizes the grid of the variant that walks tiles with a grid stride
+  const bool loop = a.rows_sel != a.rows_cap;
+  const int64_t n_blocks = std::max<int64_t>((a.rows_sel + 31) / 32, 1), tiles = n_blocks * (k.nb_total / NB);
   k.M = a.m->os_map;
   k.block_masks = a.m->block_masks;
   k.n_out_d = a.n_out_d;
   k.F = a.F;
-  k.W = W;
+  k.W = a.W;
   k.out = a.out;
   k.ld_in = a.ld_in;
   k.ld_out = a.ld_out;
@@ -1418,43 +1618,66 @@ static void launch_splitk(const ConvArgs& a, const void* W) {
   k.cin = a.cin;
   k.cout = a.cout;
   k.relu = a.relu;
-  k.nb_total = (a.cout + 31) / 32;
+  k.row_bytes = static_cast<uint32_t>(a.ld_in * sizeof(T));
+  k.w_bytes = static_cast<uint32_t>(PACKED ? MAX_OFFSET : int64_t(k.K3) * a.cin * a.cout * int64_t(sizeof(T)));  // (read where it fits)
   k.os_mask = a.os_mask;
-  constexpr int EPT = NB * 4;
-  constexpr int store = EPT * sizeof(T) < 16 ? EPT * sizeof(T) : 16;  // bytes per store
-  k.vec_store = a.cout % EPT == 0 && a.ld_out * sizeof(T) % store == 0 && reinterpret_cast<uintptr_t>(a.out) % store == 0;
+  k.has_os = a.any_os ? 1 : 0;
   if (FROM == LISTS) k.lists = ListArgs{a.m->ws_in, a.m->ws_out, a.m->list_base, a.m->list_base_in, a.m->ws_stride, a.m->sym ? 1 : 0, a.ws_mask};
-  // an estimated output count sizes the grid of the variant that walks tiles with a grid stride
-  const bool loop = a.rows_sel != a.rows_cap;
-  const int64_t n_blocks = std::max<int64_t>((a.rows_sel + 31) / 32, 1);
-  const size_t lds = splitk_lds_bytes(a.m->K3, NB, RB, AM, FROM);
-  // once per instantiation: both variants may use all of a CU's LDS (large kernels need more than the default 64 KB)
-  static const hipError_t attr = [] {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_os_splitk_kernel<T, NB, RB, D, false, AM, PACKED, FROM>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    const hipError_t f = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_os_splitk_kernel<T, NB, RB, D, true, AM, PACKED, FROM>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    return e != hipSuccess ? e : f;
-  }();
-  (void)attr;
-  k.log_waves = 2;
   int parts = 1;
-  if (RB == 1 && AM == A_VEC && NB <= 2) {
-    const int64_t tiles = n_blocks * (k.nb_total / NB);
+  if (AM == A_VEC && NB <= 2 && a.splitk_rb != 2) {
     parts = splitk_parts<T>(a, tiles);
     if (parts > 1) {
       k.partial = static_cast<float*>(pool_alloc(size_t(tiles) * parts * NB * 4096, a.s));
       if (!k.partial) parts = 1;  // (not worth failing for)
       k.arrived = a.m->arrived;
     }
-    for (int q = parts; q > 1; q >>= 1) ++k.log_waves;
   }
-  const dim3 grid(static_cast<unsigned>((n_blocks + RB - 1) / RB), k.nb_total / NB, parts);
+  k.log_share = k.log_waves = parts > 1 ? 2 : splitk_share<T>(a, AM, FROM, n_blocks);
+  for (int q = parts; q > 1; q >>= 1) ++k.log_waves;
+  const int run = k.log_share == 0 ? 16 : NB * 4;  // consecutive channels that a thread stores
+  const int per_store = std::min<int>(run, 16 / sizeof(T));
+  k.vec_store = a.cout % per_store == 0 && a.ld_out % per_store == 0 && reinterpret_cast<uintptr_t>(a.out) % (per_store * sizeof(T)) == 0;
+  k.kl_cap = ((k.K3 + (1 << k.log_share) - 1) >> k.log_share) + splitk_tail(AM);
+  k.tile_lds = splitk_idx_bytes(k.K3, k.log_share, AM, FROM) + splitk_list_bytes(k.kl_cap, k.log_share, FROM) + (STAGED ? 2048 << k.log_share : 0);
+  const int tiles_wg = SPLITK_WAVES >> k.log_share;
+  size_t lds = 0;
+  if (k.log_share == 0) {
+    k.tile_lds = std::max(k.tile_lds, 32 * splitk_pitch(1) * 4);
+    lds = size_t(tiles_wg) * k.tile_lds;
+  } else {
+    lds = std::max(size_t(tiles_wg) * k.tile_lds, size_t(splitk_areas(NB)) * 32 * splitk_pitch(NB) * 4 + 16);
+  }
+  // once per instantiation: both variants may use all of a CU's LDS (lists of large kernels need more than the default 64 KB)
+  static const hipError_t attr = [] {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_os_splitk_kernel<T, NB, false, AM, PACKED, FROM, STAGED>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    const hipError_t f = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_os_splitk_kernel<T, NB, true, AM, PACKED, FROM, STAGED>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    return e != hipSuccess ? e : f;
+  }();
+  (void)attr;
+  const dim3 grid(static_cast<unsigned>((n_blocks + tiles_wg - 1) / tiles_wg), k.nb_total / NB, parts);
   if (loop)
-    hipLaunchKernelGGL((conv_os_splitk_kernel<T, NB, RB, D, true, AM, PACKED, FROM>), grid, dim3(64 * SPLITK_WAVES), lds, a.s, k);
+    hipLaunchKernelGGL((conv_os_splitk_kernel<T, NB, true, AM, PACKED, FROM, STAGED>), grid, dim3(64 * SPLITK_WAVES), lds, a.s, k);
   else
-    hipLaunchKernelGGL((conv_os_splitk_kernel<T, NB, RB, D, false, AM, PACKED, FROM>), grid, dim3(64 * SPLITK_WAVES), lds, a.s, k);
+    hipLaunchKernelGGL((conv_os_splitk_kernel<T, NB, false, AM, PACKED, FROM, STAGED>), grid, dim3(64 * SPLITK_WAVES), lds, a.s, k);
   pool_free(k.partial, a.s);  // reuse is ordered behind this stream's work
+}
+
+// Whether gathered rows pass through LDS.  Where most cells of a block are empty (large kernels, and the lists of random
+// scenes) the lanes without a row cost the memory path little, and the way through LDS is a detour: us, direct / through LDS,
+// indoor scans 240 k voxels 5x5x5 38.8 / 40.5, hybrid 52 / 57, lists of 200 k random voxels 32->64 33.1 / 36.5; LiDAR, 120 k voxels, 32->32
+// matrix 17.9 / 16.5, 64->32 27.7 / 23.2.  Plain weights of 16-bit types are bound by their own loads: 50 k voxels 32->32 12.1 / 13.3.
+// Small fp32 layers by the chain of dependent steps: 2118 voxels 16->16 6.9 / 7.3, but 50 k 32->32 27.9 / 25.6.
+template <typename T, int NB, int AM, bool PACKED, int FROM>
+static void launch_splitk(const ConvArgs& a) {
+  if constexpr (AM != A_QUAD && FROM == MATRIX_SMALL && (PACKED || sizeof(T) == 4)) {
+    if (PACKED || (AM != A_ELEM && a.rows_sel >= 16384)) {
+      launch_splitk<T, NB, AM, PACKED, FROM, true>(a);
+      return;
+    }
+  }
+  if constexpr (!(PACKED && AM != A_QUAD && FROM == MATRIX_SMALL)) launch_splitk<T, NB, AM, PACKED, FROM, false>(a);
 }
 
 // Split-k kernel in the form that the layer's rows, weights and offsets need.
@@ -1464,86 +1687,71 @@ static void launch_os_splitk(const ConvArgs& a) {
   using Yes = std::true_type;
   using No = std::false_type;
   const bool aligned = a.ld_in % LPC == 0 && reinterpret_cast<uintptr_t>(a.F) % 16 == 0;
-  const bool quad = sizeof(T) == 2 && a.cin == 4 && a.ld_in % 4 == 0 && reinterpret_cast<uintptr_t>(a.F) % 8 == 0;
-  const bool small = a.m->K3 <= 32;
-  auto columns = [&](auto NB_) {
-    constexpr int NB = decltype(NB_)::value;
-    auto rows = [&](auto PACKED_, auto FROM_) {
-      constexpr bool PACKED = decltype(PACKED_)::value;
-      constexpr int FROM = decltype(FROM_)::value;
-      if (quad) {
-        if constexpr (sizeof(T) == 2) launch_splitk<T, NB, 1, A_QUAD, PACKED, FROM>(a, a.W);
-      } else if (!aligned || a.cin % LPC != 0) {
-        launch_splitk<T, NB, 1, A_ELEM, PACKED, FROM>(a, a.W);
-      } else if (a.cin % (2 * LPC) != 0) {
-        launch_splitk<T, NB, 1, A_RAGGED, PACKED, FROM>(a, a.W);
-      } else {
-        // Row blocks per workgroup: two blocks share each weight fragment read (less L2 traffic) but leave fewer
-        // workgroups and cost registers; one measured faster at every size (120 k voxels 64->64: 37.4 vs 39.1 us; 240 k
-        // voxels 5x5x5 32->32: 37.7 vs 47.7), so two is only taken on request.
-        if constexpr (PACKED && FROM != LISTS) {
-          if (a.splitk_rb == 2 && splitk_lds_bytes(a.m->K3, NB, 2, A_VEC, MATRIX) <= 80 * 1024) {
-            launch_splitk<T, NB, 2, A_VEC, true, MATRIX>(a, a.W);
-            return;
-          }
-        }
-        launch_splitk<T, NB, 1, A_VEC, PACKED, FROM>(a, a.W);
-      }
-    };
-    auto from = [&](auto PACKED_) {
-      if (a.any_ws) rows(PACKED_, std::integral_constant<int, LISTS>{});
-      else if (small) rows(PACKED_, std::integral_constant<int, MATRIX_SMALL>{});
-      else rows(PACKED_, std::integral_constant<int, MATRIX>{});
-    };
-    if constexpr (sizeof(T) == 2) {
-      if (a.packed) {
-        from(Yes{});
-        return;
-      }
-    }
-    from(No{});
-  };
   const int nb_total = (a.cout + 31) / 32;
+  const bool wide = wide_rows<T>(a) || int64_t(a.m->K3) * ((a.cin + 2 * LPC - 1) / (2 * LPC)) * nb_total * 1024 > int64_t(MAX_OFFSET);
+  const bool quad = sizeof(T) == 2 && a.cin == 4 && a.ld_in % 4 == 0 && reinterpret_cast<uintptr_t>(a.F) % 8 == 0 && !wide;
+  auto form = [&](auto NB_, auto PACKED_, auto FROM_) {
+    constexpr int NB = decltype(NB_)::value, FROM = decltype(FROM_)::value;
+    constexpr bool PACKED = decltype(PACKED_)::value;
+    if constexpr (NB == 4) {  // (see below)
+      launch_splitk<T, NB, A_VEC, PACKED, FROM>(a);
+    } else if (quad) {
+      if constexpr (sizeof(T) == 2) launch_splitk<T, NB, A_QUAD, PACKED, FROM>(a);
+    } else if (!aligned || a.cin % LPC != 0) {
+      launch_splitk<T, NB, A_ELEM, PACKED, FROM>(a);
+    } else if (wide) {
+      launch_splitk<T, NB, A_WIDE, PACKED, FROM>(a);
+    } else if (a.cin % (2 * LPC) != 0) {
+      launch_splitk<T, NB, A_RAGGED, PACKED, FROM>(a);
+    } else {
+      launch_splitk<T, NB, A_VEC, PACKED, FROM>(a);
+    }
+  };
+  auto from = [&](auto NB_, auto PACKED_) {
+    if (a.any_ws) form(NB_, PACKED_, std::integral_constant<int, LISTS>{});
+    else if (a.m->K3 <= 32) form(NB_, PACKED_, std::integral_constant<int, MATRIX_SMALL>{});
+    else form(NB_, PACKED_, std::integral_constant<int, MATRIX>{});
+  };
+  auto columns = [&](auto PACKED_) {
+    if (nb_total % 2 == 0) from(std::integral_constant<int, 2>{}, PACKED_);
+    else from(std::integral_constant<int, 1>{}, PACKED_);
+  };
   if constexpr (sizeof(T) == 2) {
-    if (a.packed && plain_rows<T>(a) && a.splitk_rb == 0 && splitk_wide(a) && splitk_parts<T>(a, (a.rows_sel + 31) / 32 * (a.cout / 64)) == 1) {
-      if (a.any_ws) launch_splitk<T, 4, 1, A_VEC, true, LISTS>(a, a.W);
-      else if (small) launch_splitk<T, 4, 1, A_VEC, true, MATRIX_SMALL>(a, a.W);
-      else launch_splitk<T, 4, 1, A_VEC, true, MATRIX>(a, a.W);
+    if (a.packed) {
+      if (plain_rows<T>(a) && !wide && a.splitk_rb == 0 && splitk_wide(a) && splitk_parts<T>(a, (a.rows_sel + 31) / 32 * (a.cout / 64)) == 1)
+        from(std::integral_constant<int, 4>{}, Yes{});
+      else columns(Yes{});
       return;
     }
   }
-  nb_total % 2 == 0 ? columns(std::integral_constant<int, 2>{}) : columns(std::integral_constant<int, 1>{});
+  columns(No{});
 }
 
-// Phase kernel or split-k kernel, measured on MI355X (3x3x3 layers, 32..256 channels, 6 k to 120 k voxels).  The phase
-// kernel stages every weight once per sixteen row blocks and wins where that matters: enough tiles for
-// 64 sixteen-wave workgroups (per slab of output channels; they are dealt to up to 256 workgroups, see
-// phase_wgs_per_xcd) and enough input channels behind every tile.  Below that the split-k kernel's many
-// short workgroups win in spite of their redundant weight reads: us, phase / split-k, 49 k voxels
-// 32->64 15.2 / 11.6, 64->64 19.4 / 19.1, 64->128 25.5 / 30.6; 18 k voxels 64->64 17.5 / 10.7; 120 k voxels 32->64
-// 20.6 / 22.9, 64->64 30.5 / 37.3.  With 32-column
-// slabs the split-k kernel wins or ties at every size measured (32->32: 120 k voxels 18.8 / 15.6, 10^6
-// voxels 118 / 80, 3 * 10^6 voxels 359 / 269; 64->32 at 120 k voxels 27.6 / 27.4).  Large kernels (5x5x5
-// and up) favour the split-k kernel at every size measured.
-// Layers the split-k kernel runs with 128-column slabs: the phase kernel (one workgroup of sixteen 64-column tiles per
-// CU) wins while one round of its workgroups holds the layer and leaves less than half of their waves idle: us, phase / split-k,
-// 60 k voxels 128->128 48.2 / 58.6, 35 k 37.1 / 39.4, 18 k 128->256 38.0 / 41.6; with fewer tiles 18 k 128->128 29.2 / 24.4;
-// with more, 35 k 256->256 168 / 120, 120 k 128->128 97 / 91, 256->256 336 / 317, 100 k random voxels 253 / 185.  (All of
-// this was measured where the phase kernel goes by phases; the host cannot see whether a level is one for its pooled way.)
+// Phase kernel or split-k kernel.  The phase kernel stages every weight once per sixteen row blocks, a workgroup per CU, so its
+// time goes by rounds of 256 workgroups of sixteen tiles (a row block and 64 columns), and it wins where they are well filled.
+// Below one round the split-k kernel's many short workgroups win in spite of their redundant weight reads.  us, phase / split-k,
+// 3x3x3, prepacked, LiDAR (n voxels, tiles):
+//   32->64    50 k 1563 12.5 / 11.8    70 k 2188 14.7 / 15.7   120 k 3750 18.5 / 22.4   150 k 4688 31.9 / 27.1
+//   64->64    35 k 1094 16.8 / 13.8    50 k 1563 17.8 / 17.5   120 k 3750 25.5 / 32.3   150 k 4688 42.4 / 39.1   180 k 5625 42.7 / 45.6
+//   64->128   20 k 1250 17.4 / 16.6    35 k 2188 20.4 / 22.8    50 k 3125 23.1 / 28.7    70 k 4375 40.9 / 35.8   100 k 6250 43.3 / 47.0
+//  128->128   35 k 2188 35.3 / 37.6    50 k 3125 39.3 / 47.3    70 k 4375 70.7 / 56.9   100 k 6250 76.1 / 74.0   120 k 7500 80.8 / 85.1
+//  256->256   20 k 2500 66.3 / 74.9    35 k 4375  135 /  106    50 k 6250  140 /  137    70 k 8750  204 /  180   120 k 15000 299 / 280
+// Many rounds are scenes of a million voxels and more, whose neighbourhoods are nearly empty (the pooled way): 64->64, 400 k random voxels
+// 49.3 / 65.0, 128->128 200 k 72.6 / 106, 400 k 127 / 193.
+// 32-column slabs (32->32: 120 k voxels 18.8 / 15.6, 10^6 118 / 80) and large kernels (5x5x5 and up) favour the split-k kernel.
 template <typename T>
 static bool prefer_splitk(const ConvArgs& a) {
-  const int64_t n_blocks = (a.rows_sel + 31) / 32;
-  const int n_slabs = a.cout % 64 == 0 ? a.cout / 64 : a.cout / 32;
-  const int64_t wgs = (n_blocks + 15) / 16 * n_slabs;
-  if (a.m->K3 > 64 || wgs < 64 || a.cout % 64 != 0) return true;
-  if (a.packed && plain_rows<T>(a) && a.cout % 128 == 0 && a.m->K3 >= 27) {
-    const int64_t tiles = n_blocks * n_slabs;
-    return tiles < 8 * 256 || tiles > 16 * 256;
+  if (a.m->K3 > 64 || a.cout % 64 != 0) return true;
+  const int64_t n_blocks = (a.rows_sel + 31) / 32, n_slabs = a.cout / 64, tiles = n_blocks * n_slabs;
+  const int64_t wgs = (n_blocks + 15) / 16 * n_slabs, rounds = (tiles + 4095) / 4096, room = rounds * 4096;
+  if (a.packed && plain_rows<T>(a) && a.cout % 128 == 0 && a.m->K3 >= 27) {  // (the split-k kernel takes 128 columns at a time)
+    if (tiles < 1750) return true;
+    if (rounds == 1) return false;
+    return a.cin > 128 || (rounds < 4 && tiles * 50 < room * 39);
   }
-  // a last round of phase workgroups that is far from full costs as much as a full one: us, phase / split-k, 64->64, 150 k
-  // voxels (1.14 rounds) 55 / 46, 300 k (2.3) 66 / 60, 400 k (3.05) 79 / 73; 200 k (1.53) 57 / 58
-  const int64_t tiles = n_blocks * n_slabs, room = (tiles + 4095) / 4096 * 4096;
-  return wgs * a.cin < 7000 || (tiles > 4096 && tiles * 5 < room * 4);
+  // (16->64, 37 k 9.0 / 9.8, 60 k 9.8 / 13.0, 120 k 14.2 / 20.9; 2x2x2 128->128, 24 k output voxels 13.5 / 13.7, 50 k 18.3 / 25.9)
+  const int64_t least = a.cin <= 16 ? 64 : a.cin <= 32 ? 120 : std::max(64, 7000 / a.cin);
+  return wgs < least || (rounds > 1 && tiles * 5 < room * 4);
 }
 
 // Shapes that take prepacked weights (16-bit types): any input channels (padded to a multiple of 16), output channels a

@@ -62,3 +62,53 @@ def test_phase_kernel_far_rows(cin):
     y = B.spc_conv_forward(km, _far_apart(F), W, flags=B.CONV_OS_PHASE)
     assert_close(y.cpu().to(torch.float64).numpy(), oracle.conv(M, F64, W64), TOL[torch.float16], cin)
     km.destroy()
+
+
+# SPC_CONV_SPLITK_RB: 32-row blocks per workgroup, one (four waves share a block) or two; 0: by size
+@pytest.mark.parametrize("n,density,K", [(1, 1.0, 3), (33, 0.5, 3), (4001, 0.3, 3), (2500, 0.6, 5)])
+@pytest.mark.parametrize("cin,cout", [(4, 32), (8, 32), (16, 64), (24, 40), (32, 32), (40, 64), (48, 96), (64, 64), (96, 32)])
+@pytest.mark.parametrize("rb", [0, 1, 2])
+def test_splitk_rows(n, density, K, cin, cout, rb):
+    km, M = _level(n, density, K, B.LAYOUT_BOTH)
+    for dtype in (torch.float16, torch.bfloat16, torch.float32):
+        F, F64, W, W64 = _tensors(n, K ** 3, cin, cout, dtype)
+        ref = oracle.conv(M, F64, W64)
+        flags = B.CONV_OS_SPLITK | rb << 8
+        runs = [(W, B.DATAFLOW_OS, flags), (W, B.DATAFLOW_WS, rb << 8)]
+        if dtype != torch.float32 and cout in (32, 64):
+            Wp = B.spc_conv_prepare_weights(W)
+            runs += [(Wp, B.DATAFLOW_OS, flags | B.CONV_PACKED_WEIGHTS), (Wp, B.DATAFLOW_WS, rb << 8 | B.CONV_PACKED_WEIGHTS)]
+        for w, df, fl in runs:
+            y = B.spc_conv_forward(km, F, w, df, fl)
+            assert_close(y.cpu().to(torch.float64).numpy(), ref, TOL[dtype], (dtype, df, fl))
+        y = B.spc_conv_forward(km, F, W, flags=rb << 8, hybrid_t=2)
+        assert_close(y.cpu().to(torch.float64).numpy(), ref, TOL[dtype], (dtype, "hybrid"))
+    km.destroy()
+
+
+@pytest.mark.parametrize("n,cin,cout", [(41_003, 4, 32), (153_701, 32, 32), (16_411, 32, 32)])
+def test_splitk_two_blocks_per_workgroup(n, cin, cout):
+    """Sizes from which a workgroup takes two blocks by itself (and, of fp32, those from which rows pass through LDS)."""
+    km, M = _level(n, 0.02, 3, B.LAYOUT_BOTH)
+    for dtype in (torch.float16, torch.float32):
+        F, F64, W, W64 = _tensors(n, 27, cin, cout, dtype)
+        ref = oracle.conv(M, F64, W64)
+        for df in (B.DATAFLOW_OS, B.DATAFLOW_WS):
+            y = B.spc_conv_forward(km, F, W, df)
+            assert_close(y.cpu().to(torch.float64).numpy(), ref, TOL[dtype], (dtype, df))
+    km.destroy()
+
+
+@pytest.mark.parametrize("dtype,cin,cout", [(torch.float16, 64, 64), (torch.float16, 24, 40), (torch.float16, 4, 32), (torch.float32, 32, 32)])
+def test_splitk_far_rows(dtype, cin, cout):
+    n = 3001
+    km, M = _level(n, 0.3, 3, B.LAYOUT_BOTH)
+    F, F64, W, W64 = _tensors(n, 27, cin, cout, dtype)
+    ref, far = oracle.conv(M, F64, W64), _far_apart(F)
+    runs = [(W, B.DATAFLOW_OS, B.CONV_OS_SPLITK), (W, B.DATAFLOW_WS, 0)]
+    if cout % 32 == 0 and dtype != torch.float32:
+        runs.append((B.spc_conv_prepare_weights(W), B.DATAFLOW_OS, B.CONV_OS_SPLITK | B.CONV_PACKED_WEIGHTS))
+    for w, df, fl in runs:
+        y = B.spc_conv_forward(km, far, w, df, fl)
+        assert_close(y.cpu().to(torch.float64).numpy(), ref, TOL[dtype], (df, fl))
+    km.destroy()
