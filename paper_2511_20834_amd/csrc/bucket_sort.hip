@@ -5,9 +5,10 @@
 //
 //   count    each workgroup produces its share of the keys (packing coordinates, Section 5.3,
 //            or masking the keys of a finer level, Section 5.5), histograms the top `fb` used
-//            key bits ("fine bins") in LDS and writes one row of the table [workgroup][bin];
-//   colscan  exclusive prefixes down the table's columns: where a workgroup's keys of a bin go
-//            inside the bin, and the bin totals;
+//            key bits ("fine bins") in LDS, adds its counts to the bins' totals in memory and keeps
+//            what it found there, its place inside the bins, in its row of a table;
+//   colscan  (large inputs only, where the additions would be too many: the count pass then writes
+//            the counts) exclusive prefixes down the table's columns, and the bins' totals;
 //   scatter  each workgroup scans the bin totals (where every bin starts) and moves its keys,
 //            with their source index, to their bin's range; the workgroups also write, for every
 //            64 scattered positions, the window of whole bins that covers them;
@@ -96,10 +97,12 @@ __device__ inline T* level_ws(T* p, size_t ws_pitch) {
 }
 
 // ---------------------------------------------------------------- count
-template <typename KeyT, typename Src, typename CountT>
+// ADD: the counts go to the bins' totals (zero before), in whatever order the workgroups come; 4096 bins and 30 workgroups with
+// keys in all of them take 1.7 us, fewer bins are hit the shorter a workgroup's share is.
+template <typename KeyT, typename Src, bool ADD>
 __global__ __launch_bounds__(BS_WIDE) void bs_count_kernel(const Src srcs, int64_t n, int per, int shift, int n_bin,
-                                                           KeyT* __restrict__ keys0, CountT* __restrict__ table,
-                                                           size_t ws_pitch) {
+                                                           KeyT* __restrict__ keys0, int32_t* __restrict__ table, size_t ws_pitch,
+                                                           int32_t* __restrict__ tot, size_t tot_pitch) {
   extern __shared__ int hist[];  // [n_bin]
   const auto src = srcs.level(blockIdx.y);
   using Level = std::remove_const_t<decltype(src)>;
@@ -129,17 +132,43 @@ __global__ __launch_bounds__(BS_WIDE) void bs_count_kernel(const Src srcs, int64
   }
   src.report(bad);
   __syncthreads();
-  for (int b = threadIdx.x; b < n_bin; b += BS_WIDE) table[int64_t(blockIdx.x) * n_bin + b] = static_cast<CountT>(hist[b]);
+  table += int64_t(blockIdx.x) * n_bin;
+  if constexpr (ADD) {
+    tot = level_ws(tot, tot_pitch);
+    for (int b0 = threadIdx.x; b0 < n_bin; b0 += 4 * BS_WIDE) {
+      int c[4], at[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) c[u] = b0 + u * BS_WIDE < n_bin ? hist[b0 + u * BS_WIDE] : 0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (c[u]) at[u] = __hip_atomic_fetch_add(tot + b0 + u * BS_WIDE, c[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (c[u]) table[b0 + u * BS_WIDE] = at[u];  // (the scatter pass uses the others as little)
+    }
+  } else {
+    for (int b = threadIdx.x; b < n_bin; b += BS_WIDE) table[b] = hist[b];
+  }
+}
+// Clears the totals (one row of the grid per level) where they are not kept cleared.
+__global__ __launch_bounds__(BS_THREADS) void bs_clear_kernel(int32_t* __restrict__ tot, int n_bin, size_t tot_pitch) {
+  const int b = blockIdx.x * BS_THREADS + threadIdx.x;
+  if (b < n_bin) level_ws(tot, tot_pitch)[b] = 0;
+}
+// The same by the last kernel of a sort, for the next one.
+__device__ inline void bs_clear_after(int32_t* tot, int n_bin) {
+  if (tot)
+    for (int b = blockIdx.x * blockDim.x + threadIdx.x; b < n_bin; b += gridDim.x * blockDim.x) tot[b] = 0;
 }
 
-// ---------------------------------------------------------------- column scan (tables too large for the scatter pass to sum)
+// ---------------------------------------------------------------- column scan (large inputs)
 // One thread per four bins: before[w][f] receives the number of keys of bin f held by workgroups
-// < w, tot[f] the bin's total.  The loads of 16 table rows are in flight together.
+// < w, tot[f] the bin's total.  The loads of 32 table rows are in flight together (16: 1 us more from 500 k keys on).
 constexpr int BS_COL_THREADS = 64;
 __global__ __launch_bounds__(BS_COL_THREADS) void bs_colscan_kernel(const int32_t* __restrict__ table,
                                                                     int32_t* __restrict__ before, int n_wg, int n_bin,
                                                                     int32_t* __restrict__ tot, size_t ws_pitch) {
-  constexpr int ROWS = 16;
+  constexpr int ROWS = 32;
   table = level_ws(table, ws_pitch);
   before = level_ws(before, ws_pitch);
   tot = level_ws(tot, ws_pitch);
@@ -167,22 +196,19 @@ __global__ __launch_bounds__(BS_COL_THREADS) void bs_colscan_kernel(const int32_
 // Every workgroup scans the bin totals on its own (16 KB; cheaper than one more launch): start
 // of bin f, then the workgroup's first position in the bin, and moves its keys, with their source
 // index, to their bin's range.
-// SUM (small tables of 16-bit counts, see bucket_plan): the totals and the counts of the workgroups before this one are
-// summed here from the whole table, which saves the column scan's launch (4 to 5 us).  A thread sums four bins, two per
-// register: a workgroup counts at most 4096 keys, so 15 rows fit 16 bits before they have to be widened.  It also prepares the rank pass: for every BS_PART scattered
+// It also prepares the rank pass: for every BS_PART scattered
 // positions the window of whole bins that covers them, BS_PAD_KEYS all-ones keys behind the last
 // key, the number of keys that take part and, for the downsampling variant (DEDUP: of a run of
 // equal adjacent keys only the first takes part), the cleared position bitmap and chunk counters.
-constexpr int BS_SUM_ROWS = 15;
-constexpr int BS_SUM_MAX_WG = 8;  // rows of the largest table that is summed here
+// What bounds it: the scattered stores, of which a CU issues one lane per cycle, so the shares of the workgroups are short
+// (see bucket_plan).
 // REC (pack + sort of 32-bit keys that bs_rank_lds_kernel ranks): a key and its source index leave as one 8-byte record.
 // From half a million keys on hardly two keys of a workgroup share a bin, so every scattered store is a memory
 // transaction of its own, and one array of records takes half as many as two arrays.
-template <typename KeyT, bool DEDUP, bool SUM, bool REC>
+template <typename KeyT, bool DEDUP, bool REC>
 __global__ __launch_bounds__(BS_WIDE) void bs_scatter_kernel(const KeyT* __restrict__ keys0, int64_t n, int per, int shift,
                                                              int n_bin, const int32_t* __restrict__ before,
-                                                             const int32_t* __restrict__ tot,
-                                                             const uint16_t* __restrict__ table, BsElem<KeyT, REC>* __restrict__ keys1,
+                                                             const int32_t* __restrict__ tot, size_t tot_pitch, BsElem<KeyT, REC>* __restrict__ keys1,
                                                              int32_t* __restrict__ vals1, int2* __restrict__ win,
                                                              int32_t* __restrict__ n_part_keys, uint32_t* __restrict__ bits,
                                                              int n_words, int32_t* __restrict__ ccnt, int n_chunks,
@@ -191,8 +217,7 @@ __global__ __launch_bounds__(BS_WIDE) void bs_scatter_kernel(const KeyT* __restr
   if (DEDUP) {
     keys0 = level_ws(keys0, ws_pitch);
     before = level_ws(before, ws_pitch);
-    tot = level_ws(tot, ws_pitch);
-    table = level_ws(table, ws_pitch);
+    tot = level_ws(tot, tot_pitch);
     keys1 = level_ws(keys1, ws_pitch);
     win = level_ws(win, ws_pitch);
     n_part_keys = level_ws(n_part_keys, ws_pitch);
@@ -226,32 +251,8 @@ __global__ __launch_bounds__(BS_WIDE) void bs_scatter_kernel(const KeyT* __restr
     const int f0 = r0 + t * 4;
     int4 c = make_int4(0, 0, 0, 0), bef = c;
     if (f0 < n_bin) {
-      if constexpr (SUM) {
-        auto add_rows = [&](int w, int w_end, int4& acc) {
-          for (; w < w_end; w += BS_SUM_ROWS) {
-            uint2 row[BS_SUM_ROWS];
-#pragma unroll
-            for (int r = 0; r < BS_SUM_ROWS; ++r)
-              row[r] = *reinterpret_cast<const uint2*>(table + int64_t(min(w + r, w_end - 1)) * n_bin + f0);
-            unsigned a = 0, b = 0;  // two 16-bit sums each
-#pragma unroll
-            for (int r = 0; r < BS_SUM_ROWS; ++r) {
-              a += w + r < w_end ? row[r].x : 0u;
-              b += w + r < w_end ? row[r].y : 0u;
-            }
-            acc.x += a & 0xffffu;
-            acc.y += a >> 16;
-            acc.z += b & 0xffffu;
-            acc.w += b >> 16;
-          }
-        };
-        add_rows(0, blockIdx.x, bef);
-        c = bef;
-        add_rows(blockIdx.x, gridDim.x, c);
-      } else {
-        c = *reinterpret_cast<const int4*>(tot + f0);
-        bef = *reinterpret_cast<const int4*>(before + int64_t(blockIdx.x) * n_bin + f0);
-      }
+      c = *reinterpret_cast<const int4*>(tot + f0);
+      bef = *reinterpret_cast<const int4*>(before + int64_t(blockIdx.x) * n_bin + f0);
     }
     const int sum = c.x + c.y + c.z + c.w;
     int x = sum;
@@ -470,7 +471,8 @@ __device__ inline void bs_rank_part(int part, const BsElem<KeyT, REC>* __restric
 template <typename KeyT, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void bs_rank_kernel(const KeyT* __restrict__ keys1, const int32_t* __restrict__ vals1,
                                                              const int2* __restrict__ win, int n, KeyT* __restrict__ out_k,
-                                                             int32_t* __restrict__ out_v) {
+                                                             int32_t* __restrict__ out_v, int32_t* __restrict__ tot, int n_bin) {
+  bs_clear_after(tot, n_bin);
   bs_rank_part<KeyT, WAVES>(blockIdx.x, keys1, vals1, win, n, out_k, out_v);
 }
 
@@ -565,7 +567,8 @@ template <typename KeyT>
 __global__ __launch_bounds__(BS_THREADS) void bs_compact_kernel(const KeyT* __restrict__ sorted, const uint32_t* __restrict__ bits,
                                                                 const int32_t* __restrict__ ccnt,
                                                                 const int32_t* __restrict__ n_kept, const LevelOut<KeyT> lo,
-                                                                size_t ws_pitch) {
+                                                                size_t ws_pitch, int32_t* __restrict__ tot, size_t tot_pitch, int n_bin) {
+  if (tot) bs_clear_after(level_ws(tot, tot_pitch), n_bin);
   sorted = level_ws(sorted, ws_pitch);
   bits = level_ws(bits, ws_pitch);
   ccnt = level_ws(ccnt, ws_pitch);
@@ -1048,7 +1051,11 @@ int small_mask_unique(int key_bits, const void* keys_in, int64_t n, const LevelJ
 // ---------------------------------------------------------------- host
 BucketPlan bucket_plan(int64_t n, int used_bits) {
   BucketPlan p{};
-  int n_wg = static_cast<int>(std::min<int64_t>(std::max<int64_t>((n + 4095) / 4096, 1), BS_MAX_WG));
+  p.add = n <= BS_ADD_N;
+  // keys per workgroup: short shares spread the scattered stores over the chip, and the additions over fewer bins; where the
+  // table is scanned every workgroup adds a row to it
+  const int share = n <= BS_SHORT_N ? BS_SHORT_SHARE : p.add ? BS_ADD_SHARE : 4096;
+  int n_wg = static_cast<int>(std::min<int64_t>(std::max<int64_t>((n + share - 1) / share, 1), p.add ? n : BS_MAX_WG));
   p.per = static_cast<int>(((n + n_wg - 1) / n_wg + BS_WIDE - 1) / BS_WIDE * BS_WIDE);
   p.n_wg = static_cast<int>(std::max<int64_t>((n + p.per - 1) / p.per, 1));
   // About 16 keys per bin of the key space up to 4096 bins: packing descriptors round every field up
@@ -1060,10 +1067,6 @@ BucketPlan bucket_plan(int64_t n, int used_bits) {
   while (fb < 12 && (int64_t(16) << fb) < n) ++fb;
   if (n > 200000) fb = 13;
   if (n > 524288) fb = 14;
-  // The scatter pass sums tables of a few rows itself: pack + sort, column scan / summed, 4.1 k keys 14.4 / 12.5 us, 12 k
-  // 16.3 / 15.3, 30 k (8 rows) 17.6 / 16.9, 45 k (11 rows) 19.2 / 19.9, 120 k 26.0 / 27.0 (every workgroup then reads up to
-  // half a megabyte that other XCDs have written)
-  p.sum = fb <= 12 && p.per <= 4096 && p.n_wg <= BS_SUM_MAX_WG;
   static_assert(BS_MAX_BIN_BITS >= 14, "bin table sizes");
   fb = std::max(2, std::min(fb, used_bits));
   p.shift = used_bits - fb;
@@ -1103,7 +1106,7 @@ Ws<KeyT> carve(void* ws, int64_t n) {
   const BucketPlan cap = bucket_plan(n, 64);  // as many workgroups and at least as many bins as any plan for n keys
   const size_t tbl = (size_t(cap.n_wg) * cap.n_bin + 63) / 64 * 64;
   w.before = w.table + tbl;
-  w.fstart = w.before + tbl;
+  w.fstart = w.before + (cap.add ? 0 : tbl);
   w.win = reinterpret_cast<int2*>(w.fstart + cap.n_bin + 64);  // 8-byte aligned: every part above is a multiple of 256 bytes
   w.n_kept = reinterpret_cast<int32_t*>(w.win + (nn / BS_PART + 2));
   w.ccnt = w.n_kept + 2;
@@ -1115,52 +1118,88 @@ Ws<KeyT> carve(void* ws, int64_t n) {
   return w;
 }
 
-// count, column scan, scatter: keys1 (vals1) partitioned by fine bin, rank windows
-template <typename KeyT, bool DEDUP, bool REC, typename Src>
-void partition(const Src& src, int64_t n, const BucketPlan& p, const Ws<KeyT>& w, int n_levels, size_t ws_pitch, hipStream_t s) {
-  if (p.sum) {
-    uint16_t* table = reinterpret_cast<uint16_t*>(w.table);
-    hipLaunchKernelGGL((bs_count_kernel<KeyT, Src, uint16_t>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(p.n_bin) * 4, s, src, n,
-                       p.per, p.shift, p.n_bin, w.keys0, table, ws_pitch);
-    hipLaunchKernelGGL((bs_scatter_kernel<KeyT, DEDUP, true, false>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(2 * p.n_bin + 2) * 4, s,
-                       w.keys0, n, p.per, p.shift, p.n_bin, static_cast<const int32_t*>(nullptr), static_cast<const int32_t*>(nullptr),
-                       table, w.keys1, w.vals1, w.win, DEDUP ? w.n_kept : static_cast<int32_t*>(nullptr), w.bits, w.n_words, w.ccnt,
-                       w.n_chunks, w.rest_count, ws_pitch);
-    return;
+// The bins' totals of a sort: in a block that the library keeps cleared between its sorts (the last kernel clears it again),
+// or, where none is to be had (under capture, whose replays know nothing of other sorts; for callers that forbid
+// allocation), in the workspace, cleared by a kernel of its own.
+struct Totals {
+  int32_t* p = nullptr;
+  size_t pitch = 0, bytes = 0;
+  bool kept = false;
+  hipStream_t s;
+  Totals(const BucketPlan& plan, int32_t* in_ws, size_t ws_pitch, int n_levels, bool may_alloc, hipStream_t s_) : p(in_ws), pitch(ws_pitch), s(s_) {
+    if (!plan.add) return;
+    bytes = size_t(plan.n_bin) * 4 * n_levels;
+    if (may_alloc) p = static_cast<int32_t*>(zeroed_alloc(bytes, s));
+    kept = may_alloc && p;
+    if (kept) {
+      pitch = size_t(plan.n_bin) * 4;
+      return;
+    }
+    p = in_ws;
+    hipLaunchKernelGGL(bs_clear_kernel, dim3((plan.n_bin + BS_THREADS - 1) / BS_THREADS, n_levels), dim3(BS_THREADS), 0, s, p, plan.n_bin, pitch);
   }
-  hipLaunchKernelGGL((bs_count_kernel<KeyT, Src, int32_t>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(p.n_bin) * 4, s, src, n, p.per,
-                     p.shift, p.n_bin, w.keys0, w.table, ws_pitch);
-  const int col_wg = (p.n_bin / 4 + BS_COL_THREADS - 1) / BS_COL_THREADS;
-  hipLaunchKernelGGL(bs_colscan_kernel, dim3(col_wg, n_levels), dim3(BS_COL_THREADS), 0, s, w.table, w.before, p.n_wg, p.n_bin,
-                     w.fstart, ws_pitch);
+  int32_t* to_clear() const { return kept ? p : nullptr; }
+  // once all kernels of the sort are enqueued
+  int done(const char* what) {
+    const bool ok = hipGetLastError() == hipSuccess;
+    if (kept) zeroed_free(p, bytes, s, ok);
+    return ok ? SPC_OK : set_error(SPC_ERR_HIP, "%s launch failed", what);
+  }
+};
+
+// count, (column scan,) scatter: keys1 (vals1) partitioned by fine bin, rank windows
+template <typename KeyT, bool DEDUP, bool REC, typename Src>
+void partition(const Src& src, int64_t n, const BucketPlan& p, const Ws<KeyT>& w, int n_levels, size_t ws_pitch, const Totals& t, hipStream_t s) {
+  const int32_t* before = w.table;
+  if (p.add) {
+    hipLaunchKernelGGL((bs_count_kernel<KeyT, Src, true>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(p.n_bin) * 4, s, src, n, p.per,
+                       p.shift, p.n_bin, w.keys0, w.table, ws_pitch, t.p, t.pitch);
+  } else {
+    hipLaunchKernelGGL((bs_count_kernel<KeyT, Src, false>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(p.n_bin) * 4, s, src, n, p.per,
+                       p.shift, p.n_bin, w.keys0, w.table, ws_pitch, static_cast<int32_t*>(nullptr), size_t(0));
+    const int col_wg = (p.n_bin / 4 + BS_COL_THREADS - 1) / BS_COL_THREADS;
+    hipLaunchKernelGGL(bs_colscan_kernel, dim3(col_wg, n_levels), dim3(BS_COL_THREADS), 0, s, w.table, w.before, p.n_wg, p.n_bin,
+                       t.p, ws_pitch);
+    before = w.before;
+  }
   // (the scatter pass holds two ints per bin: beyond 8191 bins that is more than the default LDS limit)
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bs_scatter_kernel<KeyT, DEDUP, false, REC>),
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bs_scatter_kernel<KeyT, DEDUP, REC>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (2 * BS_MAX_BIN + 2) * 4);
   (void)attr;
-  hipLaunchKernelGGL((bs_scatter_kernel<KeyT, DEDUP, false, REC>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(2 * p.n_bin + 2) * 4, s, w.keys0,
-                     n, p.per, p.shift, p.n_bin, w.before, w.fstart, static_cast<const uint16_t*>(nullptr), reinterpret_cast<BsElem<KeyT, REC>*>(w.keys1), w.vals1, w.win, DEDUP ? w.n_kept : static_cast<int32_t*>(nullptr), w.bits, w.n_words, w.ccnt,
-                     w.n_chunks, w.rest_count, ws_pitch);
+  hipLaunchKernelGGL((bs_scatter_kernel<KeyT, DEDUP, REC>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(2 * p.n_bin + 2) * 4, s, w.keys0,
+                     n, p.per, p.shift, p.n_bin, before, t.p, t.pitch, reinterpret_cast<BsElem<KeyT, REC>*>(w.keys1), w.vals1, w.win,
+                     DEDUP ? w.n_kept : static_cast<int32_t*>(nullptr), w.bits, w.n_words, w.ccnt, w.n_chunks, w.rest_count, ws_pitch);
 }
 }  // namespace
+
+// Entries of the tables of a sort of up to n keys (a workspace for n keys serves fewer as well).
+static size_t table_entries(int64_t n) {
+  size_t most = 0;
+  for (int64_t m : {std::min(n, BS_SHORT_N), std::min(n, BS_ADD_N), n}) {
+    const BucketPlan p = bucket_plan(m, 64);
+    most = std::max(most, (size_t(p.n_wg) * p.n_bin + 63) / 64 * 64 * (p.add ? 1 : 2));
+  }
+  return most;
+}
 
 size_t bucket_sort_ws_bytes(int key_bits, int64_t n) {
   const size_t nn = static_cast<size_t>(std::max<int64_t>(n, 1));
   const size_t k = ((nn + BS_PAD_KEYS) * (key_bits / 8) + 255) / 256 * 256, v = ((nn + BS_PAD_KEYS) * 4 + 255) / 256 * 256;
   const BucketPlan cap = bucket_plan(n, 64);
-  const size_t tbl = (size_t(cap.n_wg) * cap.n_bin + 63) / 64 * 64;
-  return 2 * k + v + (2 * tbl + cap.n_bin + 64 + 2 * (nn / BS_PART + 2) + 2 + chunks_for(n) + words_for(n) + (nn / BS_LP + 2)) * 4;
+  return 2 * k + v + (table_entries(n) + cap.n_bin + 64 + 2 * (nn / BS_PART + 2) + 2 + chunks_for(n) + words_for(n) + (nn / BS_LP + 2)) * 4;
 }
 
 template <typename KeyT>
 static int pack_sort_t(const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status, void* keys_out,
-                       int32_t* perm_out, void* ws, hipStream_t s) {
+                       int32_t* perm_out, void* ws, bool may_alloc, hipStream_t s) {
   const BucketPlan p = bucket_plan(n, used_bits);
   const Ws<KeyT> w = carve<KeyT>(ws, n);
+  Totals tot(p, w.fstart, 0, 1, may_alloc, s);
   // one element array (see REC): over keys1 and vals1 together, which lie one behind the other
   constexpr bool REC = sizeof(KeyT) == 4;
   const SrcPack<KeyT> src{coords, pp, status};
-  if (n >= BS_RANK_LDS_N) partition<KeyT, false, REC>(src, n, p, w, 1, 0, s);
-  else partition<KeyT, false, false>(src, n, p, w, 1, 0, s);
+  if (n >= BS_RANK_LDS_N) partition<KeyT, false, REC>(src, n, p, w, 1, 0, tot, s);
+  else partition<KeyT, false, false>(src, n, p, w, 1, 0, tot, s);
   const int n_part = static_cast<int>((n + BS_PART - 1) / BS_PART);
   // Four waves share a part's window while the launch is latency-bound (its time is that of the part with
   // the largest window); from BS_RANK_SOLO_N keys on (25 parts per CU) the pass is bound by how many parts
@@ -1179,18 +1218,17 @@ static int pack_sort_t(const int4* coords, int64_t n, const PackParams& pp, int 
                        perm_out, static_cast<uint32_t*>(nullptr), static_cast<int32_t*>(nullptr), size_t(0));
   } else if (n >= BS_RANK_SOLO_N)
     hipLaunchKernelGGL((bs_rank_kernel<KeyT, 1>), dim3(n_part), dim3(64), 0, s, w.keys1, w.vals1, w.win, static_cast<int>(n),
-                       static_cast<KeyT*>(keys_out), perm_out);
+                       static_cast<KeyT*>(keys_out), perm_out, tot.to_clear(), p.n_bin);
   else
     hipLaunchKernelGGL((bs_rank_kernel<KeyT, BS_THREADS / 64>), dim3(n_part), dim3(BS_THREADS), 0, s, w.keys1, w.vals1, w.win,
-                       static_cast<int>(n), static_cast<KeyT*>(keys_out), perm_out);
-  if (hipGetLastError() != hipSuccess) return set_error(SPC_ERR_HIP, "sort launch failed");
-  return SPC_OK;
+                       static_cast<int>(n), static_cast<KeyT*>(keys_out), perm_out, tot.to_clear(), p.n_bin);
+  return tot.done("sort");
 }
 
 int bucket_pack_sort(int key_bits, const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status,
-                     void* keys_out, int32_t* perm_out, void* ws, hipStream_t s) {
-  return key_bits == 32 ? pack_sort_t<uint32_t>(coords, n, pp, used_bits, status, keys_out, perm_out, ws, s)
-                        : pack_sort_t<uint64_t>(coords, n, pp, used_bits, status, keys_out, perm_out, ws, s);
+                     void* keys_out, int32_t* perm_out, void* ws, bool may_alloc, hipStream_t s) {
+  return key_bits == 32 ? pack_sort_t<uint32_t>(coords, n, pp, used_bits, status, keys_out, perm_out, ws, may_alloc, s)
+                        : pack_sort_t<uint64_t>(coords, n, pp, used_bits, status, keys_out, perm_out, ws, may_alloc, s);
 }
 
 template <typename KeyT>
@@ -1201,7 +1239,8 @@ static int mask_unique_t(const void* keys_in, int64_t n, const LevelJob* jobs, i
   SrcMasks<KeyT> src;
   LevelOut<KeyT> lo;
   batch_args(keys_in, jobs, n_levels, &src, &lo);
-  partition<KeyT, true, false>(src, n, p, w, n_levels, ws_pitch, s);
+  Totals tot(p, w.fstart, ws_pitch, n_levels, true, s);
+  partition<KeyT, true, false>(src, n, p, w, n_levels, ws_pitch, tot, s);
   // the sorted keys (with gaps) go to keys0, which is free again by now
   const int n_part = static_cast<int>((n + BS_PART - 1) / BS_PART), n_chunk = static_cast<int>((n + BS_CHUNK - 1) / BS_CHUNK);
   if (n >= BS_RANK_LDS_N) {
@@ -1215,9 +1254,8 @@ static int mask_unique_t(const void* keys_in, int64_t n, const LevelJob* jobs, i
     hipLaunchKernelGGL(bs_rank_unique_kernel<KeyT>, dim3(n_part, n_levels), dim3(BS_THREADS), 0, s, w.keys1, w.win, w.n_kept, w.keys0,
                        w.bits, w.ccnt, ws_pitch);
   hipLaunchKernelGGL(bs_compact_kernel<KeyT>, dim3(n_chunk, n_levels), dim3(BS_THREADS), 0, s, w.keys0, w.bits, w.ccnt, w.n_kept, lo,
-                     ws_pitch);
-  if (hipGetLastError() != hipSuccess) return set_error(SPC_ERR_HIP, "downsample launch failed");
-  return SPC_OK;
+                     ws_pitch, tot.to_clear(), tot.pitch, p.n_bin);
+  return tot.done("downsample");
 }
 
 int bucket_mask_unique(int key_bits, const void* keys_in, int64_t n, const LevelJob* jobs, int n_levels, int used_bits, void* ws,

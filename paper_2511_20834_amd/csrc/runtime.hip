@@ -32,6 +32,8 @@ struct Pool {
   std::mutex mu;
   std::map<std::pair<size_t, hipStream_t>, std::vector<void*>> free_blocks;
   std::unordered_map<void*, size_t> live;  // block -> rounded size
+  std::map<std::pair<size_t, hipStream_t>, std::vector<void*>> zeroed;  // (live as far as the above is concerned)
+  size_t n_zeroed = 0;
 };
 Pool& pool() {
   static Pool* p = new Pool;  // never destroyed: device memory is reclaimed by the driver at exit
@@ -86,6 +88,49 @@ void pool_free(void* p, hipStream_t stream) {
   if (it == P.live.end()) return;
   P.free_blocks[{it->second, stream}].push_back(p);
   P.live.erase(it);
+}
+
+namespace {
+constexpr size_t MAX_ZEROED = 256;  // kept blocks; further ones go back to the ordinary cache
+__global__ __launch_bounds__(256) void clear_kernel(uint4* p, size_t n) {
+  const size_t i = blockIdx.x * size_t(256) + threadIdx.x;
+  if (i < n) p[i] = make_uint4(0, 0, 0, 0);
+}
+}  // namespace
+
+void* zeroed_alloc(size_t bytes, hipStream_t stream) {
+  if (stream_is_capturing(stream)) return nullptr;
+  const size_t r = round_size(bytes);
+  Pool& P = pool();
+  {
+    std::lock_guard<std::mutex> lk(P.mu);
+    auto it = P.zeroed.find({r, stream});
+    if (it != P.zeroed.end() && !it->second.empty()) {
+      void* p = it->second.back();
+      it->second.pop_back();
+      --P.n_zeroed;
+      return p;
+    }
+  }
+  void* p = pool_alloc(r, stream);
+  if (!p) return nullptr;
+  hipLaunchKernelGGL(clear_kernel, dim3(static_cast<unsigned>((r / 16 + 255) / 256)), dim3(256), 0, stream, static_cast<uint4*>(p), r / 16);
+  if (hipGetLastError() == hipSuccess) return p;
+  pool_free(p, stream);
+  return nullptr;
+}
+
+void zeroed_free(void* p, size_t bytes, hipStream_t stream, bool clean) {
+  Pool& P = pool();
+  if (clean) {
+    std::lock_guard<std::mutex> lk(P.mu);
+    if (P.n_zeroed < MAX_ZEROED) {
+      P.zeroed[{round_size(bytes), stream}].push_back(p);
+      ++P.n_zeroed;
+      return;
+    }
+  }
+  pool_free(p, stream);
 }
 
 namespace {
@@ -201,6 +246,13 @@ int pool_release_all() {
     for (auto& kv : P.free_blocks)
       for (void* b : kv.second) blocks.push_back(b);
     P.free_blocks.clear();
+    for (auto& kv : P.zeroed)
+      for (void* b : kv.second) {
+        blocks.push_back(b);
+        P.live.erase(b);
+      }
+    P.zeroed.clear();
+    P.n_zeroed = 0;
   }
   if (!blocks.empty()) (void)hipDeviceSynchronize();
   for (void* b : blocks) (void)hipFree(b);

@@ -36,6 +36,12 @@ int set_error(int code, const char* fmt, ...);
 void* pool_alloc(size_t bytes, hipStream_t stream);  // nullptr on failure (error set)
 void pool_free(void* p, hipStream_t stream);
 int pool_release_all();
+// Blocks that hold zeros between their uses: whoever takes one leaves it cleared by the last kernel it enqueues on the
+// stream (clean = false: it may not be).  As above, a block goes back to work on the same stream only; one that is taken is in nobody
+// else's hands until it is given back.  NULL while the stream is being captured (replays of the graph would share the block with
+// later calls), or when there is no memory.
+void* zeroed_alloc(size_t bytes, hipStream_t stream);
+void zeroed_free(void* p, size_t bytes, hipStream_t stream, bool clean);
 // Makes everything enqueued on `waiter` from now on run after what `producer` holds at this moment
 // (an event recorded on `producer`; nothing happens when the two are the same stream, or when `waiter` has been
 // ordered behind `producer` before and the library has enqueued nothing on `producer` since and has never been recorded
@@ -184,17 +190,23 @@ constexpr int BS_MAX_BIN = 1 << BS_MAX_BIN_BITS;  // fine bins (top used key bit
 // the rank pass outgrow its LDS beyond that).  3 * 10^6 keys: pack + sort 89 us against 177 us with rocPRIM.
 constexpr int64_t BS_MIN_N = 4096, BS_MAX_N = 8192 * 1024;
 inline bool use_bucket_sort(int64_t n) { return n >= BS_MIN_N && n <= BS_MAX_N; }
+// Keys up to which the count pass adds its counts to the bins' totals, and how many a workgroup takes then.  Pack + sort, us, column
+// scan with 4096 keys per workgroup / this: LiDAR 20 k 16.2 / 13.3, 50 k 19.3 / 15.4, 120 k 24.9 / 20.6, 180 k 29.8 / 25.7; indoor 240 k
+// 34.9 / 32.7; random 300 k 35.5 / 32.5, 500 k 44.6 / 41.2.  Beyond, the table of 16384 bins would outgrow what is sorted.
+constexpr int64_t BS_ADD_N = 524288, BS_SHORT_N = 65536;
+constexpr int BS_ADD_SHARE = 2048, BS_SHORT_SHARE = 1024;
 constexpr int BS_PART = 64;         // keys per rank workgroup
 constexpr int BS_PAD_KEYS = 32;     // all-ones keys kept behind the scattered keys
 struct BucketPlan {
   int n_wg, per, shift, n_bin;
-  bool sum;  // the scatter pass sums the counts itself (no column scan)
+  bool add;  // the count pass adds the counts up itself (no column scan)
 };
 BucketPlan bucket_plan(int64_t n, int used_bits);
 size_t bucket_sort_ws_bytes(int key_bits, int64_t n);
-// coords -> sorted keys (+ permutation); enqueues three kernels (count, scatter, rank), or four with the column scan of large tables
+// coords -> sorted keys (+ permutation); enqueues three kernels (count, scatter, rank), or four with the column scan of large inputs
+// or, where the library may not allocate, with the clearing of the totals
 int bucket_pack_sort(int key_bits, const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status,
-                     void* keys_out, int32_t* perm_out, void* ws, hipStream_t s);
+                     void* keys_out, int32_t* perm_out, void* ws, bool may_alloc, hipStream_t s);
 // One level to produce: the sorted distinct values of keys_in & mask, and their count.
 constexpr int BS_MAX_LEVELS = 8;  // levels of one batch (the block rows of its launches)
 struct LevelJob {
