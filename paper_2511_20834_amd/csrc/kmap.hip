@@ -311,6 +311,10 @@ __global__ __launch_bounds__(64 * K) void kmap_search_kernel(const SearchBatch<K
     }
     return static_cast<unsigned>(((static_cast<unsigned long long>(hi) << 32) | lo) >> (b & 31));
   };
+  // every column of this x offset goes to the matrix, in the order of the queries, and nothing else is asked for
+  bool plain = M && !inv_parent && !sp.zrev;
+#pragma unroll
+  for (int i = 0; i < G; i += 32) plain = plain && (~subset_bits(os_k, ix * G + i) & (G - i >= 32 ? ~0u : (1u << ((G - i) & 31)) - 1u)) == 0u;
   auto search_groups = [&](auto N_, auto IY_, int c, KeyT ok) {
     constexpr int N = decltype(N_)::value, IY = decltype(IY_)::value;  // y offsets IY .. IY + N - 1
     const int v = c * 64 + lane;
@@ -392,29 +396,77 @@ __global__ __launch_bounds__(64 * K) void kmap_search_kernel(const SearchBatch<K
     }
     // A query that reaches the all-ones key could take the padding behind its window for a voxel, and a lane past the
     // last row must not hit at all: waves with such lanes look at every key's place.
+    KeyT least = KeyT(~q0[0]);
 #pragma unroll
-    for (int j = 0; j < N; ++j) {
-      if (__ballot(KeyT(~q0[j]) <= zspan || !act)) {
+    for (int j = 1; j < N; ++j) least = min(least, KeyT(~q0[j]));
+    if (__ballot(least <= zspan || !act)) {
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
         const int rem = static_cast<int>(unsigned(lwin + unsigned(wsz) * KB - KB - ab[j]) / KB);  // keys of the window from the lower bound on
 #pragma unroll
         for (int i = 0; i < K; ++i) d[j][i] = act && (sampled || i < rem) ? d[j][i] : KeyT(q0[j] - 1);
       }
     }
     constexpr int BIT0 = IY * K;
-    const unsigned osb = M ? subset_bits(os_k, ix * G + BIT0) : 0u, wsb = PAIRS ? subset_bits(ws_k, ix * G + BIT0) : 0u;
     unsigned hb = 0u;  // bit j * K + t: query t of group j hit
+    // Every store into the blocked map M[block][k][32] is two full 128-byte segments; rows past the end of the last
+    // block hold -1.  Column of query t: offsets of a group ascend with z, queries too unless the z offsets descend with iz.
+    const bool in_block = c * 64 + (lane & 32) < rows;
+    SPC_GLOBAL char* Mg = M + ((b0 + c * 2) * int64_t(K3) + ix * G + BIT0) * 128;  // uniform
+    // (the usual case has a way of its own: what is decided per group below costs as many scalar instructions as the hits vector
+    // ones.  Build of one map, us, before / after: 120 k voxels 12.1 / 11.7, 180 k 15.5 / 14.7, 10^6 42.7 / 39.8, 3 * 10^6 98 / 91.5)
+    const bool usual = !PAIRS && plain;
+    const unsigned osb = usual ? ~0u : M ? subset_bits(os_k, ix * G + BIT0) : 0u, wsb = PAIRS ? subset_bits(ws_k, ix * G + BIT0) : 0u;
+    struct Rows {
+      int32_t t[K];
+    };
+    // where the rows of a group go, unless it is the usual case
+    auto emit = [&](int j, Rows r) __attribute__((always_inline)) {
+      const int gj = ix * K + IY + j;
+      // Inverse of a strided map whose offsets partition the inputs (K = layer stride): every input voxel is hit by
+      // exactly one (output, offset), which is all its transposed twin needs (such maps are built without a
+      // row permutation, so r holds positions)
+      if (inv_parent) {
+#pragma unroll
+        for (int t = 0; t < K; ++t)
+          if (r.t[t] >= 0) inv_parent[r.t[t]] = (i0 + v) * K3 + gj * K + (sp.zrev ? K - 1 - t : t);
+      }
+      if constexpr (PAIRS) {
+        // the tile's records stay in LDS; hits are counted per offset (a wave speaks for its 64 rows)
+        s_hit[gj * TILE + v] = static_cast<uint8_t>((hb >> (j * K)) & ((1u << K) - 1u));
+        if ((wsb >> (j * K)) & ((1u << K) - 1u)) {
+#pragma unroll
+          for (int t = 0; t < K; ++t) {
+            const int col = sp.zrev ? K - 1 - t : t;
+            const unsigned long long bal = __ballot(r.t[t] >= 0);
+            if (bal && ((wsb >> (j * K + col)) & 1u) && lane == 0) atomicAdd(&s_cnt[gj * K + col], __popcll(bal));
+          }
+        }
+      }
+      const unsigned osf = (osb >> (j * K)) & ((1u << K) - 1u);
+      if (!M || osf == 0u) return;  // no offset goes to the matrix (uniform)
+      if (in_block) {
+#pragma unroll
+        for (int t = 0; t < K; ++t) {
+          const int col = sp.zrev ? K - 1 - t : t;
+          if ((osf >> col) & 1u) *(SPC_GLOBAL int32_t*)(Mg + (j * K + col) * 128 + lane_off) = r.t[t];
+        }
+      }
+    };
+    constexpr bool BATCH = K < 5;  // all groups' rows are found before any is stored (large kernels have no registers for that)
+    Rows rows_of[BATCH ? N : 1];
 #pragma unroll
     for (int j = 0; j < N; ++j) {
       // query t (ascending z) sits i <= t positions behind the lower bound, i = number of earlier queries that hit:
       // the key looked at moves on by one where a query has hit
-      int32_t r[K];
+      Rows r;
       bool hit[K];
 #pragma unroll
       for (int i = 0; i < K; ++i) d[j][i] -= q0[j];
 #pragma unroll
       for (int t = 0; t < K; ++t) {
         hit[t] = d[j][0] == KeyT(t) * sp.zstep;
-        r[t] = hit[t] ? val[j][0] : -1;
+        r.t[t] = hit[t] ? val[j][0] : -1;
 #pragma unroll
         for (int i = 0; i + 1 < K - t; ++i) {
           d[j][i] = hit[t] ? d[j][i + 1] : d[j][i];
@@ -425,44 +477,28 @@ __global__ __launch_bounds__(64 * K) void kmap_search_kernel(const SearchBatch<K
 #pragma unroll
       for (int t = K - 1; t >= 0; --t) hm = hm + hm + (hit[t] ? 1u : 0u);
       hb |= hm << (j * K);
-      const int gj = ix * K + IY + j;
-      // column of query t: offsets of a group ascend with z, queries too unless the z offsets descend with iz.
-      // Inverse of a strided map whose offsets partition the inputs (K = layer stride): every input voxel is hit by
-      // exactly one (output, offset), which is all its transposed twin needs (such maps are built without a
-      // row permutation, so r holds positions)
-      if (inv_parent) {
+      if constexpr (BATCH) {
+        rows_of[j] = r;
+      } else if (usual) {
+        if (in_block) {
 #pragma unroll
-        for (int t = 0; t < K; ++t)
-          if (hit[t]) inv_parent[r[t]] = (i0 + v) * K3 + gj * K + (sp.zrev ? K - 1 - t : t);
-      }
-      if constexpr (PAIRS) {
-        // the tile's records stay in LDS; hits are counted per offset (a wave speaks for its 64 rows)
-        s_hit[gj * TILE + v] = static_cast<uint8_t>(hm);
-        if ((wsb >> (j * K)) & ((1u << K) - 1u)) {
-#pragma unroll
-          for (int t = 0; t < K; ++t) {
-            const int col = sp.zrev ? K - 1 - t : t;
-            const unsigned long long bal = __ballot(hit[t]);
-            if (bal && ((wsb >> (j * K + col)) & 1u) && lane == 0) atomicAdd(&s_cnt[gj * K + col], __popcll(bal));
-          }
+          for (int t = 0; t < K; ++t) *(SPC_GLOBAL int32_t*)(Mg + (j * K + t) * 128 + lane_off) = r.t[t];
         }
+      } else {
+        emit(j, r);
       }
-      const unsigned osf = (osb >> (j * K)) & ((1u << K) - 1u);
-      if (!M || osf == 0u) continue;  // no offset goes to the matrix (uniform)
-      // Every store into the blocked map M[block][k][32] is two full 128-byte segments; rows past the end of the last
-      // block hold -1.
-      if (c * 64 + (lane & 32) < rows) {
-        SPC_GLOBAL char* Mg = M + ((b0 + c * 2) * int64_t(K3) + gj * K) * 128;  // uniform
-        if (!sp.zrev && osf == (1u << K) - 1u) {  // the usual case
+    }
+    if constexpr (BATCH) {
+      if (usual) {
+        if (in_block) {
 #pragma unroll
-          for (int t = 0; t < K; ++t) *(SPC_GLOBAL int32_t*)(Mg + t * 128 + lane_off) = r[t];
-        } else {
+          for (int j = 0; j < N; ++j)
 #pragma unroll
-          for (int t = 0; t < K; ++t) {
-            const int col = sp.zrev ? K - 1 - t : t;
-            if ((osf >> col) & 1u) *(SPC_GLOBAL int32_t*)(Mg + col * 128 + lane_off) = r[t];
-          }
+            for (int t = 0; t < K; ++t) *(SPC_GLOBAL int32_t*)(Mg + (j * K + t) * 128 + lane_off) = rows_of[j].t[t];
         }
+      } else {
+#pragma unroll
+        for (int j = 0; j < N; ++j) emit(j, rows_of[j]);
       }
     }
     if (M) {  // the blocks' masks
