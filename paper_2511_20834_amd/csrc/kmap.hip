@@ -414,8 +414,10 @@ __global__ __launch_bounds__(64 * K) void kmap_search_kernel(const SearchBatch<K
     const bool in_block = c * 64 + (lane & 32) < rows;
     SPC_GLOBAL char* Mg = M + ((b0 + c * 2) * int64_t(K3) + ix * G + BIT0) * 128;  // uniform
     // (the usual case has a way of its own: what is decided per group below costs as many scalar instructions as the hits vector
-    // ones.  Build of one map, us, before / after: 120 k voxels 12.1 / 11.7, 180 k 15.5 / 14.7, 10^6 42.7 / 39.8, 3 * 10^6 98 / 91.5)
-    const bool usual = !PAIRS && plain;
+    // ones.  Build of one map, us, before / after: 120 k voxels 12.1 / 11.7, 180 k 15.5 / 14.7, 10^6 42.7 / 39.8, 3 * 10^6 98 / 91.5.
+    // Groups of five, looked up and stored one after the other, are slower with it: 5x5x5 pass of 240 k voxels 109.9 / 112.3)
+    constexpr bool BATCH = K < 5;  // all groups' rows are found before any is stored (large kernels have no registers for that)
+    const bool usual = BATCH && !PAIRS && plain;
     const unsigned osb = usual ? ~0u : M ? subset_bits(os_k, ix * G + BIT0) : 0u, wsb = PAIRS ? subset_bits(ws_k, ix * G + BIT0) : 0u;
     struct Rows {
       int32_t t[K];
@@ -453,7 +455,6 @@ __global__ __launch_bounds__(64 * K) void kmap_search_kernel(const SearchBatch<K
         }
       }
     };
-    constexpr bool BATCH = K < 5;  // all groups' rows are found before any is stored (large kernels have no registers for that)
     Rows rows_of[BATCH ? N : 1];
 #pragma unroll
     for (int j = 0; j < N; ++j) {
@@ -479,11 +480,6 @@ __global__ __launch_bounds__(64 * K) void kmap_search_kernel(const SearchBatch<K
       hb |= hm << (j * K);
       if constexpr (BATCH) {
         rows_of[j] = r;
-      } else if (usual) {
-        if (in_block) {
-#pragma unroll
-          for (int t = 0; t < K; ++t) *(SPC_GLOBAL int32_t*)(Mg + (j * K + t) * 128 + lane_off) = r.t[t];
-        }
       } else {
         emit(j, r);
       }
