@@ -155,10 +155,13 @@ __global__ __launch_bounds__(BS_THREADS) void bs_clear_kernel(int32_t* __restric
   const int b = blockIdx.x * BS_THREADS + threadIdx.x;
   if (b < n_bin) level_ws(tot, tot_pitch)[b] = 0;
 }
-// The same by the last kernel of a sort, for the next one.
+// The same by the last kernel of a sort, for the next one.  Its grid has at least n / 4 threads in whole workgroups of 64 or
+// 256, and a plan at most 256 or n / 8 bins: a thread per bin.  (As a loop with the grid's stride, which reads the launch's sizes
+// from memory first: a sort of 6 k to 70 k keys 0.4 us longer, of 240 k 0.9.)
+template <int THREADS>
 __device__ inline void bs_clear_after(int32_t* tot, int n_bin) {
-  if (tot)
-    for (int b = blockIdx.x * blockDim.x + threadIdx.x; b < n_bin; b += gridDim.x * blockDim.x) tot[b] = 0;
+  const int b = blockIdx.x * THREADS + threadIdx.x;
+  if (tot && b < n_bin) tot[b] = 0;
 }
 
 // ---------------------------------------------------------------- column scan (large inputs)
@@ -472,7 +475,7 @@ template <typename KeyT, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void bs_rank_kernel(const KeyT* __restrict__ keys1, const int32_t* __restrict__ vals1,
                                                              const int2* __restrict__ win, int n, KeyT* __restrict__ out_k,
                                                              int32_t* __restrict__ out_v, int32_t* __restrict__ tot, int n_bin) {
-  bs_clear_after(tot, n_bin);
+  bs_clear_after<64 * WAVES>(tot, n_bin);
   bs_rank_part<KeyT, WAVES>(blockIdx.x, keys1, vals1, win, n, out_k, out_v);
 }
 
@@ -568,7 +571,7 @@ __global__ __launch_bounds__(BS_THREADS) void bs_compact_kernel(const KeyT* __re
                                                                 const int32_t* __restrict__ ccnt,
                                                                 const int32_t* __restrict__ n_kept, const LevelOut<KeyT> lo,
                                                                 size_t ws_pitch, int32_t* __restrict__ tot, size_t tot_pitch, int n_bin) {
-  if (tot) bs_clear_after(level_ws(tot, tot_pitch), n_bin);
+  if (tot) bs_clear_after<BS_THREADS>(level_ws(tot, tot_pitch), n_bin);
   sorted = level_ws(sorted, ws_pitch);
   bits = level_ws(bits, ws_pitch);
   ccnt = level_ws(ccnt, ws_pitch);
@@ -1049,12 +1052,14 @@ int small_mask_unique(int key_bits, const void* keys_in, int64_t n, const LevelJ
 }
 
 // ---------------------------------------------------------------- host
-BucketPlan bucket_plan(int64_t n, int used_bits) {
+BucketPlan bucket_plan(int64_t n, int used_bits, bool unique) {
   BucketPlan p{};
   p.add = n <= BS_ADD_N;
   // keys per workgroup: short shares spread the scattered stores over the chip, and the additions over fewer bins; where the
-  // table is scanned every workgroup adds a row to it
-  const int share = n <= BS_SHORT_N ? BS_SHORT_SHARE : p.add ? BS_ADD_SHARE : 4096;
+  // table is scanned every workgroup adds a row to it.  Coordinates, whose runs are short, add to almost all bins from some
+  // point on: us with shares of 2048 / 4096, 180 k 25.4 / 26.2, 240 k 31.8 / 31.7, 300 k 31.7 / 30.3, 500 k 40.8 / 36.0; levels
+  // made from sorted keys add to few: 300 k 53.4 / 57.1.
+  const int share = n <= BS_SHORT_N ? BS_SHORT_SHARE : p.add && (unique || n <= BS_MID_N) ? BS_ADD_SHARE : 4096;
   int n_wg = static_cast<int>(std::min<int64_t>(std::max<int64_t>((n + share - 1) / share, 1), p.add ? n : BS_MAX_WG));
   p.per = static_cast<int>(((n + n_wg - 1) / n_wg + BS_WIDE - 1) / BS_WIDE * BS_WIDE);
   p.n_wg = static_cast<int>(std::max<int64_t>((n + p.per - 1) / p.per, 1));
@@ -1103,7 +1108,7 @@ Ws<KeyT> carve(void* ws, int64_t n) {
   w.keys1 = reinterpret_cast<KeyT*>(c + k);
   w.vals1 = reinterpret_cast<int32_t*>(c + 2 * k);
   w.table = reinterpret_cast<int32_t*>(c + 2 * k + v);
-  const BucketPlan cap = bucket_plan(n, 64);  // as many workgroups and at least as many bins as any plan for n keys
+  const BucketPlan cap = bucket_plan(n, 64, true);  // as many workgroups and at least as many bins as any plan for n keys
   const size_t tbl = (size_t(cap.n_wg) * cap.n_bin + 63) / 64 * 64;
   w.before = w.table + tbl;
   w.fstart = w.before + (cap.add ? 0 : tbl);
@@ -1176,7 +1181,7 @@ void partition(const Src& src, int64_t n, const BucketPlan& p, const Ws<KeyT>& w
 static size_t table_entries(int64_t n) {
   size_t most = 0;
   for (int64_t m : {std::min(n, BS_SHORT_N), std::min(n, BS_ADD_N), n}) {
-    const BucketPlan p = bucket_plan(m, 64);
+    const BucketPlan p = bucket_plan(m, 64, true);  // (the more workgroups of the two)
     most = std::max(most, (size_t(p.n_wg) * p.n_bin + 63) / 64 * 64 * (p.add ? 1 : 2));
   }
   return most;
@@ -1185,14 +1190,14 @@ static size_t table_entries(int64_t n) {
 size_t bucket_sort_ws_bytes(int key_bits, int64_t n) {
   const size_t nn = static_cast<size_t>(std::max<int64_t>(n, 1));
   const size_t k = ((nn + BS_PAD_KEYS) * (key_bits / 8) + 255) / 256 * 256, v = ((nn + BS_PAD_KEYS) * 4 + 255) / 256 * 256;
-  const BucketPlan cap = bucket_plan(n, 64);
+  const BucketPlan cap = bucket_plan(n, 64, true);
   return 2 * k + v + (table_entries(n) + cap.n_bin + 64 + 2 * (nn / BS_PART + 2) + 2 + chunks_for(n) + words_for(n) + (nn / BS_LP + 2)) * 4;
 }
 
 template <typename KeyT>
 static int pack_sort_t(const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status, void* keys_out,
                        int32_t* perm_out, void* ws, bool may_alloc, hipStream_t s) {
-  const BucketPlan p = bucket_plan(n, used_bits);
+  const BucketPlan p = bucket_plan(n, used_bits, false);
   const Ws<KeyT> w = carve<KeyT>(ws, n);
   Totals tot(p, w.fstart, 0, 1, may_alloc, s);
   // one element array (see REC): over keys1 and vals1 together, which lie one behind the other
@@ -1234,7 +1239,7 @@ int bucket_pack_sort(int key_bits, const int4* coords, int64_t n, const PackPara
 template <typename KeyT>
 static int mask_unique_t(const void* keys_in, int64_t n, const LevelJob* jobs, int n_levels, int used_bits, void* ws, size_t ws_pitch,
                          hipStream_t s) {
-  const BucketPlan p = bucket_plan(n, used_bits);
+  const BucketPlan p = bucket_plan(n, used_bits, true);
   const Ws<KeyT> w = carve<KeyT>(ws, n);
   SrcMasks<KeyT> src;
   LevelOut<KeyT> lo;

@@ -191,9 +191,9 @@ constexpr int BS_MAX_BIN = 1 << BS_MAX_BIN_BITS;  // fine bins (top used key bit
 constexpr int64_t BS_MIN_N = 4096, BS_MAX_N = 8192 * 1024;
 inline bool use_bucket_sort(int64_t n) { return n >= BS_MIN_N && n <= BS_MAX_N; }
 // Keys up to which the count pass adds its counts to the bins' totals, and how many a workgroup takes then.  Pack + sort, us, column
-// scan with 4096 keys per workgroup / this: LiDAR 20 k 16.2 / 13.3, 50 k 19.3 / 15.4, 120 k 24.9 / 20.6, 180 k 29.8 / 25.7; indoor 240 k
-// 34.9 / 32.7; random 300 k 35.5 / 32.5, 500 k 44.6 / 41.2.  Beyond, the table of 16384 bins would outgrow what is sorted.
-constexpr int64_t BS_ADD_N = 524288, BS_SHORT_N = 65536;
+// scan with 4096 keys per workgroup / this: LiDAR 20 k 16.2 / 13.3, 50 k 19.3 / 15.4, 120 k 25.2 / 20.5, 180 k 29.9 / 25.4; indoor 240 k
+// 34.8 / 31.7; random 300 k 35.4 / 30.3, 500 k 44.5 / 36.0.  Beyond, the table of 16384 bins would outgrow what is sorted.
+constexpr int64_t BS_ADD_N = 524288, BS_MID_N = 200000, BS_SHORT_N = 65536;
 constexpr int BS_ADD_SHARE = 2048, BS_SHORT_SHARE = 1024;
 constexpr int BS_PART = 64;         // keys per rank workgroup
 constexpr int BS_PAD_KEYS = 32;     // all-ones keys kept behind the scattered keys
@@ -201,7 +201,7 @@ struct BucketPlan {
   int n_wg, per, shift, n_bin;
   bool add;  // the count pass adds the counts up itself (no column scan)
 };
-BucketPlan bucket_plan(int64_t n, int used_bits);
+BucketPlan bucket_plan(int64_t n, int used_bits, bool unique);
 size_t bucket_sort_ws_bytes(int key_bits, int64_t n);
 // coords -> sorted keys (+ permutation); enqueues three kernels (count, scatter, rank), or four with the column scan of large inputs
 // or, where the library may not allocate, with the clearing of the totals
