@@ -27,7 +27,7 @@ def _check(c, keys, perm):
     assert np.array_equal(perm.cpu().numpy(), order)
 
 
-@pytest.mark.parametrize("n", [4096, 4097, 65_535, 65_536, 65_537, 524_288, 524_289])
+@pytest.mark.parametrize("n", [4096, 4097, 65_535, 65_536, 65_537, 200_000, 200_001, 524_288, 524_289])
 @pytest.mark.parametrize("key_bits", [0, 64])
 def test_sizes(n, key_bits):
     c = _cloud(n, n)
