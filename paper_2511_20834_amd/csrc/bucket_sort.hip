@@ -22,7 +22,7 @@
 // rejected unless validation was asked for) still get distinct positions and the permutation is
 // complete whatever the input.  Downsampling ranks the masked keys alone: equal keys fall on one
 // position, first arrivals are marked in a bitmap and counted per chunk with global atomics,
-// and a fifth kernel, compact, closes the gaps.
+// and one more kernel, compact, closes the gaps.
 #include <algorithm>
 #include <type_traits>
 
@@ -887,7 +887,7 @@ __global__ __launch_bounds__(BS_THREADS) void bs_rank_rest_kernel(const int32_t*
 // index, to their bin's range; and every key's final place is its bin's start plus the number of (key, index)
 // pairs of the bin that sort before it (the index breaks ties, so equal keys of an invalid cloud still get distinct
 // places).  The downsampling form writes the sorted keys back to LDS and keeps the first key of every run of equal
-// keys (a scan over the head flags).  One launch of a few microseconds where the large path has four (five) and a
+// keys (a scan over the head flags).  One launch of a few microseconds where the large path has three or four and a
 // library sort more; nothing but kernels is enqueued, so it can be recorded into a graph.  Work is quadratic in the
 // bin sizes: a cloud whose keys all share their top 12 used bits costs n^2 = 16 M comparisons at most.  (1024 bins: 4000 voxels
 // of surfaces 15 us, their stride-2 level with its map 29; 4096 bins: 11 and 20.)

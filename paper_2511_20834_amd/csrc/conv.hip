@@ -2,8 +2,9 @@
 // output-stationary and the weight-stationary dataflow (Section 2.2, Section 5.4).
 //
 // The per-offset contraction runs on the matrix cores: 32x32x16 MFMA for fp16 / bf16, 32x32x2 for fp32, with fp32
-// accumulators that stay in registers for all offsets of 32 output voxels.  Gathered feature rows go straight from
-// global memory (L2) into the MFMA A-operand registers: lane l needs 16 consecutive bytes of row l%32.
+// accumulators that stay in registers for all offsets of 32 output voxels.  A lane of the MFMA
+// wants 16 consecutive bytes of row l%32; rows are gathered from L2 several lanes to a row where that is faster, and change
+// places between lanes (phase kernel) or in LDS (split-k kernel) on their way there.
 // An offset is skipped for a 32-row block when no row has a valid entry: outputs are spatially sorted, so emptiness is
 // coherent (the map builder records it per block).
 // The dataflows differ in where a block's (input row, output row) pairs come from: the |V_q| x K^3 matrix (OS), the
