@@ -1108,7 +1108,9 @@ Ws<KeyT> carve(void* ws, int64_t n) {
   w.keys1 = reinterpret_cast<KeyT*>(c + k);
   w.vals1 = reinterpret_cast<int32_t*>(c + 2 * k);
   w.table = reinterpret_cast<int32_t*>(c + 2 * k + v);
-  const BucketPlan cap = bucket_plan(n, 64, true);  // as many workgroups and at least as many bins as any plan for n keys
+  // as many workgroups and at least as many bins as any plan for n keys (both forms of a plan have the same bins, that for levels
+  // the more workgroups)
+  const BucketPlan cap = bucket_plan(n, 64, true);
   const size_t tbl = (size_t(cap.n_wg) * cap.n_bin + 63) / 64 * 64;
   w.before = w.table + tbl;
   w.fstart = w.before + (cap.add ? 0 : tbl);
