@@ -13,8 +13,9 @@
  *     the calling thread's last error is available from spc_last_error().
  *   - Pointers marked [device] are device (HBM) addresses on the current HIP device,
  *     owned by the caller; [host] pointers are ordinary host memory.
- *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  Calls
- *     enqueue work on it and return without waiting unless stated otherwise.
+ *   - `stream` is a hipStream_t passed as void* (NULL = the default stream of the current
+ *     device, hipStreamPerThread = the calling thread's stream).  Calls enqueue work on it and
+ *     return without waiting unless stated otherwise.
  *   - Voxel indices are int32; a kernel map entry of -1 means "no input voxel".
  *   - The offset index of a K x K x K kernel is k = (ix*K + iy)*K + iz (z fastest,
  *     the group order of Section 5.2).  Per axis, index i stands for the offset

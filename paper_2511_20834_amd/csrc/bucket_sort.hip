@@ -1132,8 +1132,8 @@ struct Totals {
   int32_t* p = nullptr;
   size_t pitch = 0, bytes = 0;
   bool kept = false;
-  hipStream_t s;
-  Totals(const BucketPlan& plan, int32_t* in_ws, size_t ws_pitch, int n_levels, bool may_alloc, hipStream_t s_) : p(in_ws), pitch(ws_pitch), s(s_) {
+  StreamId s;
+  Totals(const BucketPlan& plan, int32_t* in_ws, size_t ws_pitch, int n_levels, bool may_alloc, const StreamId& s_) : p(in_ws), pitch(ws_pitch), s(s_) {
     if (!plan.add) return;
     bytes = size_t(plan.n_bin) * 4 * n_levels;
     if (may_alloc) p = static_cast<int32_t*>(zeroed_alloc(bytes, s));
@@ -1198,7 +1198,7 @@ size_t bucket_sort_ws_bytes(int key_bits, int64_t n) {
 
 template <typename KeyT>
 static int pack_sort_t(const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status, void* keys_out,
-                       int32_t* perm_out, void* ws, bool may_alloc, hipStream_t s) {
+                       int32_t* perm_out, void* ws, bool may_alloc, const StreamId& s) {
   const BucketPlan p = bucket_plan(n, used_bits, false);
   const Ws<KeyT> w = carve<KeyT>(ws, n);
   Totals tot(p, w.fstart, 0, 1, may_alloc, s);
@@ -1233,14 +1233,14 @@ static int pack_sort_t(const int4* coords, int64_t n, const PackParams& pp, int 
 }
 
 int bucket_pack_sort(int key_bits, const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status,
-                     void* keys_out, int32_t* perm_out, void* ws, bool may_alloc, hipStream_t s) {
+                     void* keys_out, int32_t* perm_out, void* ws, bool may_alloc, const StreamId& s) {
   return key_bits == 32 ? pack_sort_t<uint32_t>(coords, n, pp, used_bits, status, keys_out, perm_out, ws, may_alloc, s)
                         : pack_sort_t<uint64_t>(coords, n, pp, used_bits, status, keys_out, perm_out, ws, may_alloc, s);
 }
 
 template <typename KeyT>
 static int mask_unique_t(const void* keys_in, int64_t n, const LevelJob* jobs, int n_levels, int used_bits, void* ws, size_t ws_pitch,
-                         hipStream_t s) {
+                         const StreamId& s) {
   const BucketPlan p = bucket_plan(n, used_bits, true);
   const Ws<KeyT> w = carve<KeyT>(ws, n);
   SrcMasks<KeyT> src;
@@ -1266,7 +1266,7 @@ static int mask_unique_t(const void* keys_in, int64_t n, const LevelJob* jobs, i
 }
 
 int bucket_mask_unique(int key_bits, const void* keys_in, int64_t n, const LevelJob* jobs, int n_levels, int used_bits, void* ws,
-                       size_t ws_pitch, hipStream_t s) {
+                       size_t ws_pitch, const StreamId& s) {
   return key_bits == 32 ? mask_unique_t<uint32_t>(keys_in, n, jobs, n_levels, used_bits, ws, ws_pitch, s)
                         : mask_unique_t<uint64_t>(keys_in, n, jobs, n_levels, used_bits, ws, ws_pitch, s);
 }

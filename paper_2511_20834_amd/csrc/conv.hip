@@ -1503,7 +1503,7 @@ struct ConvArgs {
   int64_t rows_sel;  // best host-side estimate of the output rows: kernel selection and launch shape only
   KMask os_mask, ws_mask;  // offsets of the output-stationary / weight-stationary part
   bool any_os, any_ws;
-  hipStream_t s;
+  StreamId s;
 };
 
 // Whether the feature rows are more than the 32-bit offsets of buffer loads reach.
@@ -1869,7 +1869,7 @@ static int conv_entry(spc_kmap* m, const void* feats_in, int64_t ld_in, const vo
   a.n_out_d = ol->n_host < 0 ? ol->n_dev : nullptr;
   a.rows_cap = ol->n_host < 0 ? m->out_cap : ol->n_host;
   a.rows_sel = (ol->n_host < 0 && m->n_out_hint >= 0) ? std::min(m->n_out_hint, a.rows_cap) : a.rows_cap;
-  a.s = static_cast<hipStream_t>(stream);
+  a.s = StreamId(static_cast<hipStream_t>(stream));
   const StreamWorkNote note{a.s};
   // a map of a pipelined network build: nobody has joined its build stream, this stream waits for the map itself
   // (once per consumer stream: stream order covers the later layers that share the map)

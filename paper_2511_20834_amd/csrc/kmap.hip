@@ -909,7 +909,7 @@ static void kmap_free(spc_kmap* m) {
       m->nnz_dev = nullptr;
     }
     // whoever read this map may have read the twin's arrays: the twin's release waits for them as well
-    for (hipStream_t c : m->consumers) m->twin->consumers.push_back(c);
+    for (const StreamId& c : m->consumers) m->twin->consumers.push_back(c);
     m->twin->consumers.push_back(m->stream);
     spc_kmap* t = m->twin;
     m->twin = nullptr;
@@ -917,7 +917,10 @@ static void kmap_free(spc_kmap* m) {
   }
   // The arrays return to the build stream's cache, where the next build may take them at once: that
   // stream first waits for the feature kernels other streams have enqueued on this map.
-  for (hipStream_t c : m->consumers) order_stream_after(m->stream, c);
+  if (!m->consumers.empty()) {
+    const DeviceScope scope(m->stream.device);
+    for (const StreamId& c : m->consumers) order_stream_after(m->stream, c);
+  }
   pool_free(m->os_map, m->stream);
   pool_free(m->block_masks, m->stream);
   pool_free(m->ws_in, m->stream);
@@ -980,7 +983,7 @@ static int ilog2(int v) {
 }
 
 // Makes the map object for given input/output levels (references are taken) with its arrays; nothing is searched yet.
-static int prepare_map(Level* in, Level* out, const PackInfo& pi, const spc_layer_desc& l, hipStream_t s, spc_kmap** res,
+static int prepare_map(Level* in, Level* out, const PackInfo& pi, const spc_layer_desc& l, const StreamId& s, spc_kmap** res,
                        const int32_t* in_perm, bool want_inverse) {
   spc_kmap* m = new spc_kmap;
   m->in_perm = in_perm;
@@ -1007,7 +1010,6 @@ static int prepare_map(Level* in, Level* out, const PackInfo& pi, const spc_laye
   m->out_level = out;
   out->refs++;
   out->add_reader(s);
-  (void)hipGetDevice(&m->device);
   m->out_cap = out->n_host >= 0 ? out->n_host : out->cap;
   m->tile = search_tile(l.K, m->out_cap);
   m->n_tiles = static_cast<int>((m->out_cap + m->tile - 1) / m->tile);
@@ -1053,7 +1055,7 @@ static void launch_list_base(const spc_kmap* m, const int32_t* rows, int k_lim, 
 }
 
 // Searches and lists of prepared maps that agree in kernel size, tile length, key width and in whether they have lists.
-static int search_maps(spc_kmap* const* ms, int count, hipStream_t s) {
+static int search_maps(spc_kmap* const* ms, int count, const StreamId& s) {
   SPC_RETURN_IF(ms[0]->pi.key_bits == 32 ? launch_search_k<uint32_t>(ms, count, s) : launch_search_k<uint64_t>(ms, count, s));
   for (int i = 0; i < count; ++i) {
     spc_kmap* m = ms[i];
@@ -1085,7 +1087,7 @@ static int search_maps(spc_kmap* const* ms, int count, hipStream_t s) {
 }
 
 // One map, searched on its own.
-static int build_on_levels(Level* in, Level* out, const PackInfo& pi, const spc_layer_desc& l, hipStream_t s, spc_kmap** res,
+static int build_on_levels(Level* in, Level* out, const PackInfo& pi, const spc_layer_desc& l, const StreamId& s, spc_kmap** res,
                            const int32_t* in_perm = nullptr, bool want_inverse = false) {
   const StreamWorkNote note{s};
   spc_kmap* m = nullptr;
@@ -1111,7 +1113,7 @@ static bool twin_can_share(const spc_layer_desc& strided, const spc_layer_desc& 
 // the lists by taking the twin's with inputs and outputs swapped (for a fixed offset both index sequences ascend
 // together, so the order by output index is kept).  Returns SPC_ERR_UNSUPPORTED when the twin lacks what is needed.
 static int prepare_from_twin(spc_kmap* twin, Level* coarse, Level* fine, const PackInfo& pi, const spc_layer_desc& l,
-                             hipStream_t s, spc_kmap** res) {
+                             const StreamId& s, spc_kmap** res) {
   const bool with_os = (l.layout & SPC_LAYOUT_OS) != 0, with_ws = (l.layout & SPC_LAYOUT_WS) != 0;
   if (!twin_can_share(twin->desc, l) || (l.layout & ~SPC_LAYOUT_BOTH) || (with_os && !twin->inv_parent) ||
       (with_ws && (!(twin->desc.layout & SPC_LAYOUT_WS) || twin->hybrid_t || twin->sym)))
@@ -1131,7 +1133,6 @@ static int prepare_from_twin(spc_kmap* twin, Level* coarse, Level* fine, const P
   coarse->refs++;
   m->out_level = fine;
   fine->refs++;
-  (void)hipGetDevice(&m->device);
   m->out_cap = fine->n_host >= 0 ? fine->n_host : fine->cap;
   m->tile = search_tile(l.K, m->out_cap);
   m->n_tiles = static_cast<int>((m->out_cap + m->tile - 1) / m->tile);
@@ -1195,9 +1196,10 @@ static Level* borrowed_level(const void* keys, int64_t n, int stride) {
 }
 
 // Waits for what a build has enqueued on its stream (a stream that is being captured by now cannot be waited for on
-// its own: the device is drained).
-static int wait_stream(bool captured, hipStream_t s) {
-  if (captured || stream_is_capturing(s)) SPC_HIP_CHECK(hipDeviceSynchronize());
+// its own, nor another thread's hipStreamPerThread: the device is drained).
+static int wait_stream(bool captured, const StreamId& s) {
+  const DeviceScope scope(s.device);
+  if (captured || !s.here() || stream_is_capturing(s)) SPC_HIP_CHECK(hipDeviceSynchronize());
   else SPC_HIP_CHECK(hipStreamSynchronize(s));
   return SPC_OK;
 }
@@ -1222,7 +1224,8 @@ static bool poll_count(Level* lv, int* v) {
     }
     const auto waited = Clock::now() - start;
     if (waited < POLL_SPIN) continue;
-    if (stream_is_capturing(lv->stream)) return false;
+    if (!lv->stream.here() || stream_is_capturing(lv->stream)) return false;
+    const DeviceScope scope(lv->stream.device);
     const hipError_t e = hipStreamQuery(lv->stream);
     if (e != hipErrorNotReady) {
       (void)hipGetLastError();
@@ -1304,7 +1307,7 @@ struct NetBuild {
   }
 
   // The levels the layers [0, n) need and nobody has made yet.
-  int make_levels(const spc_layer_desc* layers, int n, hipStream_t s) {
+  int make_levels(const spc_layer_desc* layers, int n, const StreamId& s) {
     std::vector<int> ms;
     std::set<int> seen;
     for (int i = 0; i < n; ++i)
@@ -1321,7 +1324,7 @@ struct NetBuild {
   // map is searched by a launch of its own).
   // A transposed layer whose strided twin has been built on the same stream takes the twin's pairs; a strided
   // layer with such a transposed twin among the wanted maps leaves its inverse behind for it.
-  int make_maps(const spc_layer_desc* layers, int n, hipStream_t s, int most) {
+  int make_maps(const spc_layer_desc* layers, int n, const StreamId& s, int most) {
     const StreamWorkNote note{s};
     using Group = std::tuple<int, int, bool>;  // kernel size, tile length, lists
     std::vector<std::pair<Group, std::vector<spc_kmap*>>> groups;
@@ -1417,7 +1420,7 @@ int spc_build_kmap_perm(const void* in_keys, int64_t n_in, const int32_t* in_per
   if (!out) return set_error(SPC_ERR_ARG, "out is NULL");
   if (n_in < 0 || n_in > 0x7fffffff || (!in_keys && n_in > 0)) return set_error(SPC_ERR_ARG, "bad in_keys / n_in");
   if (int64_t(n_in) * l->K * l->K * l->K > (int64_t(1) << 40)) return set_error(SPC_ERR_ARG, "map too large");
-  hipStream_t s = static_cast<hipStream_t>(stream);
+  const StreamId s(static_cast<hipStream_t>(stream));
   Level* given = borrowed_level(in_keys, n_in, l->in_stride);
   Level* derived = nullptr;
   int rc = SPC_OK;
@@ -1451,7 +1454,7 @@ int spc_build_kmaps_network(const void* v0_keys, int64_t n0, const spc_pack_desc
   // each for levels and searches, the same launches were slower at every size measured (a replayed 25-layer UNet step,
   // three streams / one: 20 k voxels 378 / 316 us, 120 k 507 / 457, 200 k 610 / 568, 10^6 5339 / 5325): an edge between
   // two streams costs about 14 us, and the batched launches leave little to overlap.
-  hipStream_t s = static_cast<hipStream_t>(streams[0]);
+  const StreamId s(static_cast<hipStream_t>(streams[0]));
   NetBuild b(pi, v0_keys, n0, layers, n_layers);
   if (flags & SPC_NET_SEQUENTIAL) {  // a launch per level and per map, in the order of first use
     for (int i = 0; i < n_layers; ++i) {

@@ -164,7 +164,7 @@ __global__ __launch_bounds__(UQ_THREADS) void unique_write_kernel(const KeyT* __
 
 // One level of a size the library's own sort does not take.
 template <typename KeyT>
-static int downsample_t(const void* src, int64_t n, const PackInfo& pi, int m, Level* lv, hipStream_t s) {
+static int downsample_t(const void* src, int64_t n, const PackInfo& pi, int m, Level* lv, const StreamId& s) {
   if (n > 0) SPC_RETURN_IF(refuse_if_capturing(s, n));
   const size_t ksz = sizeof(KeyT);
   const size_t tb = sort_keys_temp_bytes(pi.key_bits, n);
@@ -203,7 +203,7 @@ static int downsample_t(const void* src, int64_t n, const PackInfo& pi, int m, L
 // Up to BS_MAX_LEVELS levels of one key array.  They share every launch where the library's own sort runs (a level's
 // five launches are bound by their launch and their dependent round trips at the sizes of a network: the four levels of
 // 120 k voxels took 20 launches and 110 us one after the other).
-static int downsample_batch(const void* src, int64_t n, const PackInfo& pi, const int* m, int count, Level** lv, hipStream_t s) {
+static int downsample_batch(const void* src, int64_t n, const PackInfo& pi, const int* m, int count, Level** lv, const StreamId& s) {
   const bool bucket = use_bucket_sort(n), small = n > 0 && n < BS_MIN_N;
   if (!bucket && !small) {
     for (int i = 0; i < count; ++i)
@@ -223,7 +223,7 @@ static int downsample_batch(const void* src, int64_t n, const PackInfo& pi, cons
 }
 
 int downsample_levels(const void* src_keys, int64_t n_src, const PackInfo& pi, const int* m, int count, Level** out,
-                      hipStream_t stream) {
+                      const StreamId& stream) {
   const StreamWorkNote note{stream};
   const bool captured = stream_is_capturing(stream);
   int rc = SPC_OK;
@@ -307,7 +307,7 @@ static int pack_coords(const int32_t* coords, int64_t n, const spc_pack_desc* d,
   }
   if (*workspace_bytes < need) return set_error(SPC_ERR_ARG, "workspace too small: %zu < %zu", *workspace_bytes, need);
   if (!coords || !keys_out) return set_error(SPC_ERR_ARG, "NULL coords or keys_out");
-  hipStream_t s = static_cast<hipStream_t>(stream);
+  const StreamId s(static_cast<hipStream_t>(stream));
   const bool small = n > 0 && n < BS_MIN_N;
   if (!bucket && !small && n > 0) SPC_RETURN_IF(refuse_if_capturing(s, n));
   char* ws = static_cast<char*>(workspace);

@@ -1,10 +1,11 @@
 // Host-side runtime of libspc: error reporting, the device block cache, packing
 // descriptors and coordinate-level bookkeeping.
 #include <algorithm>
+#include <atomic>
 #include <cstring>
 #include <map>
+#include <set>
 #include <unordered_map>
-#include <unordered_set>
 #include <utility>
 #include <vector>
 
@@ -22,6 +23,30 @@ int set_error(int code, const char* fmt, ...) {
   return code;
 }
 
+// ---------------------------------------------------------------- streams
+namespace {
+void thread_ended(uint32_t thread);
+// A number for every thread that has used hipStreamPerThread (never given twice); what the caches hold for the thread's
+// stream goes to the others when it ends.
+struct ThreadNumber {
+  uint32_t n;
+  ThreadNumber() {
+    static std::atomic<uint32_t> next{0};
+    n = ++next;
+  }
+  ~ThreadNumber() { thread_ended(n); }
+};
+uint32_t this_thread() {
+  static thread_local ThreadNumber t;
+  return t.n;
+}
+}  // namespace
+
+StreamId::StreamId(hipStream_t handle) : s(handle), thread(handle == hipStreamPerThread ? this_thread() : 0) {
+  if (hipGetDevice(&device) != hipSuccess) (void)hipGetLastError();
+}
+bool StreamId::here() const { return thread == 0 || thread == this_thread(); }
+
 // ---------------------------------------------------------------- block cache
 // Freed blocks are kept for reuse, binned by rounded size AND by the stream whose work
 // last touched them: a block is handed out again only to work enqueued on that same
@@ -30,10 +55,19 @@ int set_error(int code, const char* fmt, ...) {
 namespace {
 struct Pool {
   std::mutex mu;
-  std::map<std::pair<size_t, hipStream_t>, std::vector<void*>> free_blocks;
+  std::map<std::pair<size_t, StreamId>, std::vector<void*>> free_blocks;
   std::unordered_map<void*, size_t> live;  // block -> rounded size
-  std::map<std::pair<size_t, hipStream_t>, std::vector<void*>> zeroed;  // (live as far as the above is concerned)
+  std::map<std::pair<size_t, StreamId>, std::vector<void*>> zeroed;  // (live as far as the above is concerned)
   size_t n_zeroed = 0;
+  std::map<int, std::vector<std::pair<size_t, void*>>> ended;  // by device: free blocks of threads that are no more, with their sizes
+  bool take(size_t r, const StreamId& stream, void** p) {
+    auto it = free_blocks.find({r, stream});
+    if (it == free_blocks.end() || it->second.empty()) return false;
+    *p = it->second.back();
+    it->second.pop_back();
+    live[*p] = r;
+    return true;
+  }
 };
 Pool& pool() {
   static Pool* p = new Pool;  // never destroyed: device memory is reclaimed by the driver at exit
@@ -51,20 +85,33 @@ size_t round_size(size_t b) {
 }
 }  // namespace
 
-void* pool_alloc(size_t bytes, hipStream_t stream) {
+void* pool_alloc(size_t bytes, const StreamId& stream) {
   const size_t r = round_size(bytes);
   Pool& P = pool();
+  void* p = nullptr;
+  bool adopt = false;
   {
     std::lock_guard<std::mutex> lk(P.mu);
-    auto it = P.free_blocks.find({r, stream});
-    if (it != P.free_blocks.end() && !it->second.empty()) {
-      void* p = it->second.back();
-      it->second.pop_back();
-      P.live[p] = r;
-      return p;
-    }
+    if (P.take(r, stream, &p)) return p;
+    auto it = P.ended.find(stream.device);
+    adopt = it != P.ended.end() && !it->second.empty();
   }
-  void* p = nullptr;
+  // What an ended thread's stream has used is anybody's once the device has been drained.
+  if (adopt && !stream_is_capturing(stream)) {
+    std::vector<std::pair<size_t, void*>> blocks;
+    {
+      std::lock_guard<std::mutex> lk(P.mu);
+      blocks.swap(P.ended[stream.device]);
+    }
+    const bool idle = hipDeviceSynchronize() == hipSuccess;
+    if (!idle) (void)hipGetLastError();
+    std::lock_guard<std::mutex> lk(P.mu);
+    for (const auto& b : blocks) {
+      if (idle) P.free_blocks[{b.first, stream}].push_back(b.second);
+      else P.ended[stream.device].push_back(b);
+    }
+    if (P.take(r, stream, &p)) return p;
+  }
   hipError_t e = hipMalloc(&p, r);
   if (e != hipSuccess) {
     (void)hipGetLastError();
@@ -80,7 +127,7 @@ void* pool_alloc(size_t bytes, hipStream_t stream) {
   return p;
 }
 
-void pool_free(void* p, hipStream_t stream) {
+void pool_free(void* p, const StreamId& stream) {
   if (!p) return;
   Pool& P = pool();
   std::lock_guard<std::mutex> lk(P.mu);
@@ -98,8 +145,8 @@ __global__ __launch_bounds__(256) void clear_kernel(uint4* p, size_t n) {
 }
 }  // namespace
 
-void* zeroed_alloc(size_t bytes, hipStream_t stream) {
-  if (stream_is_capturing(stream)) return nullptr;
+void* zeroed_alloc(size_t bytes, const StreamId& stream) {
+  if (stream.thread != 0 || stream_is_capturing(stream)) return nullptr;
   const size_t r = round_size(bytes);
   Pool& P = pool();
   {
@@ -120,7 +167,7 @@ void* zeroed_alloc(size_t bytes, hipStream_t stream) {
   return nullptr;
 }
 
-void zeroed_free(void* p, size_t bytes, hipStream_t stream, bool clean) {
+void zeroed_free(void* p, size_t bytes, const StreamId& stream, bool clean) {
   Pool& P = pool();
   if (clean) {
     std::lock_guard<std::mutex> lk(P.mu);
@@ -141,9 +188,9 @@ namespace {
 // event every time.
 struct StreamOrder {
   std::mutex mu;
-  std::unordered_map<hipStream_t, uint64_t> work;
-  std::map<std::pair<hipStream_t, hipStream_t>, uint64_t> ordered;
-  std::unordered_set<hipStream_t> recorded;
+  std::map<StreamId, uint64_t> work;
+  std::map<std::pair<StreamId, StreamId>, uint64_t> ordered;
+  std::set<StreamId> recorded;
   bool all_recorded = false;  // more recorded streams than are worth remembering: every stream counts as one
 };
 StreamOrder& stream_order() {
@@ -153,7 +200,7 @@ StreamOrder& stream_order() {
 constexpr size_t MAX_TRACKED_STREAMS = 1024;
 }  // namespace
 
-void note_stream_work(hipStream_t s) {
+void note_stream_work(const StreamId& s) {
   const bool recording = stream_is_capturing(s);
   StreamOrder& O = stream_order();
   std::lock_guard<std::mutex> lk(O.mu);
@@ -166,8 +213,12 @@ void note_stream_work(hipStream_t s) {
   ++O.work[s];
 }
 
-void order_stream_after(hipStream_t waiter, hipStream_t producer) {
+void order_stream_after(const StreamId& waiter, const StreamId& producer) {
   if (waiter == producer) return;
+  if (!waiter.here() || !producer.here()) {
+    if (hipDeviceSynchronize() != hipSuccess) (void)hipGetLastError();
+    return;
+  }
   // (an order recorded into a graph says nothing about eager work, and the other way round)
   StreamOrder& O = stream_order();
   std::lock_guard<std::mutex> lk(O.mu);  // held until the wait is enqueued: whoever finds the entry may rely on it
@@ -196,7 +247,8 @@ constexpr size_t SLOT_PITCH = 64, SLOTS_PER_PAGE = 64;
 struct Slots {
   std::mutex mu;
   uint32_t next_tag = 0;
-  std::map<hipStream_t, std::vector<CountSlot>> free_slots;
+  std::map<StreamId, std::vector<CountSlot>> free_slots;
+  std::vector<CountSlot> ended;  // of threads that are no more (a late store of theirs carries another tag: the host then copies the count)
 };
 Slots& slots() {
   static Slots* p = new Slots;
@@ -204,10 +256,14 @@ Slots& slots() {
 }
 }  // namespace
 
-CountSlot count_slot_alloc(hipStream_t s) {
+CountSlot count_slot_alloc(const StreamId& s) {
   Slots& S = slots();
   std::lock_guard<std::mutex> lk(S.mu);
   std::vector<CountSlot>& v = S.free_slots[s];
+  if (v.empty() && !S.ended.empty()) {
+    v.push_back(S.ended.back());
+    S.ended.pop_back();
+  }
   if (v.empty()) {
     void *h = nullptr, *d = nullptr;
     if (hipHostMalloc(&h, SLOT_PITCH * SLOTS_PER_PAGE, hipHostMallocMapped | hipHostMallocCoherent | hipHostMallocPortable) != hipSuccess ||
@@ -231,31 +287,65 @@ CountSlot count_slot_alloc(hipStream_t s) {
   return c;
 }
 
-void count_slot_free(const CountSlot& c, hipStream_t s) {
+void count_slot_free(const CountSlot& c, const StreamId& s) {
   if (!c.host) return;
   Slots& S = slots();
   std::lock_guard<std::mutex> lk(S.mu);
   S.free_slots[s].push_back(c);
 }
 
+namespace {
+void thread_ended(uint32_t thread) {
+  {
+    Pool& P = pool();
+    std::lock_guard<std::mutex> lk(P.mu);
+    for (auto it = P.free_blocks.begin(); it != P.free_blocks.end();) {
+      const StreamId& id = it->first.second;
+      if (id.thread != thread) {
+        ++it;
+        continue;
+      }
+      for (void* b : it->second) P.ended[id.device].push_back({it->first.first, b});
+      it = P.free_blocks.erase(it);
+    }
+  }
+  Slots& S = slots();
+  std::lock_guard<std::mutex> lk(S.mu);
+  for (auto it = S.free_slots.begin(); it != S.free_slots.end();) {
+    if (it->first.thread != thread) {
+      ++it;
+      continue;
+    }
+    S.ended.insert(S.ended.end(), it->second.begin(), it->second.end());
+    it = S.free_slots.erase(it);
+  }
+}
+}  // namespace
+
 int pool_release_all() {
   Pool& P = pool();
-  std::vector<void*> blocks;
+  std::map<int, std::vector<void*>> blocks;  // by device
   {
     std::lock_guard<std::mutex> lk(P.mu);
     for (auto& kv : P.free_blocks)
-      for (void* b : kv.second) blocks.push_back(b);
+      for (void* b : kv.second) blocks[kv.first.second.device].push_back(b);
     P.free_blocks.clear();
     for (auto& kv : P.zeroed)
       for (void* b : kv.second) {
-        blocks.push_back(b);
+        blocks[kv.first.second.device].push_back(b);
         P.live.erase(b);
       }
     P.zeroed.clear();
     P.n_zeroed = 0;
+    for (auto& kv : P.ended)
+      for (const auto& b : kv.second) blocks[kv.first].push_back(b.second);
+    P.ended.clear();
   }
-  if (!blocks.empty()) (void)hipDeviceSynchronize();
-  for (void* b : blocks) (void)hipFree(b);
+  for (auto& kv : blocks) {
+    const DeviceScope scope(kv.first);
+    (void)hipDeviceSynchronize();
+    for (void* b : kv.second) (void)hipFree(b);
+  }
   return SPC_OK;
 }
 
@@ -312,8 +402,10 @@ void level_unref(Level* l) {
   if (l->refs.fetch_sub(1) == 1) {
     // the blocks go back to the producing stream's cache: that stream must not reuse them before the
     // searches that read the keys on other streams have finished
-    if (l->owns_keys || l->n_dev)
-      for (hipStream_t r : l->readers) order_stream_after(l->stream, r);
+    if (!l->readers.empty() && (l->owns_keys || l->n_dev)) {
+      const DeviceScope scope(l->stream.device);
+      for (const StreamId& r : l->readers) order_stream_after(l->stream, r);
+    }
     if (l->owns_keys) pool_free(l->keys, l->stream);
     pool_free(l->n_dev, l->stream);
     count_slot_free(l->slot, l->stream);

@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <memory>
 #include <mutex>
+#include <tuple>
 #include <vector>
 
 #include "spc.h"
@@ -29,29 +30,63 @@ int set_error(int code, const char* fmt, ...);
     if (rc__ != SPC_OK) return rc__; \
   } while (0)
 
+// ---------------------------------------------------------------- streams
+// What a stream handle stands for.  The handle alone does not say: the default stream's is the same on every device, and
+// hipStreamPerThread in every thread.  An entry point makes one of these from the handle it was given; what is remembered
+// (caches, levels, maps) remembers this.
+struct StreamId {
+  hipStream_t s = nullptr;
+  int device = 0;
+  uint32_t thread = 0;  // hipStreamPerThread: the number of its thread; else 0
+  StreamId() = default;
+  explicit StreamId(hipStream_t handle);  // on the current device, for the calling thread
+  operator hipStream_t() const { return s; }
+  bool here() const;  // whether the handle means this stream in the calling thread
+  bool operator==(const StreamId& o) const { return s == o.s && device == o.device && thread == o.thread; }
+  bool operator!=(const StreamId& o) const { return !(*this == o); }
+  bool operator<(const StreamId& o) const { return std::tie(s, device, thread) < std::tie(o.s, o.device, o.thread); }
+};
+// Makes a device the current one for a scope (releases may come from a thread that works on another).
+class DeviceScope {
+  int before_ = -1;
+
+ public:
+  explicit DeviceScope(int device) {
+    int now = device;
+    if (hipGetDevice(&now) == hipSuccess && now != device && hipSetDevice(device) == hipSuccess) before_ = now;
+  }
+  ~DeviceScope() {
+    if (before_ >= 0) (void)hipSetDevice(before_);
+  }
+  DeviceScope(const DeviceScope&) = delete;
+  DeviceScope& operator=(const DeviceScope&) = delete;
+};
+
 // ---------------------------------------------------------------- device block cache
 // hipMalloc costs tens of microseconds and synchronises; kernel maps are built per
 // frame, so freed blocks are kept and handed out again — only to work on the stream
 // that last used them, which makes stream order the only synchronisation needed.
-void* pool_alloc(size_t bytes, hipStream_t stream);  // nullptr on failure (error set)
-void pool_free(void* p, hipStream_t stream);
+void* pool_alloc(size_t bytes, const StreamId& stream);  // nullptr on failure (error set)
+void pool_free(void* p, const StreamId& stream);
 int pool_release_all();
 // Blocks that hold zeros between their uses: whoever takes one leaves it cleared by the last kernel it enqueues on the
 // stream (clean = false: it may not be).  As above, a block goes back to work on the same stream only; one that is taken is in nobody
 // else's hands until it is given back.  NULL while the stream is being captured (replays of the graph would share the block with
-// later calls), or when there is no memory.
-void* zeroed_alloc(size_t bytes, hipStream_t stream);
-void zeroed_free(void* p, size_t bytes, hipStream_t stream, bool clean);
+// later calls), for hipStreamPerThread (such blocks would pile up with the threads), or when there is no memory.
+void* zeroed_alloc(size_t bytes, const StreamId& stream);
+void zeroed_free(void* p, size_t bytes, const StreamId& stream, bool clean);
 // Makes everything enqueued on `waiter` from now on run after what `producer` holds at this moment
 // (an event recorded on `producer`; nothing happens when the two are the same stream, or when `waiter` has been
 // ordered behind `producer` before and the library has enqueued nothing on `producer` since and has never been recorded
-// into a graph there).  Used before a block goes back to the cache of a stream other than the one whose kernels last read it.
-void order_stream_after(hipStream_t waiter, hipStream_t producer);
+// into a graph there).  Where one of them is another thread's hipStreamPerThread, which cannot be reached from here, the device is
+// drained instead.  Used before a block goes back to the cache of a stream other than the one whose kernels last read it;
+// the streams' device is the current one.
+void order_stream_after(const StreamId& waiter, const StreamId& producer);
 // Every library call that enqueues kernels reading pooled blocks on `s` says so once they are enqueued, or recorded (an
 // order that another thread makes meanwhile is then made again): order_stream_after relies on it.
-void note_stream_work(hipStream_t s);
+void note_stream_work(const StreamId& s);
 struct StreamWorkNote {
-  hipStream_t s;
+  StreamId s;
   ~StreamWorkNote() { note_stream_work(s); }
 };
 
@@ -79,8 +114,8 @@ struct CountSlot {
   unsigned long long* dev = nullptr;
   uint32_t tag = 0;
 };
-CountSlot count_slot_alloc(hipStream_t s);  // host == nullptr when no pinned memory is to be had
-void count_slot_free(const CountSlot& c, hipStream_t s);
+CountSlot count_slot_alloc(const StreamId& s);  // host == nullptr when no pinned memory is to be had
+void count_slot_free(const CountSlot& c, const StreamId& s);
 
 // ---------------------------------------------------------------- packing
 struct PackInfo {
@@ -128,11 +163,11 @@ struct Level {
   CountSlot slot;         // where the host polls for the count (not for levels built under capture)
   bool announced = false; // a search that fills the slot has been enqueued
   int stride = 1;
-  hipStream_t stream = nullptr;  // stream the level was produced on
-  std::vector<hipStream_t> readers;  // other streams whose kernels read the keys (map searches)
-  void add_reader(hipStream_t s) {
+  StreamId stream;               // stream the level was produced on
+  std::vector<StreamId> readers; // other streams whose kernels read the keys (map searches)
+  void add_reader(const StreamId& s) {
     if (s == stream) return;
-    for (hipStream_t r : readers)
+    for (const StreamId& r : readers)
       if (r == s) return;
     readers.push_back(s);
   }
@@ -142,7 +177,7 @@ bool stream_is_capturing(hipStream_t s);
 
 // Derive the levels with strides 2^m[i] of `src_keys` (mask, sort, unique), out[i] for i < count.  Enqueues only.
 int downsample_levels(const void* src_keys, int64_t n_src, const PackInfo& pi, const int* m, int count, Level** out,
-                      hipStream_t stream);
+                      const StreamId& stream);
 
 // ---------------------------------------------------------------- packing (Section 5.3)
 struct PackParams {
@@ -206,7 +241,7 @@ size_t bucket_sort_ws_bytes(int key_bits, int64_t n);
 // coords -> sorted keys (+ permutation); enqueues three kernels (count, scatter, rank), or four with the column scan of large inputs
 // or, where the library may not allocate, with the clearing of the totals
 int bucket_pack_sort(int key_bits, const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status,
-                     void* keys_out, int32_t* perm_out, void* ws, bool may_alloc, hipStream_t s);
+                     void* keys_out, int32_t* perm_out, void* ws, bool may_alloc, const StreamId& s);
 // One level to produce: the sorted distinct values of keys_in & mask, and their count.
 constexpr int BS_MAX_LEVELS = 8;  // levels of one batch (the block rows of its launches)
 struct LevelJob {
@@ -216,7 +251,7 @@ struct LevelJob {
 };
 // n_levels <= BS_MAX_LEVELS levels of the same keys by the same five launches; level y works in ws + y * ws_pitch
 int bucket_mask_unique(int key_bits, const void* keys_in, int64_t n, const LevelJob* jobs, int n_levels, int used_bits, void* ws,
-                       size_t ws_pitch, hipStream_t s);
+                       size_t ws_pitch, const StreamId& s);
 
 // fewer than BS_MIN_N keys: one workgroup sorts them in LDS, one launch
 int small_pack_sort(int key_bits, const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status, void* keys_out,
@@ -238,7 +273,7 @@ namespace spc {
 // order covers the maps' later uses there).
 struct MapsReady {
   hipEvent_t e = nullptr;
-  hipStream_t last_waiter = nullptr;
+  StreamId last_waiter;
   ~MapsReady() {
     if (e) (void)hipEventDestroy(e);
   }
@@ -288,7 +323,6 @@ struct spc_kmap {
   int tile = 0, n_tiles = 0;
   std::vector<int64_t> nnz_host;    // filled lazily
   std::shared_ptr<spc::MapsReady> ready;  // set when nobody has joined the build stream: consumers on other streams wait for it
-  std::vector<hipStream_t> consumers;  // streams other than `stream` whose feature kernels have read the map
-  hipStream_t stream = nullptr;     // stream the map was built on
-  int device = 0;
+  std::vector<spc::StreamId> consumers;  // streams other than `stream` whose feature kernels have read the map
+  spc::StreamId stream;             // stream the map was built on
 };

@@ -1,0 +1,212 @@
+"""The library's host code on a stand-in for the HIP runtime (no GPU): which blocks of memory it hands to which stream, and
+what it makes wait for what.  A stream handle alone does not name a stream: the default stream's is the same on every device
+and hipStreamPerThread in every thread."""
+import ctypes
+import os
+import subprocess
+import threading
+import time
+
+import pytest
+
+from paper_2511_20834_amd import binding as B
+from paper_2511_20834_amd import build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+DEFAULT, PER_THREAD, OTHER = (ctypes.c_void_p(s) for s in (None, 2, 0x5000))
+SOURCES = ["runtime.hip", "pack_sort.hip", "bucket_sort.hip", "kmap.hip", "conv.hip"]
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    out = tmp_path_factory.mktemp("host")
+    cmd = [build.HIPCC, "--offload-host-only", "-O0", "-std=c++17", "-fPIC", "-I", os.path.join(build.ROOT, "include"), "-I", build.CSRC,
+           "-Wno-unused-result", "-c"]
+    objs, procs = [], []
+    for src in [os.path.join(build.CSRC, s) for s in SOURCES] + [os.path.join(HERE, "host", "hip_standin.cpp")]:
+        objs.append(str(out / (os.path.basename(src) + ".o")))
+        procs.append(subprocess.Popen([*cmd, "-x", "hip", src, "-o", objs[-1]]))
+    assert [p.wait() for p in procs] == [0] * len(procs)
+    lib = str(out / "libspc_host.so")
+    # (the device code's images, which nobody reads here)
+    undefined = subprocess.run(["nm", "-u", *objs], check=True, capture_output=True, text=True).stdout.split()
+    images = ["-Wl,--defsym=%s=0" % s for s in undefined if s.startswith("__hip_fatbin")]
+    subprocess.check_call(["g++", "-shared", "-Wl,-Bsymbolic", "-Wl,-z,defs", *images, *objs, "-o", lib])
+    L = ctypes.CDLL(lib)
+    L.standin_log.restype = ctypes.c_char_p
+    L.spc_kmap_os_map.restype = ctypes.c_void_p
+    return Host(L)
+
+
+class Host:
+    def __init__(self, L):
+        self.L = L
+        self.desc = B.PackDesc()
+        assert L.spc_pack_desc_fit((ctypes.c_int32 * 3)(0, 0, 0), (ctypes.c_int32 * 3)(500, 500, 100), 1, 4, 4, 32, ctypes.byref(self.desc)) == 0
+
+    def log(self):
+        return [l.split() for l in self.L.standin_log().decode().splitlines()]
+
+    def on(self, device):
+        self.L.standin_set_device(device)
+
+    def device_of(self, p):
+        return self.L.standin_device_of(ctypes.c_void_p(p))
+
+    def pack(self, n, stream):
+        """Sorts n coordinates; returns what was logged."""
+        coords, keys = ctypes.create_string_buffer(16 * n), ctypes.create_string_buffer(4 * n)
+        need = ctypes.c_size_t(0)
+        args = (ctypes.byref(need), 0, stream)
+        assert self.L.spc_pack_coords(coords, ctypes.c_int64(n), ctypes.byref(self.desc), keys, None, None, *args) == 0
+        ws = ctypes.create_string_buffer(need.value)
+        self.log()
+        assert self.L.spc_pack_coords(coords, ctypes.c_int64(n), ctypes.byref(self.desc), keys, None, ws, *args) == 0
+        return self.log()
+
+    def build(self, n, stream, layer_stride=1):
+        m = ctypes.c_void_p()
+        l = B.LayerDesc(3, 1, layer_stride, 0, B.LAYOUT_OS)
+        assert self.L.spc_build_kmap(ctypes.c_void_p(64), ctypes.c_int64(n), ctypes.byref(self.desc), ctypes.byref(l), ctypes.byref(m), stream) == 0
+        return m
+
+    def os_map(self, m):
+        return self.L.spc_kmap_os_map(m)
+
+    def forward(self, m, stream):
+        p = ctypes.c_void_p(64)
+        assert self.L.spc_conv_forward(m, p, ctypes.c_int64(32), p, p, ctypes.c_int64(32), 32, 32, 0, 0, 0, stream) == 0
+
+    def destroy(self, m):
+        self.L.spc_kmap_destroy(m)
+
+
+def in_thread(f):
+    """f's result, from a thread that has ended."""
+    got = []
+    t = threading.Thread(target=lambda: got.append(f()))
+    t.start()
+    t.join()
+    while os.path.exists("/proc/self/task/%d" % t.native_id):  # (join returns a little before the thread's own data are torn down)
+        time.sleep(0.001)
+    return got[0]
+
+
+def totals_of(log):
+    return [int(l[4]) for l in log if l[0] == "launch" and "bs_count_kernel" in l[3]][0]
+
+
+def cleared_first(log):
+    return any(l[0] == "launch" and "clear" in l[3] for l in log)
+
+
+@pytest.mark.parametrize("stream", [DEFAULT, PER_THREAD], ids=["default", "per thread"])
+def test_maps_stay_on_their_device(host, stream):
+    host.on(0)
+    m = host.build(5000, stream)
+    assert host.device_of(host.os_map(m)) == 0
+    host.destroy(m)
+    host.on(1)
+    m = host.build(5000, stream)
+    assert host.device_of(host.os_map(m)) == 1
+    host.on(0)  # released while another device is the current one
+    host.destroy(m)
+    m = host.build(5000, stream)
+    assert host.device_of(host.os_map(m)) == 0
+    host.destroy(m)
+
+
+def test_sort_totals_stay_on_their_device(host):
+    for device in (0, 1, 0, 1):
+        host.on(device)
+        log = host.pack(20_000, DEFAULT)
+        where = host.device_of(totals_of(log))
+        assert where == device or (where < 0 and cleared_first(log))  # (the caller's workspace is host memory here)
+    host.on(0)
+
+
+def test_per_thread_streams_share_nothing(host):
+    """Two threads' streams of the one handle have no order between them."""
+    mine = host.build(7000, PER_THREAD)
+    block = host.os_map(mine)
+    host.destroy(mine)  # free, for this thread's stream
+    go, done = threading.Event(), threading.Event()
+    got = []
+
+    def other():
+        host.on(0)
+        m = host.build(7000, PER_THREAD)
+        got.append(host.os_map(m))
+        host.destroy(m)
+        done.set()
+        go.wait()
+
+    t = threading.Thread(target=other)
+    t.start()
+    done.wait()
+    assert got[0] != block
+    again = host.build(7000, PER_THREAD)
+    assert host.os_map(again) == block
+    host.destroy(again)
+    go.set()
+    t.join()
+
+
+def test_sorts_on_per_thread_streams_share_no_totals(host):
+    """Neither one after the other nor through a block that was left behind: there is no order to rely on."""
+    for _ in range(2):
+        log = host.pack(9000, PER_THREAD)
+        assert cleared_first(log) and host.device_of(totals_of(log)) < 0
+        log = in_thread(lambda: host.pack(9000, PER_THREAD))
+        assert cleared_first(log) and host.device_of(totals_of(log)) < 0
+
+
+def test_blocks_of_ended_threads_come_back_after_a_drain(host):
+    def left_behind():
+        host.on(0)
+        m = host.build(300_000, PER_THREAD)
+        p = host.os_map(m)
+        host.destroy(m)
+        return p
+
+    p = in_thread(left_behind)
+    host.log()
+    m = host.build(300_000, OTHER)
+    assert host.os_map(m) == p and ["drain", "0"] in host.log()
+    host.destroy(m)
+
+
+def test_map_of_another_threads_stream_is_released_behind_a_drain(host):
+    """Its stream, or a consumer's, cannot be waited for from here."""
+    m = host.build(6000, OTHER)
+    in_thread(lambda: host.forward(m, PER_THREAD))
+    host.log()
+    host.destroy(m)
+    assert ["drain", "0"] in host.log()
+    m = in_thread(lambda: host.build(6000, PER_THREAD))
+    host.forward(m, OTHER)
+    host.log()
+    host.destroy(m)
+    assert ["drain", "0"] in host.log()
+
+
+def test_count_of_another_threads_level_is_waited_for(host):
+    m = in_thread(lambda: host.build(6000, PER_THREAD, 2))
+    host.log()
+    host.L.spc_kmap_n_out.restype = ctypes.c_int64
+    assert host.L.spc_kmap_n_out(m) == 0  # (nothing runs here: the count is the zero the memory started with)
+    assert ["drain", "0"] in host.log()
+    host.destroy(m)
+
+
+def test_releases_on_two_devices_wait_each(host):
+    """What the default stream of one device has been ordered behind says nothing about the other's."""
+    for device in (0, 1):
+        host.on(device)
+        m = host.build(6000, DEFAULT)
+        host.forward(m, OTHER)
+        host.log()
+        host.on(0)
+        host.destroy(m)
+        waits = [l for l in host.log() if l[0] == "wait"]
+        assert len(waits) == 1 and waits[0][1] == str(device) and waits[0][2] == "0", waits
