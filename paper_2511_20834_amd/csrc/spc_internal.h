@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <memory>
 #include <mutex>
+#include <optional>
 #include <tuple>
 #include <vector>
 
@@ -273,7 +274,7 @@ namespace spc {
 // order covers the maps' later uses there).
 struct MapsReady {
   hipEvent_t e = nullptr;
-  StreamId last_waiter;
+  std::optional<StreamId> last_waiter;  // (none at first: the default stream is one like any other)
   ~MapsReady() {
     if (e) (void)hipEventDestroy(e);
   }

@@ -210,3 +210,17 @@ def test_releases_on_two_devices_wait_each(host):
         host.destroy(m)
         waits = [l for l in host.log() if l[0] == "wait"]
         assert len(waits) == 1 and waits[0][1] == str(device) and waits[0][2] == "0", waits
+
+
+@pytest.mark.parametrize("stream", [DEFAULT, PER_THREAD], ids=["default", "per thread"])
+def test_pipelined_maps_are_waited_for_once_per_stream(host, stream):
+    """By the first layer on every stream but the build's, the default stream included."""
+    layer, m, streams = B.LayerDesc(3, 1, 1, 0, B.LAYOUT_OS), ctypes.c_void_p(), (ctypes.c_void_p * 1)(OTHER)
+    assert host.L.spc_build_kmaps_network(ctypes.c_void_p(64), ctypes.c_int64(5000), ctypes.byref(host.desc), ctypes.byref(layer), 1,
+                                          ctypes.byref(m), streams, 1, B.NET_PIPELINED) == 0
+    for waits in (1, 0):
+        host.log()
+        host.forward(m, stream)
+        log = [l for l in host.log() if l[0] in ("wait", "launch")]
+        assert [l[0] for l in log] == ["wait"] * waits + ["launch"] and int(log[0][2]) == (stream.value or 0)
+    host.destroy(m)
