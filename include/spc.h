@@ -112,7 +112,10 @@ int spc_pack_desc_fit(const int32_t lo[3], const int32_t hi[3], int32_t n_batch,
  *   perm_out    [device] n int32, may be NULL: keys_out[r] is the key of input row
  *               perm_out[r]; the caller gathers feature rows with it once.
  *   workspace   [device] scratch; call with workspace == NULL to get the size needed
- *               in *workspace_bytes (nothing is enqueued then).
+ *               in *workspace_bytes (nothing is enqueued then).  No device memory is allocated
+ *               besides (the library's image holds 2 MiB per GPU of which a stream that sorts
+ *               keeps a few KB), so the call may be made while another thread records a graph
+ *               (not with SPC_PACK_VALIDATE, which waits).
  *   flags       SPC_PACK_VALIDATE: wait for the stream and return SPC_ERR_RANGE /
  *               SPC_ERR_DUP if a row does not fit its field or occurs twice.  Without
  *               it nothing is waited for: a row that does not fit gets the all-ones key

@@ -1126,8 +1126,8 @@ Ws<KeyT> carve(void* ws, int64_t n) {
 }
 
 // The bins' totals of a sort: in a block that the library keeps cleared between its sorts (the last kernel clears it again),
-// or, where none is to be had (under capture, whose replays know nothing of other sorts; for callers that forbid
-// allocation), in the workspace, cleared by a kernel of its own.
+// or, where none is to be had (under capture, whose replays know nothing of other sorts; on hipStreamPerThread; once the blocks of
+// the library's image are in use on other streams), in the workspace, cleared by a kernel of its own.
 struct Totals {
   int32_t* p = nullptr;
   size_t pitch = 0, bytes = 0;
@@ -1136,13 +1136,12 @@ struct Totals {
   Totals(const BucketPlan& plan, int32_t* in_ws, size_t ws_pitch, int n_levels, bool may_alloc, const StreamId& s_) : p(in_ws), pitch(ws_pitch), s(s_) {
     if (!plan.add) return;
     bytes = size_t(plan.n_bin) * 4 * n_levels;
-    if (may_alloc) p = static_cast<int32_t*>(zeroed_alloc(bytes, s));
-    kept = may_alloc && p;
-    if (kept) {
+    if (void* zeros = zeroed_alloc(bytes, s, may_alloc)) {
+      p = static_cast<int32_t*>(zeros);
       pitch = size_t(plan.n_bin) * 4;
+      kept = true;
       return;
     }
-    p = in_ws;
     hipLaunchKernelGGL(bs_clear_kernel, dim3((plan.n_bin + BS_THREADS - 1) / BS_THREADS, n_levels), dim3(BS_THREADS), 0, s, p, plan.n_bin, pitch);
   }
   int32_t* to_clear() const { return kept ? p : nullptr; }
@@ -1198,10 +1197,10 @@ size_t bucket_sort_ws_bytes(int key_bits, int64_t n) {
 
 template <typename KeyT>
 static int pack_sort_t(const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status, void* keys_out,
-                       int32_t* perm_out, void* ws, bool may_alloc, const StreamId& s) {
+                       int32_t* perm_out, void* ws, const StreamId& s) {
   const BucketPlan p = bucket_plan(n, used_bits, false);
   const Ws<KeyT> w = carve<KeyT>(ws, n);
-  Totals tot(p, w.fstart, 0, 1, may_alloc, s);
+  Totals tot(p, w.fstart, 0, 1, false, s);
   // one element array (see REC): over keys1 and vals1 together, which lie one behind the other
   constexpr bool REC = sizeof(KeyT) == 4;
   const SrcPack<KeyT> src{coords, pp, status};
@@ -1233,9 +1232,9 @@ static int pack_sort_t(const int4* coords, int64_t n, const PackParams& pp, int 
 }
 
 int bucket_pack_sort(int key_bits, const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status,
-                     void* keys_out, int32_t* perm_out, void* ws, bool may_alloc, const StreamId& s) {
-  return key_bits == 32 ? pack_sort_t<uint32_t>(coords, n, pp, used_bits, status, keys_out, perm_out, ws, may_alloc, s)
-                        : pack_sort_t<uint64_t>(coords, n, pp, used_bits, status, keys_out, perm_out, ws, may_alloc, s);
+                     void* keys_out, int32_t* perm_out, void* ws, const StreamId& s) {
+  return key_bits == 32 ? pack_sort_t<uint32_t>(coords, n, pp, used_bits, status, keys_out, perm_out, ws, s)
+                        : pack_sort_t<uint64_t>(coords, n, pp, used_bits, status, keys_out, perm_out, ws, s);
 }
 
 template <typename KeyT>

@@ -285,9 +285,8 @@ int noalloc_scratch(void** out) {
 }  // namespace spc
 
 namespace spc {
-// (may_alloc: the library may take device memory of its own besides the workspace)
 static int pack_coords(const int32_t* coords, int64_t n, const spc_pack_desc* d, void* keys_out, int32_t* perm_out, void* workspace,
-                       size_t* workspace_bytes, int32_t flags, bool may_alloc, void* stream) {
+                       size_t* workspace_bytes, int32_t flags, void* stream) {
   PackInfo pi;
   SPC_RETURN_IF(check_desc(d, &pi));
   if (n < 0 || n > 0x7fffffff) return set_error(SPC_ERR_ARG, "n out of range");
@@ -321,7 +320,7 @@ static int pack_coords(const int32_t* coords, int64_t n, const spc_pack_desc* d,
   if (status) hipLaunchKernelGGL(set_int_kernel, dim3(1), dim3(1), 0, s, status, 0);
   if (bucket) {
     SPC_RETURN_IF(bucket_pack_sort(pi.key_bits, reinterpret_cast<const int4*>(coords), n, p, pi.used_bits, status, keys_out, perm_out,
-                                   ws + off_temp, may_alloc, s));
+                                   ws + off_temp, s));
     if (flags & SPC_PACK_VALIDATE) {
       const int grid = static_cast<int>((n + 255) / 256);
       if (pi.key_bits == 32)
@@ -371,7 +370,7 @@ static int pack_coords(const int32_t* coords, int64_t n, const spc_pack_desc* d,
 
 extern "C" int spc_pack_coords(const int32_t* coords, int64_t n, const spc_pack_desc* d, void* keys_out, int32_t* perm_out,
                                void* workspace, size_t* workspace_bytes, int32_t flags, void* stream) {
-  return spc::pack_coords(coords, n, d, keys_out, perm_out, workspace, workspace_bytes, flags, true, stream);
+  return spc::pack_coords(coords, n, d, keys_out, perm_out, workspace, workspace_bytes, flags, stream);
 }
 
 extern "C" int spc_pack_coords_noalloc(const int32_t* coords, int64_t n, const spc_pack_desc* d, void* keys_out,
@@ -390,7 +389,7 @@ extern "C" int spc_pack_coords_noalloc(const int32_t* coords, int64_t n, const s
   void* ws = nullptr;
   SPC_RETURN_IF(noalloc_scratch(&ws));
   size_t have = NOALLOC_SCRATCH_BYTES;
-  // every part of the scratch that is read is written first by the kernels of the same call (the
-  // status word and the bins' totals by kernels of their own), so nothing of the previous call's contents matters
-  return pack_coords(coords, n, d, keys_out, perm_out, ws, &have, flags, false, stream);
+  // every part of the scratch that is read is written first by the kernels of the same call (the status word, and the bins'
+  // totals where they lie there, by kernels of their own), so nothing of the previous call's contents matters
+  return pack_coords(coords, n, d, keys_out, perm_out, ws, &have, flags, stream);
 }

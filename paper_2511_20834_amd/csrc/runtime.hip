@@ -53,12 +53,23 @@ bool StreamId::here() const { return thread == 0 || thread == this_thread(); }
 // stream, so stream order alone guarantees that the previous user has finished (blocks
 // are returned right after the kernels that use them were enqueued, not after they ran).
 namespace {
+// Part of the library's image, on every device: blocks for zeroed_alloc that need no allocation.  A sort of up to half a million
+// coordinates takes 4 to 32 KB per stream.
+constexpr size_t IMAGE_BYTES = size_t(2) << 20, IMAGE_MOST = size_t(32) << 10;
+__device__ __align__(256) unsigned char image_zeros[IMAGE_BYTES];
+struct Image {
+  char* base = nullptr;
+  size_t used = 0;  // from the start
+  int taken = 0;    // blocks in somebody's hands
+  bool holds(const void* p) const { return base && p >= base && p < base + IMAGE_BYTES; }
+};
 struct Pool {
   std::mutex mu;
   std::map<std::pair<size_t, StreamId>, std::vector<void*>> free_blocks;
   std::unordered_map<void*, size_t> live;  // block -> rounded size
   std::map<std::pair<size_t, StreamId>, std::vector<void*>> zeroed;  // (live as far as the above is concerned)
-  size_t n_zeroed = 0;
+  size_t n_zeroed = 0;  // of them from the cache
+  std::map<int, Image> images;  // by device
   std::map<int, std::vector<std::pair<size_t, void*>>> ended;  // by device: free blocks of threads that are no more, with their sizes
   bool take(size_t r, const StreamId& stream, void** p) {
     auto it = free_blocks.find({r, stream});
@@ -145,20 +156,34 @@ __global__ __launch_bounds__(256) void clear_kernel(uint4* p, size_t n) {
 }
 }  // namespace
 
-void* zeroed_alloc(size_t bytes, const StreamId& stream) {
+void* zeroed_alloc(size_t bytes, const StreamId& stream, bool may_alloc) {
   if (stream.thread != 0 || stream_is_capturing(stream)) return nullptr;
   const size_t r = round_size(bytes);
   Pool& P = pool();
   {
     std::lock_guard<std::mutex> lk(P.mu);
+    Image& image = P.images[stream.device];
     auto it = P.zeroed.find({r, stream});
     if (it != P.zeroed.end() && !it->second.empty()) {
       void* p = it->second.back();
       it->second.pop_back();
-      --P.n_zeroed;
+      if (image.holds(p)) ++image.taken;
+      else --P.n_zeroed;
+      return p;
+    }
+    if (!image.base && r <= IMAGE_MOST) {
+      void* p = nullptr;
+      if (hipGetSymbolAddress(&p, HIP_SYMBOL(image_zeros)) == hipSuccess) image.base = static_cast<char*>(p);
+      else (void)hipGetLastError();
+    }
+    if (image.base && r <= IMAGE_MOST && image.used + r <= IMAGE_BYTES) {
+      void* p = image.base + image.used;
+      image.used += r;
+      ++image.taken;
       return p;
     }
   }
+  if (!may_alloc) return nullptr;
   void* p = pool_alloc(r, stream);
   if (!p) return nullptr;
   hipLaunchKernelGGL(clear_kernel, dim3(static_cast<unsigned>((r / 16 + 255) / 256)), dim3(256), 0, stream, static_cast<uint4*>(p), r / 16);
@@ -169,11 +194,15 @@ void* zeroed_alloc(size_t bytes, const StreamId& stream) {
 
 void zeroed_free(void* p, size_t bytes, const StreamId& stream, bool clean) {
   Pool& P = pool();
-  if (clean) {
+  {
     std::lock_guard<std::mutex> lk(P.mu);
-    if (P.n_zeroed < MAX_ZEROED) {
+    Image& image = P.images[stream.device];
+    const bool in_image = image.holds(p);
+    if (in_image && !clean) return;  // (counts as taken for good)
+    if (clean && (in_image || P.n_zeroed < MAX_ZEROED)) {
       P.zeroed[{round_size(bytes), stream}].push_back(p);
-      ++P.n_zeroed;
+      if (in_image) --image.taken;
+      else ++P.n_zeroed;
       return;
     }
   }
@@ -325,17 +354,32 @@ void thread_ended(uint32_t thread) {
 int pool_release_all() {
   Pool& P = pool();
   std::map<int, std::vector<void*>> blocks;  // by device
+  std::set<int> images;                      // whose blocks go back to the image
   {
     std::lock_guard<std::mutex> lk(P.mu);
     for (auto& kv : P.free_blocks)
       for (void* b : kv.second) blocks[kv.first.second.device].push_back(b);
     P.free_blocks.clear();
-    for (auto& kv : P.zeroed)
-      for (void* b : kv.second) {
-        blocks[kv.first.second.device].push_back(b);
-        P.live.erase(b);
+    for (auto& kv : P.images)
+      if (kv.second.used > 0 && kv.second.taken == 0) {
+        images.insert(kv.first);
+        blocks[kv.first];
+        kv.second.used = IMAGE_BYTES;  // (nobody takes any before the device has been drained)
       }
-    P.zeroed.clear();
+    for (auto it = P.zeroed.begin(); it != P.zeroed.end();) {
+      const int device = it->first.second.device;
+      std::vector<void*> kept;
+      for (void* b : it->second) {
+        if (!P.images[device].holds(b)) {
+          blocks[device].push_back(b);
+          P.live.erase(b);
+        } else if (!images.count(device)) {
+          kept.push_back(b);
+        }
+      }
+      it->second.swap(kept);
+      it = it->second.empty() ? P.zeroed.erase(it) : std::next(it);
+    }
     P.n_zeroed = 0;
     for (auto& kv : P.ended)
       for (const auto& b : kv.second) blocks[kv.first].push_back(b.second);
@@ -343,8 +387,11 @@ int pool_release_all() {
   }
   for (auto& kv : blocks) {
     const DeviceScope scope(kv.first);
-    (void)hipDeviceSynchronize();
+    const bool idle = hipDeviceSynchronize() == hipSuccess;
     for (void* b : kv.second) (void)hipFree(b);
+    if (!images.count(kv.first) || !idle) continue;
+    std::lock_guard<std::mutex> lk(P.mu);
+    P.images[kv.first].used = 0;
   }
   return SPC_OK;
 }

@@ -74,7 +74,10 @@ int pool_release_all();
 // stream (clean = false: it may not be).  As above, a block goes back to work on the same stream only; one that is taken is in nobody
 // else's hands until it is given back.  NULL while the stream is being captured (replays of the graph would share the block with
 // later calls), for hipStreamPerThread (such blocks would pile up with the threads), or when there is no memory.
-void* zeroed_alloc(size_t bytes, const StreamId& stream);
+// Small blocks come from memory that is part of the library's image; may_alloc: others, and what does not fit there, from the cache.
+// Without it the call asks the runtime for no memory (a request would be refused, and end the recording, while another thread
+// records a graph in the global mode).
+void* zeroed_alloc(size_t bytes, const StreamId& stream, bool may_alloc);
 void zeroed_free(void* p, size_t bytes, const StreamId& stream, bool clean);
 // Makes everything enqueued on `waiter` from now on run after what `producer` holds at this moment
 // (an event recorded on `producer`; nothing happens when the two are the same stream, or when `waiter` has been
@@ -240,9 +243,9 @@ struct BucketPlan {
 BucketPlan bucket_plan(int64_t n, int used_bits, bool unique);
 size_t bucket_sort_ws_bytes(int key_bits, int64_t n);
 // coords -> sorted keys (+ permutation); enqueues three kernels (count, scatter, rank), or four with the column scan of large inputs
-// or, where the library may not allocate, with the clearing of the totals
+// or, where there is no cleared block for the totals, with their clearing.  Asks for no device memory.
 int bucket_pack_sort(int key_bits, const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status,
-                     void* keys_out, int32_t* perm_out, void* ws, bool may_alloc, const StreamId& s);
+                     void* keys_out, int32_t* perm_out, void* ws, const StreamId& s);
 // One level to produce: the sorted distinct values of keys_in & mask, and their count.
 constexpr int BS_MAX_LEVELS = 8;  // levels of one batch (the block rows of its launches)
 struct LevelJob {

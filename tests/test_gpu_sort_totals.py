@@ -92,3 +92,36 @@ def test_replays_between_eager_sorts():
         torch.cuda.synchronize()
         _check(b, kb, pb)
         _check(a, keys, perm)
+
+
+def test_first_sort_of_a_size_while_another_thread_records():
+    """The sort asks for no memory, which would be refused and end the recording."""
+    warm, c = _cloud(9001, 3), _cloud(400_009, 4)
+    B.spc_pack_coords(torch.from_numpy(warm).cuda(), fit_desc(warm, [(3, 1, 1)]))  # (the library is loaded)
+    B.spc_release_cache()
+    desc, d = fit_desc(c, [(3, 1, 1)]), torch.from_numpy(c).cuda()
+    ws = torch.empty(B.spc_pack_workspace_bytes(len(c), desc), dtype=torch.uint8, device="cuda")
+    keys, perm = torch.empty(len(c), dtype=torch.int32, device="cuda"), torch.empty(len(c), dtype=torch.int32, device="cuda")
+    x, side, own = torch.zeros(1000, device="cuda"), torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    failed = []
+
+    def sort():
+        try:
+            B.spc_pack_coords(d, desc, True, 0, own, ws, keys, perm)
+        except Exception as e:
+            failed.append(repr(e))
+
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side, capture_error_mode="global"):
+        x.add_(1.0)
+        t = threading.Thread(target=sort)
+        t.start()
+        t.join()
+    assert not failed, failed
+    torch.cuda.synchronize()
+    _check(c, keys, perm)
+    for i in range(1, 4):
+        g.replay()
+        torch.cuda.synchronize()
+        assert bool((x == i).all())

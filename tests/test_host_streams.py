@@ -224,3 +224,23 @@ def test_pipelined_maps_are_waited_for_once_per_stream(host, stream):
         log = [l for l in host.log() if l[0] in ("wait", "launch")]
         assert [l[0] for l in log] == ["wait"] * waits + ["launch"] and int(log[0][2]) == (stream.value or 0)
     host.destroy(m)
+
+
+def test_sorts_ask_for_no_memory(host):
+    """The caller has brought a workspace.  Once the image's blocks are all in use on other streams, the totals lie in there."""
+    host.on(2)
+    streams = [ctypes.c_void_p(0x10000 + 16 * i) for i in range(80)]
+    for n in (4096, 20_000, 200_000, 300_000, 524_288, 600_000):  # 1 to 32 KB of totals, and none (column scan)
+        logs = [host.pack(n, s) for s in streams]
+        assert not any(l[0] in ("malloc", "free", "drain") for log in logs for l in log)
+        if n > 524_288:
+            break
+        for log in logs:
+            assert host.device_of(totals_of(log)) == (-1 if cleared_first(log) else 2)
+        held = [totals_of(log) for log in logs if not cleared_first(log)]
+        assert len(set(held)) == len(held)  # a block of its own for every stream
+    assert all(cleared_first(host.pack(300_000, s)) for s in streams[70:])  # (no room left)
+    host.L.spc_release_cache()
+    assert not any(cleared_first(host.pack(300_000, s)) for s in streams[70:])
+    host.L.spc_release_cache()
+    host.on(0)
