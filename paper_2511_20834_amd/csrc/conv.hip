@@ -815,7 +815,9 @@ __global__ __launch_bounds__(64 * WAVES) void conv_os_phase_kernel(const int32_t
 // What a wave reads (AM): 16-byte pieces of rows (A_VEC); the same with a channel count that ends inside the last slab
 // (A_RAGGED); rows that are not 16-byte aligned or end inside a piece, one channel at a time (A_ELEM); four-channel rows
 // (A_QUAD), where a 16-channel slab holds four offsets instead of one offset and twelve zeros; features or weights of more
-// than 2 GB, which the 32-bit offsets of buffer loads do not reach (A_WIDE).
+// than 2 GB, which the 32-bit offsets of buffer loads do not reach (A_WIDE).  One channel at a time, prepacked weights are reached
+// at any distance by A_ELEM and plain ones by A_WIDE.  (A resource that starts at the fragment costs packed weights nothing; plain
+// ones, of which a lane loads a channel at a time, 20 to 50 %.)
 constexpr int SPLITK_WAVES = 4;
 constexpr int SPLITK_CHUNK = 16;  // offsets of a wave whose rows are in LDS at a time (large kernels and lists)
 enum { A_VEC = 0, A_RAGGED = 1, A_ELEM = 2, A_QUAD = 3, A_WIDE = 4 };
@@ -842,6 +844,7 @@ struct SplitkArgs {
   int mask_words, n_out_h, K3, cin, cout, relu, nb_total, vec_store;
   uint32_t row_bytes;  // pitch of the feature rows
   uint32_t w_bytes;    // of the weights, as given
+  int by_channel;      // (A_WIDE, plain weights) rows are read one channel at a time
   int has_os;          // lists: some offsets come from the matrix
   int log_share;       // log2 of a workgroup's waves that share a tile
   int log_waves;       // the same with the waves of other workgroups that share it
@@ -1230,7 +1233,7 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, PACKED ? splitk_occupancy(NB, FR
           } else {
             const int c0 = (g_n * (2 * GS) + lane_piece) * LPC;
             const T* src = F + int64_t(pos_n[u]) * ld_in + c0;
-            if constexpr (AM == A_ELEM) {
+            if (AM == A_ELEM || (AM == A_WIDE && !PACKED && a.by_channel)) {
 #pragma unroll
               for (int j = 0; j < LPC; ++j) av[E][u][j] = *(pos_n[u] < 0 || c0 + j >= cin ? zero_row : src + j);
             } else {
@@ -1242,7 +1245,12 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, PACKED ? splitk_occupancy(NB, FR
       auto issue_weights = [&](auto E_, auto S_) {  // slab S of group g_n of offset k_n
         constexpr int E = decltype(E_)::value, S = decltype(S_)::value;
         const int kk = min(GS * g_n + S, KK - 1), k = weight_k(k_n);
-        if constexpr (PACKED && AM != A_WIDE) {
+        if constexpr (PACKED && AM == A_ELEM) {
+          const T* w = W + ((int64_t(k) * KK + kk) * nb_total + slab * NB) * 512;  // uniform
+          const __amdgpu_buffer_rsrc_t here_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(w), 0, NB * 1024, 0x00020000);
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) bv[E][S][nb] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(here_rsrc, lane_off + nb * 1024, 0, 0));
+        } else if constexpr (PACKED && AM != A_WIDE) {
           const unsigned w = ((unsigned(k) * KK + kk) * nb_total + slab * NB) * 1024u;  // uniform
 #pragma unroll
           for (int nb = 0; nb < NB; ++nb) bv[E][S][nb] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, lane_off + nb * 1024, w, 0));
@@ -1553,11 +1561,17 @@ static void launch_os_mfma(const ConvArgs& a, const T* Wp) {
   else go(std::integral_constant<int, 1>{});
 }
 
+// Whether the feature rows cannot be read in pieces of 16 bytes.
+template <typename T>
+static bool by_channel(const ConvArgs& a) {
+  constexpr int LPC = Mfma<T>::LPC;
+  return a.ld_in % LPC != 0 || reinterpret_cast<uintptr_t>(a.F) % 16 != 0 || a.cin % LPC != 0;
+}
+
 // Whether the feature rows are as the vector loads and whole slabs of the split-k and phase kernels want them.
 template <typename T>
 static bool plain_rows(const ConvArgs& a) {
-  constexpr int LPC = Mfma<T>::LPC;
-  return a.ld_in % LPC == 0 && reinterpret_cast<uintptr_t>(a.F) % 16 == 0 && a.cin % (2 * LPC) == 0;
+  return !by_channel<T>(a) && a.cin % (2 * Mfma<T>::LPC) == 0;
 }
 
 // Workgroups that share the offsets of a tile (a power of two).  A tile's weights and rows go through one CU, so a layer
@@ -1620,6 +1634,7 @@ static void launch_splitk(const ConvArgs& a) {
   k.cout = a.cout;
   k.relu = a.relu;
   k.row_bytes = static_cast<uint32_t>(a.ld_in * sizeof(T));
+  k.by_channel = by_channel<T>(a) ? 1 : 0;
   k.w_bytes = static_cast<uint32_t>(PACKED ? MAX_OFFSET : int64_t(k.K3) * a.cin * a.cout * int64_t(sizeof(T)));  // (read where it fits)
   k.os_mask = a.os_mask;
   k.has_os = a.any_os ? 1 : 0;
@@ -1687,7 +1702,6 @@ static void launch_os_splitk(const ConvArgs& a) {
   constexpr int LPC = Mfma<T>::LPC;
   using Yes = std::true_type;
   using No = std::false_type;
-  const bool aligned = a.ld_in % LPC == 0 && reinterpret_cast<uintptr_t>(a.F) % 16 == 0;
   const int nb_total = (a.cout + 31) / 32;
   const bool wide = wide_rows<T>(a) || int64_t(a.m->K3) * ((a.cin + 2 * LPC - 1) / (2 * LPC)) * nb_total * 1024 > int64_t(MAX_OFFSET);
   const bool quad = sizeof(T) == 2 && a.cin == 4 && a.ld_in % 4 == 0 && reinterpret_cast<uintptr_t>(a.F) % 8 == 0 && !wide;
@@ -1698,7 +1712,7 @@ static void launch_os_splitk(const ConvArgs& a) {
       launch_splitk<T, NB, A_VEC, PACKED, FROM>(a);
     } else if (quad) {
       if constexpr (sizeof(T) == 2) launch_splitk<T, NB, A_QUAD, PACKED, FROM>(a);
-    } else if (!aligned || a.cin % LPC != 0) {
+    } else if (by_channel<T>(a) && (PACKED || !wide)) {
       launch_splitk<T, NB, A_ELEM, PACKED, FROM>(a);
     } else if (wide) {
       launch_splitk<T, NB, A_WIDE, PACKED, FROM>(a);

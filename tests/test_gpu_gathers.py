@@ -99,7 +99,8 @@ def test_splitk_two_blocks_per_workgroup(n, cin, cout):
     km.destroy()
 
 
-@pytest.mark.parametrize("dtype,cin,cout", [(torch.float16, 64, 64), (torch.float16, 24, 40), (torch.float16, 4, 32), (torch.float32, 32, 32)])
+@pytest.mark.parametrize("dtype,cin,cout", [(torch.float16, 64, 64), (torch.float16, 24, 40), (torch.float16, 4, 32), (torch.float32, 32, 32),
+                                            (torch.float16, 20, 40), (torch.float32, 30, 32)])
 def test_splitk_far_rows(dtype, cin, cout):
     n = 3001
     km, M = _level(n, 0.3, 3, B.LAYOUT_BOTH)
@@ -112,3 +113,36 @@ def test_splitk_far_rows(dtype, cin, cout):
         y = B.spc_conv_forward(km, far, w, df, fl)
         assert_close(y.cpu().to(torch.float64).numpy(), ref, TOL[dtype], (df, fl))
     km.destroy()
+
+
+@pytest.mark.parametrize("dtype,cin,pitch,cout", [
+    (torch.float16, 1001, 1001, 80_000),   # a channel count that ends inside a piece
+    (torch.bfloat16, 1000, 1003, 80_000),  # rows that are not aligned
+    (torch.float16, 1000, 1000, 80_000),
+    (torch.float32, 501, 501, 80_000),
+])
+def test_splitk_far_weights(dtype, cin, pitch, cout):
+    """Weights of more than 4 GiB: neither their bytes nor their number of 16-bit channels fits 32 bits."""
+    n = 40
+    km, M = _level(n, 0.6, 3, B.LAYOUT_BOTH)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(cin)
+    F = torch.randn(n, pitch, generator=gen, device="cuda").to(dtype)[:, pitch - cin:]
+    W = torch.empty(27, cin, cout, dtype=dtype, device="cuda")
+    assert W.numel() * W.element_size() > 1 << 32
+    ref = torch.zeros(n, cout, dtype=torch.float64, device="cuda")
+    for k in range(27):
+        W[k] = (torch.randn(cin, cout, generator=gen, device="cuda") * cin ** -0.5).to(dtype)
+        for c in range(0, cout, 16_000):  # (the products of an offset, in 64 bits)
+            j = torch.from_numpy(M[:, k].astype(np.int64)).cuda()
+            ref[:, c:c + 16_000] += (F[j.clamp_min(0)].double() * (j >= 0)[:, None]) @ W[k, :, c:c + 16_000].double()
+    runs = [(W, B.DATAFLOW_OS, B.CONV_OS_SPLITK if dtype != torch.float32 else 0), (W, B.DATAFLOW_WS, 0), (W, B.DATAFLOW_OS, 0)]
+    if dtype != torch.float32:
+        runs.append((B.spc_conv_prepare_weights(W), B.DATAFLOW_OS, B.CONV_OS_SPLITK | B.CONV_PACKED_WEIGHTS))
+    for w, df, fl in runs:
+        y = B.spc_conv_forward(km, F, w, df, fl).double()
+        scale = ref.abs().max()
+        assert float((y - ref).abs().max() / scale) <= TOL[dtype], (df, fl)
+        assert bool(((y - ref).abs() <= TOL[dtype] * (ref.abs() + ref.square().mean().sqrt())).all()), (df, fl)
+    km.destroy()
+    B.spc_release_cache()
