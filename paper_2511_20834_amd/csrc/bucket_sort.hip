@@ -1178,12 +1178,14 @@ void partition(const Src& src, int64_t n, const BucketPlan& p, const Ws<KeyT>& w
 }
 }  // namespace
 
-// Entries of the tables of a sort of up to n keys (a workspace for n keys serves fewer as well).
+// Entries of the tables of a sort of up to n keys: never fewer for more keys, so that a workspace for n keys (of this sort's
+// range) serves fewer as well.  Shares of up to BS_ADD_N keys are fixed, so a plan's own workgroups grow with n between the
+// steps; beyond, shares are rounded up and the workgroups fall at every step (128 for 655360 keys, 107 for one more).
 static size_t table_entries(int64_t n) {
-  size_t most = 0;
-  for (int64_t m : {std::min(n, BS_SHORT_N), std::min(n, BS_ADD_N), n}) {
+  size_t most = n > BS_ADD_N ? size_t(2) * BS_MAX_WG * BS_MAX_BIN : 0;
+  for (int64_t m : {std::min(n, BS_SHORT_N), std::min(n, BS_ADD_N)}) {
     const BucketPlan p = bucket_plan(m, 64, true);  // (the more workgroups of the two)
-    most = std::max(most, (size_t(p.n_wg) * p.n_bin + 63) / 64 * 64 * (p.add ? 1 : 2));
+    most = std::max(most, (size_t(p.n_wg) * p.n_bin + 63) / 64 * 64);
   }
   return most;
 }

@@ -64,6 +64,16 @@ def test_workspace_query_needs_no_gpu():
     assert B.spc_version().startswith("spc-gfx950")
 
 
+@pytest.mark.parametrize("key_bits", [32, 64])
+def test_workspace_of_more_voxels_serves_fewer(key_bits):
+    """Over the sizes of the library's own sort: the workgroups of a plan fall where their shares are rounded up."""
+    d = B.spc_pack_desc_fit([0, 0, 0], [100, 100, 100], 1, 1, 1, key_bits)
+    lines = [4095, 4096, 65_536, 200_000, 524_288, 655_360, 8_388_607]
+    sizes = sorted({*range(1, 70_000, 61), *range(70_000, 8_388_609, 4093), *lines, *(n + 1 for n in lines)})
+    need = [B.spc_pack_workspace_bytes(n, d) for n in sizes]
+    assert all(a <= b for a, b in zip(need, need[1:])), [n for n, a, b in zip(sizes[1:], need, need[1:]) if a > b][:5]
+
+
 def test_builders_reject_descriptors_that_do_not_suit_the_layer():
     """Section 5.3: packed additivity needs a guard band of at least the layer's reach, and masking
     equals floor() only if origin - pad is a multiple of the output stride.  Both are checked on the
