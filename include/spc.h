@@ -252,7 +252,9 @@ int spc_kmap_export_triples(spc_kmap* m, int32_t which, int32_t* triples, int64_
  * every replay) it assumes the upper bound n_in.  This sets a better estimate, e.g. the count a
  * previous cloud of the same scene produced.  The estimate steers kernel selection and launch
  * shape only: every kernel reads the true count on the device, so any value gives a correct
- * result.
+ * result.  The fp32 summation order goes with the kernel that is picked and, where several workgroups
+ * add up one tile (wide layers of a few thousand outputs), with the launch shape; otherwise the estimate
+ * changes no bit.
  */
 int spc_kmap_set_size_hint(spc_kmap* m, int64_t n_out_hint);
 /*

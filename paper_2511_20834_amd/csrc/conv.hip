@@ -1605,10 +1605,13 @@ static bool splitk_wide(const ConvArgs& a) {
 // 18.6, 160 k 20.2 / 20.0 / 22.8, 200 k 23.1 / 22.7, random 160 k 17.4 / 16.5, 200 k 21.0 / 18.6, 10^6 80 / 65 / 71; 4->32 (short
 // tiles) 30 k 5.6 / 5.6 / 6.6, 60 k 8.4 / 7.0 / 7.4, 120 k 13.1 / 10.3; 2x2x2 50 k output voxels 7.1 / 6.3 / 7.8, 19 k 5.9 / 6.1;
 // lists, 5x5x5, 240 k 53.3 / 51.0 / 57; matrix 5x5x5 38.8 / 39.6 / 48.  fp32 100 k 37.5 / 40.6.
+// By the rows that the level presumably holds and not by what the host knows of them: the waves are the order of the sums, which is
+// to stay when the host learns the count between two calls.
 template <typename T>
-static int splitk_share(const ConvArgs& a, int AM, int FROM, int64_t n_blocks) {
+static int splitk_share(const ConvArgs& a, int AM, int FROM) {
   if (a.splitk_rb) return a.splitk_rb == 1 ? 2 : 1;
   if (sizeof(T) == 4 || FROM == MATRIX) return 2;
+  const int64_t n_blocks = (a.m->out_level->presumed + 31) / 32;
   return n_blocks >= (AM == A_QUAD || a.m->K3 <= 8 ? 1280 : 4800) ? 1 : 2;
 }
 
@@ -1648,7 +1651,7 @@ static void launch_splitk(const ConvArgs& a) {
       k.arrived = a.m->arrived;
     }
   }
-  k.log_share = k.log_waves = parts > 1 ? 2 : splitk_share<T>(a, AM, FROM, n_blocks);
+  k.log_share = k.log_waves = parts > 1 ? 2 : splitk_share<T>(a, AM, FROM);
   for (int q = parts; q > 1; q >>= 1) ++k.log_waves;
   const int run = k.log_share == 0 ? 16 : NB * 4;  // consecutive channels that a thread stores
   const int per_store = std::min<int>(run, 16 / sizeof(T));

@@ -1190,6 +1190,7 @@ static Level* borrowed_level(const void* keys, int64_t n, int stride) {
   lv->keys = const_cast<void*>(keys);
   lv->owns_keys = false;
   lv->cap = n;
+  lv->presumed = n;
   lv->n_host = n;
   lv->stride = stride;
   return lv;
@@ -1315,7 +1316,7 @@ struct NetBuild {
         if (!levels.count(stride) && seen.insert(stride).second) ms.push_back(ilog2(stride));
     if (ms.empty()) return SPC_OK;
     std::vector<Level*> made(ms.size());
-    SPC_RETURN_IF(downsample_levels(levels[1]->keys, levels[1]->n_host, pi, ms.data(), static_cast<int>(ms.size()), made.data(), s));
+    SPC_RETURN_IF(downsample_levels(levels[1]->keys, levels[1]->n_host, 1, pi, ms.data(), static_cast<int>(ms.size()), made.data(), s));
     for (Level* lv : made) levels[lv->stride] = lv;
     return SPC_OK;
   }
@@ -1425,7 +1426,7 @@ int spc_build_kmap_perm(const void* in_keys, int64_t n_in, const int32_t* in_per
   Level* derived = nullptr;
   int rc = SPC_OK;
   const int m = ilog2(l->in_stride * l->layer_stride);
-  if (l->layer_stride > 1) rc = downsample_levels(in_keys, n_in, pi, &m, 1, &derived, s);
+  if (l->layer_stride > 1) rc = downsample_levels(in_keys, n_in, l->in_stride, pi, &m, 1, &derived, s);
   if (rc == SPC_OK) {
     if (in_perm && l->transposed) rc = set_error(SPC_ERR_ARG, "in_perm applies to the given level, which a transposed layer writes");
     else if (in_perm && (l->layout & SPC_LAYOUT_WS_SYM))

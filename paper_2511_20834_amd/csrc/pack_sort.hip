@@ -222,7 +222,7 @@ static int downsample_batch(const void* src, int64_t n, const PackInfo& pi, cons
   return rc;
 }
 
-int downsample_levels(const void* src_keys, int64_t n_src, const PackInfo& pi, const int* m, int count, Level** out,
+int downsample_levels(const void* src_keys, int64_t n_src, int src_stride, const PackInfo& pi, const int* m, int count, Level** out,
                       const StreamId& stream) {
   const StreamWorkNote note{stream};
   const bool captured = stream_is_capturing(stream);
@@ -231,6 +231,7 @@ int downsample_levels(const void* src_keys, int64_t n_src, const PackInfo& pi, c
     Level* lv = out[i] = new Level;
     lv->cap = n_src;
     lv->stride = 1 << m[i];
+    lv->presumed = n_src / (lv->stride / src_stride);  // (surfaces keep about 0.4 of their voxels per halving, random volumes 0.9)
     lv->owns_keys = true;
     lv->stream = stream;
     lv->captured = captured;

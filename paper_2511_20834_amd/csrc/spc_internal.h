@@ -161,6 +161,7 @@ struct Level {
   bool owns_keys = false;
   int64_t cap = 0;        // rows allocated / upper bound of n
   int64_t n_host = -1;    // -1: not yet fetched
+  int64_t presumed = 0;   // rows it presumably holds: settled when it is made, whatever the host learns of the count later
   int64_t n_fetched = -1; // last value read back from n_dev (equals n_host unless the level was built under capture)
   bool captured = false;  // produced while its stream was being captured into a graph: every replay rewrites it
   int* n_dev = nullptr;   // device int (nullptr when n_host is authoritative from the start)
@@ -179,8 +180,9 @@ struct Level {
 void level_unref(Level* l);
 bool stream_is_capturing(hipStream_t s);
 
-// Derive the levels with strides 2^m[i] of `src_keys` (mask, sort, unique), out[i] for i < count.  Enqueues only.
-int downsample_levels(const void* src_keys, int64_t n_src, const PackInfo& pi, const int* m, int count, Level** out,
+// Derive the levels with strides 2^m[i] of `src_keys` (mask, sort, unique), whose own stride is src_stride; out[i] for
+// i < count.  Enqueues only.
+int downsample_levels(const void* src_keys, int64_t n_src, int src_stride, const PackInfo& pi, const int* m, int count, Level** out,
                       const StreamId& stream);
 
 // ---------------------------------------------------------------- packing (Section 5.3)

@@ -146,3 +146,30 @@ def test_splitk_far_weights(dtype, cin, pitch, cout):
         assert bool(((y - ref).abs() <= TOL[dtype] * (ref.abs() + ref.square().mean().sqrt())).all()), (df, fl)
     km.destroy()
     B.spc_release_cache()
+
+
+# (grids whose bound of the output rows lies above the lines where two waves share a tile instead of four, and whose count lies below)
+@pytest.mark.parametrize("side,K,cin,cout,dataflow", [(40, 2, 32, 32, B.DATAFLOW_OS), (40, 3, 4, 32, B.DATAFLOW_OS),
+                                                      (40, 2, 32, 64, B.DATAFLOW_WS), (56, 3, 32, 32, B.DATAFLOW_OS)])
+def test_sums_are_the_same_before_and_after_the_count_is_known(side, K, cin, cout, dataflow):
+    """The same map, inputs and flags: bit by bit, whatever the host knows of the output count when the layer is enqueued."""
+    c = synth.full_grid(side)
+    n = len(c)
+    desc = fit_desc(c, [(K, 1, 2)])
+    keys, _ = gpu_pack(c, desc)
+    F, _, W, _ = _tensors(n, K ** 3, cin, cout, torch.float16)
+    km = B.spc_build_kmap(keys, desc, K, 1, 2, 0, B.LAYOUT_OS if dataflow == B.DATAFLOW_OS else B.LAYOUT_WS)
+    flags = B.CONV_OS_SPLITK if dataflow == B.DATAFLOW_OS else 0
+
+    def forward():
+        out = torch.empty((n, cout), dtype=torch.float16, device="cuda")
+        B.spc_conv_forward(km, F, W, dataflow, flags, out=out)
+        return out
+
+    bound = forward()
+    km.set_size_hint((side // 2) ** 3 // 2)
+    hinted = forward()
+    assert km.n_out == (side // 2) ** 3
+    known = forward()[: km.n_out]
+    assert torch.equal(known, bound[: km.n_out]) and torch.equal(known, hinted[: km.n_out])
+    km.destroy()
