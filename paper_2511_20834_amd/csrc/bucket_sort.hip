@@ -205,10 +205,12 @@ __global__ __launch_bounds__(BS_COL_THREADS) void bs_colscan_kernel(const int32_
 // equal adjacent keys only the first takes part), the cleared position bitmap and chunk counters.
 // What bounds it: the scattered stores, of which a CU issues one lane per cycle, so the shares of the workgroups are short
 // (see bucket_plan).
+// SUM (few workgroups, and no cleared block for the totals): `before` is the table of counts as the count pass leaves it
+// without ADD, and its rows are summed here, which saves the launch that would clear the totals.
 // REC (pack + sort of 32-bit keys that bs_rank_lds_kernel ranks): a key and its source index leave as one 8-byte record.
 // From half a million keys on hardly two keys of a workgroup share a bin, so every scattered store is a memory
 // transaction of its own, and one array of records takes half as many as two arrays.
-template <typename KeyT, bool DEDUP, bool REC>
+template <typename KeyT, bool DEDUP, bool REC, bool SUM>
 __global__ __launch_bounds__(BS_WIDE) void bs_scatter_kernel(const KeyT* __restrict__ keys0, int64_t n, int per, int shift,
                                                              int n_bin, const int32_t* __restrict__ before,
                                                              const int32_t* __restrict__ tot, size_t tot_pitch, BsElem<KeyT, REC>* __restrict__ keys1,
@@ -220,7 +222,7 @@ __global__ __launch_bounds__(BS_WIDE) void bs_scatter_kernel(const KeyT* __restr
   if (DEDUP) {
     keys0 = level_ws(keys0, ws_pitch);
     before = level_ws(before, ws_pitch);
-    tot = level_ws(tot, tot_pitch);
+    if (!SUM) tot = level_ws(tot, tot_pitch);
     keys1 = level_ws(keys1, ws_pitch);
     win = level_ws(win, ws_pitch);
     n_part_keys = level_ws(n_part_keys, ws_pitch);
@@ -254,8 +256,24 @@ __global__ __launch_bounds__(BS_WIDE) void bs_scatter_kernel(const KeyT* __restr
     const int f0 = r0 + t * 4;
     int4 c = make_int4(0, 0, 0, 0), bef = c;
     if (f0 < n_bin) {
-      c = *reinterpret_cast<const int4*>(tot + f0);
-      bef = *reinterpret_cast<const int4*>(before + int64_t(blockIdx.x) * n_bin + f0);
+      if constexpr (SUM) {
+        constexpr int ROWS = 8;  // loads in flight
+        const int n_wg = gridDim.x, me = blockIdx.x;
+        for (int w = 0; w < n_wg; w += ROWS) {
+          int4 row[ROWS];
+#pragma unroll
+          for (int r = 0; r < ROWS; ++r) row[r] = *reinterpret_cast<const int4*>(before + int64_t(min(w + r, n_wg - 1)) * n_bin + f0);
+#pragma unroll
+          for (int r = 0; r < ROWS; ++r) {
+            const int all = w + r < n_wg ? -1 : 0, mine = w + r < me ? -1 : 0;
+            c.x += row[r].x & all, c.y += row[r].y & all, c.z += row[r].z & all, c.w += row[r].w & all;
+            bef.x += row[r].x & mine, bef.y += row[r].y & mine, bef.z += row[r].z & mine, bef.w += row[r].w & mine;
+          }
+        }
+      } else {
+        c = *reinterpret_cast<const int4*>(tot + f0);
+        bef = *reinterpret_cast<const int4*>(before + int64_t(blockIdx.x) * n_bin + f0);
+      }
     }
     const int sum = c.x + c.y + c.z + c.w;
     int x = sum;
@@ -1127,7 +1145,8 @@ Ws<KeyT> carve(void* ws, int64_t n) {
 
 // The bins' totals of a sort: in a block that the library keeps cleared between its sorts (the last kernel clears it again),
 // or, where none is to be had (under capture, whose replays know nothing of other sorts; on hipStreamPerThread; once the blocks of
-// the library's image are in use on other streams), in the workspace, cleared by a kernel of its own.
+// the library's image are in use on other streams), in the workspace, cleared by a kernel of its own, or nowhere, where so few
+// workgroups have counted that the scatter pass may sum their counts itself (p is NULL then).
 struct Totals {
   int32_t* p = nullptr;
   size_t pitch = 0, bytes = 0;
@@ -1140,6 +1159,10 @@ struct Totals {
       p = static_cast<int32_t*>(zeros);
       pitch = size_t(plan.n_bin) * 4;
       kept = true;
+      return;
+    }
+    if (plan.n_wg <= BS_SUM_WG) {
+      p = nullptr;
       return;
     }
     hipLaunchKernelGGL(bs_clear_kernel, dim3((plan.n_bin + BS_THREADS - 1) / BS_THREADS, n_levels), dim3(BS_THREADS), 0, s, p, plan.n_bin, pitch);
@@ -1157,24 +1180,35 @@ struct Totals {
 template <typename KeyT, bool DEDUP, bool REC, typename Src>
 void partition(const Src& src, int64_t n, const BucketPlan& p, const Ws<KeyT>& w, int n_levels, size_t ws_pitch, const Totals& t, hipStream_t s) {
   const int32_t* before = w.table;
-  if (p.add) {
+  const bool sum = p.add && !t.p;
+  if (p.add && !sum) {
     hipLaunchKernelGGL((bs_count_kernel<KeyT, Src, true>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(p.n_bin) * 4, s, src, n, p.per,
                        p.shift, p.n_bin, w.keys0, w.table, ws_pitch, t.p, t.pitch);
   } else {
     hipLaunchKernelGGL((bs_count_kernel<KeyT, Src, false>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(p.n_bin) * 4, s, src, n, p.per,
                        p.shift, p.n_bin, w.keys0, w.table, ws_pitch, static_cast<int32_t*>(nullptr), size_t(0));
+  }
+  if (!p.add) {
     const int col_wg = (p.n_bin / 4 + BS_COL_THREADS - 1) / BS_COL_THREADS;
     hipLaunchKernelGGL(bs_colscan_kernel, dim3(col_wg, n_levels), dim3(BS_COL_THREADS), 0, s, w.table, w.before, p.n_wg, p.n_bin,
                        t.p, ws_pitch);
     before = w.before;
   }
-  // (the scatter pass holds two ints per bin: beyond 8191 bins that is more than the default LDS limit)
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bs_scatter_kernel<KeyT, DEDUP, REC>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (2 * BS_MAX_BIN + 2) * 4);
-  (void)attr;
-  hipLaunchKernelGGL((bs_scatter_kernel<KeyT, DEDUP, REC>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(2 * p.n_bin + 2) * 4, s, w.keys0,
-                     n, p.per, p.shift, p.n_bin, before, t.p, t.pitch, reinterpret_cast<BsElem<KeyT, REC>*>(w.keys1), w.vals1, w.win,
-                     DEDUP ? w.n_kept : static_cast<int32_t*>(nullptr), w.bits, w.n_words, w.ccnt, w.n_chunks, w.rest_count, ws_pitch);
+  auto scatter = [&](auto SUM_) {
+    constexpr bool SUM = decltype(SUM_)::value;
+    // (the scatter pass holds two ints per bin: beyond 8191 bins that is more than the default LDS limit)
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bs_scatter_kernel<KeyT, DEDUP, REC, SUM>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (2 * BS_MAX_BIN + 2) * 4);
+    (void)attr;
+    hipLaunchKernelGGL((bs_scatter_kernel<KeyT, DEDUP, REC, SUM>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(2 * p.n_bin + 2) * 4, s,
+                       w.keys0, n, p.per, p.shift, p.n_bin, before, t.p, t.pitch, reinterpret_cast<BsElem<KeyT, REC>*>(w.keys1), w.vals1,
+                       w.win, DEDUP ? w.n_kept : static_cast<int32_t*>(nullptr), w.bits, w.n_words, w.ccnt, w.n_chunks, w.rest_count,
+                       ws_pitch);
+  };
+  if constexpr (!REC) {
+    if (sum) return scatter(std::true_type{});
+  }
+  scatter(std::false_type{});
 }
 }  // namespace
 

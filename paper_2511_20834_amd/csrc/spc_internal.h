@@ -236,6 +236,10 @@ inline bool use_bucket_sort(int64_t n) { return n >= BS_MIN_N && n <= BS_MAX_N; 
 // 34.8 / 31.7; random 300 k 35.4 / 30.3, 500 k 44.5 / 36.0.  Beyond, the table of 16384 bins would outgrow what is sorted.
 constexpr int64_t BS_ADD_N = 524288, BS_MID_N = 200000, BS_SHORT_N = 65536;
 constexpr int BS_ADD_SHARE = 2048, BS_SHORT_SHARE = 1024;
+// Up to so many workgroups the scatter pass sums their counts itself where the totals would have to be cleared first: a launch
+// less, but every workgroup reads the whole table.  Replayed pack + sort, us, cleared / summed: 4.2 k 20.8 / 17.2, 14 k 21.1 / 18.3, 33 k
+// (32 workgroups) 22.4 / 20.5, 40 k 23.6 / 24.1, 60 k 24.0 / 27.8; with a kept block 11.7, 12.1, 13.3, 14.7, 14.8 (replays start 5 us later).
+constexpr int BS_SUM_WG = 32;
 constexpr int BS_PART = 64;         // keys per rank workgroup
 constexpr int BS_PAD_KEYS = 32;     // all-ones keys kept behind the scattered keys
 struct BucketPlan {
@@ -245,7 +249,7 @@ struct BucketPlan {
 BucketPlan bucket_plan(int64_t n, int used_bits, bool unique);
 size_t bucket_sort_ws_bytes(int key_bits, int64_t n);
 // coords -> sorted keys (+ permutation); enqueues three kernels (count, scatter, rank), or four with the column scan of large inputs
-// or, where there is no cleared block for the totals, with their clearing.  Asks for no device memory.
+// or, where there is no cleared block for the totals of more than BS_SUM_WG workgroups, with their clearing.  Asks for no device memory.
 int bucket_pack_sort(int key_bits, const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status,
                      void* keys_out, int32_t* perm_out, void* ws, const StreamId& s);
 // One level to produce: the sorted distinct values of keys_in & mask, and their count.

@@ -94,6 +94,42 @@ def test_replays_between_eager_sorts():
         _check(a, keys, perm)
 
 
+# (recorded sorts sum their workgroups' counts in the scatter pass up to 32 of them, 1024 keys each)
+@pytest.mark.parametrize("n", [4096, 4097, 9001, 32_767, 32_768, 32_769])
+@pytest.mark.parametrize("key_bits", [0, 64])
+def test_recorded_sizes(n, key_bits):
+    c = _cloud(n, n + 1)
+    desc = fit_desc(c, [(3, 1, 2)], key_bits)
+    d = torch.from_numpy(c).cuda()
+    ws = torch.empty(B.spc_pack_workspace_bytes(n, desc), dtype=torch.uint8, device="cuda")
+    keys = torch.empty(n, dtype=torch.int64 if desc.key_bits == 64 else torch.int32, device="cuda")
+    perm, side = torch.empty(n, dtype=torch.int32, device="cuda"), torch.cuda.Stream()
+
+    def step():
+        B.spc_pack_coords(d, desc, True, 0, None, ws, keys, perm)
+        return B.spc_build_kmap(keys, desc, 3, 1, 2, 0, B.LAYOUT_OS)
+
+    with torch.cuda.stream(side):
+        step().destroy()  # (warm)
+    side.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        m = step()
+    for _ in range(3):
+        keys.zero_()
+        perm.zero_()
+        ws.fill_(255)  # (nothing of an earlier replay is relied on)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        _check(c, keys, perm)
+        assert m.n_out == len(np.unique(c[:, 1:] // 2, axis=0))
+        B.spc_pack_coords(d, desc)
+    torch.cuda.synchronize()
+    del g
+    m.destroy()
+
+
 def test_first_sort_of_a_size_while_another_thread_records():
     """The sort asks for no memory, which would be refused and end the recording."""
     warm, c = _cloud(9001, 3), _cloud(400_009, 4)

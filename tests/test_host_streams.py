@@ -155,10 +155,19 @@ def test_per_thread_streams_share_nothing(host):
 def test_sorts_on_per_thread_streams_share_no_totals(host):
     """Neither one after the other nor through a block that was left behind: there is no order to rely on."""
     for _ in range(2):
-        log = host.pack(9000, PER_THREAD)
-        assert cleared_first(log) and host.device_of(totals_of(log)) < 0
-        log = in_thread(lambda: host.pack(9000, PER_THREAD))
-        assert cleared_first(log) and host.device_of(totals_of(log)) < 0
+        for n, cleared in ((9000, False), (50_000, True)):  # (small sorts have no totals then)
+            for log in (host.pack(n, PER_THREAD), in_thread(lambda: host.pack(n, PER_THREAD))):
+                assert cleared_first(log) == cleared and host.device_of(totals_of(log)) < 0
+
+
+@pytest.mark.parametrize("n,launches", [(4096, 3), (32_768, 3), (32_769, 4), (524_288, 4), (524_289, 4)])
+def test_launches_of_recorded_sorts(host, n, launches):
+    """A recorded sort keeps no totals from one replay to the next; small ones get by without clearing any."""
+    host.on(0)
+    host.L.standin_capture(OTHER)
+    log = host.pack(n, OTHER)
+    host.L.standin_capture(ctypes.c_void_p(2**64 - 1))
+    assert [l[0] for l in log] == ["launch"] * launches and cleared_first(log) == (launches == 4 and n <= 524_288)
 
 
 def test_blocks_of_ended_threads_come_back_after_a_drain(host):
