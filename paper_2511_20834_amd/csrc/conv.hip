@@ -787,9 +787,9 @@ __global__ __launch_bounds__(64 * WAVES) void conv_os_phase_kernel(const int32_t
 
 // Kernel for layers whose weight traffic is small next to the chip's L2 bandwidth (few output voxels, or few
 // channels), for fp32, for channel counts and rows that fit no tile, and for all offsets that come from lists.  A tile is
-// a block of 32 output voxels and a slab of NB*32 output channels.  One, two or four waves of a workgroup share a tile: the
+// a block of 32 output voxels and a slab of NB*32 output channels.  Two or four waves of a workgroup share a tile: the
 // offsets present in the block are dealt to them round-robin (a split of the reduction over k, Eq. (2)); a workgroup of four
-// waves holds four, two or one tiles (log_share, see splitk_share).  No barrier sits inside the loop: a wave reads the B
+// waves holds two tiles or one (log_share, see splitk_share).  No barrier sits inside the loop: a wave reads the B
 // fragments of its offsets straight from the weights (L2-resident; 1 KB coalesced per fragment) next to the gathered rows,
 // an entry (an offset and 64 bytes of channels) ahead of the MFMA that consumes them.  Where waves share a tile their
 // accumulators meet in LDS and are summed in wave order, so results are bit-reproducible; the sum leaves through LDS, each
@@ -846,7 +846,7 @@ struct SplitkArgs {
   uint32_t w_bytes;    // of the weights, as given
   int by_channel;      // (A_WIDE, plain weights) rows are read one channel at a time
   int has_os;          // lists: some offsets come from the matrix
-  int log_share;       // log2 of a workgroup's waves that share a tile
+  int log_share;       // log2 of a workgroup's waves that share a tile: 1 or 2
   int log_waves;       // the same with the waves of other workgroups that share it
   int kl_cap;          // entries of a wave's list of offsets
   int tile_lds;        // bytes
@@ -871,16 +871,10 @@ constexpr int splitk_areas(int NB) { return NB == 1 ? 4 : 2; }
 
 // Which output a thread stores as its e-th.
 template <int NB>
-__device__ inline void splitk_place(int log_share, int lane, int wave, int e, int& tile, int& row, int& col) {
-  if (log_share == 0) {
-    tile = wave;
-    row = lane >> 1;
-    col = e / 16 * 32 + (lane & 1) * 16 + e % 16;
-  } else {
-    tile = e / (NB * 4);
-    row = wave * 8 + lane / 8;
-    col = lane % 8 * (NB * 4) + e % (NB * 4);
-  }
+__device__ inline void splitk_place(int lane, int wave, int e, int& tile, int& row, int& col) {
+  tile = e / (NB * 4);
+  row = wave * 8 + lane / 8;
+  col = lane % 8 * (NB * 4) + e % (NB * 4);
 }
 // The outputs that this wave has stored as NaN, from their own pairs (see conv_by_pairs).
 using SplitkKernarg = const __attribute__((address_space(4))) SplitkArgs;
@@ -890,13 +884,13 @@ __device__ inline void splitk_redo(SplitkKernarg* a) {
   const int n_out = a->n_out_d ? *(Ints)a->n_out_d : a->n_out_h;
   const int n_blocks = (n_out + 31) >> 5, K3 = a->K3, kc = (K3 - 1) / 2;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int log_share = a->log_share, tiles = SPLITK_WAVES >> log_share, per = log_share == 0 ? NB * 16 : tiles * NB * 4;
+  const int tiles = SPLITK_WAVES >> a->log_share, per = tiles * NB * 4;
 #pragma unroll 1
   for (int first = blockIdx.x * tiles; first < n_blocks; first += LOOP ? gridDim.x * tiles : n_blocks)
 #pragma unroll 1
     for (int e = 0; e < per; ++e) {
       int tile, my_row, my_col;
-      splitk_place<NB>(log_share, lane, wave, e, tile, my_row, my_col);
+      splitk_place<NB>(lane, wave, e, tile, my_row, my_col);
       const int blk = first + tile, my_i = blk * 32 + my_row;
       my_col += blockIdx.y * (NB * 32);
       SPC_GLOBAL T* dst = (SPC_GLOBAL T*)a->out + my_i * a->ld_out + my_col;
@@ -906,7 +900,7 @@ __device__ inline void splitk_redo(SplitkKernarg* a) {
       for (unsigned long long todo = __ballot(was != was); todo; todo &= todo - 1) {
         const int l = __builtin_ctzll(todo);
         int row, col;
-        splitk_place<NB>(log_share, l, wave, e, tile, row, col);
+        splitk_place<NB>(l, wave, e, tile, row, col);
         col += blockIdx.y * (NB * 32);
         auto in_row = [&](int k) -> int {
           if ((a->os_mask.w[k >> 5] >> (k & 31)) & 1u) {
@@ -996,10 +990,6 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, PACKED ? splitk_occupancy(NB, FR
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tile = wave >> log_share, blk = first + tile;
   const bool here = blk < n_blocks;  // (the last workgroup's waves may have no tile)
-  auto sync = [&]() {  // of the waves that share a tile
-    if (log_share) __syncthreads();
-    else __builtin_amdgcn_wave_barrier();
-  };
   const int member = wave & ((1 << log_share) - 1);  // among the waves of the tile
   unsigned char* const tile_mem = smem + tile * tile_lds;
   int32_t* sIdx = reinterpret_cast<int32_t*>(tile_mem) + (FROM == MATRIX_SMALL ? 0 : member * (SPLITK_CHUNK + TAIL) * 32);
@@ -1010,16 +1000,12 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, PACKED ? splitk_occupancy(NB, FR
   int16_t* kl = reinterpret_cast<int16_t*>(kl_base + (FROM == LISTS ? (kl_cap << log_share) * 8 : 0)) + member * kl_cap;  // this wave's offsets
   V* stage = reinterpret_cast<V*>(kl_base + splitk_list_bytes(kl_cap, log_share, FROM)) + member * 128;
 
-  intx4 rows[4];
+  intx4 rows[2];
   const int lid = tid & ((64 << log_share) - 1);
   // (MATRIX_SMALL) its up to 256 pieces of map rows, 64 << log_share at a time
   auto pieces = [&](auto&& f) {
     f(std::integral_constant<int, 0>{});
     if (log_share < 2) f(std::integral_constant<int, 1>{});
-    if (log_share < 1) {
-      f(std::integral_constant<int, 2>{});
-      f(std::integral_constant<int, 3>{});
-    }
   };
   unsigned word = 0u;
   if constexpr (FROM == MATRIX_SMALL) {
@@ -1093,7 +1079,7 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, PACKED ? splitk_occupancy(NB, FR
       if (at < K3 * 8) reinterpret_cast<intx4*>(sIdx)[at] = row_pos4(rows[U]);
     });
     if (lid < 32) sIdx[K3 * 32 + lid] = row_pos(-1);
-    sync();
+    __syncthreads();
   } else {
     __builtin_amdgcn_wave_barrier();
   }
@@ -1363,125 +1349,105 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, PACKED ? splitk_occupancy(NB, FR
     }
   };
   // D layout of the 32x32 MFMA: register r of lane l is row 8*(r/4) + 4*(l/32) + r%4, column l%32.
-  if (log_share == 0) {
-    // The wave has its tile to itself: 32 columns at a time through LDS of its own
-    constexpr int P1 = splitk_pitch(1);
-    float* area = reinterpret_cast<float*>(tile_mem);
-    __builtin_amdgcn_wave_barrier();
-    static_for<NB>([&](auto NB_) {
-      constexpr int nb = decltype(NB_)::value;
+  constexpr int AREAS = splitk_areas(NB), AREA = 32 * PITCH, EPT = NB * 4;
+  float* const sums = reinterpret_cast<float*>(smem);
+  auto put = [&](float* area, bool add) {
+    float* p = area + 4 * lh * PITCH + lr;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) area[(8 * (r / 4) + 4 * lh + r % 4) * P1 + lr] = acc[nb][r];
-      __builtin_amdgcn_wave_barrier();
-      const float4* src = reinterpret_cast<const float4*>(area + (lane >> 1) * P1 + (lane & 1) * 16);
-      float4 v[4];
+    for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) v[q] = src[q];
-      __builtin_amdgcn_wave_barrier();
-      store(std::integral_constant<int, 16>{}, blk * 32 + (lane >> 1), nb * 32 + (lane & 1) * 16, reinterpret_cast<const float*>(v));
-    });
+      for (int r = 0; r < 16; ++r) {
+        float* at = p + (8 * (r / 4) + r % 4) * PITCH + nb * 32;
+        *at = add ? *at + acc[nb][r] : acc[nb][r];
+      }
+  };
+  __syncthreads();
+  if constexpr (AREAS == 4) {
+    put(sums + wave * AREA, false);
+  } else if (log_share == 2) {
+    if (wave >= 2) put(sums + (wave - 2) * AREA, false);
+    __syncthreads();
+    if (wave < 2) put(sums + wave * AREA, true);
+  } else {
+    if (member == 1) put(sums + tile * AREA, false);
+    __syncthreads();
+    if (member == 0) put(sums + tile * AREA, true);
   }
-  else {
-    constexpr int AREAS = splitk_areas(NB), AREA = 32 * PITCH, EPT = NB * 4;
-    float* const sums = reinterpret_cast<float*>(smem);
-    auto put = [&](float* area, bool add) {
-      float* p = area + 4 * lh * PITCH + lr;
+  __syncthreads();
+  // N consecutive sums of tile s
+  auto total = [&](auto N_, int s, int row, int col, float* v) {
+    constexpr int N = decltype(N_)::value;
+    using VN = float __attribute__((ext_vector_type(N)));
+    const float* p = sums + row * PITCH + col + (AREAS == 4 ? s << log_share : log_share == 2 ? 0 : s) * AREA;
+    VN t = *reinterpret_cast<const VN*>(p);
+    if (AREAS == 4 || log_share == 2) t += *reinterpret_cast<const VN*>(p + AREA);
+    if (AREAS == 4 && log_share == 2) t += *reinterpret_cast<const VN*>(p + 2 * AREA) + *reinterpret_cast<const VN*>(p + 3 * AREA);
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
+    for (int j = 0; j < N; ++j) v[j] = t[j];
+  };
+  bool summed = false;  // area 0 holds the total
+  if (SHARED && log_waves > log_share) {
+    // This workgroup's part of the sum goes to memory; whoever finds all other parts there adds them up, in the order
+    // of the parts whoever it is.  Nobody waits.  Parts travel between XCDs, whose L2s are not coherent: they are
+    // stored and loaded at device scope, and a part is announced once its stores have completed.
+    constexpr int PART = NB * 1024;
+    const int parts = gridDim.z;
+    const int64_t slot = int64_t(blockIdx.x) * gridDim.y + slab;
+    using Pair = unsigned long long;  // two sums per access
+    constexpr int PER = PART / 2 / (64 * SPLITK_WAVES);
+    Pair* part0 = reinterpret_cast<Pair*>(a.partial) + slot * parts * (PART / 2) + tid;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          float* at = p + (8 * (r / 4) + r % 4) * PITCH + nb * 32;
-          *at = add ? *at + acc[nb][r] : acc[nb][r];
+    for (int e = 0; e < PER; ++e) {
+      const int at = (tid + e * 256) * 2;
+      float t[2];
+      total(std::integral_constant<int, 2>{}, 0, at / (NB * 32), at % (NB * 32), t);
+      const Pair both = (static_cast<Pair>(__float_as_uint(t[1])) << 32) | __float_as_uint(t[0]);
+      __hip_atomic_store(part0 + blockIdx.z * (PART / 2) + e * 256, both, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    int* s_last = reinterpret_cast<int*>(sums + AREAS * AREA);
+    if (tid == 0) *s_last = __hip_atomic_fetch_add(a.arrived + slot, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1;
+    __syncthreads();
+    if (!*s_last) return;
+    if (tid == 0) __hip_atomic_store(a.arrived + slot, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
+    float2 v[PER];
+#pragma unroll
+    for (int e = 0; e < PER; ++e) v[e] = make_float2(0.f, 0.f);
+    for (int q = 0; q < parts; q += 2) {  // (an even number)
+      Pair t[2][PER];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int e = 0; e < PER; ++e)
+          t[h][e] = __hip_atomic_load(part0 + (q + h) * (PART / 2) + e * 256, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int e = 0; e < PER; ++e) {
+          v[e].x += __uint_as_float(static_cast<unsigned>(t[h][e]));
+          v[e].y += __uint_as_float(static_cast<unsigned>(t[h][e] >> 32));
         }
-    };
+    }
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      const int at = (tid + e * 256) * 2;
+      *reinterpret_cast<float2*>(sums + at / (NB * 32) * PITCH + at % (NB * 32)) = v[e];
+    }
+    summed = true;
     __syncthreads();
-    if constexpr (AREAS == 4) {
-      put(sums + wave * AREA, false);
-    } else if (log_share == 2) {
-      if (wave >= 2) put(sums + (wave - 2) * AREA, false);
-      __syncthreads();
-      if (wave < 2) put(sums + wave * AREA, true);
-    } else {
-      if (member == 1) put(sums + tile * AREA, false);
-      __syncthreads();
-      if (member == 0) put(sums + tile * AREA, true);
-    }
-    __syncthreads();
-    // N consecutive sums of tile s
-    auto total = [&](auto N_, int s, int row, int col, float* v) {
-      constexpr int N = decltype(N_)::value;
-      using VN = float __attribute__((ext_vector_type(N)));
-      const float* p = sums + row * PITCH + col + (AREAS == 4 ? s << log_share : log_share == 2 ? 0 : s) * AREA;
-      VN t = *reinterpret_cast<const VN*>(p);
-      if (AREAS == 4 || log_share == 2) t += *reinterpret_cast<const VN*>(p + AREA);
-      if (AREAS == 4 && log_share == 2) t += *reinterpret_cast<const VN*>(p + 2 * AREA) + *reinterpret_cast<const VN*>(p + 3 * AREA);
-#pragma unroll
-      for (int j = 0; j < N; ++j) v[j] = t[j];
-    };
-    bool summed = false;  // area 0 holds the total
-    if (SHARED && log_waves > log_share) {
-      // This workgroup's part of the sum goes to memory; whoever finds all other parts there adds them up, in the order
-      // of the parts whoever it is.  Nobody waits.  Parts travel between XCDs, whose L2s are not coherent: they are
-      // stored and loaded at device scope, and a part is announced once its stores have completed.
-      constexpr int PART = NB * 1024;
-      const int parts = gridDim.z;
-      const int64_t slot = int64_t(blockIdx.x) * gridDim.y + slab;
-      using Pair = unsigned long long;  // two sums per access
-      constexpr int PER = PART / 2 / (64 * SPLITK_WAVES);
-      Pair* part0 = reinterpret_cast<Pair*>(a.partial) + slot * parts * (PART / 2) + tid;
-#pragma unroll
-      for (int e = 0; e < PER; ++e) {
-        const int at = (tid + e * 256) * 2;
-        float t[2];
-        total(std::integral_constant<int, 2>{}, 0, at / (NB * 32), at % (NB * 32), t);
-        const Pair both = (static_cast<Pair>(__float_as_uint(t[1])) << 32) | __float_as_uint(t[0]);
-        __hip_atomic_store(part0 + blockIdx.z * (PART / 2) + e * 256, both, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      __syncthreads();
-      int* s_last = reinterpret_cast<int*>(sums + AREAS * AREA);
-      if (tid == 0) *s_last = __hip_atomic_fetch_add(a.arrived + slot, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1;
-      __syncthreads();
-      if (!*s_last) return;
-      if (tid == 0) __hip_atomic_store(a.arrived + slot, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
-      float2 v[PER];
-#pragma unroll
-      for (int e = 0; e < PER; ++e) v[e] = make_float2(0.f, 0.f);
-      for (int q = 0; q < parts; q += 2) {  // (an even number)
-        Pair t[2][PER];
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-          for (int e = 0; e < PER; ++e)
-            t[h][e] = __hip_atomic_load(part0 + (q + h) * (PART / 2) + e * 256, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-          for (int e = 0; e < PER; ++e) {
-            v[e].x += __uint_as_float(static_cast<unsigned>(t[h][e]));
-            v[e].y += __uint_as_float(static_cast<unsigned>(t[h][e] >> 32));
-          }
-      }
-#pragma unroll
-      for (int e = 0; e < PER; ++e) {
-        const int at = (tid + e * 256) * 2;
-        *reinterpret_cast<float2*>(sums + at / (NB * 32) * PITCH + at % (NB * 32)) = v[e];
-      }
-      summed = true;
-      __syncthreads();
-    }
-    const int row = tid >> 3, c0 = (tid & 7) * EPT;
-    for (int s = 0; s < tiles; ++s) {
-      __align__(16) float v[EPT];
-#pragma unroll
-      for (int q = 0; q < NB; ++q) {
-        if (SHARED && summed) *reinterpret_cast<float4*>(v + 4 * q) = *reinterpret_cast<const float4*>(sums + row * PITCH + c0 + 4 * q);
-        else total(std::integral_constant<int, 4>{}, s, row, c0 + 4 * q, v + 4 * q);
-      }
-      store(std::integral_constant<int, EPT>{}, (first + s) * 32 + row, c0, v);
-    }
-    if constexpr (LOOP) __syncthreads();  // the LDS tile is reused as the next tile's index area
   }
+  const int row = tid >> 3, c0 = (tid & 7) * EPT;
+  for (int s = 0; s < tiles; ++s) {
+    __align__(16) float v[EPT];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      if (SHARED && summed) *reinterpret_cast<float4*>(v + 4 * q) = *reinterpret_cast<const float4*>(sums + row * PITCH + c0 + 4 * q);
+      else total(std::integral_constant<int, 4>{}, s, row, c0 + 4 * q, v + 4 * q);
+    }
+    store(std::integral_constant<int, EPT>{}, (first + s) * 32 + row, c0, v);
+  }
+  if constexpr (LOOP) __syncthreads();  // the LDS tile is reused as the next tile's index area
   first += step;
   again = true;
   } while (LOOP && first * 32 < n_out);
@@ -1653,19 +1619,12 @@ static void launch_splitk(const ConvArgs& a) {
   }
   k.log_share = k.log_waves = parts > 1 ? 2 : splitk_share<T>(a, AM, FROM);
   for (int q = parts; q > 1; q >>= 1) ++k.log_waves;
-  const int run = k.log_share == 0 ? 16 : NB * 4;  // consecutive channels that a thread stores
-  const int per_store = std::min<int>(run, 16 / sizeof(T));
+  const int per_store = std::min<int>(NB * 4, 16 / sizeof(T));  // (a thread stores NB * 4 consecutive channels)
   k.vec_store = a.cout % per_store == 0 && a.ld_out % per_store == 0 && reinterpret_cast<uintptr_t>(a.out) % (per_store * sizeof(T)) == 0;
   k.kl_cap = ((k.K3 + (1 << k.log_share) - 1) >> k.log_share) + splitk_tail(AM);
   k.tile_lds = splitk_idx_bytes(k.K3, k.log_share, AM, FROM) + splitk_list_bytes(k.kl_cap, k.log_share, FROM) + (STAGED ? 2048 << k.log_share : 0);
   const int tiles_wg = SPLITK_WAVES >> k.log_share;
-  size_t lds = 0;
-  if (k.log_share == 0) {
-    k.tile_lds = std::max(k.tile_lds, 32 * splitk_pitch(1) * 4);
-    lds = size_t(tiles_wg) * k.tile_lds;
-  } else {
-    lds = std::max(size_t(tiles_wg) * k.tile_lds, size_t(splitk_areas(NB)) * 32 * splitk_pitch(NB) * 4 + 16);
-  }
+  const size_t lds = std::max(size_t(tiles_wg) * k.tile_lds, size_t(splitk_areas(NB)) * 32 * splitk_pitch(NB) * 4 + 16);
   // once per instantiation: both variants may use all of a CU's LDS (lists of large kernels need more than the default 64 KB)
   static const hipError_t attr = [] {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_os_splitk_kernel<T, NB, false, AM, PACKED, FROM, STAGED>),
