@@ -177,8 +177,8 @@ __device__ inline void redo_nan(const floatx16 (&acc)[NB], int rows, int lane, T
 // A tile of 1024 rows takes 26 us (listing 5, dense cells 7, products 5, additions 4, stores 3): the latencies of a chain of
 // dependent loads, of which one workgroup fills a CU's LDS.  3 M random voxels, 64->64: 513 us by phases, 326 us pooled;
 // 1 M: 176 / 104; 200 k: 43 / 33; indoor scans, 240 k: 46 / 40.  It is reached through the phase kernel: where the layer's
-// size alone makes prefer_splitk choose the other kernel (64 columns with a last round that is not full, such as 200 k and
-// 300 k voxels; most layers of 128 columns and more with prepacked weights), it is taken on request only.
+// size alone makes prefer_splitk choose the other kernel (two or three rounds of workgroups that are not full, such as 64 columns of
+// 200 k and 300 k voxels or 128 of 100 k and 150 k; wide layers of more than 128 input channels), it is taken on request only.
 constexpr int POOL_WAVES = 16, POOL_BLOCKS = 32;
 constexpr int POOL_DENSE = 8;     // valid rows from which a cell is multiplied on its own
 constexpr int POOL_PAIRS = 64;    // pairs in a block's list (a cell that does not fit any more is multiplied on its own too)
@@ -424,7 +424,7 @@ __device__ __forceinline__ void conv_pool_tile(PoolLds& L, const int64_t blk0, c
 }
 
 // Whether a level is one for the pooled way: enough tiles to give most CUs one (100 k random voxels, 64->64: 23 us by phases,
-// 25 pooled), and three quarters of 64 blocks looked at marked by the search as holding at most POOL_BLOCK_PAIRS pairs.
+// 25 pooled), and three quarters of 64 blocks looked at marked by the search (which see: POOL_MARK).
 // Every workgroup finds the same.
 __device__ inline bool pool_level(const uint32_t* __restrict__ block_masks, int64_t n_blocks, int n_slabs, int lane) {
   if (n_blocks * n_slabs < 128 * POOL_BLOCKS) return false;
@@ -1713,8 +1713,13 @@ static void launch_os_splitk(const ConvArgs& a) {
 //   64->128   20 k 1250 17.4 / 16.6    35 k 2188 20.4 / 22.8    50 k 3125 23.1 / 28.7    70 k 4375 40.9 / 35.8   100 k 6250 43.3 / 47.0
 //  128->128   35 k 2188 35.3 / 37.6    50 k 3125 39.3 / 47.3    70 k 4375 70.7 / 56.9   100 k 6250 76.1 / 74.0   120 k 7500 80.8 / 85.1
 //  256->256   20 k 2500 66.3 / 74.9    35 k 4375  135 /  106    50 k 6250  140 /  137    70 k 8750  204 /  180   120 k 15000 299 / 280
-// Many rounds are scenes of a million voxels and more, whose neighbourhoods are nearly empty (the pooled way): 64->64, 400 k random voxels
-// 49.3 / 65.0, 128->128 200 k 72.6 / 106, 400 k 127 / 193.
+// Four rounds of 64 columns are scenes of 400 k voxels and more (four of 128: 200 k), whose neighbourhoods are nearly empty (the pooled way where
+// the layer is not strided), random voxels: 16->64 400 k 43.5 / 43.5, 32->64 46.8 / 45.1, 64->64 54.5 / 67.8, 128->64 73.1 / 118; 128->128 200 k 71.9 / 110, 400 k 133 / 202;
+// stride 2, 220 k 64->128 81.0 / 84.8, 128->128 143.9 / 144.2, 430 k 140 / 156, 251 / 271, indoor 300 k 101 / 104, 181 / 178.
+// With two or three rounds the size does not tell which kernel is faster, and four fifths of 64 columns is a line between scenes: 165 k to
+// 200 k LiDAR voxels (63 to 76 % full) 32->64 31.8 to 33.2 / 27.1 to 30.5, but 64->64 42.0 to 42.6 / 40.2 to 46.5; 300 k indoor voxels (76 %)
+// 64->64 57.0 / 53.9, but random ones 47.9 / 53.4, 150 k (57 %) 26.2 / 30.5, with stride 2 40.8 / 35.4.  128 columns, LiDAR, 64->128, 100 k to 150 k (69 to 76 %) 41.6 to 61.7
+// / 43.2 to 60.9, 165 k (84 %) 62.7 / 65.1; random 100 k 26.2 / 38.0; 128->128, 165 k 114 / 112.
 // 32-column slabs (32->32: 120 k voxels 18.8 / 15.6, 10^6 118 / 80) and large kernels (5x5x5 and up) favour the split-k kernel.
 template <typename T>
 static bool prefer_splitk(const ConvArgs& a) {

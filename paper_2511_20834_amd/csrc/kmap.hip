@@ -156,6 +156,7 @@ struct SearchArgs {
   int32_t* arrived;
   KMask os_k, ws_k;
   int n_tiles_cap;
+  int mark_pairs;  // (K = 3) blocks of at most so many pairs are marked
   CountNote note_in, note_out;  // where the host polls for the levels' counts
 };
 constexpr int SEARCH_BATCH = 8;
@@ -577,7 +578,7 @@ __global__ __launch_bounds__(64 * K) void kmap_search_kernel(const SearchBatch<K
   if (M) {
     const int n_bl = (rows + 31) >> 5;
     for (int e = tid; e < n_bl * MW; e += 64 * K)
-      args.block_masks[b0 * MW + e] = s_mask[e] | (K == 3 && s_pairs[K == 3 ? e : 0] <= POOL_BLOCK_PAIRS ? POOL_MARK : 0u);
+      args.block_masks[b0 * MW + e] = s_mask[e] | (K == 3 && s_pairs[K == 3 ? e : 0] <= args.mark_pairs ? POOL_MARK : 0u);
   }
 }
 
@@ -847,6 +848,7 @@ static SearchArgs<KeyT> search_args(spc_kmap* m) {
   a.tile_sub = m->tile_sub;
   a.inv_parent = m->inv_parent;
   a.arrived = m->arrived;
+  a.mark_pairs = in == out ? POOL_BLOCK_PAIRS : -1;
   return a;
 }
 

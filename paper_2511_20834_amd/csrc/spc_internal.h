@@ -291,9 +291,11 @@ struct MapsReady {
 }  // namespace spc
 
 // The 27 offsets of a 3x3x3 kernel leave mask bits free: the search marks the blocks of few pairs, from which the feature
-// kernel tells a level whose neighbourhoods are nearly empty.  32 pairs are the voxels themselves; with 18 more on average
-// the product rows of the pooled way no longer fit its LDS at once (indoor scans, 64->64: 240 k voxels, 14 more, 40 us
-// pooled and 46 by phases; 300 k, 17 more, 73 and 66).
+// kernel tells a level whose neighbourhoods are nearly empty.  32 pairs are the voxels themselves, a cell that is multiplied on its
+// own; with 18 more on average the product rows of the pooled way no longer fit its LDS at once (indoor scans, 64->64: 240 k voxels,
+// 14 more, 40 us pooled and 46 by phases; 300 k, 17 more, 73 and 66).  Where a level's voxels are not their own neighbours (strided and
+// transposed layers) all pairs are product rows and none is marked: random voxels, stride 2, 64->128, 110 k 84 us pooled and 42 by
+// phases, 430 k 319 and 140.
 constexpr uint32_t POOL_MARK = 1u << 31;
 constexpr int POOL_BLOCK_PAIRS = 50;
 constexpr int SHARED_TILES = 1024;  // tiles of a feature kernel that may be shared by several workgroups

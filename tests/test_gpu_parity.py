@@ -868,7 +868,7 @@ def test_conv_sparse_neighbourhoods(n, cin, cout, dtype, density, cube):
 
 @pytest.mark.parametrize("transposed", [0, 1])
 def test_conv_sparse_neighbourhoods_of_strided_layers(transposed):
-    """The pooled way on a 3x3x3 stride-2 level, whose voxel count only the device knows, and on its transposed layer."""
+    """A 3x3x3 stride-2 level of few pairs, whose voxel count only the device knows, and its transposed layer."""
     n, side = 150_003, 370
     c = _lin_cloud(np.random.default_rng(81).choice(side ** 3, size=n, replace=False), (side, side, side))
     desc = fit_desc(c, [(3, 1, 2)])
@@ -876,7 +876,7 @@ def test_conv_sparse_neighbourhoods_of_strided_layers(transposed):
     cs, _ = oracle.sort_coords(c)
     src, dst, M = oracle_layer(cs, 3, 1, 2, transposed)
     pairs = np.add.reduceat((M >= 0).sum(1), np.arange(0, len(M), 32))
-    assert len(dst) > 131_072 and (pairs <= 50).mean() > 0.9  # a level for the pooled way
+    assert len(dst) > 131_072 and (pairs <= 50).mean() > 0.9  # (as few as on the levels of the pooled way)
     Ft, F64 = to_torch(synth.features(len(src), 32, np.float16, seed=82), torch.float16)
     Wt, W64 = to_torch(synth.weights(27, 32, 64, np.float16, seed=83), torch.float16)
     km = B.spc_build_kmap(keys, desc, 3, 1, 2, transposed, B.LAYOUT_OS)
@@ -885,6 +885,25 @@ def test_conv_sparse_neighbourhoods_of_strided_layers(transposed):
     assert km.n_out == len(dst)
     assert_close(out[: len(dst)].cpu().to(torch.float64).numpy(), oracle.conv(M, F64, W64), 1e-2, "pooled")
     assert bool((out[len(dst):] == 7.0).all())
+    km.destroy()
+
+
+@pytest.mark.parametrize("stride,transposed", [(1, 0), (2, 0), (2, 1)])
+def test_pooled_where_voxels_are_their_own_neighbours(stride, transposed):
+    """The pooled way takes a level of 64 Ki rows for two slabs of columns and not for one, and sums in another order: the first
+    slab's bits tell.  A strided or transposed layer has no offset that pairs every voxel, and goes by phases in both."""
+    n, side = 80_001, 300
+    c = _lin_cloud(np.random.default_rng(86).choice(side ** 3, size=n, replace=False), (side, side, side))
+    desc = fit_desc(c, [(3, 1, 2)])
+    keys, _ = gpu_pack(c, desc)
+    km = B.spc_build_kmap(keys, desc, 3, 1, stride, transposed, B.LAYOUT_OS)
+    assert km.n_out > 65_536 + 32 and km.n_out < 131_072
+    F = torch.from_numpy(synth.features(n, 32, np.float16, seed=87)).cuda()
+    W = torch.from_numpy(synth.weights(27, 32, 128, np.float16, seed=88)).cuda()
+    two = B.spc_conv_forward(km, F, W, flags=B.CONV_OS_PHASE)
+    one = B.spc_conv_forward(km, F, W[:, :, :64].contiguous(), flags=B.CONV_OS_PHASE)
+    assert_close(two[:, :64].float().cpu().numpy(), one.float().cpu().numpy(), 2e-3, "summation order")
+    assert torch.equal(two[:, :64], one) == (stride > 1)
     km.destroy()
 
 
