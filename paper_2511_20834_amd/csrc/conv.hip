@@ -1286,7 +1286,10 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, PACKED ? splitk_occupancy(NB, FR
       for (int left = n * KG; left > 0; left -= D) {
         static_for<D>([&](auto E_) {
           constexpr int E = decltype(E_)::value;
-          if (E > 0 && left <= E) return;
+          // The last entry of an odd number ends here, or (128 columns) is loaded and left alone: where only some paths have loads under
+          // way, the compiler waits for all of them at every second entry.  Passes, 5x5x5 256->256, us, ending / loading: 128 columns,
+          // 2.8 k voxels (a workgroup per CU) 137 / 115; 64 columns, 6 k 155 / 160, 1.2 k 48.5 / 49.2, fp32 64->64 30 k 246 / 249.
+          if (NB < 4 && E > 0 && left <= E) return;
           V a_now[GS];
           if constexpr (STAGED) {
             put_at[0] = av[E][0];
@@ -1302,7 +1305,8 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, PACKED ? splitk_occupancy(NB, FR
           }
           static_for<GS>([&](auto S_) {
             constexpr int S = decltype(S_)::value;
-            if (S == 0 || GS * g_c + S < KK) {  // (uniform)
+            // (uniform)
+            if ((E == 0 || left > E) && (S == 0 || GS * g_c + S < KK)) {
 #pragma unroll
               for (int nb = 0; nb < NB; ++nb) acc[nb] = Mfma<T>::mma(a_now[S], bv[E][S][nb], acc[nb]);
             }

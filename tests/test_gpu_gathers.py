@@ -148,6 +148,19 @@ def test_splitk_far_weights(dtype, cin, pitch, cout):
     B.spc_release_cache()
 
 
+# (more tiles than half the CUs: slabs of 128 columns; one and three slabs of channels per offset: odd numbers of entries per wave)
+@pytest.mark.parametrize("density", [0.02, 0.3])
+@pytest.mark.parametrize("cin", [16, 48])
+def test_wide_slabs_of_large_kernels(density, cin):
+    n, cout = 4203, 128
+    for layout, dataflow in ((B.LAYOUT_OS, B.DATAFLOW_OS), (B.LAYOUT_WS, B.DATAFLOW_WS)):
+        km, M = _level(n, density, 5, layout)
+        F, F64, W, W64 = _tensors(n, 125, cin, cout, torch.float16)
+        y = B.spc_conv_forward(km, F, B.spc_conv_prepare_weights(W), dataflow, B.CONV_PACKED_WEIGHTS)
+        assert_close(y.cpu().to(torch.float64).numpy(), oracle.conv(M, F64, W64), TOL[torch.float16], (density, cin, layout))
+        km.destroy()
+
+
 # (grids whose bound of the output rows lies above the lines where two waves share a tile instead of four, and whose count lies below)
 @pytest.mark.parametrize("side,K,cin,cout,dataflow", [(40, 2, 32, 32, B.DATAFLOW_OS), (40, 3, 4, 32, B.DATAFLOW_OS),
                                                       (40, 2, 32, 64, B.DATAFLOW_WS), (56, 3, 32, 32, B.DATAFLOW_OS)])
