@@ -1280,8 +1280,13 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, PACKED ? splitk_occupancy(NB, FR
       next_rows();
       static_for<D>([&](auto E_) {
         if (decltype(E_)::value > 0) advance();
+        // (in the loop's order: were weights requested before rows here, the loop's wait for the rows would be one for weights as well)
         issue_rows(E_);
-        static_for<GS>([&](auto S_) { issue_weights(E_, S_); });
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<GS>([&](auto S_) {
+          issue_weights(E_, S_);
+          __builtin_amdgcn_sched_barrier(0);
+        });
       });
       for (int left = n * KG; left > 0; left -= D) {
         static_for<D>([&](auto E_) {
