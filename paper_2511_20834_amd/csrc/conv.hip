@@ -1281,8 +1281,8 @@ __global__ __launch_bounds__(64 * SPLITK_WAVES, PACKED ? splitk_occupancy(NB, FR
       static_for<D>([&](auto E_) {
         if (decltype(E_)::value > 0) advance();
         // (in the loop's order: were weights requested before rows here, the loop's wait for the rows would be one for weights as well.
-        // Replayed network of 21 k voxels 262 -> 242 us.  fp32, with its four times as many loads, waits for all of them and is the
-        // faster for it: 50 k 32->32 46.8 us a pass, 47.6 with the order; 87 k 32->64 93.0 and 95.5)
+        // Replayed network of 21 k voxels 262 -> 242 us.  fp32, with its four times as many loads, gains nothing by it: 87 k voxels
+        // 32->64 95.5 us a pass with and without)
         auto keep_order = [] {
           if constexpr (sizeof(T) == 2) __builtin_amdgcn_sched_barrier(0);
         };
