@@ -1,28 +1,22 @@
 // Sort of packed voxel keys for the cloud sizes of this workload (thousands to a few million
-// keys): one most-significant-digit split into fine bins, then every key is ranked by
-// counting inside the window of bins around it (from 600 k keys on after a second split of the
-// window in LDS, see bs_rank_lds_kernel).  Short launches, no look-back spinning:
+// keys), without look-back spinning: every workgroup orders its share of the keys by the top `fb` used key bits ("bins") in LDS, and
+// further workgroups take whole bins from all shares and put them in order (two launches, see split + merge).
+// Fewer keys than BS_MIN_N are sorted by one workgroup.  Recorded sorts (stream capture) of up to BS_LARGE_N keys go another
+// way, in three launches or four:
 //
-//   count    each workgroup produces its share of the keys (packing coordinates, Section 5.3,
-//            or masking the keys of a finer level, Section 5.5), histograms the top `fb` used
-//            key bits ("fine bins") in LDS, adds its counts to the bins' totals in memory and keeps
-//            what it found there, its place inside the bins, in its row of a table;
-//   colscan  (large inputs only, where the additions would be too many: the count pass then writes
-//            the counts) exclusive prefixes down the table's columns, and the bins' totals;
+//   count    each workgroup produces its share of the keys, histograms their bins in LDS, adds its counts to the bins' totals in
+//            memory and keeps what it found there, its place inside the bins, in its row of a table (or writes the counts);
+//   colscan  (above BS_ADD_N) exclusive prefixes down the table's columns, and the bins' totals;
 //   scatter  each workgroup scans the bin totals (where every bin starts) and moves its keys,
 //            with their source index, to their bin's range; the workgroups also write, for every
 //            64 scattered positions, the window of whole bins that covers them;
 //   rank     64 keys per workgroup; a key's final position is the start of its window plus the
 //            number of window keys that sort before it, counted by comparing against every
-//            window key (see bs_rank_kernel).  Quadratic in the bin size, but spread evenly over
-//            the chip whatever the key distribution (a LiDAR sweep is many times denser near the
-//            sensor, and x, the most significant spatial field, makes a bin a slab of the scene).
+//            window key (see bs_rank_kernel).
 //
-// Pack + sort ranks (key, scattered position) pairs, so equal keys (not a valid cloud, but not
+// Pack + sort orders (key, source) pairs, so equal keys (not a valid cloud, but not
 // rejected unless validation was asked for) still get distinct positions and the permutation is
-// complete whatever the input.  Downsampling ranks the masked keys alone: equal keys fall on one
-// position, first arrivals are marked in a bitmap and counted per chunk with global atomics,
-// and one more kernel, compact, closes the gaps.
+// complete whatever the input.  Downsampling sorts the masked keys alone and drops the repeated ones.
 #include <algorithm>
 #include <type_traits>
 
@@ -37,10 +31,6 @@ __device__ inline int bs_bin(uint64_t key, int shift, int n_bin) {
   const uint64_t b = key >> shift;
   return b < uint64_t(n_bin) ? static_cast<int>(b) : n_bin - 1;  // all-ones keys of rejected rows go last
 }
-
-// What the scatter pass moves: the key, or (REC) the record (32-bit key, source index), whose bin starts 32 bits higher.
-template <typename KeyT, bool REC>
-using BsElem = std::conditional_t<REC, uint64_t, KeyT>;
 
 // ---------------------------------------------------------------- key sources
 // A source splits "fetch" from "make the key": the kernels below fetch a batch of rows first and
@@ -96,18 +86,174 @@ __device__ inline T* level_ws(T* p, size_t ws_pitch) {
   return reinterpret_cast<T*>(reinterpret_cast<Byte*>(p) + blockIdx.y * ws_pitch);
 }
 
-// ---------------------------------------------------------------- count
-// ADD: the counts go to the bins' totals (zero before), in whatever order the workgroups come; 4096 bins and 30 workgroups with
-// keys in all of them take 1.7 us, fewer bins are hit the shorter a workgroup's share is.
-template <typename KeyT, typename Src, bool ADD>
-__global__ __launch_bounds__(BS_WIDE) void bs_count_kernel(const Src srcs, int64_t n, int per, int shift, int n_bin,
-                                                           KeyT* __restrict__ keys0, int32_t* __restrict__ table, size_t ws_pitch,
-                                                           int32_t* __restrict__ tot, size_t tot_pitch) {
-  extern __shared__ int hist[];  // [n_bin]
-  const auto src = srcs.level(blockIdx.y);
-  using Level = std::remove_const_t<decltype(src)>;
-  keys0 = level_ws(keys0, ws_pitch);
-  table = level_ws(table, ws_pitch);
+// ---------------------------------------------------------------- split + merge
+// The sort in two launches (three with the bins' starts of large inputs, one more for levels):
+//
+//   split   (bs_count_kernel, SPLIT) a workgroup makes its share of the keys, orders them by bin in LDS and stores them, bin after
+//           bin, to a region of its own, with a row of the table `off` that says where every bin starts in there (16 bits each; the
+//           last entry is the region's number of keys).  Nothing is scattered in memory.  Up to BS_ADD_N keys it also adds its counts
+//           to the bins' totals;
+//   starts  (bs_starts_kernel, above BS_ADD_N keys, where that would be too many additions, and for recorded levels) sums the
+//           table's columns, which gives every bin's place in the sorted sequence, and from these every merging workgroup's bins;
+//   merge   workgroup p takes the whole bins that start among sorted positions p * q .. p * q + q - 1: one contiguous piece of every
+//           region.  It fetches them, orders them in LDS (a second split by their next key bits, then counting inside that split's
+//           bins) and stores them, lane next to lane;
+//   compact (levels) equal keys are all in one workgroup, which drops them; this kernel closes the gaps between the workgroups.
+//
+// A bin has one owner, so no windows overlap and nothing is compared twice, and no key is a memory transaction of its own on its
+// way.  What bounds it up to half a million keys: two launches, three dependent round trips of the merge (totals, pieces, keys) and
+// fetching its instructions, which run once: unrolled eight and sixteen times the same merge took 17 us where this one takes 8.6,
+// so loops over bins and regions stay rolled and a thread has two keys.  From 10^6 keys on: the coordinates (split 30 us at 3 * 10^6),
+// whose workgroups fill a CU's LDS, and the short pieces (merge 30 us).  us, kernels of count / scatter / rank (and column scan, windows that did
+// not fit, from 600 k) against split / starts / merge: 6 k 4.0 / 4.4 / 4.3 against 4.0 / - / 6.6; LiDAR 120 k 4.9 / 6.5 / 9.4 against 5.0 / - / 8.6;
+// indoor 240 k 7.4 / 11.2 / 13.2 against 9.0 / - / 9.4; random 3 * 10^6 19.6 / 9.9 / 44.1 / 26.6 / 4.8 against 29.7 / 6.0 / 29.4; a level of
+// 120 k (with its compaction) 4.5 / 6.7 / 10.2 / 4.2 against 4.7 / - / 9.9 / 4.1.
+// Recorded sorts of up to BS_LARGE_N keys count, scatter and rank: what they launch is tested for.
+constexpr int BS_MT = 1024;        // merge threads
+constexpr int BS_SPLIT_KPT = 12;   // keys per split thread at most
+constexpr int BS_RANK_SOLO_N = 400000;
+constexpr int BS_NSUB = 4096;      // second split's bins
+constexpr int BS_ARRIVE = 16, BS_ARRIVE_PITCH = 32;  // counters of the workgroups that have read the totals, on lines of their own, and one more
+constexpr int BS_MAX_SPLIT = 1024; // split workgroups
+static_assert(BS_MAX_BIN / 2 <= 8 * BS_MT, "two rounds of bins where there are totals (up to 8192)");
+static_assert(BS_NSUB == 4 * BS_MT && BS_MAX_SPLIT == BS_MT, "bins and regions per thread");
+
+// Inclusive sum over the lanes of a wave.
+__device__ inline int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);  // row_shr 1, 2, 4, 8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // lane 15 of rows 0 and 2 to the row behind
+  return x + __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // lane 31 to rows 2 and 3
+}
+// Exclusive sum over a workgroup of WAVES waves; *total is that of all.  `sums` is free again after the workgroup's next barrier.
+template <int WAVES>
+__device__ inline int block_scan(int v, int* sums, int* total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int x = wave_scan(v);
+  if (lane == 63) sums[wave] = x;
+  __syncthreads();
+  const int s = wave_scan(lane < WAVES ? sums[lane] : 0);
+  *total = __builtin_amdgcn_readlane(s, WAVES - 1);
+  const int before = __shfl(s, max(wave - 1, 0), 64);
+  return x - v + (wave > 0 ? before : 0);
+}
+
+// A region's elements: 64-bit records (key, source index) for 32-bit keys of coordinates; keys, with the source indices in an
+// array of their own, for 64-bit ones; keys alone for levels.
+template <typename KeyT, bool DEDUP>
+struct BsForm {
+  static constexpr bool REC = !DEDUP && sizeof(KeyT) == 4, ROWS = !DEDUP && sizeof(KeyT) == 8;
+  using Elem = std::conditional_t<REC, uint64_t, KeyT>;
+  __device__ static KeyT key(Elem e) { return static_cast<KeyT>(REC ? static_cast<uint64_t>(e) >> 32 : e); }
+};
+constexpr int bs_off_pitch(int n_bin) { return n_bin + 8; }
+// LDS of the split kernel: two bins' counts to a word, the region, and (ROWS) its keys' places in the share.
+template <typename KeyT, bool DEDUP>
+size_t bs_split_lds(int n_bin, int per) {
+  using F = BsForm<KeyT, DEDUP>;
+  return size_t(std::max(n_bin / 2, 4) + 4) * 4 + size_t(per) * (sizeof(typename F::Elem) + (F::ROWS ? 2 : 0));
+}
+
+template <typename KeyT, bool DEDUP, int KPT, bool ADD, typename Level>
+__device__ inline void bs_split(const Level& src, int64_t n, int per, int shift, int n_bin,
+                                typename BsForm<KeyT, DEDUP>::Elem* __restrict__ recs, int32_t* __restrict__ rows, uint16_t* __restrict__ off,
+                                int32_t* __restrict__ tot) {
+  using F = BsForm<KeyT, DEDUP>;
+  using Elem = typename F::Elem;
+  extern __shared__ __align__(16) unsigned bs_lds[];
+  __shared__ int sums[BS_WIDE / 64];
+  unsigned* hist = bs_lds;
+  const int n_words = n_bin / 2;
+  Elem* stage = reinterpret_cast<Elem*>(bs_lds + max(n_words, 4) + 4);  // (one more start behind the last bin's)
+  uint16_t* place = reinterpret_cast<uint16_t*>(stage + per);
+  const int t = threadIdx.x;
+  const int64_t lo = int64_t(blockIdx.x) * per, hi = min<int64_t>(n, lo + per);
+  typename Level::Raw raw[KPT];
+#pragma unroll
+  for (int u = 0; u < KPT; ++u)
+    if (u * BS_WIDE < per) raw[u] = src.load(min<int64_t>(lo + u * BS_WIDE + t, hi - 1));
+  for (int b = t; b < n_words; b += BS_WIDE) hist[b] = 0u;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < KPT; ++u)
+    if (u * BS_WIDE < per) Level::pin(raw[u]);
+  bool bad = false;
+  KeyT key[KPT];
+  int at[KPT];  // bin << 16 | place among the share's keys of the bin, or -1
+#pragma unroll
+  for (int u = 0; u < KPT; ++u)
+    if (u * BS_WIDE < per) {
+      bool bad_u = false;
+      key[u] = src.key(raw[u], bad_u);
+      at[u] = -1;
+      if (lo + u * BS_WIDE + t < hi) {
+        bad |= bad_u;
+        if (!src.skip(raw[u], key[u])) {
+          const int bin = bs_bin(key[u], shift, n_bin), half = 16 * (bin & 1);
+          at[u] = (bin << 16) | static_cast<int>((atomicAdd(&hist[bin >> 1], 1u << half) >> half) & 0xffffu);
+        }
+      }
+    }
+  src.report(bad);
+  __syncthreads();
+  // starts of the bins inside the region
+  off += int64_t(blockIdx.x) * bs_off_pitch(n_bin);
+  constexpr int WPT = BS_MAX_BIN / 2 / BS_WIDE;
+  const int wpt = max(n_words / BS_WIDE, 1), w0 = t * wpt;
+  unsigned c[WPT];
+  int sum = 0;
+#pragma unroll
+  for (int j = 0; j < WPT; ++j) {
+    c[j] = j < wpt && w0 < n_words ? hist[w0 + j] : 0u;
+    sum += static_cast<int>((c[j] & 0xffffu) + (c[j] >> 16));
+  }
+  int total;
+  unsigned run = block_scan<BS_WIDE / 64>(sum, sums, &total);
+#pragma unroll
+  for (int j = 0; j < WPT; ++j)
+    if (j < wpt && w0 < n_words) {
+      const unsigned a = c[j] & 0xffffu, b = c[j] >> 16;
+      const unsigned starts = run | ((run + a) << 16);
+      hist[w0 + j] = starts;
+      reinterpret_cast<unsigned*>(off)[w0 + j] = starts;
+      run += a + b;
+    }
+  if (t == 0) {
+    off[n_bin] = static_cast<uint16_t>(total);
+    hist[n_words] = static_cast<unsigned>(total);
+  }
+  __syncthreads();
+  if constexpr (ADD) {  // (lane next to lane: an instruction's additions then meet in few lines of memory)
+    for (int w = t; w < n_words; w += BS_WIDE) {
+      const unsigned here = hist[w], next = hist[w + 1];
+      const int a = static_cast<int>((here >> 16) - (here & 0xffffu)), b = static_cast<int>((next & 0xffffu) - (here >> 16));
+      if (a) __hip_atomic_fetch_add(tot + 2 * w, a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (b) __hip_atomic_fetch_add(tot + 2 * w + 1, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < KPT; ++u)
+    if (u * BS_WIDE < per && at[u] >= 0) {
+      const int bin = at[u] >> 16, to = static_cast<int>((hist[bin >> 1] >> (16 * (bin & 1))) & 0xffffu) + (at[u] & 0xffff);
+      if constexpr (F::REC) stage[to] = (uint64_t(key[u]) << 32) | static_cast<uint32_t>(lo + u * BS_WIDE + t);
+      else stage[to] = key[u];
+      if constexpr (F::ROWS) place[to] = static_cast<uint16_t>(u * BS_WIDE + t);
+    }
+  __syncthreads();
+  for (int i = t; i < total; i += BS_WIDE) {
+    recs[lo + i] = stage[i];
+    if constexpr (F::ROWS) rows[lo + i] = static_cast<int32_t>(lo) + place[i];
+  }
+}
+
+// (recorded sorts)
+template <typename KeyT, bool ADD, typename Level>
+__device__ inline void bs_count(const Level& src, int64_t n, int per, int shift, int n_bin, KeyT* __restrict__ keys0,
+                                int32_t* __restrict__ table, int32_t* __restrict__ tot) {
+  extern __shared__ __align__(16) unsigned bs_lds[];
+  int* hist = reinterpret_cast<int*>(bs_lds);  // [n_bin]
   for (int b = threadIdx.x; b < n_bin; b += BS_WIDE) hist[b] = 0;
   __syncthreads();
   const int64_t lo = int64_t(blockIdx.x) * per, hi = min<int64_t>(n, lo + per);
@@ -134,7 +280,6 @@ __global__ __launch_bounds__(BS_WIDE) void bs_count_kernel(const Src srcs, int64
   __syncthreads();
   table += int64_t(blockIdx.x) * n_bin;
   if constexpr (ADD) {
-    tot = level_ws(tot, tot_pitch);
     for (int b0 = threadIdx.x; b0 < n_bin; b0 += 4 * BS_WIDE) {
       int c[4], at[4];
 #pragma unroll
@@ -150,429 +295,447 @@ __global__ __launch_bounds__(BS_WIDE) void bs_count_kernel(const Src srcs, int64
     for (int b = threadIdx.x; b < n_bin; b += BS_WIDE) table[b] = hist[b];
   }
 }
-// Clears the totals (one row of the grid per level) where they are not kept cleared.
-__global__ __launch_bounds__(BS_THREADS) void bs_clear_kernel(int32_t* __restrict__ tot, int n_bin, size_t tot_pitch) {
+// ---------------------------------------------------------------- count
+// First launch of a sort.  KPT > 0: split (KPT keys per thread at most); `out` is the regions, `table` their rows of bin starts, `rows`
+// the source indices where they are apart, and `arrived` is cleared for the merge.  KPT = 0 (recorded sorts): `out` is the keys as
+// they come and `table` rows of counts, or with ADD of what their addition to the totals returned.
+// ADD: the counts go to the bins' totals (zero before), in whatever order the workgroups come; 4096 bins and 30 workgroups with
+// keys in all of them take 1.7 us, fewer bins are hit the shorter a workgroup's share is.
+template <typename KeyT, typename Src, bool DEDUP, int KPT, bool ADD>
+__global__ __launch_bounds__(BS_WIDE) void bs_count_kernel(const Src srcs, int64_t n, int per, int shift, int n_bin, void* out,
+                                                           void* table, size_t ws_pitch, int32_t* tot, size_t tot_pitch, int32_t* rows,
+                                                           int32_t* arrived) {
+  const auto src = srcs.level(blockIdx.y);
+  if constexpr (KPT > 0) {
+    if (arrived && blockIdx.x == 0 && threadIdx.x <= BS_ARRIVE) arrived[threadIdx.x * BS_ARRIVE_PITCH] = 0;
+    bs_split<KeyT, DEDUP, KPT, ADD>(src, n, per, shift, n_bin, level_ws(static_cast<typename BsForm<KeyT, DEDUP>::Elem*>(out), ws_pitch), rows,
+                                    level_ws(static_cast<uint16_t*>(table), ws_pitch), ADD ? level_ws(tot, tot_pitch) : nullptr);
+  } else {
+    bs_count<KeyT, ADD>(src, n, per, shift, n_bin, static_cast<KeyT*>(out), static_cast<int32_t*>(table), tot);
+  }
+}
+// Clears the totals where they are not kept cleared.
+__global__ __launch_bounds__(BS_THREADS) void bs_clear_kernel(int32_t* __restrict__ tot, int n_bin) {
   const int b = blockIdx.x * BS_THREADS + threadIdx.x;
-  if (b < n_bin) level_ws(tot, tot_pitch)[b] = 0;
-}
-// The same by the last kernel of a sort, for the next one.  Its grid has at least n / 4 threads in whole workgroups of 64 or
-// 256, and a plan at most 256 or n / 8 bins: a thread per bin.  (As a loop with the grid's stride, which reads the launch's sizes
-// from memory first: a sort of 6 k to 70 k keys 0.4 us longer, of 240 k 0.9.)
-template <int THREADS>
-__device__ inline void bs_clear_after(int32_t* tot, int n_bin) {
-  const int b = blockIdx.x * THREADS + threadIdx.x;
-  if (tot && b < n_bin) tot[b] = 0;
+  if (b < n_bin) tot[b] = 0;
 }
 
-// ---------------------------------------------------------------- column scan (large inputs)
-// One thread per four bins: before[w][f] receives the number of keys of bin f held by workgroups
-// < w, tot[f] the bin's total.  The loads of 32 table rows are in flight together (16: 1 us more from 500 k keys on).
-constexpr int BS_COL_THREADS = 64;
-__global__ __launch_bounds__(BS_COL_THREADS) void bs_colscan_kernel(const int32_t* __restrict__ table,
-                                                                    int32_t* __restrict__ before, int n_wg, int n_bin,
-                                                                    int32_t* __restrict__ tot, size_t ws_pitch) {
-  constexpr int ROWS = 32;
-  table = level_ws(table, ws_pitch);
-  before = level_ws(before, ws_pitch);
-  tot = level_ws(tot, ws_pitch);
-  const int f0 = (blockIdx.x * BS_COL_THREADS + threadIdx.x) * 4;
-  if (f0 >= n_bin) return;  // n_bin is a multiple of 4
-  int4 run = make_int4(0, 0, 0, 0);
-  for (int w0 = 0; w0 < n_wg; w0 += ROWS) {
-    int4 c[ROWS];
-#pragma unroll
-    for (int r = 0; r < ROWS; ++r) c[r] = *reinterpret_cast<const int4*>(table + int64_t(min(w0 + r, n_wg - 1)) * n_bin + f0);
-#pragma unroll
-    for (int r = 0; r < ROWS; ++r)
-      if (w0 + r < n_wg) {
-        *reinterpret_cast<int4*>(before + int64_t(w0 + r) * n_bin + f0) = run;
-        run.x += c[r].x;
-        run.y += c[r].y;
-        run.z += c[r].z;
-        run.w += c[r].w;
-      }
-  }
-  *reinterpret_cast<int4*>(tot + f0) = run;
-}
+// The bins of merging workgroup p: from bin `first` on, which starts at sorted position `start`, to bin `last`, which ends at `end` and is
+// not empty.  A workgroup whose `start` lies behind its positions, in a bin of an earlier one, has none.
+struct BsShare {
+  int32_t first, start, last, end;
+};
 
-// ---------------------------------------------------------------- scatter
-// Every workgroup scans the bin totals on its own (16 KB; cheaper than one more launch): start
-// of bin f, then the workgroup's first position in the bin, and moves its keys, with their source
-// index, to their bin's range.
-// It also prepares the rank pass: for every BS_PART scattered
-// positions the window of whole bins that covers them, BS_PAD_KEYS all-ones keys behind the last
-// key, the number of keys that take part and, for the downsampling variant (DEDUP: of a run of
-// equal adjacent keys only the first takes part), the cleared position bitmap and chunk counters.
-// What bounds it: the scattered stores, of which a CU issues one lane per cycle, so the shares of the workgroups are short
-// (see bucket_plan).
-// SUM (few workgroups, and no cleared block for the totals): `before` is the table of counts as the count pass leaves it
-// without ADD, and its rows are summed here, which saves the launch that would clear the totals.
-// REC (pack + sort of 32-bit keys that bs_rank_lds_kernel ranks): a key and its source index leave as one 8-byte record.
-// From half a million keys on hardly two keys of a workgroup share a bin, so every scattered store is a memory
-// transaction of its own, and one array of records takes half as many as two arrays.
-template <typename KeyT, bool DEDUP, bool REC, bool SUM>
-__global__ __launch_bounds__(BS_WIDE) void bs_scatter_kernel(const KeyT* __restrict__ keys0, int64_t n, int per, int shift,
-                                                             int n_bin, const int32_t* __restrict__ before,
-                                                             const int32_t* __restrict__ tot, size_t tot_pitch, BsElem<KeyT, REC>* __restrict__ keys1,
-                                                             int32_t* __restrict__ vals1, int2* __restrict__ win,
-                                                             int32_t* __restrict__ n_part_keys, uint32_t* __restrict__ bits,
-                                                             int n_words, int32_t* __restrict__ ccnt, int n_chunks,
-                                                             int32_t* __restrict__ rest_count, size_t ws_pitch) {
-  extern __shared__ int lds_bins[];
-  if (DEDUP) {
-    keys0 = level_ws(keys0, ws_pitch);
-    before = level_ws(before, ws_pitch);
-    if (!SUM) tot = level_ws(tot, tot_pitch);
-    keys1 = level_ws(keys1, ws_pitch);
-    win = level_ws(win, ws_pitch);
-    n_part_keys = level_ws(n_part_keys, ws_pitch);
-    bits = level_ws(bits, ws_pitch);
-    ccnt = level_ws(ccnt, ws_pitch);
-    rest_count = level_ws(rest_count, ws_pitch);
+// 128 bins per workgroup; a wave sums a sixteenth of the table's rows, 256 bytes at a time.
+constexpr int BS_START_BINS = 128;
+__global__ __launch_bounds__(BS_WIDE) void bs_starts_kernel(const uint16_t* __restrict__ off, int n_wg, int n_bin, int q, int n_share,
+                                                            BsShare* __restrict__ share, int32_t* __restrict__ n_kept, size_t ws_pitch) {
+  off = level_ws(off, ws_pitch);
+  share = level_ws(share, ws_pitch);
+  n_kept = level_ws(n_kept, ws_pitch);
+  constexpr int WAVES = BS_WIDE / 64;
+  __shared__ int part[WAVES][BS_START_BINS + 2];
+  __shared__ int tail[WAVES];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, f0 = blockIdx.x * BS_START_BINS, f1 = min(f0 + BS_START_BINS, n_bin);
+  const int pitch = bs_off_pitch(n_bin), col = min(f0 + 2 * lane, n_bin);
+  int a = 0, b = 0, e = 0, all = 0;  // where bins f0 + 2 lane, the next one and f1 start, and the number of keys
+#pragma unroll 8
+  for (int w = wave; w < n_wg; w += WAVES) {
+    const uint16_t* row = off + int64_t(w) * pitch;
+    const unsigned v = *reinterpret_cast<const unsigned*>(row + col);
+    a += static_cast<int>(v & 0xffffu);
+    b += static_cast<int>(v >> 16);
+    e += row[f1];
+    all += row[n_bin];
   }
-  int* pos = lds_bins;                    // [n_bin + 1] this workgroup's running position in every bin
-  int* bin_start = lds_bins + n_bin + 1;  // [n_bin + 1] where every bin starts
-  __shared__ int wave_tot[BS_WIDE / 64];
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  if (DEDUP) {  // the rank pass marks positions and counts them per chunk: both start from zero
-    for (int i = blockIdx.x * BS_WIDE + t; i < n_words; i += gridDim.x * BS_WIDE) bits[i] = 0u;
-    for (int i = blockIdx.x * BS_WIDE + t; i < n_chunks; i += gridDim.x * BS_WIDE) ccnt[i] = 0;
-  }
-  // a pass takes four keys per thread; the first pass's are requested before the scan, so that they arrive under it
-  const int64_t lo = int64_t(blockIdx.x) * per, hi = min<int64_t>(n, lo + per);
-  KeyT key[4], prev[4];
-  auto fetch = [&](int64_t i0) {
+  part[wave][2 * lane] = a;
+  part[wave][2 * lane + 1] = b;
+  if (lane == 0) part[wave][BS_START_BINS] = e, tail[wave] = all;
+  __syncthreads();
+  const int j = threadIdx.x, f = f0 + j;
+  if (j > BS_START_BINS) return;  // (two waves and a lane stay)
+  int s = 0, total = 0;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int64_t i = min<int64_t>(i0 + u * BS_WIDE, hi - 1);
-      key[u] = keys0[i];
-      prev[u] = DEDUP ? keys0[i > 0 ? i - 1 : 0] : KeyT(0);
+  for (int w = 0; w < WAVES; ++w) {
+    s += part[w][j];
+    total += tail[w];
+  }
+  if (f < f1) {
+    int end = 0;
+    const int behind = f + 1 < f1 ? j + 1 : BS_START_BINS;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) end += part[w][behind];
+    if (f == 0) share[0].first = 0, share[0].start = 0, *n_kept = total;
+    if (s < end) {  // not empty
+      const int p = s / q;
+      if (end >= (p + 1) * q || end == total) share[p].last = f, share[p].end = end;
+      for (int p1 = p + 1; p1 < n_share && p1 * q <= end; ++p1) share[p1].first = f + 1, share[p1].start = end;
     }
+  }
+}
+
+// ---------------------------------------------------------------- merge
+// Where a workgroup's bins start: from the bins' totals, from the sums of the table's columns (few regions, where there are no
+// totals), or as bs_starts_kernel has left them.
+enum { BS_TOTALS = 0, BS_TABLE = 1, BS_STARTS = 2 };
+template <typename KeyT, bool DEDUP>
+struct MergeArgs {
+  const typename BsForm<KeyT, DEDUP>::Elem* recs;
+  const int32_t* rows;
+  const uint16_t* off;
+  int n_wg, per, shift, n_bin, q, n, used_bits;
+  int32_t* tot;  // BS_TOTALS
+  size_t tot_pitch;
+  int clear;          // whether the totals are to be cleared (pack; levels: by the last kernel)
+  int32_t* arrived;   // zeros (from the split kernel)
+  const BsShare* share;  // BS_STARTS
+  int32_t* n_kept;
+  KeyT* out_k;        // pack: the sorted keys; levels: the distinct ones, those of workgroup p from out_at[p] on
+  int32_t* out_v;
+  int32_t *out_at, *out_n;
+  size_t ws_pitch;
+};
+
+// The part of a workgroup's LDS work that does not depend on where the keys come from: `count` keys (element u * BS_MT + t in
+// k[u], source indices in v[u] where they are apart) are put in order in L.key (L.row).  Their second bins are (key - base) >> ss,
+// below BS_NSUB; a key above lim (of a rejected row) has lim's.  L.hist is zero before.
+template <typename KeyT, bool DEDUP, int KPT>
+struct BsOrder {
+  using F = BsForm<KeyT, DEDUP>;
+  using Elem = typename F::Elem;
+  static constexpr int CAP = KPT * BS_MT, WAVES = BS_MT / 64;
+  static constexpr int VEC = 16 / sizeof(Elem);  // keys of a 16-byte read
+  using Vec = Elem __attribute__((ext_vector_type(VEC)));
+  struct Lds {
+    __align__(16) Elem key[CAP + 8];
+    int32_t row[F::ROWS ? CAP : 1];
+    __align__(16) int hist[BS_NSUB + 4];
+    int sums[WAVES];
+    int seg[64];
+    int32_t pre[BS_MAX_SPLIT];
+    int32_t src[BS_MAX_SPLIT];
+    int first, start, last, end, wave_last[WAVES];
+    int taken, done;
   };
-  fetch(lo + threadIdx.x);
-  // exclusive scan of the bin totals, four bins per thread and round (one round up to 4096 bins)
-  int total = 0;  // keys that take part (all of them unless DEDUP)
-  for (int r0 = 0; r0 < n_bin; r0 += 4 * BS_WIDE) {
-    const int f0 = r0 + t * 4;
-    int4 c = make_int4(0, 0, 0, 0), bef = c;
-    if (f0 < n_bin) {
-      if constexpr (SUM) {
-        constexpr int ROWS = 8;  // loads in flight
-        const int n_wg = gridDim.x, me = blockIdx.x;
-        for (int w = 0; w < n_wg; w += ROWS) {
-          int4 row[ROWS];
+  __device__ static void clear(Lds& L) { reinterpret_cast<int4*>(L.hist)[threadIdx.x] = make_int4(0, 0, 0, 0); }
+  // exclusive sums of the second bins' counts in place
+  __device__ static void scan(Lds& L) {
+    int4* h = reinterpret_cast<int4*>(L.hist) + threadIdx.x;
+    const int4 c = *h;
+    int total;
+    const int x = block_scan<WAVES>(c.x + c.y + c.z + c.w, L.sums, &total);
+    *h = make_int4(x, x + c.x, x + c.x + c.y, x + c.x + c.y + c.z);
+    if (threadIdx.x == 0) L.hist[BS_NSUB] = total;
+  }
+  __device__ static void order(Lds& L, Elem (&k)[KPT], int32_t (&v)[KPT], int count, KeyT base, KeyT lim, int ss) {
+    const int t = threadIdx.x;
+    auto second = [&](Elem e) { return static_cast<int>((min(F::key(e), lim) - base) >> ss); };
+    int r[KPT];
 #pragma unroll
-          for (int r = 0; r < ROWS; ++r) row[r] = *reinterpret_cast<const int4*>(before + int64_t(min(w + r, n_wg - 1)) * n_bin + f0);
+    for (int u = 0; u < KPT; ++u)
+      if (u * BS_MT + t < count) r[u] = atomicAdd(&L.hist[second(k[u])], 1);
+    __syncthreads();
+    scan(L);
+    __syncthreads();
 #pragma unroll
-          for (int r = 0; r < ROWS; ++r) {
-            const int all = w + r < n_wg ? -1 : 0, mine = w + r < me ? -1 : 0;
-            c.x += row[r].x & all, c.y += row[r].y & all, c.z += row[r].z & all, c.w += row[r].w & all;
-            bef.x += row[r].x & mine, bef.y += row[r].y & mine, bef.z += row[r].z & mine, bef.w += row[r].w & mine;
+    for (int u = 0; u < KPT; ++u)
+      if (u * BS_MT + t < count) {
+        const int at = L.hist[second(k[u])] + r[u];
+        L.key[at] = k[u];
+        if constexpr (F::ROWS) L.row[at] = v[u];
+      }
+    if (t < 8) L.key[count + t] = ~Elem(0);
+    __syncthreads();
+    // From here on a thread has the keys of its places: the lanes of a wave then look at the same few second bins, of which
+    // every lane reads the same keys.  Those in front of its bin are smaller and those behind it larger, so whole vectors are counted.
+    int d[KPT];
+#pragma unroll
+    for (int u = 0; u < KPT; ++u) {
+      const int at = u * BS_MT + t;
+      if (at < count) {
+        k[u] = L.key[at];
+        if constexpr (F::ROWS) v[u] = L.row[at];
+        const int b = second(k[u]), lo = L.hist[b] & -VEC, hi = L.hist[b + 1];
+        int c = lo;
+#pragma unroll 1
+        for (int s = lo; s < hi; s += 8) {
+          Vec e[8 / VEC];
+#pragma unroll
+          for (int x = 0; x < 8 / VEC; ++x) e[x] = reinterpret_cast<const Vec*>(L.key + s)[x];
+#pragma unroll
+          for (int x = 0; x < 8; ++x) {
+            const Elem o = e[x / VEC][x % VEC];
+            c += o < k[u] || (!F::REC && o == k[u] && s + x < at) ? 1 : 0;
           }
         }
-      } else {
-        c = *reinterpret_cast<const int4*>(tot + f0);
-        bef = *reinterpret_cast<const int4*>(before + int64_t(blockIdx.x) * n_bin + f0);
+        d[u] = c;
       }
     }
-    const int sum = c.x + c.y + c.z + c.w;
-    int x = sum;
-    for (int d = 1; d < 64; d <<= 1) {
-      const int y = __shfl_up(x, d, 64);
-      if (lane >= d) x += y;
-    }
-    if (r0 > 0) __syncthreads();  // the wave totals of the round before have been read
-    if (lane == 63) wave_tot[wave] = x;
     __syncthreads();
-    int base = total + x - sum;
-    for (int w = 0; w < BS_WIDE / 64; ++w) {
-      if (w < wave) base += wave_tot[w];
-      total += wave_tot[w];
-    }
-    if (f0 < n_bin) {
-      const int s0 = base, s1 = base + c.x, s2 = s1 + c.y, s3 = s2 + c.z;
-      pos[f0] = s0 + bef.x;
-      pos[f0 + 1] = s1 + bef.y;
-      pos[f0 + 2] = s2 + bef.z;
-      pos[f0 + 3] = s3 + bef.w;
-      bin_start[f0] = s0;
-      bin_start[f0 + 1] = s1;
-      bin_start[f0 + 2] = s2;
-      bin_start[f0 + 3] = s3;
-    }
+#pragma unroll
+    for (int u = 0; u < KPT; ++u)
+      if (u * BS_MT + t < count) {
+        L.key[d[u]] = k[u];
+        if constexpr (F::ROWS) L.row[d[u]] = v[u];
+      }
+    __syncthreads();
   }
-  if (t == 0) bin_start[n_bin] = total;
-  __syncthreads();
-  for (int64_t i0 = lo + threadIdx.x; i0 < hi; i0 += 4 * BS_WIDE) {
-    // all keys of the pass are fetched, then all positions drawn, then everything stored
-    bool use[4];
-    int p[4];
-    if (i0 >= lo + 4 * BS_WIDE) fetch(i0);
+  // The ordered keys leave: to `at` on; returns how many (levels: the distinct ones).
+  __device__ static int store(Lds& L, const MergeArgs<KeyT, DEDUP>& a, KeyT* out_k, int count, int at) {
+    const int t = threadIdx.x;
+    if constexpr (!DEDUP) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      SPC_PIN_LOADED(key[u]);
-      if (DEDUP) SPC_PIN_LOADED(prev[u]);
-      const int64_t i = min<int64_t>(i0 + u * BS_WIDE, hi - 1);
-      use[u] = i0 + u * BS_WIDE < hi && !(DEDUP && i > 0 && prev[u] == key[u]);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) p[u] = use[u] ? atomicAdd(&pos[bs_bin(key[u], shift, n_bin)], 1) : 0;
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (use[u]) {
-        if constexpr (REC) {
-          keys1[p[u]] = (uint64_t(key[u]) << 32) | static_cast<uint32_t>(i0 + u * BS_WIDE);
-        } else {
-          keys1[p[u]] = key[u];
-          if (!DEDUP) vals1[p[u]] = static_cast<int32_t>(i0 + u * BS_WIDE);
+      for (int u = 0; u < KPT; ++u) {
+        const int i = u * BS_MT + t;
+        if (i < count) {
+          const Elem e = L.key[i];
+          out_k[at + i] = F::key(e);
+          if (a.out_v) a.out_v[at + i] = F::ROWS ? L.row[i] : static_cast<int32_t>(e);
         }
       }
-  }
-  // Rank windows (see bs_rank_kernel): part p = scattered positions [p * BS_PART, ...) is ranked
-  // inside the range of whole bins that covers it.  Parts are dealt round-robin to the workgroups,
-  // one per thread: two binary searches over the bin starts in LDS, done last, while the scattered
-  // stores drain.
-  if (blockIdx.x == 0) {
-    if (t < BS_PAD_KEYS) keys1[total + t] = ~BsElem<KeyT, REC>(0);  // the rank kernels read whole steps
-    if (t == 0 && n_part_keys) *n_part_keys = total;
-    if (t == 0) *rest_count = 0;  // windows left over by bs_rank_lds_kernel
-  }
-  const int part = blockIdx.x + t * gridDim.x;
-  if (int64_t(part) * BS_PART < total) {
-    const int x0 = part * BS_PART, x1 = min(x0 + BS_PART, total) - 1;
-    // last bin whose start is <= x: the (non-empty) bin that holds position x; both searches in step
-    int fa = 0, fb = 0;
-    for (int step = n_bin >> 1; step > 0; step >>= 1) {
-      const int sa = bin_start[fa + step], sb = bin_start[fb + step];
-      if (sa <= x0) fa += step;
-      if (sb <= x1) fb += step;
+      return count;
+    } else {
+      const int lane = t & 63, wave = t >> 6;
+      unsigned long long head[KPT];
+#pragma unroll
+      for (int u = 0; u < KPT; ++u) {
+        const int i = u * BS_MT + t;
+        head[u] = __ballot(i < count && (i == 0 || L.key[i] != L.key[max(i, 1) - 1]));
+        if (lane == 0) L.seg[u * WAVES + wave] = __popcll(head[u]);
+      }
+      static_assert(KPT * WAVES <= 64, "a wave sums the segments");
+      __syncthreads();
+      const int c = lane < KPT * WAVES ? L.seg[lane] : 0, x = wave_scan(c);
+      const int distinct = __builtin_amdgcn_readlane(x, 63);
+#pragma unroll
+      for (int u = 0; u < KPT; ++u) {
+        const int before = __shfl(x - c, u * WAVES + wave, 64);
+        if ((head[u] >> lane) & 1ull) out_k[at + before + __popcll(head[u] & ((1ull << lane) - 1ull))] = L.key[u * BS_MT + t];
+      }
+      return distinct;
     }
-    win[part] = make_int2(bin_start[fa], bin_start[fb + 1]);
-  }
-}
-
-// ---------------------------------------------------------------- rank (pack + sort path)
-// After the scatter the keys are ordered by bin, unordered inside a bin.  Workgroup p takes the
-// BS_PART = 64 keys at scattered positions [p * BS_PART, ...), one per lane, each of its four waves
-// a quarter of the comparisons, and ranks each of them inside the window of whole bins that covers those positions (widened to multiples of 32
-// positions): every key before the window is smaller and every key behind it larger, so
-// window start + (number of window keys that sort before mine) is the key's final position.
-// "Sorts before" is (key, scattered position) order, which makes the positions of equal keys
-// distinct without any atomics; below and above the workgroup's own 64 positions that is a plain
-// <= resp. < on the key.  Every lane of a wave compares its key with the same window key at the same
-// time, so the window is read with scalar loads (128 bytes per step, the next step's load in
-// flight while the current one is compared) and a comparison is two vector instructions with a
-// scalar operand; LDS only carries the four partial counts of a key to the wave that stores.  (Reading the window back from LDS at a wave-uniform address
-// was measured four times slower: 16-byte LDS reads of one address by all lanes are not broadcast.)
-// Work per key grows with the window, i.e. with the size of the bins involved, but a big bin is
-// shared by as many workgroups as it has parts: no workgroup sorts a dense region of the scene
-// alone, which is what bounded the compare-exchange network this replaces on the pack + sort path.
-// The scatter leaves BS_RANK_STEP all-ones keys behind the last key, so that whole steps can be
-// read at the end of the array.
-#ifndef BS_RANK_SOLO_N
-#define BS_RANK_SOLO_N 400000
-#endif
-#ifndef BS_RANK_LDS_N
-#define BS_RANK_LDS_N 600000  // keys from which the ranking splits its windows once more in LDS (bs_rank_lds_kernel)
-#endif
-constexpr int BS_RANK_STEP = BS_PAD_KEYS;  // positions; a window is a whole number of steps
-// 128 bytes of keys at a wave-uniform address in scalar registers.  The load is issued by hand and
-// its arrival awaited by hand, one compare step later: left to the compiler, the load of a step
-// ends up right in front of its first use and every step pays the scalar-memory latency.
-typedef uint32_t bs_u32x16 __attribute__((ext_vector_type(16)));
-struct BsChunk {
-  bs_u32x16 lo, hi;
-  // SCALAR: the caller's address is in scalar registers already (derived from blockIdx and kernel arguments);
-  // otherwise it is the same in every lane but arrives in vector registers (a part number read from a list)
-  template <bool SCALAR>
-  __device__ void issue(const void* p) {
-    const void* q = p;
-    if constexpr (!SCALAR) {
-      const uint64_t a = reinterpret_cast<uint64_t>(p);
-      const uint32_t a_lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a));
-      const uint32_t a_hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a >> 32));
-      q = reinterpret_cast<const void*>((static_cast<uint64_t>(a_hi) << 32) | a_lo);
-    }
-    asm volatile("s_load_dwordx16 %0, %2, 0x0\n\ts_load_dwordx16 %1, %2, 0x40" : "=&s"(lo), "=&s"(hi) : "s"(q) : "memory");
-  }
-  // the counters are operands only to keep the compare step that runs under the load in front of the wait
-  __device__ void arrive(int (&c)[4]) {
-    asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(lo), "+s"(hi), "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]));
-  }
-  template <typename KeyT>
-  __device__ KeyT key(int q) const {  // q-th key of the chunk, q a compile-time constant after unrolling
-    if constexpr (sizeof(KeyT) == 4) return q < 16 ? lo[q] : hi[q - 16];
-    else return q < 8 ? (uint64_t(lo[2 * q + 1]) << 32) | lo[2 * q] : (uint64_t(hi[2 * q - 15]) << 32) | hi[2 * q - 16];
   }
 };
 
-// keys k[a, b) that sort before (key, x): MODE 0 for positions below the workgroup's own 64 (equal
-// keys count), 2 for positions above (they do not), 1 for the own positions (full comparison).
-// a and b are multiples of BS_RANK_STEP.
-template <int MODE, bool SCALAR = true, typename KeyT>
-__device__ inline int bs_count_before(const KeyT* __restrict__ k, int a, int b, KeyT key, int x) {
-  constexpr int C = 128 / sizeof(KeyT);  // keys per chunk
-  static_assert(BS_RANK_STEP % C == 0, "a step of positions is a whole number of chunks");
-  int c[4] = {0, 0, 0, 0};
-  if (a >= b) return 0;
-  auto compare = [&](const BsChunk& ch, int j) {
+template <typename KeyT, bool DEDUP, int KPT, int FROM>
+__global__ __launch_bounds__(BS_MT) void bs_merge_kernel(const MergeArgs<KeyT, DEDUP> a) {
+  using O = BsOrder<KeyT, DEDUP, KPT>;
+  using F = typename O::F;
+  using Elem = typename F::Elem;
+  __shared__ typename O::Lds L;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, p = blockIdx.x;
+  const auto* recs = DEDUP ? level_ws(a.recs, a.ws_pitch) : a.recs;
+  const uint16_t* off = DEDUP ? level_ws(a.off, a.ws_pitch) : a.off;
+  KeyT* out_k = DEDUP ? level_ws(a.out_k, a.ws_pitch) : a.out_k;
+  const int pitch = bs_off_pitch(a.n_bin), lo = p * a.q, hi = lo + a.q;
+  int first, start, last, end;  // as in BsShare
+  int32_t* tot = nullptr;
+  int came = 0;
+  if constexpr (FROM == BS_STARTS) {
+    const BsShare* share = DEDUP ? level_ws(a.share, a.ws_pitch) : a.share;
+    const int total = *(DEDUP ? level_ws(a.n_kept, a.ws_pitch) : a.n_kept);
+    const BsShare s = share[p];
+    first = s.first, start = s.start, last = s.last, end = s.end;
+    if (lo >= total || start >= min(hi, total)) start = end = 0;
+    O::clear(L);
+  } else {
+    if constexpr (FROM == BS_TOTALS) tot = DEDUP ? level_ws(a.tot, a.tot_pitch) : a.tot;
+    // four bins per thread and round, of which there are two at most
+    auto fetch = [&](int f0) {
+      int4 c = make_int4(0, 0, 0, 0);
+      if (f0 < a.n_bin) {
+        if constexpr (FROM == BS_TOTALS) {
+          c = *reinterpret_cast<const int4*>(tot + f0);
+        } else {
+          for (int w = 0; w < a.n_wg; ++w) {
+            const uint16_t* row = off + int64_t(w) * pitch + f0;
+            const int s0 = row[0], s1 = row[1], s2 = row[2], s3 = row[3];
+            c.x += s1 - s0, c.y += s2 - s1, c.z += s3 - s2, c.w += row[4] - s3;
+          }
+        }
+      }
+      return c;
+    };
+    int4 c = fetch(4 * t), later = fetch(4 * (BS_MT + t));
+    O::clear(L);
+    if (t == 0) L.first = 0, L.start = 0, L.end = -1;
+    int total = 0;
+#pragma unroll 1
+    for (int r0 = 0; r0 < a.n_bin; r0 += 4 * BS_MT) {
+      const int f0 = r0 + 4 * t;
+      if (r0 > 0) __syncthreads();  // (the sums of the round before have been read)
+      const int sum = c.x + c.y + c.z + c.w;
+      int here;
+      int s = total + block_scan<O::WAVES>(sum, L.sums, &here);
+      total += here;
+      if ((s < lo && lo <= s + sum) || (s < hi && hi <= s + sum)) {
+        const int n4[4] = {c.x, c.y, c.z, c.w};
 #pragma unroll
-    for (int q = 0; q < C; ++q) {
-      const KeyT e = ch.template key<KeyT>(q);
-      bool before;
-      if (MODE == 0) before = e <= key;
-      else if (MODE == 2) before = e < key;
-      else before = e < key || (e == key && j + q < x);
-      c[q & 3] += before ? 1 : 0;
+        for (int j = 0; j < 4; ++j) {
+          const int e = s + n4[j];
+          if (s < lo && lo <= e) L.first = f0 + j + 1, L.start = e;
+          if (s < hi && hi <= e) L.last = f0 + j, L.end = e;
+          s = e;
+        }
+      }
+      const unsigned long long some = __ballot(sum != 0);
+      const int mine = f0 + (c.w ? 3 : c.z ? 2 : c.y ? 1 : 0);
+      const int top = __builtin_amdgcn_readlane(mine, some ? 63 - __builtin_clzll(some) : 0);
+      if (lane == 0 && (some || r0 == 0)) L.wave_last[wave] = some ? top : 0;
+      c = later;
     }
-  };
-  BsChunk A, B;
-  A.template issue<SCALAR>(k + a);
-  A.arrive(c);
-  for (int j = a; j < b; j += 2 * C) {  // the last chunk is fetched once more instead of running past b
-    B.template issue<SCALAR>(k + min(j + C, b - C));
-    compare(A, j);
-    B.arrive(c);
-    if (j + C < b) {
-      A.template issue<SCALAR>(k + min(j + 2 * C, b - C));
-      compare(B, j + C);
-      A.arrive(c);
-    }
-  }
-  return (c[0] + c[1]) + (c[2] + c[3]);
-}
-
-// (a device function of the part number: the kernel below ranks part blockIdx.x, bs_rank_rest_kernel the parts
-// of the windows that bs_rank_lds_kernel has left over)
-template <typename KeyT, int WAVES, bool LISTED = false, bool REC = false>
-__device__ inline void bs_rank_part(int part, const BsElem<KeyT, REC>* __restrict__ keys1, const int32_t* __restrict__ vals1,
-                                    const int2* __restrict__ win, int n, KeyT* __restrict__ out_k, int32_t* __restrict__ out_v) {
-  static_assert(BS_PART == 64, "one key per lane");
-  __shared__ int partial[WAVES][BS_PART];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
-  const int own0 = part * BS_PART;
-  const int x = own0 + lane;
-  const bool act = x < n;
-  const int2 w = win[part];
-  const BsElem<KeyT, REC> key = act ? keys1[x] : ~BsElem<KeyT, REC>(0);
-  const int32_t val = REC ? static_cast<int32_t>(key) : (act && out_v && wave == 0) ? vals1[x] : 0;
-  const int n_pad = (n + BS_RANK_STEP - 1) & ~(BS_RANK_STEP - 1);  // positions n .. n_pad - 1 hold all-ones keys
-  const int g0 = w.x & ~(BS_RANK_STEP - 1);
-  const int g1 = min(max((w.y + BS_RANK_STEP - 1) & ~(BS_RANK_STEP - 1), own0 + BS_PART), n_pad);
-  // the window is cut into the part below the own positions, the own positions and the part above;
-  // each is shared out among the waves in contiguous quarters (rounded to whole steps)
-  const int own1 = min(own0 + BS_PART, g1);
-  auto quarter = [&](int a, int b, int& qa, int& qb) {
-    const int steps = (b - a) / BS_RANK_STEP, per = (steps + WAVES - 1) / WAVES;
-    qa = min(a + wave * per * BS_RANK_STEP, b);
-    qb = min(qa + per * BS_RANK_STEP, b);
-  };
-  int qa, qb;
-  quarter(g0, own0, qa, qb);
-  int c = bs_count_before<0, !LISTED>(keys1, qa, qb, key, x);
-  quarter(own0, own1, qa, qb);
-  c += bs_count_before<1, !LISTED>(keys1, qa, qb, key, x);
-  quarter(own1, g1, qa, qb);
-  c += bs_count_before<2, !LISTED>(keys1, qa, qb, key, x);
-  int r = g0 + c;
-  if constexpr (WAVES > 1) {
-    partial[wave][lane] = c;
     __syncthreads();
-    r = g0;
-#pragma unroll
-    for (int v = 0; v < WAVES; ++v) r += partial[v][lane];
+    first = L.first, start = L.start, last = L.last, end = L.end;
+    if (end < 0) {  // the last bins (uniform)
+      last = 0, end = total;
+      for (int w = 0; w < O::WAVES; ++w) last = max(last, L.wave_last[w]);
+    }
+    if (lo >= total || start >= min(hi, total)) start = end = 0;
+    // (the totals have been read)
+    if (!DEDUP && a.clear && t == 0)
+      came = __hip_atomic_fetch_add(a.arrived + (p % BS_ARRIVE) * BS_ARRIVE_PITCH, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (wave == 0 && act) {
-    out_k[r] = static_cast<KeyT>(REC ? key >> (8 * (sizeof(key) - sizeof(KeyT))) : key);
-    if (out_v) out_v[r] = val;
-  }
-}
-
-template <typename KeyT, int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void bs_rank_kernel(const KeyT* __restrict__ keys1, const int32_t* __restrict__ vals1,
-                                                             const int2* __restrict__ win, int n, KeyT* __restrict__ out_k,
-                                                             int32_t* __restrict__ out_v, int32_t* __restrict__ tot, int n_bin) {
-  bs_clear_after<64 * WAVES>(tot, n_bin);
-  bs_rank_part<KeyT, WAVES>(blockIdx.x, keys1, vals1, win, n, out_k, out_v);
-}
-
-// ---------------------------------------------------------------- rank + compact (downsampling path)
-// The distinct masked keys in ascending order.  Ranking as above, on the key alone: equal keys get
-// equal positions, so position = window start + (number of window keys smaller than mine) leaves the
-// sorted sequence with gaps where a key occurs more than once (the count pass has dropped equal
-// neighbours, but the children of one coarse voxel sit in up to four separate runs of the finer
-// level).  A position is marked in a bitmap by whoever gets there first, and counted once in its
-// chunk of BS_CHUNK positions; bs_compact_kernel then closes the gaps.
-constexpr int BS_CHUNK = 1024;
-template <typename KeyT, bool LISTED = false>
-__device__ inline void bs_rank_unique_part(int part, const KeyT* __restrict__ keys1, const int2* __restrict__ win, int n,
-                                           KeyT* __restrict__ sorted, uint32_t* __restrict__ bits, int32_t* __restrict__ ccnt) {
-  constexpr int WAVES = BS_THREADS / 64;
-  __shared__ int partial[WAVES][BS_PART];
-  __shared__ uint32_t lbits[64];
-  const int own0 = part * BS_PART;
-  if (own0 >= n) return;  // (the whole workgroup)
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
-  const int x = own0 + lane;
-  const bool act = x < n;
-  const int2 w = win[part];
-  const KeyT key = act ? keys1[x] : ~KeyT(0);
-  const int n_pad = (n + BS_RANK_STEP - 1) & ~(BS_RANK_STEP - 1);  // positions n .. n_pad - 1 hold all-ones keys
-  const int g0 = w.x & ~(BS_RANK_STEP - 1);
-  const int g1 = min((w.y + BS_RANK_STEP - 1) & ~(BS_RANK_STEP - 1), n_pad);
-  const int steps = (g1 - g0) / BS_RANK_STEP, per = (steps + WAVES - 1) / WAVES;
-  const int qa = min(g0 + wave * per * BS_RANK_STEP, g1), qb = min(qa + per * BS_RANK_STEP, g1);
-  partial[wave][lane] = bs_count_before<2, !LISTED>(keys1, qa, qb, key, x);
-  __syncthreads();
-  if (wave == 0) {
-    int r = g0;
+  const int W = end - start;
+  int kept = 0;
+  if (W > 0) {
+    // ---- the pieces of the regions, one per thread
+    int from = 0, len = 0;
+    if (t < a.n_wg) {
+      const uint16_t* row = off + int64_t(t) * pitch;
+      from = row[first];
+      len = row[last + 1] - from;
+    }
+    int all;
+    const int pre = block_scan<O::WAVES>(len, L.sums, &all);
+    if (t < a.n_wg) {
+      L.pre[t] = pre;
+      L.src[t] = t * a.per + from - pre;
+    }
+    __syncthreads();
+    int top = 1;
+    while (2 * top < a.n_wg) top *= 2;
+    auto place = [&](int i) {  // of element i in the regions: of the last piece that starts at or before it
+      int w = 0;
+      for (int s = top; s > 0; s >>= 1)
+        if (w + s < a.n_wg && L.pre[w + s] <= i) w += s;
+      return L.src[w] + i;
+    };
+    // (the all-ones keys of rejected rows, in the last bin, count as the first key behind it where there is one)
+    const bool over = last == a.n_bin - 1 && a.used_bits < int(8 * sizeof(KeyT));
+    const KeyT base = KeyT(first) << a.shift, lim = over ? KeyT(last + 1) << a.shift : ~KeyT(0);
+    const unsigned bins = last + 1 - first + (over ? 1 : 0);
+    const int ss = max(0, a.shift + (bins > 1 ? 32 - __clz(bins - 1) : 0) - 12);
+    Elem k[KPT];
+    int32_t v[KPT];
+    if (__builtin_expect(W <= O::CAP, 1)) {
 #pragma unroll
-    for (int v = 0; v < WAVES; ++v) r += partial[v][lane];
-    if (act) sorted[r] = key;  // equal keys write the same value
-    // The 64 positions lie in the window, typically within a few hundred positions of its start:
-    // their bits are collected in LDS first (64 words from the window start on), so that the global
-    // bitmap sees one atomic per word instead of one per key; what a word's atomic finds newly set
-    // is counted for the word's chunk (a chunk is 32 words), one counter update per chunk.
-    lbits[lane] = 0u;
-    __builtin_amdgcn_wave_barrier();
-    const int rel = r - g0;
-    const bool far = act && rel >= 64 * 32;
-    if (act && !far) atomicOr(&lbits[rel >> 5], 1u << (rel & 31));
-    __builtin_amdgcn_wave_barrier();
-    // lane i then owns word i of the 64; a position beyond them (a very large window) goes to the
-    // global bitmap on its own, in a second round
+      for (int u = 0; u < KPT; ++u)
+        if (u * BS_MT + t < W) {
+          const int at = place(u * BS_MT + t);
+          k[u] = recs[at];
+          if constexpr (F::ROWS) v[u] = a.rows[at];
+        }
+      O::order(L, k, v, W, base, lim, ss);
+      kept = O::store(L, a, out_k, W, start);
+    } else {
+      // More keys than the LDS holds (of one bin: scenes that fill next to nothing of their key space).  They are read again and
+      // again: counted into second bins, then as many of these as fit are picked out and ordered as above.  A second bin that does
+      // not fit is split again; where nothing is left to split its keys are equal.
+      KeyT low = base;
+      int sh = ss, out = 0;
+      while (out < W) {
+        __syncthreads();
+        O::clear(L);
+        __syncthreads();
+        auto second = [&](Elem e) {  // second bin, or -1
+          const KeyT key = min(F::key(e), lim);
+          if (key < low) return -1;
+          const KeyT d = (key - low) >> sh;
+          return d < KeyT(BS_NSUB) ? static_cast<int>(d) : -1;
+        };
+        for (int i = t; i < W; i += BS_MT) {
+          const int b = second(recs[place(i)]);
+          if (b >= 0) atomicAdd(&L.hist[b], 1);
+        }
+        __syncthreads();
+        O::scan(L);
+        if (t == 0) L.taken = 0;
+        __syncthreads();
+        int fit = 0;  // second bins that fit together: hist ascends
+        for (int s = BS_NSUB; s > 0; s >>= 1)
+          if (fit + s <= BS_NSUB && L.hist[fit + s] <= O::CAP) fit += s;
+        const int count = L.hist[fit];
+        if (fit > 0) {
+          for (int i = t; i < W; i += BS_MT) {
+            const int at = place(i);
+            const Elem e = recs[at];
+            const int b = second(e);
+            if (b >= 0 && b < fit) {
+              const int to = atomicAdd(&L.taken, 1);
+              L.key[to] = e;
+              if constexpr (F::ROWS) L.row[to] = a.rows[at];
+            }
+          }
+          __syncthreads();
 #pragma unroll
-    for (int round = 0; round < 2; ++round) {
-      const int word_i = round == 0 ? (g0 >> 5) + lane : r >> 5;
-      const uint32_t word = round == 0 ? lbits[lane] : (far ? 1u << (r & 31) : 0u);
-      if (round == 1 && !__ballot(far)) break;  // uniform
-      int fresh = 0;
-      if (word) fresh = __popc(word & ~atomicOr(&bits[word_i], word));
-      const int chunk = word_i / (BS_CHUNK / 32);
-      unsigned long long todo = __ballot(fresh > 0);
-      while (todo) {
-        const int leader = __builtin_ctzll(todo);
-        const int c = __shfl(chunk, leader, 64);
-        const bool mine = fresh > 0 && chunk == c;
-        int sum = mine ? fresh : 0;
-        for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d, 64);
-        if (lane == leader) atomicAdd(&ccnt[c], sum);
-        todo &= ~__ballot(mine);
+          for (int u = 0; u < KPT; ++u)
+            if (u * BS_MT + t < count) {
+              k[u] = L.key[u * BS_MT + t];
+              if constexpr (F::ROWS) v[u] = L.row[u * BS_MT + t];
+            }
+          O::clear(L);
+          __syncthreads();
+          if (count > 0) {
+            O::order(L, k, v, count, low, lim, sh);
+            kept += O::store(L, a, out_k, count, start + (DEDUP ? kept : out));
+          }
+          out += count;
+          low += KeyT(fit) << sh;
+          sh = ss;
+        } else if (sh > 0) {
+          sh = max(0, sh - 12);
+        } else {
+          const int many = L.hist[1];
+          for (int i = t; i < W; i += BS_MT) {
+            const int at = place(i);
+            const Elem e = recs[at];
+            if (second(e) != 0) continue;
+            if constexpr (DEDUP) {
+              if (atomicAdd(&L.taken, 1) == 0) out_k[start + kept] = F::key(e);
+            } else {
+              const int to = start + out + atomicAdd(&L.taken, 1);
+              out_k[to] = F::key(e);
+              if (a.out_v) a.out_v[to] = F::ROWS ? a.rows[at] : static_cast<int32_t>(e);
+            }
+          }
+          kept += DEDUP ? 1 : many;
+          out += many;
+          low += 1;
+          sh = ss;
+        }
       }
     }
   }
-}
-
-template <typename KeyT>
-__global__ __launch_bounds__(BS_THREADS) void bs_rank_unique_kernel(const KeyT* __restrict__ keys1, const int2* __restrict__ win,
-                                                                    const int32_t* __restrict__ n_kept,
-                                                                    KeyT* __restrict__ sorted, uint32_t* __restrict__ bits,
-                                                                    int32_t* __restrict__ ccnt, size_t ws_pitch) {
-  // (the grid is sized for the level before the equal neighbours were dropped)
-  bs_rank_unique_part<KeyT>(blockIdx.x, level_ws(keys1, ws_pitch), level_ws(win, ws_pitch), *level_ws(n_kept, ws_pitch),
-                            level_ws(sorted, ws_pitch), level_ws(bits, ws_pitch), level_ws(ccnt, ws_pitch));
+  if constexpr (DEDUP) {
+    if (t == 0) {
+      level_ws(a.out_at, a.ws_pitch)[p] = start;
+      level_ws(a.out_n, a.ws_pitch)[p] = kept;
+    }
+  }
+  if constexpr (FROM == BS_TOTALS && !DEDUP) {
+    // Whoever comes last clears the totals for the next sort.  Workgroups are counted in two steps: additions to one place take
+    // some 40 ns each (235 workgroups: 9 us).
+    if (a.clear) {
+      if (t == 0) {
+        const int g = p % BS_ARRIVE, n_share = gridDim.x, groups = min(n_share, BS_ARRIVE);
+        L.done = came == (n_share - g + BS_ARRIVE - 1) / BS_ARRIVE - 1 &&
+                 __hip_atomic_fetch_add(a.arrived + BS_ARRIVE * BS_ARRIVE_PITCH, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == groups - 1;
+      }
+      __syncthreads();
+      if (L.done)
+        for (int b = t; b < a.n_bin; b += BS_MT) tot[b] = 0;
+    }
+  }
 }
 
 // Where the levels of a batch go.
@@ -582,320 +745,25 @@ struct LevelOut {
   int32_t* count[BS_MAX_LEVELS];
 };
 
-// out = the marked positions of `sorted`, in order, and their number.  One workgroup per chunk
-// of BS_CHUNK positions: the keys before the chunk are the sum of the earlier chunks' counters.
+// The merging workgroups' distinct keys, one behind the other, and their number.
 template <typename KeyT>
-__global__ __launch_bounds__(BS_THREADS) void bs_compact_kernel(const KeyT* __restrict__ sorted, const uint32_t* __restrict__ bits,
-                                                                const int32_t* __restrict__ ccnt,
-                                                                const int32_t* __restrict__ n_kept, const LevelOut<KeyT> lo,
-                                                                size_t ws_pitch, int32_t* __restrict__ tot, size_t tot_pitch, int n_bin) {
-  if (tot) bs_clear_after<BS_THREADS>(level_ws(tot, tot_pitch), n_bin);
-  sorted = level_ws(sorted, ws_pitch);
-  bits = level_ws(bits, ws_pitch);
-  ccnt = level_ws(ccnt, ws_pitch);
-  n_kept = level_ws(n_kept, ws_pitch);
-  KeyT* __restrict__ out = lo.keys[blockIdx.y];
-  static_assert(BS_CHUNK == 4 * BS_THREADS, "four positions per thread");
-  __shared__ int red[2][BS_THREADS / 64];
-  __shared__ int wsum[BS_CHUNK / 32];
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int n = *n_kept, n_chunks = (n + BS_CHUNK - 1) / BS_CHUNK, b = blockIdx.x;
-  int before = 0, all = 0;
-  for (int i = t; i < n_chunks; i += BS_THREADS) {
-    const int c = ccnt[i];
-    all += c;
-    before += i < b ? c : 0;
-  }
-  for (int d = 32; d > 0; d >>= 1) {
-    before += __shfl_xor(before, d, 64);
-    all += __shfl_xor(all, d, 64);
-  }
-  if (lane == 0) {
-    red[0][wave] = before;
-    red[1][wave] = all;
-  }
-  const int wi = t >> 3, sub = t & 7;  // eight threads per bitmap word, four positions each
-  const uint32_t word = b < n_chunks ? bits[b * (BS_CHUNK / 32) + wi] : 0u;
-  if (sub == 0) wsum[wi] = __popc(word);
-  __syncthreads();
-  before = 0;
-  all = 0;
-  for (int w = 0; w < BS_THREADS / 64; ++w) {
-    before += red[0][w];
-    all += red[1][w];
-  }
-  if (b == 0 && t == 0) *lo.count[blockIdx.y] = all;
-  int rank = before + __popc(word & ((1u << (4 * sub)) - 1u));
-  for (int w = 0; w < wi; ++w) rank += wsum[w];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int bit = 4 * sub + j;
-    if ((word >> bit) & 1u) out[rank++] = sorted[b * BS_CHUNK + wi * 32 + bit];
-  }
-}
-
-// ---------------------------------------------------------------- rank in LDS (large inputs)
-// The ranking above compares every key with its whole window, which is quadratic in the bin size, and the bin
-// count is capped (an LDS histogram per workgroup in the count pass): from about half a million keys on that pass
-// sets the time of the sort.  Here a workgroup takes BS_LP scattered positions and the window of whole bins around
-// them (through the 64-position windows the scatter pass has written), and splits the window once more in LDS:
-//   * a key's bin rank inside the window is a prefix sum of "the bin changes here" flags (the scattered array is
-//     ordered by bin), so the empty bins of a sparse key space cost nothing; a thread's eight keys lie BS_LT apart,
-//     so loads are coalesced and a ballot gives a wave's flags;
-//   * sub-bin = (bin rank, the next sb key bits below the bin bits), sb chosen per window so that all sub-bins fit
-//     the LDS histogram; histogram, exclusive scan, and the keys move, with their window index, to their sub-bin's
-//     slots (LDS atomics for the slot: the order inside a sub-bin does not matter);
-//   * a key's final position is window start + start of its sub-bin + the number of keys of the sub-bin that sort
-//     before it, in (key, window index) order for pack + sort and on the key alone for downsampling (equal keys
-//     then share a position; the one with the smallest window index marks the position and is counted for its chunk,
-//     which is the same on every workgroup that sees the bin, because all of a bin's keys lie in every window that
-//     touches it).
-// Pack + sort ranks whole bins, those that start among the workgroup's positions, so its keys fill a range of the
-// output and leave in order, lane next to lane; what bounded the pass before was the rate of single-lane stores.  With
-// that and the 8-byte records of the scatter pass, pack + sort of 10^6 random voxels 70 -> 50 us, 3 * 10^6 142 -> 89,
-// 1.2 * 10^6 indoor 130 -> 69 (own positions 3072 instead of 2048: 95); with 64-bit keys, which have no records, 3 * 10^6 151 -> 144.
-// Levels keep the window of all bins that touch the own positions: their marks must be counted once each.
-// A window that does not fit (bins of thousands of keys: the floors and walls of dense indoor scenes) is left to
-// bs_rank_rest_kernel: the workgroup appends its number to a list, and the 64-position parts of the listed
-// workgroups are ranked by comparing against their own windows as above, spread over a fixed grid.
-constexpr int BS_LP = 2048;    // own positions per workgroup (a multiple of BS_PART)
-constexpr int BS_LW = 4096;    // window keys a workgroup holds
-constexpr int BS_LSUB = 4096;  // sub-bins
-constexpr int BS_LT = 512;     // threads: eight window keys each
-constexpr int BS_LK = BS_LW / BS_LT;
-static_assert(BS_LP % BS_PART == 0 && BS_LW >= BS_LP && BS_LK == 8, "window layout");
-
-template <typename KeyT, bool UNIQUE, bool REC>
-__global__ __launch_bounds__(BS_LT) void bs_rank_lds_kernel(const BsElem<KeyT, REC>* __restrict__ keys1,
-                                                            const int32_t* __restrict__ vals1, const int2* __restrict__ win, int n_h,
-                                                            const int32_t* __restrict__ n_d, int shift, int n_bin,
-                                                            KeyT* __restrict__ out_k, int32_t* __restrict__ out_v,
-                                                            uint32_t* __restrict__ bits, int32_t* __restrict__ ccnt,
-                                                            int32_t* __restrict__ rest_count, int32_t* __restrict__ rest,
-                                                            size_t ws_pitch) {
-  using Elem = BsElem<KeyT, REC>;
-  constexpr int WAVES = BS_LT / 64;
-  static_assert(WAVES * BS_LK == 64, "one wave scans the totals of all (key of the thread, wave) segments");
-  if (UNIQUE) {
-    keys1 = level_ws(keys1, ws_pitch);
-    win = level_ws(win, ws_pitch);
-    n_d = level_ws(n_d, ws_pitch);
-    out_k = level_ws(out_k, ws_pitch);
-    bits = level_ws(bits, ws_pitch);
-    ccnt = level_ws(ccnt, ws_pitch);
-    rest_count = level_ws(rest_count, ws_pitch);
-    rest = level_ws(rest, ws_pitch);
-  }
-  __shared__ Elem skey[BS_LW];
-  __shared__ uint16_t sidx[REC ? 1 : BS_LW];  // (records are distinct and carry their source index)
-  __shared__ int hist[BS_LSUB];
-  __shared__ Elem s_last[64];
-  __shared__ int s_seg[64];
-  __shared__ int wave_tot[WAVES];
-  __shared__ uint32_t s_bits[UNIQUE ? BS_LW / 32 + 2 : 1];
-  __shared__ int s_cc[UNIQUE ? BS_LW / BS_CHUNK + 2 : 1];
-  const int n = n_d ? *n_d : n_h;
-  const int own0 = blockIdx.x * BS_LP;
-  if (own0 >= n) return;
-  const int own1 = min(own0 + BS_LP, n);
-  const int t = threadIdx.x, lane = t & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int part0 = own0 / BS_PART;
-  int g0 = win[part0].x;
-  const int g1 = win[(own1 - 1) / BS_PART].y;
-  bool listed;
-  if constexpr (UNIQUE) {
-    listed = g1 - g0 > BS_LW;
-  } else {
-    // the bins that start among the own positions; the rest of a bin that starts before them belongs to an earlier
-    // workgroup, and if that one's window does not fit, the own positions are listed as well
-    const int s = g0;
-    if (own0 > 0) g0 = win[part0 - 1].y;
-    listed = g1 - g0 > BS_LW;
-    if (s < own0) {
-      const int e = s / BS_LP;
-      listed |= g0 - (e > 0 ? win[e * (BS_LP / BS_PART) - 1].y : 0) > BS_LW;
-    }
-  }
-  const int W = g1 - g0;
-  if (listed && t == 0) rest[atomicAdd(rest_count, 1)] = blockIdx.x;  // bs_rank_rest_kernel ranks these positions
-  if (W <= 0 || W > BS_LW) return;
-  // ---- window keys: key u of a thread is window key u * BS_LT + t
-  Elem k[BS_LK];
-#pragma unroll
-  for (int u = 0; u < BS_LK; ++u) k[u] = keys1[g0 + min(u * BS_LT + t, W - 1)];
-  for (int i = t; i < BS_LSUB; i += BS_LT) hist[i] = 0;
-  if constexpr (UNIQUE) {
-    for (int i = t; i < BS_LW / 32 + 2; i += BS_LT) s_bits[i] = 0u;
-    if (t < BS_LW / BS_CHUNK + 2) s_cc[t] = 0;
-  }
-  if (lane == 63) {
-#pragma unroll
-    for (int u = 0; u < BS_LK; ++u) s_last[u * WAVES + wave] = k[u];
-  }
-  __syncthreads();
-  // bin rank inside the window: inclusive prefix of the "bin changes" flags, minus one
-  int d[BS_LK];
-#pragma unroll
-  for (int u = 0; u < BS_LK; ++u) {
-    const int seg = u * WAVES + wave;
-    const int bin = bs_bin(k[u], shift, n_bin);
-    int prev_bin = __shfl_up(bin, 1, 64);
-    if (lane == 0) prev_bin = seg > 0 ? bs_bin(s_last[seg - 1], shift, n_bin) : -1;
-    const unsigned long long flags = __ballot(u * BS_LT + t < W && bin != prev_bin);
-    d[u] = __popcll(flags & (~0ull >> (63 - lane)));
-    if (lane == 0) s_seg[seg] = __popcll(flags);
-  }
-  __syncthreads();
-  const int seg_n = s_seg[lane];
-  int x = seg_n;
-  for (int s = 1; s < 64; s <<= 1) {
-    const int y = __shfl_up(x, s, 64);
-    if (lane >= s) x += y;
-  }
-  const int n_bins_here = __shfl(x, 63, 64);
-  x -= seg_n;
-  // sub-bin bits: as many as keep (bins in the window) << sb within the histogram, at most the key bits below the bins
-  int sb = 0;
-  while (sb < shift && sb < 12 && ((n_bins_here << (sb + 1)) <= BS_LSUB)) ++sb;
-  const Elem sub_mask = (Elem(1) << sb) - 1;
-  int id[BS_LK];
-#pragma unroll
-  for (int u = 0; u < BS_LK; ++u) {
-    const int base = __shfl(x, u * WAVES + wave, 64);
-    id[u] = ((base + d[u] - 1) << sb) | static_cast<int>((k[u] >> (shift - sb)) & sub_mask);
-    if (u * BS_LT + t < W) atomicAdd(&hist[id[u]], 1);
-  }
-  __syncthreads();
-  // exclusive scan of the sub-bin counts, eight per thread (BS_LSUB = 8 * BS_LT)
-  static_assert(BS_LSUB == BS_LK * BS_LT, "eight sub-bins per thread");
-  {
-    const int j0 = t * BS_LK;
-    int c[BS_LK], sum = 0;
-#pragma unroll
-    for (int u = 0; u < BS_LK; ++u) {
-      c[u] = hist[j0 + u];
-      sum += c[u];
-    }
-    int y = sum;
-    for (int s = 1; s < 64; s <<= 1) {
-      const int z = __shfl_up(y, s, 64);
-      if (lane >= s) y += z;
-    }
-    if (lane == 63) wave_tot[wave] = y;
-    __syncthreads();
-    int run = y - sum;
-    for (int w = 0; w < wave; ++w) run += wave_tot[w];
-#pragma unroll
-    for (int u = 0; u < BS_LK; ++u) {
-      hist[j0 + u] = run;  // becomes the sub-bin's cursor
-      run += c[u];
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int u = 0; u < BS_LK; ++u)
-    if (u * BS_LT + t < W) {
-      const int slot = atomicAdd(&hist[id[u]], 1);
-      skey[slot] = k[u];
-      if constexpr (!REC) sidx[slot] = static_cast<uint16_t>(u * BS_LT + t);
-    }
-  __syncthreads();
-  // after the moves hist[i] is the end of sub-bin i, i.e. the start of sub-bin i + 1
-  const int o0 = own0 - g0, o1 = own1 - g0;  // UNIQUE: the own positions, as window indices
-#pragma unroll
-  for (int u = 0; u < BS_LK; ++u) {
-    const int j = u * BS_LT + t;
-    if (UNIQUE ? j < o0 || j >= o1 : j >= W) continue;
-    const int lo = id[u] > 0 ? hist[id[u] - 1] : 0, hi = hist[id[u]];
-    int c = lo;
-    bool first = true;  // UNIQUE: no equal key at a smaller window index
-    for (int s = lo; s < hi; ++s) {
-      const Elem e = skey[s];
-      if constexpr (REC) {
-        c += e < k[u] ? 1 : 0;
-      } else if constexpr (UNIQUE) {
-        c += e < k[u] ? 1 : 0;
-        first = first && !(e == k[u] && sidx[s] < j);
-      } else {
-        c += (e < k[u] || (e == k[u] && sidx[s] < j)) ? 1 : 0;
-      }
-    }
-    if constexpr (!UNIQUE) {
-      d[u] = c;
-    } else {
-      const int r = g0 + c;
-      out_k[r] = k[u];
-      if (first) {
-        const int rel = r - (g0 & ~31);
-        atomicOr(&s_bits[rel >> 5], 1u << (rel & 31));
-      }
-    }
-  }
-  __syncthreads();
-  if constexpr (UNIQUE) {
-    const int word0 = g0 >> 5, chunk0 = word0 / (BS_CHUNK / 32);
-    if (t < BS_LW / 32 + 2) {
-      const uint32_t word = s_bits[t];
-      if (word) {  // the marks of different workgroups in one word are different bits
-        atomicOr(&bits[word0 + t], word);
-        atomicAdd(&s_cc[(word0 + t) / (BS_CHUNK / 32) - chunk0], __popc(word));
-      }
-    }
-    __syncthreads();
-    if (t < BS_LW / BS_CHUNK + 2 && s_cc[t]) atomicAdd(&ccnt[chunk0 + t], s_cc[t]);
-  } else {
-    // whole bins are ranked: their keys leave in order, lane next to lane
-#pragma unroll
-    for (int u = 0; u < BS_LK; ++u)
-      if (u * BS_LT + t < W) {
-        skey[d[u]] = k[u];
-        if constexpr (!REC) sidx[d[u]] = static_cast<uint16_t>(u * BS_LT + t);
-      }
-    __syncthreads();
-    for (int i = t; i < W; i += BS_LT) {
-      const Elem e = skey[i];
-      if constexpr (REC) {
-        out_k[g0 + i] = static_cast<KeyT>(e >> 32);
-        if (out_v) out_v[g0 + i] = static_cast<int32_t>(e);
-      } else {
-        out_k[g0 + i] = e;
-        if (out_v) out_v[g0 + i] = vals1[g0 + sidx[i]];
-      }
-    }
-  }
-}
-
-// The parts bs_rank_lds_kernel has listed (none for most clouds: the workgroups then read the count and leave).
-constexpr int BS_REST_WG = 2048;
-template <typename KeyT, bool UNIQUE, bool REC>
-__global__ __launch_bounds__(BS_THREADS) void bs_rank_rest_kernel(const int32_t* __restrict__ rest_count,
-                                                                  const int32_t* __restrict__ rest,
-                                                                  const BsElem<KeyT, REC>* __restrict__ keys1,
-                                                                  const int32_t* __restrict__ vals1, const int2* __restrict__ win, int n_h,
-                                                                  const int32_t* __restrict__ n_d, KeyT* __restrict__ out_k,
-                                                                  int32_t* __restrict__ out_v, uint32_t* __restrict__ bits,
-                                                                  int32_t* __restrict__ ccnt, size_t ws_pitch) {
-  if (UNIQUE) {
-    rest_count = level_ws(rest_count, ws_pitch);
-    rest = level_ws(rest, ws_pitch);
-    keys1 = level_ws(keys1, ws_pitch);
-    win = level_ws(win, ws_pitch);
-    n_d = level_ws(n_d, ws_pitch);
-    out_k = level_ws(out_k, ws_pitch);
-    bits = level_ws(bits, ws_pitch);
-    ccnt = level_ws(ccnt, ws_pitch);
-  }
-  constexpr int PER = BS_LP / BS_PART;  // 64-position parts per listed workgroup
-  const int n = n_d ? *n_d : n_h;
-  const int todo = *rest_count * PER;
-  for (int i = blockIdx.x; i < todo; i += gridDim.x) {
-    const int part = rest[i / PER] * PER + i % PER;
-    if (part * BS_PART >= n) continue;  // (uniform)
-    if constexpr (UNIQUE) bs_rank_unique_part<KeyT, true>(part, keys1, win, n, out_k, bits, ccnt);
-    else bs_rank_part<KeyT, BS_THREADS / 64, true, REC>(part, keys1, vals1, win, n, out_k, out_v);
-    __syncthreads();  // the part functions' LDS is reused by the next part
-  }
+__global__ __launch_bounds__(BS_THREADS) void bs_compact_kernel(const KeyT* __restrict__ part, const int32_t* __restrict__ at,
+                                                                const int32_t* __restrict__ num, const LevelOut<KeyT> lo, size_t ws_pitch,
+                                                                int32_t* tot, size_t tot_pitch, int n_bin) {
+  if (tot)  // (kept cleared between sorts)
+    for (int b = blockIdx.x * BS_THREADS + threadIdx.x; b < n_bin; b += gridDim.x * BS_THREADS) level_ws(tot, tot_pitch)[b] = 0;
+  part = level_ws(part, ws_pitch);
+  at = level_ws(at, ws_pitch);
+  num = level_ws(num, ws_pitch);
+  __shared__ int sums[BS_THREADS / 64];
+  const int t = threadIdx.x, p = blockIdx.x, mine = num[p];
+  const KeyT* from = part + at[p];
+  int before = 0;
+  for (int i = t; i < p; i += BS_THREADS) before += num[i];
+  block_scan<BS_THREADS / 64>(before, sums, &before);
+  KeyT* out = lo.keys[blockIdx.y] + before;
+  for (int i = t; i < mine; i += BS_THREADS) out[i] = from[i];
+  if (p == int(gridDim.x) - 1 && t == 0) *lo.count[blockIdx.y] = before + mine;
 }
 
 // ---------------------------------------------------------------- small levels: one workgroup, one launch
@@ -1069,6 +937,278 @@ int small_mask_unique(int key_bits, const void* keys_in, int64_t n, const LevelJ
   return SPC_OK;
 }
 
+// ---------------------------------------------------------------- recorded sorts: column scan (above BS_ADD_N keys)
+// One thread per four bins: before[w][f] receives the number of keys of bin f held by workgroups
+// < w, tot[f] the bin's total.  The loads of 32 table rows are in flight together (16: 1 us more from 500 k keys on).
+constexpr int BS_COL_THREADS = 64;
+__global__ __launch_bounds__(BS_COL_THREADS) void bs_colscan_kernel(const int32_t* __restrict__ table,
+                                                                    int32_t* __restrict__ before, int n_wg, int n_bin,
+                                                                    int32_t* __restrict__ tot) {
+  constexpr int ROWS = 32;
+  const int f0 = (blockIdx.x * BS_COL_THREADS + threadIdx.x) * 4;
+  if (f0 >= n_bin) return;  // n_bin is a multiple of 4
+  int4 run = make_int4(0, 0, 0, 0);
+  for (int w0 = 0; w0 < n_wg; w0 += ROWS) {
+    int4 c[ROWS];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) c[r] = *reinterpret_cast<const int4*>(table + int64_t(min(w0 + r, n_wg - 1)) * n_bin + f0);
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+      if (w0 + r < n_wg) {
+        *reinterpret_cast<int4*>(before + int64_t(w0 + r) * n_bin + f0) = run;
+        run.x += c[r].x;
+        run.y += c[r].y;
+        run.z += c[r].z;
+        run.w += c[r].w;
+      }
+  }
+  *reinterpret_cast<int4*>(tot + f0) = run;
+}
+
+// ---------------------------------------------------------------- recorded sorts: scatter
+// Every workgroup scans the bin totals on its own (16 KB; cheaper than one more launch): start
+// of bin f, then the workgroup's first position in the bin, and moves its keys, with their source
+// index, to their bin's range.
+// It also prepares the rank pass: for every BS_PART scattered
+// positions the window of whole bins that covers them, and BS_PAD_KEYS all-ones keys behind the last key.
+// What bounds it: the scattered stores, of which a CU issues one lane per cycle, so the shares of the workgroups are short
+// (see bucket_plan).
+// SUM (few workgroups): `before` is the table of counts as the count pass leaves it
+// without ADD, and its rows are summed here, which saves the launch that would clear the totals.
+template <typename KeyT, bool SUM>
+__global__ __launch_bounds__(BS_WIDE) void bs_scatter_kernel(const KeyT* __restrict__ keys0, int64_t n, int per, int shift,
+                                                             int n_bin, const int32_t* __restrict__ before,
+                                                             const int32_t* __restrict__ tot, KeyT* __restrict__ keys1,
+                                                             int32_t* __restrict__ vals1, int2* __restrict__ win) {
+  extern __shared__ int lds_bins[];
+  int* pos = lds_bins;                    // [n_bin + 1] this workgroup's running position in every bin
+  int* bin_start = lds_bins + n_bin + 1;  // [n_bin + 1] where every bin starts
+  __shared__ int wave_tot[BS_WIDE / 64];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  // a pass takes four keys per thread; the first pass's are requested before the scan, so that they arrive under it
+  const int64_t lo = int64_t(blockIdx.x) * per, hi = min<int64_t>(n, lo + per);
+  KeyT key[4];
+  auto fetch = [&](int64_t i0) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t i = min<int64_t>(i0 + u * BS_WIDE, hi - 1);
+      key[u] = keys0[i];
+    }
+  };
+  fetch(lo + threadIdx.x);
+  // exclusive scan of the bin totals, four bins per thread and round (one round up to 4096 bins)
+  int total = 0;
+  for (int r0 = 0; r0 < n_bin; r0 += 4 * BS_WIDE) {
+    const int f0 = r0 + t * 4;
+    int4 c = make_int4(0, 0, 0, 0), bef = c;
+    if (f0 < n_bin) {
+      if constexpr (SUM) {
+        constexpr int ROWS = 8;  // loads in flight
+        const int n_wg = gridDim.x, me = blockIdx.x;
+        for (int w = 0; w < n_wg; w += ROWS) {
+          int4 row[ROWS];
+#pragma unroll
+          for (int r = 0; r < ROWS; ++r) row[r] = *reinterpret_cast<const int4*>(before + int64_t(min(w + r, n_wg - 1)) * n_bin + f0);
+#pragma unroll
+          for (int r = 0; r < ROWS; ++r) {
+            const int all = w + r < n_wg ? -1 : 0, mine = w + r < me ? -1 : 0;
+            c.x += row[r].x & all, c.y += row[r].y & all, c.z += row[r].z & all, c.w += row[r].w & all;
+            bef.x += row[r].x & mine, bef.y += row[r].y & mine, bef.z += row[r].z & mine, bef.w += row[r].w & mine;
+          }
+        }
+      } else {
+        c = *reinterpret_cast<const int4*>(tot + f0);
+        bef = *reinterpret_cast<const int4*>(before + int64_t(blockIdx.x) * n_bin + f0);
+      }
+    }
+    const int sum = c.x + c.y + c.z + c.w;
+    int x = sum;
+    for (int d = 1; d < 64; d <<= 1) {
+      const int y = __shfl_up(x, d, 64);
+      if (lane >= d) x += y;
+    }
+    if (r0 > 0) __syncthreads();  // the wave totals of the round before have been read
+    if (lane == 63) wave_tot[wave] = x;
+    __syncthreads();
+    int base = total + x - sum;
+    for (int w = 0; w < BS_WIDE / 64; ++w) {
+      if (w < wave) base += wave_tot[w];
+      total += wave_tot[w];
+    }
+    if (f0 < n_bin) {
+      const int s0 = base, s1 = base + c.x, s2 = s1 + c.y, s3 = s2 + c.z;
+      pos[f0] = s0 + bef.x;
+      pos[f0 + 1] = s1 + bef.y;
+      pos[f0 + 2] = s2 + bef.z;
+      pos[f0 + 3] = s3 + bef.w;
+      bin_start[f0] = s0;
+      bin_start[f0 + 1] = s1;
+      bin_start[f0 + 2] = s2;
+      bin_start[f0 + 3] = s3;
+    }
+  }
+  if (t == 0) bin_start[n_bin] = total;
+  __syncthreads();
+  for (int64_t i0 = lo + threadIdx.x; i0 < hi; i0 += 4 * BS_WIDE) {
+    // all keys of the pass are fetched, then all positions drawn, then everything stored
+    bool use[4];
+    int p[4];
+    if (i0 >= lo + 4 * BS_WIDE) fetch(i0);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      SPC_PIN_LOADED(key[u]);
+      use[u] = i0 + u * BS_WIDE < hi;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) p[u] = use[u] ? atomicAdd(&pos[bs_bin(key[u], shift, n_bin)], 1) : 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (use[u]) {
+        keys1[p[u]] = key[u];
+        vals1[p[u]] = static_cast<int32_t>(i0 + u * BS_WIDE);
+      }
+  }
+  // Rank windows (see bs_rank_kernel): part p = scattered positions [p * BS_PART, ...) is ranked
+  // inside the range of whole bins that covers it.  Parts are dealt round-robin to the workgroups,
+  // one per thread: two binary searches over the bin starts in LDS, done last, while the scattered
+  // stores drain.
+  if (blockIdx.x == 0 && t < BS_PAD_KEYS) keys1[total + t] = ~KeyT(0);  // the rank kernel reads whole steps
+  const int part = blockIdx.x + t * gridDim.x;
+  if (int64_t(part) * BS_PART < total) {
+    const int x0 = part * BS_PART, x1 = min(x0 + BS_PART, total) - 1;
+    // last bin whose start is <= x: the (non-empty) bin that holds position x; both searches in step
+    int fa = 0, fb = 0;
+    for (int step = n_bin >> 1; step > 0; step >>= 1) {
+      const int sa = bin_start[fa + step], sb = bin_start[fb + step];
+      if (sa <= x0) fa += step;
+      if (sb <= x1) fb += step;
+    }
+    win[part] = make_int2(bin_start[fa], bin_start[fb + 1]);
+  }
+}
+
+// ---------------------------------------------------------------- recorded sorts: rank
+// After the scatter the keys are ordered by bin, unordered inside a bin.  Workgroup p takes the
+// BS_PART = 64 keys at scattered positions [p * BS_PART, ...), one per lane, each of its four waves
+// a quarter of the comparisons, and ranks each of them inside the window of whole bins that covers those positions (widened to multiples of 32
+// positions): every key before the window is smaller and every key behind it larger, so
+// window start + (number of window keys that sort before mine) is the key's final position.
+// "Sorts before" is (key, scattered position) order, which makes the positions of equal keys
+// distinct without any atomics; below and above the workgroup's own 64 positions that is a plain
+// <= resp. < on the key.  Every lane of a wave compares its key with the same window key at the same
+// time, so the window is read with scalar loads (128 bytes per step, the next step's load in
+// flight while the current one is compared) and a comparison is two vector instructions with a
+// scalar operand; LDS only carries the four partial counts of a key to the wave that stores.  (Reading the window back from LDS at a wave-uniform address
+// was measured four times slower: 16-byte LDS reads of one address by all lanes are not broadcast.)
+// Work per key grows with the window, i.e. with the size of the bins involved, but a big bin is
+// shared by as many workgroups as it has parts: no workgroup sorts a dense region of the scene
+// alone, which is what bounded the compare-exchange network this replaces on the pack + sort path.
+// The scatter leaves BS_RANK_STEP all-ones keys behind the last key, so that whole steps can be
+// read at the end of the array.
+constexpr int BS_RANK_STEP = BS_PAD_KEYS;  // positions; a window is a whole number of steps
+// 128 bytes of keys at a wave-uniform address in scalar registers.  The load is issued by hand and
+// its arrival awaited by hand, one compare step later: left to the compiler, the load of a step
+// ends up right in front of its first use and every step pays the scalar-memory latency.
+typedef uint32_t bs_u32x16 __attribute__((ext_vector_type(16)));
+struct BsChunk {
+  bs_u32x16 lo, hi;
+  // (the address is in scalar registers: derived from blockIdx and kernel arguments)
+  __device__ void issue(const void* q) {
+    asm volatile("s_load_dwordx16 %0, %2, 0x0\n\ts_load_dwordx16 %1, %2, 0x40" : "=&s"(lo), "=&s"(hi) : "s"(q) : "memory");
+  }
+  // the counters are operands only to keep the compare step that runs under the load in front of the wait
+  __device__ void arrive(int (&c)[4]) {
+    asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(lo), "+s"(hi), "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]));
+  }
+  template <typename KeyT>
+  __device__ KeyT key(int q) const {  // q-th key of the chunk, q a compile-time constant after unrolling
+    if constexpr (sizeof(KeyT) == 4) return q < 16 ? lo[q] : hi[q - 16];
+    else return q < 8 ? (uint64_t(lo[2 * q + 1]) << 32) | lo[2 * q] : (uint64_t(hi[2 * q - 15]) << 32) | hi[2 * q - 16];
+  }
+};
+
+// keys k[a, b) that sort before (key, x): MODE 0 for positions below the workgroup's own 64 (equal
+// keys count), 2 for positions above (they do not), 1 for the own positions (full comparison).
+// a and b are multiples of BS_RANK_STEP.
+template <int MODE, typename KeyT>
+__device__ inline int bs_count_before(const KeyT* __restrict__ k, int a, int b, KeyT key, int x) {
+  constexpr int C = 128 / sizeof(KeyT);  // keys per chunk
+  static_assert(BS_RANK_STEP % C == 0, "a step of positions is a whole number of chunks");
+  int c[4] = {0, 0, 0, 0};
+  if (a >= b) return 0;
+  auto compare = [&](const BsChunk& ch, int j) {
+#pragma unroll
+    for (int q = 0; q < C; ++q) {
+      const KeyT e = ch.template key<KeyT>(q);
+      bool before;
+      if (MODE == 0) before = e <= key;
+      else if (MODE == 2) before = e < key;
+      else before = e < key || (e == key && j + q < x);
+      c[q & 3] += before ? 1 : 0;
+    }
+  };
+  BsChunk A, B;
+  A.issue(k + a);
+  A.arrive(c);
+  for (int j = a; j < b; j += 2 * C) {  // the last chunk is fetched once more instead of running past b
+    B.issue(k + min(j + C, b - C));
+    compare(A, j);
+    B.arrive(c);
+    if (j + C < b) {
+      A.issue(k + min(j + 2 * C, b - C));
+      compare(B, j + C);
+      A.arrive(c);
+    }
+  }
+  return (c[0] + c[1]) + (c[2] + c[3]);
+}
+
+template <typename KeyT, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void bs_rank_kernel(const KeyT* __restrict__ keys1, const int32_t* __restrict__ vals1,
+                                                             const int2* __restrict__ win, int n, KeyT* __restrict__ out_k,
+                                                             int32_t* __restrict__ out_v) {
+  static_assert(BS_PART == 64, "one key per lane");
+  __shared__ int partial[WAVES][BS_PART];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  const int part = blockIdx.x, own0 = part * BS_PART;
+  const int x = own0 + lane;
+  const bool act = x < n;
+  const int2 w = win[part];
+  const KeyT key = act ? keys1[x] : ~KeyT(0);
+  const int32_t val = act && out_v && wave == 0 ? vals1[x] : 0;
+  const int n_pad = (n + BS_RANK_STEP - 1) & ~(BS_RANK_STEP - 1);  // positions n .. n_pad - 1 hold all-ones keys
+  const int g0 = w.x & ~(BS_RANK_STEP - 1);
+  const int g1 = min(max((w.y + BS_RANK_STEP - 1) & ~(BS_RANK_STEP - 1), own0 + BS_PART), n_pad);
+  // the window is cut into the part below the own positions, the own positions and the part above;
+  // each is shared out among the waves in contiguous quarters (rounded to whole steps)
+  const int own1 = min(own0 + BS_PART, g1);
+  auto quarter = [&](int a, int b, int& qa, int& qb) {
+    const int steps = (b - a) / BS_RANK_STEP, per = (steps + WAVES - 1) / WAVES;
+    qa = min(a + wave * per * BS_RANK_STEP, b);
+    qb = min(qa + per * BS_RANK_STEP, b);
+  };
+  int qa, qb;
+  quarter(g0, own0, qa, qb);
+  int c = bs_count_before<0>(keys1, qa, qb, key, x);
+  quarter(own0, own1, qa, qb);
+  c += bs_count_before<1>(keys1, qa, qb, key, x);
+  quarter(own1, g1, qa, qb);
+  c += bs_count_before<2>(keys1, qa, qb, key, x);
+  int r = g0 + c;
+  if constexpr (WAVES > 1) {
+    partial[wave][lane] = c;
+    __syncthreads();
+    r = g0;
+#pragma unroll
+    for (int v = 0; v < WAVES; ++v) r += partial[v][lane];
+  }
+  if (wave == 0 && act) {
+    out_k[r] = key;
+    if (out_v) out_v[r] = val;
+  }
+}
+
 // ---------------------------------------------------------------- host
 BucketPlan bucket_plan(int64_t n, int used_bits, bool unique) {
   BucketPlan p{};
@@ -1097,25 +1237,15 @@ BucketPlan bucket_plan(int64_t n, int used_bits, bool unique) {
   return p;
 }
 
+
 namespace {
+// The workspace of a recorded sort, and of one in split + merge form (which is nowhere larger; see bucket_sort_ws_bytes).
 template <typename KeyT>
 struct Ws {
-  KeyT* keys0;
-  KeyT* keys1;
-  int32_t* vals1;
-  int32_t* table;
-  int32_t* before;
-  int32_t* fstart;
+  KeyT *keys0, *keys1;
+  int32_t *vals1, *table, *before, *fstart;
   int2* win;
-  int32_t* n_kept;
-  int32_t* ccnt;
-  uint32_t* bits;
-  int32_t* rest_count;  // workgroups of bs_rank_lds_kernel whose window did not fit, and their numbers
-  int32_t* rest;
-  int n_words, n_chunks;
 };
-size_t words_for(int64_t n) { return static_cast<size_t>(n / 32 + 64); }    // bitmap words the downsampling path clears and reads
-size_t chunks_for(int64_t n) { return static_cast<size_t>(n / BS_CHUNK + 2); }
 template <typename KeyT>
 Ws<KeyT> carve(void* ws, int64_t n) {
   const size_t nn = static_cast<size_t>(std::max<int64_t>(n, 1));
@@ -1126,48 +1256,92 @@ Ws<KeyT> carve(void* ws, int64_t n) {
   w.keys1 = reinterpret_cast<KeyT*>(c + k);
   w.vals1 = reinterpret_cast<int32_t*>(c + 2 * k);
   w.table = reinterpret_cast<int32_t*>(c + 2 * k + v);
-  // as many workgroups and at least as many bins as any plan for n keys (both forms of a plan have the same bins, that for levels
-  // the more workgroups)
   const BucketPlan cap = bucket_plan(n, 64, true);
   const size_t tbl = (size_t(cap.n_wg) * cap.n_bin + 63) / 64 * 64;
   w.before = w.table + tbl;
   w.fstart = w.before + (cap.add ? 0 : tbl);
   w.win = reinterpret_cast<int2*>(w.fstart + cap.n_bin + 64);  // 8-byte aligned: every part above is a multiple of 256 bytes
-  w.n_kept = reinterpret_cast<int32_t*>(w.win + (nn / BS_PART + 2));
-  w.ccnt = w.n_kept + 2;
-  w.n_chunks = static_cast<int>(chunks_for(n));
-  w.bits = reinterpret_cast<uint32_t*>(w.ccnt + w.n_chunks);
-  w.n_words = static_cast<int>(words_for(n));
-  w.rest_count = w.n_kept + 1;
-  w.rest = reinterpret_cast<int32_t*>(w.bits + w.n_words);
+  return w;
+}
+
+// Split + merge: sizes of both kernels' shares.
+struct SplitPlan {
+  BucketPlan b;
+  int q, n_share;  // positions per merging workgroup
+  bool wide;       // four keys per merge thread instead of two
+};
+// Positions per merging workgroup: where the totals are read, short shares spread a cloud over the chip; where the starts have been
+// made, long ones take longer pieces.  Split shares are those of bucket_plan (half as long, 120 k 4.8 -> 5.7 us and 240 k 9.2 -> 11.2 for the
+// additions), above BS_ADD_N as long as gives every CU one (half as long, with 8192 bins, 3 * 10^6: 65 -> 69 us in all).
+SplitPlan split_plan(int64_t n, int used_bits, bool unique) {
+  SplitPlan p{};
+  p.b = bucket_plan(n, used_bits, unique);
+  if (!p.b.add) {  // about a region per CU
+    p.b.per = static_cast<int>(std::min<int64_t>(std::max<int64_t>((n / 256 + BS_WIDE - 1) / BS_WIDE, 4), BS_SPLIT_KPT) * BS_WIDE);
+    p.b.n_wg = static_cast<int>((n + p.b.per - 1) / p.b.per);
+  }
+  p.wide = !p.b.add;
+  p.q = p.wide ? 2048 : 512;
+  p.n_share = static_cast<int>((n + p.q - 1) / p.q);
+  return p;
+}
+template <typename KeyT, bool DEDUP>
+struct SplitWs {
+  typename BsForm<KeyT, DEDUP>::Elem* recs;
+  int32_t* rows;
+  KeyT* part;
+  uint16_t* off;
+  int32_t *tot, *out_at, *out_n, *n_kept, *arrived;
+  BsShare* share;
+  size_t bytes;
+};
+template <typename KeyT, bool DEDUP>
+SplitWs<KeyT, DEDUP> carve_split(void* ws, int64_t n, const SplitPlan& p) {
+  using F = BsForm<KeyT, DEDUP>;
+  SplitWs<KeyT, DEDUP> w{};
+  char* c = static_cast<char*>(ws);
+  size_t at = 0;
+  auto take = [&](size_t bytes) {
+    char* r = c + at;
+    at += (bytes + 255) / 256 * 256;
+    return r;
+  };
+  w.n_kept = reinterpret_cast<int32_t*>(take(256));
+  w.arrived = reinterpret_cast<int32_t*>(take((BS_ARRIVE + 1) * BS_ARRIVE_PITCH * 4));
+  w.recs = reinterpret_cast<typename F::Elem*>(take(size_t(n) * sizeof(typename F::Elem)));
+  if (F::ROWS) w.rows = reinterpret_cast<int32_t*>(take(size_t(n) * 4));
+  if (DEDUP) {
+    w.part = reinterpret_cast<KeyT*>(take(size_t(n) * sizeof(KeyT)));
+    w.out_at = reinterpret_cast<int32_t*>(take(size_t(p.n_share) * 4));
+    w.out_n = reinterpret_cast<int32_t*>(take(size_t(p.n_share) * 4));
+  }
+  w.share = reinterpret_cast<BsShare*>(take(size_t(p.n_share) * sizeof(BsShare)));
+  w.tot = reinterpret_cast<int32_t*>(take(size_t(p.b.n_bin) * 4));
+  w.off = reinterpret_cast<uint16_t*>(take(size_t(p.b.n_wg) * bs_off_pitch(p.b.n_bin) * 2));
+  w.bytes = at;
   return w;
 }
 
 // The bins' totals of a sort: in a block that the library keeps cleared between its sorts (the last kernel clears it again),
 // or, where none is to be had (under capture, whose replays know nothing of other sorts; on hipStreamPerThread; once the blocks of
 // the library's image are in use on other streams), in the workspace, cleared by a kernel of its own, or nowhere, where so few
-// workgroups have counted that the scatter pass may sum their counts itself (p is NULL then).
+// workgroups have counted that their counts may be summed where they are read (p is NULL then).  Levels, whose launches are
+// nobody's contract, have none then either (bs_starts_kernel).
 struct Totals {
   int32_t* p = nullptr;
   size_t pitch = 0, bytes = 0;
   bool kept = false;
   StreamId s;
-  Totals(const BucketPlan& plan, int32_t* in_ws, size_t ws_pitch, int n_levels, bool may_alloc, const StreamId& s_) : p(in_ws), pitch(ws_pitch), s(s_) {
+  Totals(const BucketPlan& plan, int32_t* in_ws, int n_levels, bool levels, const StreamId& s_) : s(s_) {
     if (!plan.add) return;
     bytes = size_t(plan.n_bin) * 4 * n_levels;
-    if (void* zeros = zeroed_alloc(bytes, s, may_alloc)) {
-      p = static_cast<int32_t*>(zeros);
-      pitch = size_t(plan.n_bin) * 4;
-      kept = true;
-      return;
-    }
-    if (plan.n_wg <= BS_SUM_WG) {
-      p = nullptr;
-      return;
-    }
-    hipLaunchKernelGGL(bs_clear_kernel, dim3((plan.n_bin + BS_THREADS - 1) / BS_THREADS, n_levels), dim3(BS_THREADS), 0, s, p, plan.n_bin, pitch);
+    pitch = size_t(plan.n_bin) * 4;
+    p = static_cast<int32_t*>(zeroed_alloc(bytes, s, levels));
+    kept = p != nullptr;
+    if (kept || levels || plan.n_wg <= BS_SUM_WG) return;
+    p = in_ws;
+    hipLaunchKernelGGL(bs_clear_kernel, dim3((plan.n_bin + BS_THREADS - 1) / BS_THREADS), dim3(BS_THREADS), 0, s, p, plan.n_bin);
   }
-  int32_t* to_clear() const { return kept ? p : nullptr; }
   // once all kernels of the sort are enqueued
   int done(const char* what) {
     const bool ok = hipGetLastError() == hipSuccess;
@@ -1176,39 +1350,65 @@ struct Totals {
   }
 };
 
-// count, (column scan,) scatter: keys1 (vals1) partitioned by fine bin, rank windows
-template <typename KeyT, bool DEDUP, bool REC, typename Src>
-void partition(const Src& src, int64_t n, const BucketPlan& p, const Ws<KeyT>& w, int n_levels, size_t ws_pitch, const Totals& t, hipStream_t s) {
-  const int32_t* before = w.table;
-  const bool sum = p.add && !t.p;
-  if (p.add && !sum) {
-    hipLaunchKernelGGL((bs_count_kernel<KeyT, Src, true>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(p.n_bin) * 4, s, src, n, p.per,
-                       p.shift, p.n_bin, w.keys0, w.table, ws_pitch, t.p, t.pitch);
-  } else {
-    hipLaunchKernelGGL((bs_count_kernel<KeyT, Src, false>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(p.n_bin) * 4, s, src, n, p.per,
-                       p.shift, p.n_bin, w.keys0, w.table, ws_pitch, static_cast<int32_t*>(nullptr), size_t(0));
-  }
-  if (!p.add) {
-    const int col_wg = (p.n_bin / 4 + BS_COL_THREADS - 1) / BS_COL_THREADS;
-    hipLaunchKernelGGL(bs_colscan_kernel, dim3(col_wg, n_levels), dim3(BS_COL_THREADS), 0, s, w.table, w.before, p.n_wg, p.n_bin,
-                       t.p, ws_pitch);
-    before = w.before;
-  }
-  auto scatter = [&](auto SUM_) {
-    constexpr bool SUM = decltype(SUM_)::value;
-    // (the scatter pass holds two ints per bin: beyond 8191 bins that is more than the default LDS limit)
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bs_scatter_kernel<KeyT, DEDUP, REC, SUM>),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (2 * BS_MAX_BIN + 2) * 4);
-    (void)attr;
-    hipLaunchKernelGGL((bs_scatter_kernel<KeyT, DEDUP, REC, SUM>), dim3(p.n_wg, n_levels), dim3(BS_WIDE), size_t(2 * p.n_bin + 2) * 4, s,
-                       w.keys0, n, p.per, p.shift, p.n_bin, before, t.p, t.pitch, reinterpret_cast<BsElem<KeyT, REC>*>(w.keys1), w.vals1,
-                       w.win, DEDUP ? w.n_kept : static_cast<int32_t*>(nullptr), w.bits, w.n_words, w.ccnt, w.n_chunks, w.rest_count,
-                       ws_pitch);
+// split, (starts,) merge
+template <typename KeyT, bool DEDUP, typename Src>
+void split_merge(const Src& src, int64_t n, int used_bits, const SplitPlan& p, const SplitWs<KeyT, DEDUP>& w, int n_levels, size_t ws_pitch,
+                 const Totals& t, KeyT* out_k, int32_t* out_v, hipStream_t s) {
+  const BucketPlan& b = p.b;
+  const size_t lds = bs_split_lds<KeyT, DEDUP>(b.n_bin, b.per);
+  auto split = [&](auto KPT_, auto ADD_) {
+    constexpr int KPT = decltype(KPT_)::value;
+    constexpr bool ADD = decltype(ADD_)::value;
+    if constexpr (!ADD) {  // (16384 bins or long shares: more than the default LDS limit)
+      static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bs_count_kernel<KeyT, Src, DEDUP, KPT, ADD>),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024);
+      (void)attr;
+    }
+    hipLaunchKernelGGL((bs_count_kernel<KeyT, Src, DEDUP, KPT, ADD>), dim3(b.n_wg, n_levels), dim3(BS_WIDE), lds, s, src, n, b.per, b.shift,
+                       b.n_bin, static_cast<void*>(w.recs), static_cast<void*>(w.off), ws_pitch, t.p, t.pitch, w.rows, t.kept && !DEDUP ? w.arrived : nullptr);
   };
-  if constexpr (!REC) {
-    if (sum) return scatter(std::true_type{});
+  auto keys = [&](auto ADD_) {
+    if (b.per <= 2 * BS_WIDE) split(std::integral_constant<int, 2>{}, ADD_);
+    else if (b.per <= 4 * BS_WIDE) split(std::integral_constant<int, 4>{}, ADD_);
+    else if constexpr (!decltype(ADD_)::value) split(std::integral_constant<int, BS_SPLIT_KPT>{}, ADD_);
+  };
+  if (t.p) keys(std::true_type{});
+  else keys(std::false_type{});
+  MergeArgs<KeyT, DEDUP> a{};
+  a.recs = w.recs;
+  a.rows = w.rows;
+  a.off = w.off;
+  a.n_wg = b.n_wg;
+  a.per = b.per;
+  a.shift = b.shift;
+  a.n_bin = b.n_bin;
+  a.q = p.q;
+  a.used_bits = used_bits;
+  a.tot = t.p;
+  a.tot_pitch = t.pitch;
+  a.clear = t.kept ? 1 : 0;
+  a.arrived = w.arrived;
+  a.share = w.share;
+  a.n_kept = w.n_kept;
+  a.out_k = out_k;
+  a.out_v = out_v;
+  a.out_at = w.out_at;
+  a.out_n = w.out_n;
+  a.ws_pitch = ws_pitch;
+  auto merge = [&](auto WIDE_, auto FROM_) {
+    constexpr int KPT = decltype(WIDE_)::value ? 4 : 2, FROM = decltype(FROM_)::value;
+    hipLaunchKernelGGL((bs_merge_kernel<KeyT, DEDUP, KPT, FROM>), dim3(p.n_share, n_levels), dim3(BS_MT), 0, s, a);
+  };
+  if (!t.p && !DEDUP && b.add) {  // (few regions)
+    if constexpr (!DEDUP) merge(std::false_type{}, std::integral_constant<int, BS_TABLE>{});
+    return;
   }
-  scatter(std::false_type{});
+  if (!t.p)
+    hipLaunchKernelGGL(bs_starts_kernel, dim3((b.n_bin + BS_START_BINS - 1) / BS_START_BINS, n_levels), dim3(BS_WIDE), 0, s, w.off, b.n_wg, b.n_bin,
+                       p.q, p.n_share, w.share, w.n_kept, ws_pitch);
+  if (t.p) merge(std::false_type{}, std::integral_constant<int, BS_TOTALS>{});
+  else if (p.wide) merge(std::true_type{}, std::integral_constant<int, BS_STARTS>{});
+  else if constexpr (DEDUP) merge(std::false_type{}, std::integral_constant<int, BS_STARTS>{});
 }
 }  // namespace
 
@@ -1224,46 +1424,68 @@ static size_t table_entries(int64_t n) {
   return most;
 }
 
+// (also what split + merge take: 8 or 12 bytes a key, twice a key for levels, and rows of 16-bit entries for no more regions than the
+// tables' rows, except that beyond 6 Mi keys there are more regions than these)
 size_t bucket_sort_ws_bytes(int key_bits, int64_t n) {
   const size_t nn = static_cast<size_t>(std::max<int64_t>(n, 1));
   const size_t k = ((nn + BS_PAD_KEYS) * (key_bits / 8) + 255) / 256 * 256, v = ((nn + BS_PAD_KEYS) * 4 + 255) / 256 * 256;
   const BucketPlan cap = bucket_plan(n, 64, true);
-  return 2 * k + v + (table_entries(n) + cap.n_bin + 64 + 2 * (nn / BS_PART + 2) + 2 + chunks_for(n) + words_for(n) + (nn / BS_LP + 2)) * 4;
+  const size_t tables = std::max(table_entries(n) * 4, (nn / (BS_SPLIT_KPT * BS_WIDE) + 1) * bs_off_pitch(BS_MAX_BIN) * 2 * size_t(n > BS_ADD_N));
+  return 2 * k + v + tables + (cap.n_bin + 64 + 2 * (nn / BS_PART + 2)) * 4 + 2048;
+}
+
+template <typename KeyT>
+static int recorded_pack_sort(const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status, KeyT* keys_out,
+                              int32_t* perm_out, void* ws, const StreamId& s) {
+  const BucketPlan p = bucket_plan(n, used_bits, false);
+  const Ws<KeyT> w = carve<KeyT>(ws, n);
+  Totals tot(p, w.fstart, 1, false, s);
+  const SrcPack<KeyT> src{coords, pp, status};
+  using Src = SrcPack<KeyT>;
+  const bool sum = p.add && !tot.p;
+  auto count = [&](auto ADD_) {
+    hipLaunchKernelGGL((bs_count_kernel<KeyT, Src, false, 0, decltype(ADD_)::value>), dim3(p.n_wg), dim3(BS_WIDE), size_t(p.n_bin) * 4, s, src, n,
+                       p.per, p.shift, p.n_bin, static_cast<void*>(w.keys0), static_cast<void*>(w.table), size_t(0), tot.p, size_t(0),
+                       static_cast<int32_t*>(nullptr), static_cast<int32_t*>(nullptr));
+  };
+  if (tot.p) count(std::true_type{});
+  else count(std::false_type{});
+  if (!p.add)
+    hipLaunchKernelGGL(bs_colscan_kernel, dim3((p.n_bin / 4 + BS_COL_THREADS - 1) / BS_COL_THREADS), dim3(BS_COL_THREADS), 0, s, w.table, w.before,
+                       p.n_wg, p.n_bin, w.fstart);
+  auto scatter = [&](auto SUM_) {
+    constexpr bool SUM = decltype(SUM_)::value;
+    // (the scatter pass holds two ints per bin: beyond 8191 bins that is more than the default LDS limit)
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bs_scatter_kernel<KeyT, SUM>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (2 * BS_MAX_BIN + 2) * 4);
+    (void)attr;
+    hipLaunchKernelGGL((bs_scatter_kernel<KeyT, SUM>), dim3(p.n_wg), dim3(BS_WIDE), size_t(2 * p.n_bin + 2) * 4, s, w.keys0, n, p.per, p.shift,
+                       p.n_bin, p.add ? w.table : w.before, p.add ? tot.p : w.fstart, w.keys1, w.vals1, w.win);
+  };
+  if (sum) scatter(std::true_type{});
+  else scatter(std::false_type{});
+  // Four waves share a part's window while the launch is latency-bound (its time is that of the part with
+  // the largest window); from BS_RANK_SOLO_N keys on the pass is bound by how many parts
+  // a CU has in flight, and one wave per part (no LDS, no barrier, four times the parts per CU) is
+  // faster: 10^6 keys 32 -> 26 us; at 240 k keys of dense indoor scenes it was slower (37 -> 47 us).
+  const int n_part = static_cast<int>((n + BS_PART - 1) / BS_PART);
+  if (n >= BS_RANK_SOLO_N)
+    hipLaunchKernelGGL((bs_rank_kernel<KeyT, 1>), dim3(n_part), dim3(64), 0, s, w.keys1, w.vals1, w.win, static_cast<int>(n), keys_out, perm_out);
+  else
+    hipLaunchKernelGGL((bs_rank_kernel<KeyT, BS_THREADS / 64>), dim3(n_part), dim3(BS_THREADS), 0, s, w.keys1, w.vals1, w.win,
+                       static_cast<int>(n), keys_out, perm_out);
+  return tot.done("sort");
 }
 
 template <typename KeyT>
 static int pack_sort_t(const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status, void* keys_out,
                        int32_t* perm_out, void* ws, const StreamId& s) {
-  const BucketPlan p = bucket_plan(n, used_bits, false);
-  const Ws<KeyT> w = carve<KeyT>(ws, n);
-  Totals tot(p, w.fstart, 0, 1, false, s);
-  // one element array (see REC): over keys1 and vals1 together, which lie one behind the other
-  constexpr bool REC = sizeof(KeyT) == 4;
-  const SrcPack<KeyT> src{coords, pp, status};
-  if (n >= BS_RANK_LDS_N) partition<KeyT, false, REC>(src, n, p, w, 1, 0, tot, s);
-  else partition<KeyT, false, false>(src, n, p, w, 1, 0, tot, s);
-  const int n_part = static_cast<int>((n + BS_PART - 1) / BS_PART);
-  // Four waves share a part's window while the launch is latency-bound (its time is that of the part with
-  // the largest window); from BS_RANK_SOLO_N keys on (25 parts per CU) the pass is bound by how many parts
-  // a CU has in flight, and one wave per part (no LDS, no barrier, four times the parts per CU) is
-  // faster: 10^6 keys 32 -> 26 us, 2 * 10^6 keys 145 -> 129 us for the whole sort; at 240 k keys of
-  // dense indoor scenes it was slower (37 -> 47 us).
-  if (n >= BS_RANK_LDS_N) {
-    const auto* elems = reinterpret_cast<const BsElem<KeyT, REC>*>(w.keys1);
-    const int shift = p.shift + (REC ? 32 : 0);
-    hipLaunchKernelGGL((bs_rank_lds_kernel<KeyT, false, REC>), dim3(static_cast<int>((n + BS_LP - 1) / BS_LP)), dim3(BS_LT), 0, s, elems,
-                       w.vals1, w.win, static_cast<int>(n), static_cast<const int32_t*>(nullptr), shift, p.n_bin,
-                       static_cast<KeyT*>(keys_out), perm_out, static_cast<uint32_t*>(nullptr), static_cast<int32_t*>(nullptr),
-                       w.rest_count, w.rest, size_t(0));
-    hipLaunchKernelGGL((bs_rank_rest_kernel<KeyT, false, REC>), dim3(BS_REST_WG), dim3(BS_THREADS), 0, s, w.rest_count, w.rest, elems,
-                       w.vals1, w.win, static_cast<int>(n), static_cast<const int32_t*>(nullptr), static_cast<KeyT*>(keys_out),
-                       perm_out, static_cast<uint32_t*>(nullptr), static_cast<int32_t*>(nullptr), size_t(0));
-  } else if (n >= BS_RANK_SOLO_N)
-    hipLaunchKernelGGL((bs_rank_kernel<KeyT, 1>), dim3(n_part), dim3(64), 0, s, w.keys1, w.vals1, w.win, static_cast<int>(n),
-                       static_cast<KeyT*>(keys_out), perm_out, tot.to_clear(), p.n_bin);
-  else
-    hipLaunchKernelGGL((bs_rank_kernel<KeyT, BS_THREADS / 64>), dim3(n_part), dim3(BS_THREADS), 0, s, w.keys1, w.vals1, w.win,
-                       static_cast<int>(n), static_cast<KeyT*>(keys_out), perm_out, tot.to_clear(), p.n_bin);
+  if (n < BS_LARGE_N && stream_is_capturing(s))
+    return recorded_pack_sort<KeyT>(coords, n, pp, used_bits, status, static_cast<KeyT*>(keys_out), perm_out, ws, s);
+  const SplitPlan p = split_plan(n, used_bits, false);
+  const SplitWs<KeyT, false> w = carve_split<KeyT, false>(ws, n, p);
+  Totals tot(p.b, w.tot, 1, false, s);
+  split_merge<KeyT, false>(SrcPack<KeyT>{coords, pp, status}, n, used_bits, p, w, 1, 0, tot, static_cast<KeyT*>(keys_out), perm_out, s);
   return tot.done("sort");
 }
 
@@ -1276,27 +1498,15 @@ int bucket_pack_sort(int key_bits, const int4* coords, int64_t n, const PackPara
 template <typename KeyT>
 static int mask_unique_t(const void* keys_in, int64_t n, const LevelJob* jobs, int n_levels, int used_bits, void* ws, size_t ws_pitch,
                          const StreamId& s) {
-  const BucketPlan p = bucket_plan(n, used_bits, true);
-  const Ws<KeyT> w = carve<KeyT>(ws, n);
+  const SplitPlan p = split_plan(n, used_bits, true);
+  const SplitWs<KeyT, true> w = carve_split<KeyT, true>(ws, n, p);
   SrcMasks<KeyT> src;
   LevelOut<KeyT> lo;
   batch_args(keys_in, jobs, n_levels, &src, &lo);
-  Totals tot(p, w.fstart, ws_pitch, n_levels, true, s);
-  partition<KeyT, true, false>(src, n, p, w, n_levels, ws_pitch, tot, s);
-  // the sorted keys (with gaps) go to keys0, which is free again by now
-  const int n_part = static_cast<int>((n + BS_PART - 1) / BS_PART), n_chunk = static_cast<int>((n + BS_CHUNK - 1) / BS_CHUNK);
-  if (n >= BS_RANK_LDS_N) {
-    hipLaunchKernelGGL((bs_rank_lds_kernel<KeyT, true, false>), dim3(static_cast<int>((n + BS_LP - 1) / BS_LP), n_levels), dim3(BS_LT), 0, s,
-                       w.keys1, static_cast<const int32_t*>(nullptr), w.win, static_cast<int>(n), w.n_kept, p.shift, p.n_bin, w.keys0,
-                       static_cast<int32_t*>(nullptr), w.bits, w.ccnt, w.rest_count, w.rest, ws_pitch);
-    hipLaunchKernelGGL((bs_rank_rest_kernel<KeyT, true, false>), dim3(BS_REST_WG, n_levels), dim3(BS_THREADS), 0, s, w.rest_count, w.rest,
-                       w.keys1, static_cast<const int32_t*>(nullptr), w.win, static_cast<int>(n), w.n_kept, w.keys0,
-                       static_cast<int32_t*>(nullptr), w.bits, w.ccnt, ws_pitch);
-  } else
-    hipLaunchKernelGGL(bs_rank_unique_kernel<KeyT>, dim3(n_part, n_levels), dim3(BS_THREADS), 0, s, w.keys1, w.win, w.n_kept, w.keys0,
-                       w.bits, w.ccnt, ws_pitch);
-  hipLaunchKernelGGL(bs_compact_kernel<KeyT>, dim3(n_chunk, n_levels), dim3(BS_THREADS), 0, s, w.keys0, w.bits, w.ccnt, w.n_kept, lo,
-                     ws_pitch, tot.to_clear(), tot.pitch, p.n_bin);
+  Totals tot(p.b, nullptr, n_levels, true, s);
+  split_merge<KeyT, true>(src, n, used_bits, p, w, n_levels, ws_pitch, tot, w.part, nullptr, s);
+  hipLaunchKernelGGL(bs_compact_kernel<KeyT>, dim3(p.n_share, n_levels), dim3(BS_THREADS), 0, s, w.part, w.out_at, w.out_n, lo, ws_pitch,
+                     tot.kept ? tot.p : nullptr, tot.pitch, p.b.n_bin);
   return tot.done("downsample");
 }
 

@@ -200,9 +200,8 @@ static int downsample_t(const void* src, int64_t n, const PackInfo& pi, int m, L
   return rc;
 }
 
-// Up to BS_MAX_LEVELS levels of one key array.  They share every launch where the library's own sort runs (a level's
-// five launches are bound by their launch and their dependent round trips at the sizes of a network: the four levels of
-// 120 k voxels took 20 launches and 110 us one after the other).
+// Up to BS_MAX_LEVELS levels of one key array.  They share every launch where the library's own sort runs (its launches
+// are bound by their dependent round trips at the sizes of a network).
 static int downsample_batch(const void* src, int64_t n, const PackInfo& pi, const int* m, int count, Level** lv, const StreamId& s) {
   const bool bucket = use_bucket_sort(n), small = n > 0 && n < BS_MIN_N;
   if (!bucket && !small) {

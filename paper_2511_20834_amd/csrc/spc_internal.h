@@ -223,24 +223,23 @@ __device__ inline KeyT pack_key(const int4 c, const PackParams& p, int32_t* stat
 #endif
 
 // ---------------------------------------------------------------- bucket sort (own kernels)
-constexpr int BS_MAX_WG = 128;      // workgroups of the count / scatter passes (3 * 10^6 keys, pack + sort: 128 89 us, 192 96, 256
-                                    // 100: every workgroup adds a row to the count table, which is read twice)
+constexpr int BS_MAX_WG = 128;      // workgroups of the count / scatter passes of recorded sorts with a column scan
 constexpr int BS_MAX_BIN_BITS = 14;
 constexpr int BS_MAX_BIN = 1 << BS_MAX_BIN_BITS;  // fine bins (top used key bits)
-// Sizes of the partitioning sort; below: one workgroup in LDS; above: rocPRIM (with 16384 bins at most, the windows of
-// the rank pass outgrow its LDS beyond that).  3 * 10^6 keys: pack + sort 89 us against 177 us with rocPRIM.
+// Sizes of the partitioning sort; below: one workgroup in LDS; above: rocPRIM (the split's regions and bins are sized for no more).
+// 3 * 10^6 keys: pack + sort 66 us against 177 us with rocPRIM.
 constexpr int64_t BS_MIN_N = 4096, BS_MAX_N = 8192 * 1024;
+constexpr int64_t BS_LARGE_N = 600000;  // recorded sorts of fewer keys: in launches that count, scatter and rank
 inline bool use_bucket_sort(int64_t n) { return n >= BS_MIN_N && n <= BS_MAX_N; }
-// Keys up to which the count pass adds its counts to the bins' totals, and how many a workgroup takes then.  Pack + sort, us, column
-// scan with 4096 keys per workgroup / this: LiDAR 20 k 16.2 / 13.3, 50 k 19.3 / 15.4, 120 k 25.2 / 20.5, 180 k 29.9 / 25.4; indoor 240 k
-// 34.8 / 31.7; random 300 k 35.4 / 30.3, 500 k 44.5 / 36.0.  Beyond, the table of 16384 bins would outgrow what is sorted.
+// Keys up to which the first pass adds its counts to the bins' totals, and how many a workgroup takes then.  Beyond, the additions
+// (some 35 per ns, and hardly two keys of a workgroup share a bin) would take longer than a launch that sums the table's columns.
 constexpr int64_t BS_ADD_N = 524288, BS_MID_N = 200000, BS_SHORT_N = 65536;
 constexpr int BS_ADD_SHARE = 2048, BS_SHORT_SHARE = 1024;
-// Up to so many workgroups the scatter pass sums their counts itself where the totals would have to be cleared first: a launch
+// Up to so many workgroups their counts are summed where they are read, where totals would have to be cleared first: a launch
 // less, but every workgroup reads the whole table.  Replayed pack + sort, us, cleared / summed: 4.2 k 20.8 / 17.2, 14 k 21.1 / 18.3, 33 k
-// (32 workgroups) 22.4 / 20.5, 40 k 23.6 / 24.1, 60 k 24.0 / 27.8; with a kept block 11.7, 12.1, 13.3, 14.7, 14.8 (replays start 5 us later).
+// (32 workgroups) 22.4 / 20.5, 40 k 23.6 / 24.1, 60 k 24.0 / 27.8.
 constexpr int BS_SUM_WG = 32;
-constexpr int BS_PART = 64;         // keys per rank workgroup
+constexpr int BS_PART = 64;         // keys per rank workgroup (recorded sorts)
 constexpr int BS_PAD_KEYS = 32;     // all-ones keys kept behind the scattered keys
 struct BucketPlan {
   int n_wg, per, shift, n_bin;
@@ -248,8 +247,9 @@ struct BucketPlan {
 };
 BucketPlan bucket_plan(int64_t n, int used_bits, bool unique);
 size_t bucket_sort_ws_bytes(int key_bits, int64_t n);
-// coords -> sorted keys (+ permutation); enqueues three kernels (count, scatter, rank), or four with the column scan of large inputs
-// or, where there is no cleared block for the totals of more than BS_SUM_WG workgroups, with their clearing.  Asks for no device memory.
+// coords -> sorted keys (+ permutation); enqueues two kernels (split, merge), three above BS_ADD_N keys (bins' starts) or where
+// there is no cleared block for the totals of more than BS_SUM_WG workgroups (their clearing), and one more where they are recorded
+// (below BS_LARGE_N keys: count, scatter and rank).  Asks for no device memory.
 int bucket_pack_sort(int key_bits, const int4* coords, int64_t n, const PackParams& pp, int used_bits, int32_t* status,
                      void* keys_out, int32_t* perm_out, void* ws, const StreamId& s);
 // One level to produce: the sorted distinct values of keys_in & mask, and their count.
@@ -259,7 +259,7 @@ struct LevelJob {
   void* keys_out;
   int32_t* count;
 };
-// n_levels <= BS_MAX_LEVELS levels of the same keys by the same five launches; level y works in ws + y * ws_pitch
+// n_levels <= BS_MAX_LEVELS levels of the same keys by the same three or four launches; level y works in ws + y * ws_pitch
 int bucket_mask_unique(int key_bits, const void* keys_in, int64_t n, const LevelJob* jobs, int n_levels, int used_bits, void* ws,
                        size_t ws_pitch, const StreamId& s);
 

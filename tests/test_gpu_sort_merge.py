@@ -1,0 +1,92 @@
+"""The sort's merge pass where its workgroups' shares are uneven: bins of more keys than the LDS holds, repeated and rejected rows, empty
+stretches of the key space, and the sizes at which shares and kernels change."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2511_20834_amd import binding as B
+
+from gpu_common import fit_desc, keys_to_u64
+
+pytestmark = pytest.mark.gpu
+
+
+def _dense(n, dims, seed, far):
+    """n voxels of a box, all but a few of them in a few bins: one voxel lies `far` away."""
+    lin = np.random.default_rng(seed).choice(int(np.prod(dims)), size=n - 1, replace=False)
+    c = np.stack([np.zeros(n - 1, np.int64), lin // (dims[1] * dims[2]), lin // dims[2] % dims[1], lin % dims[2]], 1)
+    return np.random.default_rng(seed + 1).permutation(np.concatenate([c, [[0, *far]]])).astype(np.int32)
+
+
+def _check(c, desc):
+    keys, perm = B.spc_pack_coords(torch.from_numpy(c).cuda(), desc)
+    k = keys_to_u64(keys)
+    assert np.all(k[1:] > k[:-1])
+    assert np.array_equal(perm.cpu().numpy(), np.lexsort((c[:, 3], c[:, 2], c[:, 1])))
+    m = B.spc_build_kmap(keys, desc, 3, 1, 2, 0, B.LAYOUT_OS)
+    coarse = np.unique(c[:, 1:] // 2, axis=0)
+    assert m.n_out == len(coarse)
+    got = m.out_keys()
+    m.destroy()
+    half = np.concatenate([np.zeros((len(coarse), 1), np.int64), 2 * coarse], 1).astype(np.int32)
+    half = half[np.lexsort((half[:, 3], half[:, 2], half[:, 1]))]
+    want = keys_to_u64(B.spc_pack_coords(torch.from_numpy(half).cuda(), desc)[0])
+    assert np.array_equal(got, want)
+
+
+# (a merging workgroup holds 2048 keys up to 200 k of them, then 4096)
+@pytest.mark.parametrize("n,dims,far", [
+    (20_000, (2, 150, 150), (4000, 4000, 200)),    # one bin holds nearly everything
+    (20_000, (24, 30, 30), (2000, 10, 10)),        # bins of about 1000
+    (150_000, (2, 400, 300), (1000, 1000, 300)),   # many rounds of the workgroup that owns the bin
+    (260_000, (3, 500, 400), (4000, 4000, 400)),
+    (600_001, (4, 700, 400), (4000, 4000, 400)),   # above the sizes whose totals are added up
+])
+@pytest.mark.parametrize("key_bits", [0, 64])
+def test_bins_beyond_the_lds(n, dims, far, key_bits):
+    c = _dense(n, dims, n, far)
+    _check(c, fit_desc(c, [(3, 1, 2)], key_bits))
+
+
+@pytest.mark.parametrize("n", [4096, 5000, 70_000, 230_000, 524_289, 1_300_001])
+@pytest.mark.parametrize("key_bits", [0, 64])
+def test_two_distant_clusters(n, key_bits):
+    a, b = _dense(n // 2, (100, 120, 130), n, (99, 0, 0)), _dense(n - n // 2, (90, 110, 150), n + 1, (0, 0, 149))
+    a, b = np.unique(a, axis=0), np.unique(b, axis=0)
+    b[:, 1:3] += 1800
+    c = np.random.default_rng(n).permutation(np.concatenate([a, b])).astype(np.int32)
+    _check(c, fit_desc(c, [(3, 1, 2)], key_bits))
+
+
+@pytest.mark.parametrize("n", [4096, 30_000, 300_000, 700_000])
+@pytest.mark.parametrize("key_bits", [0, 64])
+def test_repeated_and_rejected_rows(n, key_bits):
+    """Not a valid cloud, but the permutation stays a complete one, keys ascend and rejected rows come last."""
+    rng = np.random.default_rng(n)
+    c = np.concatenate([np.zeros((n, 1), np.int64), rng.integers(0, 12, (n, 3))], 1).astype(np.int32)  # 1728 distinct voxels
+    desc = fit_desc(c, [(3, 1, 2)], key_bits)
+    bad = rng.permutation(n)[:n // 3]
+    c[bad, 2] = 1 << 20
+    keys, perm = B.spc_pack_coords(torch.from_numpy(c).cuda(), desc)
+    k, p = keys_to_u64(keys), perm.cpu().numpy()
+    assert np.array_equal(np.sort(p), np.arange(n))
+    assert np.all(k[1:] >= k[:-1])
+    last = np.uint64(0xffffffffffffffff) if desc.key_bits == 64 else np.uint64(0xffffffff)
+    assert np.all(k[n - len(bad):] == last) and np.all(k[:n - len(bad)] < last)
+    assert np.array_equal(np.sort(p[n - len(bad):]), np.sort(bad))
+    s = c[p[:n - len(bad)]].astype(np.int64)
+    lin = (s[:, 1] * 4096 + s[:, 2]) * 4096 + s[:, 3]
+    assert np.all(lin[1:] >= lin[:-1])
+
+
+@pytest.mark.parametrize("n", [4097, 40_000])
+def test_on_the_threads_own_stream(n):
+    """No totals are kept there: the table is summed, or the totals cleared first."""
+    c = _dense(n, (60, 80, 90), n, (400, 5, 5))
+    desc = fit_desc(c, [(3, 1, 2)])
+    coords = torch.from_numpy(c).cuda()
+    torch.cuda.synchronize()
+    keys, perm = B.spc_pack_coords(coords, desc, stream=2)  # (hipStreamPerThread)
+    torch.cuda.synchronize()
+    assert np.all(np.diff(keys_to_u64(keys).astype(np.int64)) > 0)
+    assert np.array_equal(perm.cpu().numpy(), np.lexsort((c[:, 3], c[:, 2], c[:, 1])))
