@@ -1,0 +1,34 @@
+"""Weight-stationary lists: every offset's pairs as the search compacts them per tile and the fill pass moves them, against the oracle's
+map, at the sizes where a tile, a fill workgroup's tiles or the length of the tiles ends."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2511_20834_amd import binding as B
+
+from gpu_common import fit_desc
+
+pytestmark = pytest.mark.gpu
+
+
+def _cloud(n, density, seed):
+    side = int(round((n / density) ** (1 / 3))) + 2
+    lin = np.random.default_rng(seed).choice(side ** 3, size=n, replace=False)
+    return np.stack([np.zeros(n, np.int64), lin // (side * side), lin // side % side, lin % side], 1).astype(np.int32)
+
+
+# (tiles of 64 rows, four to a fill workgroup above 6144 counts; of 128 from 150 k rows on, 256 from 400 k; K = 7 has more offsets than
+# a workgroup has threads)
+@pytest.mark.parametrize("K,n,density", [(2, 65, 0.3), (3, 64, 0.5), (3, 14_592, 0.3), (3, 14_593, 0.05), (3, 14_785, 0.9), (5, 3200, 0.02),
+                                         (5, 3201, 0.7), (5, 3393, 0.05), (7, 1500, 0.3), (3, 150_001, 0.1), (3, 400_001, 0.05)])
+@pytest.mark.parametrize("key_bits", [0, 64])
+def test_lists(K, n, density, key_bits):
+    c, _ = oracle.sort_coords(_cloud(n, density, n + K))
+    desc = fit_desc(c, [(K, 1, 1)], key_bits)
+    keys, perm = B.spc_pack_coords(torch.from_numpy(c).cuda(), desc)
+    ref = oracle.triples(oracle.layer(c, K, 1, 1)[1])
+    for layout in (B.LAYOUT_WS, B.LAYOUT_BOTH):
+        m = B.spc_build_kmap(keys, desc, K, 1, 1, 0, layout, in_perm=perm)
+        assert np.array_equal(m.export_triples(B.LAYOUT_WS), ref)
+        m.destroy()
