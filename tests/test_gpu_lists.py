@@ -1,5 +1,5 @@
 """Weight-stationary lists: every offset's pairs as the search compacts them per tile and the fill pass moves them, against the oracle's
-map, at the sizes where a tile, a fill workgroup's tiles or the length of the tiles ends."""
+map, at the sizes where a tile, a round of the scan or the length of the tiles ends."""
 import numpy as np
 import pytest
 import torch
@@ -18,10 +18,11 @@ def _cloud(n, density, seed):
     return np.stack([np.zeros(n, np.int64), lin // (side * side), lin // side % side, lin % side], 1).astype(np.int32)
 
 
-# (tiles of 64 rows, four to a fill workgroup above 6144 counts; of 128 from 150 k rows on, 256 from 400 k; K = 7 has more offsets than
-# a workgroup has threads)
+# (tiles of 64 rows, scanned by a kernel of its own above 6144 counts, 4096 of an offset at a time; of 128 rows from 150 k on, 256 from 400 k;
+# K = 7 has more offsets than a fill workgroup has threads)
 @pytest.mark.parametrize("K,n,density", [(2, 65, 0.3), (3, 64, 0.5), (3, 14_592, 0.3), (3, 14_593, 0.05), (3, 14_785, 0.9), (5, 3200, 0.02),
-                                         (5, 3201, 0.7), (5, 3393, 0.05), (7, 1500, 0.3), (3, 150_001, 0.1), (3, 400_001, 0.05)])
+                                         (5, 3201, 0.7), (5, 3393, 0.05), (7, 1500, 0.3), (3, 150_001, 0.1), (3, 400_001, 0.05),
+                                         (5, 262_145, 0.01)])
 @pytest.mark.parametrize("key_bits", [0, 64])
 def test_lists(K, n, density, key_bits):
     c, _ = oracle.sort_coords(_cloud(n, density, n + K))
