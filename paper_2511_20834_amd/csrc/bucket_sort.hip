@@ -1,6 +1,6 @@
 // Sort of packed voxel keys for the cloud sizes of this workload (thousands to a few million
 // keys), without look-back spinning: every workgroup orders its share of the keys by the top `fb` used key bits ("bins") in LDS, and
-// further workgroups take whole bins from all shares and put them in order (two launches, see split + merge).
+// further workgroups take whole bins from all shares and put them in order (two launches, see split + merge; crowded bins are shared).
 // Fewer keys than BS_MIN_N are sorted by one workgroup.  Recorded sorts (stream capture) of up to BS_LARGE_N keys go another
 // way, in three launches or four:
 //
@@ -97,10 +97,11 @@ __device__ inline T* level_ws(T* p, size_t ws_pitch) {
 //           table's columns, which gives every bin's place in the sorted sequence, and from these every merging workgroup's bins;
 //   merge   workgroup p takes the whole bins that start among sorted positions p * q .. p * q + q - 1: one contiguous piece of every
 //           region.  It fetches them, orders them in LDS (a second split by their next key bits, then counting inside that split's
-//           bins) and stores them, lane next to lane;
+//           bins) and stores them, lane next to lane.  A bin of more keys than fit the LDS beside others is shared by the workgroups
+//           whose positions it covers: each reads all of it, but takes only the second bins that start among its positions (crowd);
 //   compact (levels) equal keys are all in one workgroup, which drops them; this kernel closes the gaps between the workgroups.
 //
-// A bin has one owner, so no windows overlap and nothing is compared twice, and no key is a memory transaction of its own on its
+// No windows overlap and nothing is compared twice, and no key is a memory transaction of its own on its
 // way.  What bounds it up to half a million keys: two launches, three dependent round trips of the merge (totals, pieces, keys) and
 // fetching its instructions, which run once: unrolled eight and sixteen times the same merge took 17 us where this one takes 8.6,
 // so loops over bins and regions stay rolled and a thread has two keys.  From 10^6 keys on: the coordinates (split 30 us at 3 * 10^6),
@@ -321,9 +322,10 @@ __global__ __launch_bounds__(BS_THREADS) void bs_clear_kernel(int32_t* __restric
 }
 
 // The bins of merging workgroup p: from bin `first` on, which starts at sorted position `start`, to bin `last`, which ends at `end` and is
-// not empty.  A workgroup whose `start` lies behind its positions, in a bin of an earlier one, has none.
+// not empty.  A workgroup whose `start` lies behind its positions, in a bin of an earlier one, has none.  `lead` is where the bin starts that
+// ends at `start` (if that is not the workgroup's first position), `tail` where `last` does.
 struct BsShare {
-  int32_t first, start, last, end;
+  int32_t first, start, lead, last, end, tail;
 };
 
 // 128 bins per workgroup; a wave sums a sixteenth of the table's rows, 256 bytes at a time.
@@ -365,11 +367,11 @@ __global__ __launch_bounds__(BS_WIDE) void bs_starts_kernel(const uint16_t* __re
     const int behind = f + 1 < f1 ? j + 1 : BS_START_BINS;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) end += part[w][behind];
-    if (f == 0) share[0].first = 0, share[0].start = 0, *n_kept = total;
+    if (f == 0) share[0].first = 0, share[0].start = 0, share[0].lead = 0, *n_kept = total;
     if (s < end) {  // not empty
       const int p = s / q;
-      if (end >= (p + 1) * q || end == total) share[p].last = f, share[p].end = end;
-      for (int p1 = p + 1; p1 < n_share && p1 * q <= end; ++p1) share[p1].first = f + 1, share[p1].start = end;
+      if (end >= (p + 1) * q || end == total) share[p].last = f, share[p].end = end, share[p].tail = s;
+      for (int p1 = p + 1; p1 < n_share && p1 * q <= end; ++p1) share[p1].first = f + 1, share[p1].start = end, share[p1].lead = s;
     }
   }
 }
@@ -396,6 +398,15 @@ struct MergeArgs {
   size_t ws_pitch;
 };
 
+// A kernel's only argument, to be loaded anew where this stands.
+template <typename Args>
+__device__ inline const Args& bs_args_anew(const Args&) {
+  using P = const Args __attribute__((address_space(4)))*;
+  P p = (P)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const Args*)p;
+}
+
 // The part of a workgroup's LDS work that does not depend on where the keys come from: `count` keys (element u * BS_MT + t in
 // k[u], source indices in v[u] where they are apart) are put in order in L.key (L.row).  Their second bins are (key - base) >> ss,
 // below BS_NSUB; a key above lim (of a rejected row) has lim's.  L.hist is zero before.
@@ -414,9 +425,11 @@ struct BsOrder {
     int seg[64];
     int32_t pre[BS_MAX_SPLIT];
     int32_t src[BS_MAX_SPLIT];
-    int first, start, last, end, wave_last[WAVES];
+    int first, start, lead, last, end, tail, wave_last[WAVES];
     int taken, done;
   };
+  // A value that all lanes have, to a scalar register: 32-bit keys leave room there, and by them two workgroups share a CU.
+  __device__ static int uniform(int v) { return sizeof(KeyT) == 4 ? __builtin_amdgcn_readfirstlane(v) : v; }
   __device__ static void clear(Lds& L) { reinterpret_cast<int4*>(L.hist)[threadIdx.x] = make_int4(0, 0, 0, 0); }
   // exclusive sums of the second bins' counts in place
   __device__ static void scan(Lds& L) {
@@ -427,8 +440,7 @@ struct BsOrder {
     *h = make_int4(x, x + c.x, x + c.x + c.y, x + c.x + c.y + c.z);
     if (threadIdx.x == 0) L.hist[BS_NSUB] = total;
   }
-  __device__ static void order(Lds& L, Elem (&k)[KPT], int32_t (&v)[KPT], int count, KeyT base, KeyT lim, int ss) {
-    const int t = threadIdx.x;
+  __device__ static void order(Lds& L, Elem (&k)[KPT], int32_t (&v)[KPT], int count, KeyT base, KeyT lim, int ss, const int t) {
     auto second = [&](Elem e) { return static_cast<int>((min(F::key(e), lim) - base) >> ss); };
     int r[KPT];
 #pragma unroll
@@ -481,8 +493,7 @@ struct BsOrder {
     __syncthreads();
   }
   // The ordered keys leave: to `at` on; returns how many (levels: the distinct ones).
-  __device__ static int store(Lds& L, const MergeArgs<KeyT, DEDUP>& a, KeyT* out_k, int count, int at) {
-    const int t = threadIdx.x;
+  __device__ static int store(Lds& L, const MergeArgs<KeyT, DEDUP>& a, KeyT* out_k, int count, int at, const int t) {
     if constexpr (!DEDUP) {
 #pragma unroll
       for (int u = 0; u < KPT; ++u) {
@@ -515,10 +526,171 @@ struct BsOrder {
       return distinct;
     }
   }
+  // Bins f0 .. f1, which start at sorted position s: one shared between workgroups, or the others of a workgroup that has a part of one (see
+  // bs_merge_kernel).  This workgroup puts those of their second bins in order that start among positions x .. stop - 1 (x is s or its
+  // first position).  A second bin of more than `most` keys is shared in its turn and split again, by the next twelve bits; where nothing
+  // is left to split its keys are equal, and are taken by their source indices, or (levels) all but one dropped by the workgroup they start at.
+  // Every level reads the bins once to count, and what is taken is picked out in one more pass: no workgroup waits for another, but keys in
+  // one bin are read as often as it has workgroups.  us of pack + sort, and of a level with its map, in brackets where the bin's owner
+  // sorted it alone, reading it again for each 2048 keys (64-bit keys; spread over the bins 120 k voxels take 15 and 25):
+  // a wall of 3 k in 20 k voxels, one plane of 12/12/8 bits in 32-bit keys, 20, 30 (34, 50); of 20 k in 120 k 28, 41 (338, 389);
+  // 20 k voxels and an outlier, all in one bin, 34, 38 (355, 441); 120 k 80, 128 (10 983, 12 490); 3 * 10^6 1660, 2680; in two bins by x
+  // 120 k 82, 89 (12 890, 10 370); 600 k 650, 275; 3 * 10^6 8100, 12 300.
+  // Returns the number of keys that left; the first went to *at.
+  __device__ __attribute__((always_inline)) static int crowd(Lds& L, const MergeArgs<KeyT, DEDUP>& args, int f0, int f1, int s, int x, int stop,
+                                                             int kept, int* at) {
+    int t = threadIdx.x;  // (what is derived from it is not to be kept in registers for other trips)
+    asm volatile("" : "+v"(t));
+    const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    __syncthreads();
+    if (t < args.n_wg) {
+      const uint16_t* row = (DEDUP ? level_ws(args.off, args.ws_pitch) : args.off) + int64_t(t) * bs_off_pitch(args.n_bin);
+      const int from = row[f0];
+      L.src[t] = t * args.per + from;
+      L.pre[t] = row[f1 + 1] - from;
+    }
+    auto log2_up = [](unsigned n) { return n > 1 ? 32 - __clz(n - 1) : 0; };
+#pragma unroll 1
+    while (x < stop) {
+      const auto& a = bs_args_anew(args);  // (kept in scalar registers over all of this, the arguments would not fit)
+      const int most = CAP - a.q;
+      const bool over = f1 == a.n_bin - 1 && a.used_bits < int(8 * sizeof(KeyT));  // all-ones keys as in bs_merge_kernel
+      const KeyT base = KeyT(f0) << a.shift, lim = over ? KeyT(f1 + 1) << a.shift : ~KeyT(0);
+      // all keys of the bins, a wave to a piece, four loads in flight: fn(key, its place in the regions, whether there is one)
+      auto each = [&](auto fn) __attribute__((always_inline)) {
+#pragma unroll 1
+        for (int w = wave; w < a.n_wg; w += WAVES) {
+          const int len = __builtin_amdgcn_readfirstlane(L.pre[w]), src = __builtin_amdgcn_readfirstlane(L.src[w]);
+#pragma unroll 1
+          for (int i0 = 0; i0 < len; i0 += 256) {
+            Elem e[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) e[u] = (DEDUP ? level_ws(a.recs, a.ws_pitch) : a.recs)[src + min(i0 + 64 * u + lane, len - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) fn(e[u], src + i0 + 64 * u + lane, i0 + 64 * u + lane < len);
+          }
+        }
+      };
+      KeyT low = base;   // the second bins are [low, low + 4096 << sh), from position ns on, or with `by_row` the rows of key `low`
+      uint32_t row0 = 0;
+      bool by_row = false;
+      int sh = max(0, a.shift + log2_up(f1 + 1 - f0 + (over ? 1 : 0)) - 12), ns = s;
+#pragma unroll 1
+      for (;;) {
+        auto second = [&](Elem e, int place, bool ok) __attribute__((always_inline)) {  // second bin, or -1
+          const KeyT key = min(F::key(e), lim);
+          if (!ok || key < low) return -1;
+          KeyT d = key - low;
+          if (!DEDUP && by_row) {
+            uint32_t row;
+            if constexpr (F::ROWS) row = static_cast<uint32_t>(a.rows[place]);
+            else row = static_cast<uint32_t>(e);
+            if (d != 0 || row < row0) return -1;
+            d = row - row0;
+          }
+          d >>= sh;
+          return d < KeyT(BS_NSUB) ? static_cast<int>(d) : -1;
+        };
+        __syncthreads();
+        clear(L);
+        __syncthreads();
+        each([&](Elem e, int place, bool ok) __attribute__((always_inline)) {
+          const int b = second(e, place, ok);
+          const unsigned long long some = __ballot(b >= 0);
+          if (some == 0ull) return;
+          const int head = __builtin_ctzll(some);
+          if (__ballot(b == __builtin_amdgcn_readlane(b, head)) == some) {  // (crowded keys: additions to one place come one by one)
+            if (lane == head) atomicAdd(&L.hist[b], __popcll(some));
+          } else if (b >= 0) {
+            atomicAdd(&L.hist[b], 1);
+          }
+        });
+        __syncthreads();
+        scan(L);
+        if (t == 0) L.taken = 0;
+        __syncthreads();
+        auto starts = [&](int b) __attribute__((always_inline)) { return ns + uniform(L.hist[b]); };
+        const int ne = starts(BS_NSUB);
+        static_assert(BS_NSUB == 64 * 64, "two steps of a wave");
+        auto holder = [&](int pos) __attribute__((always_inline)) {  // the second bin that holds position pos
+          const int b = 64 * (63 - __builtin_clzll(__ballot(ns + L.hist[64 * lane] <= pos)));
+          return b + 63 - __builtin_clzll(__ballot(ns + L.hist[b + lane] <= pos));
+        };
+        int b = holder(x), bs = starts(b), be = starts(b + 1);
+        if (bs < x && be - bs <= most) {  // an earlier workgroup's
+          x = be;
+          if (x >= min(stop, ne)) break;
+          b = holder(x), bs = x, be = starts(b + 1);
+        }
+        if (be - bs > most) {
+          ns = bs;
+          if (by_row) row0 += static_cast<uint32_t>(b) << sh;
+          else low += KeyT(b) << sh;
+          if (sh > 0) {
+            sh = max(0, sh - 12);
+            continue;
+          }
+          if constexpr (!DEDUP) {  // equal keys
+            by_row = true;
+            sh = max(0, log2_up(a.n_wg * a.per) - 12);
+            continue;
+          } else {
+            if (bs == x) {
+              if (kept == 0) *at = x;
+              each([&](Elem e, int place, bool ok) __attribute__((always_inline)) {
+                if (ok && min(F::key(e), lim) == low) level_ws(a.out_k, a.ws_pitch)[*at + kept] = F::key(e);  // (one value)
+              });
+              ++kept;
+            }
+            x = be;
+            break;
+          }
+        }
+        int b1 = holder(min(stop, ne) - 1);  // (not empty)
+        if (starts(b1 + 1) - starts(b1) <= most) ++b1;
+        const int x1 = starts(b1), count = x1 - x;
+        each([&](Elem e, int place, bool ok) __attribute__((always_inline)) {
+          const int to_bin = second(e, place, ok);
+          const bool mine = to_bin >= b && to_bin < b1;
+          const unsigned long long some = __ballot(mine);
+          if (some == 0ull) return;
+          const int head = __builtin_ctzll(some);
+          int to = 0;
+          if (lane == head) to = atomicAdd(&L.taken, __popcll(some));
+          to = __builtin_amdgcn_readlane(to, head) + __popcll(some & ((1ull << lane) - 1ull));
+          if (mine) {
+            L.key[to] = e;
+            if constexpr (F::ROWS) L.row[to] = a.rows[place];
+          }
+        });
+        __syncthreads();
+        Elem k[KPT] = {};
+        int32_t v[KPT] = {};
+        int tt = t;  // (as t)
+        asm volatile("" : "+v"(tt));
+#pragma unroll
+        for (int u = 0; u < KPT; ++u)
+          if (u * BS_MT + tt < count) {
+            k[u] = L.key[u * BS_MT + tt];
+            if constexpr (F::ROWS) v[u] = L.row[u * BS_MT + tt];
+          }
+        clear(L);
+        __syncthreads();
+        order(L, k, v, count, by_row ? low : low + (KeyT(b) << sh), lim, by_row ? 0 : max(0, sh + log2_up(b1 - b) - 12), tt);
+        if (kept == 0) *at = x;
+        kept += store(L, a, DEDUP ? level_ws(a.out_k, a.ws_pitch) : a.out_k, count, DEDUP ? *at + kept : x, tt);
+        x = x1;
+        break;
+      }
+    }
+    return kept;
+  }
 };
 
+// (32-bit keys: two workgroups to a CU, for which a wave may have 64 vector and 80 scalar registers; with one, 3 * 10^6 keys 28 -> 39 us,
+// 150 k 16 -> 20 in all)
 template <typename KeyT, bool DEDUP, int KPT, int FROM>
-__global__ __launch_bounds__(BS_MT) void bs_merge_kernel(const MergeArgs<KeyT, DEDUP> a) {
+__global__ __launch_bounds__(BS_MT, sizeof(KeyT) == 4 ? 8 : 4) void bs_merge_kernel(const MergeArgs<KeyT, DEDUP> a) {
   using O = BsOrder<KeyT, DEDUP, KPT>;
   using F = typename O::F;
   using Elem = typename F::Elem;
@@ -528,15 +700,14 @@ __global__ __launch_bounds__(BS_MT) void bs_merge_kernel(const MergeArgs<KeyT, D
   const uint16_t* off = DEDUP ? level_ws(a.off, a.ws_pitch) : a.off;
   KeyT* out_k = DEDUP ? level_ws(a.out_k, a.ws_pitch) : a.out_k;
   const int pitch = bs_off_pitch(a.n_bin), lo = p * a.q, hi = lo + a.q;
-  int first, start, last, end;  // as in BsShare
+  int first, start, lead, last, end, tail, total;  // as in BsShare
   int32_t* tot = nullptr;
   int came = 0;
   if constexpr (FROM == BS_STARTS) {
     const BsShare* share = DEDUP ? level_ws(a.share, a.ws_pitch) : a.share;
-    const int total = *(DEDUP ? level_ws(a.n_kept, a.ws_pitch) : a.n_kept);
+    total = *(DEDUP ? level_ws(a.n_kept, a.ws_pitch) : a.n_kept);
     const BsShare s = share[p];
-    first = s.first, start = s.start, last = s.last, end = s.end;
-    if (lo >= total || start >= min(hi, total)) start = end = 0;
+    first = s.first, start = s.start, lead = s.lead, last = s.last, end = s.end, tail = s.tail;
     O::clear(L);
   } else {
     if constexpr (FROM == BS_TOTALS) tot = DEDUP ? level_ws(a.tot, a.tot_pitch) : a.tot;
@@ -558,8 +729,8 @@ __global__ __launch_bounds__(BS_MT) void bs_merge_kernel(const MergeArgs<KeyT, D
     };
     int4 c = fetch(4 * t), later = fetch(4 * (BS_MT + t));
     O::clear(L);
-    if (t == 0) L.first = 0, L.start = 0, L.end = -1;
-    int total = 0;
+    if (t == 0) L.first = 0, L.start = 0, L.lead = 0, L.end = -1;
+    total = 0;
 #pragma unroll 1
     for (int r0 = 0; r0 < a.n_bin; r0 += 4 * BS_MT) {
       const int f0 = r0 + 4 * t;
@@ -573,8 +744,8 @@ __global__ __launch_bounds__(BS_MT) void bs_merge_kernel(const MergeArgs<KeyT, D
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const int e = s + n4[j];
-          if (s < lo && lo <= e) L.first = f0 + j + 1, L.start = e;
-          if (s < hi && hi <= e) L.last = f0 + j, L.end = e;
+          if (s < lo && lo <= e) L.first = f0 + j + 1, L.start = e, L.lead = s;
+          if (s < hi && hi <= e) L.last = f0 + j, L.end = e, L.tail = s;
           s = e;
         }
       }
@@ -585,19 +756,33 @@ __global__ __launch_bounds__(BS_MT) void bs_merge_kernel(const MergeArgs<KeyT, D
       c = later;
     }
     __syncthreads();
-    first = L.first, start = L.start, last = L.last, end = L.end;
-    if (end < 0) {  // the last bins (uniform)
-      last = 0, end = total;
+    first = L.first, start = L.start, lead = L.lead, last = L.last, end = L.end, tail = L.tail;
+    if (end < 0) {  // the last bins (uniform), not behind this workgroup's positions
+      last = 0, end = tail = total;
       for (int w = 0; w < O::WAVES; ++w) last = max(last, L.wave_last[w]);
     }
-    if (lo >= total || start >= min(hi, total)) start = end = 0;
     // (the totals have been read)
     if (!DEDUP && a.clear && t == 0)
       came = __hip_atomic_fetch_add(a.arrived + (p % BS_ARRIVE) * BS_ARRIVE_PITCH, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  const int W = end - start;
-  int kept = 0;
-  if (W > 0) {
+  for (int* v : {&first, &start, &lead, &last, &end, &tail, &total}) *v = O::uniform(*v);
+  // A bin of more than `most` keys is shared: of its second bins a workgroup takes those that start among its positions, lo .. hi - 1.
+  // Without its part of shared bins (the first, or the last: most >= q) a workgroup's keys fit the LDS.
+  const int most = O::CAP - a.q;
+  const bool shared_lead = lo < total && start > lo && start - lead > most;
+  const bool none = lo >= total || start >= min(hi, total);
+  const bool shared_tail = !none && end - tail > most;
+  const int W = none ? 0 : end - start;
+  int kept = 0, at0 = start;
+  if (__builtin_expect(shared_lead || shared_tail, 0)) {
+#pragma unroll 1
+    for (int part = 0; part < 3; ++part) {
+      int f0 = first, f1 = shared_tail ? last - 1 : last, s = start, x = start, stop = none ? start : shared_tail ? tail : end;
+      if (part == 0) f0 = f1 = first - 1, s = lead, x = lo, stop = shared_lead ? min(hi, start) : lo;
+      if (part == 2) f0 = f1 = last, s = x = tail, stop = shared_tail ? hi : tail;
+      if (x < stop) kept = O::crowd(L, a, f0, f1, s, x, stop, kept, &at0);
+    }
+  } else if (W > 0) {
     // ---- the pieces of the regions, one per thread
     int from = 0, len = 0;
     if (t < a.n_wg) {
@@ -627,98 +812,19 @@ __global__ __launch_bounds__(BS_MT) void bs_merge_kernel(const MergeArgs<KeyT, D
     const int ss = max(0, a.shift + (bins > 1 ? 32 - __clz(bins - 1) : 0) - 12);
     Elem k[KPT];
     int32_t v[KPT];
-    if (__builtin_expect(W <= O::CAP, 1)) {
 #pragma unroll
-      for (int u = 0; u < KPT; ++u)
-        if (u * BS_MT + t < W) {
-          const int at = place(u * BS_MT + t);
-          k[u] = recs[at];
-          if constexpr (F::ROWS) v[u] = a.rows[at];
-        }
-      O::order(L, k, v, W, base, lim, ss);
-      kept = O::store(L, a, out_k, W, start);
-    } else {
-      // More keys than the LDS holds (of one bin: scenes that fill next to nothing of their key space).  They are read again and
-      // again: counted into second bins, then as many of these as fit are picked out and ordered as above.  A second bin that does
-      // not fit is split again; where nothing is left to split its keys are equal.
-      KeyT low = base;
-      int sh = ss, out = 0;
-      while (out < W) {
-        __syncthreads();
-        O::clear(L);
-        __syncthreads();
-        auto second = [&](Elem e) {  // second bin, or -1
-          const KeyT key = min(F::key(e), lim);
-          if (key < low) return -1;
-          const KeyT d = (key - low) >> sh;
-          return d < KeyT(BS_NSUB) ? static_cast<int>(d) : -1;
-        };
-        for (int i = t; i < W; i += BS_MT) {
-          const int b = second(recs[place(i)]);
-          if (b >= 0) atomicAdd(&L.hist[b], 1);
-        }
-        __syncthreads();
-        O::scan(L);
-        if (t == 0) L.taken = 0;
-        __syncthreads();
-        int fit = 0;  // second bins that fit together: hist ascends
-        for (int s = BS_NSUB; s > 0; s >>= 1)
-          if (fit + s <= BS_NSUB && L.hist[fit + s] <= O::CAP) fit += s;
-        const int count = L.hist[fit];
-        if (fit > 0) {
-          for (int i = t; i < W; i += BS_MT) {
-            const int at = place(i);
-            const Elem e = recs[at];
-            const int b = second(e);
-            if (b >= 0 && b < fit) {
-              const int to = atomicAdd(&L.taken, 1);
-              L.key[to] = e;
-              if constexpr (F::ROWS) L.row[to] = a.rows[at];
-            }
-          }
-          __syncthreads();
-#pragma unroll
-          for (int u = 0; u < KPT; ++u)
-            if (u * BS_MT + t < count) {
-              k[u] = L.key[u * BS_MT + t];
-              if constexpr (F::ROWS) v[u] = L.row[u * BS_MT + t];
-            }
-          O::clear(L);
-          __syncthreads();
-          if (count > 0) {
-            O::order(L, k, v, count, low, lim, sh);
-            kept += O::store(L, a, out_k, count, start + (DEDUP ? kept : out));
-          }
-          out += count;
-          low += KeyT(fit) << sh;
-          sh = ss;
-        } else if (sh > 0) {
-          sh = max(0, sh - 12);
-        } else {
-          const int many = L.hist[1];
-          for (int i = t; i < W; i += BS_MT) {
-            const int at = place(i);
-            const Elem e = recs[at];
-            if (second(e) != 0) continue;
-            if constexpr (DEDUP) {
-              if (atomicAdd(&L.taken, 1) == 0) out_k[start + kept] = F::key(e);
-            } else {
-              const int to = start + out + atomicAdd(&L.taken, 1);
-              out_k[to] = F::key(e);
-              if (a.out_v) a.out_v[to] = F::ROWS ? a.rows[at] : static_cast<int32_t>(e);
-            }
-          }
-          kept += DEDUP ? 1 : many;
-          out += many;
-          low += 1;
-          sh = ss;
-        }
+    for (int u = 0; u < KPT; ++u)
+      if (u * BS_MT + t < W) {
+        const int at = place(u * BS_MT + t);
+        k[u] = recs[at];
+        if constexpr (F::ROWS) v[u] = a.rows[at];
       }
-    }
+    O::order(L, k, v, W, base, lim, ss, t);
+    kept = O::store(L, a, out_k, W, start, t);
   }
   if constexpr (DEDUP) {
     if (t == 0) {
-      level_ws(a.out_at, a.ws_pitch)[p] = start;
+      level_ws(a.out_at, a.ws_pitch)[p] = at0;
       level_ws(a.out_n, a.ws_pitch)[p] = kept;
     }
   }

@@ -1,4 +1,4 @@
-"""The sort's merge pass where its workgroups' shares are uneven: bins of more keys than the LDS holds, repeated and rejected rows, empty
+"""The sort's merge pass where its workgroups' shares are uneven: bins that are shared between workgroups, repeated and rejected rows, empty
 stretches of the key space, and the sizes at which shares and kernels change."""
 import numpy as np
 import pytest
@@ -34,18 +34,84 @@ def _check(c, desc):
     assert np.array_equal(got, want)
 
 
-# (a merging workgroup holds 2048 keys up to 200 k of them, then 4096)
+# (up to 524 288 keys a bin of more than 1536 of them is shared, and a workgroup has two keys to a thread; beyond, 2048 and four)
 @pytest.mark.parametrize("n,dims,far", [
     (20_000, (2, 150, 150), (4000, 4000, 200)),    # one bin holds nearly everything
     (20_000, (24, 30, 30), (2000, 10, 10)),        # bins of about 1000
-    (150_000, (2, 400, 300), (1000, 1000, 300)),   # many rounds of the workgroup that owns the bin
+    (20_000, (30, 30, 30), (1 << 19, 1 << 19, 1 << 19)),  # second bins, and theirs, are split again
+    (150_000, (2, 400, 300), (1000, 1000, 300)),
     (260_000, (3, 500, 400), (4000, 4000, 400)),
-    (600_001, (4, 700, 400), (4000, 4000, 400)),   # above the sizes whose totals are added up
+    (524_288, (4, 700, 400), (4000, 4000, 400)),
+    (524_289, (4, 700, 400), (4000, 4000, 400)),
+    (600_001, (4, 700, 400), (4000, 4000, 400)),
 ])
 @pytest.mark.parametrize("key_bits", [0, 64])
 def test_bins_beyond_the_lds(n, dims, far, key_bits):
     c = _dense(n, dims, n, far)
     _check(c, fit_desc(c, [(3, 1, 2)], key_bits))
+
+
+# (a bin is a plane of x here)
+@pytest.mark.parametrize("n,planes,most,q", [(20_000, 2000, 1536, 512), (530_000, 16_000, 2048, 2048)])
+@pytest.mark.parametrize("key_bits", [0, 64])
+def test_bins_around_the_line(n, planes, most, q, key_bits):
+    sizes = [most - 1, most, most + 1, q - 1, 1, most + 1, q, q + 1, most + q]
+    x = np.concatenate([np.full(s, p) for p, s in enumerate(sizes)] + [np.full(most + 1, planes - 1), np.full(most, planes - 3)])
+    rest = np.random.default_rng(n).integers(len(sizes), planes - 3, size=n - len(x))
+    x = np.concatenate([x, rest])
+    yz = np.random.default_rng(n + 1).choice(300 * 200, size=n, replace=n > 300 * 200)
+    c = np.unique(np.stack([np.zeros(n, np.int64), x, yz // 200, yz % 200], 1), axis=0)
+    if len(c) < n:  # (the rows that met, in planes of their own)
+        i = np.arange(n - len(c))
+        c = np.concatenate([c, np.stack([0 * i, 20 + i // 50, 300 + 0 * i, i % 50], 1)])
+    _check(np.random.default_rng(n + 2).permutation(c).astype(np.int32), fit_desc(c, [(3, 1, 2)], key_bits))
+
+
+def _microseconds(f):
+    f()
+    start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    best = float("inf")
+    for _ in range(5):
+        start.record()
+        f()
+        f()
+        end.record()
+        end.synchronize()
+        best = min(best, 500 * start.elapsed_time(end))
+    return best
+
+
+@pytest.mark.parametrize("kind", ["wall", "outlier", "slab"])
+def test_crowded_bins_are_shared(kind):
+    """120 k voxels, many or all of them in one bin, against as many spread over the key space.  A crowded bin is 2 to 6 times the time
+    (levels: 2 to 7); with one workgroup to sort it, it was 24 to 900 times."""
+    n = 120_000
+    rng = np.random.default_rng(7)
+
+    def box(m, dims, at=(0, 0, 0)):
+        lin = rng.choice(int(np.prod(dims)), size=m, replace=False)
+        return np.stack([np.zeros(m, np.int64), at[0] + lin // (dims[1] * dims[2]), at[1] + lin // dims[2] % dims[1], at[2] + lin % dims[2]], 1)
+
+    spread = box(n, (2000, 2000, 100))
+    if kind == "wall":  # a sixth of the scene in one plane of x
+        c = np.concatenate([box(n // 6, (1, 1000, 200), (501, 0, 0)), box(n - n // 6, (500, 2000, 200))])
+    elif kind == "outlier":  # all of it but one voxel
+        c = np.concatenate([box(n - 1, (136, 136, 136)), [[0, 600_000, 0, 0]]])
+    else:
+        c = np.concatenate([box(n - 1, (2, 348, 348)), [[0, 60_000, 0, 0]]])
+    times = []
+    for cloud in (spread, c):
+        cloud = rng.permutation(cloud).astype(np.int32)
+        desc = fit_desc(cloud, [(2, 1, 2)], 64)
+        if kind == "wall":
+            desc.bits_x, desc.bits_y, desc.bits_z = 12, 12, 8
+        d = torch.from_numpy(cloud).cuda()
+        ws = torch.empty(B.spc_pack_workspace_bytes(n, desc), dtype=torch.uint8, device="cuda")
+        keys, perm = torch.empty(n, dtype=torch.int64, device="cuda"), torch.empty(n, dtype=torch.int32, device="cuda")
+        times.append((_microseconds(lambda: B.spc_pack_coords(d, desc, True, 0, None, ws, keys, perm)),
+                      _microseconds(lambda: B.spc_build_kmap(keys, desc, 2, 1, 2, 0, B.LAYOUT_OS).destroy())))
+        assert bool((keys[1:] > keys[:-1]).all())
+    assert times[1][0] < 15 * times[0][0] and times[1][1] < 15 * times[0][1], times
 
 
 @pytest.mark.parametrize("n", [4096, 5000, 70_000, 230_000, 524_289, 1_300_001])
