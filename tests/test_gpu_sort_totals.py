@@ -94,8 +94,9 @@ def test_replays_between_eager_sorts():
         _check(a, keys, perm)
 
 
-# (recorded sorts sum their workgroups' counts in the scatter pass up to 32 of them, 1024 keys each)
-@pytest.mark.parametrize("n", [4096, 4097, 9001, 32_767, 32_768, 32_769])
+# (recorded sorts sum their workgroups' counts in the scatter pass up to 32 of them, 1024 keys each; they have 8192 bins above 200 k keys, a
+# wave to a rank part from 400 k on, 16384 bins and a column scan above 524 288, and are split and merged from 600 k on)
+@pytest.mark.parametrize("n", [4096, 4097, 9001, 32_767, 32_768, 32_769, 200_000, 200_001, 399_999, 400_001, 524_288, 524_289, 599_999, 600_000])
 @pytest.mark.parametrize("key_bits", [0, 64])
 def test_recorded_sizes(n, key_bits):
     c = _cloud(n, n + 1)
