@@ -145,6 +145,47 @@ def test_repeated_and_rejected_rows(n, key_bits):
     assert np.all(lin[1:] >= lin[:-1])
 
 
+@pytest.mark.parametrize("n,dims", [(20_000, (2, 150, 150)), (40_000, (40, 40, 40)), (150_000, (2, 400, 300))])
+@pytest.mark.parametrize("key_bits", [0, 64])
+def test_shared_bins_without_kept_totals(n, dims, key_bits):
+    """On the thread's own stream (the table is summed, or the totals cleared first), and recorded (so are the levels' bins)."""
+    c = _dense(n, dims, n, (4000, 4000, 400))
+    desc, order = fit_desc(c, [(3, 1, 2)], key_bits), np.lexsort((c[:, 3], c[:, 2], c[:, 1]))
+    coords = torch.from_numpy(c).cuda()
+    torch.cuda.synchronize()
+    keys, perm = B.spc_pack_coords(coords, desc, stream=2)  # (hipStreamPerThread)
+    torch.cuda.synchronize()
+    assert np.array_equal(perm.cpu().numpy(), order)
+    m = B.spc_build_kmap(keys, desc, 3, 1, 2, 0, B.LAYOUT_OS)
+    want = m.out_keys()
+    m.destroy()
+    ws = torch.empty(B.spc_pack_workspace_bytes(n, desc), dtype=torch.uint8, device="cuda")
+    side, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+
+    def step():
+        B.spc_pack_coords(coords, desc, True, 0, None, ws, keys, perm)
+        return B.spc_build_kmap(keys, desc, 3, 1, 2, 0, B.LAYOUT_OS)
+
+    with torch.cuda.stream(side):
+        step().destroy()  # (warm)
+    side.synchronize()
+    with torch.cuda.graph(g, stream=side):
+        m = step()
+    for _ in range(3):
+        keys.zero_()
+        perm.zero_()
+        ws.fill_(255)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(perm.cpu().numpy(), order)
+        assert np.array_equal(m.out_keys(), want)
+        B.spc_pack_coords(coords, desc)
+    torch.cuda.synchronize()
+    del g
+    m.destroy()
+
+
 @pytest.mark.parametrize("n", [4097, 40_000])
 def test_on_the_threads_own_stream(n):
     """No totals are kept there: the table is summed, or the totals cleared first."""
