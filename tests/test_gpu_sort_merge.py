@@ -197,3 +197,27 @@ def test_on_the_threads_own_stream(n):
     torch.cuda.synchronize()
     assert np.all(np.diff(keys_to_u64(keys).astype(np.int64)) > 0)
     assert np.array_equal(perm.cpu().numpy(), np.lexsort((c[:, 3], c[:, 2], c[:, 1])))
+
+
+# (beyond 2.9 M keys a split workgroup's share is the longest, 12 288 of them; beyond 6 M there are more regions than rows in the tables of
+# recorded sorts, and the workspace has a term for them)
+@pytest.mark.parametrize("n", [3_000_001, 6_500_000, 8192 * 1024])
+@pytest.mark.parametrize("key_bits", [0, 64])
+def test_largest_sizes(n, key_bits):
+    """With a workspace exactly as large as reported."""
+    lin = np.random.default_rng(n).permutation(n).astype(np.int64) * 7 + 3
+    c = np.stack([0 * lin, lin // 140_000, lin // 200 % 700, lin % 200], 1).astype(np.int32)
+    desc = fit_desc(c, [(3, 1, 2)], key_bits)
+    need = B.spc_pack_workspace_bytes(n, desc)
+    block = torch.full((need + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    keys = torch.empty(n, dtype=torch.int64 if desc.key_bits == 64 else torch.int32, device="cuda")
+    perm = torch.empty(n, dtype=torch.int32, device="cuda")
+    B.spc_pack_coords(torch.from_numpy(c).cuda(), desc, True, 0, None, block[:need], keys, perm)
+    assert np.array_equal(perm.cpu().numpy(), np.argsort(lin))
+    k = keys_to_u64(keys)
+    assert np.all(k[1:] > k[:-1])
+    assert bool((block[need:] == 0xA5).all())
+    m = B.spc_build_kmap(keys, desc, 2, 1, 2, 0, B.LAYOUT_OS)
+    half = (c[:, 1] // 2).astype(np.int64) * 35_000 + c[:, 2] // 2 * 100 + c[:, 3] // 2
+    assert m.n_out == np.count_nonzero(np.bincount(half))
+    m.destroy()
