@@ -34,7 +34,7 @@ def _check(c, desc):
     assert np.array_equal(got, want)
 
 
-# (up to 524 288 keys a bin of more than 1536 of them is shared, and a workgroup has two keys to a thread; beyond, 2048 and four)
+# (a bin of more than 2048 keys is shared, beyond 524 288 keys in all one of more than 4096)
 @pytest.mark.parametrize("n,dims,far", [
     (20_000, (2, 150, 150), (4000, 4000, 200)),    # one bin holds nearly everything
     (20_000, (24, 30, 30), (2000, 10, 10)),        # bins of about 1000
@@ -52,10 +52,10 @@ def test_bins_beyond_the_lds(n, dims, far, key_bits):
 
 
 # (a bin is a plane of x here)
-@pytest.mark.parametrize("n,planes,most,q", [(20_000, 2000, 1536, 512), (530_000, 16_000, 2048, 2048)])
+@pytest.mark.parametrize("n,planes,most,q", [(20_000, 2000, 2048, 512), (530_000, 16_000, 4096, 2048)])
 @pytest.mark.parametrize("key_bits", [0, 64])
 def test_bins_around_the_line(n, planes, most, q, key_bits):
-    sizes = [most - 1, most, most + 1, q - 1, 1, most + 1, q, q + 1, most + q]
+    sizes = [most - 1, most, most + 1, q - 1, most - q + 2, 1, most + 1, q, q + 1, most + q]
     x = np.concatenate([np.full(s, p) for p, s in enumerate(sizes)] + [np.full(most + 1, planes - 1), np.full(most, planes - 3)])
     rest = np.random.default_rng(n).integers(len(sizes), planes - 3, size=n - len(x))
     x = np.concatenate([x, rest])
