@@ -610,7 +610,8 @@ struct BsOrder {
         if (t == 0) L.taken = 0;
         __syncthreads();
         auto starts = [&](int b) __attribute__((always_inline)) { return ns + uniform(L.hist[b]); };
-        const int ne = starts(BS_NSUB);
+        const int ne = min(starts(BS_NSUB), a.n);
+        if (x >= ne) return kept;  // (totals that are not the regions': no trip but gets further, or ends here)
         static_assert(BS_NSUB == 64 * 64, "two steps of a wave");
         auto holder = [&](int pos) __attribute__((always_inline)) {  // the second bin that holds position pos
           const int b = 64 * (63 - __builtin_clzll(__ballot(ns + L.hist[64 * lane] <= pos)));
@@ -631,6 +632,7 @@ struct BsOrder {
             continue;
           }
           if constexpr (!DEDUP) {  // equal keys
+            if (by_row) return kept;  // (as above: no row occurs twice)
             by_row = true;
             sh = max(0, log2_up(a.n_wg * a.per) - 12);
             continue;
@@ -648,7 +650,7 @@ struct BsOrder {
         }
         int b1 = holder(min(stop, ne) - 1);  // (not empty)
         if (starts(b1 + 1) - starts(b1) <= most) ++b1;
-        const int x1 = starts(b1), count = x1 - x;
+        const int x1 = min(starts(b1), ne), count = x1 - x;
         each([&](Elem e, int place, bool ok) __attribute__((always_inline)) {
           const int to_bin = second(e, place, ok);
           const bool mine = to_bin >= b && to_bin < b1;
@@ -658,7 +660,7 @@ struct BsOrder {
           int to = 0;
           if (lane == head) to = atomicAdd(&L.taken, __popcll(some));
           to = __builtin_amdgcn_readlane(to, head) + __popcll(some & ((1ull << lane) - 1ull));
-          if (mine) {
+          if (mine && to < CAP) {
             L.key[to] = e;
             if constexpr (F::ROWS) L.row[to] = a.rows[place];
           }
@@ -767,20 +769,22 @@ __global__ __launch_bounds__(BS_MT, sizeof(KeyT) == 4 ? 8 : 4) void bs_merge_ker
   }
   first = O::uniform(first), start = O::uniform(start), lead = O::uniform(lead);
   last = O::uniform(last), end = O::uniform(end), tail = O::uniform(tail), total = O::uniform(total);
+  // (calls that overlap on one workspace leave totals that are not the regions': nothing is written outside the outputs then, and all loops end)
+  total = min(total, FROM == BS_STARTS ? bs_args_anew(a).n : a.n), end = min(end, total);  // (anew: else the frame of 64-bit levels is not empty)
   // A bin of more keys than the LDS holds is shared: of its second bins a workgroup takes those that start among its positions, lo .. hi - 1.
   // (LiDAR clouds of 120 k voxels have bins of up to 1700 or so: shared from 1536 on, the pass of such a cloud took 56 us in place of 51.)
   // Where the last bin does not fit beside the others it is taken on its own.
   const bool shared_lead = lo < total && start > lo && start - lead > O::CAP;
   const bool none = lo >= total || start >= min(hi, total);
   const bool apart = !none && end - start > O::CAP;
-  const int W = none ? 0 : end - start;
+  int W = none ? 0 : end - start;
   int kept = 0, at0 = start;
   if (__builtin_expect(shared_lead || apart, 0)) {
 #pragma unroll 1
     for (int part = 0; part < 3; ++part) {
       int f0 = first, f1 = apart ? last - 1 : last, s = start, x = start, stop = none ? start : apart ? tail : end;
-      if (part == 0) f0 = f1 = first - 1, s = lead, x = lo, stop = shared_lead ? min(hi, start) : lo;
-      if (part == 2) f0 = f1 = last, s = x = tail, stop = !apart ? tail : end - tail > O::CAP ? hi : end;
+      if (part == 0) f0 = f1 = first - 1, s = lead, x = lo, stop = shared_lead ? min(hi, min(start, total)) : lo;
+      if (part == 2) f0 = f1 = last, s = x = tail, stop = !apart ? tail : end - tail > O::CAP ? min(hi, total) : end;
       if (x < stop) kept = O::crowd(L, a, f0, f1, s, x, stop, kept, &at0);
     }
   } else if (W > 0) {
@@ -793,6 +797,7 @@ __global__ __launch_bounds__(BS_MT, sizeof(KeyT) == 4 ? 8 : 4) void bs_merge_ker
     }
     int all;
     const int pre = block_scan<O::WAVES>(len, L.sums, &all);
+    W = min(W, all);
     if (t < a.n_wg) {
       L.pre[t] = pre;
       L.src[t] = t * a.per + from - pre;
@@ -1490,6 +1495,7 @@ void split_merge(const Src& src, int64_t n, int used_bits, const SplitPlan& p, c
   a.shift = b.shift;
   a.n_bin = b.n_bin;
   a.q = p.q;
+  a.n = static_cast<int>(n);
   a.used_bits = used_bits;
   a.tot = t.p;
   a.tot_pitch = t.pitch;
