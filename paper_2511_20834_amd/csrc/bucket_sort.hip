@@ -409,7 +409,7 @@ __device__ inline const Args& bs_args_anew(const Args&) {
 
 // The part of a workgroup's LDS work that does not depend on where the keys come from: `count` keys (element u * BS_MT + t in
 // k[u], source indices in v[u] where they are apart) are put in order in L.key (L.row).  Their second bins are (key - base) >> ss,
-// below BS_NSUB; a key above lim (of a rejected row) has lim's.  L.hist is zero before.
+// below BS_NSUB; a key above lim (of a rejected row) has lim's, one below base (see bs_merge_kernel) base's.  L.hist is zero before.
 template <typename KeyT, bool DEDUP, int KPT>
 struct BsOrder {
   using F = BsForm<KeyT, DEDUP>;
@@ -441,7 +441,7 @@ struct BsOrder {
     if (threadIdx.x == 0) L.hist[BS_NSUB] = total;
   }
   __device__ static void order(Lds& L, Elem (&k)[KPT], int32_t (&v)[KPT], int count, KeyT base, KeyT lim, int ss, const int t) {
-    auto second = [&](Elem e) { return static_cast<int>((min(F::key(e), lim) - base) >> ss); };
+    auto second = [&](Elem e) { return static_cast<int>((min(max(F::key(e), base), lim) - base) >> ss); };
     int r[KPT];
 #pragma unroll
     for (int u = 0; u < KPT; ++u)
@@ -545,9 +545,9 @@ struct BsOrder {
     __syncthreads();
     if (t < args.n_wg) {
       const uint16_t* row = (DEDUP ? level_ws(args.off, args.ws_pitch) : args.off) + int64_t(t) * bs_off_pitch(args.n_bin);
-      const int from = row[f0];
+      const int from = min<int>(row[f0], args.per);  // (as in bs_merge_kernel)
       L.src[t] = t * args.per + from;
-      L.pre[t] = row[f1 + 1] - from;
+      L.pre[t] = min(row[f1 + 1] - from, args.per - from);
     }
     auto log2_up = [](unsigned n) { return n > 1 ? 32 - __clz(n - 1) : 0; };
 #pragma unroll 1
@@ -769,13 +769,18 @@ __global__ __launch_bounds__(BS_MT, sizeof(KeyT) == 4 ? 8 : 4) void bs_merge_ker
   }
   first = O::uniform(first), start = O::uniform(start), lead = O::uniform(lead);
   last = O::uniform(last), end = O::uniform(end), tail = O::uniform(tail), total = O::uniform(total);
-  // (calls that overlap on one workspace leave totals that are not the regions': nothing is written outside the outputs then, and all loops end)
+  // (Calls that overlap on one workspace leave totals, shares and rows of the table that are not the regions': nothing outside outputs and
+  // workspace is touched then, and all loops end.)
+  if constexpr (FROM == BS_STARTS && !DEDUP) {
+    first = min(max(first, 0), a.n_bin), last = min(max(last, 0), a.n_bin - 1);
+    start = max(start, lo), tail = max(tail, start);
+  }
   total = min(total, FROM == BS_STARTS ? bs_args_anew(a).n : a.n), end = min(end, total);  // (anew: else the frame of 64-bit levels is not empty)
   // A bin of more keys than the LDS holds is shared: of its second bins a workgroup takes those that start among its positions, lo .. hi - 1.
   // (LiDAR clouds of 120 k voxels have bins of up to 1700 or so: shared from 1536 on, the pass of such a cloud took 56 us in place of 51.)
   // Where the last bin does not fit beside the others it is taken on its own.
   const bool shared_lead = lo < total && start > lo && start - lead > O::CAP;
-  const bool none = lo >= total || start >= min(hi, total);
+  const bool none = lo >= total || start >= min(hi, total) || (FROM == BS_STARTS && first > last);
   const bool apart = !none && end - start > O::CAP;
   int W = none ? 0 : end - start;
   int kept = 0, at0 = start;
@@ -792,8 +797,8 @@ __global__ __launch_bounds__(BS_MT, sizeof(KeyT) == 4 ? 8 : 4) void bs_merge_ker
     int from = 0, len = 0;
     if (t < a.n_wg) {
       const uint16_t* row = off + int64_t(t) * pitch;
-      from = row[first];
-      len = row[last + 1] - from;
+      from = min<int>(row[first], a.per);
+      len = min(max(row[last + 1] - from, 0), a.per - from);
     }
     int all;
     const int pre = block_scan<O::WAVES>(len, L.sums, &all);
@@ -813,7 +818,7 @@ __global__ __launch_bounds__(BS_MT, sizeof(KeyT) == 4 ? 8 : 4) void bs_merge_ker
     };
     // (the all-ones keys of rejected rows, in the last bin, count as the first key behind it where there is one)
     const bool over = last == a.n_bin - 1 && a.used_bits < int(8 * sizeof(KeyT));
-    const KeyT base = KeyT(first) << a.shift, lim = over ? KeyT(last + 1) << a.shift : ~KeyT(0);
+    const KeyT base = KeyT(first) << a.shift, lim = (KeyT(last + 1) << a.shift) - (over ? 0 : 1);
     const unsigned bins = last + 1 - first + (over ? 1 : 0);
     const int ss = max(0, a.shift + (bins > 1 ? 32 - __clz(bins - 1) : 0) - 12);
     Elem k[KPT];

@@ -10,6 +10,8 @@ namespace {
 bool keep_totals, recording;
 std::vector<int32_t> totals;  // the library's cleared block
 int disturb_how = -1;
+uint16_t* disturb_ws;
+size_t disturb_words;
 std::mt19937 disturb_rng;
 int launches;
 }  // namespace
@@ -33,7 +35,10 @@ void zeroed_free(void*, size_t, const StreamId&, bool) {
 
 void emu::before_launch(const char* kernel) {
   ++launches;
-  if (disturb_how < 0 || totals.empty() || !strstr(kernel, "merge")) return;
+  if (disturb_how < 0 || !strstr(kernel, "merge")) return;
+  for (size_t i = 0; i < disturb_words; ++i)
+    if (disturb_rng() % 97 == 0) disturb_ws[i] = static_cast<uint16_t>(disturb_rng());
+  if (disturb_words > 0 || totals.empty()) return;
   for (int i = 0; i < 256; ++i) {
     int32_t& t = totals[disturb_rng() % totals.size()];
     t = disturb_how == 0 ? 2 * t : disturb_how == 1 ? 0 : disturb_how == 2 ? t + 3000 : t / 2;
@@ -51,7 +56,10 @@ void* emu_guarded(size_t bytes, size_t align) {
   memset(p, 0xee, bytes);
   return p;
 }
-void emu_mode(int keep, int record, int disturb, int seed) {
+// disturb: -1, how the totals are changed before they are read (0 to 3), or that the workspace is, if one is given
+void emu_mode(int keep, int record, int disturb, int seed, void* ws, size_t ws_bytes) {
+  disturb_ws = static_cast<uint16_t*>(ws);
+  disturb_words = ws_bytes / 2;
   keep_totals = keep != 0;
   recording = record != 0;
   disturb_how = disturb;

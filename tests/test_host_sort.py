@@ -1,6 +1,6 @@
 """The sort's kernels on the CPU (tests/host/emulated): bins that are shared between workgroups, in memory that ends where nothing may be
-touched and in a workspace as large as reported, and what becomes of a sort whose totals are not those of its keys.  Every case runs in a
-process of its own, with a time limit."""
+touched and in a workspace as large as reported, and what becomes of a sort whose totals or workspace another call has changed.  Every case
+runs in a process of its own, with a time limit."""
 import ctypes
 import os
 import re
@@ -56,6 +56,7 @@ CLOUDS = {
     "few": (9000, (10, 10, 10)),       # four, and some others
     "rejected": (9000, (10, 10, 9)),   # half of the rows do not fit
     "band": (5200, (8, 12, 8)),        # bins that fit the LDS alone, but not beside others
+    "large": (524_289, (11, 11, 8)),   # the smallest whose bins' starts a kernel of its own finds
 }
 
 
@@ -83,6 +84,8 @@ def cloud(kind, rng):
     elif kind == "rejected":
         c = anywhere(n)
         c[: n // 2, 0] = -5
+    elif kind == "large":
+        c = np.concatenate([box(9000, (1, 200, 200)), box(n - 15_000, (1500, 400, 200), (1, 0, 0)), np.full((6000, 3), -5)])
     else:
         c = np.concatenate([box(s, (1, 200, 200), (x, 0, 0)) for x, s in enumerate([500, 1900, 1, 400, 2048, 350, 1])])
     c = rng.permutation(np.concatenate([np.zeros((len(c), 1), np.int64), c], 1)).astype(np.int32)
@@ -105,7 +108,7 @@ def run(so, kind, key_bits, keep, record, disturb, seed):
     ws, (dc, coords) = guarded(np.uint8, need, 256)[0], guarded(np.int32, 4 * n)
     (dk, keys), (dp, perm) = guarded(ktype, n), guarded(np.int32, n)
     coords[:] = c.reshape(-1)
-    L.emu_mode(keep, record, disturb, seed)
+    L.emu_mode(keep, record, disturb, seed, ctypes.c_void_p(ws if disturb == 4 else None), ctypes.c_size_t(need if disturb == 4 else 0))
     args = [ctypes.c_void_p(p) for p in (dk, dp, ws)]
     assert L.emu_pack_sort(key_bits, ctypes.c_void_p(dc), ctypes.c_int64(n), (ctypes.c_int * 3)(*bits), PAD, *args) == 0
     if disturb < 0:
@@ -116,6 +119,8 @@ def run(so, kind, key_bits, keep, record, disturb, seed):
         assert np.array_equal(keys, k[perm]) and np.all(keys[1:] >= keys[:-1])
         if key_bits == 32 and not record:
             assert np.array_equal(perm, np.argsort(k, kind="stable"))
+    elif disturb == 4:
+        return
     else:
         keys[:] = np.sort(np.random.default_rng(seed).integers(0, 2 ** min(used, 63), n).astype(ktype))
     masks = []
@@ -135,16 +140,23 @@ def run(so, kind, key_bits, keep, record, disturb, seed):
             assert count == len(want) and np.array_equal(out[:count], want)
 
 
-@pytest.mark.parametrize("kind,key_bits", [(k, b) for k in CLOUDS for b in (32, 64) if b == 64 or sum(CLOUDS[k][1]) <= 32])
 @pytest.mark.parametrize("keep,record", [(1, 0), (0, 0), (0, 1)], ids=["kept totals", "no totals", "recorded"])
+@pytest.mark.parametrize("kind,key_bits", [(k, b) for k in CLOUDS for b in (32, 64) if k != "large" and (b == 64 or sum(CLOUDS[k][1]) <= 32)])
 def test_shared_bins(lib, kind, key_bits, keep, record):
     in_child(lib, kind, key_bits, keep, record, -1, 3)
 
 
-@pytest.mark.parametrize("disturb", [0, 1, 2, 3], ids=["twice", "none", "more", "half"])
-@pytest.mark.parametrize("kind,key_bits", [("wall", 32), ("few", 64), ("band", 32)])
+@pytest.mark.parametrize("key_bits", [32, 64])
+def test_shared_bins_of_a_large_cloud(lib, key_bits):
+    in_child(lib, "large", key_bits, 0, 0, -1, 3)
+
+
+# (totals twice as large, cleared, larger, halved, or words of the workspace changed; "large" has no totals)
+@pytest.mark.parametrize("kind,key_bits,disturb", [(k, b, d) for k, b in (("wall", 32), ("few", 64), ("band", 32), ("large", 32), ("large", 64))
+                                                   for d in range(5) if k != "large" or d == 4])
 def test_totals_that_are_not_the_keys(lib, kind, key_bits, disturb):
-    """Calls that overlap on one workspace may leave such: the result is meaningless, but every loop ends and nothing is written outside."""
+    """As a caller that uses one workspace in two calls at once may leave them: the result is meaningless, but every loop ends and nothing
+    outside is touched."""
     in_child(lib, kind, key_bits, 1, 0, disturb, 4, timeout=60)
 
 
