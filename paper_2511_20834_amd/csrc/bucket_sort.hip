@@ -14,9 +14,10 @@
 //            number of window keys that sort before it, counted by comparing against every
 //            window key (see bs_rank_kernel).
 //
-// Pack + sort orders (key, source) pairs, so equal keys (not a valid cloud, but not
-// rejected unless validation was asked for) still get distinct positions and the permutation is
-// complete whatever the input.  Downsampling sorts the masked keys alone and drops the repeated ones.
+// Equal keys (not a valid cloud, but not rejected unless validation was asked for) get distinct positions, so the permutation is
+// complete whatever the input.  32-bit keys that are split and merged are ordered as (key, source) pairs; among equal 64-bit keys, and in
+// recorded sorts that scatter, the order is that of LDS atomics and not the same from run to run.  Downsampling sorts the masked keys
+// alone and drops the repeated ones.
 #include <algorithm>
 #include <type_traits>
 
@@ -109,7 +110,9 @@ __device__ inline T* level_ws(T* p, size_t ws_pitch) {
 // not fit, from 600 k) against split / starts / merge: 6 k 4.0 / 4.4 / 4.3 against 4.0 / - / 6.6; LiDAR 120 k 4.9 / 6.5 / 9.4 against 5.0 / - / 8.6;
 // indoor 240 k 7.4 / 11.2 / 13.2 against 9.0 / - / 9.4; random 3 * 10^6 19.6 / 9.9 / 44.1 / 26.6 / 4.8 against 29.7 / 6.0 / 29.4; a level of
 // 120 k (with its compaction) 4.5 / 6.7 / 10.2 / 4.2 against 4.7 / - / 9.9 / 4.1.
-// Recorded sorts of up to BS_LARGE_N keys count, scatter and rank: what they launch is tested for.
+// Recorded sorts of up to BS_LARGE_N keys still count, scatter and rank.  That is not the faster way: replayed, us, against split and
+// merge, 33 k 23.0 / 20.0, 120 k 27.8 / 22.2, 240 k 36.6 / 27.3, 524 k 45.8 / 43.6, 599 k 57 / 33; 64-bit keys 120 k 30.2 / 23.3, 400 k
+// 46.6 / 47.9 (up to 14 k the same).
 constexpr int BS_MT = 1024;        // merge threads
 constexpr int BS_SPLIT_KPT = 12;   // keys per split thread at most
 constexpr int BS_RANK_SOLO_N = 400000;
@@ -1330,19 +1333,21 @@ __global__ __launch_bounds__(64 * WAVES) void bs_rank_kernel(const KeyT* __restr
 BucketPlan bucket_plan(int64_t n, int used_bits, bool unique) {
   BucketPlan p{};
   p.add = n <= BS_ADD_N;
-  // keys per workgroup: short shares spread the scattered stores over the chip, and the additions over fewer bins; where the
-  // table is scanned every workgroup adds a row to it.  Coordinates, whose runs are short, add to almost all bins from some
-  // point on: us with shares of 2048 / 4096, 180 k 25.4 / 26.2, 240 k 31.8 / 31.7, 300 k 31.7 / 30.3, 500 k 40.8 / 36.0; levels
-  // made from sorted keys add to few: 300 k 53.4 / 57.1.
+  // keys per workgroup: short shares spread the work over the chip, long ones are fewer rows for the merge to look into and, for
+  // coordinates, which have keys in almost all bins, fewer additions.  us of pack + sort with shares of 1024 / 2048 / 4096: 20 k 11.3 / 11.4,
+  // 60 k 13.2 / 12.3, 120 k 16.8 / 14.4 / 13.3, 180 k 21.7 / 16.4 / 14.9, 240 k - / 21.8 / 19.0, 500 k - / 39.3 / 32.0; of a level with its map,
+  // whose sorted keys add to few bins: 20 k 18.0 / 19.9, 60 k 20.5 / 20.8, 120 k 22.3 / 23.5 / 24.0, 180 k 27.1 / 28.1 / 28.8, 500 k
+  // 53.1 / 48.8 / 48.7.  The lines for coordinates were drawn where they are scattered (recorded sorts: 180 k 25.4 / 26.2 with 2048 / 4096).
   const int share = n <= BS_SHORT_N ? BS_SHORT_SHARE : p.add && (unique || n <= BS_MID_N) ? BS_ADD_SHARE : 4096;
   int n_wg = static_cast<int>(std::min<int64_t>(std::max<int64_t>((n + share - 1) / share, 1), p.add ? n : BS_MAX_WG));
   p.per = static_cast<int>(((n + n_wg - 1) / n_wg + BS_WIDE - 1) / BS_WIDE * BS_WIDE);
   p.n_wg = static_cast<int>(std::max<int64_t>((n + p.per - 1) / p.per, 1));
   // About 16 keys per bin of the key space up to 4096 bins: packing descriptors round every field up
   // to whole bits and scenes are far from cubic, so typically a quarter of the bins is populated.
-  // Beyond that, more bins only pay once the rank pass is bound by its comparisons and not by its
-  // launch: 8192 bins from 200 k keys, 16384 from 512 k (10^6 keys: rank 51 -> 32 us; 300 k keys
-  // with 16384 bins: slower by 2 us for the longer scans).
+  // Beyond that, more bins only pay where the rank pass of a recorded sort is bound by its comparisons: 8192 bins from 200 k keys,
+  // 16384 from 512 k (10^6 keys: rank 51 -> 32 us; 300 k keys with 16384 bins: slower by 2 us for the longer scans).  Split and merge do
+  // not need them: us with 4096 / 8192 / 16384 bins, 210 k 15.9 / 18.7, 300 k 20.9 / 24.6, 500 k 27.0 / 32.2, 700 k 24.1 / 25.4 / 29.3,
+  // 3 * 10^6 49 / 51 / 56; but fewer are crowded earlier (a level of 3 * 10^6 with its map 262 / 116 / 120).
   int fb = 8;
   while (fb < 12 && (int64_t(16) << fb) < n) ++fb;
   if (n > 200000) fb = 13;
@@ -1389,11 +1394,13 @@ struct SplitPlan {
 };
 // Positions per merging workgroup: where the totals are read, short shares spread a cloud over the chip; where the starts have been
 // made, long ones take longer pieces.  Split shares are those of bucket_plan (half as long, 120 k 4.8 -> 5.7 us and 240 k 9.2 -> 11.2 for the
-// additions), above BS_ADD_N as long as gives every CU one (half as long, with 8192 bins, 3 * 10^6: 65 -> 69 us in all).
+// additions).  Above BS_ADD_N a CU gets one as long as 12288 keys last (half as long, with 8192 bins, 3 * 10^6: 65 -> 69 us in all), but none is
+// shorter than 4096, so that from 524 289 to a million keys 129 to 245 CUs have one: us in all with shares of at least 2048 / 3072 / 4096,
+// 530 k 28.1 / 28.2 / 26.6, 700 k 30.7 / 30.7 / 29.1, 10^6 33.2 / 33.1 / 33.1.
 SplitPlan split_plan(int64_t n, int used_bits, bool unique) {
   SplitPlan p{};
   p.b = bucket_plan(n, used_bits, unique);
-  if (!p.b.add) {  // about a region per CU
+  if (!p.b.add) {
     p.b.per = static_cast<int>(std::min<int64_t>(std::max<int64_t>((n / 256 + BS_WIDE - 1) / BS_WIDE, 4), BS_SPLIT_KPT) * BS_WIDE);
     p.b.n_wg = static_cast<int>((n + p.b.per - 1) / p.b.per);
   }

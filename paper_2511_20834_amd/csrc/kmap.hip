@@ -130,9 +130,9 @@ constexpr int search_win_cap(int tile) { return tile == 64 ? 384 : tile == 128 ?
 //   ws_k: (PAIRS = true) weight-stationary lists.  They never pass through a matrix: a tile keeps, per (group,
 //         row), the place of its lower bound and the hit bits of the group's K queries in LDS (5 bytes where
 //         the matrix has 4 K), and once all groups are searched it writes the hits of the ws_k offsets as
-//         compacted (in, out) pairs, offset-major and row-ascending, into its own slab of `tile_pairs` (slab =
-//         tile * K^3 pairs, of which only the first sum-of-hits are touched); tile_counts gets the hits per
-//         (offset, tile).
+//         compacted pairs (input row, offset << 8 | row of the tile), offset-major and row-ascending, into its own
+//         slab of `tile_pairs` (slab = tile * K^3 pairs, of which only the first sum-of-hits are touched);
+//         tile_counts gets the hits per (offset, tile).
 // x offsets none of whose columns is wanted are not searched (the second half of a symmetric map, for example).
 //
 // One launch searches NB maps of the same kernel size, block row y map y (NB = 1: a map of its own).  The maps of a
@@ -554,7 +554,9 @@ __global__ __launch_bounds__(64 * K) void kmap_search_kernel(const SearchBatch<K
     // compaction: a wave takes its own offsets, 64 rows at a time.  The hits of a group follow each other from its lower bound
     // on.  A pair goes to the slab as (input row, offset << 8 | row of the tile): with the offset at hand the fill pass need
     // not search it.  (An offset at a time, with its group's records read again for each, and counts added by lane 0 behind two
-    // branches per offset: search of 120 k LiDAR voxels 17.4 us, now 16.1; 240 k indoor voxels, 5x5x5, hybrid 66.0, now 59.4)
+    // branches per offset: search of 120 k LiDAR voxels 17.4 us, now 16.1; 240 k indoor voxels, 5x5x5, hybrid 66.0, now 59.4;
+    // whole builds of other kernels, tiles and keys: 2x2x2 20 k 13.2, 12.0; 3x3x3 200 k, tiles of 128 rows, 38.4, 32.7; 600 k, of 256, 64-bit
+    // keys 100, 83; 5x5x5 240 k 64-bit keys 150, 127; 7x7x7 20 k 53.9, 46.9; 240 k 64-bit keys 297, 257)
     static_assert(TILE <= 256, "a row of the tile in eight bits");
     int2* slab = args.tile_pairs + int64_t(blockIdx.x) * TILE * K3;
     uint8_t* sub = args.tile_sub + int64_t(blockIdx.x) * K3 * MAX_BLOCKS;  // (unused for offsets without pairs)

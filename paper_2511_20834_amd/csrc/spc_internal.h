@@ -229,10 +229,11 @@ constexpr int BS_MAX_BIN = 1 << BS_MAX_BIN_BITS;  // fine bins (top used key bit
 // Sizes of the partitioning sort; below: one workgroup in LDS; above: rocPRIM (the split's regions and bins are sized for no more).
 // 3 * 10^6 keys: pack + sort 66 us against 177 us with rocPRIM.
 constexpr int64_t BS_MIN_N = 4096, BS_MAX_N = 8192 * 1024;
-constexpr int64_t BS_LARGE_N = 600000;  // recorded sorts of fewer keys: in launches that count, scatter and rank
+constexpr int64_t BS_LARGE_N = 600000;  // recorded sorts of fewer keys: in launches that count, scatter and rank (measured where these are)
 inline bool use_bucket_sort(int64_t n) { return n >= BS_MIN_N && n <= BS_MAX_N; }
 // Keys up to which the first pass adds its counts to the bins' totals, and how many a workgroup takes then.  Beyond, the additions
-// (some 35 per ns, and hardly two keys of a workgroup share a bin) would take longer than a launch that sums the table's columns.
+// (some 35 per ns, and hardly two keys of a workgroup share a bin) would take longer than a launch that sums the table's columns
+// (pack + sort of 500 k random voxels with them 32 us, of 530 k without 26.6).
 constexpr int64_t BS_ADD_N = 524288, BS_MID_N = 200000, BS_SHORT_N = 65536;
 constexpr int BS_ADD_SHARE = 2048, BS_SHORT_SHARE = 1024;
 // Up to so many workgroups their counts are summed where they are read, where totals would have to be cleared first: a launch
@@ -327,7 +328,7 @@ struct spc_kmap {
   int32_t* list_base = nullptr;     // [n_blocks+1][K3]: first entry of every list whose output row is >= 32 * block
   int32_t* list_base_in = nullptr;  // symmetric half-map: the same by input row
   uint8_t* tile_sub = nullptr;      // [n_tiles][K3][tile/32]: pairs of the tile before every 32-row block (scratch of the list build)
-  int2* tile_pairs = nullptr;       // per search tile a slab of compacted (in, out) pairs (scratch of the list build)
+  int2* tile_pairs = nullptr;       // per search tile a slab of compacted pairs (in, offset << 8 | row of the tile) (scratch of the list build)
   int64_t ws_stride = 0;            // entries between consecutive lists in ws_in / ws_out
   int32_t* arrived = nullptr;       // [SHARED_TILES] counters of feature kernels whose workgroups share tiles: zeroed by the build, left zero
   int32_t* inv_parent = nullptr;    // strided maps, on request: for every INPUT voxel p its pair (out q, offset k) as q*K^3+k

@@ -206,7 +206,7 @@ def test_capture_of_a_small_cloud_replays():
 
 
 def test_capture_of_a_large_cloud_replays():
-    """The library's own sort runs up to 8 Mi keys (from 600 k on with the ranking that splits its windows in LDS), so
+    """The library's own sort runs up to 8 Mi keys (recorded from 600 k on by split and merge, as when it is called), so
     steps of that size can be recorded: pack + sort and a strided map (whose level is downsampled from 2.2 M voxels) go
     into a graph and are replayed; every replay equals the eager result."""
     n = 2_200_000
