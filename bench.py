@@ -394,16 +394,16 @@ def main() -> int:
     elt = 4 if tdt == torch.float32 else 2
     conv_bytes = (n * cin + n_out * cout + K3 * cin * cout) * elt + (n_out * K3 * 4 if layout == B.LAYOUT_OS else nnz * 8)
     conv_gbs = conv_bytes / (phase_ms["conv"] * 1e-3) / 1e9
-    # Which feature kernel ran: the split-k kernel for fp32 and wherever offsets come from lists, else the library's
-    # choice between its two output-stationary kernels.  They sum in different orders and each gives the same bits every
-    # time, so the phase kernel ran if forcing it changes nothing.
+    # Which feature kernel ran.  They sum in different orders and each gives the same bits every time, so the one that was
+    # taken is the one that changes nothing when it is forced (the split-k kernel where that holds for it too).
     kname = "conv_os_splitk_kernel"
-    if tdt != torch.float32 and dataflow == B.DATAFLOW_OS and args.hybrid_t is None:
-        km_b = B.spc_build_kmap(keys, desc, K, 1, s_l, 0, layout, in_perm=perm)
-        forced = B.spc_conv_forward(km_b, F_raw, Wp if use_packed else W, dataflow, conv_flags | B.CONV_OS_PHASE, n_out=n_out)
+    km_b = B.spc_build_kmap(keys, desc, K, 1, s_l, 0, layout, in_perm=perm)
+    for name, force in (("conv_os_splitk_kernel", B.CONV_OS_SPLITK), ("conv_os_phase_kernel", B.CONV_OS_PHASE), ("conv_resident_kernel", B.CONV_RESIDENT)):
+        forced = B.spc_conv_forward(km_b, F_raw, Wp if use_packed else W, dataflow, conv_flags | force, n_out=n_out, hybrid_t=args.hybrid_t)
         if torch.equal(forced, out):
-            kname = "conv_os_phase_kernel"
-        km_b.destroy()
+            kname = name
+            break
+    km_b.destroy()
     # Which roof binds: the layer's arithmetic intensity (useful flops per compulsory byte) against the machine
     # balance (2.5 PFLOP/s / 8 TB/s = 312 flop/B; fp32 20).  Below it the HBM roof is the nearer one and is the one
     # reported; the other roof's fraction rides along in "parts".  Both use the duration of the feature phase

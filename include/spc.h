@@ -68,7 +68,8 @@ extern "C" {
 #define SPC_CONV_PACKED_WEIGHTS 2 /* spc_conv_forward: `weights` came from spc_conv_prepare_weights */
 #define SPC_CONV_OS_PHASE 4  /* spc_conv_forward, OS, 16-bit types: force the LDS-staged phase kernel */
 #define SPC_CONV_OS_SPLITK 8 /* spc_conv_forward, OS, 16-bit types: force the split-k kernel */
-#define SPC_CONV_SPLITK_RB(rb) ((rb) << 8) /* with SPC_CONV_OS_SPLITK: 32-row blocks per workgroup (1, 2; 0 = by size) */
+#define SPC_CONV_RESIDENT 16 /* spc_conv_forward: the kernel that keeps the weights in LDS, where the layer has a form of it (else by size) */
+#define SPC_CONV_SPLITK_RB(rb) ((rb) << 8) /* with SPC_CONV_OS_SPLITK: 32-row blocks per workgroup (1, 2; 0 = by size); SPC_CONV_RESIDENT: waves per tile */
 #define SPC_NET_SEQUENTIAL 1 /* spc_build_kmaps_network: a launch per level and per map (for comparison) */
 #define SPC_NET_PHASE_BARRIER 2 /* spc_build_kmaps_network: all levels before any map search (always the case but with SPC_NET_SEQUENTIAL) */
 #define SPC_NET_PIPELINED 4 /* spc_build_kmaps_network: the maps may be used on streams that have not been ordered behind streams[0] */
@@ -284,8 +285,8 @@ void spc_kmap_destroy(spc_kmap* m);
  *   Infinities and NaN in features or weights reach an output through its own pairs only, in
  *             every dtype, dataflow and kernel.
  *   flags     SPC_CONV_RELU (NaN becomes 0, as in C's fmax); SPC_CONV_PACKED_WEIGHTS (see spc_conv_prepare_weights);
- *             SPC_CONV_OS_PHASE or SPC_CONV_OS_SPLITK pick one of the two OS MFMA kernels
- *             (default: chosen from the layer's size; both give the same result up to the
+ *             SPC_CONV_OS_PHASE, SPC_CONV_OS_SPLITK or SPC_CONV_RESIDENT pick one of the MFMA kernels
+ *             (default: chosen from the layer's size; all give the same result up to the
  *             fp32 summation order, and each one alone is bit-reproducible).
  * Every shape and type runs on the matrix cores.  Where the phase kernel is taken, input
  * channel counts that are not a multiple of 16, and rows that are not 16-byte aligned, are

@@ -32,6 +32,7 @@ CONV_RELU = 1
 CONV_PACKED_WEIGHTS = 2
 CONV_OS_PHASE = 4
 CONV_OS_SPLITK = 8
+CONV_RESIDENT = 16
 NET_SEQUENTIAL = 1
 NET_PHASE_BARRIER = 2
 NET_PIPELINED = 4

@@ -22,12 +22,14 @@ def build(force: bool = True, verbose: bool = False) -> str:
     os.makedirs(objdir, exist_ok=True)
     hdrs = [os.path.join(CSRC, "spc_internal.h"), os.path.join(ROOT, "include", "spc.h")]
     newest_hdr = max(os.path.getmtime(h) for h in hdrs)
+    own_hdrs = {"conv.hip": ["conv_common.h", "conv_resident.h"]}  # read by one source only
     objs, procs = [], []
     for src in SOURCES:
         s = os.path.join(CSRC, src)
         o = os.path.join(objdir, src.replace(".hip", ".o"))
         objs.append(o)
-        if force or not os.path.exists(o) or os.path.getmtime(o) < max(os.path.getmtime(s), newest_hdr):
+        if force or not os.path.exists(o) or os.path.getmtime(o) < max(
+                [os.path.getmtime(s), newest_hdr] + [os.path.getmtime(os.path.join(CSRC, h)) for h in own_hdrs.get(src, [])]):
             cmd = [HIPCC, *FLAGS, "-c", s, "-o", o]
             if verbose:
                 print(" ".join(cmd), flush=True)
