@@ -174,7 +174,7 @@ struct SearchBatch {
 
 template <typename KeyT, int K, int TILE, bool PAIRS>
 constexpr size_t search_lds_bytes() {
-  return size_t(K) * (search_win_cap(TILE) * (sizeof(KeyT) + 4) + N_PROBES * sizeof(KeyT)) + (PAIRS ? size_t(K) * K * TILE * 5 : 0);
+  return size_t(K) * search_win_cap(TILE) * (sizeof(KeyT) + 4) + N_PROBES * sizeof(KeyT) + (PAIRS ? size_t(K) * K * TILE * 5 : 0);
 }
 
 // Wave w of the K waves of a workgroup owns x offset w: it finds the window of the input array that the tile's queries
@@ -208,8 +208,8 @@ __global__ __launch_bounds__(64 * K) void kmap_search_kernel(const SearchBatch<K
   const int ix = __builtin_amdgcn_readfirstlane(tid >> 6);
   int32_t* wval = reinterpret_cast<int32_t*>(smem) + ix * WIN_CAP;                                     // row numbers of the staged keys
   KeyT* win = reinterpret_cast<KeyT*>(smem + size_t(K) * WIN_CAP * 4) + ix * WIN_CAP;                  // staged window
-  KeyT* s_probe = reinterpret_cast<KeyT*>(smem + size_t(K) * WIN_CAP * (4 + KB)) + ix * N_PROBES;
-  unsigned char* s_rec = smem + size_t(K) * (WIN_CAP * (4 + KB) + N_PROBES * KB);
+  KeyT* s_probe = reinterpret_cast<KeyT*>(smem + size_t(K) * WIN_CAP * (4 + KB));
+  unsigned char* s_rec = smem + size_t(K) * WIN_CAP * (4 + KB) + N_PROBES * KB;
   int32_t* s_pos = reinterpret_cast<int32_t*>(s_rec);             // PAIRS: [G][TILE] place of the group's lower bound among the staged row numbers, or ~position in the input
   uint8_t* s_hit = reinterpret_cast<uint8_t*>(s_pos + G * TILE);  // PAIRS: [G][TILE] bit t: the group's t-th query (ascending z) hit
 
@@ -241,14 +241,16 @@ __global__ __launch_bounds__(64 * K) void kmap_search_kernel(const SearchBatch<K
   int wlo = 0, wsz = n_in;  // a small level is one window as a whole
   if (n_in + PAD > WIN_CAP) {
     const int chunk0 = (n_in + N_PROBES - 1) / N_PROBES;
-    KeyT pr[N_PROBES / 64];
+    constexpr int PR = (N_PROBES + 64 * K - 1) / (64 * K);  // probes per thread
+    KeyT pr[PR];
 #pragma unroll
-    for (int u = 0; u < N_PROBES / 64; ++u)  // (slices past the end are never looked at)
-      pr[u] = in_keys[min((long long)(u * 64 + lane + 1) * chunk0 - 1, (long long)n_in - 1)];
+    for (int u = 0; u < PR; ++u)  // (slices past the end are never looked at)
+      pr[u] = in_keys[min((long long)(u * (64 * K) + tid + 1) * chunk0 - 1, (long long)n_in - 1)];
     const KeyT kfirst = out_keys[i0], klast = out_keys[i0 + rows - 1];
 #pragma unroll
-    for (int u = 0; u < N_PROBES / 64; ++u) s_probe[u * 64 + lane] = pr[u];
-    __builtin_amdgcn_wave_barrier();
+    for (int u = 0; u < PR; ++u)
+      if (u * (64 * K) + tid < N_PROBES) s_probe[u * (64 * K) + tid] = pr[u];
+    __syncthreads();
     const KeyT q = lane >= 32 ? KeyT(klast + xoff + sp.ymax + zspan) : KeyT(kfirst + xoff + sp.ymin);
     const int b = half_wave_bound<KeyT>(in_keys, n_in, s_probe, q, BOUND_SLACK);
     wlo = __builtin_amdgcn_readlane(b, 0);
