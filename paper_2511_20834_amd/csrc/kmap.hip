@@ -115,10 +115,14 @@ __device__ inline int half_wave_bound(const SPC_GLOBAL KeyT* keys, int n, const 
 
 // Output voxels per search workgroup (a multiple of the wave size).
 // Short tiles spread a small level over the chip
-// and keep a workgroup's life short; longer ones pay for their windows less often: us, 64 / 128 / 256 rows, 3x3x3,
-// 30 k voxels 6.3 / 7.1 / 10.1, 120 k 12.0 / 12.4 / 16.1, 190 k 17.0 / 15.9 / 18.5, 500 k 34.6 / 27.0 / 24.8,
-// 3 * 10^6 179 / 122 / 103; 5x5x5, 64 / 128 rows: 30 k 10.6 / 13.1, 240 k 44 / 46.
-inline int search_tile(int K, int64_t n_out) { return K > 3 ? 64 : n_out >= 400000 ? 256 : n_out >= 150000 ? 128 : 64; }
+// and keep a workgroup's life short; longer ones pay for their windows less often: build of a map, us, 64 / 128 / 256 rows, 3x3x3,
+// 30 k voxels 5.4 / 6.3 / 9.0, 120 k 9.6 / 10.9 / 14.9, 150 k 10.6 / 11.7 / 16.0, 190 k 12.5 / 12.4 / 16.2, 300 k 16.7 / 16.1 / 15.8, 500 k 24.3 / 21.4 /
+// 19.4, 10^6 42.6 / 36.2 / 32.2, 3 * 10^6 124 / 102 / 92; 64-bit keys 400 k 23.1 / 21.5 / 24.1, 600 k 31.5 / 28.4 / 29.7, 10^6 49.0 / 41.5 / 41.9; with lists, whose
+// records of 256 rows leave a CU few workgroups, 400 k 41.8 / 36.4 / 42.2, 10^6 85 / 71 / 79, 2.5 * 10^6 193 / 156 / 169; 5x5x5, 64 / 128 rows: 30 k 10.6 / 13.1, 240 k 44 / 46.
+inline int search_tile(int K, int64_t n_out, int key_bits, bool lists) {
+  if (K > 3 || n_out < 185000) return 64;
+  return lists || n_out < (key_bits == 32 ? 400000 : 1000000) ? 128 : 256;
+}
 // Input keys (with their row numbers) that the window of one x offset may occupy in LDS.  A window holds what the tile's
 // rows can reach: about as many keys as the tile has rows (more where the input level is finer than the output level),
 // a few columns of the scene, and the slack of its bounds.
@@ -179,7 +183,7 @@ constexpr size_t search_lds_bytes() {
 
 // Wave w of the K waves of a workgroup owns x offset w: it finds the window of the input array that the tile's queries
 // with this x offset can hit, stages it in LDS and searches the tile's rows, 64 at a time, for its K y offsets.  The
-// waves never wait for each other before the block masks are put together.
+// waves wait for each other where the probes have come, and before the block masks are put together.
 template <typename KeyT, int K, int TILE, bool PAIRS, int NB>
 __global__ __launch_bounds__(64 * K) void kmap_search_kernel(const SearchBatch<KeyT, NB> batch) {
   const SearchArgs<KeyT>& args = batch.a[NB == 1 ? 0 : blockIdx.y];
@@ -242,6 +246,8 @@ __global__ __launch_bounds__(64 * K) void kmap_search_kernel(const SearchBatch<K
   if (n_in + PAD > WIN_CAP) {
     const int chunk0 = (n_in + N_PROBES - 1) / N_PROBES;
     constexpr int PR = (N_PROBES + 64 * K - 1) / (64 * K);  // probes per thread
+    // A load of 64 keys far apart keeps the memory path 64 cycles and brings 64 lines: the workgroup asks for them once, not every
+    // wave for itself.  Build of a map, us, before / now: 50 k 7.8 / 6.2, 120 k 12.9 / 9.6, 10^6 38.3 / 32.2, 3 * 10^6 98 / 87, 5x5x5 240 k 39.8 / 34.6.
     KeyT pr[PR];
 #pragma unroll
     for (int u = 0; u < PR; ++u)  // (slices past the end are never looked at)
@@ -288,7 +294,7 @@ __global__ __launch_bounds__(64 * K) void kmap_search_kernel(const SearchBatch<K
       }
     }
   }
-  __syncthreads();  // the counters and masks are cleared (the wave's own window needs no barrier)
+  __syncthreads();  // (counters and masks are cleared; the wave's own window needs no barrier)
 
   // ---- per-lane searches, 64 output voxels at a time, the K y offsets interleaved (independent LDS chains hide each
   // other's latency).  The phase is bound by the number of instructions, so everything that is the same for the 64
@@ -902,8 +908,13 @@ static void launch_search(spc_kmap* const* ms, int count, hipStream_t s) {
     if (n_tiles == 0) continue;
     using One = std::integral_constant<int, 1>;
     using Most = std::integral_constant<int, MOST>;
-    if (n == 1) pairs ? go(std::true_type{}, One{}, first, n, n_tiles) : go(std::false_type{}, One{}, first, n, n_tiles);
-    else pairs ? go(std::true_type{}, Most{}, first, n, n_tiles) : go(std::false_type{}, Most{}, first, n, n_tiles);
+    if constexpr (TILE < 256) {  // (longer tiles have no lists)
+      if (pairs) {
+        n == 1 ? go(std::true_type{}, One{}, first, n, n_tiles) : go(std::true_type{}, Most{}, first, n, n_tiles);
+        continue;
+      }
+    }
+    n == 1 ? go(std::false_type{}, One{}, first, n, n_tiles) : go(std::false_type{}, Most{}, first, n, n_tiles);
   }
   g_search_launches.fetch_add(count, std::memory_order_relaxed);
 }
@@ -1038,7 +1049,7 @@ static int prepare_map(Level* in, Level* out, const PackInfo& pi, const spc_laye
   out->refs++;
   out->add_reader(s);
   m->out_cap = out->n_host >= 0 ? out->n_host : out->cap;
-  m->tile = search_tile(l.K, m->out_cap);
+  m->tile = search_tile(l.K, m->out_cap, pi.key_bits, (l.layout & SPC_LAYOUT_WS) != 0);
   m->n_tiles = static_cast<int>((m->out_cap + m->tile - 1) / m->tile);
   m->n_blocks_cap = (m->out_cap + 31) / 32;
   m->mask_words = (m->K3 + 31) / 32;
@@ -1161,7 +1172,7 @@ static int prepare_from_twin(spc_kmap* twin, Level* coarse, Level* fine, const P
   m->out_level = fine;
   fine->refs++;
   m->out_cap = fine->n_host >= 0 ? fine->n_host : fine->cap;
-  m->tile = search_tile(l.K, m->out_cap);
+  m->tile = search_tile(l.K, m->out_cap, pi.key_bits, (l.layout & SPC_LAYOUT_WS) != 0);
   m->n_tiles = static_cast<int>((m->out_cap + m->tile - 1) / m->tile);
   m->n_blocks_cap = (m->out_cap + 31) / 32;
   m->mask_words = 1;
