@@ -1345,9 +1345,8 @@ BucketPlan bucket_plan(int64_t n, int used_bits, bool unique) {
   // About 16 keys per bin of the key space up to 4096 bins: packing descriptors round every field up
   // to whole bits and scenes are far from cubic, so typically a quarter of the bins is populated.
   // Beyond that, more bins only pay where the rank pass of a recorded sort is bound by its comparisons: 8192 bins from 200 k keys,
-  // 16384 from 512 k (10^6 keys: rank 51 -> 32 us; 300 k keys with 16384 bins: slower by 2 us for the longer scans).  Split and merge do
-  // not need them: us with 4096 / 8192 / 16384 bins, 210 k 15.9 / 18.7, 300 k 20.9 / 24.6, 500 k 27.0 / 32.2, 700 k 24.1 / 25.4 / 29.3,
-  // 3 * 10^6 49 / 51 / 56; but fewer are crowded earlier (a level of 3 * 10^6 with its map 262 / 116 / 120).
+  // 16384 from 512 k (10^6 keys: rank 51 -> 32 us; 300 k keys with 16384 bins: slower by 2 us for the longer scans).  Split and merge have
+  // fewer (split_plan).
   int fb = 8;
   while (fb < 12 && (int64_t(16) << fb) < n) ++fb;
   if (n > 200000) fb = 13;
@@ -1387,24 +1386,37 @@ Ws<KeyT> carve(void* ws, int64_t n) {
 }
 
 // Split + merge: sizes of both kernels' shares.
+// Levels of more keys: wide workgroups merge also where the totals are read (coordinates: above BS_MID_N).  There are a quarter as many then, and
+// each reads all totals first; below, they are too few for the chip.  us, narrow / wide: pack + sort, LiDAR 160 k 15.9 / 20.5, 199 k 15.7 / 19.9, 205 k 30.4 /
+// 23.0, indoor 180 k 18.2 / 17.7, 240 k 19.9 / 19.5, 320 k 26.1 / 21.9, with 64-bit keys 240 k 26.3 / 21.5, random 180 k 15.9 / 16.2, 300 k 24.5 / 19.6, 500 k 32.4 /
+// 24.3, with 64-bit keys 44.4 / 27.4; a level with its map, LiDAR 190 k 24.0 / 31.1, 260 k 28.2 / 32.1, indoor 240 k 30.0 / 32.0, 320 k 38.3 / 34.7, random 300 k
+// 37.0 / 32.4, 500 k 47.2 / 41.0, with 64-bit keys 57.0 / 43.8.
+constexpr int64_t BS_WIDE_LEVEL_N = 300000;
+// Keys up to which 8192 bins do: us, 16384 / 8192, 530 k 26.5 / 21.8, 700 k 28.9 / 25.6, 10^6 33.2 / 29.5, 3 * 10^6 56.4 / 51.0, with 64-bit keys 81.5 /
+// 73.2.  (4096: 530 k 20.8, 3 * 10^6 49.2, but indoor 320 k 38.4 against 20.7, its bins being shared.)  A quarter of the bins is
+// populated, and beyond these many keys an average one of 8192 nears what a workgroup holds.
+constexpr int64_t BS_FEW_BINS_N = 4000000;
 struct SplitPlan {
   BucketPlan b;
   int q, n_share;  // positions per merging workgroup
   bool wide;       // four keys per merge thread instead of two
 };
-// Positions per merging workgroup: where the totals are read, short shares spread a cloud over the chip; where the starts have been
-// made, long ones take longer pieces.  Split shares are those of bucket_plan (half as long, 120 k 4.8 -> 5.7 us and 240 k 9.2 -> 11.2 for the
+// Positions per merging workgroup: short shares spread a small cloud over the chip; long ones take longer pieces and read the totals less often.  Split shares are those of bucket_plan (half as long, 120 k 4.8 -> 5.7 us and 240 k 9.2 -> 11.2 for the
 // additions).  Above BS_ADD_N a CU gets one as long as 12288 keys last (half as long, with 8192 bins, 3 * 10^6: 65 -> 69 us in all), but none is
 // shorter than 4096, so that from 524 289 to a million keys 129 to 245 CUs have one: us in all with shares of at least 2048 / 3072 / 4096,
 // 530 k 28.1 / 28.2 / 26.6, 700 k 30.7 / 30.7 / 29.1, 10^6 33.2 / 33.1 / 33.1.
 SplitPlan split_plan(int64_t n, int used_bits, bool unique) {
   SplitPlan p{};
   p.b = bucket_plan(n, used_bits, unique);
+  if (p.b.n_bin > BS_MAX_BIN / 2 && n <= BS_FEW_BINS_N) {
+    p.b.n_bin /= 2;
+    ++p.b.shift;
+  }
   if (!p.b.add) {
     p.b.per = static_cast<int>(std::min<int64_t>(std::max<int64_t>((n / 256 + BS_WIDE - 1) / BS_WIDE, 4), BS_SPLIT_KPT) * BS_WIDE);
     p.b.n_wg = static_cast<int>((n + p.b.per - 1) / p.b.per);
   }
-  p.wide = !p.b.add;
+  p.wide = !p.b.add || n > (unique ? BS_WIDE_LEVEL_N : BS_MID_N);
   p.q = p.wide ? 2048 : 512;
   p.n_share = static_cast<int>((n + p.q - 1) / p.q);
   return p;
@@ -1483,7 +1495,7 @@ void split_merge(const Src& src, int64_t n, int used_bits, const SplitPlan& p, c
   auto split = [&](auto KPT_, auto ADD_) {
     constexpr int KPT = decltype(KPT_)::value;
     constexpr bool ADD = decltype(ADD_)::value;
-    if constexpr (!ADD) {  // (16384 bins or long shares: more than the default LDS limit)
+    if constexpr (!ADD) {  // (long shares: more than the default LDS limit)
       static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bs_count_kernel<KeyT, Src, DEDUP, KPT, ADD>),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024);
       (void)attr;
@@ -1531,7 +1543,8 @@ void split_merge(const Src& src, int64_t n, int used_bits, const SplitPlan& p, c
   if (!t.p)
     hipLaunchKernelGGL(bs_starts_kernel, dim3((b.n_bin + BS_START_BINS - 1) / BS_START_BINS, n_levels), dim3(BS_WIDE), 0, s, w.off, b.n_wg, b.n_bin,
                        p.q, p.n_share, w.share, w.n_kept, ws_pitch);
-  if (t.p) merge(std::false_type{}, std::integral_constant<int, BS_TOTALS>{});
+  if (t.p && p.wide) merge(std::true_type{}, std::integral_constant<int, BS_TOTALS>{});
+  else if (t.p) merge(std::false_type{}, std::integral_constant<int, BS_TOTALS>{});
   else if (p.wide) merge(std::true_type{}, std::integral_constant<int, BS_STARTS>{});
   else if constexpr (DEDUP) merge(std::false_type{}, std::integral_constant<int, BS_STARTS>{});
 }
