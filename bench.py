@@ -198,7 +198,7 @@ def bench_network(args, torch, B, synth) -> int:
                                "step replayed from a HIP graph" % n,
                    "n_voxels": n, "levels": level_sizes, "voxel_offsets": vo, "useful_flops": flops},
         "parts": part, "tuning": tuned,
-        "roofline": {"kernel": "conv_os_splitk_kernel + conv_os_phase_kernel (all 25 layers)", "bound": "mfma",
+        "roofline": {"kernel": "conv_os_splitk_kernel + conv_os_phase_kernel + conv_resident_kernel (all 25 layers)", "bound": "mfma",
                      "achieved": part["forward_useful_TFLOPs"],
                      "peak": PEAK_MFMA_F16_TFLOPS, "unit": "TFLOP/s", "frac": part["forward_useful_TFLOPs"] / PEAK_MFMA_F16_TFLOPS,
                      "traffic": None},
@@ -397,13 +397,14 @@ def main() -> int:
     # Which feature kernel ran.  They sum in different orders and each gives the same bits every time, so the one that was
     # taken is the one that changes nothing when it is forced (the split-k kernel where that holds for it too).
     kname = "conv_os_splitk_kernel"
-    km_b = B.spc_build_kmap(keys, desc, K, 1, s_l, 0, layout, in_perm=perm)
-    for name, force in (("conv_os_splitk_kernel", B.CONV_OS_SPLITK), ("conv_os_phase_kernel", B.CONV_OS_PHASE), ("conv_resident_kernel", B.CONV_RESIDENT)):
-        forced = B.spc_conv_forward(km_b, F_raw, Wp if use_packed else W, dataflow, conv_flags | force, n_out=n_out, hybrid_t=args.hybrid_t)
-        if torch.equal(forced, out):
-            kname = name
-            break
-    km_b.destroy()
+    if not args.sym:  # (half-maps have no other, and rows in key order)
+        km_b = B.spc_build_kmap(keys, desc, K, 1, s_l, 0, layout, in_perm=perm)
+        for name, force in (("conv_os_splitk_kernel", B.CONV_OS_SPLITK), ("conv_os_phase_kernel", B.CONV_OS_PHASE), ("conv_resident_kernel", B.CONV_RESIDENT)):
+            forced = B.spc_conv_forward(km_b, F_raw, Wp if use_packed else W, dataflow, conv_flags | force, n_out=n_out, hybrid_t=args.hybrid_t)
+            if torch.equal(forced, out):
+                kname = name
+                break
+        km_b.destroy()
     # Which roof binds: the layer's arithmetic intensity (useful flops per compulsory byte) against the machine
     # balance (2.5 PFLOP/s / 8 TB/s = 312 flop/B; fp32 20).  Below it the HBM roof is the nearer one and is the one
     # reported; the other roof's fraction rides along in "parts".  Both use the duration of the feature phase
