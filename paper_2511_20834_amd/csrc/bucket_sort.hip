@@ -1345,8 +1345,9 @@ BucketPlan bucket_plan(int64_t n, int used_bits, bool unique) {
   // About 16 keys per bin of the key space up to 4096 bins: packing descriptors round every field up
   // to whole bits and scenes are far from cubic, so typically a quarter of the bins is populated.
   // Beyond that, more bins only pay where the rank pass of a recorded sort is bound by its comparisons: 8192 bins from 200 k keys,
-  // 16384 from 512 k (10^6 keys: rank 51 -> 32 us; 300 k keys with 16384 bins: slower by 2 us for the longer scans).  Split and merge have
-  // fewer (split_plan).
+  // 16384 from 512 k (10^6 keys: rank 51 -> 32 us; 300 k keys with 16384 bins: slower by 2 us for the longer scans).  Split and merge would
+  // do with fewer: us with 8192 / 16384 bins, 530 k 21.8 / 26.5, 700 k 25.6 / 28.9, 10^6 29.5 / 33.2, 3 * 10^6 51.0 / 56.4; but fewer are crowded
+  // earlier (a level of 3 * 10^6 with its map, 4096 / 8192 / 16384 bins, 262 / 116 / 120; 1.5 * 10^6 in a box beside one far voxel 163 / 83, with a wall of 250 k 168 / 126).
   int fb = 8;
   while (fb < 12 && (int64_t(16) << fb) < n) ++fb;
   if (n > 200000) fb = 13;
@@ -1391,11 +1392,9 @@ Ws<KeyT> carve(void* ws, int64_t n) {
 // 23.0, indoor 180 k 18.2 / 17.7, 240 k 19.9 / 19.5, 320 k 26.1 / 21.9, with 64-bit keys 240 k 26.3 / 21.5, random 180 k 15.9 / 16.2, 300 k 24.5 / 19.6, 500 k 32.4 /
 // 24.3, with 64-bit keys 44.4 / 27.4; a level with its map, LiDAR 190 k 24.0 / 31.1, 260 k 28.2 / 32.1, indoor 240 k 30.0 / 32.0, 320 k 38.3 / 34.7, random 300 k
 // 37.0 / 32.4, 500 k 47.2 / 41.0, with 64-bit keys 57.0 / 43.8.
+// (Bins that just fit a wide workgroup lose: 300 k in a box beside one far voxel 20 / 34; those that do not fit a narrow one win: 260 k in three planes
+// 172 / 137, 524 k in four 403 / 186.)
 constexpr int64_t BS_WIDE_LEVEL_N = 300000;
-// Keys up to which 8192 bins do: us, 16384 / 8192, 530 k 26.5 / 21.8, 700 k 28.9 / 25.6, 10^6 33.2 / 29.5, 3 * 10^6 56.4 / 51.0, with 64-bit keys 81.5 /
-// 73.2.  (4096: 530 k 20.8, 3 * 10^6 49.2, but indoor 320 k 38.4 against 20.7, its bins being shared.)  A quarter of the bins is
-// populated, and beyond these many keys an average one of 8192 nears what a workgroup holds.
-constexpr int64_t BS_FEW_BINS_N = 4000000;
 struct SplitPlan {
   BucketPlan b;
   int q, n_share;  // positions per merging workgroup
@@ -1408,10 +1407,6 @@ struct SplitPlan {
 SplitPlan split_plan(int64_t n, int used_bits, bool unique) {
   SplitPlan p{};
   p.b = bucket_plan(n, used_bits, unique);
-  if (p.b.n_bin > BS_MAX_BIN / 2 && n <= BS_FEW_BINS_N) {
-    p.b.n_bin /= 2;
-    ++p.b.shift;
-  }
   if (!p.b.add) {
     p.b.per = static_cast<int>(std::min<int64_t>(std::max<int64_t>((n / 256 + BS_WIDE - 1) / BS_WIDE, 4), BS_SPLIT_KPT) * BS_WIDE);
     p.b.n_wg = static_cast<int>((n + p.b.per - 1) / p.b.per);
@@ -1495,7 +1490,7 @@ void split_merge(const Src& src, int64_t n, int used_bits, const SplitPlan& p, c
   auto split = [&](auto KPT_, auto ADD_) {
     constexpr int KPT = decltype(KPT_)::value;
     constexpr bool ADD = decltype(ADD_)::value;
-    if constexpr (!ADD) {  // (long shares: more than the default LDS limit)
+    if constexpr (!ADD) {  // (16384 bins or long shares: more than the default LDS limit)
       static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bs_count_kernel<KeyT, Src, DEDUP, KPT, ADD>),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024);
       (void)attr;

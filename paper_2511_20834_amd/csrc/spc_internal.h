@@ -233,7 +233,7 @@ constexpr int64_t BS_LARGE_N = 600000;  // recorded sorts of fewer keys: in laun
 inline bool use_bucket_sort(int64_t n) { return n >= BS_MIN_N && n <= BS_MAX_N; }
 // Keys up to which the first pass adds its counts to the bins' totals, and how many a workgroup takes then.  Beyond, the additions
 // (some 35 per ns, and hardly two keys of a workgroup share a bin) would take longer than a launch that sums the table's columns
-// (pack + sort of 500 k random voxels with them 24.3 us, of 530 k without 21.8).
+// (pack + sort of 500 k random voxels with them 24.3 us, without 21.8; below the line eager sorts keep to two launches).
 constexpr int64_t BS_ADD_N = 524288, BS_MID_N = 200000, BS_SHORT_N = 65536;
 constexpr int BS_ADD_SHARE = 2048, BS_SHORT_SHARE = 1024;
 // Up to so many workgroups their counts are summed where they are read, where totals would have to be cleared first: a launch

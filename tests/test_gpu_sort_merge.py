@@ -67,19 +67,11 @@ def test_bins_around_the_line(n, planes, most, q, key_bits):
     _check(np.random.default_rng(n + 2).permutation(c).astype(np.int32), fit_desc(c, [(3, 1, 2)], key_bits))
 
 
-# (wide workgroups, fed by totals or by starts, and 8192 bins: a plane of x each)
-@pytest.mark.parametrize("n", [200_000, 200_001, 300_000, 300_001, 524_288, 524_289, 600_001])
+# (wide workgroups that read the totals, and 8192 bins: a plane of x each)
+@pytest.mark.parametrize("n", [200_001, 300_000, 300_001, 524_288])
 @pytest.mark.parametrize("key_bits", [0, 64])
 def test_bins_around_the_line_of_wide_merges(n, key_bits):
     test_bins_around_the_line(n, 8000, 4096, 2048, key_bits)
-
-
-@pytest.mark.parametrize("n", [3_999_999, 4_000_000, 4_000_001])
-def test_where_the_bins_double(n):
-    side = int(round((n / 0.05) ** (1 / 3))) + 2
-    lin = np.random.default_rng(n).choice(side ** 3, size=n, replace=False)
-    c = np.stack([np.zeros(n, np.int64), lin // (side * side), lin // side % side, lin % side], 1).astype(np.int32)
-    _check(c, fit_desc(c, [(3, 1, 2)], 0))
 
 
 def _microseconds(f):
