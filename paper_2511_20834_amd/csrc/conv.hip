@@ -1459,7 +1459,7 @@ static void launch_os_splitk(const ConvArgs& a) {
   using Yes = std::true_type;
   using No = std::false_type;
   const int nb_total = (a.cout + 31) / 32;
-  const bool wide = wide_rows<T>(a) || int64_t(a.m->K3) * ((a.cin + 2 * LPC - 1) / (2 * LPC)) * nb_total * 1024 > int64_t(MAX_OFFSET);
+  const bool wide = wide_rows<T>(a) || wide_weights<T>(a);
   const bool quad = sizeof(T) == 2 && a.cin == 4 && a.ld_in % 4 == 0 && reinterpret_cast<uintptr_t>(a.F) % 8 == 0 && !wide;
   auto form = [&](auto NB_, auto PACKED_, auto FROM_) {
     constexpr int NB = decltype(NB_)::value, FROM = decltype(FROM_)::value;

@@ -240,6 +240,13 @@ static bool wide_rows(const ConvArgs& a) {
   return (il->n_host < 0 ? il->cap : il->n_host) * a.ld_in * int64_t(sizeof(T)) > int64_t(MAX_OFFSET);
 }
 
+// Whether the weights are, in operand order (the plain ones are no more).
+template <typename T>
+static bool wide_weights(const ConvArgs& a) {
+  constexpr int SLAB = 2 * Mfma<T>::LPC;
+  return int64_t(a.m->K3) * ((a.cin + SLAB - 1) / SLAB) * ((a.cout + 31) / 32) * 1024 > int64_t(MAX_OFFSET);
+}
+
 // Whether the feature rows cannot be read in pieces of 16 bytes.
 template <typename T>
 static bool by_channel(const ConvArgs& a) {

@@ -217,7 +217,7 @@ __global__ __launch_bounds__(64 * RES_WAVES) void conv_resident_kernel(const Res
         }
       }
     } else {
-      const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(W), 0, K3 * cin * cout * int(sizeof(T)), 0x00020000);
+      const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(W), 0, static_cast<uint32_t>(K3) * cin * cout * uint32_t(sizeof(T)), 0x00020000);
       constexpr int U = 4;  // fragments in flight
       for (int f0 = wave; f0 < total; f0 += U * RES_WAVES) {
         V v[U];
@@ -460,7 +460,8 @@ template <typename T>
 static bool conv_resident(const ConvArgs& a) {
   constexpr int LPC = Mfma<T>::LPC, ELEM = sizeof(T), LDS = 160 * 1024;
   const int K3 = a.m->K3, nb_total = (a.cout + 31) / 32;
-  if (K3 != RES_K3 || a.m->sym || by_channel<T>(a) || wide_rows<T>(a) || a.cin > 8 * LPC) return false;
+  // (plain weights are read at offsets of 32 bits; packed ones need not be, but the choice is the same for both)
+  if (K3 != RES_K3 || a.m->sym || by_channel<T>(a) || wide_rows<T>(a) || wide_weights<T>(a) || a.cin > 8 * LPC) return false;
   const int nkk = a.cin <= 2 * LPC ? 1 : a.cin <= 4 * LPC ? 2 : 4;
   const bool two = nb_total % 2 == 0 && nkk < 4;  // 64 columns at a time
   const int n_slabs = two ? nb_total / 2 : nb_total;

@@ -120,6 +120,8 @@ def test_splitk_far_rows(dtype, cin, cout):
     (torch.bfloat16, 1000, 1003, 80_000),  # rows that are not aligned
     (torch.float16, 1000, 1000, 80_000),
     (torch.float32, 501, 501, 80_000),
+    (torch.float16, 64, 64, 1_250_016),    # channels of which the kernel with resident weights has a form, and tiles enough for it
+    (torch.float32, 32, 32, 1_250_016),
 ])
 def test_splitk_far_weights(dtype, cin, pitch, cout):
     """Weights of more than 4 GiB: neither their bytes nor their number of 16-bit channels fits 32 bits."""

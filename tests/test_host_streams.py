@@ -253,3 +253,26 @@ def test_sorts_ask_for_no_memory(host):
     assert not any(cleared_first(host.pack(300_000, s)) for s in streams[70:])
     host.L.spc_release_cache()
     host.on(0)
+
+
+# ---- which feature kernel a layer gets
+F16, F32 = 0, 2
+
+
+def feature_kernel(host, m, ld_in, cin, cout, dtype=F16, dataflow=B.DATAFLOW_OS, flags=0, ld_out=None):
+    """The name of the feature kernel that a call enqueues."""
+    p = ctypes.c_void_p(64)
+    host.log()
+    assert host.L.spc_conv_forward(m, p, ctypes.c_int64(ld_in), p, p, ctypes.c_int64(ld_out or cout), cin, cout, dtype, dataflow, flags, OTHER) == 0
+    names = [l[3] for l in host.log() if l[0] == "launch"]
+    return [k for k in ("resident", "phase", "splitk") if any("conv_%s_kernel" % k in n or "conv_os_%s_kernel" % k in n for n in names)][-1]
+
+
+@pytest.mark.parametrize("flags", [0, B.CONV_RESIDENT])
+@pytest.mark.parametrize("dtype,cin,cout", [(F16, 64, 1_250_000), (F16, 64, 700_000), (F32, 32, 1_250_000)])
+def test_weights_beyond_32_bit_offsets_are_left_to_the_splitk_kernel(host, flags, dtype, cin, cout):
+    """The kernel with resident weights reads plain ones at 32-bit offsets, of which the upper half is the mark of what is not there."""
+    m = host.build(40, OTHER)
+    assert feature_kernel(host, m, cin, cin, cout, dtype, flags=flags) == "splitk"
+    assert feature_kernel(host, m, cin, cin, 40, dtype, flags=B.CONV_RESIDENT) == "resident"
+    host.destroy(m)
