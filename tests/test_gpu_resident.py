@@ -112,3 +112,20 @@ def test_resident_by_itself(n, density, cin, cout, dtype, ws, want):
     own = B.spc_conv_forward(km, F, W, df)
     assert torch.equal(own, B.spc_conv_forward(km, F, W, df, B.CONV_RESIDENT)) == want
     km.destroy()
+
+
+def test_rows_that_lie_4_gib_apart():
+    """Outputs whose pitch no 32-bit number holds: the split-k kernel's, also where this one is asked for."""
+    c = np.array([[0, 0, 0, 0], [0, 0, 0, 1]], np.int32)
+    desc = fit_desc(c, [(3, 1, 1)])
+    keys, _ = gpu_pack(c, desc)
+    km = B.spc_build_kmap(keys, desc, 3, layout=B.LAYOUT_OS)
+    F, _ = to_torch(synth.features(2, 32, np.float16, seed=7), torch.float16)
+    W, _ = to_torch(synth.weights(27, 32, 32, np.float16, seed=8), torch.float16)
+    apart = torch.zeros((1 << 31) + 32, dtype=torch.float16, device="cuda")
+    out = apart.as_strided((2, 32), (1 << 31, 1))
+    B.spc_conv_forward(km, F, W, flags=B.CONV_RESIDENT, out=out)
+    assert torch.equal(out, B.spc_conv_forward(km, F, W, flags=B.CONV_OS_SPLITK))
+    assert int(torch.count_nonzero(apart)) == int(torch.count_nonzero(out))
+    km.destroy()
+    B.spc_release_cache()

@@ -276,3 +276,10 @@ def test_weights_beyond_32_bit_offsets_are_left_to_the_splitk_kernel(host, flags
     assert feature_kernel(host, m, cin, cin, cout, dtype, flags=flags) == "splitk"
     assert feature_kernel(host, m, cin, cin, 40, dtype, flags=B.CONV_RESIDENT) == "resident"
     host.destroy(m)
+
+
+def test_output_rows_beyond_32_bit_pitches_are_left_to_the_splitk_kernel(host):
+    m = host.build(40, OTHER)
+    for ld_out, kernel in ((2**31 - 1, "resident"), (2**31, "splitk"), (2**32 + 32, "splitk")):
+        assert feature_kernel(host, m, 32, 32, 32, flags=B.CONV_RESIDENT, ld_out=ld_out) == kernel
+    host.destroy(m)
