@@ -235,9 +235,13 @@ struct ConvArgs {
 
 // Whether the feature rows are more than the 32-bit offsets of buffer loads reach.
 template <typename T>
+static bool wide_rows(const ConvArgs& a, int64_t rows) {
+  return rows * a.ld_in * int64_t(sizeof(T)) > int64_t(MAX_OFFSET);
+}
+template <typename T>
 static bool wide_rows(const ConvArgs& a) {
   const Level* il = a.m->in_level;
-  return (il->n_host < 0 ? il->cap : il->n_host) * a.ld_in * int64_t(sizeof(T)) > int64_t(MAX_OFFSET);
+  return wide_rows<T>(a, il->n_host < 0 ? il->cap : il->n_host);
 }
 
 // Whether the weights are, in operand order (the plain ones are no more).

@@ -461,7 +461,8 @@ static bool conv_resident(const ConvArgs& a) {
   constexpr int LPC = Mfma<T>::LPC, ELEM = sizeof(T), LDS = 160 * 1024;
   const int K3 = a.m->K3, nb_total = (a.cout + 31) / 32;
   // (plain weights are read at offsets of 32 bits; packed ones need not be, but the choice is the same for both)
-  if (K3 != RES_K3 || a.m->sym || by_channel<T>(a) || wide_rows<T>(a) || wide_weights<T>(a) || a.cin > 8 * LPC) return false;
+  if (K3 != RES_K3 || a.m->sym || by_channel<T>(a) || wide_weights<T>(a) || a.cin > 8 * LPC) return false;
+  if (wide_rows<T>(a, a.m->in_level->cap)) return false;  // (by the level's bound: its count may be known from one call to the next)
   if (a.ld_out > INT32_MAX) return false;  // (the kernel's pitch)
   const int nkk = a.cin <= 2 * LPC ? 1 : a.cin <= 4 * LPC ? 2 : 4;
   const bool two = nb_total % 2 == 0 && nkk < 4;  // 64 columns at a time

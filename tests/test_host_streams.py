@@ -283,3 +283,18 @@ def test_output_rows_beyond_32_bit_pitches_are_left_to_the_splitk_kernel(host):
     for ld_out, kernel in ((2**31 - 1, "resident"), (2**31, "splitk"), (2**32 + 32, "splitk")):
         assert feature_kernel(host, m, 32, 32, 32, flags=B.CONV_RESIDENT, ld_out=ld_out) == kernel
     host.destroy(m)
+
+
+def test_choice_does_not_follow_the_count(host):
+    """Rows that lie beyond 32-bit offsets by the level's bound, and not by its count once the host has asked for it: every kernel has an
+    order of sums of its own, so the layer keeps its kernel."""
+    layers = (B.LayerDesc * 2)(B.LayerDesc(3, 2, 1, 0, B.LAYOUT_OS), B.LayerDesc(3, 2, 2, 0, B.LAYOUT_OS))
+    m, streams = (ctypes.c_void_p * 2)(), (ctypes.c_void_p * 1)(OTHER)
+    assert host.L.spc_build_kmaps_network(ctypes.c_void_p(64), ctypes.c_int64(300_000), ctypes.byref(host.desc), layers, 2, m, streams, 1, 0) == 0
+    a, b = (ctypes.c_void_p(x) for x in m)
+    before = feature_kernel(host, b, 4096, 32, 32, flags=B.CONV_RESIDENT)
+    assert host.L.spc_kmap_n_out(a) == 0  # (the stride-2 level; nothing runs here)
+    assert feature_kernel(host, b, 4096, 32, 32, flags=B.CONV_RESIDENT) == before == "splitk"
+    assert feature_kernel(host, b, 32, 32, 32, flags=B.CONV_RESIDENT) == "resident"
+    host.destroy(a)
+    host.destroy(b)
