@@ -88,7 +88,7 @@ __global__ __launch_bounds__(64 * RES_WAVES) void conv_resident_kernel(const Res
   // of these loads).
   auto touch = [&](const int32_t* p) __attribute__((always_inline)) {
     const unsigned at = static_cast<unsigned>(reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) int*)s_junk));
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(__builtin_amdgcn_readfirstlane(at)), "v"(p) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(__builtin_amdgcn_readfirstlane(at)), "v"(p) : "memory", "m0");
   };
   // ---- steps: (tile, offset), in the order in which this wave takes them
   int mv = 0;            // (matrix) lane i: the mask of tile j with j % 64 == i
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(64 * RES_WAVES) void conv_resident_kernel(const Res
         if (kk < KK) {
           const V* src = reinterpret_cast<const V*>(W) + ((int64_t(k) * KK + kk) * a.nb_total + slab * NB + nb) * 64 + lane;
           const unsigned at = static_cast<unsigned>(reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) V*)(sW + f * 64)));
-          asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(__builtin_amdgcn_readfirstlane(at)), "v"(src) : "memory");
+          asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(__builtin_amdgcn_readfirstlane(at)), "v"(src) : "memory", "m0");
         } else {
           sW[f * 64 + lane] = V{};
         }
