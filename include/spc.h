@@ -68,7 +68,7 @@ extern "C" {
 #define SPC_CONV_PACKED_WEIGHTS 2 /* spc_conv_forward: `weights` came from spc_conv_prepare_weights */
 #define SPC_CONV_OS_PHASE 4  /* spc_conv_forward, OS, 16-bit types: force the LDS-staged phase kernel */
 #define SPC_CONV_OS_SPLITK 8 /* spc_conv_forward, OS, 16-bit types: force the split-k kernel */
-#define SPC_CONV_RESIDENT 16 /* spc_conv_forward: the kernel that keeps the weights in LDS, where the layer has a form of it (else by size) */
+#define SPC_CONV_RESIDENT 16 /* spc_conv_forward: the kernel that keeps the weights in LDS, where the layer has a form of it (else as without the flag: spc_resident_count) */
 #define SPC_CONV_SPLITK_RB(rb) ((rb) << 8) /* with SPC_CONV_OS_SPLITK: 32-row blocks per workgroup (1, 2; 0 = by size); SPC_CONV_RESIDENT: waves per tile */
 #define SPC_NET_SEQUENTIAL 1 /* spc_build_kmaps_network: a launch per level and per map (for comparison) */
 #define SPC_NET_PHASE_BARRIER 2 /* spc_build_kmaps_network: all levels before any map search (always the case but with SPC_NET_SEQUENTIAL) */
@@ -236,6 +236,9 @@ int spc_kmap_search_info(const spc_kmap* m, int32_t* tile_rows, int32_t* window_
  * to the layer stride, as the 2x2x2 stride-2 layers of a UNet) is part of the same build: that map is derived from
  * the twin's pairs (Section 5.5, maps shared between layers). */
 int64_t spc_search_count(void);
+/* Number of feature calls this process has enqueued so far that took the kernel with resident weights (host counter, no wait): tells
+ * whether SPC_CONV_RESIDENT, or the choice by size, came to it. */
+int64_t spc_resident_count(void);
 /* nnz_host [host] int64[K^3]: valid entries per offset.  Waits for the build. */
 int spc_kmap_nnz(spc_kmap* m, int64_t* nnz_host);
 /*
@@ -285,7 +288,7 @@ void spc_kmap_destroy(spc_kmap* m);
  *   Infinities and NaN in features or weights reach an output through its own pairs only, in
  *             every dtype, dataflow and kernel.
  *   flags     SPC_CONV_RELU (NaN becomes 0, as in C's fmax); SPC_CONV_PACKED_WEIGHTS (see spc_conv_prepare_weights);
- *             SPC_CONV_OS_PHASE, SPC_CONV_OS_SPLITK or SPC_CONV_RESIDENT pick one of the MFMA kernels
+ *             SPC_CONV_OS_PHASE, SPC_CONV_OS_SPLITK or SPC_CONV_RESIDENT pick one of the MFMA kernels, at most one of them
  *             (default: chosen from the layer's size; all give the same result up to the
  *             fp32 summation order, and each one alone is bit-reproducible).
  * Every shape and type runs on the matrix cores.  Where the phase kernel is taken, input

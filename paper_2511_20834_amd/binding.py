@@ -41,7 +41,7 @@ ERR_ARG, ERR_RANGE, ERR_DUP, ERR_UNSUPPORTED, ERR_HIP, ERR_NOMEM = -1, -2, -3, -
 EXPORTS = [
     "spc_pack_desc_fit", "spc_pack_coords", "spc_pack_coords_noalloc", "spc_build_kmap", "spc_build_kmap_perm", "spc_build_kmaps_network", "spc_kmap_n_in",
     "spc_kmap_n_out", "spc_kmap_kvol", "spc_kmap_copy_out_keys", "spc_kmap_out_keys", "spc_kmap_in_keys", "spc_kmap_os_map",
-    "spc_kmap_ws_lists", "spc_kmap_nnz", "spc_kmap_search_info", "spc_search_count", "spc_kmap_export_triples", "spc_kmap_set_size_hint", "spc_kmap_destroy",
+    "spc_kmap_ws_lists", "spc_kmap_nnz", "spc_kmap_search_info", "spc_search_count", "spc_resident_count", "spc_kmap_export_triples", "spc_kmap_set_size_hint", "spc_kmap_destroy",
     "spc_conv_forward", "spc_conv_forward_hybrid", "spc_conv_tune_threshold",
     "spc_conv_prepare_weights", "spc_permute_rows",
     "spc_probe_copy", "spc_probe_mfma",
@@ -101,6 +101,7 @@ def lib():
         L.spc_kmap_nnz.argtypes = [vp, ctypes.POINTER(i64)]
         L.spc_kmap_search_info.argtypes = [vp, ctypes.POINTER(i32), ctypes.POINTER(i32)]
         L.spc_search_count.restype = i64
+        L.spc_resident_count.restype = i64
         L.spc_kmap_export_triples.argtypes = [vp, i32, vp, i64, ctypes.POINTER(i64)]
         L.spc_kmap_set_size_hint.argtypes = [vp, i64]
         L.spc_kmap_destroy.argtypes = [vp]
@@ -272,6 +273,11 @@ class KMap:
 def spc_search_count() -> int:
     """Kernel-map searches enqueued by this process so far."""
     return int(lib().spc_search_count())
+
+
+def spc_resident_count() -> int:
+    """Feature calls enqueued by this process so far that took the kernel with resident weights."""
+    return int(lib().spc_resident_count())
 
 
 def spc_kmap_search_info(kmap: KMap):

@@ -1579,12 +1579,13 @@ static int conv_phase(ConvArgs a) {
 }
 
 template <typename T>
-static int conv_typed(const ConvArgs& a) {
+static int conv_typed(ConvArgs a) {
   if (a.packed && !(sizeof(T) == 2 && packed_shape(a.cout, a.any_ws)))
     return set_error(SPC_ERR_ARG, "packed weights given for a shape that does not take them");
   if (a.rows_cap <= 0) return SPC_OK;
   bool phase = false;
   const bool resident = (a.os_variant == 3 || (a.os_variant == 0 && a.splitk_rb == 0)) && conv_resident<T>(a);
+  if (a.os_variant == 3) a.os_variant = a.splitk_rb = 0;  // (without a form of it: as if nothing had been asked for)
   if constexpr (sizeof(T) == 2) {
     phase = !resident && !a.any_ws && a.cout % 32 == 0 && a.os_variant != 2 && (a.os_variant == 1 || !prefer_splitk<T>(a));
     if (phase) SPC_RETURN_IF(conv_phase<T>(a));
@@ -1635,7 +1636,8 @@ static int conv_entry(spc_kmap* m, const void* feats_in, int64_t ld_in, const vo
   a.cout = cout;
   a.relu = (flags & SPC_CONV_RELU) ? 1 : 0;
   a.packed = (flags & SPC_CONV_PACKED_WEIGHTS) ? 1 : 0;
-  if ((flags & SPC_CONV_OS_PHASE) && (flags & SPC_CONV_OS_SPLITK)) return set_error(SPC_ERR_ARG, "two OS kernel variants requested");
+  const int asked_for = flags & (SPC_CONV_OS_PHASE | SPC_CONV_OS_SPLITK | SPC_CONV_RESIDENT);
+  if (asked_for & (asked_for - 1)) return set_error(SPC_ERR_ARG, "two kernel variants requested");
   a.os_variant = (flags & SPC_CONV_OS_PHASE) ? 1 : (flags & SPC_CONV_OS_SPLITK) ? 2 : (flags & SPC_CONV_RESIDENT) ? 3 : 0;
   a.splitk_rb = (flags >> 8) & 7;  // tuning aid: SPC_CONV_OS_SPLITK | (rb << 8), SPC_CONV_RESIDENT | (waves << 8)
   if (a.splitk_rb != 0 && a.splitk_rb != 1 && a.splitk_rb != 2)
@@ -1666,6 +1668,8 @@ static int conv_entry(spc_kmap* m, const void* feats_in, int64_t ld_in, const vo
 }
 
 }  // namespace spc
+
+extern "C" int64_t spc_resident_count(void) { return spc::g_resident_launches.load(std::memory_order_relaxed); }
 
 extern "C" int spc_conv_forward(spc_kmap* m, const void* feats_in, int64_t ld_in, const void* weights, void* feats_out,
                                 int64_t ld_out, int32_t cin, int32_t cout, int32_t dtype, int32_t dataflow, int32_t flags,

@@ -398,6 +398,8 @@ __global__ __launch_bounds__(64 * RES_WAVES) void conv_resident_kernel(const Res
 }
 
 // ---------------------------------------------------------------- dispatch
+static std::atomic<int64_t> g_resident_launches{0};  // see spc_resident_count
+
 template <typename T, int NB, int NKK, int FROM>
 static void launch_resident(const ConvArgs& a, int log_share) {
   ResidentArgs k{};
@@ -433,6 +435,7 @@ static void launch_resident(const ConvArgs& a, int log_share) {
   const int64_t tiles = (a.rows_cap + 31) / 32;
   const int64_t most = std::max<int64_t>(256 / n_slabs / 8, 1), wgs = std::min<int64_t>((tiles + 7) / 8, most);
   hipLaunchKernelGGL((conv_resident_kernel<T, NB, NKK, FROM>), dim3(static_cast<unsigned>(wgs * 8), n_slabs), dim3(64 * RES_WAVES), lds, a.s, k);
+  g_resident_launches.fetch_add(1, std::memory_order_relaxed);
 }
 
 template <typename T, int NB, int NKK>

@@ -298,3 +298,20 @@ def test_choice_does_not_follow_the_count(host):
     assert feature_kernel(host, b, 32, 32, 32, flags=B.CONV_RESIDENT) == "resident"
     host.destroy(a)
     host.destroy(b)
+
+
+def test_at_most_one_kernel_may_be_asked_for(host):
+    m, p = host.build(40, OTHER), ctypes.c_void_p(64)
+    for flags in (B.CONV_OS_PHASE | B.CONV_OS_SPLITK, B.CONV_OS_PHASE | B.CONV_RESIDENT, B.CONV_OS_SPLITK | B.CONV_RESIDENT):
+        assert host.L.spc_conv_forward(m, p, ctypes.c_int64(32), p, p, ctypes.c_int64(32), 32, 32, F16, B.DATAFLOW_OS, flags, OTHER) == B.ERR_ARG
+    host.destroy(m)
+
+
+def test_layers_of_the_resident_kernel_are_counted(host):
+    host.L.spc_resident_count.restype = ctypes.c_int64
+    m = host.build(40, OTHER)
+    for cin, kernel, more in ((32, "resident", 1), (128, "splitk", 0)):
+        before = host.L.spc_resident_count()
+        assert feature_kernel(host, m, cin, cin, 32, flags=B.CONV_RESIDENT) == kernel
+        assert host.L.spc_resident_count() - before == more
+    host.destroy(m)
