@@ -117,6 +117,7 @@ constexpr int BS_MT = 1024;        // merge threads
 constexpr int BS_SPLIT_KPT = 12;   // keys per split thread at most
 constexpr int BS_RANK_SOLO_N = 400000;
 constexpr int BS_NSUB = 4096;      // second split's bins
+constexpr int BS_CROWDED = 128;    // keys of a second bin beyond which all are split once more (see order_crowded)
 constexpr int BS_ARRIVE = 16, BS_ARRIVE_PITCH = 32;  // counters of the workgroups that have read the totals, on lines of their own, and one more
 constexpr int BS_MAX_SPLIT = 1024; // split workgroups
 static_assert(BS_MAX_BIN / 2 <= 8 * BS_MT, "two rounds of bins where there are totals (up to 8192)");
@@ -418,6 +419,7 @@ struct BsOrder {
   using F = BsForm<KeyT, DEDUP>;
   using Elem = typename F::Elem;
   static constexpr int CAP = KPT * BS_MT, WAVES = BS_MT / 64;
+  static_assert(CAP <= BS_NSUB && BS_NSUB <= 1 << 12, "a place for every key, and their numbers in 12 bits");
   static constexpr int VEC = 16 / sizeof(Elem);  // keys of a 16-byte read
   using Vec = Elem __attribute__((ext_vector_type(VEC)));
   struct Lds {
@@ -429,20 +431,25 @@ struct BsOrder {
     int32_t pre[BS_MAX_SPLIT];
     int32_t src[BS_MAX_SPLIT];
     int first, start, lead, last, end, tail, wave_last[WAVES];
-    int taken, done;
+    int taken, done, crowded;
   };
   // A value that all lanes have, to a scalar register: 32-bit keys leave room there, and by them two workgroups share a CU.
   __device__ static int uniform(int v) { return sizeof(KeyT) == 4 ? __builtin_amdgcn_readfirstlane(v) : v; }
-  __device__ static void clear(Lds& L) { reinterpret_cast<int4*>(L.hist)[threadIdx.x] = make_int4(0, 0, 0, 0); }
+  __device__ static void clear(Lds& L) {
+    reinterpret_cast<int4*>(L.hist)[threadIdx.x] = make_int4(0, 0, 0, 0);
+    if (threadIdx.x == 0) L.crowded = 0;
+  }
   // exclusive sums of the second bins' counts in place
   __device__ static void scan(Lds& L) {
     int4* h = reinterpret_cast<int4*>(L.hist) + threadIdx.x;
     const int4 c = *h;
+    if (max(max(c.x, c.y), max(c.z, c.w)) > BS_CROWDED) L.crowded = 1;
     int total;
     const int x = block_scan<WAVES>(c.x + c.y + c.z + c.w, L.sums, &total);
     *h = make_int4(x, x + c.x, x + c.x + c.y, x + c.x + c.y + c.z);
     if (threadIdx.x == 0) L.hist[BS_NSUB] = total;
   }
+  template <bool AGAIN>
   __device__ static void order(Lds& L, Elem (&k)[KPT], int32_t (&v)[KPT], int count, KeyT base, KeyT lim, int ss, const int t) {
     auto second = [&](Elem e) { return static_cast<int>((min(max(F::key(e), base), lim) - base) >> ss); };
     int r[KPT];
@@ -452,6 +459,12 @@ struct BsOrder {
     __syncthreads();
     scan(L);
     __syncthreads();
+    if constexpr (AGAIN) {
+      if (__builtin_expect(L.crowded, 0)) {
+        order_crowded(L, k, v, r, count, base, lim, ss, t);
+        return;
+      }
+    }
 #pragma unroll
     for (int u = 0; u < KPT; ++u)
       if (u * BS_MT + t < count) {
@@ -492,6 +505,65 @@ struct BsOrder {
       if (u * BS_MT + t < count) {
         L.key[d[u]] = k[u];
         if constexpr (F::ROWS) L.row[d[u]] = v[u];
+      }
+    __syncthreads();
+  }
+  // The rest of order() where a second bin has many keys: every one is split once more, into as many places as it has keys, by where a
+  // key lies between its bounds.  A key is compared with all of its second bin, and these cover the workgroup's whole range of bins:
+  // where that is long and mostly empty (in front of a voxel that lies far away, between a LiDAR cloud's rings), a few of them hold
+  // what there is, up to a thousand keys, and one workgroup took longer than all others.  us of pack + sort without / with: 300 k in a box beside one far
+  // voxel 34.1 / 18.5, with 64-bit keys 51.3 / 20.4, LiDAR 200 k (shares of 512 positions) 17.9 / 16.5, 260 k 30.8 / 21.3, 310 k 45.7 / 23.0, with 64-bit
+  // keys 71.7 / 27.0; a level with its map, LiDAR 310 k 45.6 / 36.3, 350 k 52.3 / 36.9; clouds without such bins the same (random 500 k 24.7 / 24.6).
+  // Not for the bins that several workgroups share (crowd): with it there the kernel would not keep its registers.
+  __device__ static void order_crowded(Lds& L, Elem (&k)[KPT], int32_t (&v)[KPT], int (&r)[KPT], int count, KeyT base, KeyT lim, int ss, int t) {
+    asm volatile("" : "+v"(t));  // (what is derived from it is not to be kept in registers from before)
+    const int cut = max(ss - 20, 0);  // (20 bits of the key and 12 of the count)
+#pragma unroll
+    for (int u = 0; u < KPT; ++u)
+      if (u * BS_MT + t < count) {
+        const KeyT d = min(max(F::key(k[u]), base), lim) - base;
+        const int b = static_cast<int>(d >> ss), lo = L.hist[b];
+        const uint32_t low = static_cast<uint32_t>((d & ((KeyT(1) << ss) - 1)) >> cut), n = L.hist[b + 1] - lo;
+        r[u] = lo + static_cast<int>((low * n) >> (ss - cut));
+      }
+    __syncthreads();
+    clear(L);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < KPT; ++u)
+      if (u * BS_MT + t < count) r[u] |= atomicAdd(&L.hist[r[u]], 1) << 16;  // (place | which of its keys)
+    __syncthreads();
+    scan(L);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < KPT; ++u)
+      if (u * BS_MT + t < count) L.key[L.hist[r[u] & 0xffff] + (r[u] >> 16)] = k[u];
+    if (t < 8) L.key[count + t] = ~Elem(0);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < KPT; ++u)
+      if (u * BS_MT + t < count) {
+        const int first = L.hist[r[u] & 0xffff], at = first + (r[u] >> 16), lo = first & -VEC, hi = L.hist[(r[u] & 0xffff) + 1];
+        int c = lo;
+#pragma unroll 1
+        for (int s = lo; s < hi; s += 8) {
+          Vec e[8 / VEC];
+#pragma unroll
+          for (int x = 0; x < 8 / VEC; ++x) e[x] = reinterpret_cast<const Vec*>(L.key + s)[x];
+#pragma unroll
+          for (int x = 0; x < 8; ++x) {
+            const Elem o = e[x / VEC][x % VEC];
+            c += o < k[u] || (!F::REC && o == k[u] && s + x < at) ? 1 : 0;
+          }
+        }
+        r[u] = c;
+      }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < KPT; ++u)
+      if (u * BS_MT + t < count) {
+        L.key[r[u]] = k[u];
+        if constexpr (F::ROWS) L.row[r[u]] = v[u];
       }
     __syncthreads();
   }
@@ -681,7 +753,7 @@ struct BsOrder {
           }
         clear(L);
         __syncthreads();
-        order(L, k, v, count, by_row ? low : low + (KeyT(b) << sh), lim, by_row ? 0 : max(0, sh + log2_up(b1 - b) - 12), tt);
+        order<false>(L, k, v, count, by_row ? low : low + (KeyT(b) << sh), lim, by_row ? 0 : max(0, sh + log2_up(b1 - b) - 12), tt);
         if (kept == 0) *at = x;
         kept += store(L, a, DEDUP ? level_ws(a.out_k, a.ws_pitch) : a.out_k, count, DEDUP ? *at + kept : x, tt);
         x = x1;
@@ -833,7 +905,7 @@ __global__ __launch_bounds__(BS_MT, sizeof(KeyT) == 4 ? 8 : 4) void bs_merge_ker
         k[u] = recs[at];
         if constexpr (F::ROWS) v[u] = a.rows[at];
       }
-    O::order(L, k, v, W, base, lim, ss, t);
+    O::template order<true>(L, k, v, W, base, lim, ss, t);
     kept = O::store(L, a, out_k, W, start, t);
   }
   if constexpr (DEDUP) {

@@ -121,6 +121,30 @@ def test_crowded_bins_are_shared(kind):
     assert times[1][0] < 15 * times[0][0] and times[1][1] < 15 * times[0][1], times
 
 
+# (the last workgroup takes what is left of the box and the far voxel's bin: a few second bins hold all its keys)
+@pytest.mark.parametrize("n,dims,far", [(6000, (40, 20, 20), (4000, 0, 0)), (120_000, (60, 60, 60), (1500, 10, 10)), (200_001, (70, 70, 70), (2000, 10, 10)),
+                                        (300_000, (80, 80, 80), (2000, 10, 10)), (300_001, (400, 400, 100), (4000, 4000, 100)),
+                                        (524_288, (96, 96, 96), (500, 10, 10)), (700_000, (110, 110, 110), (2000, 10, 10))])
+@pytest.mark.parametrize("key_bits", [0, 64])
+def test_second_bins_that_hold_many(n, dims, far, key_bits):
+    c = _dense(n, dims, n, far)
+    _check(c, fit_desc(c, [(3, 1, 2)], key_bits))
+
+
+@pytest.mark.parametrize("key_bits", [0, 64])
+def test_a_far_voxel_costs_no_more_than_a_spread_cloud(key_bits):
+    """300 k voxels in a box beside one far away: 0.9 times as long as spread ones; 1.7 (64-bit keys 2.3) where the last workgroup compared all its keys with each other."""
+    n, times = 300_000, []
+    for c in (_dense(n, (350, 350, 200), 5, (0, 0, 0)), _dense(n, (80, 80, 80), 5, (2000, 10, 10))):
+        c = np.unique(c, axis=0)
+        c = np.random.default_rng(6).permutation(c).astype(np.int32)
+        desc, d = fit_desc(c, [(3, 1, 2)], key_bits), torch.from_numpy(c).cuda()
+        ws = torch.empty(B.spc_pack_workspace_bytes(len(c), desc), dtype=torch.uint8, device="cuda")
+        keys, perm = B.spc_pack_coords(d, desc)
+        times.append(_microseconds(lambda: [B.spc_pack_coords(d, desc, True, 0, None, ws, keys, perm) for _ in range(10)]))
+    assert times[1] < 1.3 * times[0], times
+
+
 @pytest.mark.parametrize("n", [4096, 5000, 70_000, 230_000, 524_289, 1_300_001])
 @pytest.mark.parametrize("key_bits", [0, 64])
 def test_two_distant_clusters(n, key_bits):

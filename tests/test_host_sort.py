@@ -56,6 +56,7 @@ CLOUDS = {
     "few": (9000, (10, 10, 10)),       # four, and some others
     "rejected": (9000, (10, 10, 9)),   # half of the rows do not fit
     "band": (5200, (8, 12, 8)),        # bins that fit the LDS alone, but not beside others
+    "outlier": (6000, (12, 9, 9)),     # the last workgroup's bins reach from a box to a voxel far away: all keys in a few second bins
     "large": (524_289, (11, 11, 8)),   # the smallest whose bins' starts a kernel of its own finds
 }
 
@@ -77,6 +78,8 @@ def cloud(kind, rng):
         c = np.concatenate([box(n - 1, (2, 300, 300)), [[top[0] - 1, 0, 0]]])
     elif kind == "cluster":
         c = np.concatenate([box(n - 1, (30, 30, 30)), [[t - 1 for t in top]]])
+    elif kind == "outlier":
+        c = np.concatenate([box(n - 1, (40, 20, 20)), [[top[0] - 1, 0, 0]]])
     elif kind == "one":
         c = np.tile([[5, 6, 7]], (n, 1))
     elif kind == "few":
