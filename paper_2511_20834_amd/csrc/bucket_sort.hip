@@ -1410,7 +1410,7 @@ BucketPlan bucket_plan(int64_t n, int used_bits, bool unique) {
   // 60 k 13.2 / 12.3, 120 k 16.8 / 14.4 / 13.3, 180 k 21.7 / 16.4 / 14.9, 240 k - / 21.8 / 19.0, 500 k - / 39.3 / 32.0; of a level with its map,
   // whose sorted keys add to few bins: 20 k 18.0 / 19.9, 60 k 20.5 / 20.8, 120 k 22.3 / 23.5 / 24.0, 180 k 27.1 / 28.1 / 28.8, 500 k
   // 53.1 / 48.8 / 48.7.  The lines for coordinates were drawn where they are scattered (recorded sorts: 180 k 25.4 / 26.2 with 2048 / 4096).
-  const int share = n <= BS_SHORT_N ? BS_SHORT_SHARE : p.add && (unique || n <= BS_MID_N) ? BS_ADD_SHARE : 4096;
+  const int share = n <= BS_SHORT_N ? BS_SHORT_SHARE : p.add && (unique || n <= BS_MID_N) ? BS_ADD_SHARE : BS_LONG_SHARE;
   int n_wg = static_cast<int>(std::min<int64_t>(std::max<int64_t>((n + share - 1) / share, 1), p.add ? n : BS_MAX_WG));
   p.per = static_cast<int>(((n + n_wg - 1) / n_wg + BS_WIDE - 1) / BS_WIDE * BS_WIDE);
   p.n_wg = static_cast<int>(std::max<int64_t>((n + p.per - 1) / p.per, 1));
@@ -1604,6 +1604,7 @@ void split_merge(const Src& src, int64_t n, int used_bits, const SplitPlan& p, c
     hipLaunchKernelGGL((bs_merge_kernel<KeyT, DEDUP, KPT, FROM>), dim3(p.n_share, n_levels), dim3(BS_MT), 0, s, a);
   };
   if (!t.p && !DEDUP && b.add) {  // (few regions)
+    static_assert(BS_MID_N / BS_LONG_SHARE >= BS_SUM_WG, "never where workgroups merge wide: this form takes 512 positions");
     if constexpr (!DEDUP) merge(std::false_type{}, std::integral_constant<int, BS_TABLE>{});
     return;
   }

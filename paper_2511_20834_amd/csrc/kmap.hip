@@ -921,6 +921,9 @@ static void launch_search(spc_kmap* const* ms, int count, hipStream_t s) {
 
 template <typename KeyT>
 static int launch_search_k(spc_kmap* const* ms, int count, hipStream_t s) {
+  // (search_tile gives a map with lists no longer ones: their records would not fit)
+  if (ms[0]->tile > 128 && (ms[0]->desc.layout & SPC_LAYOUT_WS))
+    return set_error(SPC_ERR_UNSUPPORTED, "lists are not built by tiles of %d rows", ms[0]->tile);
   auto by_tile = [&](auto K_) {
     constexpr int K = decltype(K_)::value;
     switch (ms[0]->tile) {

@@ -235,7 +235,7 @@ inline bool use_bucket_sort(int64_t n) { return n >= BS_MIN_N && n <= BS_MAX_N; 
 // (some 35 per ns, and hardly two keys of a workgroup share a bin) would take longer than a launch that sums the table's columns
 // (pack + sort of 500 k random voxels with them 24.3 us, without 21.8; below the line eager sorts keep to two launches).
 constexpr int64_t BS_ADD_N = 524288, BS_MID_N = 200000, BS_SHORT_N = 65536;
-constexpr int BS_ADD_SHARE = 2048, BS_SHORT_SHARE = 1024;
+constexpr int BS_ADD_SHARE = 2048, BS_SHORT_SHARE = 1024, BS_LONG_SHARE = 4096;
 // Up to so many workgroups their counts are summed where they are read, where totals would have to be cleared first: a launch
 // less, but every workgroup reads the whole table.  Replayed pack + sort, us, cleared / summed: 4.2 k 20.8 / 17.2, 14 k 21.1 / 18.3, 33 k
 // (32 workgroups) 22.4 / 20.5, 40 k 23.6 / 24.1, 60 k 24.0 / 27.8.
