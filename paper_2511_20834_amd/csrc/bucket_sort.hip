@@ -1460,12 +1460,16 @@ Ws<KeyT> carve(void* ws, int64_t n) {
 
 // Split + merge: sizes of both kernels' shares.
 // Levels of more keys: wide workgroups merge also where the totals are read (coordinates: above BS_MID_N).  There are a quarter as many then, and
-// each reads all totals first; below, they are too few for the chip.  us, narrow / wide: pack + sort, LiDAR 160 k 15.9 / 20.5, 199 k 15.7 / 19.9, 205 k 30.4 /
-// 23.0, indoor 180 k 18.2 / 17.7, 240 k 19.9 / 19.5, 320 k 26.1 / 21.9, with 64-bit keys 240 k 26.3 / 21.5, random 180 k 15.9 / 16.2, 300 k 24.5 / 19.6, 500 k 32.4 /
-// 24.3, with 64-bit keys 44.4 / 27.4; a level with its map, LiDAR 190 k 24.0 / 31.1, 260 k 28.2 / 32.1, indoor 240 k 30.0 / 32.0, 320 k 38.3 / 34.7, random 300 k
-// 37.0 / 32.4, 500 k 47.2 / 41.0, with 64-bit keys 57.0 / 43.8.
-// (Bins that just fit a wide workgroup lose: 300 k in a box beside one far voxel 20 / 34; those that do not fit a narrow one win: 260 k in three planes
-// 172 / 137, 524 k in four 403 / 186.)
+// each reads all totals first; below, they are too few for the chip.  us, narrow / wide:
+//   pack + sort   LiDAR 160 k 15.9 / 20.5, 199 k 15.7 / 19.9 (measured before order_crowded), 210 k 20.5 / 22.2, 240 k 20.2 / 21.4, 270 k 37.0 / 21.5, 310 k
+//                 38.3 / 22.7, 350 k 26.1 / 23.6, indoor 180 k 18.2 / 17.7, 210 k 19.6 / 19.2, 290 k 25.8 / 21.3, 400 k 29.7 / 25.0, random 180 k 15.9 / 16.2, 210 k 18.4 /
+//                 17.8, 290 k 24.4 / 19.7, 400 k 29.7 / 22.3; 64-bit keys, LiDAR 210 k 28.4 / 28.5, 310 k 50.5 / 26.7, indoor 210 k 25.4 / 21.2, random 400 k 41.8 / 25.2
+//   a level with its map   LiDAR 240 k 31.7 / 33.8, 290 k 33.1 / 35.0, 310 k 33.4 / 36.2, 350 k 33.8 / 37.6, indoor 250 k 36.2 / 38.6, 290 k 43.3 / 41.2, 320 k 45.8 / 43.5, 400 k
+//                 54.4 / 50.1, random 250 k 35.7 / 36.8, 290 k 43.6 / 41.1, 400 k 51.7 / 46.8; 64-bit keys, LiDAR 240 k 37.8 / 36.2, 350 k 42.5 / 41.0, indoor 290 k 53.7 / 46.0
+// So the line for levels is where indoor and random scenes cross; LiDAR clouds of 32-bit keys, whose levels hold fewer keys, lose two to four us above it
+// (64-bit keys would gain below it already).
+// (Bins that do not fit a narrow workgroup: 260 k in three planes 171 / 138, 524 k in four 403 / 189, 300 k in a box beside a voxel so far away that its
+// bins are of 2900 keys 51.7 / 19.0, 64-bit keys 71.2 / 21.3; of 1500 20.1 / 18.4.)
 constexpr int64_t BS_WIDE_LEVEL_N = 300000;
 struct SplitPlan {
   BucketPlan b;
