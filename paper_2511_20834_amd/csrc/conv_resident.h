@@ -400,6 +400,9 @@ __global__ __launch_bounds__(64 * RES_WAVES) void conv_resident_kernel(const Res
 // ---------------------------------------------------------------- dispatch
 static std::atomic<int64_t> g_resident_launches{0};  // see spc_resident_count
 
+// Workgroups of a slab: one per CU for all slabs together, in equal numbers per XCD.
+static int64_t resident_workgroups(int n_slabs) { return std::max<int64_t>(32 / n_slabs, 1) * 8; }
+
 template <typename T, int NB, int NKK, int FROM>
 static void launch_resident(const ConvArgs& a, int log_share) {
   ResidentArgs k{};
@@ -433,8 +436,8 @@ static void launch_resident(const ConvArgs& a, int log_share) {
   k.vec_store = a.cout % Mfma<T>::LPC == 0 && a.ld_out % Mfma<T>::LPC == 0 && reinterpret_cast<uintptr_t>(a.out) % 16 == 0;
   const int n_slabs = (k.nb_total + NB - 1) / NB;
   const int64_t tiles = (a.rows_cap + 31) / 32;
-  const int64_t most = std::max<int64_t>(256 / n_slabs / 8, 1), wgs = std::min<int64_t>((tiles + 7) / 8, most);
-  hipLaunchKernelGGL((conv_resident_kernel<T, NB, NKK, FROM>), dim3(static_cast<unsigned>(wgs * 8), n_slabs), dim3(64 * RES_WAVES), lds, a.s, k);
+  const int64_t wgs = std::min<int64_t>((tiles + 7) / 8 * 8, resident_workgroups(n_slabs));
+  hipLaunchKernelGGL((conv_resident_kernel<T, NB, NKK, FROM>), dim3(static_cast<unsigned>(wgs), n_slabs), dim3(64 * RES_WAVES), lds, a.s, k);
   g_resident_launches.fetch_add(1, std::memory_order_relaxed);
 }
 
@@ -443,6 +446,16 @@ static void launch_resident_from(const ConvArgs& a, int log_share) {
   if (!a.any_ws) launch_resident<T, NB, NKK, RES_MATRIX>(a, log_share);
   else if (!a.any_os) launch_resident<T, NB, NKK, RES_LISTS>(a, log_share);
   else launch_resident<T, NB, NKK, RES_BOTH>(a, log_share);
+}
+
+// Whether a layer's slabs and rows give all CUs work.  Every workgroup brings the weights of its slab, and a slab's tiles go to the XCDs in chunks:
+// with few rows some XCDs have a chunk more than others.  us, split-k kernel / this: plain 64->1056 (33 slabs: a second round) 5 k rows half-filled 66 / 83, random
+// 32 / 45, packed 41 / 79; 64->544 (17: 136 workgroups) 30 k 123 / 132, random 54 / 61; fp32 32->1024 5 k 114 / 131, 32->2048 2 k 93 / 143, 32->544 30 k 314 / 493,
+// random 126 / 204; but 64->800 (25: 200) 30 k 182 / 140, plain 32->2048 5 k 63 / 35, lists 64->1024 5 k 63 / 52, fp32 32->1024 8.2 k 182 / 138.
+template <typename T>
+static bool resident_fills(int64_t rows, int n_slabs) {
+  const int64_t wgs = resident_workgroups(n_slabs) * n_slabs;
+  return wgs <= 256 && wgs >= (sizeof(T) == 4 ? 240 : 192) && rows >= (sizeof(T) == 4 ? 8192 : 4096);
 }
 
 // Whether a layer is taken (or asked for: os_variant 3), from what it is and from the rows that its level presumably holds: the
@@ -477,7 +490,7 @@ static bool conv_resident(const ConvArgs& a) {
   else if (a.any_ws) least = even && !two ? 4200 : 2500;
   else if (a.cout % 64 == 0) least = two ? 4097 : INT64_MAX;
   else least = a.cout % 32 != 0 ? 1600 : 3000;
-  if (a.os_variant != 3 && tiles < least) return false;
+  if (a.os_variant != 3 && (tiles < least || !resident_fills<T>(a.m->out_level->presumed, n_slabs))) return false;
   int log_share = a.splitk_rb ? a.splitk_rb - 1 : (ELEM == 2 && tiles >= 8000) || (two && tiles >= 2000) ? 0 : 1;
   if (resident_lds(K3, nkk, two ? 2 : 1, ELEM, log_share) > LDS) log_share = 1;
   if (resident_lds(K3, nkk, two ? 2 : 1, ELEM, log_share) > LDS) return false;

@@ -64,9 +64,9 @@ class Host:
         assert self.L.spc_pack_coords(coords, ctypes.c_int64(n), ctypes.byref(self.desc), keys, None, ws, *args) == 0
         return self.log()
 
-    def build(self, n, stream, layer_stride=1):
+    def build(self, n, stream, layer_stride=1, layout=B.LAYOUT_OS):
         m = ctypes.c_void_p()
-        l = B.LayerDesc(3, 1, layer_stride, 0, B.LAYOUT_OS)
+        l = B.LayerDesc(3, 1, layer_stride, 0, layout)
         assert self.L.spc_build_kmap(ctypes.c_void_p(64), ctypes.c_int64(n), ctypes.byref(self.desc), ctypes.byref(l), ctypes.byref(m), stream) == 0
         return m
 
@@ -314,4 +314,14 @@ def test_layers_of_the_resident_kernel_are_counted(host):
         before = host.L.spc_resident_count()
         assert feature_kernel(host, m, cin, cin, 32, flags=B.CONV_RESIDENT) == kernel
         assert host.L.spc_resident_count() - before == more
+    host.destroy(m)
+
+
+# (33 and 64 slabs of columns: more than one round of workgroups; 17: half of the CUs; too few rows for all XCDs)
+@pytest.mark.parametrize("n,dtype,cin,cout,taken", [
+    (5000, F16, 64, 1056, False), (30_000, F16, 64, 544, False), (30_000, F32, 32, 544, False), (2000, F32, 32, 2048, False), (5000, F32, 32, 1024, False),
+    (4000, F16, 32, 2048, False), (5000, F16, 32, 2048, True), (30_000, F16, 64, 800, True), (8200, F32, 32, 1024, True), (12_000, F16, 32, 1600, True)])
+def test_layers_that_leave_cus_idle_are_not_the_resident_kernels(host, n, dtype, cin, cout, taken):
+    m = host.build(n, OTHER)
+    assert (feature_kernel(host, m, cin, cin, cout, dtype) == "resident") == taken
     host.destroy(m)
