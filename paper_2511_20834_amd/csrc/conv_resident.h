@@ -459,8 +459,8 @@ static bool resident_fills(int64_t rows, int n_slabs) {
 }
 
 // Whether a layer is taken (or asked for: os_variant 3), from what it is and from the rows that its level presumably holds: the
-// waves that share a tile are the order of the sums, which is to stay when the host learns the count between two calls, and whatever the
-// form of the weights.  us, other kernel / this, at the lines (tiles of all slabs; LiDAR, random, indoor scenes):
+// waves that share a tile are the order of the sums, which is to stay when the host learns the count between two calls.  us, other kernel /
+// this, at the lines (tiles of all slabs; LiDAR, random, indoor scenes):
 //   lists, 16 bits        32->32  60 k 12.3 / 10.7, 70 k 10.7 / 10.9, 60 k 9.7 / 9.8; 64->96 40 k 38.9 / 24.5, 28.0 / 20.7
 //     64 channels at a time would do (64->64, 64->128)  45 k 20.6 / 17.9, 70 k 19.5 / 19.4, 60 k 17.0 / 18.6; 40 k 27.6 / 25.2, 20.2 / 19.9
 //   matrix, 16 bits       32->32  75 k 10.5 / 10.2, 110 k 11.4 / 10.6, 120 k 13.1 / 11.9; 48->96 30 k 17.7 / 15.7, 14.1 / 13.5
@@ -469,6 +469,11 @@ static bool resident_fills(int64_t rows, int n_slabs) {
 //     never prepacked      24->40  45 k 14.3 / 12.8, 70 k 16.7 / 13.8, 60 k 14.2 / 11.4; 30 k 11.5 / 12.3, 9.2 / 11.6
 //   fp32                  32->64  30 k 34.7 / 30.5, 25.5 / 23.1; 16->64 70 k 33.0 / 31.0, 27.7 / 26.4
 //     32 columns at a time  32->32 160 k 52.6 / 54.3, 200 k 61.9 / 60.8, 150 k 44.4 / 43.1; lists 75 k 38.9 / 38.8, 110 k 42.6 / 39.1
+// Three slabs of input channels (16 bits 33 to 48, fp32 17 to 24) are gathered, read and multiplied as four, where the split-k kernel takes three.  So not in
+//   fp32                  20->128 LiDAR 80 k 75.3 / 93.2, random 66.4 / 76.8, indoor 68.3 / 81.7; 24->64 49.6 / 52.1, 43.7 / 43.3, 44.6 / 45.8
+//   lists, prepacked      64 columns at a time  48->64 LiDAR 90 k 25.2 / 25.4, random 70 k 16.9 / 18.9, indoor 100 k 22.9 / 25.3, half as many rows of a level of stride 2 12.4 / 16.4
+//     (but plain 48->64 37.7 / 27.8, 26.3 / 21.2, 37.5 / 27.4); 40->32 80 k 17.6 / 17.1, 13.5 / 14.5, 14.1 / 14.3, 200 k as the others
+//   matrix, ragged columns, one slab  40->8 52 k 13.4 / 14.7, 10.7 / 12.6, 9.8 / 12.1; 100 k 21.4 / 18.8, 16.6 / 15.8, 17.5 / 16.4
 // 2x2x2 layers are over before the weights pay (50 k rows 64->64 9.8 / 12.3).
 // A wave to a tile where there are tiles enough for all, two where not: 32->32 lists 45 k 12.3 / 9.5, 250 k 20.4 / 21.3, 10^6 51 / 60; with 64 columns at a time
 // two have twice the sums to exchange: 32->64 lists 60 k 15.0 / 13.8, 75 k 16.2 / 16.7, 10^6 71 / 86.
@@ -490,6 +495,11 @@ static bool conv_resident(const ConvArgs& a) {
   else if (a.any_ws) least = even && !two ? 4200 : 2500;
   else if (a.cout % 64 == 0) least = two ? 4097 : INT64_MAX;
   else least = a.cout % 32 != 0 ? 1600 : 3000;
+  if ((a.cin + 2 * LPC - 1) / (2 * LPC) == 3) {  // (a slab of four is empty)
+    if (ELEM == 4) least = INT64_MAX;
+    else if (a.any_ws && a.packed) least = even ? INT64_MAX : 6000;
+    else if (!a.any_ws && a.cout % 32 != 0 && !even) least = 3000;
+  }
   if (a.os_variant != 3 && (tiles < least || !resident_fills<T>(a.m->out_level->presumed, n_slabs))) return false;
   int log_share = a.splitk_rb ? a.splitk_rb - 1 : (ELEM == 2 && tiles >= 8000) || (two && tiles >= 2000) ? 0 : 1;
   if (resident_lds(K3, nkk, two ? 2 : 1, ELEM, log_share) > LDS) log_share = 1;

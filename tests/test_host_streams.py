@@ -325,3 +325,16 @@ def test_layers_that_leave_cus_idle_are_not_the_resident_kernels(host, n, dtype,
     m = host.build(n, OTHER)
     assert (feature_kernel(host, m, cin, cin, cout, dtype) == "resident") == taken
     host.destroy(m)
+
+
+# (three slabs of 16 channels, fp32 of 8, are taken as four)
+@pytest.mark.parametrize("n,dtype,cin,cout,ws,packed,taken", [
+    (200_000, F32, 20, 64, False, False, False), (200_000, F32, 24, 32, True, False, False), (200_000, F32, 28, 64, False, False, True), (200_000, F32, 16, 64, True, False, True),
+    (200_000, F16, 48, 64, True, True, False), (200_000, F16, 40, 128, True, True, False), (200_000, F16, 48, 64, True, False, True), (200_000, F16, 56, 64, True, True, True),
+    (200_000, F16, 32, 64, True, True, True), (100_000, F16, 48, 32, True, True, False), (200_000, F16, 48, 32, True, True, True), (100_000, F16, 48, 32, True, False, True),
+    (80_000, F16, 40, 8, False, False, False), (100_000, F16, 40, 8, False, False, True), (80_000, F16, 24, 8, False, False, True)])
+def test_layers_of_three_slabs_of_channels_are_taken_where_four_pay(host, n, dtype, cin, cout, ws, packed, taken):
+    m = host.build(n, OTHER, layout=B.LAYOUT_WS if ws else B.LAYOUT_OS)
+    kernel = feature_kernel(host, m, cin, cin, cout, dtype, B.DATAFLOW_WS if ws else B.DATAFLOW_OS, B.CONV_PACKED_WEIGHTS if packed else 0)
+    assert (kernel == "resident") == taken
+    host.destroy(m)
