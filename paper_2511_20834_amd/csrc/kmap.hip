@@ -119,7 +119,10 @@ __device__ inline int half_wave_bound(const SPC_GLOBAL KeyT* keys, int n, const 
 // 30 k voxels 5.4 / 6.3 / 9.0, 120 k 9.6 / 10.9 / 14.9, 150 k 10.6 / 11.7 / 16.0, 190 k 12.5 / 12.4 / 16.2, 300 k 16.7 / 16.1 / 15.8, 500 k 24.3 / 21.4 /
 // 19.4, 10^6 42.6 / 36.2 / 32.2, 3 * 10^6 124 / 102 / 92; 64-bit keys 400 k 23.1 / 21.5 / 24.1, 600 k 31.5 / 28.4 / 29.7, 10^6 49.0 / 41.5 / 41.9; with lists, whose
 // records of 256 rows leave a CU few workgroups, 400 k 41.8 / 36.4 / 42.2, 10^6 85 / 71 / 79, 2.5 * 10^6 193 / 156 / 169; 5x5x5, 64 / 128 rows: 30 k 10.6 / 13.1, 240 k 44 / 46.
+// (1x1x1, whose rows cost next to nothing and whose list's counts are one column: 64 / 128 / 256 rows, 160 k 8.3 / 5.8 / 7.0, 300 k 8.8 / 7.0 / 7.8, 600 k 12.0 / 9.3 / 8.9, 64-bit keys
+// 12.9 / 10.6 / 9.1; with lists 160 k 14.7 / 12.9 / 14.0, 600 k 30.1 / 22.3 / 19.2, 2 * 10^6 82.7 / 53.3 / 40.8.)
 inline int search_tile(int K, int64_t n_out, int key_bits, bool lists) {
+  if (K == 1) return n_out < 150000 ? 64 : n_out < 400000 ? 128 : 256;
   if (K > 3 || n_out < 185000) return 64;
   return lists || n_out < (key_bits == 32 ? 400000 : 1000000) ? 128 : 256;
 }
@@ -706,7 +709,9 @@ __global__ __launch_bounds__(256) void ws_fill_pairs_kernel(const int2* __restri
 
 // Counts up to which the fill pass adds them up itself: build with lists, 4.1 k voxels 13.8 -> 12.0 us, 20 k (8451 counts)
 // 15.7 / 15.2, 30 k 16.5 / 16.6, 60 k 19.6 / 21.7.
-constexpr int64_t WS_SCAN_IN_FILL = 6144;
+// Eight threads add a column, so that no column may be long: 1x1x1, added / scanned, 20 k (313 tiles) 9.5 / 11.0, 40 k (625) 12.2 / 10.7, tiles of 128 rows 60 k (469) 11.9 /
+// 11.9, 200 k 18.6 / 13.2, 600 k 47.3 / 22.3.
+constexpr int64_t WS_SCAN_IN_FILL = 6144, WS_TILES_IN_FILL = 448;
 // One workgroup per offset k: exclusive scan of that offset's per-tile counts in place, total into nnz[k].
 // A thread owns a run of consecutive tiles; the runs are fetched in batches of WS_SCAN_U loads per thread that are
 // all in flight together (a loop of load, scan, store rounds over 256 tiles at a time took 7.6 us for 3750 tiles:
@@ -908,7 +913,7 @@ static void launch_search(spc_kmap* const* ms, int count, hipStream_t s) {
     if (n_tiles == 0) continue;
     using One = std::integral_constant<int, 1>;
     using Most = std::integral_constant<int, MOST>;
-    if constexpr (TILE < 256) {  // (longer tiles have no lists)
+    if constexpr (TILE < 256 || K == 1) {  // (longer tiles of others have no lists)
       if (pairs) {
         n == 1 ? go(std::true_type{}, One{}, first, n, n_tiles) : go(std::true_type{}, Most{}, first, n, n_tiles);
         continue;
@@ -922,7 +927,7 @@ static void launch_search(spc_kmap* const* ms, int count, hipStream_t s) {
 template <typename KeyT>
 static int launch_search_k(spc_kmap* const* ms, int count, hipStream_t s) {
   // (search_tile gives a map with lists no longer ones: their records would not fit)
-  if (ms[0]->tile > 128 && (ms[0]->desc.layout & SPC_LAYOUT_WS))
+  if (ms[0]->tile > 128 && ms[0]->desc.K > 1 && (ms[0]->desc.layout & SPC_LAYOUT_WS))
     return set_error(SPC_ERR_UNSUPPORTED, "lists are not built by tiles of %d rows", ms[0]->tile);
   auto by_tile = [&](auto K_) {
     constexpr int K = decltype(K_)::value;
@@ -1109,7 +1114,7 @@ static int search_maps(spc_kmap* const* ms, int count, const StreamId& s) {
                          m->out_cap, m->k_lim, m->list_base);
     };
     // (a level that may turn out empty leaves its list lengths to the scan)
-    if (out->n_host > 0 && int64_t(m->n_tiles) * m->k_lim <= WS_SCAN_IN_FILL) {
+    if (out->n_host > 0 && m->n_tiles <= WS_TILES_IN_FILL && int64_t(m->n_tiles) * m->k_lim <= WS_SCAN_IN_FILL) {
       fill(std::true_type{});
     } else {
       hipLaunchKernelGGL(ws_scan_kernel, dim3(m->K3), dim3(WS_SCAN_THREADS), 0, s, m->tile_counts, m->n_tiles, m->tile, n_out_h,

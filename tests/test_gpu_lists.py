@@ -33,3 +33,20 @@ def test_lists(K, n, density, key_bits):
         m = B.spc_build_kmap(keys, desc, K, 1, 1, 0, layout, in_perm=perm)
         assert np.array_equal(m.export_triples(B.LAYOUT_WS), ref)
         m.destroy()
+
+
+# (counts added by the fill pass up to 448 tiles, scanned beyond; tiles of 128 rows from 150 k on, 256 from 400 k)
+@pytest.mark.parametrize("n", [1, 28_672, 28_673, 149_999, 150_000, 400_000, 524_289])
+@pytest.mark.parametrize("key_bits", [0, 64])
+def test_lists_of_one_offset(n, key_bits):
+    c, _ = oracle.sort_coords(_cloud(n, 0.2, n))
+    desc = fit_desc(c, [(1, 1, 1)], key_bits)
+    keys, perm = B.spc_pack_coords(torch.from_numpy(c).cuda(), desc)
+    ref = oracle.triples(oracle.layer(c, 1, 1, 1)[1])
+    F = torch.randn(n, 8, device="cuda")
+    for layout in (B.LAYOUT_WS, B.LAYOUT_BOTH):
+        m = B.spc_build_kmap(keys, desc, 1, 1, 1, 0, layout, in_perm=perm)
+        assert np.array_equal(m.export_triples(B.LAYOUT_WS), ref)
+        # (the lists' block prefixes as well: every output is its own input, times one)
+        assert torch.equal(B.spc_conv_forward(m, F, torch.eye(8, device="cuda")[None].contiguous(), B.DATAFLOW_WS), F[perm.long()])
+        m.destroy()

@@ -64,9 +64,9 @@ class Host:
         assert self.L.spc_pack_coords(coords, ctypes.c_int64(n), ctypes.byref(self.desc), keys, None, ws, *args) == 0
         return self.log()
 
-    def build(self, n, stream, layer_stride=1, layout=B.LAYOUT_OS):
+    def build(self, n, stream, layer_stride=1, layout=B.LAYOUT_OS, K=3):
         m = ctypes.c_void_p()
-        l = B.LayerDesc(3, 1, layer_stride, 0, layout)
+        l = B.LayerDesc(K, 1, layer_stride, 0, layout)
         assert self.L.spc_build_kmap(ctypes.c_void_p(64), ctypes.c_int64(n), ctypes.byref(self.desc), ctypes.byref(l), ctypes.byref(m), stream) == 0
         return m
 
@@ -337,4 +337,20 @@ def test_layers_of_three_slabs_of_channels_are_taken_where_four_pay(host, n, dty
     m = host.build(n, OTHER, layout=B.LAYOUT_WS if ws else B.LAYOUT_OS)
     kernel = feature_kernel(host, m, cin, cin, cout, dtype, B.DATAFLOW_WS if ws else B.DATAFLOW_OS, B.CONV_PACKED_WEIGHTS if packed else 0)
     assert (kernel == "resident") == taken
+    host.destroy(m)
+
+
+# ---- how a map's tiles and lists are made
+@pytest.mark.parametrize("K,n,layout,rows,scanned", [
+    (1, 28_672, B.LAYOUT_WS, 64, False), (1, 28_673, B.LAYOUT_WS, 64, True), (1, 149_999, B.LAYOUT_OS, 64, False), (1, 150_000, B.LAYOUT_WS, 128, True),
+    (1, 399_999, B.LAYOUT_OS, 128, False), (1, 400_000, B.LAYOUT_WS, 256, True), (3, 14_528, B.LAYOUT_WS, 64, False), (3, 14_592, B.LAYOUT_WS, 64, True),
+    (3, 184_999, B.LAYOUT_WS, 64, True), (3, 185_000, B.LAYOUT_OS, 128, False), (3, 400_000, B.LAYOUT_WS, 128, True), (3, 400_000, B.LAYOUT_OS, 256, False)])
+def test_tiles_of_a_search_and_who_adds_their_counts(host, K, n, layout, rows, scanned):
+    """A column of one offset's counts is added by eight threads of every fill workgroup: not where it is long."""
+    host.log()
+    m = host.build(n, OTHER, layout=layout, K=K)
+    names = [l[3] for l in host.log() if l[0] == "launch"]
+    tile, window = ctypes.c_int32(0), ctypes.c_int32(0)
+    assert host.L.spc_kmap_search_info(m, ctypes.byref(tile), ctypes.byref(window)) == 0
+    assert tile.value == rows and any("ws_scan_kernel" in x for x in names) == scanned
     host.destroy(m)
