@@ -158,7 +158,8 @@ __device__ inline void lane_exchange(intx4& a, intx4& b, intx4& c, intx4& d) {
   a = t;
   c = u;
 }
-// Lanes 2i and 2i+1, for one pair of registers.
+// Lanes 2i and 2i+1, for one pair of registers.  (Phase kernel, 32 channels, exchanged as two pairs of which one is thrown away / so: 32->64 120 k LiDAR 18.9 / 18.0 us,
+// random 16.6 / 15.5, 32->128 60 k 18.1 / 17.2, 10^6 random 87 / 87.)
 __device__ inline void lane_exchange(intx4& a, intx4& b) {
   intx4 t;
   asm("s_mov_b64 vcc, %12\n\ts_nop 0\n\t"

@@ -460,15 +460,19 @@ static bool resident_fills(int64_t rows, int n_slabs) {
 
 // Whether a layer is taken (or asked for: os_variant 3), from what it is and from the rows that its level presumably holds: the
 // waves that share a tile are the order of the sums, which is to stay when the host learns the count between two calls.  us, other kernel /
-// this, at the lines (tiles of all slabs; LiDAR, random, indoor scenes):
-//   lists, 16 bits        32->32  60 k 12.3 / 10.7, 70 k 10.7 / 10.9, 60 k 9.7 / 9.8; 64->96 40 k 38.9 / 24.5, 28.0 / 20.7
-//     64 channels at a time would do (64->64, 64->128)  45 k 20.6 / 17.9, 70 k 19.5 / 19.4, 60 k 17.0 / 18.6; 40 k 27.6 / 25.2, 20.2 / 19.9
-//   matrix, 16 bits       32->32  75 k 10.5 / 10.2, 110 k 11.4 / 10.6, 120 k 13.1 / 11.9; 48->96 30 k 17.7 / 15.7, 14.1 / 13.5
-//     where one round of the phase kernel does  32->64 120 k 17.6 / 17.6, 16->128 40 k 10.4 / 11.2; beyond 70 k 22.8 / 16.3, 20.8 / 13.5, 20.7 / 12.4
-//     (and never 64->64 or 64->128 there: 120 k 24.8 / 27.3)
-//     never prepacked      24->40  45 k 14.3 / 12.8, 70 k 16.7 / 13.8, 60 k 14.2 / 11.4; 30 k 11.5 / 12.3, 9.2 / 11.6
-//   fp32                  32->64  30 k 34.7 / 30.5, 25.5 / 23.1; 16->64 70 k 33.0 / 31.0, 27.7 / 26.4
-//     32 columns at a time  32->32 160 k 52.6 / 54.3, 200 k 61.9 / 60.8, 150 k 44.4 / 43.1; lists 75 k 38.9 / 38.8, 110 k 42.6 / 39.1
+// this, next to the lines (tiles of all slabs; L, R, I: LiDAR, random, indoor scenes; prepacked where nothing else is said and the layer takes that):
+//   lists, 16 bits, from 2500 tiles  32->32 L 60 k 12.3 / 10.7, 90 k 15.2 / 12.9, R 130 k 17.0 / 13.9, I 100 k 14.3 / 12.5; 8->32 L 90 k 11.3 / 11.7, R 130 k 14.0 / 12.3, I 100 k
+//       12.0 / 11.2; 32->64 L 90 k 20.6 / 16.6, R 130 k 22.6 / 16.6, I 100 k 19.3 / 15.9; plain 24->40 L 90 k 24.9 / 18.7, R 130 k 30.3 / 18.7, I 100 k 25.3 / 18.0
+//     64 channels, even slabs of columns, from 4200  64->64 L 90 k 29.9 / 25.9, R 70 k 18.8 / 19.0, I 100 k 25.8 / 25.5; 64->128 40 k L 26.0 / 24.5, R 20.1 / 20.0, I 18.1 / 18.7
+//   matrix, 16 bits, from 3000  32->32 L 130 k 14.9 / 13.5, R 12.9 / 11.9, I 100 k 11.2 / 10.4; 64->32 L 130 k 21.8 / 20.2, R 17.7 / 17.0, I 100 k 15.6 / 14.7; 48->96 40 k L 21.3 / 18.5,
+//       R 16.6 / 16.1, I 14.8 / 14.0
+//     whole slabs of 64 columns, from 4097, where one round of the phase kernel would not do  32->64 L 200 k 29.7 / 24.6, R 300 k 35.0 / 24.6, I 160 k 22.1 / 18.8; 16->128 L 90 k
+//       24.4 / 18.9, R 70 k 19.5 / 13.8, I 100 k 21.3 / 17.4 (below: L 120 k 32->64 17.6 / 17.6, 40 k 16->128 10.4 / 11.2; never 64->64 or 64->128: L 120 k 24.8 / 27.3)
+//     ragged columns, never prepacked, from 1600  24->40 L 60 k 17.3 / 14.4, R 70 k 16.1 / 13.5, I 60 k 14.1 / 12.8 (below: L 30 k 11.5 / 12.3, R 9.2 / 11.6); 8->40 52 k L 11.1 / 9.4,
+//       R 10.2 / 8.9, I 9.9 / 8.9; 64->72 25 k L 28.0 / 17.7, I 15.2 / 12.9; 8->16 52 k L 7.6 / 7.8, R 6.9 / 7.2, I 9.5 / 7.0
+//   fp32, from 2000  32->64 40 k L 38.4 / 34.2, R 30.2 / 26.9, I 26.2 / 24.4; 16->64 L 90 k 37.7 / 35.4, R 70 k 27.5 / 26.7, I 100 k 39.0 / 35.5; 32->128 L 25 k 48.4 / 41.7, I 27.3 / 25.8
+//     odd slabs of columns, from 6000  32->32 L 200 k 61.7 / 61.2, R 300 k 79.7 / 72.6, I 300 k 76.5 / 69.4; 32->96 L 90 k 83.0 / 80.8, R 70 k 59.4 / 61.8, I 100 k 89.3 / 83.6
+//       lists, from 3000  32->32 L 130 k 57.5 / 53.6, R 49.9 / 46.2, I 100 k 44.1 / 39.6
 // Three slabs of input channels (16 bits 33 to 48, fp32 17 to 24) are gathered, read and multiplied as four, where the split-k kernel takes three.  So not in
 //   fp32                  20->128 LiDAR 80 k 75.3 / 93.2, random 66.4 / 76.8, indoor 68.3 / 81.7; 24->64 49.6 / 52.1, 43.7 / 43.3, 44.6 / 45.8
 //   lists, prepacked      64 columns at a time  48->64 LiDAR 90 k 25.2 / 25.4, random 70 k 16.9 / 18.9, indoor 100 k 22.9 / 25.3, half as many rows of a level of stride 2 12.4 / 16.4
